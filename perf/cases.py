@@ -109,14 +109,14 @@ def draw(rng: random.Random):
         mean = float((lo + hi) // 3) if rng.random() < 0.4 else 0.0
         pre = (0, 0)
         if rng.random() < 0.5:
-            pre_hi = _log(rng, 16, max(32, min(16384, 200000 // B)))
+            pre_hi = _log(rng, 16, max(32, min(16384, 800000 // (B * heads[1]))))
             pre = (rng.choice((0, pre_hi // 2, pre_hi)), pre_hi)
         # the rows times what they see, kept to an eighth of the largest listed case's products
         while 4.0 * heads[0] * 128 * B * hi * (pre[1] + hi / 2) > 1.1e12:
             B, hi = max(1, B // 2), max(16, hi * 3 // 4)
             lo = min(lo, hi)
         mean = min(mean, float(hi))
-        small = B * hi * heads[0] < 200000
+        small = B * hi * heads[0] < 200000 and B * (hi + pre[1]) * heads[1] < 200000
         c = _prefill("", heads, B, lo, hi, 8 if small else 2, mean=mean, pre_lo=pre[0], pre_hi=pre[1],
                      fused_rows=rng.random() < 0.4, lse=rng.random() < 0.3, len_seed=ls)
     else:
