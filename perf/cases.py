@@ -204,16 +204,19 @@ def prepare(case, seed):
         ctx.set_option(binding.OPT_DECODE_ADAPTIVE, 1)
     T = int(new.sum())
     n = num_blocks * Hkv * BS * D
-    s = {"case": c, "ctx": ctx, "B": B, "T": T, "layers": layers, "bt": _i32(table), "before": _i32(before),
+    s = {"case": c, "ctx": ctx, "bt": _i32(table), "before": _i32(before),
          "cu": _i32(wl.cu_from_lengths(new)), "total": _i32(before + new), "max_new": int(new.max()), "max_total": int((before + new).max()),
          "k": _randn((layers, n), c["dtype"], gen), "v": _randn((layers, n), c["dtype"], gen),
          "out": torch.zeros((layers, T, Hq, D), dtype=ctx.torch_dtype, device="cuda"),
          "lse": torch.zeros((layers, T, Hq), dtype=torch.float32, device="cuda") if c.get("lse") else None}
     if c.get("fused_rows"):
         rows = _randn((layers, T, Hq + 2 * Hkv, D), c["dtype"], gen)
-        s["q"], s["kn"], s["vn"] = rows[:, :, :Hq], rows[:, :, Hq:Hq + Hkv], rows[:, :, Hq + Hkv:]
+        q, kn, vn = rows[:, :, :Hq], rows[:, :, Hq:Hq + Hkv], rows[:, :, Hq + Hkv:]
     else:
-        s["q"], s["kn"], s["vn"] = (_randn((layers, T, h, D), c["dtype"], gen) for h in (Hq, Hkv, Hkv))
+        q, kn, vn = (_randn((layers, T, h, D), c["dtype"], gen) for h in (Hq, Hkv, Hkv))
+    # each layer's tensors, as a model's layers hold them
+    s["layers"] = list(zip(*((t.unbind(0) if t is not None else (None,) * layers)
+                             for t in (q, kn, vn, s["k"], s["v"], s["out"], s["lse"]))))
     if c["kind"] == "cycle":
         s["steps"] = [{"q": _randn((B, Hq, D), c["dtype"], gen), "kn": _randn((B, Hkv, D), c["dtype"], gen),
                        "vn": _randn((B, Hkv, D), c["dtype"], gen), "total": _i32(new + i + 1), "max_total": int(new.max()) + i + 1,
@@ -233,9 +236,7 @@ def prepare(case, seed):
 
 def _decode_step(s):
     ctx, entry = s["ctx"], s["case"]["entry"]
-    for l in range(s["layers"]):
-        k, v, q, kn, vn, out = s["k"][l], s["v"][l], s["q"][l], s["kn"][l], s["vn"][l], s["out"][l]
-        lse = s["lse"][l] if s["lse"] is not None else None
+    for q, kn, vn, k, v, out, lse in s["layers"]:
         if entry == "append":
             ctx.attn_decode_append(q, kn, vn, k, v, s["bt"], s["total"], out, s["max_total"], lse)
             continue
@@ -252,11 +253,9 @@ def _prefill_step(s):
     ctx, fused = s["ctx"], s["case"].get("fused_rows")
     append, attend = (ctx.kv_append_strided, ctx.attn_prefill_strided) if fused else (ctx.kv_append, ctx.attn_prefill)
     ctx.set_option(binding.OPT_PREFILL_REUSE_PLAN, 1)  # the layers of this step share their list of query tiles
-    for l in range(s["layers"]):
-        k, v = s["k"][l], s["v"][l]
-        append(k, v, s["kn"][l], s["vn"][l], s["cu"], s["before"], s["bt"], max_new_len=s["max_new"])
-        attend(s["q"][l], k, v, s["cu"], s["before"], s["bt"], s["out"][l], s["lse"][l] if s["lse"] is not None else None,
-               max_q_len=s["max_new"])
+    for q, kn, vn, k, v, out, lse in s["layers"]:
+        append(k, v, kn, vn, s["cu"], s["before"], s["bt"], max_new_len=s["max_new"])
+        attend(q, k, v, s["cu"], s["before"], s["bt"], out, lse, max_q_len=s["max_new"])
 
 
 def run(state):
@@ -272,7 +271,7 @@ def run(state):
     if kind == "cycle":
         ctx = state["ctx"]
         for t in state["steps"]:
-            ctx.attn_decode_append(t["q"], t["kn"], t["vn"], state["k"][0], state["v"][0], state["bt"], t["total"], t["out"],
-                                   t["max_total"])
+            _, _, _, k, v, _, _ = state["layers"][0]
+            ctx.attn_decode_append(t["q"], t["kn"], t["vn"], k, v, state["bt"], t["total"], t["out"], t["max_total"])
         got["steps"] = [t["out"] for t in state["steps"]]
     return got
