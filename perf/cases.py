@@ -275,3 +275,69 @@ def run(state):
             ctx.attn_decode_append(t["q"], t["kn"], t["vn"], k, v, state["bt"], t["total"], t["out"], t["max_total"])
         got["steps"] = [t["out"] for t in state["steps"]]
     return got
+
+
+# ---- the same in 64 bits ------------------------------------------------------------------------
+
+
+def _cached(pool, c, blocks, n, is_k):
+    """The first n cached tokens of a sequence as fp64 [Hkv, n, D], taken out of a pool's blocks."""
+    Hkv, D, x = c["Hkv"], c["D"], 8 if c["dtype"] == "bf16" else 4
+    if is_k:
+        t = pool.view(-1, Hkv, D // x, BS, x)[blocks].permute(1, 0, 3, 2, 4)
+    else:
+        t = pool.view(-1, Hkv, D, BS)[blocks].permute(1, 0, 3, 2)
+    return t.reshape(Hkv, -1, D)[:, :n].double()
+
+
+def _attend(c, q, k, v):
+    """fp64 (out, log-sum-exp) of the last len(q) positions of k/v [Hkv, n, D], each seeing itself and what precedes it."""
+    S, (Hkv, n, D) = q.shape[0], k.shape
+    G = c["Hq"] // Hkv
+    kt = k.transpose(1, 2).contiguous()
+    out = torch.empty((S, c["Hq"], D), dtype=torch.float64, device="cuda")
+    lse = torch.empty((S, c["Hq"]), dtype=torch.float64, device="cuda")
+    step = max(1, min(S, int(1.2e8 / (c["Hq"] * n))))
+    for r in range(0, S, step):
+        e = min(S, r + step)
+        seen = n - S + e  # keys that the last row of this piece sees
+        qs = q[r:e].double().view(e - r, Hkv, G, D).permute(1, 2, 0, 3).reshape(Hkv, G * (e - r), D)
+        s = torch.bmm(qs, kt[:, :, :seen].contiguous()).view(Hkv, G, e - r, seen) / math.sqrt(D)
+        if S > 1:
+            pos = torch.arange(n - S + r, seen, device="cuda")
+            s.masked_fill_(torch.arange(seen, device="cuda") > pos[:, None], -math.inf)
+        z = torch.logsumexp(s, -1)
+        p = s.sub_(z[..., None]).exp_().view(Hkv, G * (e - r), seen)
+        o = torch.bmm(p, v[:, :seen].contiguous()).view(Hkv, G, e - r, D)
+        out[r:e] = o.permute(2, 0, 1, 3).reshape(e - r, c["Hq"], D)
+        lse[r:e] = z.permute(2, 0, 1).reshape(e - r, c["Hq"])
+    return out, lse
+
+
+def exact(case, seed):
+    c = dict(case)
+    s = prepare(case, seed)
+    before, new = _lengths(c)
+    cu, bt = np.concatenate(([0], np.cumsum(new))), s["bt"].long()
+    outs, lses, steps = [], [], [torch.empty(t["out"].shape, dtype=torch.float64, device="cuda") for t in s.get("steps", ())]
+    for q, kn, vn, kp, vp, _, _ in s["layers"]:
+        rows = []
+        for b in range(c["B"]):
+            a, e, n = int(cu[b]), int(cu[b + 1]), int(before[b])
+            k, v = (x[a:e].double().transpose(0, 1) for x in (kn, vn))
+            if n:
+                blocks = bt[b, :(n + BS - 1) // BS]
+                k = torch.cat((_cached(kp, c, blocks, n, True), k), 1)
+                v = torch.cat((_cached(vp, c, blocks, n, False), v), 1)
+            rows.append(_attend(c, q[a:e], k, v))
+            for i, t in enumerate(s.get("steps", ())):
+                k = torch.cat((k, t["kn"][b:b + 1].double().transpose(0, 1)), 1)
+                v = torch.cat((v, t["vn"][b:b + 1].double().transpose(0, 1)), 1)
+                steps[i][b:b + 1] = _attend(c, t["q"][b:b + 1], k, v)[0]
+        outs.append(torch.cat([o for o, _ in rows]))
+        lses.append(torch.cat([z for _, z in rows]))
+    # the pools hold copies of the inputs: no computed numbers
+    got = {"out": torch.stack(outs), "lse": torch.stack(lses) if c.get("lse") else None, "k": None, "v": None}
+    if c["kind"] == "cycle":
+        got["steps"] = steps
+    return got
