@@ -79,9 +79,9 @@ enum { ECOSERVE_BF16 = 0, ECOSERVE_F32 = 1 };
 
 /* Head layout and paging of one layer's cache.
  * Supported: block_size == 16; num_q_heads % num_kv_heads == 0 with
- * G = Hq/Hkv <= 16; dtype BF16 with head_dim 128 (matrix-core kernels) or any
- * head_dim that is a multiple of 8 up to 256 (plain kernels); dtype F32 with
- * head_dim a multiple of 4 up to 256 (plain kernels). */
+ * G = Hq/Hkv <= 16; dtype BF16 with head_dim 128 (the tuned kernels) or any
+ * head_dim that is a multiple of 8 up to 256; dtype F32 with head_dim a
+ * multiple of 4 up to 256 (matrix-core kernels of their own, weights in fp32). */
 typedef struct {
   int32_t num_q_heads;
   int32_t num_kv_heads;

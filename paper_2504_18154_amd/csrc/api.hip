@@ -402,8 +402,11 @@ int ecoserve_attn_prefill_strided(ecoserve_ctx* c, const void* q, int64_t q_row_
     key.B = B;
     key.T = T;
     key.n_wg = grid;
-  } else
+  } else if (c->opt_force_plain) {
     e = launch_prefill_plain(a, cu_q, ctx_before, T, s);
+  } else {
+    e = launch_prefill_any(a, cu_q, ctx_before, T, s);
+  }
   return e == hipSuccess ? ECOSERVE_OK : ECOSERVE_EHIP;
 }
 
@@ -458,17 +461,19 @@ static int decode_impl(ecoserve_ctx* c, const void* q, int64_t q_row_stride, con
   hipStream_t s = (hipStream_t)stream;
   AttnArgs a = make_args(c, q, q_row_stride, k_cache, v_cache, block_table, bt_stride, out, lse, B);
   hipError_t e;
-  if (k_new && !use_mfma(c)) {
+  if (k_new && c->opt_force_plain) {
     // the plain kernels do not fuse: the one-token append runs as its own kernel first (position = ctx_len - 1)
     ProfileScope prof(c, ECOSERVE_KERNEL_APPEND, s);
     e = launch_kv_append(c, k_cache, v_cache, k_new, v_new, (int32_t)new_row_stride, nullptr, ctx_len, block_table,
                          bt_stride, B, B, 1, -1, s);
     if (e != hipSuccess) return ECOSERVE_EHIP;
   }
-  if (use_mfma(c)) {
+  if (!c->opt_force_plain) {
     a.k_new = k_new;
     a.v_new = v_new;
     a.new_row_stride = (int32_t)new_row_stride;
+  }
+  if (use_mfma(c)) {
     const int n_wgs = c->num_cu * kDecodeWgsPerCu;
     const bool adaptive = c->opt_adaptive && c->opt_split_tokens == 0 && n_wgs % 8 == 0;
     const float* const share_in = adaptive ? c->ws_share + 8 * c->share_parity : nullptr;
@@ -488,12 +493,15 @@ static int decode_impl(ecoserve_ctx* c, const void* q, int64_t q_row_stride, con
                                  n_wgs * 4, s);
     return e == hipSuccess ? ECOSERVE_OK : ECOSERVE_EHIP;
   }
-  const int32_t split_tokens = plan_split_tokens(c, B, max_ctx_len);
+  const int32_t split_tokens = c->opt_force_plain || c->opt_split_tokens > 0
+                                   ? plan_split_tokens(c, B, max_ctx_len)
+                                   : decode_any_split_tokens(B, a.Hkv, max_ctx_len, c->num_cu);
   const int32_t n_split_max = ceil_div(max_ctx_len, split_tokens);
   if (n_split_max > c->ws_splits) return ECOSERVE_EINVAL;  // cannot happen for split_tokens >= kMinSplitTokens
   {
     ProfileScope prof(c, ECOSERVE_KERNEL_DECODE, s);
-    e = launch_decode_plain(a, ctx_len, split_tokens, n_split_max, c->ws_acc, c->ws_ml, c->ws_splits, s);
+    e = c->opt_force_plain ? launch_decode_plain(a, ctx_len, split_tokens, n_split_max, c->ws_acc, c->ws_ml, c->ws_splits, s)
+                           : launch_decode_any(a, ctx_len, split_tokens, n_split_max, c->ws_acc, c->ws_ml, c->ws_splits, s);
   }
   if (e != hipSuccess) return ECOSERVE_EHIP;
   if (n_split_max > 1) {

@@ -1,0 +1,562 @@
+// Paged attention on gfx950 matrix cores for every layout except bf16 with head size 128: bf16 of any head size
+// that is a multiple of 8 and fp32 of any that is a multiple of 4, up to 256.
+//
+// Eq. 2 of Section 2.1 over the paged cache, as the kernels for (bf16, 128) evaluate it, with the arithmetic of
+// the plain kernels: scores, weights and sums are fp32.
+//   scores  S^T[key][row] = K . Q^T      fp32: v_mfma_f32_16x16x4_f32;  bf16: v_mfma_f32_16x16x32_bf16
+//   values  O^T[d][row]  += V^T . P^T    fp32: v_mfma_f32_16x16x4_f32;  bf16: v_mfma_f32_16x16x16_bf16, twice: the
+//           weight as a bf16 number and the bf16 number nearest to what that left over (together 2^-18 of the
+//           weight, where the result's own rounding to bf16 is 2^-9)
+// A cache block is in operand layout already (see attn_decode_mfma.hip): lane (col, quad) reads the 16-byte units
+// (4 j + quad, token col) of K, whose elements are the K dimension of a step (the order inside a step does not
+// matter as long as Q has the same), and row 16 dt + col, tokens 4 quad .. + 3 of V.  No LDS staging, no
+// transposition; the scores' accumulator layout is the weights' operand layout.  Head sizes that do not fill the
+// last step read zeros there: the loads go through a descriptor that ends with the block.
+//
+// Rows that share a K/V head share its loads: the 16 columns of a product are the query heads of the group
+// (decode), or (position, query head of the group) pairs of a prompt (prefill), position-major.
+//
+// What bounds them: such models are small (tens of MB of K/V at most), so a step is latency: launches, the chain
+// length -> block ids -> blocks, and the walk of the blocks.  Hence decode takes contexts up to 1024 tokens in one
+// launch, eight wavefronts per (sequence, K/V head) and the step's append inside (one launch instead of three).
+// Measured beside the plain kernels (one wavefront per query row, a scalar product per lane): a prompt batch of 4 x
+// 50..600 tokens and 8 decode steps, bf16, head size 64, 32/8 heads: 399 -> 108 us (prefill kernel 243 -> 13.5 us, a
+// decode step's kernels 21.9 -> 5.6 us); 4 x 37..700 tokens in fp32, 4/2 heads: 196 -> 108 us (55 -> 30 us, 19.1 -> 7.5
+// us); both are now bound by the host's calls.
+#include <type_traits>
+
+#include "common.h"
+
+namespace eco {
+
+constexpr int kRsrc32 = 0x00020000;  // buffer descriptor: untyped 32-bit data, no swizzle, no stride
+constexpr float kRaise = 8.f;        // the exponent offset is raised when a score exceeds it by more (log2 units)
+
+// Operands of one cache block for head sizes up to 32 KS, and the two products.
+template <typename E, int KS>
+struct Block {
+  static constexpr bool kF32 = std::is_same<E, float>::value;
+  static constexpr int X = Elem<E>::X;
+  static constexpr int NK = kF32 ? 2 * KS : KS;  // 16-byte loads of K (and of a query row) per lane
+  static constexpr int NV = 2 * KS;              // 16-row tiles of V^T
+  typedef typename std::conditional<kF32, f32x4, s16x4>::type VFrag;
+  u32x4 k[NK];
+  VFrag v[NV];
+
+  // `bytes`: size of one (block, head) piece of the pool, 0 for a load of nothing (zeros, no memory access)
+  __device__ __forceinline__ void load(const char* kbase, const char* vbase, int bytes, int lane, int col, int quad) {
+    const __amdgpu_buffer_rsrc_t rk = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(kbase), 0, bytes, kRsrc32);
+    const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(vbase), 0, bytes, kRsrc32);
+#pragma unroll
+    for (int j = 0; j < NK; ++j)
+      k[j] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rk, lane * 16 + j * 1024, 0, 0));
+#pragma unroll
+    for (int dt = 0; dt < NV; ++dt) {
+      if constexpr (kF32)
+        v[dt] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rv, col * 64 + quad * 16 + dt * 1024, 0, 0));
+      else
+        v[dt] = __builtin_bit_cast(s16x4, __builtin_amdgcn_raw_buffer_load_b64(rv, col * 32 + quad * 8 + dt * 512, 0, 0));
+    }
+  }
+  // slots >= n hold no token: their V entries (stale bits, possibly NaN) must not meet their zero weights
+  __device__ __forceinline__ void clear_tail(int n, int quad) {
+#pragma unroll
+    for (int dt = 0; dt < NV; ++dt)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (4 * quad + e >= n) v[dt][e] = 0;
+  }
+  // the token in `slot` comes from a K row and a V row (D elements each) instead of the cache
+  __device__ __forceinline__ void put_token(const E* krow, const E* vrow, int slot, int D, int col, int quad) {
+    if (col == slot) {
+#pragma unroll
+      for (int j = 0; j < NK; ++j) {
+        const int d = (4 * j + quad) * X;
+        if (d < D) k[j] = *reinterpret_cast<const u32x4*>(krow + d);
+      }
+    }
+    if (quad == (slot >> 2)) {
+#pragma unroll
+      for (int dt = 0; dt < NV; ++dt) {
+        const int d = dt * 16 + col;
+        if (d < D) {
+          const E x = vrow[d];
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (e == (slot & 3)) {
+              if constexpr (kF32) v[dt][e] = x;
+              else v[dt][e] = (short)x;
+            }
+        }
+      }
+    }
+  }
+  // S^T[key 4 quad + i][row col]
+  __device__ __forceinline__ f32x4 scores(const u32x4 (&q)[NK]) const {
+    f32x4 s = {0.f, 0.f, 0.f, 0.f};
+    if constexpr (kF32) {
+      f32x4 t = {0.f, 0.f, 0.f, 0.f};  // (two chains: a dependent matrix instruction cannot issue back to back)
+#pragma unroll
+      for (int j = 0; j < NK; ++j) {
+        const f32x4 a = __builtin_bit_cast(f32x4, k[j]), b = __builtin_bit_cast(f32x4, q[j]);
+        s = __builtin_amdgcn_mfma_f32_16x16x4f32(a[0], b[0], s, 0, 0, 0);
+        t = __builtin_amdgcn_mfma_f32_16x16x4f32(a[1], b[1], t, 0, 0, 0);
+        s = __builtin_amdgcn_mfma_f32_16x16x4f32(a[2], b[2], s, 0, 0, 0);
+        t = __builtin_amdgcn_mfma_f32_16x16x4f32(a[3], b[3], t, 0, 0, 0);
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) s[i] += t[i];
+    } else {
+#pragma unroll
+      for (int j = 0; j < NK; ++j)
+        s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, k[j]), __builtin_bit_cast(bf16x8, q[j]), s, 0, 0, 0);
+    }
+    return s;
+  }
+  // O^T[d][row] += V^T P^T for the weights p of keys 4 quad .. + 3
+  __device__ __forceinline__ void values(const f32x4& p, f32x4 (&acc)[NV]) const {
+    if constexpr (kF32) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int dt = 0; dt < NV; ++dt) acc[dt] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[dt][e], p[e], acc[dt], 0, 0, 0);
+    } else {
+      const bf16x4 hi = __builtin_convertvector(p, bf16x4);
+      const bf16x4 lo = __builtin_convertvector(p - __builtin_convertvector(hi, f32x4), bf16x4);
+      const s16x4 h = __builtin_bit_cast(s16x4, hi), r = __builtin_bit_cast(s16x4, lo);
+#pragma unroll
+      for (int dt = 0; dt < NV; ++dt) acc[dt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(v[dt], h, acc[dt], 0, 0, 0);
+#pragma unroll
+      for (int dt = 0; dt < NV; ++dt) acc[dt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(v[dt], r, acc[dt], 0, 0, 0);
+    }
+  }
+};
+
+// Online softmax of one row (a column of the products; its keys are spread over the four 16-lane groups).
+// `m`: exponent offset, -inf until the row has seen a key; `l`: this lane's share of the sum of weights.  The
+// offset is raised only when a score exceeds it by more than 2^kRaise, so the rescaling leaves the loop; weights
+// are fp32, which holds 2^8 as exactly as 1.
+template <int NV>
+__device__ __forceinline__ f32x4 softmax_step(const f32x4& s, float& m, float& l, f32x4 (&acc)[NV]) {
+  float bm = fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]));
+  if (__any(bm > m + kRaise)) {
+    bm = fmaxf(bm, __shfl_xor(bm, 16));
+    bm = fmaxf(bm, __shfl_xor(bm, 32));
+    const float m_new = bm > m + kRaise ? bm : m;
+    const float alpha = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - m_new);
+    l *= alpha;
+#pragma unroll
+    for (int dt = 0; dt < NV; ++dt) acc[dt] *= alpha;
+    m = m_new;
+  }
+  const float mu = m == -INFINITY ? 0.f : m;  // (a row all of whose keys so far are masked)
+  f32x4 p;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) p[i] = __builtin_amdgcn_exp2f(s[i] - mu);
+  l += (p[0] + p[1]) + (p[2] + p[3]);
+  return p;
+}
+
+// One row over keys [t0, t1), one wavefront, key after key: what a row falls back to when its result is not a
+// number although its weights are.  A V element that is infinite or not a number then meets the zero weight of a
+// masked key, or the zero remainder of a bf16 weight, in the products above; here it meets only the rows that see
+// it.  Lane owns elements lane + 64 r.
+template <typename E>
+__device__ __forceinline__ void attend_row(const E* __restrict__ qrow, const E* __restrict__ k_cache, const E* __restrict__ v_cache,
+                                        const int32_t* __restrict__ bt_row, int g, int Hkv, int D, int t0, int t1, float scale_log2e,
+                                        float& m, float& l, float (&o)[4]) {
+  constexpr int X = Elem<E>::X;
+  const int lane = threadIdx.x & 63;
+  m = -INFINITY;
+  l = 0.f;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) o[r] = 0.f;
+  for (int t = t0; t < t1; ++t) {
+    const int64_t blk = bt_row[t >> 4];
+    float s = 0.f;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int d = lane + 64 * r;
+      if (d < D) s += Elem<E>::load(qrow + d) * Elem<E>::load(k_cache + k_index<X>(blk, g, t & 15, d, Hkv, D));
+    }
+    s = wave_sum(s) * scale_log2e;
+    const float m_new = fmaxf(m, s), mu = m_new == -INFINITY ? 0.f : m_new;
+    const float alpha = m == -INFINITY ? 0.f : exp2f(m - mu), p = exp2f(s - mu);
+    l = l * alpha + p;
+    m = m_new;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int d = lane + 64 * r;
+      if (d < D) o[r] = o[r] * alpha + p * Elem<E>::load(v_cache + v_index(blk, g, t & 15, d, Hkv, D));
+    }
+  }
+}
+
+// Decode: grid (splits, Hkv, B), W wavefronts; the blocks of a slice of `split_tokens` tokens of one (sequence, K/V
+// head) go to the wavefronts in turn, whose states are combined through LDS.  With one slice the result is final,
+// otherwise it is a partial state for decode_merge_kernel.  With k_new given the workgroup of the last slice takes
+// the newest token (position ctx_len - 1) from the new rows and stores it into the cache.
+template <typename E, int KS, int W>
+__global__ __launch_bounds__(W * 64) void decode_any_kernel(
+    const E* __restrict__ q, int q_row_stride, const E* __restrict__ k_new, const E* __restrict__ v_new, int new_row_stride,
+    E* k_cache, E* v_cache, const int32_t* __restrict__ block_table, int bt_stride, const int32_t* __restrict__ ctx_len,
+    E* __restrict__ out, float* __restrict__ lse, float* __restrict__ ws_acc, float* __restrict__ ws_ml, int ws_splits,
+    int split_tokens, int Hq, int Hkv, int G, int D, float scale_log2e) {
+  typedef Block<E, KS> Blk;
+  constexpr int X = Elem<E>::X, NK = Blk::NK, NV = Blk::NV;
+  constexpr int kTiles = NV < 4 ? NV : 4, kSlice = kTiles * 16;  // elements of a head vector combined at a time
+  __shared__ __attribute__((aligned(16))) E s_new[2][256];
+  __shared__ float s_m[W][16], s_l[W][16], s_tot[2][16];
+  __shared__ __attribute__((aligned(16))) float s_acc[W][16][kSlice + 4];
+  __shared__ int s_bad;
+  const int sp = blockIdx.x, g = blockIdx.y, b = blockIdx.z;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int col = lane & 15, quad = lane >> 4;
+  // asked for before anything that depends on the length
+  const bool fused = k_new != nullptr;
+  E kn = 0, vn = 0;
+  if (fused && tid < D) {
+    kn = k_new[(size_t)b * new_row_stride + (size_t)g * D + tid];
+    vn = v_new[(size_t)b * new_row_stride + (size_t)g * D + tid];
+  }
+  u32x4 qf[NK];
+#pragma unroll
+  for (int j = 0; j < NK; ++j) {
+    const int d = (4 * j + quad) * X;
+    const u32x4 z = {0u, 0u, 0u, 0u};
+    qf[j] = col < G && d < D ? *reinterpret_cast<const u32x4*>(q + (size_t)b * q_row_stride + (size_t)(g * G + col) * D + d) : z;
+  }
+  const int L = ctx_len[b];
+  const int n_split = (L + split_tokens - 1) / split_tokens;
+  if (sp >= n_split) return;
+  const int t0 = sp * split_tokens, t1 = min(L, t0 + split_tokens);
+  const int blk0 = t0 >> 4, n_blk = ((t1 + 15) >> 4) - blk0;
+  const int n = wave < n_blk ? (n_blk - wave + W - 1) / W : 0;  // this wavefront's blocks: blk0 + wave + W i
+  const int32_t* const bt_row = block_table + (size_t)b * bt_stride;
+  const size_t piece = (size_t)16 * D * sizeof(E);
+  const bool newest = fused && sp == n_split - 1;
+  if (newest && tid < D) {
+    s_new[0][tid] = kn;
+    s_new[1][tid] = vn;
+  }
+  if (tid == 0) s_bad = 0;
+  const char* const kc = reinterpret_cast<const char*>(k_cache);
+  const char* const vc = reinterpret_cast<const char*>(v_cache);
+
+  f32x4 acc[NV];
+#pragma unroll
+  for (int dt = 0; dt < NV; ++dt) acc[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float m = -INFINITY, l = 0.f;
+  __syncthreads();
+  for (int base = 0; base < n; base += 64) {  // windows of the 64 block ids one register holds
+    const int nw = min(64, n - base);
+    const int ids = lane < nw ? bt_row[blk0 + wave + W * (base + lane)] : 0;
+    Blk f[2];
+    auto fetch = [&](Blk& fr, int i) {
+      const size_t off = ((size_t)__builtin_amdgcn_readlane(ids, min(i, nw - 1)) * Hkv + g) * piece;
+      fr.load(kc + off, vc + off, i < nw ? (int)piece : 0, lane, col, quad);
+    };
+    auto work = [&](Blk& fr, int i) {
+      const int first = (blk0 + wave + W * (base + i)) << 4;
+      const int tail = t1 - first;
+      if (tail <= 16) {
+        asm volatile("" ::: "memory");  // (a real branch: the last block only)
+        if (newest) fr.put_token(s_new[0], s_new[1], tail - 1, D, col, quad);
+        if (tail < 16) fr.clear_tail(tail, quad);
+      }
+      f32x4 s = fr.scores(qf) * scale_log2e;
+      if (tail < 16) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (4 * quad + e >= tail) s[e] = -INFINITY;
+      }
+      const f32x4 p = softmax_step<NV>(s, m, l, acc);
+      fr.values(p, acc);
+    };
+    fetch(f[0], 0);
+    for (int i = 0; i < nw; i += 2) {
+      fetch(f[1], i + 1);
+      work(f[0], i);
+      fetch(f[0], i + 2);
+      if (i + 1 < nw) work(f[1], i + 1);
+    }
+  }
+  l += __shfl_xor(l, 16);
+  l += __shfl_xor(l, 32);
+  if (quad == 0) {
+    s_m[wave][col] = m;
+    s_l[wave][col] = l;
+  }
+  __syncthreads();
+  if (newest && tid < D) {  // (every wavefront's loads have been consumed: nothing in this launch reads the slot any more)
+    const int64_t blk = bt_row[(L - 1) >> 4];
+    k_cache[k_index<X>(blk, g, (L - 1) & 15, tid, Hkv, D)] = kn;
+    v_cache[v_index(blk, g, (L - 1) & 15, tid, Hkv, D)] = vn;
+  }
+  float M = -INFINITY, total = 0.f;
+#pragma unroll
+  for (int w = 0; w < W; ++w) M = fmaxf(M, s_m[w][col]);
+#pragma unroll
+  for (int w = 0; w < W; ++w) total += s_m[w][col] == -INFINITY ? s_l[w][col] : s_l[w][col] * __builtin_amdgcn_exp2f(s_m[w][col] - M);
+  const float mine = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - M);
+  if (tid < 16) {
+    s_tot[0][col] = M;
+    s_tot[1][col] = total;
+  }
+  const bool final_result = n_split == 1;
+  const size_t slot0 = ((size_t)b * Hq + (size_t)g * G) * ws_splits + sp;
+#pragma unroll
+  for (int t = 0; t < NV; t += kTiles) {
+#pragma unroll
+    for (int i = 0; i < kTiles; ++i)
+      if (t + i < NV) *reinterpret_cast<f32x4*>(&s_acc[wave][col][i * 16 + 4 * quad]) = acc[t + i] * mine;
+    __syncthreads();
+    for (int idx = tid; idx < G * kSlice; idx += W * 64) {
+      const int h = idx / kSlice, dl = idx % kSlice, d = t * 16 + dl;
+      if (d >= D) continue;
+      float o = 0.f;
+#pragma unroll
+      for (int w = 0; w < W; ++w) o += s_acc[w][h][dl];
+      const float sum = s_tot[1][h];
+      if (o != o && sum == sum) s_bad = 1;  // (see attend_row)
+      if (final_result) Elem<E>::store(out + ((size_t)b * Hq + g * G + h) * D + d, o / sum);
+      else ws_acc[(slot0 + (size_t)h * ws_splits) * D + d] = o;
+    }
+    __syncthreads();
+  }
+  if (tid < G) {
+    if (final_result) {
+      if (lse) lse[(size_t)b * Hq + g * G + tid] = (s_tot[0][tid] + log2f(s_tot[1][tid])) * kLn2;
+    } else {
+      ws_ml[(slot0 + (size_t)tid * ws_splits) * 2 + 0] = s_tot[0][tid];
+      ws_ml[(slot0 + (size_t)tid * ws_splits) * 2 + 1] = s_tot[1][tid];
+    }
+  }
+  if (s_bad) {
+    __syncthreads();
+    for (int h = wave; h < G; h += W) {
+      float rm, rl, o[4];
+      attend_row<E>(q + (size_t)b * q_row_stride + (size_t)(g * G + h) * D, k_cache, v_cache, bt_row, g, Hkv, D, t0, t1, scale_log2e, rm, rl, o);
+      for (int r = 0; r < 4; ++r) {
+        const int d = lane + 64 * r;
+        if (d >= D) continue;
+        if (final_result) Elem<E>::store(out + ((size_t)b * Hq + g * G + h) * D + d, o[r] / rl);
+        else ws_acc[(slot0 + (size_t)h * ws_splits) * D + d] = o[r];
+      }
+      if (!final_result && lane == 0) {
+        ws_ml[(slot0 + (size_t)h * ws_splits) * 2 + 0] = rm;
+        ws_ml[(slot0 + (size_t)h * ws_splits) * 2 + 1] = rl;
+      }
+    }
+  }
+}
+
+// Prefill.  The rows of one (sequence, K/V head) are (position, query head of the group) pairs, position-major:
+// row r = position r / G, head r % G, so the 16 columns of a product cover few positions and the causal bound cuts
+// close.  A workgroup takes 4 x 16 NC consecutive rows, a wavefront 16 NC of them; each wavefront walks the key
+// blocks up to its own diagonal by itself (the four of a workgroup read the same blocks at about the same time:
+// the caches serve three of them).
+// Sequence b's tiles are numbered from cu_q[b] G / R + b (R rows per tile): consecutive sequences are then at least
+// ceil(S G / R) numbers apart, so no prefix sum over the batch is needed, and every workgroup finds its sequence
+// with a search over cu_q, 64 candidates at a time.  Later tiles of a sequence are longer and go first.
+template <typename E, int KS, int NC>
+__global__ __launch_bounds__(256) void prefill_any_kernel(
+    const E* __restrict__ q, int q_row_stride, const E* __restrict__ k_cache, const E* __restrict__ v_cache,
+    const int32_t* __restrict__ cu_q, const int32_t* __restrict__ ctx_before, const int32_t* __restrict__ block_table, int bt_stride,
+    E* __restrict__ out, float* __restrict__ lse, int B, int Hq, int Hkv, int G, int D, float scale_log2e) {
+  typedef Block<E, KS> Blk;
+  constexpr int X = Elem<E>::X, NK = Blk::NK, NV = Blk::NV, R = 4 * 16 * NC;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int col = lane & 15, quad = lane >> 4, g = blockIdx.y;
+  const int tile_no = (int)(gridDim.x - 1 - blockIdx.x);
+  int b = 0, cand = B;  // largest b with cu_q[b] G / R + b <= tile_no
+  while (cand > 1) {
+    const int stride = (cand + 63) >> 6, idx = b + lane * stride;
+    const bool le = idx < b + cand && (long long)cu_q[min(idx, B)] * G / R + idx <= tile_no;
+    const int last = __popcll(__ballot(le)) - 1;
+    const int nb = b + last * stride;
+    cand = min(stride, b + cand - nb);
+    b = nb;
+  }
+  const int tok0 = cu_q[b], S = cu_q[b + 1] - tok0;
+  const long long r0 = ((long long)tile_no - ((long long)tok0 * G / R + b)) * R + wave * (16 * NC);
+  const long long n_rows = (long long)S * G;
+  if (r0 >= n_rows) return;
+  const int cb = ctx_before[b];
+  const int32_t* const bt_row = block_table + (size_t)b * bt_stride;
+  const size_t piece = (size_t)16 * D * sizeof(E);
+  const int L = cb + S;
+
+  int pos[NC], head[NC];
+  bool ok[NC];
+  u32x4 qf[NC][NK];
+  f32x4 acc[NC][NV];
+  float m[NC], l[NC];
+#pragma unroll
+  for (int c = 0; c < NC; ++c) {
+    const long long r = r0 + c * 16 + col;
+    ok[c] = r < n_rows;
+    pos[c] = ok[c] ? (int)((unsigned long long)r / (unsigned)G) : 0;
+    head[c] = ok[c] ? (int)(r - (long long)pos[c] * G) : 0;
+    const E* qrow = q + (size_t)(tok0 + pos[c]) * q_row_stride + (size_t)(g * G + head[c]) * D;
+#pragma unroll
+    for (int j = 0; j < NK; ++j) {
+      const int d = (4 * j + quad) * X;
+      const u32x4 z = {0u, 0u, 0u, 0u};
+      qf[c][j] = ok[c] && d < D ? *reinterpret_cast<const u32x4*>(qrow + d) : z;
+    }
+#pragma unroll
+    for (int dt = 0; dt < NV; ++dt) acc[c][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    m[c] = -INFINITY;
+    l[c] = 0.f;
+  }
+  // keys every row of the wavefront sees, and those at least one of them sees (rows that do not exist: as row 0)
+  const long long r_last = min(n_rows, r0 + 16 * NC) - 1;
+  const int all_see = cb + (int)((unsigned long long)r0 / (unsigned)G) + 1, some_see = cb + (int)((unsigned long long)r_last / (unsigned)G) + 1;
+  const int n_blk = (some_see + 15) >> 4;
+  const char* const kc = reinterpret_cast<const char*>(k_cache);
+  const char* const vc = reinterpret_cast<const char*>(v_cache);
+
+  int ids = lane < n_blk ? bt_row[lane] : 0;
+  for (int base = 0; base < n_blk; base += 64) {
+    const int nw = min(64, n_blk - base);
+    const int my = ids;
+    if (base + 64 + lane < n_blk) ids = bt_row[base + 64 + lane];
+    Blk f[2];
+    auto fetch = [&](Blk& fr, int i) {
+      const size_t off = ((size_t)__builtin_amdgcn_readlane(my, min(i, nw - 1)) * Hkv + g) * piece;
+      fr.load(kc + off, vc + off, i < nw ? (int)piece : 0, lane, col, quad);
+    };
+    auto work = [&](Blk& fr, int i) {
+      const int first = (base + i) << 4;
+      f32x4 s[NC];
+#pragma unroll
+      for (int c = 0; c < NC; ++c) s[c] = fr.scores(qf[c]) * scale_log2e;
+      if (first + 16 > all_see) {
+        asm volatile("" ::: "memory");  // (a real branch: the blocks at the diagonal only)
+        if (first + 16 > L) fr.clear_tail(L - first, quad);
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (first + 4 * quad + e > cb + pos[c]) s[c][e] = -INFINITY;
+      }
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        const f32x4 p = softmax_step<NV>(s[c], m[c], l[c], acc[c]);
+        fr.values(p, acc[c]);
+      }
+    };
+    fetch(f[0], 0);
+    for (int i = 0; i < nw; i += 2) {
+      fetch(f[1], i + 1);
+      work(f[0], i);
+      fetch(f[0], i + 2);
+      if (i + 1 < nw) work(f[1], i + 1);
+    }
+  }
+
+#pragma unroll
+  for (int c = 0; c < NC; ++c) {
+    l[c] += __shfl_xor(l[c], 16);
+    l[c] += __shfl_xor(l[c], 32);
+    const float inv = 1.f / l[c];
+    const size_t row = (size_t)(tok0 + pos[c]) * Hq + (size_t)g * G + head[c];
+    bool bad = false;
+    if (ok[c]) {
+#pragma unroll
+      for (int dt = 0; dt < NV; ++dt) {
+        const int d = dt * 16 + 4 * quad;
+        if (d < D) {
+          const f32x4 o = acc[c][dt];
+          if constexpr (Blk::kF32) {
+            *reinterpret_cast<f32x4*>(out + row * D + d) = o * inv;
+          } else {
+            u32x2 w;
+            w[0] = pack_bf16x2(o[0] * inv, o[1] * inv);
+            w[1] = pack_bf16x2(o[2] * inv, o[3] * inv);
+            *reinterpret_cast<u32x2*>(out + row * D + d) = w;
+          }
+#pragma unroll
+          for (int e = 0; e < 4; ++e) bad = bad || o[e] != o[e];
+        }
+      }
+      if (lse && quad == 0) lse[row] = (m[c] + log2f(l[c])) * kLn2;
+    }
+    unsigned long long redo = __ballot(bad && l[c] == l[c]);
+    redo = (redo | redo >> 16 | redo >> 32 | redo >> 48) & 0xffffu;  // rows whose result is to be taken again (see attend_row)
+    while (redo) {
+      const int rc = __ffsll(redo) - 1;
+      redo &= redo - 1;
+      const int p = __shfl(pos[c], rc), h = __shfl(head[c], rc);
+      float rm, rl, o[4];
+      attend_row<E>(q + (size_t)(tok0 + p) * q_row_stride + (size_t)(g * G + h) * D, k_cache, v_cache, bt_row, g, Hkv, D, 0, cb + p + 1,
+                    scale_log2e, rm, rl, o);
+      for (int r = 0; r < 4; ++r) {
+        const int d = lane + 64 * r;
+        if (d < D) Elem<E>::store(out + ((size_t)(tok0 + p) * Hq + g * G + h) * D + d, o[r] / rl);
+      }
+    }
+  }
+}
+
+namespace {
+
+// Calls f(std::integral_constant<int, KS>) for the smallest instantiated KS with 32 KS >= D.
+template <typename F>
+void for_head_size(int D, F f) {
+  if (D <= 32) f(std::integral_constant<int, 1>());
+  else if (D <= 64) f(std::integral_constant<int, 2>());
+  else if (D <= 96) f(std::integral_constant<int, 3>());
+  else if (D <= 128) f(std::integral_constant<int, 4>());
+  else if (D <= 192) f(std::integral_constant<int, 6>());
+  else f(std::integral_constant<int, 8>());
+}
+
+template <typename E>
+void launch_prefill_typed(const AttnArgs& a, const int32_t* cu_q, const int32_t* ctx_before, int32_t T, hipStream_t s) {
+  const int G = a.Hq / a.Hkv;
+  for_head_size(a.D, [&](auto ks) {
+    constexpr int KS = decltype(ks)::value, NC = KS <= 4 ? 2 : 1;  // two sets of 16 rows while their state fits the registers
+    const int64_t tiles = (int64_t)T * G / (64 * NC) + a.B;
+    hipLaunchKernelGGL((prefill_any_kernel<E, KS, NC>), dim3((unsigned)tiles, (unsigned)a.Hkv), dim3(256), 0, s, (const E*)a.q,
+                       a.q_row_stride, (const E*)a.k_cache, (const E*)a.v_cache, cu_q, ctx_before, a.block_table, a.bt_stride,
+                       (E*)a.out, a.lse, a.B, a.Hq, a.Hkv, G, a.D, a.scale_log2e);
+  });
+}
+
+template <typename E>
+void launch_decode_typed(const AttnArgs& a, const int32_t* ctx_len, int32_t split_tokens, int32_t n_split_max, float* ws_acc,
+                         float* ws_ml, int32_t ws_splits, hipStream_t s) {
+  for_head_size(a.D, [&](auto ks) {
+    // eight wavefronts per workgroup while two blocks of K and V fit beside the rest in 256 registers
+    constexpr int KS = decltype(ks)::value, W = KS > (sizeof(E) == 4 ? 4 : 6) ? 4 : 8;
+    hipLaunchKernelGGL((decode_any_kernel<E, KS, W>), dim3((unsigned)n_split_max, (unsigned)a.Hkv, (unsigned)a.B), dim3(W * 64), 0, s,
+                       (const E*)a.q, a.q_row_stride, (const E*)a.k_new, (const E*)a.v_new, a.new_row_stride,
+                       (E*)const_cast<void*>(a.k_cache), (E*)const_cast<void*>(a.v_cache), a.block_table, a.bt_stride, ctx_len,
+                       (E*)a.out, a.lse, ws_acc, ws_ml, ws_splits, split_tokens, a.Hq, a.Hkv, a.Hq / a.Hkv, a.D, a.scale_log2e);
+  });
+}
+
+}  // namespace
+
+int32_t decode_any_split_tokens(int32_t B, int32_t Hkv, int32_t max_ctx_len, int32_t num_cu) {
+  int32_t st = 1024;
+  while (st > 256 && max_ctx_len > 1024 && (int64_t)B * Hkv * ((max_ctx_len + st - 1) / st) < num_cu) st >>= 1;
+  return st;
+}
+
+hipError_t launch_prefill_any(const AttnArgs& a, const int32_t* cu_q, const int32_t* ctx_before, int32_t T, hipStream_t s) {
+  if (a.dtype == ECOSERVE_BF16) launch_prefill_typed<uint16_t>(a, cu_q, ctx_before, T, s);
+  else launch_prefill_typed<float>(a, cu_q, ctx_before, T, s);
+  return hipGetLastError();
+}
+
+hipError_t launch_decode_any(const AttnArgs& a, const int32_t* ctx_len, int32_t split_tokens, int32_t n_split_max, float* ws_acc,
+                             float* ws_ml, int32_t ws_splits, hipStream_t s) {
+  if (a.dtype == ECOSERVE_BF16) launch_decode_typed<uint16_t>(a, ctx_len, split_tokens, n_split_max, ws_acc, ws_ml, ws_splits, s);
+  else launch_decode_typed<float>(a, ctx_len, split_tokens, n_split_max, ws_acc, ws_ml, ws_splits, s);
+  return hipGetLastError();
+}
+
+}  // namespace eco

@@ -4,9 +4,9 @@
 // They evaluate Eq. 2 of Section 2.1, softmax(Q K^T / sqrt(d_k)) V, over the paged cache
 // with fp32 arithmetic and an online (running max / running sum) softmax in the exp2
 // domain.  One wavefront handles one (query row, query head, context slice): lanes own
-// tokens for the score pass and own head-vector elements for the value pass.  These
-// kernels serve the fp32 configuration and odd head sizes; they are the correctness
-// path, not the tuned one.
+// tokens for the score pass and own head-vector elements for the value pass.  They run
+// when ECOSERVE_OPT_FORCE_PLAIN asks for them (a second opinion on the matrix-core kernels);
+// the merge kernel also serves decode on matrix cores for layouts other than (bf16, 128).
 #include "common.h"
 
 namespace eco {

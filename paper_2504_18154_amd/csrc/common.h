@@ -155,6 +155,14 @@ hipError_t launch_decode_plain(const AttnArgs& a, const int32_t* ctx_len, int32_
 hipError_t launch_decode_merge(const AttnArgs& a, const int32_t* ctx_len, int32_t split_tokens, const float* ws_acc,
                                const float* ws_ml, int32_t ws_splits, hipStream_t s);
 
+// attn_any_mfma.hip: every layout but (bf16, D = 128), on matrix cores
+// (with a.k_new given, the decode launch appends the step's tokens too; split_tokens: a multiple of 16 per slice of
+// the context, n_split_max slices, partial states as in the plain decode, merged by launch_decode_merge if > 1)
+int32_t decode_any_split_tokens(int32_t B, int32_t Hkv, int32_t max_ctx_len, int32_t num_cu);
+hipError_t launch_prefill_any(const AttnArgs& a, const int32_t* cu_q, const int32_t* ctx_before, int32_t T, hipStream_t s);
+hipError_t launch_decode_any(const AttnArgs& a, const int32_t* ctx_len, int32_t split_tokens, int32_t n_split_max,
+                             float* ws_acc, float* ws_ml, int32_t ws_splits, hipStream_t s);
+
 // attn_decode_mfma.hip: bf16, D = 128
 // (split_tokens 0 = equal share per wavefront of the persistent grid; > 0 forces the chunk size)
 // (share_in / share_out: per-XCD shares [8] read and left for the next launch; xcd_speed [8]: speeds the merge

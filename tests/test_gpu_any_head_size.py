@@ -1,0 +1,122 @@
+"""The matrix-core kernels for every layout but (bf16, head size 128) against the fp64 CPU oracle: head sizes at and
+beside the edges of a matrix step (16 elements of fp32, 32 of bf16), every group shape of the 16 columns, contexts at
+the edges of blocks, wavefront rounds and slices, with and without a cached prefix."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import oracle as orc
+from paper_2504_18154_amd import workloads as wl
+from tests.parity_util import Layer, compare, compare_lse, dev_i32, say
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [("f32", 4, 2, 1), ("f32", 20, 4, 2), ("f32", 64, 4, 2), ("f32", 100, 3, 3), ("f32", 128, 6, 3), ("f32", 160, 16, 1),
+          ("f32", 256, 5, 1), ("bf16", 8, 2, 2), ("bf16", 40, 10, 2), ("bf16", 64, 32, 8), ("bf16", 72, 7, 1), ("bf16", 80, 8, 8),
+          ("bf16", 96, 8, 2), ("bf16", 120, 16, 1), ("bf16", 136, 4, 2), ("bf16", 192, 3, 1), ("bf16", 256, 8, 1)]
+
+
+@pytest.mark.parametrize("dtype,D,Hq,Hkv", SHAPES, ids=[f"{s[0]}-d{s[1]}-{s[2]}x{s[3]}" for s in SHAPES])
+def test_prefill_and_decode_against_the_oracle(dtype, D, Hq, Hkv):
+    """One prefill batch (an empty prompt, one token, block edges, several tiles; some behind a cached prefix), then
+    two decode steps, the second with the append fused in, then forced slices of the context."""
+    from paper_2504_18154_amd import binding
+    model = wl.ModelShape(f"{dtype}-d{D}", Hq, Hkv, D, 1, dtype)
+    before = np.array([0, 0, 5, 0, 16, 300, 0, 31, 0], dtype=np.int32)
+    new = np.array([1, 0, 1, 15, 17, 40, 64, 33, 150], dtype=np.int32)
+    say(f"{dtype}, head size {D}, heads {Hq}/{Hkv}: prefill {new.tolist()} behind {before.tolist()}")
+    pb = wl.prefill_batch(model, before + new, 300 + D, grow=3)
+    B = len(new)
+    layer = Layer(model, pb.num_blocks, B, pb.block_table.shape[1])
+    zero = np.zeros(B, dtype=np.int32)
+    rows = lambda n, h, seed: wl.randn((int(n), h, D), dtype, seed)
+    layer.append(rows(before.sum(), Hkv, 1), rows(before.sum(), Hkv, 2), wl.cu_from_lengths(before), zero, pb.block_table)
+    cu = wl.cu_from_lengths(new)
+    layer.append(rows(new.sum(), Hkv, 3), rows(new.sum(), Hkv, 4), cu, before, pb.block_table)
+    q = rows(new.sum(), Hq, 5)
+    out, lse = layer.prefill_gpu(q, cu, before, pb.block_table)
+    ref, ref_lse = layer.prefill_oracle(q, cu, before, pb.block_table)
+    compare("prefill", out, ref, dtype)
+    compare_lse("prefill", lse, ref_lse, dtype)
+
+    live = np.flatnonzero(before + new > 0)          # (the empty sequence has no context to decode over)
+    table, ctx = pb.block_table[live], (before + new)[live]
+    B = len(live)
+    ones = wl.cu_from_lengths([1] * B)
+    for step in range(2):
+        q, k, v = rows(B, Hq, 10 + step), rows(B, Hkv, 20 + step), rows(B, Hkv, 30 + step)
+        if step == 0:
+            layer.append(k, v, ones, ctx, table, max_new_len=1)
+            out, lse = layer.decode_gpu(q, table, ctx + 1)
+        else:
+            orc.kv_append(layer.shape, layer.okc, layer.ovc, wl.to_bits(k), wl.to_bits(v), ones, ctx, table)
+            out = torch.full((B, Hq, D), float("nan"), dtype=q.dtype, device="cuda")
+            lse = torch.full((B, Hq), float("nan"), dtype=torch.float32, device="cuda")
+            layer.ctx.attn_decode_append(q.cuda(), k.cuda(), v.cuda(), layer.kc, layer.vc, dev_i32(table), dev_i32(ctx + 1), out,
+                                         int(ctx.max()) + 1, lse)
+        ctx = ctx + 1
+        layer.assert_cache_bit_exact()
+        ref, ref_lse = layer.decode_oracle(q, table, ctx)
+        compare(f"decode step {step}", out, ref, dtype)
+        compare_lse(f"decode step {step}", lse, ref_lse, dtype)
+    for split in (64, 192):
+        layer.ctx.set_option(binding.OPT_DECODE_SPLIT_TOKENS, split)
+        out, lse = layer.decode_gpu(q, table, ctx)
+        compare(f"decode in slices of {split}", out, ref, dtype)
+        compare_lse(f"decode in slices of {split}", lse, ref_lse, dtype)
+    layer.close()
+
+
+@pytest.mark.parametrize("dtype,D", [("f32", 64), ("bf16", 64)])
+def test_decode_over_contexts_of_several_slices(dtype, D):
+    """Contexts above 1024 tokens are cut into slices whose states are merged, the newest token in the last one:
+    lengths around the slices' edges, alone (slices of 256) and beside many sequences (slices of 1024)."""
+    model = wl.ModelShape(f"{dtype}-d{D}", 4, 2, D, 1, dtype)
+    for lens in ([2049], [1024, 1025, 1, 2047, 2048] + [40] * 130):
+        lens = np.asarray(lens, dtype=np.int32)
+        say(f"{dtype}, head size {D}: decode over up to {lens.max()} tokens, {len(lens)} sequences")
+        pb = wl.prefill_batch(model, lens, 77)
+        layer = Layer(model, pb.num_blocks, pb.B, pb.block_table.shape[1])
+        k, v = (wl.randn((pb.T, 2, D), dtype, s) for s in (1, 2))
+        layer.append(k, v, pb.cu_q, pb.ctx_before, pb.block_table)
+        q = wl.randn((pb.B, 4, D), dtype, 3)
+        ref, ref_lse = layer.decode_oracle(q, pb.block_table, lens)
+        out, lse = layer.decode_gpu(q, pb.block_table, lens)
+        compare("decode", out, ref, dtype)
+        compare_lse("decode", lse, ref_lse, dtype)
+        last = torch.as_tensor(pb.cu_q[1:] - 1, dtype=torch.long)
+        fused = torch.full_like(out, float("nan"))
+        layer.ctx.attn_decode_append(q.cuda(), k[last].cuda(), v[last].cuda(), layer.kc, layer.vc, dev_i32(pb.block_table), dev_i32(lens),
+                                     fused, int(lens.max()))
+        torch.cuda.synchronize()
+        assert torch.equal(fused, out), "the fused append changes the result"
+        layer.assert_cache_bit_exact()
+        layer.close()
+
+
+@pytest.mark.parametrize("dtype,D", [("f32", 64), ("bf16", 96)])
+def test_infinite_values_reach_only_the_rows_that_see_them(dtype, D):
+    """An infinite V element: rows before it must not notice (its weight there is a zero that must not meet it), rows
+    that see it are infinite in that element and finite in the others, as in the plain kernels."""
+    from paper_2504_18154_amd import binding
+    model = wl.ModelShape(f"{dtype}-d{D}", 4, 2, D, 1, dtype)
+    pb = wl.prefill_batch(model, [70, 20], 78)
+    layer = Layer(model, pb.num_blocks, pb.B, pb.block_table.shape[1])
+    k, v, q = (wl.randn((pb.T, h, D), dtype, s) for s, h in ((1, 2), (2, 2), (3, 4)))
+    v[33, 1, 5] = float("inf")
+    layer.append(k, v, pb.cu_q, pb.ctx_before, pb.block_table)
+    got, glse = layer.prefill_gpu(q, pb.cu_q, pb.ctx_before, pb.block_table)
+    qd = q[torch.as_tensor(pb.cu_q[1:] - 1, dtype=torch.long)]
+    gd, _ = layer.decode_gpu(qd, pb.block_table, pb.q_len)
+    layer.ctx.set_option(binding.OPT_FORCE_PLAIN, 1)
+    want, wlse = layer.prefill_gpu(q, pb.cu_q, pb.ctx_before, pb.block_table)
+    wd, _ = layer.decode_gpu(qd, pb.block_table, pb.q_len)
+    assert torch.equal(torch.isfinite(got), torch.isfinite(want)) and torch.equal(torch.isfinite(gd), torch.isfinite(wd))
+    assert torch.isfinite(got[:33]).all() and torch.isinf(got[33:70, 2:, 5]).all() and torch.isinf(gd[0, 2:, 5]).all()
+    # both kernels are within half a spacing of the same sums: a spacing of bf16 (2^-7 of |o| < 4) apart at most, fp32 by its sums
+    tol = 2.0 ** -6 if dtype == "bf16" else 1e-5
+    fin = torch.isfinite(want)
+    assert (got[fin].float() - want[fin].float()).abs().max() <= tol
+    assert (gd.float() - wd.float())[torch.isfinite(wd)].abs().max() <= tol
+    assert (glse - wlse).abs().max() <= 1e-4
+    layer.close()
