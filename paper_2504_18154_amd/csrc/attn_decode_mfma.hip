@@ -700,13 +700,32 @@ __device__ __forceinline__ void merge_partials(const float* __restrict__ ws_acc,
       o1 += ak[k].y * wk;
     }
   } else {
-    for (int k = 0; k < n_split; ++k) M = fmaxf(M, ws_ml[slot(k) * 2]);
-    for (int k = 0; k < n_split; ++k) {
-      const float wk = exp2f(ws_ml[slot(k) * 2] - M);
-      lsum += ws_ml[slot(k) * 2 + 1] * wk;
-      const float2 a = *reinterpret_cast<const float2*>(ws_acc + slot(k) * 128 + 2 * lane);
-      o0 += a.x * wk;
-      o1 += a.y * wk;
+    // 64 splits at a time: lane k holds the (max, sum) of split k, and the states are asked for eight at a time
+    // (one after the other, each waiting for the one before, a batch of 16 sequences of 20..2000 tokens - up to 26
+    // splits each - spent 16.6 us here, more than in the decode kernel: 8.9 us now; one sequence of 777 tokens 9.2,
+    // now 5.7 us)
+    for (int base = 0; base < n_split; base += 64) {
+      const int n = min(64, n_split - base);
+      const float mk = lane < n ? ws_ml[slot(base + lane) * 2] : -INFINITY;
+      const float lk = lane < n ? ws_ml[slot(base + lane) * 2 + 1] : 0.f;
+      const float M_new = fmaxf(M, wave_max(mk));
+      const float old = base ? exp2f(M - M_new) : 0.f, wk = lane < n ? exp2f(mk - M_new) : 0.f;
+      M = M_new;
+      lsum = lsum * old + wave_sum(lk * wk);
+      o0 *= old;
+      o1 *= old;
+      for (int k = 0; k < n; k += 8) {
+        float2 ak[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+          ak[j] = k + j < n ? *reinterpret_cast<const float2*>(ws_acc + slot(base + k + j) * 128 + 2 * lane) : float2{0.f, 0.f};
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          const float w = k + j < n ? __shfl(wk, k + j) : 0.f;
+          o0 += ak[j].x * w;
+          o1 += ak[j].y * w;
+        }
+      }
     }
   }
   const float inv = 1.f / lsum;
