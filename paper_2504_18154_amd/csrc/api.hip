@@ -116,7 +116,12 @@ int alloc_fixed_workspace(ecoserve_ctx* c) {
     (void)hipGetLastError();
     return ECOSERVE_EHIP;
   }
-  c->ws_bytes += meta_bytes + plan_bytes;
+  const size_t count_bytes = (size_t)c->max_batch * c->lay.num_kv_heads * sizeof(int32_t);
+  if (hipMalloc(&c->ws_count, count_bytes) != hipSuccess || hipMemset(c->ws_count, 0, count_bytes) != hipSuccess) {
+    (void)hipGetLastError();
+    return ECOSERVE_ENOMEM;
+  }
+  c->ws_bytes += meta_bytes + plan_bytes + count_bytes;
   return ECOSERVE_OK;
 }
 
@@ -214,6 +219,7 @@ int ecoserve_create(ecoserve_ctx** out, int device, const ecoserve_layout* layou
   c->ws_ml = nullptr;
   c->ws_meta = nullptr;
   c->ws_plan = nullptr;
+  c->ws_count = nullptr;
   c->plan_tiles = 0;
   c->ws_splits = 0;
   c->ws_slots = 0;
@@ -248,6 +254,7 @@ int ecoserve_destroy(ecoserve_ctx* c) {
   if (c->ws_ml) (void)hipFree(c->ws_ml);
   if (c->ws_meta) (void)hipFree(c->ws_meta);
   if (c->ws_plan) (void)hipFree(c->ws_plan);
+  if (c->ws_count) (void)hipFree(c->ws_count);
   if (c->ws_share) (void)hipFree(c->ws_share);
   for (int i = 0; i < 3; ++i)
     for (EventPair& e : c->ev[i]) { (void)hipEventDestroy(e.start); (void)hipEventDestroy(e.stop); }
@@ -473,7 +480,10 @@ static int decode_impl(ecoserve_ctx* c, const void* q, int64_t q_row_stride, con
     a.v_new = v_new;
     a.new_row_stride = (int32_t)new_row_stride;
   }
-  if (use_mfma(c)) {
+  const int32_t split_tokens = c->opt_force_plain || c->opt_split_tokens > 0
+                             ? plan_split_tokens(c, B, max_ctx_len)
+                             : decode_any_split_tokens(B, a.Hkv, max_ctx_len, c->num_cu);
+  if (use_mfma(c) && (c->opt_split_tokens > 0 || !decode_any_fits(B, a.Hkv, max_ctx_len, split_tokens, c->num_cu))) {
     const int n_wgs = c->num_cu * kDecodeWgsPerCu;
     const bool adaptive = c->opt_adaptive && c->opt_split_tokens == 0 && n_wgs % 8 == 0;
     const float* const share_in = adaptive ? c->ws_share + 8 * c->share_parity : nullptr;
@@ -493,18 +503,16 @@ static int decode_impl(ecoserve_ctx* c, const void* q, int64_t q_row_stride, con
                                  n_wgs * 4, s);
     return e == hipSuccess ? ECOSERVE_OK : ECOSERVE_EHIP;
   }
-  const int32_t split_tokens = c->opt_force_plain || c->opt_split_tokens > 0
-                                   ? plan_split_tokens(c, B, max_ctx_len)
-                                   : decode_any_split_tokens(B, a.Hkv, max_ctx_len, c->num_cu);
   const int32_t n_split_max = ceil_div(max_ctx_len, split_tokens);
-  if (n_split_max > c->ws_splits) return ECOSERVE_EINVAL;  // cannot happen for split_tokens >= kMinSplitTokens
+  // cannot happen: split_tokens >= kMinSplitTokens, and (bf16, 128) comes here with one slice per workgroup that fits
+  if (n_split_max > 1 && (use_mfma(c) ? (int64_t)B * a.Hq * n_split_max > c->ws_slots : n_split_max > c->ws_splits)) return ECOSERVE_EINVAL;
   {
     ProfileScope prof(c, ECOSERVE_KERNEL_DECODE, s);
     e = c->opt_force_plain ? launch_decode_plain(a, ctx_len, split_tokens, n_split_max, c->ws_acc, c->ws_ml, c->ws_splits, s)
-                           : launch_decode_any(a, ctx_len, split_tokens, n_split_max, c->ws_acc, c->ws_ml, c->ws_splits, s);
+                           : launch_decode_any(a, ctx_len, split_tokens, n_split_max, c->ws_acc, c->ws_ml, c->ws_count, c->num_cu, s);
   }
   if (e != hipSuccess) return ECOSERVE_EHIP;
-  if (n_split_max > 1) {
+  if (c->opt_force_plain && n_split_max > 1) {
     e = launch_decode_merge(a, ctx_len, split_tokens, c->ws_acc, c->ws_ml, c->ws_splits, s);
     if (e != hipSuccess) return ECOSERVE_EHIP;
   }

@@ -1,5 +1,6 @@
 // Paged attention on gfx950 matrix cores for every layout except bf16 with head size 128: bf16 of any head size
-// that is a multiple of 8 and fp32 of any that is a multiple of 4, up to 256.
+// that is a multiple of 8 and fp32 of any that is a multiple of 4, up to 256.  The decode kernel here also serves
+// small batches of that layout (decode_any_fits).
 //
 // Eq. 2 of Section 2.1 over the paged cache, as the kernels for (bf16, 128) evaluate it, with the arithmetic of
 // the plain kernels: scores, weights and sums are fp32.
@@ -16,7 +17,7 @@
 // Rows that share a K/V head share its loads: the 16 columns of a product are the query heads of the group
 // (decode), or (position, query head of the group) pairs of a prompt (prefill), position-major.
 //
-// What bounds them: such models are small (tens of MB of K/V at most), so a step is latency: launches, the chain
+// What bounds them: such batches are small (tens of MB of K/V at most), so a step is latency: launches, the chain
 // length -> block ids -> blocks, and the walk of the blocks.  Hence decode takes contexts up to 1024 tokens in one
 // launch, eight wavefronts per (sequence, K/V head) and the step's append inside (one launch instead of three).
 // Measured beside the plain kernels (one wavefront per query row, a scalar product per lane): a prompt batch of 4 x
@@ -30,10 +31,11 @@
 namespace eco {
 
 constexpr int kRsrc32 = 0x00020000;  // buffer descriptor: untyped 32-bit data, no swizzle, no stride
+constexpr int kNonTemporal = 2;      // cache policy: do not keep the lines
 constexpr float kRaise = 8.f;        // the exponent offset is raised when a score exceeds it by more (log2 units)
 
-// Operands of one cache block for head sizes up to 32 KS, and the two products.
-template <typename E, int KS>
+// Operands of one cache block for head sizes up to 32 KS, and the two products.  AUX: cache policy of the loads.
+template <typename E, int KS, int AUX = 0>
 struct Block {
   static constexpr bool kF32 = std::is_same<E, float>::value;
   static constexpr int X = Elem<E>::X;
@@ -49,13 +51,13 @@ struct Block {
     const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(vbase), 0, bytes, kRsrc32);
 #pragma unroll
     for (int j = 0; j < NK; ++j)
-      k[j] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rk, lane * 16 + j * 1024, 0, 0));
+      k[j] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rk, lane * 16 + j * 1024, 0, AUX));
 #pragma unroll
     for (int dt = 0; dt < NV; ++dt) {
       if constexpr (kF32)
-        v[dt] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rv, col * 64 + quad * 16 + dt * 1024, 0, 0));
+        v[dt] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rv, col * 64 + quad * 16 + dt * 1024, 0, AUX));
       else
-        v[dt] = __builtin_bit_cast(s16x4, __builtin_amdgcn_raw_buffer_load_b64(rv, col * 32 + quad * 8 + dt * 512, 0, 0));
+        v[dt] = __builtin_bit_cast(s16x4, __builtin_amdgcn_raw_buffer_load_b64(rv, col * 32 + quad * 8 + dt * 512, 0, AUX));
     }
   }
   // slots >= n hold no token: their V entries (stale bits, possibly NaN) must not meet their zero weights
@@ -192,32 +194,41 @@ __device__ __forceinline__ void attend_row(const E* __restrict__ qrow, const E* 
   }
 }
 
+// Values that another workgroup of the same launch reads, possibly on another XCD: past the caches that XCDs do not share.
+__device__ __forceinline__ void store_shared(float* p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ float load_shared(float* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
 // Decode: grid (splits, Hkv, B), W wavefronts; the blocks of a slice of `split_tokens` tokens of one (sequence, K/V
 // head) go to the wavefronts in turn, whose states are combined through LDS.  With one slice the result is final,
-// otherwise it is a partial state for decode_merge_kernel.  With k_new given the workgroup of the last slice takes
+// otherwise it is a partial state, and the last workgroup of the (sequence, K/V head) to be done merges them
+// (`counters`, one per (sequence, K/V head): zero before and after).  With k_new given the workgroup of the last slice takes
 // the newest token (position ctx_len - 1) from the new rows and stores it into the cache.
-template <typename E, int KS, int W>
+template <typename E, int KS, int W, int AUX = 0>
 __global__ __launch_bounds__(W * 64) void decode_any_kernel(
     const E* __restrict__ q, int q_row_stride, const E* __restrict__ k_new, const E* __restrict__ v_new, int new_row_stride,
     E* k_cache, E* v_cache, const int32_t* __restrict__ block_table, int bt_stride, const int32_t* __restrict__ ctx_len,
-    E* __restrict__ out, float* __restrict__ lse, float* __restrict__ ws_acc, float* __restrict__ ws_ml, int ws_splits,
-    int split_tokens, int Hq, int Hkv, int G, int D, float scale_log2e) {
-  typedef Block<E, KS> Blk;
+    E* __restrict__ out, float* __restrict__ lse, float* ws_acc, float* ws_ml, uint32_t* counters, int split_tokens, int Hq,
+    int Hkv, int G, int D, float scale_log2e) {
+  typedef Block<E, KS, AUX> Blk;
   constexpr int X = Elem<E>::X, NK = Blk::NK, NV = Blk::NV;
   constexpr int kTiles = NV < 4 ? NV : 4, kSlice = kTiles * 16;  // elements of a head vector combined at a time
   __shared__ __attribute__((aligned(16))) E s_new[2][256];
   __shared__ float s_m[W][16], s_l[W][16], s_tot[2][16];
   __shared__ __attribute__((aligned(16))) float s_acc[W][16][kSlice + 4];
-  __shared__ int s_bad;
+  __shared__ int s_bad, s_order;
   const int sp = blockIdx.x, g = blockIdx.y, b = blockIdx.z;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int col = lane & 15, quad = lane >> 4;
   // asked for before anything that depends on the length
   const bool fused = k_new != nullptr;
-  E kn = 0, vn = 0;
-  if (fused && tid < D) {
-    kn = k_new[(size_t)b * new_row_stride + (size_t)g * D + tid];
-    vn = v_new[(size_t)b * new_row_stride + (size_t)g * D + tid];
+  constexpr int NN = (32 * KS + W * 64 - 1) / (W * 64);  // elements of the new rows per thread
+  E kn[NN], vn[NN];
+#pragma unroll
+  for (int i = 0; i < NN; ++i) {
+    const int d = tid + i * W * 64;
+    const bool in = fused && d < D;
+    kn[i] = in ? k_new[(size_t)b * new_row_stride + (size_t)g * D + d] : E(0);
+    vn[i] = in ? v_new[(size_t)b * new_row_stride + (size_t)g * D + d] : E(0);
   }
   u32x4 qf[NK];
 #pragma unroll
@@ -227,18 +238,21 @@ __global__ __launch_bounds__(W * 64) void decode_any_kernel(
     qf[j] = col < G && d < D ? *reinterpret_cast<const u32x4*>(q + (size_t)b * q_row_stride + (size_t)(g * G + col) * D + d) : z;
   }
   const int L = ctx_len[b];
-  const int n_split = (L + split_tokens - 1) / split_tokens;
+  const int n_split = min((L + split_tokens - 1) / split_tokens, (int)gridDim.x);
   if (sp >= n_split) return;
-  const int t0 = sp * split_tokens, t1 = min(L, t0 + split_tokens);
+  const int t0 = sp * split_tokens, t1 = sp == n_split - 1 ? L : t0 + split_tokens;
   const int blk0 = t0 >> 4, n_blk = ((t1 + 15) >> 4) - blk0;
   const int n = wave < n_blk ? (n_blk - wave + W - 1) / W : 0;  // this wavefront's blocks: blk0 + wave + W i
   const int32_t* const bt_row = block_table + (size_t)b * bt_stride;
   const size_t piece = (size_t)16 * D * sizeof(E);
   const bool newest = fused && sp == n_split - 1;
-  if (newest && tid < D) {
-    s_new[0][tid] = kn;
-    s_new[1][tid] = vn;
-  }
+  if (newest)
+#pragma unroll
+    for (int i = 0; i < NN; ++i)
+      if (tid + i * W * 64 < D) {
+        s_new[0][tid + i * W * 64] = kn[i];
+        s_new[1][tid + i * W * 64] = vn[i];
+      }
   if (tid == 0) s_bad = 0;
   const char* const kc = reinterpret_cast<const char*>(k_cache);
   const char* const vc = reinterpret_cast<const char*>(v_cache);
@@ -288,10 +302,15 @@ __global__ __launch_bounds__(W * 64) void decode_any_kernel(
     s_l[wave][col] = l;
   }
   __syncthreads();
-  if (newest && tid < D) {  // (every wavefront's loads have been consumed: nothing in this launch reads the slot any more)
+  if (newest) {  // (every wavefront's loads have been consumed: nothing in this launch reads the slot any more)
     const int64_t blk = bt_row[(L - 1) >> 4];
-    k_cache[k_index<X>(blk, g, (L - 1) & 15, tid, Hkv, D)] = kn;
-    v_cache[v_index(blk, g, (L - 1) & 15, tid, Hkv, D)] = vn;
+#pragma unroll
+    for (int i = 0; i < NN; ++i) {
+      const int d = tid + i * W * 64;
+      if (d >= D) continue;
+      k_cache[k_index<X>(blk, g, (L - 1) & 15, d, Hkv, D)] = kn[i];
+      v_cache[v_index(blk, g, (L - 1) & 15, d, Hkv, D)] = vn[i];
+    }
   }
   float M = -INFINITY, total = 0.f;
 #pragma unroll
@@ -304,7 +323,7 @@ __global__ __launch_bounds__(W * 64) void decode_any_kernel(
     s_tot[1][col] = total;
   }
   const bool final_result = n_split == 1;
-  const size_t slot0 = ((size_t)b * Hq + (size_t)g * G) * ws_splits + sp;
+  const size_t slot0 = ((size_t)b * Hq + (size_t)g * G) * gridDim.x + sp, slot_step = gridDim.x;  // partial states: [B][Hq][slices]
 #pragma unroll
   for (int t = 0; t < NV; t += kTiles) {
 #pragma unroll
@@ -320,7 +339,7 @@ __global__ __launch_bounds__(W * 64) void decode_any_kernel(
       const float sum = s_tot[1][h];
       if (o != o && sum == sum) s_bad = 1;  // (see attend_row)
       if (final_result) Elem<E>::store(out + ((size_t)b * Hq + g * G + h) * D + d, o / sum);
-      else ws_acc[(slot0 + (size_t)h * ws_splits) * D + d] = o;
+      else store_shared(ws_acc + (slot0 + h * slot_step) * D + d, o);
     }
     __syncthreads();
   }
@@ -328,8 +347,8 @@ __global__ __launch_bounds__(W * 64) void decode_any_kernel(
     if (final_result) {
       if (lse) lse[(size_t)b * Hq + g * G + tid] = (s_tot[0][tid] + log2f(s_tot[1][tid])) * kLn2;
     } else {
-      ws_ml[(slot0 + (size_t)tid * ws_splits) * 2 + 0] = s_tot[0][tid];
-      ws_ml[(slot0 + (size_t)tid * ws_splits) * 2 + 1] = s_tot[1][tid];
+      store_shared(ws_ml + (slot0 + tid * slot_step) * 2 + 0, s_tot[0][tid]);
+      store_shared(ws_ml + (slot0 + tid * slot_step) * 2 + 1, s_tot[1][tid]);
     }
   }
   if (s_bad) {
@@ -337,17 +356,63 @@ __global__ __launch_bounds__(W * 64) void decode_any_kernel(
     for (int h = wave; h < G; h += W) {
       float rm, rl, o[4];
       attend_row<E>(q + (size_t)b * q_row_stride + (size_t)(g * G + h) * D, k_cache, v_cache, bt_row, g, Hkv, D, t0, t1, scale_log2e, rm, rl, o);
+#pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int d = lane + 64 * r;
         if (d >= D) continue;
         if (final_result) Elem<E>::store(out + ((size_t)b * Hq + g * G + h) * D + d, o[r] / rl);
-        else ws_acc[(slot0 + (size_t)h * ws_splits) * D + d] = o[r];
+        else store_shared(ws_acc + (slot0 + h * slot_step) * D + d, o[r]);
       }
       if (!final_result && lane == 0) {
-        ws_ml[(slot0 + (size_t)h * ws_splits) * 2 + 0] = rm;
-        ws_ml[(slot0 + (size_t)h * ws_splits) * 2 + 1] = rl;
+        store_shared(ws_ml + (slot0 + h * slot_step) * 2 + 0, rm);
+        store_shared(ws_ml + (slot0 + h * slot_step) * 2 + 1, rl);
       }
     }
+  }
+  if (final_result) return;
+
+  // The slice that is done last merges them all:
+  //   M = max_k m_k;  l = sum_k l_k 2^(m_k - M);  o = sum_k acc_k 2^(m_k - M) / l.
+  // Every thread's stores have reached the level the XCDs share before its workgroup is counted (store_shared, and the
+  // wait below), and what is read back is read from there, so no cache has to be written back or dropped.
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (tid == 0) s_order = (int)atomicInc(counters + (size_t)b * Hkv + g, (unsigned)n_split - 1);  // (the last one wraps it to zero)
+  __syncthreads();
+  if (s_order != n_split - 1) return;
+  for (int h = wave; h < G; h += W) {
+    const size_t slot = slot0 - sp + h * slot_step;
+    float m2 = -INFINITY, l2 = 0.f, o2[4] = {0.f, 0.f, 0.f, 0.f};
+    for (int base = 0; base < n_split; base += 64) {  // 64 slices at a time: lane k holds the (max, sum) of slice k
+      const int nk = min(64, n_split - base);
+      const float mk = lane < nk ? load_shared(ws_ml + (slot + base + lane) * 2) : -INFINITY;
+      const float lk = lane < nk ? load_shared(ws_ml + (slot + base + lane) * 2 + 1) : 0.f;
+      const float m_new = fmaxf(m2, wave_max(mk));
+      const float old = base ? __builtin_amdgcn_exp2f(m2 - m_new) : 0.f, wk = lane < nk ? __builtin_amdgcn_exp2f(mk - m_new) : 0.f;
+      m2 = m_new;
+      l2 = l2 * old + wave_sum(lk * wk);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) o2[r] *= old;
+      for (int k = 0; k < nk; k += 4) {
+        float ak[4][(KS + 1) / 2];
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+          for (int r = 0; r < (KS + 1) / 2; ++r)
+            ak[j][r] = k + j < nk && lane + 64 * r < D ? load_shared(ws_acc + (slot + base + k + j) * D + lane + 64 * r) : 0.f;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const float w = k + j < nk ? __shfl(wk, k + j) : 0.f;
+#pragma unroll
+          for (int r = 0; r < (KS + 1) / 2; ++r) o2[r] += ak[j][r] * w;
+        }
+      }
+    }
+    E* const orow = out + ((size_t)b * Hq + g * G + h) * D;
+#pragma unroll
+    for (int r = 0; r < (KS + 1) / 2; ++r)
+      if (lane + 64 * r < D) Elem<E>::store(orow + lane + 64 * r, o2[r] / l2);
+    if (lse && lane == 0) lse[(size_t)b * Hq + g * G + h] = (m2 + log2f(l2)) * kLn2;
   }
 }
 
@@ -527,23 +592,42 @@ void launch_prefill_typed(const AttnArgs& a, const int32_t* cu_q, const int32_t*
 
 template <typename E>
 void launch_decode_typed(const AttnArgs& a, const int32_t* ctx_len, int32_t split_tokens, int32_t n_split_max, float* ws_acc,
-                         float* ws_ml, int32_t ws_splits, hipStream_t s) {
+                         float* ws_ml, uint32_t* counters, bool many, hipStream_t s) {
+  auto launch = [&](auto kernel, int W) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)n_split_max, (unsigned)a.Hkv, (unsigned)a.B), dim3(W * 64), 0, s,
+                       (const E*)a.q, a.q_row_stride, (const E*)a.k_new, (const E*)a.v_new, a.new_row_stride,
+                       (E*)const_cast<void*>(a.k_cache), (E*)const_cast<void*>(a.v_cache), a.block_table, a.bt_stride, ctx_len,
+                       (E*)a.out, a.lse, ws_acc, ws_ml, counters, split_tokens, a.Hq, a.Hkv, a.Hq / a.Hkv, a.D, a.scale_log2e);
+  };
   for_head_size(a.D, [&](auto ks) {
     // eight wavefronts per workgroup while two blocks of K and V fit beside the rest in 256 registers
     constexpr int KS = decltype(ks)::value, W = KS > (sizeof(E) == 4 ? 4 : 6) ? 4 : 8;
-    hipLaunchKernelGGL((decode_any_kernel<E, KS, W>), dim3((unsigned)n_split_max, (unsigned)a.Hkv, (unsigned)a.B), dim3(W * 64), 0, s,
-                       (const E*)a.q, a.q_row_stride, (const E*)a.k_new, (const E*)a.v_new, a.new_row_stride,
-                       (E*)const_cast<void*>(a.k_cache), (E*)const_cast<void*>(a.v_cache), a.block_table, a.bt_stride, ctx_len,
-                       (E*)a.out, a.lse, ws_acc, ws_ml, ws_splits, split_tokens, a.Hq, a.Hkv, a.Hq / a.Hkv, a.D, a.scale_log2e);
+    if constexpr (KS == 4 && sizeof(E) == 2)
+      if (many) return launch(decode_any_kernel<E, KS, 4, kNonTemporal>, 4);
+    launch(decode_any_kernel<E, KS, W>, W);
   });
 }
 
 }  // namespace
 
+// Contexts up to 1024 tokens stay whole (no merge); longer ones are cut into slices of 256 tokens, or of 512 or 1024
+// when that already makes enough workgroups.  (One sequence of 2000 / 8000 tokens, 8 K/V heads: 10.5 / 17.6 us in slices
+// of 256, 11.2 / 15.6 of 512, 13.7 / 18.6 of 1024.)
 int32_t decode_any_split_tokens(int32_t B, int32_t Hkv, int32_t max_ctx_len, int32_t num_cu) {
-  int32_t st = 1024;
-  while (st > 256 && max_ctx_len > 1024 && (int64_t)B * Hkv * ((max_ctx_len + st - 1) / st) < num_cu) st >>= 1;
+  int32_t st = max_ctx_len > 1024 ? 256 : 1024;
+  while (st < 1024 && (int64_t)B * Hkv * ((max_ctx_len + st - 1) / st) > num_cu / 2) st *= 2;
   return st;
+}
+
+// For (bf16, 128): whether the batch is small enough for this kernel, i.e. all its workgroups run at once - one of eight
+// wavefronts per CU, or (short contexts) two of four.  It needs no numbering of the batch and no second launch, which
+// is what such a batch spends its time on in the persistent kernel (us per layer there and here, 8 K/V heads: 1 x 777
+// tokens 14.6, 9.7; 1 x 8000: 32.0, 15.6; 4 x 2000: 22.5, 14.5; 16 x 1000: 22.7, 19.0; 32 x 200: 17.2, 11.6; 64 x 500:
+// 38.7, 30.2), but nothing evens out the lengths of more workgroups than fit: 128 sequences around 500 tokens, lognormal,
+// take 66 there and 73 to 88 here.
+bool decode_any_fits(int32_t B, int32_t Hkv, int32_t max_ctx_len, int32_t split_tokens, int32_t num_cu) {
+  const int64_t pairs = (int64_t)B * Hkv;
+  return pairs * ((max_ctx_len + split_tokens - 1) / split_tokens) <= num_cu || (max_ctx_len <= 512 && pairs <= 2 * num_cu);
 }
 
 hipError_t launch_prefill_any(const AttnArgs& a, const int32_t* cu_q, const int32_t* ctx_before, int32_t T, hipStream_t s) {
@@ -553,9 +637,10 @@ hipError_t launch_prefill_any(const AttnArgs& a, const int32_t* cu_q, const int3
 }
 
 hipError_t launch_decode_any(const AttnArgs& a, const int32_t* ctx_len, int32_t split_tokens, int32_t n_split_max, float* ws_acc,
-                             float* ws_ml, int32_t ws_splits, hipStream_t s) {
-  if (a.dtype == ECOSERVE_BF16) launch_decode_typed<uint16_t>(a, ctx_len, split_tokens, n_split_max, ws_acc, ws_ml, ws_splits, s);
-  else launch_decode_typed<float>(a, ctx_len, split_tokens, n_split_max, ws_acc, ws_ml, ws_splits, s);
+                             float* ws_ml, uint32_t* counters, int32_t num_cu, hipStream_t s) {
+  const bool many = (int64_t)a.B * a.Hkv * n_split_max > num_cu;
+  if (a.dtype == ECOSERVE_BF16) launch_decode_typed<uint16_t>(a, ctx_len, split_tokens, n_split_max, ws_acc, ws_ml, counters, many, s);
+  else launch_decode_typed<float>(a, ctx_len, split_tokens, n_split_max, ws_acc, ws_ml, counters, many, s);
   return hipGetLastError();
 }
 

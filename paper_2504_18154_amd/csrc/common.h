@@ -94,6 +94,7 @@ struct ecoserve_ctx {
   float* ws_share;             // per-XCD shares (mean 1) [2][8], speeds [8], then as int32 [2 * wavefronts]: units, ticks,
                                // then [4 * wavefronts]: the cut (sequence, K/V head) each chunk reports to the merge
   int share_parity;            // which of the two share vectors the next adaptive decode launch reads
+  uint32_t* ws_count;          // [max_batch][Hkv], zero between launches: slices of a (sequence, K/V head) that are done
   int32_t ws_splits;
   int32_t* ws_plan;            // prefill plan: header and one record per query tile of the last prefill launch
   int64_t plan_tiles;          // records ws_plan has room for
@@ -155,13 +156,14 @@ hipError_t launch_decode_plain(const AttnArgs& a, const int32_t* ctx_len, int32_
 hipError_t launch_decode_merge(const AttnArgs& a, const int32_t* ctx_len, int32_t split_tokens, const float* ws_acc,
                                const float* ws_ml, int32_t ws_splits, hipStream_t s);
 
-// attn_any_mfma.hip: every layout but (bf16, D = 128), on matrix cores
-// (with a.k_new given, the decode launch appends the step's tokens too; split_tokens: a multiple of 16 per slice of
-// the context, n_split_max slices, partial states as in the plain decode, merged by launch_decode_merge if > 1)
+// attn_any_mfma.hip: every layout on matrix cores (bf16, D = 128: small decode batches only)
+// (one launch; with a.k_new given it appends the step's tokens too; split_tokens: a multiple of 16 per slice of the
+// context, n_split_max slices; partial states [B][Hq][n_split_max], counters [B][Hkv] that are zero and stay so)
 int32_t decode_any_split_tokens(int32_t B, int32_t Hkv, int32_t max_ctx_len, int32_t num_cu);
+bool decode_any_fits(int32_t B, int32_t Hkv, int32_t max_ctx_len, int32_t split_tokens, int32_t num_cu);
 hipError_t launch_prefill_any(const AttnArgs& a, const int32_t* cu_q, const int32_t* ctx_before, int32_t T, hipStream_t s);
 hipError_t launch_decode_any(const AttnArgs& a, const int32_t* ctx_len, int32_t split_tokens, int32_t n_split_max,
-                             float* ws_acc, float* ws_ml, int32_t ws_splits, hipStream_t s);
+                             float* ws_acc, float* ws_ml, uint32_t* counters, int32_t num_cu, hipStream_t s);
 
 // attn_decode_mfma.hip: bf16, D = 128
 // (split_tokens 0 = equal share per wavefront of the persistent grid; > 0 forces the chunk size)

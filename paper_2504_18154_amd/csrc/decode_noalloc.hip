@@ -1,17 +1,18 @@
 // Decode attention for callers that cannot allocate: ecoserve_attn_decode_noalloc.
 //
-// The same two launches as ecoserve_attn_decode on the matrix-core path (persistent split-context kernel,
-// then the merge of the cut (sequence, head)s), without a context: the scratch memory those kernels need -
-// the partial softmax states of cut pieces, the launch's numbering, each chunk's report to the merge - is a
+// The same launches as ecoserve_attn_decode on the matrix-core path (for a small batch one kernel, else the
+// persistent split-context kernel, then the merge of the cut (sequence, head)s), without a context: the scratch memory those kernels need -
+// the partial softmax states of cut pieces, the launch's numbering, each chunk's report to the merge, the
+// counters of the small-batch kernel - is a
 // file-scope device array of fixed size instead of a workspace allocated by ecoserve_create.  The call makes
 // no allocation of any kind (no hipMalloc / hipFree, no events, no library routine that allocates), so it can
 // be used under graph capture, in serving loops and in harnesses that forbid allocation.
 //
 // Every GPU holds its own copy of the array at its own address; the address is looked up once per device
 // (hipGetSymbolAddress with that device current) and kept.  All calls on one GPU share that GPU's array:
-// calls that overlap on one GPU (two streams, two threads) race on it.  Nothing in the array has to start
-// at zero: a launch writes every word it later reads (each wavefront writes its report, the merge reads only
-// the states a report names).
+// calls that overlap on one GPU (two streams, two threads) race on it.  The counters start at zero, as the array does,
+// and every launch leaves them there; nothing else has to: a launch writes every word it later reads (each wavefront
+// writes its report, the merge reads only the states a report names).
 #include <mutex>
 
 #include "common.h"
@@ -25,7 +26,8 @@ constexpr size_t kAccFloats = (size_t)2 * kNoallocMaxWaves * kMaxGroup * 128;  /
 constexpr size_t kMlFloats = (size_t)2 * kNoallocMaxWaves * kMaxGroup * 2;
 constexpr size_t kMetaInts = (kMaxBatch + 19 + 63) / 64 * 64;
 constexpr size_t kCutInts = (size_t)4 * kNoallocMaxWaves;
-constexpr size_t kScratchBytes = (kAccFloats + kMlFloats + kMetaInts + kCutInts) * 4;  // 16.3 MiB
+constexpr size_t kCountInts = (size_t)2 * kNoallocMaxWgs;  // decode_any_fits: at most this many (sequence, K/V head)s
+constexpr size_t kScratchBytes = (kAccFloats + kMlFloats + kMetaInts + kCutInts + kCountInts) * 4;  // 16.3 MiB
 
 // On the host this name is only a handle for hipGetSymbolAddress; device code and kernel arguments use the
 // address looked up below.
@@ -120,6 +122,14 @@ extern "C" int ecoserve_attn_decode_noalloc(int device, const ecoserve_layout* l
 
   const int n_wgs = dev.num_cu * kDecodeWgsPerCu < kNoallocMaxWgs ? dev.num_cu * kDecodeWgsPerCu : kNoallocMaxWgs;
   hipStream_t s = (hipStream_t)stream;
+  const int32_t split_tokens = decode_any_split_tokens(B, a.Hkv, max_ctx_len, n_wgs);
+  if (decode_any_fits(B, a.Hkv, max_ctx_len, split_tokens, n_wgs)) {
+    // (at most n_wgs slices in all, or one per (sequence, K/V head): B Hq n_split partial states fit the two groups of
+    // kMaxGroup slots per wavefront)
+    return launch_decode_any(a, ctx_len, split_tokens, (max_ctx_len + split_tokens - 1) / split_tokens, ws_acc, ws_ml,
+                             reinterpret_cast<uint32_t*>(ws_cut + kCutInts),
+                             n_wgs, s) == hipSuccess ? ECOSERVE_OK : ECOSERVE_EHIP;
+  }
   // (a slot group holds G <= kMaxGroup states, so the array covers kNoallocMaxWaves wavefronts whatever G is)
   hipError_t e = launch_decode_mfma(a, ctx_len, 0, max_ctx_len, n_wgs, ws_acc, ws_ml, ws_meta, kNoallocMaxWaves,
                                     nullptr, nullptr, nullptr, nullptr, ws_cut, s);
