@@ -211,7 +211,7 @@ __global__ __launch_bounds__(W * 64) void decode_any_kernel(
     int Hkv, int G, int D, float scale_log2e) {
   typedef Block<E, KS, AUX> Blk;
   constexpr int X = Elem<E>::X, NK = Blk::NK, NV = Blk::NV;
-  constexpr int kTiles = NV < 4 ? NV : 4, kSlice = kTiles * 16;  // elements of a head vector combined at a time
+  constexpr int kTiles = NV < 8 ? NV : 8, kSlice = kTiles * 16;  // elements of a head vector combined at a time
   __shared__ __attribute__((aligned(16))) E s_new[2][256];
   __shared__ float s_m[W][16], s_l[W][16], s_tot[2][16];
   __shared__ __attribute__((aligned(16))) float s_acc[W][16][kSlice + 4];
@@ -219,7 +219,11 @@ __global__ __launch_bounds__(W * 64) void decode_any_kernel(
   const int sp = blockIdx.x, g = blockIdx.y, b = blockIdx.z;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int col = lane & 15, quad = lane >> 4;
-  // asked for before anything that depends on the length
+  // Asked for before anything that depends on the length: the ids of this wavefront's first 64 blocks (blk0 + wave +
+  // W i; entries behind the sequence's last block are read and never used), the new rows, the query rows.
+  const int32_t* const bt_row = block_table + (size_t)b * bt_stride;
+  const int blk0 = (sp * split_tokens) >> 4;
+  int ids = bt_row[min(blk0 + wave + W * lane, bt_stride - 1)];
   const bool fused = k_new != nullptr;
   constexpr int NN = (32 * KS + W * 64 - 1) / (W * 64);  // elements of the new rows per thread
   E kn[NN], vn[NN];
@@ -241,11 +245,42 @@ __global__ __launch_bounds__(W * 64) void decode_any_kernel(
   const int n_split = min((L + split_tokens - 1) / split_tokens, (int)gridDim.x);
   if (sp >= n_split) return;
   const int t0 = sp * split_tokens, t1 = sp == n_split - 1 ? L : t0 + split_tokens;
-  const int blk0 = t0 >> 4, n_blk = ((t1 + 15) >> 4) - blk0;
-  const int n = wave < n_blk ? (n_blk - wave + W - 1) / W : 0;  // this wavefront's blocks: blk0 + wave + W i
-  const int32_t* const bt_row = block_table + (size_t)b * bt_stride;
+  const int n_blk = ((t1 + 15) >> 4) - blk0;
+  const int n = wave < n_blk ? (n_blk - wave + W - 1) / W : 0;  // this wavefront's blocks
   const size_t piece = (size_t)16 * D * sizeof(E);
   const bool newest = fused && sp == n_split - 1;
+  const char* const kc = reinterpret_cast<const char*>(k_cache);
+  const char* const vc = reinterpret_cast<const char*>(v_cache);
+
+  // The blocks are walked in windows of the 64 ids a register holds (one window for slices up to 1024 W tokens), two in
+  // flight.  A wavefront's last block comes first in its window: it may be the slice's last one, and what that needs
+  // (the newest token, the slots behind the end) then stands once, in front of the loop - a short context is latency
+  // from the first instruction on, and code that runs once costs its fetch.
+  Blk f[2];
+  int base = 0, nw = min(64, n);
+  auto fetch = [&](Blk& fr, int i) {
+    const int at = base + 64 < n ? i : i == 0 ? nw - 1 : i - 1;
+    const size_t off = ((size_t)__builtin_amdgcn_readlane(ids, max(min(at, nw - 1), 0)) * Hkv + g) * piece;
+    fr.load(kc + off, vc + off, i < nw ? (int)piece : 0, lane, col, quad);
+  };
+  f32x4 acc[NV];
+#pragma unroll
+  for (int dt = 0; dt < NV; ++dt) acc[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float m = -INFINITY, l = 0.f;
+  auto work = [&](const Blk& fr, int tail) {
+    f32x4 s = fr.scores(qf) * scale_log2e;
+    if (tail < 16) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (4 * quad + e >= tail) s[e] = -INFINITY;
+    }
+    const f32x4 p = softmax_step<NV>(s, m, l, acc);
+    fr.values(p, acc);
+  };
+  if (n > 0) {
+    fetch(f[0], 0);
+    fetch(f[1], 1);
+  }
   if (newest)
 #pragma unroll
     for (int i = 0; i < NN; ++i)
@@ -254,45 +289,27 @@ __global__ __launch_bounds__(W * 64) void decode_any_kernel(
         s_new[1][tid + i * W * 64] = vn[i];
       }
   if (tid == 0) s_bad = 0;
-  const char* const kc = reinterpret_cast<const char*>(k_cache);
-  const char* const vc = reinterpret_cast<const char*>(v_cache);
-
-  f32x4 acc[NV];
-#pragma unroll
-  for (int dt = 0; dt < NV; ++dt) acc[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float m = -INFINITY, l = 0.f;
   __syncthreads();
-  for (int base = 0; base < n; base += 64) {  // windows of the 64 block ids one register holds
-    const int nw = min(64, n - base);
-    const int ids = lane < nw ? bt_row[blk0 + wave + W * (base + lane)] : 0;
-    Blk f[2];
-    auto fetch = [&](Blk& fr, int i) {
-      const size_t off = ((size_t)__builtin_amdgcn_readlane(ids, min(i, nw - 1)) * Hkv + g) * piece;
-      fr.load(kc + off, vc + off, i < nw ? (int)piece : 0, lane, col, quad);
-    };
-    auto work = [&](Blk& fr, int i) {
-      const int first = (blk0 + wave + W * (base + i)) << 4;
-      const int tail = t1 - first;
-      if (tail <= 16) {
-        asm volatile("" ::: "memory");  // (a real branch: the last block only)
-        if (newest) fr.put_token(s_new[0], s_new[1], tail - 1, D, col, quad);
-        if (tail < 16) fr.clear_tail(tail, quad);
-      }
-      f32x4 s = fr.scores(qf) * scale_log2e;
-      if (tail < 16) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (4 * quad + e >= tail) s[e] = -INFINITY;
-      }
-      const f32x4 p = softmax_step<NV>(s, m, l, acc);
-      fr.values(p, acc);
-    };
-    fetch(f[0], 0);
+  while (base < n) {
+    int tail = 16;
+    if (base + 64 >= n && wave + W * (n - 1) == n_blk - 1) {  // f[0] is the slice's last block
+      tail = t1 - ((blk0 + n_blk - 1) << 4);
+      if (newest) f[0].put_token(s_new[0], s_new[1], tail - 1, D, col, quad);
+      if (tail < 16) f[0].clear_tail(tail, quad);
+    }
     for (int i = 0; i < nw; i += 2) {
-      fetch(f[1], i + 1);
-      work(f[0], i);
+      work(f[0], tail);
+      tail = 16;
       fetch(f[0], i + 2);
-      if (i + 1 < nw) work(f[1], i + 1);
+      if (i + 1 < nw) work(f[1], 16);
+      fetch(f[1], i + 3);
+    }
+    base += 64;
+    if (base < n) {
+      nw = min(64, n - base);
+      ids = lane < nw ? bt_row[blk0 + wave + W * (base + lane)] : 0;
+      fetch(f[0], 0);
+      fetch(f[1], 1);
     }
   }
   l += __shfl_xor(l, 16);
@@ -328,7 +345,7 @@ __global__ __launch_bounds__(W * 64) void decode_any_kernel(
   for (int t = 0; t < NV; t += kTiles) {
 #pragma unroll
     for (int i = 0; i < kTiles; ++i)
-      if (t + i < NV) *reinterpret_cast<f32x4*>(&s_acc[wave][col][i * 16 + 4 * quad]) = acc[t + i] * mine;
+      if (t + i < NV && col < G) *reinterpret_cast<f32x4*>(&s_acc[wave][col][i * 16 + 4 * quad]) = acc[t + i] * mine;
     __syncthreads();
     for (int idx = tid; idx < G * kSlice; idx += W * 64) {
       const int h = idx / kSlice, dl = idx % kSlice, d = t * 16 + dl;
