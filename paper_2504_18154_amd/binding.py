@@ -137,28 +137,33 @@ def probe_mfma_valu(with_mfma: bool, fma_per_slot: int, exp_per_slot: int, waves
     return clocks.value, ghz.value
 
 
+# A hot call on a small batch keeps the GPU busy for 6 to 10 us, less than the marshalling of its arguments used to take
+# (11 us for attn_decode_append: 7 of them four times _row_stride, a Python call into the tensor per dimension).  So:
+# addresses go to ctypes as plain integers, a tensor is asked once for all its strides, and the stream's handle comes
+# without a Stream object around it.
 def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else None
+    return t.data_ptr() if t is not None else None
 
 
 def attn_decode_noalloc(layout: Layout, q, k_cache, v_cache, block_table, ctx_len, out, max_ctx_len, lse=None,
                         device: int = 0) -> int:
     """ecoserve_attn_decode without a context and without any allocation; returns the status code."""
     return int(_lib.ecoserve_attn_decode_noalloc(int(device), ctypes.byref(layout), _ptr(q), _ptr(k_cache),
-                                                 _ptr(v_cache), _ptr(block_table), int(block_table.shape[1]),
-                                                 _ptr(ctx_len), _ptr(out), _ptr(lse), int(ctx_len.numel()),
+                                                 _ptr(v_cache), _ptr(block_table), block_table.shape[1],
+                                                 _ptr(ctx_len), _ptr(out), _ptr(lse), ctx_len.numel(),
                                                  int(max_ctx_len), _stream()))
 
 
 def _row_stride(t) -> int:
     """Elements between consecutive tokens of a [tokens, heads, D] tensor or view whose heads are contiguous."""
-    if t.dim() != 3 or t.stride(2) != 1 or t.stride(1) != t.shape[2]:
+    shape, stride = t.shape, t.stride()
+    if len(shape) != 3 or stride[2] != 1 or stride[1] != shape[2]:
         raise ValueError("expected a [tokens, heads, D] tensor with contiguous heads")
-    return int(t.stride(0)) if t.shape[0] > 1 else int(t.shape[1] * t.shape[2])
+    return stride[0] if shape[0] > 1 else shape[1] * shape[2]
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())  # torch.cuda.current_stream().cuda_stream
 
 
 class Context:
@@ -221,8 +226,8 @@ class Context:
         if max_new_len is None:
             max_new_len = T
         _check(_lib.ecoserve_kv_append(self._h, _ptr(k_cache), _ptr(v_cache), _ptr(k_new), _ptr(v_new), _ptr(cu_q),
-                                       _ptr(ctx_before), _ptr(block_table), int(block_table.shape[1]), int(B),
-                                       int(T), int(max_new_len), _stream()), "ecoserve_kv_append")
+                                       _ptr(ctx_before), _ptr(block_table), block_table.shape[1], B,
+                                       T, int(max_new_len), _stream()), "ecoserve_kv_append")
 
     def attn_prefill(self, q, k_cache, v_cache, cu_q, ctx_before, block_table, out, lse=None, max_q_len=None):
         B = ctx_before.numel()
@@ -230,8 +235,8 @@ class Context:
         if max_q_len is None:
             max_q_len = T
         _check(_lib.ecoserve_attn_prefill(self._h, _ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(cu_q),
-                                          _ptr(ctx_before), _ptr(block_table), int(block_table.shape[1]), _ptr(out),
-                                          _ptr(lse), int(B), int(T), int(max_q_len), _stream()),
+                                          _ptr(ctx_before), _ptr(block_table), block_table.shape[1], _ptr(out),
+                                          _ptr(lse), B, T, int(max_q_len), _stream()),
                "ecoserve_attn_prefill")
 
     # the same on views into wider rows (e.g. slices of a fused projection output [T, Hq + 2 Hkv, D])
@@ -240,11 +245,12 @@ class Context:
         T = k_new.shape[0]
         if max_new_len is None:
             max_new_len = T
-        if _row_stride(k_new) != _row_stride(v_new):
+        new_stride = _row_stride(k_new)
+        if new_stride != _row_stride(v_new):
             raise ValueError("k_new and v_new must have the same row stride")
         _check(_lib.ecoserve_kv_append_strided(self._h, _ptr(k_cache), _ptr(v_cache), _ptr(k_new), _ptr(v_new),
-                                               _row_stride(k_new), _ptr(cu_q), _ptr(ctx_before), _ptr(block_table),
-                                               int(block_table.shape[1]), int(B), int(T), int(max_new_len),
+                                               new_stride, _ptr(cu_q), _ptr(ctx_before), _ptr(block_table),
+                                               block_table.shape[1], B, T, int(max_new_len),
                                                _stream()), "ecoserve_kv_append_strided")
 
     def attn_prefill_strided(self, q, k_cache, v_cache, cu_q, ctx_before, block_table, out, lse=None,
@@ -255,30 +261,31 @@ class Context:
             max_q_len = T
         _check(_lib.ecoserve_attn_prefill_strided(self._h, _ptr(q), _row_stride(q), _ptr(k_cache), _ptr(v_cache),
                                                   _ptr(cu_q), _ptr(ctx_before), _ptr(block_table),
-                                                  int(block_table.shape[1]), _ptr(out), _ptr(lse), int(B), int(T),
+                                                  block_table.shape[1], _ptr(out), _ptr(lse), B, T,
                                                   int(max_q_len), _stream()), "ecoserve_attn_prefill_strided")
 
     def attn_decode_strided(self, q, k_cache, v_cache, block_table, ctx_len, out, max_ctx_len, lse=None):
         B = ctx_len.numel()
         _check(_lib.ecoserve_attn_decode_strided(self._h, _ptr(q), _row_stride(q), _ptr(k_cache), _ptr(v_cache),
-                                                 _ptr(block_table), int(block_table.shape[1]), _ptr(ctx_len),
-                                                 _ptr(out), _ptr(lse), int(B), int(max_ctx_len), _stream()),
+                                                 _ptr(block_table), block_table.shape[1], _ptr(ctx_len),
+                                                 _ptr(out), _ptr(lse), B, int(max_ctx_len), _stream()),
                "ecoserve_attn_decode_strided")
 
     def attn_decode_append(self, q, k_new, v_new, k_cache, v_cache, block_table, ctx_len, out, max_ctx_len, lse=None):
         """Decode with the append of the step's one new token per sequence fused in (ctx_len counts it)."""
         B = ctx_len.numel()
-        if _row_stride(k_new) != _row_stride(v_new):
+        new_stride = _row_stride(k_new)
+        if new_stride != _row_stride(v_new):
             raise ValueError("k_new and v_new must have the same row stride")
         _check(_lib.ecoserve_attn_decode_append(self._h, _ptr(q), _row_stride(q), _ptr(k_new), _ptr(v_new),
-                                                _row_stride(k_new), _ptr(k_cache), _ptr(v_cache), _ptr(block_table),
-                                                int(block_table.shape[1]), _ptr(ctx_len), _ptr(out), _ptr(lse), int(B),
+                                                new_stride, _ptr(k_cache), _ptr(v_cache), _ptr(block_table),
+                                                block_table.shape[1], _ptr(ctx_len), _ptr(out), _ptr(lse), B,
                                                 int(max_ctx_len), _stream()), "ecoserve_attn_decode_append")
 
     def attn_decode(self, q, k_cache, v_cache, block_table, ctx_len, out, max_ctx_len, lse=None):
         B = ctx_len.numel()
         _check(_lib.ecoserve_attn_decode(self._h, _ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(block_table),
-                                         int(block_table.shape[1]), _ptr(ctx_len), _ptr(out), _ptr(lse), int(B),
+                                         block_table.shape[1], _ptr(ctx_len), _ptr(out), _ptr(lse), B,
                                          int(max_ctx_len), _stream()), "ecoserve_attn_decode")
 
     # ---- debugging / profiling -----------------------------------------------------------
