@@ -439,8 +439,8 @@ __global__ __launch_bounds__(W * 64) void decode_any_kernel(
 // blocks up to its own diagonal by itself (the four of a workgroup read the same blocks at about the same time:
 // the caches serve three of them).
 // Sequence b's tiles are numbered from cu_q[b] G / R + b (R rows per tile): consecutive sequences are then at least
-// ceil(S G / R) numbers apart, so no prefix sum over the batch is needed, and every workgroup finds its sequence
-// with a search over cu_q, 64 candidates at a time.  Later tiles of a sequence are longer and go first.
+// ceil(S G / R) numbers apart, so no prefix sum over the batch is needed (find_sequence).  Later tiles of a sequence
+// are longer and go first.
 template <typename E, int KS, int NC>
 __global__ __launch_bounds__(256) void prefill_any_kernel(
     const E* __restrict__ q, int q_row_stride, const E* __restrict__ k_cache, const E* __restrict__ v_cache,
@@ -451,20 +451,12 @@ __global__ __launch_bounds__(256) void prefill_any_kernel(
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int col = lane & 15, quad = lane >> 4, g = blockIdx.y;
   const int tile_no = (int)(gridDim.x - 1 - blockIdx.x);
-  int b = 0, cand = B;  // largest b with cu_q[b] G / R + b <= tile_no
-  while (cand > 1) {
-    const int stride = (cand + 63) >> 6, idx = b + lane * stride;
-    const bool le = idx < b + cand && (long long)cu_q[min(idx, B)] * G / R + idx <= tile_no;
-    const int last = __popcll(__ballot(le)) - 1;
-    const int nb = b + last * stride;
-    cand = min(stride, b + cand - nb);
-    b = nb;
-  }
-  const int tok0 = cu_q[b], S = cu_q[b + 1] - tok0;
-  const long long r0 = ((long long)tile_no - ((long long)tok0 * G / R + b)) * R + wave * (16 * NC);
+  auto first_tile = [&](int cu, int b) { return (long long)((unsigned long long)(unsigned)cu * (unsigned)G / (unsigned)R) + b; };
+  const SeqOf seq = find_sequence(cu_q, ctx_before, B, tile_no, first_tile);
+  const int b = seq.b, tok0 = seq.tok0, S = seq.S, cb = seq.cb;
+  const long long r0 = (tile_no - first_tile(tok0, b)) * R + wave * (16 * NC);
   const long long n_rows = (long long)S * G;
   if (r0 >= n_rows) return;
-  const int cb = ctx_before[b];
   const int32_t* const bt_row = block_table + (size_t)b * bt_stride;
   const size_t piece = (size_t)16 * D * sizeof(E);
   const int L = cb + S;

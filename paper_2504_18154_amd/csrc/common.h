@@ -136,8 +136,8 @@ struct AttnArgs {
 bool layout_ok(const ecoserve_layout* L, int* status);
 
 // kv_append.hip
-// (at context creation: a batch of thousands needs more dynamic LDS than a kernel may use by default, and the
-// limit is raised here, once, rather than by a hot call)
+// (at context creation: large fp32 heads need more dynamic LDS than a kernel may use by default, and the limit is
+// raised here, once, rather than by a hot call)
 hipError_t prepare_kv_append(const ecoserve_ctx* ctx);
 // (new_row_stride: elements between the K rows, and between the V rows, of consecutive tokens.  With
 // max_new_len <= 1, cu_q may be NULL: one token per sequence, token b for sequence b, stored at position
@@ -263,6 +263,35 @@ __device__ __forceinline__ void append_one_row(E* __restrict__ k_cache, E* __res
     *reinterpret_cast<u4*>(kdst + (size_t)c * 16 * X) = *reinterpret_cast<const u4*>(ksrc + c * X);
   E* vdst = v_cache + ((size_t)blk * Hkv + g) * D * 16 + slot;
   for (int d = lane; d < D; d += 64) vdst[(size_t)d * 16] = vsrc[d];
+}
+
+// The sequence that work unit `unit` belongs to, for units numbered so that sequence b's begin at
+// first(cu_q[b], b), increasing in b, first(0, 0) = 0: a search with 64 candidates at a time, no prefix sum over the batch
+// and no barrier; what the caller needs of the batch description comes along with the last round.  Whole wavefronts.
+struct SeqOf {
+  int b, tok0, S, cb;  // sequence, its first packed token, new tokens, cached tokens
+};
+template <typename F>
+__device__ __forceinline__ SeqOf find_sequence(const int32_t* __restrict__ cu_q, const int32_t* __restrict__ ctx_before, int B,
+                                               long long unit, F first) {
+  const int lane = threadIdx.x & 63;
+  int lo = 0, cand = B;
+  while (cand > 64) {
+    const int stride = (cand + 63) >> 6, idx = lo + lane * stride;
+    const bool le = idx < lo + cand && first(cu_q[min(idx, B)], idx) <= unit;
+    const int next = lo + max((int)__popcll(__ballot(le)) - 1, 0) * stride;
+    cand = min(stride, lo + cand - next);
+    lo = next;
+  }
+  const int idx = min(lo + lane, B - 1);
+  const int c0 = cu_q[idx], c1 = cu_q[idx + 1], cb = ctx_before[idx];
+  const int last = max((int)__popcll(__ballot(lane < cand && first(c0, idx) <= unit)) - 1, 0);
+  SeqOf r;
+  r.b = lo + last;
+  r.tok0 = __builtin_amdgcn_readlane(c0, last);
+  r.S = __builtin_amdgcn_readlane(c1, last) - r.tok0;
+  r.cb = __builtin_amdgcn_readlane(cb, last);
+  return r;
 }
 
 __device__ __forceinline__ float wave_max(float v) {

@@ -21,9 +21,12 @@
 // (the first block of an append that continues a sequence, the last block) write only the
 // addressed slots, element by element where a 16-byte unit is not completely new.
 //
-// The destination blocks of the whole batch are numbered sequence after sequence; the grid
-// covers an upper bound on their number that the host can compute (T/16 + 2 per sequence),
-// and every workgroup finds its (sequence, block) from a prefix sum over the batch.
+// The destination blocks of the whole batch are numbered sequence after sequence, those of
+// sequence b from cu_q[b] / 16 + 2 b: S new tokens touch at most S / 16 + 2 blocks, so the
+// numbers of consecutive sequences do not meet, and a workgroup finds its (sequence, block)
+// with a search over cu_q (find_sequence) where a prefix sum over the batch used to cost two
+// barriers and a trip through LDS in front of everything else (one prompt of 93 tokens: 6.7 ->
+// 5.4 us; the tables of the whole batch also no longer take the LDS of a workgroup).
 // A call that brings at most one token per sequence (the decode step) takes a leaner kernel:
 // one wavefront per (sequence, K/V head), no numbering, no staging.
 #include "common.h"
@@ -31,47 +34,6 @@
 namespace eco {
 
 constexpr int kAppendThreads = 256;
-
-// Exclusive prefix sums over the batch of the number of cache blocks each sequence's new
-// tokens touch: pre[b] = blocks of sequences 0..b-1, pre[B] = all.  The batch description is
-// kept beside them (tok[b] = cu_q[b], tok[B] = T; cbs[b] = ctx_before[b]) so that the
-// workgroup does not go back to global memory for it.  Called by all threads.
-__device__ __forceinline__ void scan_touched_blocks(int* pre, int* tok, int* cbs, int* wsum,
-                                                    const int32_t* __restrict__ cu_q,
-                                                    const int32_t* __restrict__ ctx_before, int B) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int per = (B + kAppendThreads - 1) / kAppendThreads;
-  const int b0 = tid * per;
-  auto touched = [&](int b) {
-    const int S = cu_q[b + 1] - cu_q[b], cb = ctx_before[b];
-    return S > 0 ? ((cb + S - 1) >> 4) - (cb >> 4) + 1 : 0;
-  };
-  int local = 0;
-  for (int i = 0; i < per; ++i)
-    if (b0 + i < B) {
-      local += touched(b0 + i);
-      tok[b0 + i] = cu_q[b0 + i];
-      cbs[b0 + i] = ctx_before[b0 + i];
-    }
-  if (tid == 0) tok[B] = cu_q[B];
-  int x = local;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int y = __shfl_up(x, o);
-    if (lane >= o) x += y;
-  }
-  if (lane == 63) wsum[wave] = x;
-  __syncthreads();
-  int run = x - local;
-  for (int w = 0; w < wave; ++w) run += wsum[w];
-  for (int i = 0; i < per; ++i)
-    if (b0 + i < B) {
-      pre[b0 + i] = run;
-      run += touched(b0 + i);
-    }
-  if (tid == 0) pre[B] = wsum[0] + wsum[1] + wsum[2] + wsum[3];
-  __syncthreads();
-}
 
 template <typename E, int HPW>
 __global__ __launch_bounds__(kAppendThreads) void kv_append_kernel(E* __restrict__ k_cache, E* __restrict__ v_cache,
@@ -83,26 +45,17 @@ __global__ __launch_bounds__(kAppendThreads) void kv_append_kernel(E* __restrict
                                                                     int bt_stride, int B, int Hkv, int D) {
   constexpr int X = Elem<E>::X;
   typedef uint32_t u4 __attribute__((ext_vector_type(4)));
-  // Sized by the launch (append_lds_bytes): three arrays of B + 1 ints, then HPW staged V tiles of
-  // 16 rows of D + X elements (padded rows).  A small batch leaves room for more workgroups per CU.
-  extern __shared__ __attribute__((aligned(16))) int pre[];
-  int* tok = pre + (B + 1);
-  int* cbs = tok + (B + 1);
+  // HPW staged V tiles of 16 rows of D + X elements (padded rows), sized by the launch (append_lds_bytes)
+  extern __shared__ __attribute__((aligned(16))) char staged[];
   const int vrow = D + X;
-  E* vt = reinterpret_cast<E*>(pre + ((3 * (B + 1) + 3) & ~3));
-  __shared__ int wsum[kAppendThreads / 64];
-  scan_touched_blocks(pre, tok, cbs, wsum, cu_q, ctx_before, B);
-  if ((int)blockIdx.x >= pre[B]) return;
-  int lo_b = 0, hi_b = B;
-  while (hi_b - lo_b > 1) {
-    const int mid = (lo_b + hi_b) >> 1;
-    if (pre[mid] <= (int)blockIdx.x) lo_b = mid; else hi_b = mid;
-  }
-  const int b = lo_b, first_unit = pre[b];
-  const int unit = blockIdx.x;  // destination block number within the batch
+  E* vt = reinterpret_cast<E*>(staged);
+  auto first_unit = [](int cu, int b) { return (cu >> 4) + 2 * b; };
+  const SeqOf seq = find_sequence(cu_q, ctx_before, B, blockIdx.x, first_unit);
+  const int b = seq.b, tok0 = seq.tok0, S = seq.S, cb = seq.cb;
+  const int nth = (int)blockIdx.x - first_unit(tok0, b);  // destination block number within the sequence
+  if (S <= 0 || nth > ((cb + S - 1) >> 4) - (cb >> 4)) return;
   const int g0 = blockIdx.y * HPW, tid = threadIdx.x;
-  const int tok0 = tok[b], S = tok[b + 1] - tok0, cb = cbs[b];
-  const int j = (cb >> 4) + (unit - first_unit);      // logical block of the sequence
+  const int j = (cb >> 4) + nth;                            // logical block of the sequence
   const int lo = max(0, cb - (j << 4));               // addressed slots [lo, hi) of this block
   const int hi = min(16, cb + S - (j << 4));
   const int t_slot0 = tok0 + (j << 4) - cb;           // packed token index of slot 0 (may be < tok0)
@@ -182,22 +135,20 @@ __global__ __launch_bounds__(kAppendThreads) void kv_append_one_kernel(E* __rest
                     v_new + (size_t)tok * new_row_stride + g * D, blk, g, p & 15, Hkv, D, lane);
 }
 
-// Dynamic LDS of the tiled kernel: the batch tables, then HPW staged V tiles.
+// Dynamic LDS of the tiled kernel: HPW staged V tiles.
 template <typename E>
-static size_t append_lds_bytes(int B, int D, int hpw) {
-  const size_t tables = (size_t)((3 * (B + 1) + 3) & ~3) * sizeof(int);
-  return tables + (size_t)hpw * 16 * (D + Elem<E>::X) * sizeof(E);
+static size_t append_lds_bytes(int D, int hpw) {
+  return (size_t)hpw * 16 * (D + Elem<E>::X) * sizeof(E);
 }
 
 template <typename E, int HPW>
 static void launch_tiled(const ecoserve_layout& L, void* k_cache, void* v_cache, const void* k_new, const void* v_new,
                          int32_t new_row_stride, const int32_t* cu_q, const int32_t* ctx_before, const int32_t* block_table,
                          int32_t bt_stride, int32_t B, int32_t T, hipStream_t s) {
-  // a sequence with S new tokens touches at most S/16 + 2 blocks (ragged at both ends), and none if S == 0
-  const int64_t max_units = (int64_t)T / 16 + 2 * (int64_t)(B < T ? B : T);
+  const int64_t max_units = (int64_t)T / 16 + 2 * (int64_t)B;  // (the numbering of the kernel, up to sequence B)
   const dim3 grid((unsigned)max_units, (unsigned)(L.num_kv_heads / HPW));
-  // (above 64 KiB - a batch of thousands - the kernel's limit was raised when the context was created)
-  const size_t lds = append_lds_bytes<E>(B, L.head_dim, HPW);
+  // (above 64 KiB - fp32 with large heads - the kernel's limit was raised when the context was created)
+  const size_t lds = append_lds_bytes<E>(L.head_dim, HPW);
   hipLaunchKernelGGL((kv_append_kernel<E, HPW>), grid, dim3(kAppendThreads), lds, s, (E*)k_cache, (E*)v_cache,
                      (const E*)k_new, (const E*)v_new, new_row_stride, cu_q, ctx_before, block_table, bt_stride, B,
                      L.num_kv_heads, L.head_dim);
@@ -225,7 +176,7 @@ static void launch_typed(const ecoserve_layout& L, void* k_cache, void* v_cache,
 
 template <typename E, int HPW>
 static hipError_t raise_lds_limit(const ecoserve_ctx* ctx) {
-  const size_t lds = append_lds_bytes<E>(ctx->max_batch, ctx->lay.head_dim, HPW);
+  const size_t lds = append_lds_bytes<E>(ctx->lay.head_dim, HPW);
   if (lds <= 60 * 1024) return hipSuccess;
   return hipFuncSetAttribute(reinterpret_cast<const void*>(&kv_append_kernel<E, HPW>),
                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
