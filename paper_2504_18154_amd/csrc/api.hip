@@ -104,9 +104,11 @@ int ensure_partial_states(ecoserve_ctx* c) {
 int alloc_fixed_workspace(ecoserve_ctx* c) {
   const size_t meta_bytes = ((size_t)c->max_batch + 19) * sizeof(int32_t);
   // a prefill batch cannot bring more new tokens than the pool holds
+  // (T / 128 + min(B, T) is what a call is held to; it has at most G times as many tiles)
   c->plan_tiles = prefill_plan_tiles(c->max_batch, (int32_t)std::min<int64_t>(
-                                                        (int64_t)c->lay.num_blocks * kBlockSize, 0x7fffffffLL));
-  const size_t plan_bytes = ((size_t)kPlanHeaderInts + (size_t)c->plan_tiles * kRecInts) * sizeof(int32_t);
+                                                        (int64_t)c->lay.num_blocks * kBlockSize, 0x7fffffffLL), 1);
+  const size_t plan_records = (size_t)(c->plan_tiles + 1) * (c->lay.num_q_heads / c->lay.num_kv_heads);
+  const size_t plan_bytes = ((size_t)kPlanHeaderInts + plan_records * kRecInts) * sizeof(int32_t);
   if (hipMalloc(&c->ws_meta, meta_bytes) != hipSuccess || hipMalloc(&c->ws_plan, plan_bytes) != hipSuccess) {
     (void)hipGetLastError();
     return ECOSERVE_ENOMEM;
@@ -116,12 +118,7 @@ int alloc_fixed_workspace(ecoserve_ctx* c) {
     (void)hipGetLastError();
     return ECOSERVE_EHIP;
   }
-  const size_t count_bytes = (size_t)c->max_batch * c->lay.num_kv_heads * sizeof(int32_t);
-  if (hipMalloc(&c->ws_count, count_bytes) != hipSuccess || hipMemset(c->ws_count, 0, count_bytes) != hipSuccess) {
-    (void)hipGetLastError();
-    return ECOSERVE_ENOMEM;
-  }
-  c->ws_bytes += meta_bytes + plan_bytes + count_bytes;
+  c->ws_bytes += meta_bytes + plan_bytes;
   return ECOSERVE_OK;
 }
 
@@ -230,8 +227,10 @@ int ecoserve_create(ecoserve_ctx** out, int device, const ecoserve_layout* layou
   if (st == ECOSERVE_OK && prepare_kv_append(c) != hipSuccess) st = ECOSERVE_EHIP;
   if (st != ECOSERVE_OK) { (void)ecoserve_destroy(c); return st; }
   {
-    // per-XCD shares start equal; samples of 4 wavefronts per CU follow, then each chunk's report to the merge
-    const size_t share_bytes = (24 + 6 * (size_t)c->num_cu * kDecodeWgsPerCu * 4) * sizeof(int32_t);
+    // per-XCD shares start equal; samples of 4 wavefronts per CU follow, then each chunk's report to the merge, then
+    // the small-batch kernel's counters (one allocation: creating a context is a few of them and their clearing)
+    const size_t share_words = 24 + 6 * (size_t)c->num_cu * kDecodeWgsPerCu * 4;
+    const size_t share_bytes = (share_words + (size_t)c->max_batch * c->lay.num_kv_heads) * sizeof(int32_t);
     const float ones[16] = {1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f};
     if (hipMalloc(&c->ws_share, share_bytes) != hipSuccess || hipMemset(c->ws_share, 0, share_bytes) != hipSuccess ||
         hipMemcpy(c->ws_share, ones, sizeof(ones), hipMemcpyHostToDevice) != hipSuccess) {
@@ -239,6 +238,7 @@ int ecoserve_create(ecoserve_ctx** out, int device, const ecoserve_layout* layou
       (void)ecoserve_destroy(c);
       return ECOSERVE_ENOMEM;
     }
+    c->ws_count = reinterpret_cast<uint32_t*>(c->ws_share + share_words);
     c->ws_bytes += share_bytes;
   }
   *out = c;
@@ -254,7 +254,6 @@ int ecoserve_destroy(ecoserve_ctx* c) {
   if (c->ws_ml) (void)hipFree(c->ws_ml);
   if (c->ws_meta) (void)hipFree(c->ws_meta);
   if (c->ws_plan) (void)hipFree(c->ws_plan);
-  if (c->ws_count) (void)hipFree(c->ws_count);
   if (c->ws_share) (void)hipFree(c->ws_share);
   for (int i = 0; i < 3; ++i)
     for (EventPair& e : c->ev[i]) { (void)hipEventDestroy(e.start); (void)hipEventDestroy(e.stop); }
@@ -376,7 +375,7 @@ int ecoserve_attn_prefill_strided(ecoserve_ctx* c, const void* q, int64_t q_row_
   if (B > c->max_batch || bt_stride <= 0 || max_q_len > T || max_q_len == 0) return ECOSERVE_EINVAL;
   if (!aligned16(q) || !aligned16(k_cache) || !aligned16(v_cache) || !aligned16(out)) return ECOSERVE_EINVAL;
   if (lse && (reinterpret_cast<uintptr_t>(lse) & 3u)) return ECOSERVE_EINVAL;
-  if (prefill_plan_tiles(B, T) > c->plan_tiles) return ECOSERVE_EINVAL;  // more new tokens than the pool holds
+  if (prefill_plan_tiles(B, T, 1) > c->plan_tiles) return ECOSERVE_EINVAL;  // more new tokens than the pool holds
   DeviceGuard guard(c->device);
   if (!guard.ok) return ECOSERVE_EHIP;
   hipStream_t s = (hipStream_t)stream;

@@ -7,8 +7,13 @@
 // ctx_before[b] + i and sees keys 0..that position (a cached prefix is handled by the
 // same loop).
 //
-// Work decomposition: one work item = 128 query rows (a query tile) of one query head,
-// computed by one workgroup (4 wavefronts, 32 rows each).  A small plan kernel lists the
+// Work decomposition: the rows of one (sequence, K/V head) are (position, query head of the group) pairs, position
+// after position; one work item = 128 such rows (a query tile), computed by one workgroup (4 wavefronts, 32 rows
+// each).  All rows of a tile share the staged K/V, and since they span few positions (128 / G of them for G query heads
+// per K/V head) the causal bound cuts close: a tile of 128 positions of one head spends two of its key steps at the
+// diagonal, half of them for wavefronts or keys that are masked, and a prompt of S < 128 positions fills S of a tile's
+// 128 rows, where here it fills S G rows of its tiles (measured: prefill_plan_kernel).
+// A small plan kernel lists the
 // batch's query tiles, heaviest (most key steps) first; the attention kernel is persistent:
 // two workgroups per CU (one's softmax VALU work runs under the other's matrix work), each
 // taking items from the list until it is empty.  While an item's last key step is being
@@ -19,9 +24,6 @@
 // first in the K/V head, and a workgroup serves the items whose index is congruent to its
 // XCD (workgroup ids are dealt round-robin to the 8 XCDs): with 8 K/V heads each XCD's L2
 // holds one head's K/V.
-// A prompt of at most 128 / G new tokens (G = query heads per K/V head) gets a packed tile
-// instead: its rows are (query head of the group, position), so one item serves all G heads
-// over the same K/V (see the plan kernel).
 //
 // Per 64-key step the four 16-token cache blocks of K and of V go straight from global
 // memory into LDS (global_load ... lds, 16 bytes per lane, double buffered, one barrier per
@@ -55,7 +57,7 @@
 
 namespace eco {
 
-constexpr int kTQ = kPrefillTileRows;          // query rows per work item
+constexpr int kTQ = kPrefillTileRows;          // rows per work item
 constexpr int kTK = 64;                        // keys per step
 constexpr int kKTileBytes = 16 * kTK * 16;     // [16 units][64 keys][16 B]
 constexpr int kVOctStride = 128 * 16 + 64;     // one 8-key octet: [128 d][16 B] + pad
@@ -212,31 +214,34 @@ __device__ __forceinline__ void exp_tile(const f32x16& s, bf16x8 (&pf)[2], float
 
 // ---- plan: the query tiles of a batch, heaviest first ------------------------------------------
 //
-// Plan layout (int32): [0] number of query tiles, [1] positions per packed tile and their reciprocal (0: no tile can be packed), [2] number of ordinary tiles (the packed ones follow them),
+// Plan layout (int32): [0] number of query tiles,
 // [kPlanCounter0 + kPlanCounterStride * (kQueues * p
 // + i)] ticket counter of work queue i in counter set p (one cache line each; launches alternate
 // between the two sets and each launch leaves the other set ready for the next, so a tile list can
 // serve many launches without being rebuilt), then from kPlanHeaderInts one record of kRecInts per
 // query tile:
 //   0 sequence, 1 tile inside the sequence, 2 first packed token of the sequence, 3 S,
-//   4 ctx_before, 5 number of 64-key steps, 6 the tile's first query row, 7 the row behind its last,
+//   4 ctx_before, 5 number of 64-key steps, 6 the tile's first row (of the S G of its sequence and K/V head), 7 the row
+//   behind its last,
 //   8..19 physical ids of the sequence's first 12 blocks
 // (clamped to its last block), i.e. everything a workgroup needs to start on the tile with one
 // load.
-// Where a prompt's tiles begin: a prompt of S = 128 n + r new tokens (0 < r < 128) has one ragged tile of r
-// rows.  As the last tile it would cost as many key steps as a full one (its rows see the whole prompt);
-// as the first tile it costs one or two.  Moving it to the front shifts the other tiles by r rows, which
-// costs each of them ceil((ctx_before + r) / 64) - ceil(ctx_before / 64) steps more: without a cached
-// prefix that is at most as many as the two steps saved per tile, and fewer when r <= 64.  tile_rows()
-// takes whichever alignment has fewer key steps in total.  Records are sorted by the number of key steps, largest first, with a counting sort
+// Where a prompt's tiles begin: S G = 128 n + r rows (0 < r < 128) have one ragged tile of r rows.  As the last tile it
+// would cost as many key steps as a full one (its rows see the whole prompt); as the first it costs those of the first
+// r / G positions.  Moving it to the front shifts the other tiles by r / G positions, less than a key step, so at most
+// r / (64 G) of them gain a step.  Records are sorted by the number of key steps, largest first, with a counting sort
 // (tiles with kPlanBins - 1 or more steps share a class; the order inside a class is arbitrary).
+// Rows over the group against tiles of 128 positions of one head (kernel us, 8 K/V heads; before / now): 64 query heads,
+// 256 x 20 tokens 177 / 64, 256 x 40 194 / 120, 128 x 100 behind 100 cached 242 / 163, 4 x 512 36.0 / 33.4; 40 query
+// heads, 64 x 50 tokens 32.9 / 23.2, 16 x 93 20.6 / 16.2; the benchmark's 16 prompts of 128..4096 tokens 4% less, its
+// 8 x 8192 tokens the same.  (It also replaces a second kernel that packed the G heads of prompts up to 128 / G tokens.)
 __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(const int32_t* __restrict__ cu_q,
                                                                     const int32_t* __restrict__ ctx_before,
                                                                     const int32_t* __restrict__ block_table,
                                                                     int bt_stride, int B, int n_main_wgs,
-                                                                    int max_tiles, int G, int32_t* __restrict__ plan) {
+                                                                    int max_tiles, int G, Divisor div_g, int32_t* __restrict__ plan) {
   __shared__ int pre[kMaxBatch + 1];
-  __shared__ int bins[2 * kPlanBins];  // weight classes of the ordinary tiles, then of the packed ones
+  __shared__ int bins[kPlanBins];  // weight classes
   __shared__ int wsum[kPlanThreads / 64];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   // exclusive prefix of one value per thread over the workgroup; `total` receives the sum
@@ -258,29 +263,18 @@ __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(const int32_
     __syncthreads();
     return run;
   };
-  auto tiles_of = [&](int b) { return (cu_q[b + 1] - cu_q[b] + kTQ - 1) / kTQ; };
-  // rows [first, last) of tile qt of a prompt of S new tokens behind cb cached ones
-  auto tile_rows = [&](int S, long long cb, int qt, int& first, int& last) {
-    const int r = S % kTQ;
-    const long long up = (cb + r + kTK - 1) / kTK - (cb + kTK - 1) / kTK;  // steps each full tile gains if shifted by r
-    if (r > 0 && up < 2) {  // ragged tile first
-      first = qt == 0 ? 0 : r + (qt - 1) * kTQ;
-      last = qt == 0 ? r : first + kTQ;
-    } else {
-      first = qt * kTQ;
-      last = min(S, first + kTQ);
-    }
+  auto tiles_of = [&](int b) { return ((cu_q[b + 1] - cu_q[b]) * G + kTQ - 1) / kTQ; };
+  // rows [first, last) of tile qt of a prompt of S new tokens
+  auto tile_rows = [&](int S, int qt, int& first, int& last) {
+    const int r = S * G % kTQ;
+    first = r > 0 ? (qt == 0 ? 0 : r + (qt - 1) * kTQ) : qt * kTQ;
+    last = r > 0 && qt == 0 ? r : first + kTQ;
   };
 
   const int per = (B + kPlanThreads - 1) / kPlanThreads, b0 = tid * per;
   int local = 0;
   for (int i = 0; i < per; ++i)
     if (b0 + i < B) local += tiles_of(b0 + i);
-  // Packed tiles: a prompt with at most P = kTQ / G new tokens fits a tile G times over, so its tile holds
-  // all G query heads of a K/V head (row = head * P + position) and one item does what G items would, over
-  // the same staged K/V: hundreds of 20-token prompts are otherwise one item per (prompt, query head) with a
-  // sixth of its rows in use.  Packed tiles are listed behind the ordinary ones.
-  const int P = G > 1 ? kTQ / G : 0;
   int n_tiles_all;
   int run = block_scan(local, n_tiles_all);
   // never more records than the host sized the launch (and the plan buffer) for, whatever cu_q says
@@ -291,7 +285,7 @@ __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(const int32_
       run += tiles_of(b0 + i);
     }
   if (tid == 0) pre[B] = n_tiles_all;
-  for (int i = tid; i < 2 * kPlanBins; i += kPlanThreads) bins[i] = 0;
+  for (int i = tid; i < kPlanBins; i += kPlanThreads) bins[i] = 0;
   __syncthreads();
 
   // tile i of the batch (sequence after sequence) -> sequence, tile, key steps, weight class
@@ -305,11 +299,10 @@ __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(const int32_
     qt = i - pre[b];
     const int S = cu_q[b + 1] - cu_q[b];
     int first, last;
-    tile_rows(S, ctx_before[b], qt, first, last);
-    const long long kv_end = (long long)ctx_before[b] + last;
+    tile_rows(S, qt, first, last);
+    const long long kv_end = (long long)ctx_before[b] + fast_div(last - 1, div_g) + 1;
     steps = (int)((kv_end + kTK - 1) / kTK);
-    const int cls = kPlanBins - 1 - min(steps, kPlanBins - 1);  // class 0 = heaviest
-    return S <= P ? kPlanBins + cls : cls;
+    return kPlanBins - 1 - min(steps, kPlanBins - 1);  // class 0 = heaviest
   };
   for (int i = tid; i < n_tiles_all; i += kPlanThreads) {
     int b, qt, steps;
@@ -317,7 +310,7 @@ __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(const int32_
   }
   __syncthreads();
   {
-    constexpr int kPer = 2 * kPlanBins / kPlanThreads;
+    constexpr int kPer = kPlanBins / kPlanThreads;
     int cnt[kPer], sum = 0;
 #pragma unroll
     for (int i = 0; i < kPer; ++i) {
@@ -333,11 +326,6 @@ __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(const int32_
     }
   }
   __syncthreads();
-  if (tid == 0) {
-    plan[1] = P ? (P | ((65536 / P + 1) << 8)) : 0;
-    plan[2] = bins[kPlanBins];  // number of ordinary tiles = where the packed ones begin
-  }
-  __syncthreads();
   for (int i = tid; i < n_tiles_all; i += kPlanThreads) {
     int b, qt, steps;
     const int cls = locate(i, b, qt, steps);
@@ -350,7 +338,7 @@ __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(const int32_
     rec[3] = S;
     rec[4] = cb;
     rec[5] = steps;
-    tile_rows(S, cb, qt, rec[6], rec[7]);
+    tile_rows(S, qt, rec[6], rec[7]);
     for (int j = 0; j < 12; ++j) rec[8 + j] = block_table[(size_t)b * bt_stride + min(j, nblk_total - 1)];
   }
   if (tid == 0) plan[0] = n_tiles_all;
@@ -359,19 +347,16 @@ __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(const int32_
     plan[kPlanCounter0 + kPlanCounterStride * tid] = 2 * ((n_main_wgs - tid % kQueues + kQueues - 1) / kQueues);
 }
 
-// Wave-uniform description of one work item (a query tile of one query head).
-constexpr int kPackedItem = 1 << 30;  // flag in the query head number handed to describe(): a packed tile
+// Wave-uniform description of one work item (a query tile of one K/V head).
 struct Item {
-  int tok0, S, cb, q0, q_end, g, h, n_tiles;  // q0, q_end: the tile's query rows [q0, q_end) of the prompt's S
-  bool pk;  // packed tile: rows are (query head h + row / P, position row % P)
+  int tok0, S, cb, q0, q_end, g, n_tiles;  // q0, q_end: the tile's rows [q0, q_end) of the S G of its sequence and head
   const int32_t* bt_row;
   __device__ __forceinline__ int L_total() const { return cb + S; }
   __device__ __forceinline__ int nblk_total() const { return (cb + S + 15) >> 4; }
 };
 
-// `rec` holds field l of the tile's plan record in lane l; g, h: the item's K/V and query head.
-__device__ __forceinline__ Item describe(int rec, int g, int h, const int32_t* __restrict__ block_table,
-                                         int bt_stride) {
+// `rec` holds field l of the tile's plan record in lane l; g: the item's K/V head.
+__device__ __forceinline__ Item describe(int rec, int g, const int32_t* __restrict__ block_table, int bt_stride) {
   Item t;
   const int b = __builtin_amdgcn_readlane(rec, 0);
   t.tok0 = __builtin_amdgcn_readlane(rec, 2);
@@ -379,19 +364,16 @@ __device__ __forceinline__ Item describe(int rec, int g, int h, const int32_t* _
   t.cb = __builtin_amdgcn_readlane(rec, 4);
   t.n_tiles = __builtin_amdgcn_readlane(rec, 5);
   t.g = g;
-  t.h = h & (kPackedItem - 1);
-  t.pk = (h & kPackedItem) != 0;
   t.q0 = __builtin_amdgcn_readlane(rec, 6);
   t.q_end = __builtin_amdgcn_readlane(rec, 7);
   t.bt_row = block_table + (size_t)b * bt_stride;
   return t;
 }
 
-template <bool kMayPack>
 __global__ __launch_bounds__(256, 2) void prefill_mfma_kernel(
     const uint16_t* __restrict__ q, int q_row_stride, const char* __restrict__ k_cache,
     const char* __restrict__ v_cache, const int32_t* __restrict__ block_table, int bt_stride,
-    uint16_t* __restrict__ out, float* __restrict__ lse, int32_t* __restrict__ plan, int parity, int Hq, int Hkv, int G, Divisor div_heads, Divisor div_hkv,
+    uint16_t* __restrict__ out, float* __restrict__ lse, int32_t* __restrict__ plan, int parity, int Hq, int Hkv, int G, Divisor div_g, Divisor div_hkv,
     float scale_log2e) {
   __shared__ __attribute__((aligned(16))) char smem[2 * kKTileBytes + 2 * kVTileBytes + 16 + 64];
   char* const kbufs = smem;
@@ -407,15 +389,7 @@ __global__ __launch_bounds__(256, 2) void prefill_mfma_kernel(
                              // load: an outstanding scalar load would force full waits on every LDS read)
   const float c = scale_log2e;
   const size_t blk_stride = (size_t)Hkv * 4096;
-  // Packed tiles: P positions per tile (row = head * P + position) in the low byte, above it p_inv with
-  // row / P == (row * p_inv) >> 16 for rows 0..127.  kMayPack false: every tile is taken as an ordinary one
-  // and none of the packing code is compiled in (this kernel has no register to spare for it; the launcher
-  // picks that variant for batches of long prompts); true: the tiles the plan lists as packed are.
-  const int packing = kMayPack ? plan[1] : 0;
-  const int heads = G * Hkv;  // items of an ordinary tile
-  const int n_ord_tiles = packing ? plan[2] : plan[0];
-  const int n_ordinary = n_ord_tiles * heads;  // items of the ordinary tiles; one per K/V head of the packed ones follow
-  const int n_flat = n_ordinary + (plan[0] - n_ord_tiles) * Hkv;
+  const int n_flat = plan[0] * Hkv;  // items
   const int32_t* const recs = plan + kPlanHeaderInts;
   // Work items are dealt to kQueues queues (item f belongs to queue f % kQueues) and workgroup w
   // serves queue w % kQueues.  kQueues is a multiple of 8: workgroup ids are dealt round-robin to
@@ -464,21 +438,11 @@ __global__ __launch_bounds__(256, 2) void prefill_mfma_kernel(
     prev_items = plan[kPlanMeta0 + (parity ^ 1)];
     prev_grid = plan[kPlanMeta0 + 2 + (parity ^ 1)];
   }
-  // item f is query head f % (G Hkv) of tile f / (G Hkv), the K/V head varying fastest
-  int tile_of_f, g_of_f, h_of_f;
+  // item f is K/V head f % Hkv of tile f / Hkv
+  int tile_of_f, g_of_f;
   auto split = [&](int f) {
-    if (kMayPack && f >= n_ordinary) {  // a packed tile: one item per K/V head, its G query heads share it
-      const int fp = f - n_ordinary, t = fast_div(fp, div_hkv);
-      tile_of_f = n_ord_tiles + t;
-      g_of_f = fp - t * Hkv;
-      h_of_f = (g_of_f * G) | kPackedItem;
-      return;
-    }
-    tile_of_f = fast_div(f, div_heads);
-    const int hp = f - tile_of_f * heads;
-    const int hg = fast_div(hp, div_hkv);
-    g_of_f = hp - hg * Hkv;
-    h_of_f = g_of_f * G + hg;
+    tile_of_f = fast_div(f, div_hkv);
+    g_of_f = f - tile_of_f * Hkv;
   };
   auto load_rec = [&](int tile) { return recs[(size_t)tile * kRecInts + min(lane, kRecInts - 1)]; };
 
@@ -502,37 +466,30 @@ __global__ __launch_bounds__(256, 2) void prefill_mfma_kernel(
   split(f_cur);
   int rec_next = load_rec(tile_of_f);  // record of the next item (here: of the first)
   int pend = 0;                        // (thread 0) ticket on its way
-  Item cur = describe(rec_next, g_of_f, h_of_f, block_table, bt_stride);
-  int g_next = 0, h_next = 0;                    // heads of the next item
+  Item cur = describe(rec_next, g_of_f, block_table, bt_stride);
+  int g_next = 0;                      // K/V head of the next item
 
   // per-lane view of the current item
   int pos, w_pmin, n_w;
   size_t head_off;
-  // tile row -> (query row inside the sequence, query head inside the group, row in use)
+  // this lane's row -> (position inside the prompt, query head inside the group, row in use)
   auto map_row = [&](const Item& t, int& r, int& hq, bool& ok) {
-    const int rr = wave * 32 + col;
-    if (kMayPack && t.pk) {
-      hq = (rr * (packing >> 8)) >> 16;
-      r = rr - hq * (packing & 255);
-      ok = hq < G && r < t.S;
-    } else {
-      hq = 0;
-      r = t.q0 + rr;
-      ok = r < t.q_end;
-    }
+    const int rr = t.q0 + wave * 32 + col;
+    r = fast_div(rr, div_g);
+    hq = rr - r * G;
+    ok = rr < t.q_end;
   };
   auto enter = [&](const Item& t) {
     int row, hsel;
     bool row_valid;
     map_row(t, row, hsel, row_valid);
     pos = t.cb + row;                                      // absolute position = causal bound
-    // smallest / largest bound in this wavefront (packed: of the tile, every wavefront sees every position)
-    w_pmin = kMayPack && t.pk ? t.cb : t.cb + t.q0 + wave * 32;
-    const int w_pmax = kMayPack && t.pk ? t.cb + t.S - 1 : t.cb + min(t.q_end - 1, t.q0 + wave * 32 + 31);
+    // smallest / largest bound in this wavefront
+    w_pmin = t.cb + fast_div(t.q0 + wave * 32, div_g);
+    const int w_pmax = t.cb + fast_div(min(t.q_end - 1, t.q0 + wave * 32 + 31), div_g);
     // steps not wholly above this wavefront's diagonal; a wavefront none of whose rows exists (the ragged
-    // last tile of a prompt) has nothing to compute at all
-    const bool any_row = (kMayPack && t.pk) || t.q0 + wave * 32 < t.q_end;
-    n_w = any_row ? min(t.n_tiles, w_pmax / kTK + 1) : 0;
+    // tile of a prompt) has nothing to compute at all
+    n_w = t.q0 + wave * 32 < t.q_end ? min(t.n_tiles, w_pmax / kTK + 1) : 0;
     head_off = (size_t)t.g * 4096;
   };
   enter(cur);
@@ -543,7 +500,7 @@ __global__ __launch_bounds__(256, 2) void prefill_mfma_kernel(
     int r, hq;
     bool ok;
     map_row(t, r, hq, ok);
-    const uint16_t* qrow = q + (size_t)(t.tok0 + r) * q_row_stride + (t.h + hq) * 128 + half * 8;
+    const uint16_t* qrow = q + (size_t)(t.tok0 + r) * q_row_stride + (t.g * G + hq) * 128 + half * 8;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       bf16x8 z = {0, 0, 0, 0, 0, 0, 0, 0};
@@ -662,7 +619,7 @@ __global__ __launch_bounds__(256, 2) void prefill_mfma_kernel(
         next_ids();
       }
     } else if (f_next >= 0) {
-      const Item nxt = describe(rec_next, g_next, h_next, block_table, bt_stride);
+      const Item nxt = describe(rec_next, g_next, block_table, bt_stride);
       stage_first(nxt, rec_next, pj ^ 1);
       load_q(nxt);  // the current item's scores are all computed: its query rows make room
     }
@@ -787,7 +744,6 @@ __global__ __launch_bounds__(256, 2) void prefill_mfma_kernel(
     if (f_next >= 0) {
       split(f_next);
       g_next = g_of_f;
-      h_next = h_of_f;
       rec_next = load_rec(tile_of_f);
       if (tid == 0) pend = atomicAdd(counter, 1);
     }
@@ -837,7 +793,7 @@ __global__ __launch_bounds__(256, 2) void prefill_mfma_kernel(
       int row, hsel;  // (worked out again rather than kept in registers through the item)
       bool row_valid;
       map_row(cur, row, hsel, row_valid);
-      uint16_t* orow = out + ((size_t)(cur.tok0 + row) * Hq + cur.h + hsel) * 128 + half * 8;
+      uint16_t* orow = out + ((size_t)(cur.tok0 + row) * Hq + cur.g * G + hsel) * 128 + half * 8;
       auto pack = [&](float a, float b) {
         const bf16x2 v = {(__bf16)(a * inv), (__bf16)(b * inv)};
         return __builtin_bit_cast(uint32_t, v);
@@ -863,13 +819,13 @@ __global__ __launch_bounds__(256, 2) void prefill_mfma_kernel(
       int row, hsel;
       bool row_valid;
       map_row(cur, row, hsel, row_valid);
-      if (row_valid) lse[(size_t)(cur.tok0 + row) * Hq + cur.h + hsel] = (m * c + log2f(l)) * kLn2;
+      if (row_valid) lse[(size_t)(cur.tok0 + row) * Hq + cur.g * G + hsel] = (m * c + log2f(l)) * kLn2;
     }
     if (f_next < 0) break;
 
     // next item: its first steps were staged by the last step above, into the other parity
     par = (par + cur.n_tiles) & 1;
-    cur = describe(rec_next, g_next, h_next, block_table, bt_stride);
+    cur = describe(rec_next, g_next, block_table, bt_stride);
     f_next = __builtin_amdgcn_readfirstlane(slot[0]);
     enter(cur);
     next_idk = __shfl(rec_next, 16 + kq);
@@ -887,8 +843,7 @@ __global__ __launch_bounds__(256, 2) void prefill_mfma_kernel(
 // Workgroups of the attention launch: the persistent grid, or fewer if the batch cannot hold that
 // many items (0: nothing to do, -1: too many items to number).
 int32_t prefill_mfma_grid(const AttnArgs& a, int32_t T, int32_t n_persistent_wgs) {
-  // sum over sequences of ceil(S_b / kTQ) <= T / kTQ + (number of non-empty sequences)
-  const int64_t n_items = prefill_plan_tiles(a.B, T) * a.Hq;
+  const int64_t n_items = prefill_plan_tiles(a.B, T, a.Hq / a.Hkv) * a.Hkv;
   if (n_items <= 0) return 0;
   if (n_items > 0x7fffffffLL - (1 << 20)) return -1;
   return (int32_t)(n_items < n_persistent_wgs ? n_items : n_persistent_wgs);
@@ -898,26 +853,17 @@ hipError_t launch_prefill_mfma(const AttnArgs& a, const int32_t* cu_q, const int
                                int32_t max_q_len, int32_t* ws_plan, int32_t n_persistent_wgs, bool make_plan,
                                int parity, hipStream_t s) {
   const int G = a.Hq / a.Hkv;
-  const int64_t max_tiles = prefill_plan_tiles(a.B, T);
+  const int64_t max_tiles = prefill_plan_tiles(a.B, T, G);
   const int32_t n_wg = prefill_mfma_grid(a, T, n_persistent_wgs);
   if (n_wg == 0) return hipSuccess;
   if (n_wg < 0) return hipErrorInvalidValue;
   if (make_plan)
     hipLaunchKernelGGL(prefill_plan_kernel, dim3(1), dim3(kPlanThreads), 0, s, cu_q, ctx_before, a.block_table,
-                       a.bt_stride, a.B, (int)n_wg, (int)max_tiles, G, ws_plan);
-  auto launch = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, dim3((unsigned)n_wg), dim3(256), 0, s, (const uint16_t*)a.q, a.q_row_stride,
-                       (const char*)a.k_cache, (const char*)a.v_cache, a.block_table, a.bt_stride, (uint16_t*)a.out,
-                       a.lse, ws_plan, parity, a.Hq, a.Hkv, G, make_divisor((uint32_t)(G * a.Hkv)),
-                       make_divisor((uint32_t)a.Hkv), a.scale_log2e);
-  };
-  // The variant that can pack short prompts' tiles for batches that may hold many of them (few new tokens
-  // per sequence on average); which tiles are packed is decided by the tile list, from the lengths themselves.
+                       a.bt_stride, a.B, (int)n_wg, (int)max_tiles, G, make_divisor((uint32_t)G), ws_plan);
   (void)max_q_len;
-  if (G > 1 && (int64_t)T <= (int64_t)a.B * 2 * (kTQ / G))
-    launch(prefill_mfma_kernel<true>);
-  else
-    launch(prefill_mfma_kernel<false>);
+  hipLaunchKernelGGL(prefill_mfma_kernel, dim3((unsigned)n_wg), dim3(256), 0, s, (const uint16_t*)a.q, a.q_row_stride,
+                     (const char*)a.k_cache, (const char*)a.v_cache, a.block_table, a.bt_stride, (uint16_t*)a.out,
+                     a.lse, ws_plan, parity, a.Hq, a.Hkv, G, make_divisor((uint32_t)G), make_divisor((uint32_t)a.Hkv), a.scale_log2e);
   return hipGetLastError();
 }
 

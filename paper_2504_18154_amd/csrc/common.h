@@ -16,7 +16,7 @@ constexpr int kMinSplitTokens = 64;   // smallest decode split
 constexpr int kMaxSplitTokens = 4096; // largest forced decode split
 constexpr int kDecodeWgsPerCu = 1;    // persistent decode grid: workgroups per CU (one wavefront per SIMD)
 constexpr int kMaxBatch = 4096;       // largest max_batch a context accepts (batch prefix sums live in LDS)
-constexpr int kPrefillTileRows = 128; // query rows of one prefill work item
+constexpr int kPrefillTileRows = 128; // rows ((position, query head) pairs) of one prefill work item
 constexpr int kPrefillWgsPerCu = 2;   // persistent prefill grid: workgroups per CU
 constexpr int kPlanMaxQueues = 8;     // prefill plan: most work queues
 constexpr int kPlanCounter0 = 32;     // prefill plan: first queue counter; each counter has a cache line of its own
@@ -49,10 +49,10 @@ inline Divisor make_divisor(uint32_t d) {
   return v;
 }
 
-// Upper bound, computable on the host, on the number of query tiles of a prefill batch:
-// sum over sequences of ceil(S_b / 128) <= T / 128 + (number of non-empty sequences).
-inline int64_t prefill_plan_tiles(int32_t B, int32_t T) {
-  return (int64_t)T / kPrefillTileRows + (B < T ? B : T);
+// Upper bound, computable on the host, on the number of query tiles of a prefill batch: a sequence of S new tokens has
+// ceil(S G / 128) of them, G rows per token and tiles of 128 rows.
+inline int64_t prefill_plan_tiles(int32_t B, int32_t T, int32_t G) {
+  return (int64_t)T * G / kPrefillTileRows + (B < T ? B : T);
 }
 
 // Makes `dev` the calling thread's current device for a scope, and puts the previous one back.
@@ -97,7 +97,7 @@ struct ecoserve_ctx {
   uint32_t* ws_count;          // [max_batch][Hkv], zero between launches: slices of a (sequence, K/V head) that are done
   int32_t ws_splits;
   int32_t* ws_plan;            // prefill plan: header and one record per query tile of the last prefill launch
-  int64_t plan_tiles;          // records ws_plan has room for
+  int64_t plan_tiles;          // largest T / 128 + min(B, T) a prefill call may have; ws_plan has room for G records each
   int plan_parity;             // which of the plan's two sets of queue counters the next prefill launch takes
   struct {                     // the batch the tile list in ws_plan was made for (valid = false: none)
     bool valid;
@@ -184,7 +184,7 @@ hipError_t launch_decode_mfma_merge(const AttnArgs& a, const int32_t* ctx_len, c
                                     const int32_t* ws_wave, const int32_t* ws_cut, int32_t n_waves, hipStream_t s);
 
 // attn_prefill_mfma.hip: bf16, D = 128
-// (ws_plan must hold kPlanHeaderInts + prefill_plan_tiles(B, T) * kRecInts int32; make_plan false: the tile list
+// (ws_plan must hold kPlanHeaderInts + prefill_plan_tiles(B, T, G) * kRecInts int32; make_plan false: the tile list
 // of an earlier launch for the same batch and grid is still in ws_plan; parity alternates from launch to launch)
 int32_t prefill_mfma_grid(const AttnArgs& a, int32_t T, int32_t n_persistent_wgs);
 hipError_t launch_prefill_mfma(const AttnArgs& a, const int32_t* cu_q, const int32_t* ctx_before, int32_t T,
