@@ -21,9 +21,9 @@
 // length -> block ids -> blocks, and the walk of the blocks.  Hence decode takes contexts up to 1024 tokens in one
 // launch, eight wavefronts per (sequence, K/V head) and the step's append inside (one launch instead of three).
 // Measured beside the plain kernels (one wavefront per query row, a scalar product per lane): a prompt batch of 4 x
-// 50..600 tokens and 8 decode steps, bf16, head size 64, 32/8 heads: 399 -> 108 us (prefill kernel 243 -> 13.5 us, a
-// decode step's kernels 21.9 -> 5.6 us); 4 x 37..700 tokens in fp32, 4/2 heads: 196 -> 108 us (55 -> 30 us, 19.1 -> 7.5
-// us); both are now bound by the host's calls.
+// 50..600 tokens and 8 decode steps, bf16, head size 64, 32/8 heads: 399 -> 60 us (prefill kernel 243 -> 13 us, a
+// decode step's kernels 21.9 -> 5.6 us); 4 x 37..700 tokens in fp32, 4/2 heads: 197 -> 72 us (55 -> 13 us, 19.1 -> 7 us).
+#include <algorithm>
 #include <type_traits>
 
 #include "common.h"
@@ -133,6 +133,11 @@ struct Block {
     }
   }
 };
+
+__device__ __forceinline__ void store4(float* p, const f32x4& v) { *reinterpret_cast<f32x4*>(p) = v; }
+__device__ __forceinline__ void store4(uint16_t* p, const f32x4& v) {
+  *reinterpret_cast<u32x2*>(p) = u32x2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
+}
 
 // Online softmax of one row (a column of the products; its keys are spread over the four 16-lane groups).
 // `m`: exponent offset, -inf until the row has seen a key; `l`: this lane's share of the sum of weights.  The
@@ -435,28 +440,36 @@ __global__ __launch_bounds__(W * 64) void decode_any_kernel(
 
 // Prefill.  The rows of one (sequence, K/V head) are (position, query head of the group) pairs, position-major:
 // row r = position r / G, head r % G, so the 16 columns of a product cover few positions and the causal bound cuts
-// close.  A workgroup takes 4 x 16 NC consecutive rows, a wavefront 16 NC of them; each wavefront walks the key
-// blocks up to its own diagonal by itself (the four of a workgroup read the same blocks at about the same time:
-// the caches serve three of them).
+// close.  Two ways to share the work in a workgroup of four wavefronts:
+//   kSplitKeys false: 4 x 16 NC consecutive rows, 16 NC per wavefront, each walking the key blocks up to its own diagonal
+//     by itself (the four read the same blocks at about the same time: the caches serve three of them);
+//   kSplitKeys true: 16 rows, every fourth key block per wavefront, the four states combined through LDS.  A batch that
+//     does not fill the chip is bound by one wavefront's walk (0.4 to 0.9 us per block), which this cuts to a quarter.
 // Sequence b's tiles are numbered from cu_q[b] G / R + b (R rows per tile): consecutive sequences are then at least
 // ceil(S G / R) numbers apart, so no prefix sum over the batch is needed (find_sequence).  Later tiles of a sequence
 // are longer and go first.
-template <typename E, int KS, int NC>
+template <typename E, int KS, int NC, bool kSplitKeys>
 __global__ __launch_bounds__(256) void prefill_any_kernel(
     const E* __restrict__ q, int q_row_stride, const E* __restrict__ k_cache, const E* __restrict__ v_cache,
     const int32_t* __restrict__ cu_q, const int32_t* __restrict__ ctx_before, const int32_t* __restrict__ block_table, int bt_stride,
-    E* __restrict__ out, float* __restrict__ lse, int B, int Hq, int Hkv, int G, int D, float scale_log2e) {
+    E* __restrict__ out, float* __restrict__ lse, int B, int Hq, int Hkv, int G, Divisor div_g, int D, float scale_log2e) {
   typedef Block<E, KS> Blk;
-  constexpr int X = Elem<E>::X, NK = Blk::NK, NV = Blk::NV, R = 4 * 16 * NC;
+  constexpr int X = Elem<E>::X, NK = Blk::NK, NV = Blk::NV, R = (kSplitKeys ? 1 : 4) * 16 * NC;
+  constexpr int kRow = KS * 32 + 4;
+  static_assert(!kSplitKeys || NC == 1, "one set of rows per workgroup");
+  __shared__ float s_m[4][16], s_l[4][16], s_tot[2][16];
+  __shared__ __attribute__((aligned(16))) float s_acc[kSplitKeys ? 4 : 1][16][kSplitKeys ? kRow : 4];
+  __shared__ int s_bad;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int col = lane & 15, quad = lane >> 4, g = blockIdx.y;
   const int tile_no = (int)(gridDim.x - 1 - blockIdx.x);
-  auto first_tile = [&](int cu, int b) { return (long long)((unsigned long long)(unsigned)cu * (unsigned)G / (unsigned)R) + b; };
+  auto first_tile = [&](int cu, int b) { return (long long)cu * G / R + b; };
   const SeqOf seq = find_sequence(cu_q, ctx_before, B, tile_no, first_tile);
   const int b = seq.b, tok0 = seq.tok0, S = seq.S, cb = seq.cb;
-  const long long r0 = (tile_no - first_tile(tok0, b)) * R + wave * (16 * NC);
-  const long long n_rows = (long long)S * G;
-  if (r0 >= n_rows) return;
+  const int n_rows = S * G;
+  const long long tile_r0 = (tile_no - first_tile(tok0, b)) * R + (kSplitKeys ? 0 : wave * (16 * NC));
+  if (tile_r0 >= n_rows) return;
+  const int r0 = (int)tile_r0;
   const int32_t* const bt_row = block_table + (size_t)b * bt_stride;
   const size_t piece = (size_t)16 * D * sizeof(E);
   const int L = cb + S;
@@ -468,10 +481,10 @@ __global__ __launch_bounds__(256) void prefill_any_kernel(
   float m[NC], l[NC];
 #pragma unroll
   for (int c = 0; c < NC; ++c) {
-    const long long r = r0 + c * 16 + col;
+    const int r = r0 + c * 16 + col;
     ok[c] = r < n_rows;
-    pos[c] = ok[c] ? (int)((unsigned long long)r / (unsigned)G) : 0;
-    head[c] = ok[c] ? (int)(r - (long long)pos[c] * G) : 0;
+    pos[c] = ok[c] ? fast_div(r, div_g) : 0;
+    head[c] = ok[c] ? r - pos[c] * G : 0;
     const E* qrow = q + (size_t)(tok0 + pos[c]) * q_row_stride + (size_t)(g * G + head[c]) * D;
 #pragma unroll
     for (int j = 0; j < NK; ++j) {
@@ -485,24 +498,25 @@ __global__ __launch_bounds__(256) void prefill_any_kernel(
     l[c] = 0.f;
   }
   // keys every row of the wavefront sees, and those at least one of them sees (rows that do not exist: as row 0)
-  const long long r_last = min(n_rows, r0 + 16 * NC) - 1;
-  const int all_see = cb + (int)((unsigned long long)r0 / (unsigned)G) + 1, some_see = cb + (int)((unsigned long long)r_last / (unsigned)G) + 1;
-  const int n_blk = (some_see + 15) >> 4;
+  const int all_see = cb + fast_div(r0, div_g) + 1, some_see = cb + fast_div(min(n_rows, r0 + 16 * NC) - 1, div_g) + 1;
+  // this wavefront's key blocks: blk0 + step i, i < n
+  const int n_all = (some_see + 15) >> 4, blk0 = kSplitKeys ? wave : 0, step = kSplitKeys ? 4 : 1;
+  const int n = kSplitKeys ? (n_all - wave + 3) >> 2 : n_all;
   const char* const kc = reinterpret_cast<const char*>(k_cache);
   const char* const vc = reinterpret_cast<const char*>(v_cache);
 
-  int ids = lane < n_blk ? bt_row[lane] : 0;
-  for (int base = 0; base < n_blk; base += 64) {
-    const int nw = min(64, n_blk - base);
+  int ids = lane < n ? bt_row[blk0 + step * lane] : 0;
+  for (int base = 0; base < n; base += 64) {
+    const int nw = min(64, n - base);
     const int my = ids;
-    if (base + 64 + lane < n_blk) ids = bt_row[base + 64 + lane];
+    if (base + 64 + lane < n) ids = bt_row[blk0 + step * (base + 64 + lane)];
     Blk f[2];
     auto fetch = [&](Blk& fr, int i) {
       const size_t off = ((size_t)__builtin_amdgcn_readlane(my, min(i, nw - 1)) * Hkv + g) * piece;
       fr.load(kc + off, vc + off, i < nw ? (int)piece : 0, lane, col, quad);
     };
     auto work = [&](Blk& fr, int i) {
-      const int first = (base + i) << 4;
+      const int first = (blk0 + step * (base + i)) << 4;
       f32x4 s[NC];
 #pragma unroll
       for (int c = 0; c < NC; ++c) s[c] = fr.scores(qf[c]) * scale_log2e;
@@ -530,6 +544,62 @@ __global__ __launch_bounds__(256) void prefill_any_kernel(
     }
   }
 
+  auto redo_row = [&](int r) {
+    const int p = fast_div(r, div_g), h = r - p * G;
+    float rm, rl, o[4];
+    attend_row<E>(q + (size_t)(tok0 + p) * q_row_stride + (size_t)(g * G + h) * D, k_cache, v_cache, bt_row, g, Hkv, D, 0, cb + p + 1,
+                  scale_log2e, rm, rl, o);
+    for (int k = 0; k < 4; ++k) {
+      const int d = lane + 64 * k;
+      if (d < D) Elem<E>::store(out + ((size_t)(tok0 + p) * Hq + g * G + h) * D + d, o[k] / rl);
+    }
+  };
+  if constexpr (kSplitKeys) {
+    l[0] += __shfl_xor(l[0], 16);
+    l[0] += __shfl_xor(l[0], 32);
+    if (quad == 0) {
+      s_m[wave][col] = m[0];
+      s_l[wave][col] = l[0];
+    }
+    if (threadIdx.x == 0) s_bad = 0;
+    __syncthreads();
+    const float M = fmaxf(fmaxf(s_m[0][col], s_m[1][col]), fmaxf(s_m[2][col], s_m[3][col]));
+    float total = 0.f;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) total += s_m[w][col] == -INFINITY ? s_l[w][col] : s_l[w][col] * __builtin_amdgcn_exp2f(s_m[w][col] - M);
+    const float mine = m[0] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m[0] - M);
+    if (threadIdx.x < 16) {
+      s_tot[0][col] = M;
+      s_tot[1][col] = total;
+    }
+#pragma unroll
+    for (int dt = 0; dt < NV; ++dt) *reinterpret_cast<f32x4*>(&s_acc[wave][col][dt * 16 + 4 * quad]) = acc[0][dt] * mine;
+    __syncthreads();
+    // sixteen threads per row, four elements each
+    const int rr = (int)threadIdx.x >> 4, r = r0 + rr;
+    if (r < n_rows) {
+      const int p = fast_div(r, div_g), h = r - p * G;
+      const size_t row = (size_t)(tok0 + p) * Hq + (size_t)g * G + h;
+      const float sum = s_tot[1][rr], inv = 1.f / sum;
+      bool bad = false;
+#pragma unroll
+      for (int d0 = 0; d0 < KS * 32; d0 += 64) {
+        const int d = d0 + ((int)threadIdx.x & 15) * 4;
+        if (d >= D) continue;
+        f32x4 o = *reinterpret_cast<const f32x4*>(&s_acc[0][rr][d]);
+#pragma unroll
+        for (int w = 1; w < 4; ++w) o += *reinterpret_cast<const f32x4*>(&s_acc[w][rr][d]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) bad = bad || o[e] != o[e];
+        store4(out + row * D + d, o * inv);
+      }
+      if (bad && sum == sum) atomicOr(&s_bad, 1 << rr);
+      if (lse && ((int)threadIdx.x & 15) == 0) lse[row] = (s_tot[0][rr] + log2f(sum)) * kLn2;
+    }
+    __syncthreads();
+    for (int c = wave; c < 16; c += 4)  // (see attend_row)
+      if (s_bad >> c & 1) redo_row(r0 + c);
+  } else {
 #pragma unroll
   for (int c = 0; c < NC; ++c) {
     l[c] += __shfl_xor(l[c], 16);
@@ -543,14 +613,7 @@ __global__ __launch_bounds__(256) void prefill_any_kernel(
         const int d = dt * 16 + 4 * quad;
         if (d < D) {
           const f32x4 o = acc[c][dt];
-          if constexpr (Blk::kF32) {
-            *reinterpret_cast<f32x4*>(out + row * D + d) = o * inv;
-          } else {
-            u32x2 w;
-            w[0] = pack_bf16x2(o[0] * inv, o[1] * inv);
-            w[1] = pack_bf16x2(o[2] * inv, o[3] * inv);
-            *reinterpret_cast<u32x2*>(out + row * D + d) = w;
-          }
+          store4(out + row * D + d, o * inv);
 #pragma unroll
           for (int e = 0; e < 4; ++e) bad = bad || o[e] != o[e];
         }
@@ -562,15 +625,9 @@ __global__ __launch_bounds__(256) void prefill_any_kernel(
     while (redo) {
       const int rc = __ffsll(redo) - 1;
       redo &= redo - 1;
-      const int p = __shfl(pos[c], rc), h = __shfl(head[c], rc);
-      float rm, rl, o[4];
-      attend_row<E>(q + (size_t)(tok0 + p) * q_row_stride + (size_t)(g * G + h) * D, k_cache, v_cache, bt_row, g, Hkv, D, 0, cb + p + 1,
-                    scale_log2e, rm, rl, o);
-      for (int r = 0; r < 4; ++r) {
-        const int d = lane + 64 * r;
-        if (d < D) Elem<E>::store(out + ((size_t)(tok0 + p) * Hq + g * G + h) * D + d, o[r] / rl);
-      }
+      redo_row(r0 + c * 16 + rc);
     }
+  }
   }
 }
 
@@ -592,10 +649,20 @@ void launch_prefill_typed(const AttnArgs& a, const int32_t* cu_q, const int32_t*
   const int G = a.Hq / a.Hkv;
   for_head_size(a.D, [&](auto ks) {
     constexpr int KS = decltype(ks)::value, NC = KS <= 4 ? 2 : 1;  // two sets of 16 rows while their state fits the registers
-    const int64_t tiles = (int64_t)T * G / (64 * NC) + a.B;
-    hipLaunchKernelGGL((prefill_any_kernel<E, KS, NC>), dim3((unsigned)tiles, (unsigned)a.Hkv), dim3(256), 0, s, (const E*)a.q,
-                       a.q_row_stride, (const E*)a.k_cache, (const E*)a.v_cache, cu_q, ctx_before, a.block_table, a.bt_stride,
-                       (E*)a.out, a.lse, a.B, a.Hq, a.Hkv, G, a.D, a.scale_log2e);
+    auto launch = [&](auto kernel, int rows) {
+      hipLaunchKernelGGL(kernel, dim3((unsigned)((int64_t)T * G / rows + a.B), (unsigned)a.Hkv), dim3(256), 0, s, (const E*)a.q,
+                         a.q_row_stride, (const E*)a.k_cache, (const E*)a.v_cache, cu_q, ctx_before, a.block_table, a.bt_stride,
+                         (E*)a.out, a.lse, a.B, a.Hq, a.Hkv, G, make_divisor((uint32_t)G), a.D, a.scale_log2e);
+    };
+    // Batches too small to fill the chip share the keys of 16 rows out instead of the rows, unless the prompts are so short
+    // that there is little to share.  The line (rows x head size, against 5 Mi, or in proportion for prompts below 256
+    // tokens on average) lies between what was measured to gain and to lose by it, us: fp32, 64: 4 x 350 tokens 37 -> 13,
+    // 16 x 100 15 -> 8; fp32, 128, 6 heads: 8 x 300 59 -> 44, 32 x 300 113 -> 148; bf16, 64, 32 heads: 4 x 330 25 -> 22,
+    // 4 x 600 53 -> 43, 8 x 600 67 -> 75, 16 x 100 14 -> 18, 100 x 20 12 -> 24; bf16, 256, 8 heads: 4 x 300 34 -> 27, 40 x 16
+    // 9 -> 15, 64 x 100 47 -> 94.
+    const int64_t line = std::min<int64_t>((int64_t)5 << 20, ((int64_t)5 << 12) * T / a.B);
+    if ((int64_t)T * a.Hq * (32 * KS) <= line) launch(prefill_any_kernel<E, KS, 1, true>, 16);
+    else launch(prefill_any_kernel<E, KS, NC, false>, 64 * NC);
   });
 }
 

@@ -120,3 +120,28 @@ def test_infinite_values_reach_only_the_rows_that_see_them(dtype, D):
     assert (gd.float() - wd.float())[torch.isfinite(wd)].abs().max() <= tol
     assert (glse - wlse).abs().max() <= 1e-4
     layer.close()
+
+
+@pytest.mark.parametrize("dtype,D,Hq,Hkv", [("f32", 64, 16, 2), ("bf16", 64, 32, 8), ("bf16", 80, 24, 8), ("bf16", 256, 8, 1), ("f32", 160, 8, 4)],
+                         ids=["f32-d64", "bf16-d64", "bf16-d80", "bf16-d256", "f32-d160"])
+def test_prefill_of_many_short_prompts(dtype, D, Hq, Hkv):
+    """Batches that share out the rows of a tile instead of its keys (many short prompts), some behind cached tokens: more
+    sequences than one round of the search for a tile's sequence holds, lengths around the tiles' edges, empty ones."""
+    model = wl.ModelShape(f"{dtype}-d{D}", Hq, Hkv, D, 1, dtype)
+    rng = np.random.default_rng(D)
+    new = np.r_[0, 0, 1, 16, 17, 63, 64, 65, 0, 130, rng.integers(0, 50, size=80)].astype(np.int32)
+    before = np.where(rng.random(len(new)) < 0.3, rng.integers(0, 90, size=len(new)), 0).astype(np.int32)
+    say(f"{dtype}, head size {D}: {len(new)} prompts, {new.sum()} tokens")
+    pb = wl.prefill_batch(model, np.maximum(before + new, 1), 91)
+    layer = Layer(model, pb.num_blocks, len(new), pb.block_table.shape[1])
+    rows = lambda n, h, seed: wl.randn((int(n), h, D), dtype, seed)
+    layer.append(rows(before.sum(), Hkv, 1), rows(before.sum(), Hkv, 2), wl.cu_from_lengths(before), np.zeros_like(before), pb.block_table)
+    cu = wl.cu_from_lengths(new)
+    layer.append(rows(new.sum(), Hkv, 3), rows(new.sum(), Hkv, 4), cu, before, pb.block_table)
+    layer.assert_cache_bit_exact()
+    q = rows(new.sum(), Hq, 5)
+    out, lse = layer.prefill_gpu(q, cu, before, pb.block_table)
+    ref, ref_lse = layer.prefill_oracle(q, cu, before, pb.block_table)
+    compare("prefill", out, ref, dtype)
+    compare_lse("prefill", lse, ref_lse, dtype)
+    layer.close()
