@@ -389,8 +389,32 @@ __global__ __launch_bounds__(256, 2) void prefill_mfma_kernel(
                              // load: an outstanding scalar load would force full waits on every LDS read)
   const float c = scale_log2e;
   const size_t blk_stride = (size_t)Hkv * 4096;
-  const int n_flat = plan[0] * Hkv;  // items
   const int32_t* const recs = plan + kPlanHeaderInts;
+  // the other counter set is idle (the launch that used it is over): start it for the next launch
+  auto start_other_counters = [&]() {
+    if (blockIdx.x == 0 && threadIdx.x < kQueues)
+      plan[kPlanCounter0 + kPlanCounterStride * (kQueues * (parity ^ 1) + threadIdx.x)] =
+          2 * (((int)gridDim.x - (int)threadIdx.x + kQueues - 1) / kQueues);
+  };
+  // item f is K/V head f % Hkv of tile f / Hkv
+  int tile_of_f, g_of_f;
+  auto split = [&](int f) {
+    tile_of_f = fast_div(f, div_hkv);
+    g_of_f = f - tile_of_f * Hkv;
+  };
+  auto load_rec = [&](int tile) { return recs[(size_t)tile * kRecInts + min(lane, kRecInts - 1)]; };
+
+  // The first two tickets of every workgroup are fixed (the plan starts the counters behind them: several hundred
+  // workgroups asking eight counters at once would wait on each other): the first is item blockIdx.x, whose record is
+  // asked for together with the number of items (the grid is no larger than the bound the plan is sized for).
+  split(blockIdx.x);
+  int rec_next = load_rec(tile_of_f);  // record of the next item (here: of the first)
+  const int n_flat = __builtin_amdgcn_readfirstlane(plan[0]) * Hkv;  // items
+  if ((int)blockIdx.x >= n_flat) {
+    if (threadIdx.x == 0 && blockIdx.x < kPlanMaxWgs) plan[kPlanBusy0 + parity * kPlanMaxWgs + blockIdx.x] = 0;
+    start_other_counters();
+    return;
+  }
   // Work items are dealt to kQueues queues (item f belongs to queue f % kQueues) and workgroup w
   // serves queue w % kQueues.  kQueues is a multiple of 8: workgroup ids are dealt round-robin to
   // the 8 XCDs and with eight K/V heads item f reads K/V head f % 8, so an XCD's L2 sees one head's
@@ -402,17 +426,9 @@ __global__ __launch_bounds__(256, 2) void prefill_mfma_kernel(
   // works through (its quota, below), from the busy times of the launch before.
   const int queue = blockIdx.x % kQueues;
   int* const counter = plan + kPlanCounter0 + kPlanCounterStride * (kQueues * parity + queue);
-  // the other counter set is idle (the launch that used it is over): start it for the next launch
-  if (blockIdx.x == 0 && threadIdx.x < kQueues)
-    plan[kPlanCounter0 + kPlanCounterStride * (kQueues * (parity ^ 1) + threadIdx.x)] =
-        2 * (((int)gridDim.x - (int)threadIdx.x + kQueues - 1) / kQueues);
-  auto resolve0 = [&](int k) -> int {  // ticket k of the own queue -> item of the own list, -1 past its end
-    const int f = kQueues * k + queue;
-    return f < n_flat ? f : -1;
-  };
-  // The same with the queues' quotas (qtab, set up below): a queue that gives items away stops short of the
-  // end of its list, and the lists' ends so left over are dealt, in queue order, to the queues that take
-  // more than their own.  Thread 0 only.
+  // Ticket k of the own queue -> item, -1 past its end, with the queues' quotas (qtab, set up below): a queue that
+  // gives items away stops short of the end of its list, and the lists' ends so left over are dealt, in queue order,
+  // to the queues that take more than their own.  Thread 0 only.
   auto resolve = [&](int k) -> int {
     const int quota = qtab[queue], own = qtab[kQueues + queue];
     if (k < min(quota, own)) return kQueues * k + queue;
@@ -427,44 +443,20 @@ __global__ __launch_bounds__(256, 2) void prefill_mfma_kernel(
     }
     return -1;
   };
+  start_other_counters();
   // What the previous launch left behind for this one (the other set): each workgroup's busy time, the
   // queues' shares and which batch they belong to.  Wavefront 0 asks for them now and uses them below.
   int prev_items = 0, prev_grid = 0;
   float busy_sum = 0.f, share = 0.f;  // (a float: 64 busy times of a long launch do not fit an int)
-  if (wave == 0) {
+  if (wave == 0 && n_flat >= kBalanceMinItems) {
     const int32_t* bp = plan + kPlanBusy0 + (parity ^ 1) * kPlanMaxWgs;
     for (int w = lane; w < (int)gridDim.x && w < kPlanMaxWgs; w += 64) busy_sum += (float)bp[w];
     share = reinterpret_cast<const float*>(plan)[kPlanShare0 + kQueues * (parity ^ 1) + (lane & 7)];
     prev_items = plan[kPlanMeta0 + (parity ^ 1)];
     prev_grid = plan[kPlanMeta0 + 2 + (parity ^ 1)];
   }
-  // item f is K/V head f % Hkv of tile f / Hkv
-  int tile_of_f, g_of_f;
-  auto split = [&](int f) {
-    tile_of_f = fast_div(f, div_hkv);
-    g_of_f = f - tile_of_f * Hkv;
-  };
-  auto load_rec = [&](int tile) { return recs[(size_t)tile * kRecInts + min(lane, kRecInts - 1)]; };
-
-  // The first two tickets of every workgroup are fixed (the plan starts the counters behind them):
-  // several hundred workgroups asking eight counters at once would wait on each other.
-  if (tid == 0) {
-    const int iq = blockIdx.x / kQueues;                                   // index in the queue's crew
-    const int nq = ((int)gridDim.x - queue + kQueues - 1) / kQueues;       // size of the crew
-    const int f0 = resolve0(iq);  // (a queue's quota is never below these two rounds)
-    slot[0] = f0;
-    slot[1] = f0 >= 0 ? resolve0(iq + nq) : -1;
-  }
-  __syncthreads();
-  int f_cur = __builtin_amdgcn_readfirstlane(slot[0]);    // the item being computed
-  int f_next = __builtin_amdgcn_readfirstlane(slot[1]);   // the one after it (-1: none)
-  if (f_cur < 0) {
-    if (tid == 0 && blockIdx.x < kPlanMaxWgs) plan[kPlanBusy0 + parity * kPlanMaxWgs + blockIdx.x] = 0;
-    return;
-  }
-
-  split(f_cur);
-  int rec_next = load_rec(tile_of_f);  // record of the next item (here: of the first)
+  int f_next = (int)blockIdx.x + kQueues * (((int)gridDim.x - queue + kQueues - 1) / kQueues);  // the item after the current one
+  if (f_next >= n_flat) f_next = -1;   // (-1: none)
   int pend = 0;                        // (thread 0) ticket on its way
   Item cur = describe(rec_next, g_of_f, block_table, bt_stride);
   int g_next = 0;                      // K/V head of the next item
@@ -543,29 +535,34 @@ __global__ __launch_bounds__(256, 2) void prefill_mfma_kernel(
   // of proportional control per launch; the items that change hands are the lightest ones at the lists' ends,
   // hence the gain above one).  Which workgroup computes an item does not change its result.
   if (wave == 0) {
-    // workgroup w runs on XCD w % 8, and lane l summed workgroups l, l + 64, ...: all of XCD l % 8
-    float sum = busy_sum;
-    sum += __shfl_xor(sum, 8);
-    sum += __shfl_xor(sum, 16);
-    sum += __shfl_xor(sum, 32);
-    auto over_queues_i = [&](int v) { v += __shfl_xor(v, 1); v += __shfl_xor(v, 2); v += __shfl_xor(v, 4); return v; };
-    auto over_queues_f = [&](float v) { v += __shfl_xor(v, 1); v += __shfl_xor(v, 2); v += __shfl_xor(v, 4); return v; };
     const int x = lane & 7;
-    const int crew = ((int)gridDim.x - x + kQueues - 1) / kQueues;
     const int own = max(n_flat - x + kQueues - 1, 0) / kQueues;
-    const float T = sum / (float)max(crew, 1);
-    const float T_mean = over_queues_f(T) * 0.125f;
-    const bool big = n_flat >= kBalanceMinItems && (int)gridDim.x <= kPlanMaxWgs && gridDim.x % kQueues == 0;
-    const bool same = prev_items == n_flat && prev_grid == (int)gridDim.x;
-    float sh = same && share > 0.f ? share : 1.f;
-    if (big && same && __all(T > 0.f))
-      sh = fminf(kShareMax, fmaxf(kShareMin, sh + kShareGain * (T_mean - T) / T_mean));
-    sh *= 8.f / over_queues_f(sh);
-    int quota = (int)((float)own * sh + 0.5f);
-    const int quota_sum = over_queues_i(quota);
-    if (x == kQueues - 1) quota += n_flat - quota_sum;  // the last queue takes the rounding
-    const bool ok = big && __all(quota >= 2 * crew && own >= 2 * crew);
-    if (!ok) quota = own;
+    int quota = own;
+    float sh = 1.f;
+    bool ok = false;
+    if (n_flat >= kBalanceMinItems) {
+      // workgroup w runs on XCD w % 8, and lane l summed workgroups l, l + 64, ...: all of XCD l % 8
+      float sum = busy_sum;
+      sum += __shfl_xor(sum, 8);
+      sum += __shfl_xor(sum, 16);
+      sum += __shfl_xor(sum, 32);
+      auto over_queues_i = [&](int v) { v += __shfl_xor(v, 1); v += __shfl_xor(v, 2); v += __shfl_xor(v, 4); return v; };
+      auto over_queues_f = [&](float v) { v += __shfl_xor(v, 1); v += __shfl_xor(v, 2); v += __shfl_xor(v, 4); return v; };
+      const int crew = ((int)gridDim.x - x + kQueues - 1) / kQueues;
+      const float T = sum / (float)max(crew, 1);
+      const float T_mean = over_queues_f(T) * 0.125f;
+      const bool big = (int)gridDim.x <= kPlanMaxWgs && gridDim.x % kQueues == 0;
+      const bool same = prev_items == n_flat && prev_grid == (int)gridDim.x;
+      sh = same && share > 0.f ? share : 1.f;
+      if (big && same && __all(T > 0.f))
+        sh = fminf(kShareMax, fmaxf(kShareMin, sh + kShareGain * (T_mean - T) / T_mean));
+      sh *= 8.f / over_queues_f(sh);
+      quota = (int)((float)own * sh + 0.5f);
+      const int quota_sum = over_queues_i(quota);
+      if (x == kQueues - 1) quota += n_flat - quota_sum;  // the last queue takes the rounding
+      ok = big && __all(quota >= 2 * crew && own >= 2 * crew);
+      if (!ok) quota = own;
+    }
     if (lane < kQueues) {
       qtab[lane] = quota;
       qtab[kQueues + lane] = own;
