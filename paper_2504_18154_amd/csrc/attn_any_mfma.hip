@@ -266,7 +266,7 @@ __global__ __launch_bounds__(W * 64) void decode_any_kernel(
   auto fetch = [&](Blk& fr, int i) {
     const int at = base + 64 < n ? i : i == 0 ? nw - 1 : i - 1;
     const size_t off = ((size_t)__builtin_amdgcn_readlane(ids, max(min(at, nw - 1), 0)) * Hkv + g) * piece;
-    fr.load(kc + off, vc + off, i < nw ? (int)piece : 0, lane, col, quad);
+    fr.load(kc + off, vc + off, (int)piece, lane, col, quad);
   };
   f32x4 acc[NV];
 #pragma unroll
@@ -282,10 +282,8 @@ __global__ __launch_bounds__(W * 64) void decode_any_kernel(
     const f32x4 p = softmax_step<NV>(s, m, l, acc);
     fr.values(p, acc);
   };
-  if (n > 0) {
-    fetch(f[0], 0);
-    fetch(f[1], 1);
-  }
+  if (n > 0) fetch(f[0], 0);
+  if (n > 1) fetch(f[1], 1);
   if (newest)
 #pragma unroll
     for (int i = 0; i < NN; ++i)
@@ -302,19 +300,28 @@ __global__ __launch_bounds__(W * 64) void decode_any_kernel(
       if (newest) f[0].put_token(s_new[0], s_new[1], tail - 1, D, col, quad);
       if (tail < 16) f[0].clear_tail(tail, quad);
     }
-    for (int i = 0; i < nw; i += 2) {
-      work(f[0], tail);
-      tail = 16;
-      fetch(f[0], i + 2);
-      if (i + 1 < nw) work(f[1], 16);
-      fetch(f[1], i + 3);
+    // Only blocks that exist are asked for: a load of nothing still takes its turn in the address unit, and three such
+    // blocks (36 loads) per wavefront were 1 us of a context of 100 tokens.  Inside the loop every path issues the same
+    // loads, so its waits are exact.
+    work(f[0], tail);
+    int i = 1;
+    for (; i + 2 < nw; i += 2) {
+      fetch(f[0], i + 1);
+      work(f[1], 16);
+      fetch(f[1], i + 2);
+      work(f[0], 16);
+    }
+    if (i < nw) {
+      if (i + 1 < nw) fetch(f[0], i + 1);
+      work(f[1], 16);
+      if (i + 1 < nw) work(f[0], 16);
     }
     base += 64;
     if (base < n) {
       nw = min(64, n - base);
       ids = lane < nw ? bt_row[blk0 + wave + W * (base + lane)] : 0;
       fetch(f[0], 0);
-      fetch(f[1], 1);
+      if (nw > 1) fetch(f[1], 1);
     }
   }
   l += __shfl_xor(l, 16);
