@@ -45,7 +45,7 @@ struct Block {
   u32x4 k[NK];
   VFrag v[NV];
 
-  // `bytes`: size of one (block, head) piece of the pool, 0 for a load of nothing (zeros, no memory access)
+  // `bytes`: size of one (block, head) piece of the pool
   __device__ __forceinline__ void load(const char* kbase, const char* vbase, int bytes, int lane, int col, int quad) {
     const __amdgpu_buffer_rsrc_t rk = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(kbase), 0, bytes, kRsrc32);
     const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(vbase), 0, bytes, kRsrc32);
@@ -520,7 +520,7 @@ __global__ __launch_bounds__(256) void prefill_any_kernel(
     Blk f[2];
     auto fetch = [&](Blk& fr, int i) {
       const size_t off = ((size_t)__builtin_amdgcn_readlane(my, min(i, nw - 1)) * Hkv + g) * piece;
-      fr.load(kc + off, vc + off, i < nw ? (int)piece : 0, lane, col, quad);
+      fr.load(kc + off, vc + off, (int)piece, lane, col, quad);
     };
     auto work = [&](Blk& fr, int i) {
       const int first = (blk0 + step * (base + i)) << 4;
@@ -543,12 +543,19 @@ __global__ __launch_bounds__(256) void prefill_any_kernel(
       }
     };
     fetch(f[0], 0);
-    for (int i = 0; i < nw; i += 2) {
+    int i = 0;
+    for (; i + 2 < nw; i += 2) {
       fetch(f[1], i + 1);
       work(f[0], i);
       fetch(f[0], i + 2);
-      if (i + 1 < nw) work(f[1], i + 1);
+      work(f[1], i + 1);
     }
+    // The last one or two: only blocks that exist are asked for, and the loop above has no branch around a block, so its
+    // waits are exact (with a branch, and loads of nothing behind the end: fp32, 4 x 350 tokens 13.1 against 11.3 us; bf16,
+    // head size 80, 60 x 500 125 against 91; 256, 64 x 100 47 against 33).
+    if (i + 1 < nw) fetch(f[1], i + 1);
+    work(f[0], i);
+    if (i + 1 < nw) work(f[1], i + 1);
   }
 
   auto redo_row = [&](int r) {
@@ -666,7 +673,8 @@ void launch_prefill_typed(const AttnArgs& a, const int32_t* cu_q, const int32_t*
     // tokens on average) lies between what was measured to gain and to lose by it, us: fp32, 64: 4 x 350 tokens 37 -> 13,
     // 16 x 100 15 -> 8; fp32, 128, 6 heads: 8 x 300 59 -> 44, 32 x 300 113 -> 148; bf16, 64, 32 heads: 4 x 330 25 -> 22,
     // 4 x 600 53 -> 43, 8 x 600 67 -> 75, 16 x 100 14 -> 18, 100 x 20 12 -> 24; bf16, 256, 8 heads: 4 x 300 34 -> 27, 40 x 16
-    // 9 -> 15, 64 x 100 47 -> 94.
+    // 9 -> 15, 64 x 100 47 -> 94 (both ways before the walk below stopped asking for blocks that do not exist; with that
+    // the first of each pair that gains: 11, 8, 35, 18, 19 us).
     const int64_t line = std::min<int64_t>((int64_t)5 << 20, ((int64_t)5 << 12) * T / a.B);
     if ((int64_t)T * a.Hq * (32 * KS) <= line) launch(prefill_any_kernel<E, KS, 1, true>, 16);
     else launch(prefill_any_kernel<E, KS, NC, false>, 64 * NC);
