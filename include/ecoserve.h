@@ -293,7 +293,8 @@ int ecoserve_attn_decode_strided(ecoserve_ctx* ctx, const void* q, int64_t q_row
  * ecoserve_attn_decode_strided, in one launch less: the wavefront that
  * streams a sequence's last cache block takes the new token's K and V from
  * the new rows, and the small launch that merges the split contexts also
- * stores them into the block.  The cache holds the new tokens when the
+ * stores them into the block (batches small enough for a single launch: that
+ * launch does both).  The cache holds the new tokens when the
  * call's work on `stream` is complete, like every other result.
  *
  *   k_new, v_new     : dev, row b = the new token of sequence b, [Hkv][D], rows
@@ -311,8 +312,8 @@ int ecoserve_attn_decode_append(ecoserve_ctx* ctx, const void* q, int64_t q_row_
  * ecoserve_attn_decode for callers that cannot allocate device memory: code
  * under HIP graph capture, tight serving loops, harnesses that forbid
  * hipMalloc.  No context: the layout is passed directly, and the scratch
- * memory of the two launches (partial softmax states of the split contexts,
- * the launch's numbering, the list of cut sequences) is a fixed array of
+ * memory of the launches (partial softmax states of the split contexts, the
+ * launch's numbering, the list of cut sequences, merge counters) is a fixed array of
  * 16.3 MiB inside the library's device code, one copy per GPU, held until the
  * process ends.  The call allocates nothing (no hipMalloc / hipFree, no
  * events), does not synchronise, and launches the same kernels as
@@ -330,9 +331,10 @@ int ecoserve_attn_decode_append(ecoserve_ctx* ctx, const void* q, int64_t q_row_
  *                 workgroups; nothing else about the inputs is limited)
  *
  * All calls on one GPU share that GPU's array: calls that overlap there (two
- * streams, two threads) race; order them.  The array needs no clearing
- * between calls (a launch writes every word it later reads), and a call may
- * follow a larger one.
+ * streams, two threads) race, and a race may spoil later calls too (it can
+ * leave a merge counter away from zero); order them.  The array needs no
+ * clearing between calls (a launch writes every word it later reads, and
+ * leaves the counters at zero), and a call may follow a larger one.
  */
 int ecoserve_attn_decode_noalloc(int device, const ecoserve_layout* layout, const void* q, const void* k_cache,
                                  const void* v_cache, const int32_t* block_table, int32_t bt_stride,

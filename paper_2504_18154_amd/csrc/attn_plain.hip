@@ -1,12 +1,11 @@
 // Plain (no matrix-core) attention kernels for any supported head size and element type,
-// plus the split-context merge kernel that both decode paths share.
+// plus the merge of the split contexts.
 //
 // They evaluate Eq. 2 of Section 2.1, softmax(Q K^T / sqrt(d_k)) V, over the paged cache
 // with fp32 arithmetic and an online (running max / running sum) softmax in the exp2
 // domain.  One wavefront handles one (query row, query head, context slice): lanes own
 // tokens for the score pass and own head-vector elements for the value pass.  They run
-// when ECOSERVE_OPT_FORCE_PLAIN asks for them (a second opinion on the matrix-core kernels);
-// the merge kernel also serves decode on matrix cores for layouts other than (bf16, 128).
+// when ECOSERVE_OPT_FORCE_PLAIN asks for them (a second opinion on the matrix-core kernels).
 #include "common.h"
 
 namespace eco {

@@ -152,7 +152,7 @@ hipError_t launch_prefill_plain(const AttnArgs& a, const int32_t* cu_q, const in
                                 hipStream_t s);
 hipError_t launch_decode_plain(const AttnArgs& a, const int32_t* ctx_len, int32_t split_tokens, int32_t n_split_max,
                                float* ws_acc, float* ws_ml, int32_t ws_splits, hipStream_t s);
-// merges split partials into out/lse (shared by the plain and matrix-core decode paths)
+// merges the split partials of launch_decode_plain into out/lse
 hipError_t launch_decode_merge(const AttnArgs& a, const int32_t* ctx_len, int32_t split_tokens, const float* ws_acc,
                                const float* ws_ml, int32_t ws_splits, hipStream_t s);
 
