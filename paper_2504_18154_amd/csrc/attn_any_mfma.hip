@@ -21,8 +21,8 @@
 // length -> block ids -> blocks, and the walk of the blocks.  Hence decode takes contexts up to 1024 tokens in one
 // launch, eight wavefronts per (sequence, K/V head) and the step's append inside (one launch instead of three).
 // Measured beside the plain kernels (one wavefront per query row, a scalar product per lane): a prompt batch of 4 x
-// 50..600 tokens and 8 decode steps, bf16, head size 64, 32/8 heads: 399 -> 60 us (prefill kernel 243 -> 13 us, a
-// decode step's kernels 21.9 -> 5.6 us); 4 x 37..700 tokens in fp32, 4/2 heads: 197 -> 72 us (55 -> 13 us, 19.1 -> 7 us).
+// 50..600 tokens and 8 decode steps, bf16, head size 64, 32/8 heads: 399 -> 61 us (prefill kernel 243 -> 10 us, a
+// decode step's kernels 21.9 -> 5.6 us); 4 x 37..700 tokens in fp32, 4/2 heads: 195 -> 72 us (55 -> 8 us, 19.1 -> 7 us).
 #include <algorithm>
 #include <type_traits>
 
