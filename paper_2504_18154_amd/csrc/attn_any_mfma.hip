@@ -164,10 +164,12 @@ __device__ __forceinline__ f32x4 softmax_step(const f32x4& s, float& m, float& l
   return p;
 }
 
-// One row over keys [t0, t1), one wavefront, key after key: what a row falls back to when its result is not a
-// number although its weights are.  A V element that is infinite or not a number then meets the zero weight of a
+// One row over keys [t0, t1), one wavefront, key after key: what a row falls back to when its sums are not finite
+// although its weights are.  Either a V element that is infinite or not a number met the zero weight of a
 // masked key, or the zero remainder of a bf16 weight, in the products above; here it meets only the rows that see
-// it.  Lane owns elements lane + 64 r.
+// it.  Or values within a factor of 2^kRaise of the largest fp32 overflowed under weights above 1; here weights are
+// taken relative to the largest score so far and do not exceed 1.  Lane owns elements lane + 64 r.
+__device__ __forceinline__ bool not_finite(float x) { return !(fabsf(x) < INFINITY); }
 template <typename E>
 __device__ __forceinline__ void attend_row(const E* __restrict__ qrow, const E* __restrict__ k_cache, const E* __restrict__ v_cache,
                                         const int32_t* __restrict__ bt_row, int g, int Hkv, int D, int t0, int t1, float scale_log2e,
@@ -366,7 +368,7 @@ __global__ __launch_bounds__(W * 64) void decode_any_kernel(
 #pragma unroll
       for (int w = 0; w < W; ++w) o += s_acc[w][h][dl];
       const float sum = s_tot[1][h];
-      if (o != o && sum == sum) s_bad = 1;  // (see attend_row)
+      if (not_finite(o) && sum == sum) s_bad = 1;  // (see attend_row)
       if (final_result) Elem<E>::store(out + ((size_t)b * Hq + g * G + h) * D + d, o / sum);
       else store_shared(ws_acc + (slot0 + h * slot_step) * D + d, o);
     }
@@ -604,7 +606,7 @@ __global__ __launch_bounds__(256) void prefill_any_kernel(
 #pragma unroll
         for (int w = 1; w < 4; ++w) o += *reinterpret_cast<const f32x4*>(&s_acc[w][rr][d]);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) bad = bad || o[e] != o[e];
+        for (int e = 0; e < 4; ++e) bad = bad || not_finite(o[e]);
         store4(out + row * D + d, o * inv);
       }
       if (bad && sum == sum) atomicOr(&s_bad, 1 << rr);
@@ -629,7 +631,7 @@ __global__ __launch_bounds__(256) void prefill_any_kernel(
           const f32x4 o = acc[c][dt];
           store4(out + row * D + d, o * inv);
 #pragma unroll
-          for (int e = 0; e < 4; ++e) bad = bad || o[e] != o[e];
+          for (int e = 0; e < 4; ++e) bad = bad || not_finite(o[e]);
         }
       }
       if (lse && quad == 0) lse[row] = (m[c] + log2f(l[c])) * kLn2;
