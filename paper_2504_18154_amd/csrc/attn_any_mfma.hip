@@ -150,16 +150,16 @@ __device__ __forceinline__ f32x4 softmax_step(const f32x4& s, float& m, float& l
     bm = fmaxf(bm, __shfl_xor(bm, 16));
     bm = fmaxf(bm, __shfl_xor(bm, 32));
     const float m_new = bm > m + kRaise ? bm : m;
-    const float alpha = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - m_new);
+    const float alpha = m == -INFINITY ? 0.f : exp2f(m - m_new);
     l *= alpha;
 #pragma unroll
     for (int dt = 0; dt < NV; ++dt) acc[dt] *= alpha;
     m = m_new;
   }
   const float mu = m == -INFINITY ? 0.f : m;  // (a row all of whose keys so far are masked)
-  f32x4 p;
+  f32x4 p;  // exp2f: the bare instruction flushes weights below 2^-126, which large values can still make count
 #pragma unroll
-  for (int i = 0; i < 4; ++i) p[i] = __builtin_amdgcn_exp2f(s[i] - mu);
+  for (int i = 0; i < 4; ++i) p[i] = exp2f(s[i] - mu);
   l += (p[0] + p[1]) + (p[2] + p[3]);
   return p;
 }
@@ -348,7 +348,7 @@ __global__ __launch_bounds__(W * 64) void decode_any_kernel(
   for (int w = 0; w < W; ++w) M = fmaxf(M, s_m[w][col]);
 #pragma unroll
   for (int w = 0; w < W; ++w) total += s_m[w][col] == -INFINITY ? s_l[w][col] : s_l[w][col] * __builtin_amdgcn_exp2f(s_m[w][col] - M);
-  const float mine = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - M);
+  const float mine = m == -INFINITY ? 0.f : exp2f(m - M);
   if (tid < 16) {
     s_tot[0][col] = M;
     s_tot[1][col] = total;
@@ -419,7 +419,7 @@ __global__ __launch_bounds__(W * 64) void decode_any_kernel(
       const float mk = lane < nk ? load_shared(ws_ml + (slot + base + lane) * 2) : -INFINITY;
       const float lk = lane < nk ? load_shared(ws_ml + (slot + base + lane) * 2 + 1) : 0.f;
       const float m_new = fmaxf(m2, wave_max(mk));
-      const float old = base ? __builtin_amdgcn_exp2f(m2 - m_new) : 0.f, wk = lane < nk ? __builtin_amdgcn_exp2f(mk - m_new) : 0.f;
+      const float old = base ? exp2f(m2 - m_new) : 0.f, wk = lane < nk ? exp2f(mk - m_new) : 0.f;
       m2 = m_new;
       l2 = l2 * old + wave_sum(lk * wk);
 #pragma unroll
@@ -583,7 +583,7 @@ __global__ __launch_bounds__(256) void prefill_any_kernel(
     float total = 0.f;
 #pragma unroll
     for (int w = 0; w < 4; ++w) total += s_m[w][col] == -INFINITY ? s_l[w][col] : s_l[w][col] * __builtin_amdgcn_exp2f(s_m[w][col] - M);
-    const float mine = m[0] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m[0] - M);
+    const float mine = m[0] == -INFINITY ? 0.f : exp2f(m[0] - M);
     if (threadIdx.x < 16) {
       s_tot[0][col] = M;
       s_tot[1][col] = total;

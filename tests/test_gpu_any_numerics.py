@@ -84,3 +84,14 @@ def test_large_values_do_not_overflow_the_sums(dtype, D, Hkv):
             say(f"{dtype}, head size {D}, {s.B} sequences, {name}: {got.min():.4g} .. {got.max():.4g}")
             # the mean of equal values: fp32 sums of 320 terms are within 320 2^-24, rounding to bf16 is 2^-9
             assert ((got / 2.0 ** 120 - 1).abs() <= (2.0 ** -8 if dtype == "bf16" else 320 * 2.0 ** -24)).all(), name
+
+
+@pytest.mark.parametrize("dtype,D,Hkv", LAYOUTS, ids=IDS)
+def test_weights_below_the_normal_numbers_count(dtype, D, Hkv):
+    """One key of weight 1 and value 0, nineteen of weight 2^-128 and value 2^125: 19 / 8, not 0."""
+    log2_w = np.r_[0.0, np.full(19, -128.0)]
+    values = np.r_[np.zeros((1, D)), np.full((19, D), 2.0 ** 125)]
+    for s in _both_prefills(dtype=dtype, D=D, Hkv=Hkv, log2_w=log2_w, values=values):
+        for name, got in s.ways():
+            say(f"{dtype}, head size {D}, {s.B} sequences, {name}: {got.min():.6g} .. {got.max():.6g} (19/8 = 2.375)")
+            assert ((got - 2.375).abs() <= 1e-5).all(), name    # (exact in bf16; powers of two and small sums in fp32)
