@@ -424,7 +424,9 @@ __global__ __launch_bounds__(W * 64) void decode_any_kernel(
       const float mk = lane < nk ? load_shared(ws_ml + (slot + base + lane) * 2) : -INFINITY;
       const float lk = lane < nk ? load_shared(ws_ml + (slot + base + lane) * 2 + 1) : 0.f;
       const float m_new = fmaxf(m2, wave_max(mk));
-      const float old = base ? exp2f(m2 - m_new) : 0.f, wk = lane < nk ? exp2f(mk - m_new) : 0.f;
+      // (slices whose scores are all -inf so far weigh nothing: their m is -inf, their sums are zero)
+      const float mu = m_new == -INFINITY ? 0.f : m_new;
+      const float old = m2 == -INFINITY ? 0.f : exp2f(m2 - mu), wk = lane < nk ? exp2f(mk - mu) : 0.f;
       m2 = m_new;
       l2 = l2 * old + wave_sum(lk * wk);
 #pragma unroll

@@ -119,3 +119,19 @@ def test_weights_have_the_bits_of_fp32(dtype, D, Hkv):
             err = float(((got - want).norm(dim=-1) / want.norm()).max())
             say(f"{dtype}, head size {D}, {s.B} sequences, {name}: off by {err:.3f} of what the sums leave")
             assert err <= 0.2, name
+
+
+@pytest.mark.parametrize("dtype,D", [("f32", 64), ("bf16", 64)], ids=["f32-d64", "bf16-d64"])
+def test_slices_whose_scores_are_all_minus_infinity(dtype, D):
+    """Decode in slices of 64 tokens whose first 64 (a whole round of the merge) or 65 hold nothing but scores of minus
+    infinity: they weigh nothing, and the result is that of the keys behind them."""
+    for dead in (64, 65):
+        n = dead * 64 + 70
+        log2_w = np.r_[np.full(dead * 64, -np.inf), np.zeros(70)]
+        values = np.r_[np.ones((dead * 64, D)), np.full((70, D), 3.0)]
+        s = Scored(dtype, D, 2, log2_w, values)
+        s.ctx.set_option(binding.OPT_DECODE_SPLIT_TOKENS, 64)
+        got = s.decode()
+        say(f"{dtype}, head size {D}, {dead} slices of minus infinity of {(n + 63) // 64}: {got.min():.6g} .. {got.max():.6g}")
+        assert ((got - 3.0).abs() <= 1e-5).all()
+        s.ctx.close()
