@@ -27,6 +27,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "decode_slices.h"
 
 namespace eco {
 
@@ -231,11 +232,10 @@ __global__ __launch_bounds__(W * 64) void decode_any_kernel(
   const int sp = blockIdx.x, g = blockIdx.y, b = blockIdx.z;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int col = lane & 15, quad = lane >> 4;
-  // Asked for before anything that depends on the length: the ids of this wavefront's first 64 blocks (blk0 + wave +
-  // W i; entries behind the sequence's last block are read and never used), the new rows, the query rows.
+  // Asked for with the length, before anything that depends on it: the new rows, the query rows.  (The block ids have to
+  // wait: entries behind the sequence's last block are not read.)
+  const int L = ctx_len[b];
   const int32_t* const bt_row = block_table + (size_t)b * bt_stride;
-  const int blk0 = (sp * split_tokens) >> 4;
-  int ids = bt_row[min(blk0 + wave + W * lane, bt_stride - 1)];
   const bool fused = k_new != nullptr;
   constexpr int NN = (32 * KS + W * 64 - 1) / (W * 64);  // elements of the new rows per thread
   E kn[NN], vn[NN];
@@ -253,12 +253,12 @@ __global__ __launch_bounds__(W * 64) void decode_any_kernel(
     const u32x4 z = {0u, 0u, 0u, 0u};
     qf[j] = col < G && d < D ? *reinterpret_cast<const u32x4*>(q + (size_t)b * q_row_stride + (size_t)(g * G + col) * D + d) : z;
   }
-  const int L = ctx_len[b];
-  const int n_split = min((L + split_tokens - 1) / split_tokens, (int)gridDim.x);
+  const Slice slice = decode_slice(L, split_tokens, (int)gridDim.x, sp);
+  const int n_split = slice.n, t0 = slice.t0, t1 = slice.t1;
   if (sp >= n_split) return;
-  const int t0 = sp * split_tokens, t1 = sp == n_split - 1 ? L : t0 + split_tokens;
-  const int n_blk = ((t1 + 15) >> 4) - blk0;
-  const int n = wave < n_blk ? (n_blk - wave + W - 1) / W : 0;  // this wavefront's blocks
+  const WaveBlocks blocks = wave_blocks(t0, t1, wave, W);  // this wavefront's
+  const int n = blocks.n;
+  int ids = lane < n ? bt_row[blocks.first + W * lane] : 0;
   const size_t piece = (size_t)16 * D * sizeof(E);
   const bool newest = fused && sp == n_split - 1;
   const char* const kc = reinterpret_cast<const char*>(k_cache);
@@ -302,8 +302,9 @@ __global__ __launch_bounds__(W * 64) void decode_any_kernel(
   __syncthreads();
   while (base < n) {
     int tail = 16;
-    if (base + 64 >= n && wave + W * (n - 1) == n_blk - 1) {  // f[0] is the slice's last block
-      tail = t1 - ((blk0 + n_blk - 1) << 4);
+    const int last = blocks.first + W * (n - 1);
+    if (base + 64 >= n && last == (t1 - 1) >> 4) {  // f[0] is the slice's last block
+      tail = t1 - (last << 4);
       if (newest) f[0].put_token(s_new[0], s_new[1], tail - 1, D, col, quad);
       if (tail < 16) f[0].clear_tail(tail, quad);
     }
@@ -326,7 +327,7 @@ __global__ __launch_bounds__(W * 64) void decode_any_kernel(
     base += 64;
     if (base < n) {
       nw = min(64, n - base);
-      ids = lane < nw ? bt_row[blk0 + wave + W * (base + lane)] : 0;
+      ids = lane < nw ? bt_row[blocks.first + W * (base + lane)] : 0;
       fetch(f[0], 0);
       if (nw > 1) fetch(f[1], 1);
     }
