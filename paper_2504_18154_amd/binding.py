@@ -162,8 +162,16 @@ def _row_stride(t) -> int:
     return stride[0] if shape[0] > 1 else shape[1] * shape[2]
 
 
-def _stream():
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())  # torch.cuda.current_stream().cuda_stream
+def _stream_source(c=torch._C):
+    """What hands out torch.cuda.current_stream().cuda_stream: through two functions of torch's private module where it has
+    them (the public call builds a Stream object around the handle), through the public call where it has not."""
+    if hasattr(c, "_cuda_getCurrentRawStream") and hasattr(c, "_cuda_getDevice"):
+        handle, device = c._cuda_getCurrentRawStream, c._cuda_getDevice
+        return lambda: handle(device())
+    return lambda: torch.cuda.current_stream().cuda_stream
+
+
+_stream = _stream_source()
 
 
 class Context:

@@ -132,3 +132,17 @@ def test_split_merge_identity_in_fp64():
         w = np.exp(m - M)
         out = (acc * w[:, None]).sum(0) / (l * w).sum()
         np.testing.assert_allclose(out, ref, rtol=0, atol=1e-13)
+
+
+def test_the_stream_handle_does_not_depend_on_torchs_private_functions(binding, monkeypatch):
+    """With the two private functions and without them, the binding hands out the current stream's handle."""
+    class Private:
+        _cuda_getDevice = staticmethod(lambda: 3)
+        _cuda_getCurrentRawStream = staticmethod(lambda device: 1000 + device)
+
+    class Stream:
+        cuda_stream = 77
+
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: Stream)
+    assert binding._stream_source(Private)() == 1003
+    assert binding._stream_source(object())() == 77
