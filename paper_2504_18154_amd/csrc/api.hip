@@ -104,10 +104,12 @@ int ensure_partial_states(ecoserve_ctx* c) {
 int alloc_fixed_workspace(ecoserve_ctx* c) {
   const size_t meta_bytes = ((size_t)c->max_batch + 19) * sizeof(int32_t);
   // a prefill batch cannot bring more new tokens than the pool holds
-  // (T / 128 + min(B, T) is what a call is held to; it has at most G times as many tiles)
+  // (T / 128 + min(B, T) is what a call is held to, whatever the layout; the list is (bf16, 128)'s, with at most G times
+  // as many tiles)
   c->plan_tiles = prefill_plan_tiles(c->max_batch, (int32_t)std::min<int64_t>(
                                                         (int64_t)c->lay.num_blocks * kBlockSize, 0x7fffffffLL), 1);
-  const size_t plan_records = (size_t)(c->plan_tiles + 1) * (c->lay.num_q_heads / c->lay.num_kv_heads);
+  const bool listed = c->lay.dtype == ECOSERVE_BF16 && c->lay.head_dim == 128;
+  const size_t plan_records = listed ? (size_t)(c->plan_tiles + 1) * (c->lay.num_q_heads / c->lay.num_kv_heads) : 0;
   const size_t plan_bytes = ((size_t)kPlanHeaderInts + plan_records * kRecInts) * sizeof(int32_t);
   if (hipMalloc(&c->ws_meta, meta_bytes) != hipSuccess || hipMalloc(&c->ws_plan, plan_bytes) != hipSuccess) {
     (void)hipGetLastError();

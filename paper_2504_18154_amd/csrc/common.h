@@ -97,7 +97,7 @@ struct ecoserve_ctx {
   uint32_t* ws_count;          // [max_batch][Hkv], zero between launches: slices of a (sequence, K/V head) that are done
   int32_t ws_splits;
   int32_t* ws_plan;            // prefill plan: header and one record per query tile of the last prefill launch
-  int64_t plan_tiles;          // largest T / 128 + min(B, T) a prefill call may have; ws_plan has room for G records each
+  int64_t plan_tiles;          // largest T / 128 + min(B, T) a prefill call may have; ws_plan has room for G records each (bf16, D = 128)
   int plan_parity;             // which of the plan's two sets of queue counters the next prefill launch takes
   struct {                     // the batch the tile list in ws_plan was made for (valid = false: none)
     bool valid;

@@ -145,3 +145,17 @@ def test_prefill_of_many_short_prompts(dtype, D, Hq, Hkv):
     compare("prefill", out, ref, dtype)
     compare_lse("prefill", lse, ref_lse, dtype)
     layer.close()
+
+
+def test_workspace_does_not_hold_a_tile_list_for_layouts_that_have_none():
+    """The list of query tiles is what the workspace grows by with the pool: G records of 80 bytes per 128 tokens for (bf16,
+    128), and nothing for the other layouts, whatever their group size."""
+    from paper_2504_18154_amd import binding
+    blocks = 1 << 16
+    for dtype, D, Hq, want in (("f32", 64, 32, 0), ("bf16", 64, 2, 0), ("bf16", 128, 2, 80 * blocks // 8), ("bf16", 128, 32, 16 * 80 * blocks // 8)):
+        sizes = []
+        for n in (8, 8 + blocks):
+            ctx = binding.Context(Hq, 2, D, n, dtype, 1, 8)
+            sizes.append(ctx.workspace_bytes())
+            ctx.close()
+        assert sizes[1] - sizes[0] == want, (dtype, D, Hq, sizes)
