@@ -61,6 +61,14 @@ class Layer:
                            max_new_len=max_new_len)
         orc.kv_append(self.shape, self.okc, self.ovc, wl.to_bits(k_new), wl.to_bits(v_new), cu_q, ctx_before, table)
 
+    def wipe_newest(self, table, ctx_len):
+        """Overwrites the last token of every sequence with NaN rows in the device's cache (and not in the oracle's): what a
+        fused append has to bring back."""
+        n = len(ctx_len)
+        wipe = torch.full((n, self.model.Hkv, self.model.D), float("nan"), dtype=self.kc.dtype, device="cuda")
+        self.ctx.kv_append(self.kc, self.vc, wipe, wipe, dev_i32(np.arange(n + 1)), dev_i32(np.asarray(ctx_len) - 1), dev_i32(table),
+                           max_new_len=1)
+
     def assert_cache_bit_exact(self):
         torch.cuda.synchronize()
         gk = wl.to_bits(self.ctx.k_logical(self.kc))

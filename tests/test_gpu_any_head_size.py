@@ -85,11 +85,12 @@ def test_decode_over_contexts_of_several_slices(dtype, D):
         compare("decode", out, ref, dtype)
         compare_lse("decode", lse, ref_lse, dtype)
         last = torch.as_tensor(pb.cu_q[1:] - 1, dtype=torch.long)
-        fused = torch.full_like(out, float("nan"))
+        fused, fused_lse = torch.full_like(out, float("nan")), torch.full_like(lse, float("nan"))
+        layer.wipe_newest(pb.block_table, lens)
         layer.ctx.attn_decode_append(q.cuda(), k[last].cuda(), v[last].cuda(), layer.kc, layer.vc, dev_i32(pb.block_table), dev_i32(lens),
-                                     fused, int(lens.max()))
+                                     fused, int(lens.max()), fused_lse)
         torch.cuda.synchronize()
-        assert torch.equal(fused, out), "the fused append changes the result"
+        assert torch.equal(fused, out) and torch.equal(fused_lse, lse), "the fused append changes the result"
         layer.assert_cache_bit_exact()
         layer.close()
 
@@ -119,6 +120,74 @@ def test_infinite_values_reach_only_the_rows_that_see_them(dtype, D):
     assert (got[fin].float() - want[fin].float()).abs().max() <= tol
     assert (gd.float() - wd.float())[torch.isfinite(wd)].abs().max() <= tol
     assert (glse - wlse).abs().max() <= 1e-4
+    layer.close()
+
+
+@pytest.mark.parametrize("dtype,D,prompts", [("f32", 64, 1), ("bf16", 96, 1), ("f32", 64, 12), ("bf16", 96, 12)],
+                         ids=["f32-d64", "bf16-d96", "f32-d64-shared-rows", "bf16-d96-shared-rows"])
+def test_infinite_values_in_long_contexts_and_shared_rows(dtype, D, prompts):
+    """The same where the row that is taken again is one of a tile whose rows are shared out (12 prompts with 32 query heads), and
+    where a decode step's context is cut into slices: infinities in the first, a middle and the last of nine, the last one in
+    the token that the fused append brings."""
+    from paper_2504_18154_amd import binding
+    model = wl.ModelShape(f"{dtype}-d{D}", 32, 2, D, 1, dtype)
+    lens = np.asarray([2300] if prompts == 1 else [70] * prompts, dtype=np.int32)
+    pb = wl.prefill_batch(model, lens, 79)
+    layer = Layer(model, pb.num_blocks, pb.B, pb.block_table.shape[1])
+    k, v, q = (wl.randn((pb.T, h, D), dtype, s) for s, h in ((1, 2), (2, 2), (3, 32)))
+    bad = [(33, 5), (1100, 6), (2299, 7)] if prompts == 1 else [(33, 5), (150, 6), (pb.T - 1, 7)]
+    for t, d in bad:
+        v[t, 1, d] = float("inf")
+    layer.append(k, v, pb.cu_q, pb.ctx_before, pb.block_table)
+    last = torch.as_tensor(pb.cu_q[1:] - 1, dtype=torch.long)
+    rows = slice(None) if prompts > 1 else slice(1000, 1200)  # (the plain kernels' time; a chunk behind 1000 cached tokens)
+    cu, before = (pb.cu_q, pb.ctx_before) if prompts > 1 else (wl.cu_from_lengths([200]), np.asarray([1000], np.int32))
+
+    def both():
+        out, lse = layer.prefill_gpu(q[rows], cu, before, pb.block_table)
+        layer.wipe_newest(pb.block_table, lens)
+        dec = torch.full((pb.B, 32, D), float("nan"), dtype=q.dtype, device="cuda")
+        dec_lse = torch.full((pb.B, 32), float("nan"), dtype=torch.float32, device="cuda")
+        layer.ctx.attn_decode_append(q[last].cuda(), k[last].cuda(), v[last].cuda(), layer.kc, layer.vc, dev_i32(pb.block_table), dev_i32(lens),
+                                     dec, int(lens.max()), dec_lse)
+        torch.cuda.synchronize()
+        return out, lse, dec, dec_lse
+
+    got = both()
+    layer.assert_cache_bit_exact()
+    layer.ctx.set_option(binding.OPT_FORCE_PLAIN, 1)
+    want = both()
+    tol = 2.0 ** -6 if dtype == "bf16" else 1e-5  # (as above)
+    for g, w in zip(got[::2], want[::2]):
+        fin = torch.isfinite(w)
+        assert torch.equal(torch.isfinite(g), fin) and torch.equal(torch.isinf(g), torch.isinf(w))
+        assert not fin.all() and (g[fin].float() - w[fin].float()).abs().max() <= tol
+    for g, w in zip(got[1::2], want[1::2]):
+        assert (g - w).abs().max() <= 1e-4
+    layer.close()
+
+
+@pytest.mark.parametrize("dtype,D,Hq,Hkv,before,new", [
+    ("f32", 64, 32, 2, [1021, 1023, 1024, 2100, 0, 3, 60] + [5] * 6, [3] * 13), ("bf16", 96, 32, 2, [1021, 1023, 1024, 2100] + [0] * 9, [3] * 13),
+    ("f32", 256, 32, 2, [1022, 1030] + [0] * 10, [2, 5] + [1] * 10), ("f32", 64, 4, 2, [4090, 8300], [7, 3]), ("bf16", 80, 4, 4, [4094, 60], [4, 9])],
+    ids=["f32-d64-shared-rows", "bf16-d96-shared-rows", "f32-d256-shared-rows", "f32-d64-shared-keys", "bf16-d80-shared-keys"])
+def test_prefill_behind_long_prefixes(dtype, D, Hq, Hkv, before, new):
+    """A wavefront walks its blocks 64 ids at a time: rows that see more than 1024 keys (rows shared out: each wavefront walks them
+    all), or more than 4096 (keys shared out: every fourth block), at and beside the first change of ids, and the second."""
+    model = wl.ModelShape(f"{dtype}-d{D}", Hq, Hkv, D, 1, dtype)
+    before, new = np.asarray(before, np.int32), np.asarray(new, np.int32)
+    say(f"{dtype}, head size {D}, heads {Hq}/{Hkv}: prefill {new.tolist()} behind {before.tolist()}")
+    pb = wl.prefill_batch(model, before + new, 92)
+    layer = Layer(model, pb.num_blocks, len(new), pb.block_table.shape[1])
+    rows = lambda n, h, seed: wl.randn((int(n), h, D), dtype, seed)
+    layer.append(rows(before.sum(), Hkv, 1), rows(before.sum(), Hkv, 2), wl.cu_from_lengths(before), np.zeros_like(before), pb.block_table)
+    cu = wl.cu_from_lengths(new)
+    layer.append(rows(new.sum(), Hkv, 3), rows(new.sum(), Hkv, 4), cu, before, pb.block_table)
+    q = rows(new.sum(), Hq, 5)
+    out, lse = layer.prefill_gpu(q, cu, before, pb.block_table)
+    ref, ref_lse = layer.prefill_oracle(q, cu, before, pb.block_table)
+    compare("prefill", out, ref, dtype)
+    compare_lse("prefill", lse, ref_lse, dtype)
     layer.close()
 
 

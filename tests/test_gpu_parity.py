@@ -373,7 +373,8 @@ def test_bf16_decode_random_batches():
 def test_bf16_decode_passes_over_sequences_without_tokens():
     """A context length of zero is not a valid decode input (the step's own token counts), but a batch that
     holds one - first, last or in the middle, alone or several in a row - must not cost the other sequences
-    their results: their rows are held to the oracle, the empty sequences' rows are left alone."""
+    their results: their rows are held to the oracle, the empty sequences' rows are left alone.  (With the automatic split
+    the batch is small enough for the single launch; the persistent kernel has its own such test beside that kernel's.)"""
     model = M30
     lens = np.asarray([0, 700, 0, 0, 33, 257, 0, 1500, 16, 0], dtype=np.int32)
     say(f"bf16 decode with empty sequences in the batch {lens.tolist()}")

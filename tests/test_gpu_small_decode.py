@@ -34,14 +34,86 @@ def test_small_decode_batches(heads, lens):
     again, lse2 = layer.decode_gpu(q, pb.block_table, lens)
     assert torch.equal(again, out) and torch.equal(lse2, lse), "a second call differs"
     last = torch.as_tensor(pb.cu_q[1:] - 1, dtype=torch.long)
-    fused = torch.full_like(out, float("nan"))
+    fused, fused_lse = torch.full_like(out, float("nan")), torch.full_like(lse, float("nan"))
+    layer.wipe_newest(pb.block_table, lens)
     layer.ctx.attn_decode_append(q.cuda(), k[last].cuda(), v[last].cuda(), layer.kc, layer.vc, dev_i32(pb.block_table), dev_i32(lens),
-                                 fused, int(lens.max()))
+                                 fused, int(lens.max()), fused_lse)
     no = torch.full_like(out, float("nan"))
     st = binding.attn_decode_noalloc(layer.ctx.layout, q.cuda(), layer.kc, layer.vc, dev_i32(pb.block_table), dev_i32(lens), no, int(lens.max()))
     assert st == binding.OK
     torch.cuda.synchronize()
-    assert torch.equal(fused, out), "the fused append changes the result"
+    assert torch.equal(fused, out) and torch.equal(fused_lse, lse), "the fused append changes the result"
     assert torch.equal(no, out), "the call without a context differs"
     layer.assert_cache_bit_exact()
+    layer.close()
+
+
+@pytest.mark.parametrize("lens,bound", [([9000, 20], 16), ([30] * 32 + [4200], 512)], ids=["eight-wavefronts", "four-wavefronts"])
+def test_a_bound_on_the_lengths_that_is_too_low_costs_time_only(lens, bound):
+    """max_ctx_len is to be an upper bound; the persistent kernel never used it, and where this kernel's grid ends short of a
+    context its last slice takes the rest: more blocks than the 64 ids a wavefront holds, so it walks them in windows."""
+    model = wl.ModelShape("small", 40, 8, 128, 1, "bf16")
+    lens = np.asarray(lens, dtype=np.int32)
+    pb = wl.prefill_batch(model, lens, 56)
+    layer = Layer(model, pb.num_blocks, pb.B, pb.block_table.shape[1])
+    layer.append(*(wl.randn((pb.T, 8, 128), "bf16", s) for s in (1, 2)), pb.cu_q, pb.ctx_before, pb.block_table)
+    q = wl.randn((pb.B, 40, 128), "bf16", 3)
+    ref, ref_lse = layer.decode_oracle(q, pb.block_table, lens)
+    out, lse = layer.decode_gpu(q, pb.block_table, lens, max_ctx_len=bound)
+    compare("decode", out, ref, "bf16")
+    compare_lse("decode", lse, ref_lse, "bf16")
+    layer.close()
+
+
+@pytest.mark.parametrize("lens", [[300, 40], [3000, 40]], ids=["one-slice", "slices"])
+def test_infinite_values_reach_only_their_own_elements(lens):
+    """Infinite V elements (the weights' remainders are zero for some keys, and must not make them NaN), one of them in the token
+    that the fused append brings: infinite there, elsewhere as the plain kernels have it."""
+    model = wl.ModelShape("small", 40, 8, 128, 1, "bf16")
+    lens = np.asarray(lens, dtype=np.int32)
+    pb = wl.prefill_batch(model, lens, 57)
+    layer = Layer(model, pb.num_blocks, pb.B, pb.block_table.shape[1])
+    k, v = (wl.randn((pb.T, 8, 128), "bf16", s) for s in (1, 2))
+    for t, g, d in ((33, 1, 5), (int(lens[0]) // 2, 1, 6), (int(lens[0]) - 1, 2, 7)):
+        v[t, g, d] = float("inf")
+    layer.append(k, v, pb.cu_q, pb.ctx_before, pb.block_table)
+    q = wl.randn((pb.B, 40, 128), "bf16", 3)
+    last = torch.as_tensor(pb.cu_q[1:] - 1, dtype=torch.long)
+    res = []
+    for plain in (0, 1):
+        layer.ctx.set_option(binding.OPT_FORCE_PLAIN, plain)
+        layer.wipe_newest(pb.block_table, lens)
+        out = torch.full((pb.B, 40, 128), float("nan"), dtype=torch.bfloat16, device="cuda")
+        layer.ctx.attn_decode_append(q.cuda(), k[last].cuda(), v[last].cuda(), layer.kc, layer.vc, dev_i32(pb.block_table), dev_i32(lens), out,
+                                     int(lens.max()))
+        torch.cuda.synchronize()
+        layer.assert_cache_bit_exact()
+        res.append(out.float())
+    got, want = res
+    fin = torch.isfinite(want)
+    assert torch.isinf(want[0, 5:10, 5:7]).all() and torch.isinf(want[0, 10:15, 7]).all() and int((~fin).sum()) == 15
+    assert torch.equal(torch.isfinite(got), fin) and torch.equal(torch.isinf(got), torch.isinf(want))
+    assert (got[fin] - want[fin]).abs().max() <= 2.0 ** -6   # half a spacing of bf16 (2^-7 of |o| < 4) each, and the weights' 2^-17
+    layer.close()
+
+
+def test_the_persistent_kernel_passes_over_sequences_without_tokens():
+    """A batch too large for the single launch (40 sequences of up to 1500 tokens: 640 slices for 256 workgroups), with lengths of zero first,
+    in the middle, several in a row, and last; with a context and without."""
+    model = wl.ModelShape("30B-heads", 40, 8, 128, 1, "bf16")
+    rng = np.random.default_rng(58)
+    lens = np.r_[0, 0, 700, 0, rng.integers(1, 600, size=15), 0, 0, 1500, 0, rng.integers(1, 600, size=15), 16, 0].astype(np.int32)
+    pb = wl.prefill_batch(model, np.maximum(lens, 1), 59)
+    layer = Layer(model, pb.num_blocks, len(lens), pb.block_table.shape[1])
+    layer.append(*(wl.randn((int(lens.sum()), 8, 128), "bf16", s) for s in (1, 2)), wl.cu_from_lengths(lens), np.zeros_like(lens), pb.block_table)
+    q = wl.randn((len(lens), 40, 128), "bf16", 3)
+    live = np.flatnonzero(lens > 0)
+    ref, ref_lse = layer.decode_oracle(q[live], pb.block_table[live], lens[live])
+    out, lse = layer.decode_gpu(q, pb.block_table, lens)
+    no = torch.full_like(out, float("nan"))
+    assert binding.attn_decode_noalloc(layer.ctx.layout, q.cuda(), layer.kc, layer.vc, dev_i32(pb.block_table), dev_i32(lens), no, 1500) == binding.OK
+    torch.cuda.synchronize()
+    compare("rows of the non-empty sequences", out, ref, "bf16", rows=live)
+    compare_lse("rows of the non-empty sequences", lse, ref_lse, "bf16", rows=live)
+    compare("without a context", no, ref, "bf16", rows=live)
     layer.close()

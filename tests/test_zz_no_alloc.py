@@ -49,8 +49,12 @@ def test_noalloc_decode_matches_the_context_call_twice_in_a_row():
     _decode_both_ways(model, np.r_[1, 15, 16, 17, 2049, rng.integers(1, 3000, size=91)].astype(np.int32), 901)
     say("noalloc decode: 5 sequences right after it (the scratch array still holds the larger call's states)")
     _decode_both_ways(model, np.array([700, 3, 64, 1, 129], dtype=np.int32), 902)
-    say("noalloc decode: group size 8, one long sequence cut into hundreds of pieces")
+    say("noalloc decode: group size 8, one long sequence in slices, small enough for the single launch")
     _decode_both_ways(wl.ModelShape("70B-heads", 64, 8, 128, 1, "bf16"), np.array([8000, 40], dtype=np.int32), 903)
+    # (544 slices of 1024 tokens are more than run at once: the persistent kernel, about 125 states per (sequence, head), so the
+    # merge of the cut ones goes through its rounds of 64)
+    say("noalloc decode: group size 8, one long sequence cut into hundreds of pieces")
+    _decode_both_ways(wl.ModelShape("70B-heads", 64, 8, 128, 1, "bf16"), np.array([34000, 40], dtype=np.int32), 904)
 
 
 def test_noalloc_decode_rejects_what_it_cannot_hold():
