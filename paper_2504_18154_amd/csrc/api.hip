@@ -400,7 +400,7 @@ int ecoserve_attn_prefill_strided(ecoserve_ctx* c, const void* q, int64_t q_row_
     const bool same = c->opt_reuse_plan && key.valid && key.cu_q == cu_q && key.ctx_before == ctx_before &&
                       key.block_table == block_table && key.bt_stride == bt_stride && key.B == B && key.T == T &&
                       key.n_wg == grid;
-    e = launch_prefill_mfma(a, cu_q, ctx_before, T, max_q_len, c->ws_plan, n_wgs, !same, c->plan_parity, s);
+    e = launch_prefill_mfma(a, cu_q, ctx_before, T, c->ws_plan, n_wgs, !same, c->plan_parity, s);
     c->plan_parity ^= 1;
     key.valid = e == hipSuccess;
     key.cu_q = cu_q;

@@ -188,30 +188,6 @@ __device__ __forceinline__ float mask_and_max(f32x16 (&s)[2], int k0, int half, 
   return across_halves(bm);
 }
 
-// Scores of one 32-key accumulator -> bf16 weights 2^(s c - mc) (two B-operand fragments of
-// 8 keys each); the weights as rounded are added to this lane's share of the row sum.
-__device__ __forceinline__ void exp_tile(const f32x16& s, bf16x8 (&pf)[2], float& l, float mc, float c) {
-  const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
-  float l0 = l, l1 = 0.f;
-#pragma unroll
-  for (int i = 0; i < 16; i += 4) {
-    const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[i + 0], c, -mc));
-    const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[i + 1], c, -mc));
-    const float p2 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[i + 2], c, -mc));
-    const float p3 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[i + 3], c, -mc));
-    const bf16x2 a = {(__bf16)p0, (__bf16)p1};
-    const bf16x2 b = {(__bf16)p2, (__bf16)p3};
-    l0 = __builtin_amdgcn_fdot2_f32_bf16(a, ones, l0, false);
-    l1 = __builtin_amdgcn_fdot2_f32_bf16(b, ones, l1, false);
-    const int f = i >> 3, e = i & 7;
-    pf[f][e + 0] = a[0];
-    pf[f][e + 1] = a[1];
-    pf[f][e + 2] = b[0];
-    pf[f][e + 3] = b[1];
-  }
-  l = l0 + l1;
-}
-
 // ---- plan: the query tiles of a batch, heaviest first ------------------------------------------
 //
 // Plan layout (int32): [0] number of query tiles,
@@ -873,7 +849,7 @@ int32_t prefill_mfma_grid(const AttnArgs& a, int32_t T, int32_t n_persistent_wgs
 }
 
 hipError_t launch_prefill_mfma(const AttnArgs& a, const int32_t* cu_q, const int32_t* ctx_before, int32_t T,
-                               int32_t max_q_len, int32_t* ws_plan, int32_t n_persistent_wgs, bool make_plan,
+                               int32_t* ws_plan, int32_t n_persistent_wgs, bool make_plan,
                                int parity, hipStream_t s) {
   const int G = a.Hq / a.Hkv;
   const int64_t max_tiles = prefill_plan_tiles(a.B, T, G);
@@ -883,7 +859,6 @@ hipError_t launch_prefill_mfma(const AttnArgs& a, const int32_t* cu_q, const int
   if (make_plan)
     hipLaunchKernelGGL(prefill_plan_kernel, dim3(1), dim3(kPlanThreads), 0, s, cu_q, ctx_before, a.block_table,
                        a.bt_stride, a.B, (int)n_wg, (int)max_tiles, G, make_divisor((uint32_t)G), ws_plan);
-  (void)max_q_len;
   hipLaunchKernelGGL(prefill_mfma_kernel, dim3((unsigned)n_wg), dim3(256), 0, s, (const uint16_t*)a.q, a.q_row_stride,
                      (const char*)a.k_cache, (const char*)a.v_cache, a.block_table, a.bt_stride, (uint16_t*)a.out,
                      a.lse, ws_plan, parity, a.Hq, a.Hkv, G, make_divisor((uint32_t)G), make_divisor((uint32_t)a.Hkv), a.scale_log2e);

@@ -188,7 +188,7 @@ hipError_t launch_decode_mfma_merge(const AttnArgs& a, const int32_t* ctx_len, c
 // of an earlier launch for the same batch and grid is still in ws_plan; parity alternates from launch to launch)
 int32_t prefill_mfma_grid(const AttnArgs& a, int32_t T, int32_t n_persistent_wgs);
 hipError_t launch_prefill_mfma(const AttnArgs& a, const int32_t* cu_q, const int32_t* ctx_before, int32_t T,
-                               int32_t max_q_len, int32_t* ws_plan, int32_t n_persistent_wgs, bool make_plan,
+                               int32_t* ws_plan, int32_t n_persistent_wgs, bool make_plan,
                                int parity, hipStream_t s);
 
 }  // namespace eco
