@@ -684,7 +684,7 @@ def run_tiny(E: Env, args):
     torch.cuda.synchronize()
     gpu_ms = e0.elapsed_time(e1) / reps
     r = {"workload": "BASELINE config index 0: tiny PaDG cycle, fp32, 4 q / 2 kv heads, D 64: prefill-only batch (37 + 100 tokens), "
-                     "then 8 decode-only steps (plain kernels; 18 launches, launch-bound by construction)",
+                     "then 8 decode-only steps (fp32 matrix-core kernels; 18 launches, launch-bound by construction)",
          "gpu_ms_per_cycle": gpu_ms, "launches_per_cycle": 18, "roofline": None}
     if not args.no_cpu_baseline:
         from oracle import oracle as orc

@@ -28,7 +28,10 @@
  *   - One call handles one layer; callers loop over layers.
  *   - Calls that share a context must be issued on one stream (or be ordered
  *     by the caller): they share the context's workspace (split-context partial
- *     states of decode, the query-tile list of prefill).
+ *     states and merge counters of decode, the query-tile list and its queues'
+ *     counters of prefill).  Calls that overlap all the same may spoil their own
+ *     results and those of later calls on the context (a counter left away from
+ *     its start); a new context is free of that.
  *   - With the default options the hot calls may be recorded into a HIP graph
  *     (they neither allocate nor synchronise, and record no memset nodes).
  *     Options whose state advances on the host from call to call
@@ -213,7 +216,8 @@ int ecoserve_attn_prefill(ecoserve_ctx* ctx, const void* q, const void* k_cache,
  *   q           : dev, E[B][Hq][D]
  *   ctx_len     : dev, int32[B]
  *   out         : dev, E[B][Hq][D];  lse : dev, float[B][Hq] or NULL
- *   max_ctx_len : upper bound on ctx_len[] (sizes the launch);
+ *   max_ctx_len : upper bound on ctx_len[] (sizes the launch; a loose one may pick
+ *                 a kernel meant for larger batches);
  *                 must be <= max_blocks_per_seq * block_size and <= bt_stride * block_size
  */
 int ecoserve_attn_decode(ecoserve_ctx* ctx, const void* q, const void* k_cache, const void* v_cache,

@@ -19,10 +19,13 @@
 //
 // What bounds them: such batches are small (tens of MB of K/V at most), so a step is latency: launches, the chain
 // length -> block ids -> blocks, and the walk of the blocks.  Hence decode takes contexts up to 1024 tokens in one
-// launch, eight wavefronts per (sequence, K/V head) and the step's append inside (one launch instead of three).
+// launch, eight wavefronts per (sequence, K/V head) (four for large heads and for batches of more than one workgroup per
+// CU) and the step's append inside (one launch instead of three).
 // Measured beside the plain kernels (one wavefront per query row, a scalar product per lane): a prompt batch of 4 x
-// 50..600 tokens and 8 decode steps, bf16, head size 64, 32/8 heads: 399 -> 61 us (prefill kernel 243 -> 10 us, a
-// decode step's kernels 21.9 -> 5.6 us); 4 x 37..700 tokens in fp32, 4/2 heads: 195 -> 72 us (55 -> 8 us, 19.1 -> 7 us).
+// 50..600 tokens and 8 decode steps, bf16, head size 64, 32/8 heads: 398 -> 65 us (prefill kernel 243 -> 11 us, a
+// decode step's kernels 21.8 -> 6.1 us); 4 x 37..700 tokens in fp32, 4/2 heads: 195 -> 75 us (55 -> 8 us, 19.1 -> 7.8 us).
+// Not gained: a prompt of 8 tokens or fewer with nothing cached (a graph of such calls: 0.2 to 0.9 us more than the plain
+// kernel's 3 to 8); with 40 to 100 tokens cached, which the host cannot see, the plain kernel takes up to six times as long.
 #include <algorithm>
 #include <type_traits>
 
@@ -264,8 +267,9 @@ __global__ __launch_bounds__(W * 64) void decode_any_kernel(
   const char* const kc = reinterpret_cast<const char*>(k_cache);
   const char* const vc = reinterpret_cast<const char*>(v_cache);
 
-  // The blocks are walked in windows of the 64 ids a register holds (one window for slices up to 1024 W tokens), two in
-  // flight.  A wavefront's last block comes first in its window: it may be the slice's last one, and what that needs
+  // The blocks are walked in windows of the 64 ids a register holds, two blocks in flight.  Slices are at most 1024 W tokens
+  // and take one window; a second one is for a context longer than the caller's max_ctx_len, which the persistent kernel
+  // never minded and whose last slice takes the rest here.  A wavefront's last block comes first in its window: it may be the slice's last one, and what that needs
   // (the newest token, the slots behind the end) then stands once, in front of the loop - a short context is latency
   // from the first instruction on, and code that runs once costs its fetch.
   Blk f[2];
@@ -680,11 +684,12 @@ void launch_prefill_typed(const AttnArgs& a, const int32_t* cu_q, const int32_t*
     };
     // Batches too small to fill the chip share the keys of 16 rows out instead of the rows, unless the prompts are so short
     // that there is little to share.  The line (rows x head size, against 5 Mi, or in proportion for prompts below 256
-    // tokens on average) lies between what was measured to gain and to lose by it, us: fp32, 64: 4 x 350 tokens 37 -> 13,
-    // 16 x 100 15 -> 8; fp32, 128, 6 heads: 8 x 300 59 -> 44, 32 x 300 113 -> 148; bf16, 64, 32 heads: 4 x 330 25 -> 22,
-    // 4 x 600 53 -> 43, 8 x 600 67 -> 75, 16 x 100 14 -> 18, 100 x 20 12 -> 24; bf16, 256, 8 heads: 4 x 300 34 -> 27, 40 x 16
-    // 9 -> 15, 64 x 100 47 -> 94 (both ways before the walk below stopped asking for blocks that do not exist; with that
-    // the first of each pair that gains: 11, 8, 35, 18, 19 us).
+    // tokens on average) lies between what gains and what loses by it (us, rows shared / keys shared): fp32, 64, 4 heads:
+    // 4 x 350 tokens 33 / 11, 16 x 100 13 / 7; fp32, 128, 6 heads: 8 x 300 50 / 36, 32 x 300 96 / 120; bf16, 64, 32 heads:
+    // 4 x 330 23 / 18, 4 x 600 44 / 39, 8 x 600 70 / 70, 16 x 100 11 / 16, 100 x 20 12 / 21; bf16, 256, 8 heads: 4 x 300 21 / 20,
+    // 40 x 16 7 / 11, 64 x 100 34 / 75.  It is good to a factor of two: head sizes of 128 in fp32 and of 256 meet at half of
+    // it (bf16, 256, 8 x 300, keys shared: 38 where rows would take 29), few long prompts at 1.2 times it (bf16, 64, 1 x
+    // 3000, rows shared: 207 where keys would take 152).
     const int64_t line = std::min<int64_t>((int64_t)5 << 20, ((int64_t)5 << 12) * T / a.B);
     if ((int64_t)T * a.Hq * (32 * KS) <= line) launch(prefill_any_kernel<E, KS, 1, true>, 16);
     else launch(prefill_any_kernel<E, KS, NC, false>, 64 * NC);
@@ -714,8 +719,8 @@ void launch_decode_typed(const AttnArgs& a, const int32_t* ctx_len, int32_t spli
 }  // namespace
 
 // Contexts up to 1024 tokens stay whole (no merge); longer ones are cut into slices of 256 tokens, or of 512 or 1024
-// when that already makes enough workgroups.  (One sequence of 2000 / 8000 tokens, 8 K/V heads: 10.5 / 17.6 us in slices
-// of 256, 11.2 / 15.6 of 512, 13.7 / 18.6 of 1024.)
+// when that already makes enough workgroups.  (8 K/V heads, bf16, 128, us in slices of 256 / 512 / 1024: one sequence of 2000
+// tokens 9.6 / 10.3 / 12.7, of 8000 14.9 / 12.6 / 13.8; 4 x 2000 11.1 / 10.9 / 13.3.)
 int32_t decode_any_split_tokens(int32_t B, int32_t Hkv, int32_t max_ctx_len, int32_t num_cu) {
   int32_t st = max_ctx_len > 1024 ? 256 : 1024;
   while (st < 1024 && (int64_t)B * Hkv * ((max_ctx_len + st - 1) / st) > num_cu / 2) st *= 2;
@@ -724,10 +729,10 @@ int32_t decode_any_split_tokens(int32_t B, int32_t Hkv, int32_t max_ctx_len, int
 
 // For (bf16, 128): whether the batch is small enough for this kernel, i.e. all its workgroups run at once - one of eight
 // wavefronts per CU, or (short contexts) two of four.  It needs no numbering of the batch and no second launch, which
-// is what such a batch spends its time on in the persistent kernel (us per layer there and here, 8 K/V heads: 1 x 777
-// tokens 14.6, 9.7; 1 x 8000: 32.0, 15.6; 4 x 2000: 22.5, 14.5; 16 x 1000: 22.7, 19.0; 32 x 200: 17.2, 11.6; 64 x 500:
-// 38.7, 30.2), but nothing evens out the lengths of more workgroups than fit: 128 sequences around 500 tokens, lognormal,
-// take 66 there and 73 to 88 here.
+// is what such a batch spends its time on in the persistent kernel (us per call there and here, 40 query heads on 8 K/V
+// heads, the same buffers from call to call: 1 x 777 tokens 14.7, 9.0; 1 x 8000: 30.3, 12.7; 4 x 2000: 21.1, 11.0; 16 x 1000:
+// 20.7, 14.1; 32 x 200: 15.7, 7.4; 64 x 500: 35.0, 23.5), but nothing evens out the lengths of more workgroups than fit: 128
+// sequences around 500 tokens, lognormal, take 62 there and 74 here, 40 of them 25 and 28 (128 of 500 each: 54 and 50).
 bool decode_any_fits(int32_t B, int32_t Hkv, int32_t max_ctx_len, int32_t split_tokens, int32_t num_cu) {
   const int64_t pairs = (int64_t)B * Hkv;
   return pairs * ((max_ctx_len + split_tokens - 1) / split_tokens) <= num_cu || (max_ctx_len <= 512 && pairs <= 2 * num_cu);

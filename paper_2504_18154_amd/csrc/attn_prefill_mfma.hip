@@ -204,8 +204,9 @@ __device__ __forceinline__ float mask_and_max(f32x16 (&s)[2], int k0, int half, 
 // load.
 // Where a prompt's tiles begin: S G = 128 n + r rows (0 < r < 128) have one ragged tile of r rows.  As the last tile it
 // would cost as many key steps as a full one (its rows see the whole prompt); as the first it costs those of the first
-// r / G positions.  Moving it to the front shifts the other tiles by r / G positions, less than a key step, so at most
-// r / (64 G) of them gain a step.  Records are sorted by the number of key steps, largest first, with a counting sort
+// r / G positions.  Moving it to the front shifts the other tiles by r / G positions: for G >= 2 less than a key step (64), so
+// at most r / (64 G) of them gain a step; for G = 1 each may gain up to two, the two that a full tile spans, and the sum over
+// the prompt is then what it was.  Records are sorted by the number of key steps, largest first, with a counting sort
 // (the last class holds all tiles above it; the order inside a class is arbitrary).  A class is two key steps wide: it
 // then holds about G neighbouring tiles of a sequence, which a wavefront of the plan lists one behind the other, so the
 // workgroups that take them start together and share the K/V they stream through their XCD's L2 (with classes of one
@@ -213,7 +214,8 @@ __device__ __forceinline__ float mask_and_max(f32x16 (&s)[2], int k0, int half, 
 // Rows over the group against tiles of 128 positions of one head (kernel us, 8 K/V heads; before / now): 64 query heads,
 // 256 x 20 tokens 177 / 64, 256 x 40 194 / 120, 128 x 100 behind 100 cached 242 / 163, 4 x 512 36.0 / 33.4; 40 query
 // heads, 64 x 50 tokens 32.9 / 23.2, 16 x 93 20.6 / 16.2; the benchmark's 16 prompts of 128..4096 tokens 4% less, its
-// 8 x 8192 tokens the same.  (It also replaces a second kernel that packed the G heads of prompts up to 128 / G tokens.)
+// 8 x 8192 tokens the same (8.0 to 8.2 ms, within the noise; their list, G times as many records, takes 15 us instead
+// of 8).  (It also replaces a second kernel that packed the G heads of prompts up to 128 / G tokens.)
 __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(const int32_t* __restrict__ cu_q,
                                                                     const int32_t* __restrict__ ctx_before,
                                                                     const int32_t* __restrict__ block_table,
