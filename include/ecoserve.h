@@ -113,8 +113,9 @@ enum {
    * follow the speeds measured in the context's earlier decode calls (the XCDs of one device
    * differ by several percent and finish together only with unequal shares).  Results stay
    * within the tolerance of the split-context merge but are no longer bit-identical from call
-   * to call, because the cut points move with the measurements.  0 (default): equal shares,
-   * bit-reproducible. */
+   * to call, because the cut points move with the measurements.  Batches small enough for a single
+   * launch have no shares, and their results are bit-identical from call to call either way.
+   * 0 (default): equal shares, bit-reproducible. */
   ECOSERVE_OPT_DECODE_ADAPTIVE = 4,
   /* 1: consecutive ecoserve_attn_prefill calls (bf16, head size 128) that pass the same cu_q,
    * ctx_before and block_table pointers, bt_stride, B and T are taken to describe the same
