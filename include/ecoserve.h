@@ -133,7 +133,8 @@ enum { ECOSERVE_KERNEL_APPEND = 0, ECOSERVE_KERNEL_PREFILL = 1, ECOSERVE_KERNEL_
 
 /* Create a context on `device` for batches of at most max_batch sequences whose
  * block tables have at most max_blocks_per_seq entries per sequence.
- * Allocates the decode workspace (split-context partial results).  On failure
+ * Allocates the workspace (partial results of split contexts: a few MB for decode, and 65 MiB for
+ * prefill in bf16 layouts of head size 128 whose sequences may exceed 512 tokens).  On failure
  * *out is NULL. */
 int ecoserve_create(ecoserve_ctx** out, int device, const ecoserve_layout* layout,
                     int32_t max_batch, int32_t max_blocks_per_seq);
@@ -194,6 +195,9 @@ int ecoserve_kv_append(ecoserve_ctx* ctx, void* k_cache, void* v_cache, const vo
  *   T / 128 + min(B, T) must not exceed num_blocks / 8 + max_batch (a batch cannot bring more
  *   new tokens than the pool holds; the context's list of query tiles is sized for that), else
  *   ECOSERVE_EINVAL.  The list lives in the context's workspace: see the rule on sharing a context.
+ *   Batches of few query tiles behind long contexts (bf16, head size 128) have the keys of a tile
+ *   shared out among workgroups; partial states go through the workspace and are merged exactly,
+ *   in an order that the lengths, B, T and bt_stride decide.
  *   The workspace also carries, from one launch to the next, how long each workgroup was busy and
  *   the work queues' shares (ecoserve_debug_prefill_queue_shares): they decide which workgroup
  *   computes which query tile, never a result; out and lse of a call are the same bits whatever

@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "common.h"
+#include "prefill_shares.h"
 
 using namespace eco;
 
@@ -110,17 +111,24 @@ int alloc_fixed_workspace(ecoserve_ctx* c) {
                                                         (int64_t)c->lay.num_blocks * kBlockSize, 0x7fffffffLL), 1);
   const bool listed = c->lay.dtype == ECOSERVE_BF16 && c->lay.head_dim == 128;
   const size_t plan_records = listed ? (size_t)(c->plan_tiles + 1) * (c->lay.num_q_heads / c->lay.num_kv_heads) : 0;
-  const size_t plan_bytes = ((size_t)kPlanHeaderInts + plan_records * kRecInts) * sizeof(int32_t);
-  if (hipMalloc(&c->ws_meta, meta_bytes) != hipSuccess || hipMalloc(&c->ws_plan, plan_bytes) != hipSuccess) {
+  const size_t plan_bytes = (((size_t)kPlanHeaderInts + plan_records * kRecInts) * sizeof(int32_t) + 255) & ~(size_t)255;
+  // (contexts whose sequences are too short for it never share out a batch's key steps)
+  const bool pieces = listed && (int64_t)c->max_blocks_per_seq * kBlockSize >= 64 * kShareMinUnits;
+  const size_t piece_bytes = pieces ? (size_t)prefill_piece_floats(c->num_cu * kPrefillWgsPerCu) * sizeof(float) : 0;
+  // (one allocation: plan, pieces, numbering)
+  if (hipMalloc(&c->ws_plan, plan_bytes + piece_bytes + meta_bytes) != hipSuccess) {
     (void)hipGetLastError();
     return ECOSERVE_ENOMEM;
   }
+  char* const rest = reinterpret_cast<char*>(c->ws_plan) + plan_bytes;
+  if (pieces) c->ws_pieces = reinterpret_cast<float*>(rest);
+  c->ws_meta = reinterpret_cast<int32_t*>(rest + piece_bytes);
   // the plan's header carries state from one prefill launch to the next (queue shares, busy times): none yet
   if (hipMemset(c->ws_plan, 0, (size_t)kPlanHeaderInts * sizeof(int32_t)) != hipSuccess) {
     (void)hipGetLastError();
     return ECOSERVE_EHIP;
   }
-  c->ws_bytes += meta_bytes + plan_bytes;
+  c->ws_bytes += meta_bytes + plan_bytes + piece_bytes;
   return ECOSERVE_OK;
 }
 
@@ -218,6 +226,7 @@ int ecoserve_create(ecoserve_ctx** out, int device, const ecoserve_layout* layou
   c->ws_ml = nullptr;
   c->ws_meta = nullptr;
   c->ws_plan = nullptr;
+  c->ws_pieces = nullptr;
   c->ws_count = nullptr;
   c->plan_tiles = 0;
   c->ws_splits = 0;
@@ -254,7 +263,6 @@ int ecoserve_destroy(ecoserve_ctx* c) {
   if (!guard.ok || hipDeviceSynchronize() != hipSuccess) rc = ECOSERVE_EHIP;
   if (c->ws_acc) (void)hipFree(c->ws_acc);
   if (c->ws_ml) (void)hipFree(c->ws_ml);
-  if (c->ws_meta) (void)hipFree(c->ws_meta);
   if (c->ws_plan) (void)hipFree(c->ws_plan);
   if (c->ws_share) (void)hipFree(c->ws_share);
   for (int i = 0; i < 3; ++i)
@@ -389,7 +397,7 @@ int ecoserve_attn_prefill_strided(ecoserve_ctx* c, const void* q, int64_t q_row_
     // vouches that calls naming the same arrays, B and T see the same contents (the layers of one step),
     // and the list of the first such call serves the following ones.
     const int32_t n_wgs = c->num_cu * kPrefillWgsPerCu;
-    const int32_t grid = prefill_mfma_grid(a, T, n_wgs);
+    const int32_t grid = prefill_mfma_grid(a, T, n_wgs, c->ws_pieces);
     auto& key = c->plan_key;
     if (c->opt_reuse_plan) {
       // whether a recorded launch builds the list or relies on an earlier one would be frozen into the graph
@@ -400,7 +408,7 @@ int ecoserve_attn_prefill_strided(ecoserve_ctx* c, const void* q, int64_t q_row_
     const bool same = c->opt_reuse_plan && key.valid && key.cu_q == cu_q && key.ctx_before == ctx_before &&
                       key.block_table == block_table && key.bt_stride == bt_stride && key.B == B && key.T == T &&
                       key.n_wg == grid;
-    e = launch_prefill_mfma(a, cu_q, ctx_before, T, c->ws_plan, n_wgs, !same, c->plan_parity, s);
+    e = launch_prefill_mfma(a, cu_q, ctx_before, T, c->ws_plan, c->ws_pieces, n_wgs, !same, c->plan_parity, s);
     c->plan_parity ^= 1;
     key.valid = e == hipSuccess;
     key.cu_q = cu_q;

@@ -25,6 +25,12 @@
 // XCD (workgroup ids are dealt round-robin to the 8 XCDs): with 8 K/V heads each XCD's L2
 // holds one head's K/V.
 //
+// A batch of few items behind long contexts (chunks of prompts, few long prompts) would leave most of the chip waiting for
+// its longest item.  There the plan cuts the key steps of all items into equal shares, one per workgroup (prefill_shares.h
+// has the arithmetic and the line between the two, with its figures): a share is the end of one item, whole items, and the
+// beginning of another.  An item that is cut leaves one unnormalised state per piece (64 KiB: 128 rows of fp32) in the
+// workspace, and the workgroup that is done last with it adds them up in the order of the keys.
+//
 // Per 64-key step the four 16-token cache blocks of K and of V go straight from global
 // memory into LDS (global_load ... lds, 16 bytes per lane, double buffered, one barrier per
 // step, the eight copies of a wavefront issued one per slot under the step's first matrix
@@ -51,9 +57,11 @@
 // Lane layout relied upon for 32x32x16 (lane = 32*half + col):
 //   A[row = col][k = 8*half .. +7],  B[k = 8*half .. +7][col],
 //   C[row = 8*(i/4) + 4*half + i%4][col], i = 0..15.
+#include <algorithm>
 #include <type_traits>
 
 #include "common.h"
+#include "prefill_shares.h"
 
 namespace eco {
 
@@ -68,6 +76,11 @@ constexpr int kPlanBins = 4096;                // weight classes of the plan's c
 constexpr int kBalanceMinItems = 3072;          // batches with fewer items keep equal queues
 constexpr float kShareGain = 2.5f, kShareMin = 0.5f, kShareMax = 1.5f;  // control of the queues' shares
 constexpr int kQueues = 8;                     // work queues (a multiple of 8; more did not help)
+constexpr int kShareMaxTiles = kPlanBins - 1;   // shares: most query tiles of a batch (their step sums lie in LDS)
+constexpr int kShareMaxRounds = 4;              // shares: most items per workgroup of a batch (more even themselves out)
+constexpr int kPieceFloats = kTQ * 128;         // partial state of a piece: unnormalised outputs, then (max, sum) per row
+constexpr int kPieceStride = kPieceFloats + 2 * kTQ;
+constexpr int kAgentScope = 16;                 // cache policy sc1: past the caches that the XCDs do not share
 static_assert(kQueues % 8 == 0 && kQueues <= kPlanMaxQueues, "queues come in multiples of the XCD count");
 
 typedef const void __attribute__((address_space(1)))* gptr_t;
@@ -190,7 +203,8 @@ __device__ __forceinline__ float mask_and_max(f32x16 (&s)[2], int k0, int half, 
 
 // ---- plan: the query tiles of a batch, heaviest first ------------------------------------------
 //
-// Plan layout (int32): [0] number of query tiles,
+// Plan layout (int32): [0] number of query tiles, [kPlanActive] number of shares (0: queues), [kPlanShareRec0 ..] one record
+// per share, [kPlanPieces0 ..] its counter,
 // [kPlanCounter0 + kPlanCounterStride * (kQueues * p
 // + i)] ticket counter of work queue i in counter set p (one cache line each; launches alternate
 // between the two sets and each launch leaves the other set ready for the next, so a tile list can
@@ -216,14 +230,32 @@ __device__ __forceinline__ float mask_and_max(f32x16 (&s)[2], int k0, int half, 
 // heads, 64 x 50 tokens 32.9 / 23.2, 16 x 93 20.6 / 16.2; the benchmark's 16 prompts of 128..4096 tokens 4% less, its
 // 8 x 8192 tokens the same (8.0 to 8.2 ms, within the noise; their list, G times as many records, takes 15 us instead
 // of 8).  (It also replaces a second kernel that packed the G heads of prompts up to 128 / G tokens.)
+// A share record: the first piece's tile record (field 1: the share's number; 5: the step behind the piece's last; the
+// block ids are those of its first three steps), then these fields.
+constexpr int kShareLeft = 20;     // items behind the first one (-1: the share is empty)
+constexpr int kShareStep0 = 21;    // the first piece's first step
+constexpr int kShareItem = 22;     // the first item: tile * Hkv + K/V head
+constexpr int kShareEnd = 23;      // where the last item is cut (0: it is not)
+constexpr int kShareBegin0 = 24;   // the share that begins the first item
+constexpr int kSharePieces0 = 25;  // pieces of the first item
+constexpr int kSharePieces1 = 26;  // pieces of the last item
+constexpr int kTabItems = 31;      // (in the workgroup's copy in LDS: items of the batch)
+static_assert(kSharePieces1 < kShareInts && kRecInts <= kShareLeft, "fields of a share record");
+
 __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(const int32_t* __restrict__ cu_q,
                                                                     const int32_t* __restrict__ ctx_before,
                                                                     const int32_t* __restrict__ block_table,
                                                                     int bt_stride, int B, int n_main_wgs,
-                                                                    int max_tiles, int G, Divisor div_g, int32_t* __restrict__ plan) {
+                                                                    int max_tiles, int G, Divisor div_g, int Hkv, bool host_allows,
+                                                                    int32_t* __restrict__ plan) {
   __shared__ int pre[kMaxBatch + 1];
-  __shared__ int bins[kPlanBins];  // weight classes
+  __shared__ int bins[kPlanBins];   // weight classes
+  __shared__ int units[kPlanBins];  // (shares) the tiles' units, one K/V head's
+  __shared__ int s_weight[3];       // their sum; the largest and the smallest number of key steps
+  __shared__ Cut s_cut[kPlanMaxWgs + 1];
   __shared__ int wsum[kPlanThreads / 64];
+  __shared__ __attribute__((aligned(16))) int s_rec[kPlanThreads / 64][64][kRecInts];
+  __shared__ int s_slot[kPlanThreads / 64][64];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   // exclusive prefix of one value per thread over the workgroup; `total` receives the sum
   auto block_scan = [&](int local, int& total) -> int {
@@ -253,9 +285,13 @@ __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(const int32_
   };
 
   const int per = (B + kPlanThreads - 1) / kPlanThreads, b0 = tid * per;
-  int local = 0;
+  int local = 0, tiles0 = 0;  // (tiles0: of the thread's first sequence, its only one up to kPlanThreads of them)
   for (int i = 0; i < per; ++i)
-    if (b0 + i < B) local += tiles_of(b0 + i);
+    if (b0 + i < B) {
+      const int n = tiles_of(b0 + i);
+      local += n;
+      if (i == 0) tiles0 = n;
+    }
   int n_tiles_all;
   int run = block_scan(local, n_tiles_all);
   // never more records than the host sized the launch (and the plan buffer) for, whatever cu_q says
@@ -263,13 +299,12 @@ __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(const int32_
   for (int i = 0; i < per; ++i)
     if (b0 + i < B) {
       pre[b0 + i] = run;
-      run += tiles_of(b0 + i);
+      run += i == 0 ? tiles0 : tiles_of(b0 + i);
     }
   if (tid == 0) pre[B] = n_tiles_all;
-  for (int i = tid; i < kPlanBins; i += kPlanThreads) bins[i] = 0;
   __syncthreads();
 
-  // tile i of the batch (sequence after sequence) -> sequence, tile, key steps, weight class
+  // tile i of the batch (sequence after sequence) -> sequence, tile, key steps, first row; its weight class
   auto locate = [&](int i, int& b, int& qt, int& steps) -> int {
     int lo = 0, hi = B;
     while (hi - lo > 1) {
@@ -285,39 +320,127 @@ __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(const int32_
     steps = (int)((kv_end + kTK - 1) / kTK);
     return kPlanBins - 1 - min((steps + 1) >> 1, kPlanBins - 1);  // class 0 = heaviest
   };
-  for (int i = tid; i < n_tiles_all; i += kPlanThreads) {
-    int b, qt, steps;
-    atomicAdd(&bins[locate(i, b, qt, steps)], 1);
-  }
-  __syncthreads();
-  {
+  // v[] <- its exclusive prefix sums (its last readers are behind a barrier; so are the sums' first)
+  auto scan_array = [&](int* v) {
     constexpr int kPer = kPlanBins / kPlanThreads;
     int cnt[kPer], sum = 0;
 #pragma unroll
     for (int i = 0; i < kPer; ++i) {
-      cnt[i] = bins[tid * kPer + i];
+      cnt[i] = v[tid * kPer + i];
       sum += cnt[i];
     }
     int total;
     int start = block_scan(sum, total);
 #pragma unroll
     for (int i = 0; i < kPer; ++i) {
-      bins[tid * kPer + i] = start;
+      v[tid * kPer + i] = start;
       start += cnt[i];
+    }
+    __syncthreads();
+  };
+  // One look at every tile: weight classes for the queues, and what decides between them and shares (share_wgs).
+  const bool may_share = host_allows && n_tiles_all <= kShareMaxTiles;
+  for (int i = tid; i < kPlanBins; i += kPlanThreads) {
+    bins[i] = 0;
+    if (may_share && i >= n_tiles_all) units[i] = 0;
+  }
+  if (tid < 3) s_weight[tid] = tid == 2 ? 0x7fffffff : 0;
+  __syncthreads();
+  int sum = 0, heaviest = 0, lightest = 0x7fffffff;
+  for (int i = tid; i < n_tiles_all; i += kPlanThreads) {
+    int b, qt, steps;
+    atomicAdd(&bins[locate(i, b, qt, steps)], 1);
+    if (may_share) units[i] = steps + kItemCost;
+    sum += steps + kItemCost;
+    heaviest = max(heaviest, steps);
+    lightest = min(lightest, steps);
+  }
+  if (may_share && __any(sum > 0)) {  // (a wavefront at a time: a thousand atomics on one address take 10 us)
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      sum += __shfl_xor(sum, o);
+      heaviest = max(heaviest, __shfl_xor(heaviest, o));
+      lightest = min(lightest, __shfl_xor(lightest, o));
+    }
+    if (lane == 0) {
+      atomicAdd(&s_weight[0], sum);
+      atomicMax(&s_weight[1], heaviest);
+      atomicMin(&s_weight[2], lightest);
     }
   }
   __syncthreads();
+  const int n_items = n_tiles_all * Hkv, head_units = s_weight[0];  // units: key steps and kItemCost, of one K/V head's tiles
+  const int n_active = may_share ? share_wgs(n_items, (long long)head_units * Hkv, s_weight[1], s_weight[2], n_main_wgs) : 0;
+  if (n_active > 0) {
+    scan_array(units);
+    // boundary r of the shares: unit head_units * Hkv * r / n_active, as the item and the key step it falls on
+    for (int r = tid; r <= n_active; r += kPlanThreads) {
+      const int u = share_begin(head_units * Hkv, n_active, r), g = u / head_units, v = u - g * head_units;
+      int lo = 0, hi = n_tiles_all;
+      while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (units[mid] <= v) lo = mid; else hi = mid;
+      }
+      int b, qt, steps, first, last;
+      locate(lo, b, qt, steps);
+      tile_rows(cu_q[b + 1] - cu_q[b], qt, first, last);
+      s_cut[r] = r == n_active ? Cut{n_items, 0} : share_cut(g * n_tiles_all + lo, v - units[lo], steps, (ctx_before[b] + fast_div(first, div_g)) / kTK);
+    }
+    __syncthreads();
+    // (records go through LDS and out in neighbouring words, as the tiles' do below)
+    int* const share_rec = &s_rec[0][0][0];
+    constexpr int kPad = kShareInts + 1;
+    static_assert(sizeof(s_rec) >= kPlanMaxWgs / 2 * kPad * sizeof(int), "half of the shares at a time");
+    for (int w0 = 0; w0 < n_main_wgs; w0 += kPlanMaxWgs / 2) {
+      const int w = w0 + tid;
+      if (tid < kPlanMaxWgs / 2 && w < n_active) {
+        int* const rec = share_rec + tid * kPad;
+        const int r = share_of_wg(w, n_active);
+        const int i0 = s_cut[r].item, j0 = s_cut[r].step, j_end = s_cut[r + 1].step, i_last = s_cut[r + 1].item - (j_end == 0 ? 1 : 0);
+        rec[kShareLeft] = i_last - i0;
+        if (i_last >= i0) {  // (else nothing lies between the two boundaries)
+          const int g = i0 / n_tiles_all, t = i0 - g * n_tiles_all;
+          int b, qt, steps;
+          locate(t, b, qt, steps);
+          const int cb = ctx_before[b], S = cu_q[b + 1] - cu_q[b];
+          const int nblk_total = (int)(((long long)cb + S + 15) >> 4);
+#pragma unroll
+          for (int j = 0; j < 12; ++j) rec[8 + j] = block_table[(size_t)b * bt_stride + min(4 * j0 + j, nblk_total - 1)];
+          rec[0] = b;
+          rec[1] = r;
+          rec[2] = cu_q[b];
+          rec[3] = S;
+          rec[4] = cb;
+          rec[5] = i0 == i_last && j_end > 0 ? j_end : steps;
+          tile_rows(S, qt, rec[6], rec[7]);
+          const int begin0 = share_that_begins(s_cut, r);
+          rec[kShareStep0] = j0;
+          rec[kShareItem] = t * Hkv + g;
+          rec[kShareEnd] = j_end;
+          rec[kShareBegin0] = begin0;
+          rec[kSharePieces0] = share_that_ends(s_cut, n_active, r, i0) - begin0 + 1;
+          rec[kSharePieces1] = share_that_ends(s_cut, n_active, r, i_last) - (i_last == i0 ? begin0 : r) + 1;
+        }
+      }
+      __syncthreads();
+      const int n = min(kPlanMaxWgs / 2, n_active - w0);
+      for (int i = tid; i < n * kShareInts; i += kPlanThreads)
+        plan[kPlanShareRec0 + (size_t)w0 * kShareInts + i] = share_rec[(i / kShareInts) * kPad + i % kShareInts];
+      if (tid < kPlanMaxWgs / 2 && w < n_main_wgs) plan[kPlanPieces0 + w] = 0;
+      __syncthreads();
+    }
+  } else {
+    scan_array(bins);
+  }
   // A wavefront's 64 records go through LDS and out in 16-byte pieces, neighbouring lanes writing neighbouring pieces: one
   // record per lane, 80 bytes apart, every store instruction touches 64 cache lines, and one workgroup writes them all
   // (4096 tiles: 20.5 -> 15.4 us; 600: 9.0 -> 7.7).
-  __shared__ __attribute__((aligned(16))) int s_rec[kPlanThreads / 64][64][kRecInts];
-  __shared__ int s_slot[kPlanThreads / 64][64];
   for (int base = wave * 64; base < n_tiles_all; base += kPlanThreads) {
     const int i = base + lane, n = min(64, n_tiles_all - base);
     if (lane < n) {
       int b, qt, steps;
       const int cls = locate(i, b, qt, steps);
-      s_slot[wave][lane] = atomicAdd(&bins[cls], 1);
+      s_slot[wave][lane] = n_active > 0 ? i : atomicAdd(&bins[cls], 1);
       int* const rec = s_rec[wave][lane];
       const int cb = ctx_before[b], S = cu_q[b + 1] - cu_q[b];
       const int nblk_total = (int)(((long long)cb + S + 15) >> 4);
@@ -345,7 +468,10 @@ __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(const int32_
     __builtin_amdgcn_wave_barrier();  // (the next round overwrites the records)
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   }
-  if (tid == 0) plan[0] = n_tiles_all;
+  if (tid == 0) {
+    plan[0] = n_tiles_all;
+    plan[kPlanActive] = n_active;
+  }
   // each workgroup of the attention kernel owns the first two tickets of its queue outright
   if (tid < 2 * kQueues)
     plan[kPlanCounter0 + kPlanCounterStride * tid] = 2 * ((n_main_wgs - tid % kQueues + kQueues - 1) / kQueues);
@@ -353,7 +479,8 @@ __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(const int32_
 
 // Wave-uniform description of one work item (a query tile of one K/V head).
 struct Item {
-  int tok0, S, cb, q0, q_end, g, n_tiles;  // q0, q_end: the tile's rows [q0, q_end) of the S G of its sequence and head
+  int tok0, S, cb, q0, q_end, g;  // q0, q_end: the tile's rows [q0, q_end) of the S G of its sequence and head
+  int j0, n_tiles;                // key steps [j0, n_tiles): all of the tile's, or a piece of them (shares)
   const int32_t* bt_row;
   __device__ __forceinline__ int L_total() const { return cb + S; }
   __device__ __forceinline__ int nblk_total() const { return (cb + S + 15) >> 4; }
@@ -366,6 +493,7 @@ __device__ __forceinline__ Item describe(int rec, int g, const int32_t* __restri
   t.tok0 = __builtin_amdgcn_readlane(rec, 2);
   t.S = __builtin_amdgcn_readlane(rec, 3);
   t.cb = __builtin_amdgcn_readlane(rec, 4);
+  t.j0 = 0;
   t.n_tiles = __builtin_amdgcn_readlane(rec, 5);
   t.g = g;
   t.q0 = __builtin_amdgcn_readlane(rec, 6);
@@ -374,17 +502,22 @@ __device__ __forceinline__ Item describe(int rec, int g, const int32_t* __restri
   return t;
 }
 
-__global__ __launch_bounds__(256, 2) void prefill_mfma_kernel(
-    const uint16_t* __restrict__ q, int q_row_stride, const char* __restrict__ k_cache,
+constexpr int kSmemBytes = 2 * kKTileBytes + 2 * kVTileBytes + 16 + kShareInts * 4;
+
+// kShared: the workgroup computes its share of the batch's key steps, else items that it draws tickets for.  (Two bodies:
+// with both in one, the step loop's registers spill, 1 to 2 us per launch.)  rec_first: the first item's record (the
+// share's); n_flat: items.
+template <bool kShared>
+__device__ __forceinline__ void prefill_work(
+    char* const smem, long long t_begin, int rec_first, int n_flat, const uint16_t* __restrict__ q, int q_row_stride, const char* __restrict__ k_cache,
     const char* __restrict__ v_cache, const int32_t* __restrict__ block_table, int bt_stride,
-    uint16_t* __restrict__ out, float* __restrict__ lse, int32_t* __restrict__ plan, int parity, int Hq, int Hkv, int G, Divisor div_g, Divisor div_hkv,
-    float scale_log2e) {
-  __shared__ __attribute__((aligned(16))) char smem[2 * kKTileBytes + 2 * kVTileBytes + 16 + 64];
+    uint16_t* __restrict__ out, float* __restrict__ lse, int32_t* __restrict__ plan, int parity, float* ws_pieces, int Hq, int Hkv, int G, Divisor div_g,
+    Divisor div_hkv, float scale_log2e) {
   char* const kbufs = smem;
   char* const vbufs = smem + 2 * kKTileBytes;
   int* const slot = reinterpret_cast<int*>(smem + 2 * kKTileBytes + 2 * kVTileBytes);  // tickets from thread 0
   int* const qtab = slot + 4;  // [x]: items queue x works through, [8 + x]: items on its own list (wavefront 0 only)
-  const long long t_begin = wall_clock64();
+  int* const stab = qtab;  // the share's record instead
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int col = lane & 31, half = lane >> 5;
@@ -394,12 +527,6 @@ __global__ __launch_bounds__(256, 2) void prefill_mfma_kernel(
   const float c = scale_log2e;
   const size_t blk_stride = (size_t)Hkv * 4096;
   const int32_t* const recs = plan + kPlanHeaderInts;
-  // the other counter set is idle (the launch that used it is over): start it for the next launch
-  auto start_other_counters = [&]() {
-    if (blockIdx.x == 0 && threadIdx.x < kQueues)
-      plan[kPlanCounter0 + kPlanCounterStride * (kQueues * (parity ^ 1) + threadIdx.x)] =
-          2 * (((int)gridDim.x - (int)threadIdx.x + kQueues - 1) / kQueues);
-  };
   // item f is K/V head f % Hkv of tile f / Hkv
   int tile_of_f, g_of_f;
   auto split = [&](int f) {
@@ -407,18 +534,12 @@ __global__ __launch_bounds__(256, 2) void prefill_mfma_kernel(
     g_of_f = f - tile_of_f * Hkv;
   };
   auto load_rec = [&](int tile) { return recs[(size_t)tile * kRecInts + min(lane, kRecInts - 1)]; };
+  // item f + 1 in the order of the shares: head after head, tile after tile
+  auto after = [&](int f, int n_flat) { return f + Hkv < n_flat ? f + Hkv : f + Hkv - n_flat + 1; };
 
-  // The first two tickets of every workgroup are fixed (the plan starts the counters behind them: several hundred
-  // workgroups asking eight counters at once would wait on each other): the first is item blockIdx.x, whose record is
-  // asked for together with the number of items (the grid is no larger than the bound the plan is sized for).
   split(blockIdx.x);
-  int rec_next = load_rec(tile_of_f);  // record of the next item (here: of the first)
-  const int n_flat = __builtin_amdgcn_readfirstlane(plan[0]) * Hkv;  // items
-  if ((int)blockIdx.x >= n_flat) {
-    if (threadIdx.x == 0 && blockIdx.x < kPlanMaxWgs) plan[kPlanBusy0 + parity * kPlanMaxWgs + blockIdx.x] = 0;
-    start_other_counters();
-    return;
-  }
+  int rec_next = rec_first;  // record of the next item (here: of the first)
+  const int rec_share = rec_first;
   // Work items are dealt to kQueues queues (item f belongs to queue f % kQueues) and workgroup w
   // serves queue w % kQueues.  kQueues is a multiple of 8: workgroup ids are dealt round-robin to
   // the 8 XCDs and with eight K/V heads item f reads K/V head f % 8, so an XCD's L2 sees one head's
@@ -429,11 +550,14 @@ __global__ __launch_bounds__(256, 2) void prefill_mfma_kernel(
   // tens of microseconds.  What does pay is decided before the first ticket: how many items each queue
   // works through (its quota, below), from the busy times of the launch before.
   const int queue = blockIdx.x % kQueues;
+  int f_next = (int)blockIdx.x + kQueues * (((int)gridDim.x - queue + kQueues - 1) / kQueues);  // the item after the current one
   int* const counter = plan + kPlanCounter0 + kPlanCounterStride * (kQueues * parity + queue);
   // Ticket k of the own queue -> item, -1 past its end, with the queues' quotas (qtab, set up below): a queue that
   // gives items away stops short of the end of its list, and the lists' ends so left over are dealt, in queue order,
   // to the queues that take more than their own.  Thread 0 only.
+  // Shares: the item after the next one, -1 behind the share's last.
   auto resolve = [&](int k) -> int {
+    if constexpr (kShared) return --stab[kShareLeft] > 0 ? after(f_next, stab[kTabItems]) : -1;
     const int quota = qtab[queue], own = qtab[kQueues + queue];
     if (k < min(quota, own)) return kQueues * k + queue;
     if (k >= quota) return -1;
@@ -447,7 +571,6 @@ __global__ __launch_bounds__(256, 2) void prefill_mfma_kernel(
     }
     return -1;
   };
-  start_other_counters();
   // What the previous launch left behind for this one (the other set): each workgroup's busy time, the
   // queues' shares and which batch they belong to.  Wavefront 0 asks for them now and uses them below.
   int prev_items = 0, prev_grid = 0;
@@ -459,10 +582,21 @@ __global__ __launch_bounds__(256, 2) void prefill_mfma_kernel(
     prev_items = plan[kPlanMeta0 + (parity ^ 1)];
     prev_grid = plan[kPlanMeta0 + 2 + (parity ^ 1)];
   }
-  int f_next = (int)blockIdx.x + kQueues * (((int)gridDim.x - queue + kQueues - 1) / kQueues);  // the item after the current one
   if (f_next >= n_flat) f_next = -1;   // (-1: none)
+  if constexpr (kShared) {
+    const int f = __builtin_amdgcn_readlane(rec_share, kShareItem);
+    split(f);
+    f_next = __builtin_amdgcn_readlane(rec_share, kShareLeft) > 0 ? after(f, n_flat) : -1;
+  }
   int pend = 0;                        // (thread 0) ticket on its way
   Item cur = describe(rec_next, g_of_f, block_table, bt_stride);
+  if constexpr (kShared) {
+    cur.j0 = __builtin_amdgcn_readlane(rec_share, kShareStep0);
+    // (what the ends of items need of the record lies in LDS: the step loop has no registers to spare)
+    if (tid < kShareInts) stab[tid] = rec_share;
+    if (tid == 0) stab[kTabItems] = n_flat;
+  }
+  bool first = true;                   // the current item is the workgroup's first
   int g_next = 0;                      // K/V head of the next item
 
   // per-lane view of the current item
@@ -523,14 +657,14 @@ __global__ __launch_bounds__(256, 2) void prefill_mfma_kernel(
   const int a_k_off = (half * kTK + krow) * 16;            // + (2 t * 64 + 32 sub) * 16
   const int a_v_off = half * kVOctStride + col * 16;       // + 2 u * stride + 32 dt * 16
 
-  stage_first(cur, rec_next, 0);
+  stage_first(cur, rec_next, 0);  // (cur.j0 is step 0 of its parity: see par)
   load_q(cur);
   int next_idk = __shfl(rec_next, 16 + kq);                // K ids run two steps ahead of the scores
   int next_idv = __shfl(rec_next, 12 + vq);                // V ids one step ahead
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
-  if (kTK > cur.L_total()) {  // the first step already runs past the end of the sequence
-    fix_tail(vbufs, cur.L_total(), tid);
+  if ((cur.j0 + 1) * kTK > cur.L_total()) {  // the first step already runs past the end of the sequence
+    fix_tail(vbufs, cur.L_total() - cur.j0 * kTK, tid);
     __syncthreads();
   }
   // Quotas of the queues.  The XCDs of one device do not run this kernel equally fast (their workgroups end up
@@ -538,7 +672,7 @@ __global__ __launch_bounds__(256, 2) void prefill_mfma_kernel(
   // queue's share of the items follows its XCD's busy time in the previous launch of the same batch (one step
   // of proportional control per launch; the items that change hands are the lightest ones at the lists' ends,
   // hence the gain above one).  Which workgroup computes an item does not change its result.
-  if (wave == 0) {
+  if (!kShared && wave == 0) {
     const int x = lane & 7;
     const int own = max(n_flat - x + kQueues - 1, 0) / kQueues;
     int quota = own;
@@ -579,7 +713,11 @@ __global__ __launch_bounds__(256, 2) void prefill_mfma_kernel(
       }
     }
   }
-  int par = 0;  // buffer that holds step 0 of the current item
+  if (kShared && blockIdx.x == 0 && wave == 0) {  // no queues: nothing for a later launch to go by
+    if (lane < kQueues) reinterpret_cast<float*>(plan)[kPlanShare0 + kQueues * parity + lane] = 1.f;
+    if (lane == 0) plan[kPlanMeta0 + parity] = 0;
+  }
+  int par = cur.j0 & 1;  // step j of the current item lies in buffer (j + par) & 1
 
   f32x16 sa[2], sb[2];  // scores of the current / next step, roles alternate
 
@@ -738,54 +876,8 @@ __global__ __launch_bounds__(256, 2) void prefill_mfma_kernel(
     }
   };
 
-  for (;;) {
-    // K steps 0 and 1 and V step 0 of the current item are in LDS (step 0 in the buffers of
-    // parity `par`), its query rows in qf.  Ask for the record of the next item and for the
-    // ticket of the one after it; both arrive while this item is being computed.
-    if (f_next >= 0) {
-      split(f_next);
-      g_next = g_of_f;
-      rec_next = load_rec(tile_of_f);
-      if (tid == 0) pend = atomicAdd(counter, 1);
-    }
-    if (n_w > 0) {
-#pragma unroll
-      for (int sub = 0; sub < 2; ++sub)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) sa[sub][i] = 0.f;
-      const char* kb = kbufs + par * kKTileBytes + a_k_off;
-#pragma unroll
-      for (int t = 0; t < 8; ++t)
-#pragma unroll
-        for (int sub = 0; sub < 2; ++sub) {
-          const bf16x8 a = *reinterpret_cast<const bf16x8*>(kb + (2 * t * kTK + 32 * sub) * 16);
-          sa[sub] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[t], sa[sub], 0, 0, 0);
-        }
-      m = mask_and_max(sa, 0, half, pos, kTK - 1 > w_pmin);
-    }
-    __syncthreads();  // K step 0 is consumed: its buffer receives step 2
-
-    {
-      // plain steps run in pairs (sa -> sb -> sa); the last step always takes its scores from sa, so a
-      // left-over single plain step is followed by a copy
-      int j = 0;
-      for (; j + 2 < cur.n_tiles; j += 2) {
-        iteration(std::false_type(), j, sa, sb);
-        iteration(std::false_type(), j + 1, sb, sa);
-      }
-      if (j + 2 == cur.n_tiles) {
-        iteration(std::false_type(), j, sa, sb);
-#pragma unroll
-        for (int sub = 0; sub < 2; ++sub) sa[sub] = sb[sub];
-        ++j;
-      }
-      iteration(std::true_type(), j, sa, sb);
-    }
-
-    {
-      const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(l), __float_as_uint(l), false, false);
-      l = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-    }
+  // the item's results: o / l (l summed over the lanes of a row)
+  auto write_rows = [&](const Item& t) {
     {
       // Registers 4 i4 .. 4 i4 + 3 of o[dt] hold d = 32 dt + 8 i4 + 4 half + (0..3): 8 bytes of output.
       // The two lanes of a row exchange halves (one v_permlane32_swap per register pair) so that
@@ -793,8 +885,8 @@ __global__ __launch_bounds__(256, 2) void prefill_mfma_kernel(
       const float inv = 1.f / l;
       int row, hsel;  // (worked out again rather than kept in registers through the item)
       bool row_valid;
-      map_row(cur, row, hsel, row_valid);
-      uint16_t* orow = out + ((size_t)(cur.tok0 + row) * Hq + cur.g * G + hsel) * 128 + half * 8;
+      map_row(t, row, hsel, row_valid);
+      uint16_t* orow = out + ((size_t)(t.tok0 + row) * Hq + t.g * G + hsel) * 128 + half * 8;
       auto pack = [&](float a, float b) {
         const bf16x2 v = {(__bf16)(a * inv), (__bf16)(b * inv)};
         return __builtin_bit_cast(uint32_t, v);
@@ -819,15 +911,110 @@ __global__ __launch_bounds__(256, 2) void prefill_mfma_kernel(
     if (lse && half == 0) {
       int row, hsel;
       bool row_valid;
-      map_row(cur, row, hsel, row_valid);
-      if (row_valid) lse[(size_t)(cur.tok0 + row) * Hq + cur.g * G + hsel] = (m * c + log2f(l)) * kLn2;
+      map_row(t, row, hsel, row_valid);
+      if (row_valid) lse[(size_t)(t.tok0 + row) * Hq + t.g * G + hsel] = (m * c + log2f(l)) * kLn2;
+    }
+  };
+  // Shares: a piece of a tile leaves its state in the workspace, past the caches that the XCDs do not share.
+  auto field = [&](int i) { return __builtin_amdgcn_readfirstlane(stab[i]); };
+  auto pieces_done = [&](int begin) { return reinterpret_cast<unsigned*>(plan) + kPlanPieces0 + begin; };
+  auto piece_rsrc = [&](int share, int begin) {
+    return __builtin_amdgcn_make_buffer_rsrc(ws_pieces + (size_t)piece_slot(share, begin) * kPieceStride, 0, kPieceStride * 4, 0x00020000);
+  };
+  auto store_piece = [&](int begin) {
+    const auto r = piece_rsrc(field(1), begin);
+    int ln = lane;
+    asm volatile("" : "+v"(ln));  // (the addresses are worked out here, not kept through the step loop)
+    const int at = (wave * 4096 + ln * 4) * 4, at_ml = (kPieceFloats + 2 * (wave * 32 + (ln & 31))) * 4;
+#pragma unroll
+    for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+      for (int p = 0; p < 4; ++p) {
+        const f32x4 v = {o[dt][4 * p], o[dt][4 * p + 1], o[dt][4 * p + 2], o[dt][4 * p + 3]};
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), r, at + (dt * 4 + p) * 1024, 0, kAgentScope);
+      }
+    const u32x2 ml = {__float_as_uint(m), __float_as_uint(l)};
+    if (ln < 32) __builtin_amdgcn_raw_buffer_store_b64(ml, r, at_ml, 0, kAgentScope);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+  };
+
+  for (;;) {
+    // K steps 0 and 1 and V step 0 of the current item are in LDS (step 0 in the buffers of
+    // parity `par`), its query rows in qf.  Ask for the record of the next item and for the
+    // ticket of the one after it; both arrive while this item is being computed.
+    if (f_next >= 0) {
+      split(f_next);
+      g_next = g_of_f;
+      rec_next = load_rec(tile_of_f);
+      if (!kShared && tid == 0) pend = atomicAdd(counter, 1);
+      if (kShared && tid == 0 && cur.j0 > 0) slot[0] = resolve(0);  // (a first piece without step 0, where it would be published)
+    }
+    if (n_w > cur.j0) {
+#pragma unroll
+      for (int sub = 0; sub < 2; ++sub)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) sa[sub][i] = 0.f;
+      const char* kb = kbufs + ((cur.j0 + par) & 1) * kKTileBytes + a_k_off;
+#pragma unroll
+      for (int t = 0; t < 8; ++t)
+#pragma unroll
+        for (int sub = 0; sub < 2; ++sub) {
+          const bf16x8 a = *reinterpret_cast<const bf16x8*>(kb + (2 * t * kTK + 32 * sub) * 16);
+          sa[sub] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[t], sa[sub], 0, 0, 0);
+        }
+      m = mask_and_max(sa, cur.j0 * kTK, half, pos, (cur.j0 + 1) * kTK - 1 > w_pmin);
+      // scores of minus infinity (from infinite inputs) in all of a later piece's first step weigh nothing, as they would
+      // behind the steps before it
+      if (cur.j0 > 0 && m == -INFINITY) m = -3.0e38f / fmaxf(c, 1.f);
+    }
+    __syncthreads();  // K step 0 is consumed: its buffer receives step 2
+
+    {
+      // plain steps run in pairs (sa -> sb -> sa); the last step always takes its scores from sa, so a
+      // left-over single plain step is followed by a copy
+      int j = cur.j0;
+      for (; j + 2 < cur.n_tiles; j += 2) {
+        iteration(std::false_type(), j, sa, sb);
+        iteration(std::false_type(), j + 1, sb, sa);
+      }
+      if (j + 2 == cur.n_tiles) {
+        iteration(std::false_type(), j, sa, sb);
+#pragma unroll
+        for (int sub = 0; sub < 2; ++sub) sa[sub] = sb[sub];
+        ++j;
+      }
+      iteration(std::true_type(), j, sa, sb);
+    }
+
+    {
+      const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(l), __float_as_uint(l), false, false);
+      l = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    }
+    if constexpr (kShared) {
+      if (f_next < 0 && field(first ? kSharePieces0 : kSharePieces1) > 1) break;  // the last piece of a cut item: see below
+      if (first && field(kSharePieces0) > 1) {
+        // the end of an item that began in an earlier share
+        const int begin = field(kShareBegin0);
+        store_piece(begin);
+        if (tid == 0) slot[2] = (int)atomicInc(pieces_done(begin), (unsigned)stab[kSharePieces0] - 1);
+      } else {
+        write_rows(cur);
+      }
+    } else {
+      write_rows(cur);
     }
     if (f_next < 0) break;
 
     // next item: its first steps were staged by the last step above, into the other parity
     par = (par + cur.n_tiles) & 1;
     cur = describe(rec_next, g_next, block_table, bt_stride);
+    first = false;
     f_next = __builtin_amdgcn_readfirstlane(slot[0]);
+    if (kShared && f_next < 0) {  // the last item of a share may go on in the next one
+      const int end = __builtin_amdgcn_readfirstlane(stab[kShareEnd]);
+      if (end > 0) cur.n_tiles = end;
+    }
     enter(cur);
     next_idk = __shfl(rec_next, 16 + kq);
     next_idv = __shfl(rec_next, 12 + vq);
@@ -837,33 +1024,156 @@ __global__ __launch_bounds__(256, 2) void prefill_mfma_kernel(
       for (int i = 0; i < 16; ++i) o[dt][i] = 0.f;
     l = 0.f;
   }
+  if constexpr (kShared) {
+    // The workgroup that is done last with a cut item takes all its pieces, in the order of the keys, so the result does
+    // not depend on which one that is:  M = max_k m_k;  l = sum_k l_k 2^(m_k - M);  o = sum_k o_k 2^(m_k - M).
+    // The share's last item comes first, its state still in registers; when it is the item's first piece and the others
+    // are done (the usual case: they began their shares with it) it stays there.
+    const bool last_cut = field(first ? kSharePieces0 : kSharePieces1) > 1;
+    const bool first_mine = !first && field(kSharePieces0) > 1 && __builtin_amdgcn_readfirstlane(slot[2]) == field(kSharePieces0) - 1;
+#pragma unroll 1
+    for (int which = last_cut ? 0 : 1; which < (first_mine ? 2 : 1); ++which) {
+      const bool of_first = which == 1 || first;
+      const int n_pieces = field(of_first ? kSharePieces0 : kSharePieces1), begin = field(of_first ? kShareBegin0 : 1);
+      bool all_done = which == 1, kept = false;
+      if (which == 0) {
+        unsigned* const done = pieces_done(begin);
+        if (field(1) == begin) {
+          if (tid == 0) {
+            const unsigned n = __hip_atomic_load(done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if ((int)n == n_pieces - 1) __hip_atomic_store(done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            slot[1] = (int)n;
+          }
+          __syncthreads();
+          all_done = kept = __builtin_amdgcn_readfirstlane(slot[1]) == n_pieces - 1;
+        }
+        if (!kept) {
+          store_piece(begin);
+          if (tid == 0) slot[3] = (int)atomicInc(done, (unsigned)n_pieces - 1);  // (the last one wraps it to zero)
+          __syncthreads();
+          all_done = __builtin_amdgcn_readfirstlane(slot[3]) == n_pieces - 1;
+        }
+      }
+      if (!all_done) continue;
+      const int at = (wave * 4096 + lane * 4) * 4, at_ml = (kPieceFloats + 2 * (wave * 32 + col)) * 4;
+      auto state = [&](int k, u32x2& ml, f32x4 (&v)[16]) {
+        const auto r = piece_rsrc(begin + k, begin);
+        ml = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(r, at_ml, 0, kAgentScope));
+#pragma unroll
+        for (int p = 0; p < 16; ++p)
+          v[p] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, at + p * 1024, 0, kAgentScope));
+      };
+      if (!kept) {
+        u32x2 ml;
+        f32x4 v[16];
+        state(0, ml, v);
+        m = __uint_as_float(ml[0]);
+        l = __uint_as_float(ml[1]);
+#pragma unroll
+        for (int p = 0; p < 16; ++p)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) o[p >> 2][4 * (p & 3) + e] = v[p][e];
+      }
+#pragma unroll 1
+      for (int k = 1; k < n_pieces; ++k) {
+        u32x2 ml;
+        f32x4 v[16];
+        state(k, ml, v);
+        const float M = fmaxf(m, __uint_as_float(ml[0]));
+        const float old = exp2f((m - M) * c), wk = exp2f((__uint_as_float(ml[0]) - M) * c);
+        m = M;
+        l = l * old + __uint_as_float(ml[1]) * wk;
+#pragma unroll
+        for (int p = 0; p < 16; ++p)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) o[p >> 2][4 * (p & 3) + e] = o[p >> 2][4 * (p & 3) + e] * old + v[p][e] * wk;
+      }
+      if (which == 1) cur = describe(stab[lane & (kShareInts - 1)], field(kShareItem) % Hkv, block_table, bt_stride);
+      write_rows(cur);
+    }
+  }
   if (tid == 0 && blockIdx.x < kPlanMaxWgs)
     plan[kPlanBusy0 + parity * kPlanMaxWgs + blockIdx.x] = (int)(wall_clock64() - t_begin);
 }
 
+// kMayShare: the plan has had the choice between shares and queues (else: queues).
+template <bool kMayShare>
+__global__ __launch_bounds__(256, 2) void prefill_mfma_kernel(
+    const uint16_t* __restrict__ q, int q_row_stride, const char* __restrict__ k_cache,
+    const char* __restrict__ v_cache, const int32_t* __restrict__ block_table, int bt_stride,
+    uint16_t* __restrict__ out, float* __restrict__ lse, int32_t* __restrict__ plan, int parity, float* ws_pieces, int max_tiles, int Hq, int Hkv, int G, Divisor div_g,
+    Divisor div_hkv, float scale_log2e) {
+  __shared__ __attribute__((aligned(16))) char smem[kSmemBytes];
+  const long long t_begin = wall_clock64();  // (asked for first: its answer takes 0.2 us)
+  const int lane = threadIdx.x & 63;
+  // The first two tickets of every workgroup are fixed (the plan starts the counters behind them: several hundred
+  // workgroups asking eight counters at once would wait on each other): the first is item blockIdx.x, whose record is
+  // asked for together with the number of items, and with the workgroup's share, should the plan have made shares.
+  // (Without shares the grid is no larger than the bound the plan is sized for.)
+  const int tile = fast_div((int)blockIdx.x, div_hkv);
+  const int rec_item = plan[kPlanHeaderInts + (size_t)(kMayShare ? min(tile, max_tiles - 1) : tile) * kRecInts + min(lane, kRecInts - 1)];
+  const int rec_share = kMayShare ? plan[kPlanShareRec0 + (size_t)blockIdx.x * kShareInts + (lane & (kShareInts - 1))] : 0;
+  const int n_flat = __builtin_amdgcn_readfirstlane(plan[0]) * Hkv;  // items
+  const int n_active = kMayShare ? __builtin_amdgcn_readfirstlane(plan[kPlanActive]) : 0;
+  // the other counter set is idle (the launch that used it is over): start it for the next launch
+  if (blockIdx.x == 0 && threadIdx.x < kQueues)
+    plan[kPlanCounter0 + kPlanCounterStride * (kQueues * (parity ^ 1) + threadIdx.x)] =
+        2 * (((int)gridDim.x - (int)threadIdx.x + kQueues - 1) / kQueues);
+  if constexpr (kMayShare) {
+    if (n_active > 0) {
+      if ((int)blockIdx.x >= n_active || __builtin_amdgcn_readlane(rec_share, kShareLeft) < 0) return;
+      prefill_work<true>(smem, t_begin, rec_share, n_flat, q, q_row_stride, k_cache, v_cache, block_table, bt_stride, out, lse, plan, parity, ws_pieces, Hq,
+                         Hkv, G, div_g, div_hkv, scale_log2e);
+      return;
+    }
+  }
+  if ((int)blockIdx.x >= n_flat) {
+    if (threadIdx.x == 0 && blockIdx.x < kPlanMaxWgs) plan[kPlanBusy0 + parity * kPlanMaxWgs + blockIdx.x] = 0;
+    return;
+  }
+  prefill_work<false>(smem, t_begin, rec_item, n_flat, q, q_row_stride, k_cache, v_cache, block_table, bt_stride, out, lse, plan, parity, ws_pieces, Hq,
+                      Hkv, G, div_g, div_hkv, scale_log2e);
+}
+
+// Key steps of a row of the block table: no item has more.
+static int64_t table_steps(const AttnArgs& a) { return ((int64_t)a.bt_stride * kBlockSize + kTK - 1) / kTK; }
+
+// Whether the plan may share out the batch's key steps: not for tables so short or batches of so many items that it never would.
+static bool may_share(const AttnArgs& a, int64_t n_items, int32_t n_persistent_wgs, const float* ws_pieces) {
+  return ws_pieces && n_persistent_wgs <= kPlanMaxWgs && table_steps(a) >= kShareMinUnits && n_items <= (int64_t)kShareMaxRounds * n_persistent_wgs;
+}
+
 // Workgroups of the attention launch: the persistent grid, or fewer if the batch cannot hold that
-// many items (0: nothing to do, -1: too many items to number).
-int32_t prefill_mfma_grid(const AttnArgs& a, int32_t T, int32_t n_persistent_wgs) {
+// many items and its key steps cannot be shared among them (0: nothing to do, -1: too many items to number).
+int32_t prefill_mfma_grid(const AttnArgs& a, int32_t T, int32_t n_persistent_wgs, const float* ws_pieces) {
   const int64_t n_items = prefill_plan_tiles(a.B, T, a.Hq / a.Hkv) * a.Hkv;
   if (n_items <= 0) return 0;
   if (n_items > 0x7fffffffLL - (1 << 20)) return -1;
-  return (int32_t)(n_items < n_persistent_wgs ? n_items : n_persistent_wgs);
+  // (the block table's width bounds the steps)
+  const int64_t shares = may_share(a, n_items, n_persistent_wgs, ws_pieces) ? n_items * (table_steps(a) + kItemCost) / kShareMinUnits : 0;
+  return (int32_t)std::min<int64_t>(n_persistent_wgs, std::max(n_items, shares));
+}
+
+// Workspace of the pieces of cut items, in floats: two per workgroup.
+int64_t prefill_piece_floats(int32_t n_persistent_wgs) {
+  return (int64_t)2 * std::min(n_persistent_wgs, (int32_t)kPlanMaxWgs) * kPieceStride;
 }
 
 hipError_t launch_prefill_mfma(const AttnArgs& a, const int32_t* cu_q, const int32_t* ctx_before, int32_t T,
-                               int32_t* ws_plan, int32_t n_persistent_wgs, bool make_plan,
+                               int32_t* ws_plan, float* ws_pieces, int32_t n_persistent_wgs, bool make_plan,
                                int parity, hipStream_t s) {
   const int G = a.Hq / a.Hkv;
   const int64_t max_tiles = prefill_plan_tiles(a.B, T, G);
-  const int32_t n_wg = prefill_mfma_grid(a, T, n_persistent_wgs);
+  const int32_t n_wg = prefill_mfma_grid(a, T, n_persistent_wgs, ws_pieces);
   if (n_wg == 0) return hipSuccess;
   if (n_wg < 0) return hipErrorInvalidValue;
+  const bool share = may_share(a, max_tiles * a.Hkv, n_persistent_wgs, ws_pieces);
   if (make_plan)
     hipLaunchKernelGGL(prefill_plan_kernel, dim3(1), dim3(kPlanThreads), 0, s, cu_q, ctx_before, a.block_table,
-                       a.bt_stride, a.B, (int)n_wg, (int)max_tiles, G, make_divisor((uint32_t)G), ws_plan);
-  hipLaunchKernelGGL(prefill_mfma_kernel, dim3((unsigned)n_wg), dim3(256), 0, s, (const uint16_t*)a.q, a.q_row_stride,
+                       a.bt_stride, a.B, (int)n_wg, (int)max_tiles, G, make_divisor((uint32_t)G), a.Hkv, share, ws_plan);
+  hipLaunchKernelGGL(share ? prefill_mfma_kernel<true> : prefill_mfma_kernel<false>, dim3((unsigned)n_wg), dim3(256), 0, s, (const uint16_t*)a.q, a.q_row_stride,
                      (const char*)a.k_cache, (const char*)a.v_cache, a.block_table, a.bt_stride, (uint16_t*)a.out,
-                     a.lse, ws_plan, parity, a.Hq, a.Hkv, G, make_divisor((uint32_t)G), make_divisor((uint32_t)a.Hkv), a.scale_log2e);
+                     a.lse, ws_plan, parity, ws_pieces, (int)max_tiles, a.Hq, a.Hkv, G, make_divisor((uint32_t)G), make_divisor((uint32_t)a.Hkv), a.scale_log2e);
   return hipGetLastError();
 }
 

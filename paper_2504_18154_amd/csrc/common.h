@@ -25,7 +25,11 @@ constexpr int kPlanShare0 = 8;        // prefill plan: two sets of 8 floats, the
 constexpr int kPlanMeta0 = 24;        // prefill plan: per set, the item count [24 + p] and the grid [26 + p] of the launch that wrote it
 constexpr int kPlanMaxWgs = 1024;     // prefill plan: most workgroups whose busy times a launch records
 constexpr int kPlanBusy0 = kPlanCounter0 + kPlanCounterStride * 2 * kPlanMaxQueues;  // two sets of kPlanMaxWgs busy times (10 ns units)
-constexpr int kPlanHeaderInts = kPlanBusy0 + 2 * kPlanMaxWgs;  // two counter sets, the busy times, then the records
+constexpr int kPlanActive = 1;        // prefill plan: workgroups that share out the batch's key steps (0: items go through the queues)
+constexpr int kPlanPieces0 = kPlanBusy0 + 2 * kPlanMaxWgs;  // per share: pieces of the item it begins that are done (zero between launches)
+constexpr int kPlanShareRec0 = kPlanPieces0 + kPlanMaxWgs;   // one record of kShareInts per workgroup: its share of the key steps
+constexpr int kShareInts = 32;
+constexpr int kPlanHeaderInts = kPlanShareRec0 + kPlanMaxWgs * kShareInts;  // then the query-tile records
 constexpr int kRecInts = 20;          // prefill plan: int32 fields per query-tile record
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
@@ -97,6 +101,7 @@ struct ecoserve_ctx {
   uint32_t* ws_count;          // [max_batch][Hkv], zero between launches: slices of a (sequence, K/V head) that are done
   int32_t ws_splits;
   int32_t* ws_plan;            // prefill plan: header and one record per query tile of the last prefill launch
+  float* ws_pieces;            // prefill: states of the pieces of tiles whose key steps are shared out (bf16, D = 128)
   int64_t plan_tiles;          // largest T / 128 + min(B, T) a prefill call may have; ws_plan has room for G records each (bf16, D = 128)
   int plan_parity;             // which of the plan's two sets of queue counters the next prefill launch takes
   struct {                     // the batch the tile list in ws_plan was made for (valid = false: none)
@@ -185,10 +190,12 @@ hipError_t launch_decode_mfma_merge(const AttnArgs& a, const int32_t* ctx_len, c
 
 // attn_prefill_mfma.hip: bf16, D = 128
 // (ws_plan must hold kPlanHeaderInts + prefill_plan_tiles(B, T, G) * kRecInts int32; make_plan false: the tile list
-// of an earlier launch for the same batch and grid is still in ws_plan; parity alternates from launch to launch)
-int32_t prefill_mfma_grid(const AttnArgs& a, int32_t T, int32_t n_persistent_wgs);
+// of an earlier launch for the same batch and grid is still in ws_plan; parity alternates from launch to launch;
+// ws_pieces: prefill_piece_floats() floats, or NULL: key steps are not shared out)
+int64_t prefill_piece_floats(int32_t n_persistent_wgs);
+int32_t prefill_mfma_grid(const AttnArgs& a, int32_t T, int32_t n_persistent_wgs, const float* ws_pieces);
 hipError_t launch_prefill_mfma(const AttnArgs& a, const int32_t* cu_q, const int32_t* ctx_before, int32_t T,
-                               int32_t* ws_plan, int32_t n_persistent_wgs, bool make_plan,
+                               int32_t* ws_plan, float* ws_pieces, int32_t n_persistent_wgs, bool make_plan,
                                int parity, hipStream_t s);
 
 }  // namespace eco

@@ -1,0 +1,104 @@
+// How a prefill batch of few query tiles is cut into shares of its key steps, one per workgroup (attn_prefill_mfma.hip).
+// The items (tile, K/V head) are numbered head after head, tile after tile; an item is worth its key steps and kItemCost
+// units in front of them for what it costs besides, and the units of all items are cut into equal shares.  Plain integer
+// arithmetic, for the plan kernel and for a host program alike.
+#pragma once
+
+#if defined(__HIPCC__)
+#define ECO_HD __host__ __device__ __forceinline__
+#else
+#define ECO_HD inline
+#endif
+
+namespace eco {
+
+constexpr int kItemCost = 3;
+constexpr int kShareMinUnits = 8;  // fewest units of a share
+
+// Workgroups that take shares, 0: the items go through the queues instead, whole.  `units` of all items together, `heaviest`
+// and `lightest` item in key steps, n_wgs workgroups, two per CU.
+//
+// Shares cost a state of 64 KiB or two per cut, written, read and added up, and even out nothing while they run; items
+// cost what the last of them leave idle.  Both are estimated in microseconds (a step takes about 1.06 with a workgroup alone
+// on its CU, 1.95 with two; an item that shares its CU with another for s steps ends 0.65 s later; 8 are the start and a
+// first merge, 0.9 each further piece of the longest item).  Kernel us, items whole / shares (query / K/V heads, new +
+// cached tokens):
+//   shares:  64/8 366+4351, 366+11326: 228 / 200    64/8 512+16000: 280 / 264     40/8 32+2000: 36 / 19    40/8 32+16000: 244 / 40
+//            40/8 3 x 300+5000: 137 / 111   8/1 5 x 293+8333: 134 / 69    8/1 8192+0: 170 / 148    8/1 2000+0: 36 / 27
+//            52/52 200+4000: 72 / 45        8/1 16 x 100+3000: 57 / 41    40/8 584 items of 170 steps, 72 of them in a second
+//            round: 427 / 370               64/8 8+30000: 445 / 48
+//   whole:   64/8 512+0: 15 / 18            64/8 512+2000: 53 / 53        32/8 4 x 749+89: 40 / 41      40/8 4 x 1024+0: 61 / 63
+//            64/8 4 x 256+2000: 79 / 84     64/8 8 x 256+8000: 513 / 525  8/1 16 x 500+500: 35 / 40     64/8 2048+0: 86 / 84
+ECO_HD int share_wgs(int n_items, long long units, int heaviest, int lightest, int n_wgs) {
+  if (heaviest < kShareMinUnits || n_items <= 0 || n_wgs <= 0 || units > 0x7fffffff) return 0;
+  const float w = (float)n_wgs, u = (float)units;
+  // a share is no shorter than what its merge takes: a tile of s steps then has about 0.7 sqrt(s) pieces at most
+  int least = kShareMinUnits;
+  while (least * least < 2 * heaviest) ++least;
+  const long long most = units / least;
+  const int n = most < 1 ? 1 : most < n_wgs ? (int)most : n_wgs;
+  const float share = u / (float)n, all = 1.95f * u / w;
+  const float alone = 1.06f * share, t_share = (alone > all ? alone : all) + 8.f + 0.9f * (float)heaviest / share;
+  float t_items;
+  if (n_items <= n_wgs) {
+    // the heaviest item, beside the one of rank n_wgs / 2, which is the mean if all are alike, or about this much if not
+    const float mean = u / (float)n_items, h = (float)(heaviest + kItemCost), half = 0.5f * w;
+    const float rest = (float)n_items - half;
+    float second = 0.f;
+    if (rest > 0.f) {
+      second = 2.f * mean * rest / (float)n_items;
+      const float low = (u - half * h) / rest;
+      second = low > second ? low : second;
+      second = second < h ? second : h;
+    }
+    t_items = 1.06f * h + 0.65f * second;
+    t_items = t_items > all ? t_items : all;
+  } else {
+    // the last round is not full, and it is made of the lightest items
+    const int last = n_items % n_wgs;
+    t_items = all + (last > 0 ? 0.6f * (1.f - (float)last / w) * (float)lightest : 0.f);
+  }
+  return t_share < 0.97f * t_items ? n : 0;
+}
+
+// Where a share begins: key step `step` of item `item`.
+struct Cut {
+  int item, step;
+};
+
+// The boundary `off` units into an item of `steps` steps.  It leaves two steps on either side, and lies no later than step
+// `last` (the one that holds the first row's last key: every row then sees a key in the first step of every piece).
+ECO_HD Cut share_cut(int item, int off, int steps, int last) {
+  const int j = off - kItemCost;
+  if (j < 2) return {item, 0};
+  if (j > steps - 2 || j > last) return {item + 1, 0};
+  return {item, j};
+}
+
+// Boundary r of n, in units of all items together.
+ECO_HD int share_begin(int units, int n, int r) { return units / n * r + units % n * r / n; }
+
+// cuts[0..n]: the boundaries, the first at (0, 0), the last behind the last item.  The share that begins the item in which
+// share r begins: the last one that begins at the item's step 0 or before it.
+ECO_HD int share_that_begins(const Cut* cuts, int r) {
+  const int item = cuts[r].item;
+  while (cuts[r].item == item && cuts[r].step > 0) --r;
+  return r;
+}
+// The share that ends `item`, of which share r computes a piece: the last one that begins before the next item.
+ECO_HD int share_that_ends(const Cut* cuts, int n, int r, int item) {
+  while (r + 1 < n && cuts[r + 1].item == item) ++r;
+  return r;
+}
+
+// Workgroup w of n takes share share_of_wg(w, n): workgroup ids go round-robin to the 8 XCDs, and consecutive shares to one.
+ECO_HD int share_of_wg(int w, int n) {
+  const int x = w & 7;
+  return x * (n >> 3) + (x < (n & 7) ? x : n & 7) + (w >> 3);
+}
+
+// The state of an item's piece that share `share` computes: two places per share, since it may hold the end of an item that
+// began before it and the beginning of one that goes on behind it.
+ECO_HD int piece_slot(int share, int begin) { return 2 * share + (share == begin ? 1 : 0); }
+
+}  // namespace eco
