@@ -489,10 +489,9 @@ static int decode_impl(ecoserve_ctx* c, const void* q, int64_t q_row_stride, con
     a.v_new = v_new;
     a.new_row_stride = (int32_t)new_row_stride;
   }
-  const int32_t split_tokens = c->opt_force_plain || c->opt_split_tokens > 0
-                             ? plan_split_tokens(c, B, max_ctx_len)
-                             : decode_any_split_tokens(B, a.Hkv, max_ctx_len, c->num_cu);
-  if (use_mfma(c) && (c->opt_split_tokens > 0 || !decode_any_fits(B, a.Hkv, max_ctx_len, split_tokens, c->num_cu))) {
+  const bool automatic = !c->opt_force_plain && c->opt_split_tokens == 0;
+  const SmallDecode small = use_mfma(c) && automatic ? small_decode(B, a.Hkv, max_ctx_len, c->num_cu) : SmallDecode{0, 0};
+  if (use_mfma(c) && small.n_split == 0) {
     const int n_wgs = c->num_cu * kDecodeWgsPerCu;
     const bool adaptive = c->opt_adaptive && c->opt_split_tokens == 0 && n_wgs % 8 == 0;
     const float* const share_in = adaptive ? c->ws_share + 8 * c->share_parity : nullptr;
@@ -512,9 +511,12 @@ static int decode_impl(ecoserve_ctx* c, const void* q, int64_t q_row_stride, con
                                  n_wgs * 4, s);
     return e == hipSuccess ? ECOSERVE_OK : ECOSERVE_EHIP;
   }
-  const int32_t n_split_max = ceil_div(max_ctx_len, split_tokens);
+  const int32_t split_tokens = use_mfma(c) ? small.split_tokens
+                             : automatic ? decode_any_split_tokens(B, a.Hkv, max_ctx_len, c->num_cu)
+                                         : plan_split_tokens(c, B, max_ctx_len);
+  const int32_t n_split_max = use_mfma(c) ? small.n_split : ceil_div(max_ctx_len, split_tokens);
   // cannot happen: split_tokens >= kMinSplitTokens, and (bf16, 128) comes here with one slice per workgroup that fits
-  if (n_split_max > 1 && (use_mfma(c) ? (int64_t)B * a.Hq * n_split_max > c->ws_slots : n_split_max > c->ws_splits)) return ECOSERVE_EINVAL;
+  if (n_split_max > 1 && (use_mfma(c) ? (int64_t)(split_tokens ? B : 1) * a.Hq * n_split_max > c->ws_slots : n_split_max > c->ws_splits)) return ECOSERVE_EINVAL;
   {
     ProfileScope prof(c, ECOSERVE_KERNEL_DECODE, s);
     e = c->opt_force_plain ? launch_decode_plain(a, ctx_len, split_tokens, n_split_max, c->ws_acc, c->ws_ml, c->ws_splits, s)

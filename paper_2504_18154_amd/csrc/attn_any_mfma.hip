@@ -1,6 +1,6 @@
 // Paged attention on gfx950 matrix cores for every layout except bf16 with head size 128: bf16 of any head size
 // that is a multiple of 8 and fp32 of any that is a multiple of 4, up to 256.  The decode kernel here also serves
-// small batches of that layout (decode_any_fits).
+// small batches of that layout (small_decode).
 //
 // Eq. 2 of Section 2.1 over the paged cache, as the kernels for (bf16, 128) evaluate it, with the arithmetic of
 // the plain kernels: scores, weights and sums are fp32.
@@ -214,16 +214,73 @@ __device__ __forceinline__ void attend_row(const E* __restrict__ qrow, const E* 
 __device__ __forceinline__ void store_shared(float* p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ float load_shared(float* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
-// Decode: grid (splits, Hkv, B), W wavefronts; the blocks of a slice of `split_tokens` tokens of one (sequence, K/V
+// Inclusive prefix sums and the maximum over the lanes of a wavefront, for non-negative x, within the vector unit (a
+// shuffle takes a trip through LDS per step, six of them 0.2 us).
+template <typename F>
+__device__ __forceinline__ int lanes_scan(int x, F f) {
+  x = f(x, __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false));  // row_shr:1
+  x = f(x, __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false));  // row_shr:2
+  x = f(x, __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false));  // row_shr:4
+  x = f(x, __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false));  // row_shr:8
+  x = f(x, __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false));  // row_bcast:15
+  x = f(x, __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false));  // row_bcast:31
+  return x;
+}
+__device__ __forceinline__ int lanes_prefix_sum(int x) {
+  return lanes_scan(x, [](int a, int b) { return a + b; });
+}
+__device__ __forceinline__ int lanes_max(int x) {
+  return __builtin_amdgcn_readlane(lanes_scan(x, [](int a, int b) { return max(a, b); }), 63);
+}
+
+// Balanced slices: lane b holds the number of blocks of sequence b; every K/V head has `slots` workgroups.  Whole contexts,
+// or slices of whole rounds of the W wavefronts, as short as all sequences' slices fit the workgroups and a merge stays short
+// (least_slice).  Returns the slice in blocks; `end`: inclusive prefix sums of the sequences' numbers of slices, `n`.
+// (A trial is one scan; with all lanes as candidates and a loop over the sequences, 16 of them took 0.3 us longer.)
+__device__ __forceinline__ int balanced_slice_blocks(int nb, int Hkv, int slots, int W, int& n, int& end) {
+  const int longest = lanes_max(nb), sum = __builtin_amdgcn_readlane(lanes_prefix_sum(nb), 63);
+  const bool whole = whole_context((float)longest, (float)sum * (float)Hkv);
+  const float shortest = fmaxf(least_slice((float)longest) - 0.5f * (float)W, (float)sum * __builtin_amdgcn_rcpf((float)slots));
+  int st = whole ? max(longest, 1) : ((int)shortest / W + 1) * W;
+  for (;;) {
+    // (exact up to 2^21 blocks; a slice too many would find nothing left to do, and the last of one too few takes the rest)
+    n = (int)(((float)nb + ((float)st - 0.5f)) * __builtin_amdgcn_rcpf((float)st));
+    end = lanes_prefix_sum(n);
+    if (st >= longest || __builtin_amdgcn_readlane(end, 63) <= slots) return st;
+    st += max(st >> 2, W) / W * W;
+  }
+}
+
+// Which slice a workgroup of the decode kernel computes: slice `sp` (-1: none) of sequence b, L tokens in slices of `tokens`, `most`
+// at most.
+struct SliceOf {
+  int b, sp, L, tokens, most;
+};
+template <bool BALANCED>
+__device__ __forceinline__ SliceOf slice_of_workgroup(const int32_t* __restrict__ ctx_len, int B, int Hkv, int split_tokens, int W) {
+  if constexpr (BALANCED) {
+    const int x = blockIdx.y;
+    const int lane = threadIdx.x & 63, len = lane < B ? ctx_len[lane] : 0, nb = (len + 15) >> 4;
+    int n, end;
+    const int st = balanced_slice_blocks(nb, Hkv, gridDim.y, W, n, end);
+    if (x >= __builtin_amdgcn_readlane(end, 63)) return {0, -1, 0, 16, 1};
+    const int b = __popcll(__ballot(end - n <= x)) - 1;  // (lanes behind B have no slices: their first is behind the last)
+    return {b, x - __builtin_amdgcn_readlane(end - n, b), __builtin_amdgcn_readlane(len, b), st * 16, __builtin_amdgcn_readlane(n, b)};
+  } else {
+    return {(int)blockIdx.z, (int)blockIdx.x, ctx_len[blockIdx.z], split_tokens, (int)gridDim.x};
+  }
+}
+
+// Decode: grid (splits, Hkv, B), or (Hkv, slices of all sequences) with balanced slices, W wavefronts; the blocks of a slice of `split_tokens` tokens of one (sequence, K/V
 // head) go to the wavefronts in turn, whose states are combined through LDS.  With one slice the result is final,
 // otherwise it is a partial state, and the last workgroup of the (sequence, K/V head) to be done merges them
 // (`counters`, one per (sequence, K/V head): zero before and after).  With k_new given the workgroup of the last slice takes
 // the newest token (position ctx_len - 1) from the new rows and stores it into the cache.
-template <typename E, int KS, int W, int AUX = 0, bool FULL = true>
+template <typename E, int KS, int W, int AUX = 0, bool FULL = true, bool BALANCED = false>
 __global__ __launch_bounds__(W * 64) void decode_any_kernel(
     const E* __restrict__ q, int q_row_stride, const E* __restrict__ k_new, const E* __restrict__ v_new, int new_row_stride,
     E* k_cache, E* v_cache, const int32_t* __restrict__ block_table, int bt_stride, const int32_t* __restrict__ ctx_len,
-    E* __restrict__ out, float* __restrict__ lse, float* ws_acc, float* ws_ml, uint32_t* counters, int split_tokens, int Hq,
+    E* __restrict__ out, float* __restrict__ lse, float* ws_acc, float* ws_ml, uint32_t* counters, int split_tokens, int B, int Hq,
     int Hkv, int G, int D, float scale_log2e) {
   typedef Block<E, KS, AUX, FULL> Blk;
   constexpr int X = Elem<E>::X, NK = Blk::NK, NV = Blk::NV;
@@ -232,12 +289,14 @@ __global__ __launch_bounds__(W * 64) void decode_any_kernel(
   __shared__ float s_m[W][16], s_l[W][16], s_tot[2][16];
   __shared__ __attribute__((aligned(16))) float s_acc[W][16][kSlice + 4];
   __shared__ int s_bad, s_order;
-  const int sp = blockIdx.x, g = blockIdx.y, b = blockIdx.z;
+  const int g = BALANCED ? blockIdx.x : blockIdx.y;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int col = lane & 15, quad = lane >> 4;
   // Asked for with the length, before anything that depends on it: the new rows, the query rows.  (The block ids have to
   // wait: entries behind the sequence's last block are not read.)
-  const int L = ctx_len[b];
+  const SliceOf at = slice_of_workgroup<BALANCED>(ctx_len, B, Hkv, split_tokens, W);
+  if (at.sp < 0) return;
+  const int b = at.b, sp = at.sp, L = at.L;
   const int32_t* const bt_row = block_table + (size_t)b * bt_stride;
   const bool fused = k_new != nullptr;
   constexpr int NN = (32 * KS + W * 64 - 1) / (W * 64);  // elements of the new rows per thread
@@ -245,7 +304,7 @@ __global__ __launch_bounds__(W * 64) void decode_any_kernel(
 #pragma unroll
   for (int i = 0; i < NN; ++i) {
     const int d = tid + i * W * 64;
-    const bool in = fused && d < D;
+    const bool in = (BALANCED ? at.sp == at.most - 1 && fused : fused) && d < D;
     kn[i] = in ? k_new[(size_t)b * new_row_stride + (size_t)g * D + d] : E(0);
     vn[i] = in ? v_new[(size_t)b * new_row_stride + (size_t)g * D + d] : E(0);
   }
@@ -256,13 +315,17 @@ __global__ __launch_bounds__(W * 64) void decode_any_kernel(
     const u32x4 z = {0u, 0u, 0u, 0u};
     qf[j] = col < G && d < D ? *reinterpret_cast<const u32x4*>(q + (size_t)b * q_row_stride + (size_t)(g * G + col) * D + d) : z;
   }
-  const Slice slice = decode_slice(L, split_tokens, (int)gridDim.x, sp);
+  const Slice slice = decode_slice(L, at.tokens, at.most, sp);
   const int n_split = slice.n, t0 = slice.t0, t1 = slice.t1;
   if (sp >= n_split) return;
   const WaveBlocks blocks = wave_blocks(t0, t1, wave, W);  // this wavefront's
   const int n = blocks.n;
   int ids = lane < n ? bt_row[blocks.first + W * lane] : 0;
-  const size_t piece = (size_t)16 * D * sizeof(E);
+  // (a scalar copy of its own: the merge below takes D into vector registers, and the blocks' addresses with it, were it the
+  // same value - every load then goes through a loop over its descriptors, 1 us per call)
+  int d_scalar = D;
+  asm("" : "+s"(d_scalar));
+  const size_t piece = (size_t)16 * d_scalar * sizeof(E);
   const bool newest = fused && sp == n_split - 1;
   const char* const kc = reinterpret_cast<const char*>(k_cache);
   const char* const vc = reinterpret_cast<const char*>(v_cache);
@@ -364,7 +427,9 @@ __global__ __launch_bounds__(W * 64) void decode_any_kernel(
     s_tot[1][col] = total;
   }
   const bool final_result = n_split == 1;
-  const size_t slot0 = ((size_t)b * Hq + (size_t)g * G) * gridDim.x + sp, slot_step = gridDim.x;  // partial states: [B][Hq][slices]
+  // Partial states: [B][Hq][slices], or (balanced) [slices of all sequences][Hq].  slot0: of this slice and the group's first head.
+  const size_t slot0 = BALANCED ? (size_t)blockIdx.y * Hq + (size_t)g * G : ((size_t)b * Hq + (size_t)g * G) * gridDim.x + sp;
+  const size_t slot_step = BALANCED ? 1 : gridDim.x, next_slice = BALANCED ? Hq : 1;
 #pragma unroll
   for (int t = 0; t < NV; t += kTiles) {
 #pragma unroll
@@ -422,12 +487,21 @@ __global__ __launch_bounds__(W * 64) void decode_any_kernel(
   __syncthreads();
   if (s_order != n_split - 1) return;
   for (int h = wave; h < G; h += W) {
-    const size_t slot = slot0 - sp + h * slot_step;
+    const size_t slot = slot0 - sp * next_slice + h * slot_step;
+    auto states = [&](int k, float (&ak)[8][(KS + 1) / 2]) {  // of slices k .. k + 7
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+#pragma unroll
+        for (int r = 0; r < (KS + 1) / 2; ++r)
+          ak[j][r] = k + j < n_split && lane + 64 * r < D ? load_shared(ws_acc + (slot + (k + j) * next_slice) * D + lane + 64 * r) : 0.f;
+    };
+    float ak[8][(KS + 1) / 2];
+    states(0, ak);  // (asked for together with the slices' maxima)
     float m2 = -INFINITY, l2 = 0.f, o2[4] = {0.f, 0.f, 0.f, 0.f};
     for (int base = 0; base < n_split; base += 64) {  // 64 slices at a time: lane k holds the (max, sum) of slice k
       const int nk = min(64, n_split - base);
-      const float mk = lane < nk ? load_shared(ws_ml + (slot + base + lane) * 2) : -INFINITY;
-      const float lk = lane < nk ? load_shared(ws_ml + (slot + base + lane) * 2 + 1) : 0.f;
+      const float mk = lane < nk ? load_shared(ws_ml + (slot + (base + lane) * next_slice) * 2) : -INFINITY;
+      const float lk = lane < nk ? load_shared(ws_ml + (slot + (base + lane) * next_slice) * 2 + 1) : 0.f;
       const float m_new = fmaxf(m2, wave_max(mk));
       // (slices whose scores are all -inf so far weigh nothing: their m is -inf, their sums are zero)
       const float mu = m_new == -INFINITY ? 0.f : m_new;
@@ -436,15 +510,10 @@ __global__ __launch_bounds__(W * 64) void decode_any_kernel(
       l2 = l2 * old + wave_sum(lk * wk);
 #pragma unroll
       for (int r = 0; r < 4; ++r) o2[r] *= old;
-      for (int k = 0; k < nk; k += 4) {
-        float ak[4][(KS + 1) / 2];
+      for (int k = 0; k < nk; k += 8) {
+        if (base + k > 0) states(base + k, ak);
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-          for (int r = 0; r < (KS + 1) / 2; ++r)
-            ak[j][r] = k + j < nk && lane + 64 * r < D ? load_shared(ws_acc + (slot + base + k + j) * D + lane + 64 * r) : 0.f;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
+        for (int j = 0; j < 8; ++j) {
           const float w = k + j < nk ? __shfl(wk, k + j) : 0.f;
 #pragma unroll
           for (int r = 0; r < (KS + 1) / 2; ++r) o2[r] += ak[j][r] * w;
@@ -699,16 +768,18 @@ void launch_prefill_typed(const AttnArgs& a, const int32_t* cu_q, const int32_t*
 template <typename E>
 void launch_decode_typed(const AttnArgs& a, const int32_t* ctx_len, int32_t split_tokens, int32_t n_split_max, float* ws_acc,
                          float* ws_ml, uint32_t* counters, bool many, hipStream_t s) {
+  const bool balanced = split_tokens == 0;
   auto launch = [&](auto kernel, int W) {
-    hipLaunchKernelGGL(kernel, dim3((unsigned)n_split_max, (unsigned)a.Hkv, (unsigned)a.B), dim3(W * 64), 0, s,
+    hipLaunchKernelGGL(kernel, balanced ? dim3((unsigned)a.Hkv, (unsigned)n_split_max) : dim3((unsigned)n_split_max, (unsigned)a.Hkv, (unsigned)a.B), dim3(W * 64), 0, s,
                        (const E*)a.q, a.q_row_stride, (const E*)a.k_new, (const E*)a.v_new, a.new_row_stride,
                        (E*)const_cast<void*>(a.k_cache), (E*)const_cast<void*>(a.v_cache), a.block_table, a.bt_stride, ctx_len,
-                       (E*)a.out, a.lse, ws_acc, ws_ml, counters, split_tokens, a.Hq, a.Hkv, a.Hq / a.Hkv, a.D, a.scale_log2e);
+                       (E*)a.out, a.lse, ws_acc, ws_ml, counters, split_tokens, a.B, a.Hq, a.Hkv, a.Hq / a.Hkv, a.D, a.scale_log2e);
   };
   for_head_size(a.D, [&](auto ks) {
     // eight wavefronts per workgroup while two blocks of K and V fit beside the rest in 256 registers
     constexpr int KS = decltype(ks)::value, W = KS > (sizeof(E) == 4 ? 4 : 6) ? 4 : 8;
     if constexpr (KS == 4 && sizeof(E) == 2) {
+      if (a.D == 128 && balanced) return launch(decode_any_kernel<E, KS, W, 0, false, true>, W);
       if (a.D == 128) return many ? launch(decode_any_kernel<E, KS, 4, kNonTemporal, false>, 4) : launch(decode_any_kernel<E, KS, W, 0, false>, W);
       if (many) return launch(decode_any_kernel<E, KS, 4, kNonTemporal>, 4);
     }
@@ -727,15 +798,33 @@ int32_t decode_any_split_tokens(int32_t B, int32_t Hkv, int32_t max_ctx_len, int
   return st;
 }
 
-// For (bf16, 128): whether the batch is small enough for this kernel, i.e. all its workgroups run at once - one of eight
-// wavefronts per CU, or (short contexts) two of four.  It needs no numbering of the batch and no second launch, which
-// is what such a batch spends its time on in the persistent kernel (us per call there and here, 40 query heads on 8 K/V
-// heads, the same buffers from call to call: 1 x 777 tokens 14.7, 9.0; 1 x 8000: 30.3, 12.7; 4 x 2000: 21.1, 11.0; 16 x 1000:
-// 20.7, 14.1; 32 x 200: 15.7, 7.4; 64 x 500: 35.0, 23.5), but nothing evens out the lengths of more workgroups than fit: 128
-// sequences around 500 tokens, lognormal, take 62 there and 74 here, 40 of them 25 and 28 (128 of 500 each: 54 and 50).
-bool decode_any_fits(int32_t B, int32_t Hkv, int32_t max_ctx_len, int32_t split_tokens, int32_t num_cu) {
+// For (bf16, 128): how this kernel takes a small batch, n_split 0 if it does not.  It needs no numbering of the batch and no
+// second launch, which is what such a batch spends its time on in the persistent kernel.
+//   Several sequences, one of them of more than 768 tokens, and eight workgroups (one per CU) or more per five (sequence, K/V
+//   head)s: balanced slices.  Us per call before (uniform slices or the persistent kernel) / balanced: 64 query heads on 8, 16 x
+//   20..2000 tokens 18.4 / 15.9, 8 x 20..8000 19.2 / 15.3; 5 on 1, 13 x 745..5960 16.2 / 12.8; 8 on 1, 64 x 50..8000 37.0 / 16.2; 32 on 8,
+//   18 x 116..935 15.5 / 14.4, 9 x 1196..9574 35.6 / 31.5; 40 on 8, 20 x 2000 38.9 / 34.5, 20 x 100..3000 30.2 / 28.8.  Finding the slices
+//   takes half a microsecond, which equal lengths do not give back: 16 x 2000 29.1 / 29.7, 4 x 2000 13.9 / 14.9.  Fewer spare workgroups
+//   even out too little (24 x 100..3000 33 / 34, 24 x 1000..10000 84 / 98), and from 400 MB on the persistent kernel's
+//   stream is the faster one (16 x 8000 93 / 99).
+//   No balancing where every sequence may have as many slices as one of max_ctx_len tokens gets for itself: the slices of
+//   balanced_slice_blocks for that (1 x 777: 9.4 / 8.5, 1 x 1000: 10.7 / 8.9, 1 x 16000: 21.9 / 20.8).
+//   Else uniform slices if all workgroups run at once - one of eight wavefronts per CU, or (short contexts) two of four (us per call
+//   persistent / here: 16 x 1000 tokens 20.7 / 14.1; 32 x 200: 15.7 / 7.4; 64 x 500: 35.0 / 23.5), but nothing evens out the
+//   lengths of more workgroups than fit: 128 sequences around 500 tokens, lognormal, take 62 there and 74 here, 40 of them 25
+//   and 28 (128 of 500 each: 54 and 50).
+SmallDecode small_decode(int32_t B, int32_t Hkv, int32_t max_ctx_len, int32_t num_cu) {
   const int64_t pairs = (int64_t)B * Hkv;
-  return pairs * ((max_ctx_len + split_tokens - 1) / split_tokens) <= num_cu || (max_ctx_len <= 512 && pairs <= 2 * num_cu);
+  const int32_t nb = (max_ctx_len + kBlockSize - 1) / kBlockSize, slots = num_cu / Hkv;
+  const bool whole = whole_context((float)nb, (float)nb * (float)Hkv);  // (also of more sequences, then)
+  if (!whole && slots > 0 && pairs * ((max_ctx_len + 1023) / 1024) <= num_cu) {
+    int32_t st = ((int32_t)least_slice((float)nb) + 4) / 8 * 8;  // whole rounds of eight wavefronts
+    if (B == 1) st = std::max(st, (nb + 8 * slots - 1) / (8 * slots) * 8);
+    if (B * ((nb + st - 1) / st) <= slots && (B == 1 || nb > 48)) return {st * kBlockSize, (nb + st - 1) / st};
+  }
+  if (B > 1 && B <= 64 && nb > 48 && 8 * B <= 5 * slots && pairs * max_ctx_len <= 800000) return {0, slots};
+  const int32_t st = decode_any_split_tokens(B, Hkv, max_ctx_len, num_cu), n = (max_ctx_len + st - 1) / st;
+  return pairs * n <= num_cu || (max_ctx_len <= 512 && pairs <= 2 * num_cu) ? SmallDecode{st, n} : SmallDecode{0, 0};
 }
 
 hipError_t launch_prefill_any(const AttnArgs& a, const int32_t* cu_q, const int32_t* ctx_before, int32_t T, hipStream_t s) {

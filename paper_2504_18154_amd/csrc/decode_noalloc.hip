@@ -26,7 +26,7 @@ constexpr size_t kAccFloats = (size_t)2 * kNoallocMaxWaves * kMaxGroup * 128;  /
 constexpr size_t kMlFloats = (size_t)2 * kNoallocMaxWaves * kMaxGroup * 2;
 constexpr size_t kMetaInts = (kMaxBatch + 19 + 63) / 64 * 64;
 constexpr size_t kCutInts = (size_t)4 * kNoallocMaxWaves;
-constexpr size_t kCountInts = (size_t)2 * kNoallocMaxWgs;  // decode_any_fits: at most this many (sequence, K/V head)s
+constexpr size_t kCountInts = (size_t)2 * kNoallocMaxWgs;  // small_decode: at most this many (sequence, K/V head)s
 constexpr size_t kScratchBytes = (kAccFloats + kMlFloats + kMetaInts + kCutInts + kCountInts) * 4;  // 16.3 MiB
 
 // On the host this name is only a handle for hipGetSymbolAddress; device code and kernel arguments use the
@@ -122,12 +122,11 @@ extern "C" int ecoserve_attn_decode_noalloc(int device, const ecoserve_layout* l
 
   const int n_wgs = dev.num_cu * kDecodeWgsPerCu < kNoallocMaxWgs ? dev.num_cu * kDecodeWgsPerCu : kNoallocMaxWgs;
   hipStream_t s = (hipStream_t)stream;
-  const int32_t split_tokens = decode_any_split_tokens(B, a.Hkv, max_ctx_len, n_wgs);
-  if (decode_any_fits(B, a.Hkv, max_ctx_len, split_tokens, n_wgs)) {
-    // (at most n_wgs slices in all, or one per (sequence, K/V head): B Hq n_split partial states fit the two groups of
-    // kMaxGroup slots per wavefront)
-    return launch_decode_any(a, ctx_len, split_tokens, (max_ctx_len + split_tokens - 1) / split_tokens, ws_acc, ws_ml,
-                             reinterpret_cast<uint32_t*>(ws_cut + kCutInts),
+  const SmallDecode small = small_decode(B, a.Hkv, max_ctx_len, n_wgs);
+  if (small.n_split > 0) {
+    // (at most n_wgs slices in all, or one per (sequence, K/V head) of up to twice as many: their states of Hq / Hkv <= kMaxGroup
+    // heads fit the two groups of kMaxGroup slots per wavefront)
+    return launch_decode_any(a, ctx_len, small.split_tokens, small.n_split, ws_acc, ws_ml, reinterpret_cast<uint32_t*>(ws_cut + kCutInts),
                              n_wgs, s) == hipSuccess ? ECOSERVE_OK : ECOSERVE_EHIP;
   }
   // (a slot group holds G <= kMaxGroup states, so the array covers kNoallocMaxWaves wavefronts whatever G is)

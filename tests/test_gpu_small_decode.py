@@ -117,3 +117,43 @@ def test_the_persistent_kernel_passes_over_sequences_without_tokens():
     compare_lse("rows of the non-empty sequences", lse, ref_lse, "bf16", rows=live)
     compare("without a context", no, ref, "bf16", rows=live)
     layer.close()
+
+
+# several sequences, cut into slices that fill the workgroups: lengths and slices at the edges of blocks, of the wavefronts' rounds
+# and of the rule that leaves contexts whole; empty sequences; as many sequences as a wavefront has lanes
+BALANCED = [((40, 8), [769, 1]), ((40, 8), [2000, 128, 129, 127, 16, 17, 0, 1024]), ((64, 8), [1025] * 20), ((5, 1), [0, 3000, 0, 0, 2999, 1, 0]),
+            ((16, 1), [4095, 4096, 4097] + [1] * 61), ((3, 3), [900, 700, 5000]), ((52, 52), [800, 1500]), ((8, 1), [30000, 20, 700])]
+
+
+@pytest.mark.parametrize("heads,lens", BALANCED, ids=[f"{h[0]}x{h[1]}-B{len(n)}-L{max(n)}" for h, n in BALANCED])
+@pytest.mark.parametrize("loose", [False, True], ids=["tight", "loose"])
+def test_balanced_slices(heads, lens, loose):
+    model = wl.ModelShape("balanced", heads[0], heads[1], 128, 1, "bf16")
+    lens = np.asarray(lens, dtype=np.int32)
+    say(f"decode, balanced slices, heads {heads}, lengths {lens.tolist()}")
+    pb = wl.prefill_batch(model, lens, 57)
+    bound = int(lens.max()) + (3000 if loose else 0)  # the caller's bound on the lengths
+    table = np.pad(pb.block_table, ((0, 0), (0, (bound + 15) // 16 - pb.block_table.shape[1])), constant_values=2**30)  # never read there
+    layer = Layer(model, pb.num_blocks, pb.B, table.shape[1])
+    k, v = (wl.randn((pb.T, model.Hkv, 128), "bf16", s) for s in (1, 2))
+    layer.append(k, v, pb.cu_q, pb.ctx_before, pb.block_table)
+    q = wl.randn((pb.B, model.Hq, 128), "bf16", 3)
+    some = np.flatnonzero(lens)
+    ref, ref_lse = layer.decode_oracle(q[torch.as_tensor(some)], pb.block_table[some], lens[some])
+    out, lse = layer.decode_gpu(q, table, lens, bound)
+    idx = torch.as_tensor(some, device="cuda")
+    compare("decode", out[idx], ref, "bf16")
+    compare_lse("decode", lse[idx], ref_lse, "bf16")
+    last = torch.as_tensor(np.maximum(pb.cu_q[1:] - 1, 0), dtype=torch.long)
+    layer.wipe_newest(pb.block_table[some], lens[some])
+    bt, tot = dev_i32(table), dev_i32(lens)
+    for call in range(3):
+        fused, fused_lse = torch.full_like(out, float("nan")), torch.full_like(lse, float("nan"))
+        layer.ctx.attn_decode_append(q.cuda(), k[last].cuda(), v[last].cuda(), layer.kc, layer.vc, bt, tot, fused, bound, fused_lse)
+        assert torch.equal(fused[idx], out[idx]) and torch.equal(fused_lse[idx], lse[idx]), f"call {call} with the append fused in differs"
+    no = torch.full_like(out, float("nan"))
+    assert binding.attn_decode_noalloc(layer.ctx.layout, q.cuda(), layer.kc, layer.vc, bt, tot, no, bound) == binding.OK
+    torch.cuda.synchronize()
+    assert torch.equal(no[idx], out[idx]), "the call without a context differs"
+    layer.assert_cache_bit_exact()
+    layer.close()
