@@ -280,8 +280,8 @@ template <typename E, int KS, int W, int AUX = 0, bool FULL = true, bool BALANCE
 __global__ __launch_bounds__(W * 64) void decode_any_kernel(
     const E* __restrict__ q, int q_row_stride, const E* __restrict__ k_new, const E* __restrict__ v_new, int new_row_stride,
     E* k_cache, E* v_cache, const int32_t* __restrict__ block_table, int bt_stride, const int32_t* __restrict__ ctx_len,
-    E* __restrict__ out, float* __restrict__ lse, float* ws_acc, float* ws_ml, uint32_t* counters, int split_tokens, int B, int Hq,
-    int Hkv, int G, int D, float scale_log2e) {
+    E* __restrict__ out, float* __restrict__ lse, float* ws_acc, float* ws_ml, uint32_t* counters, int split_tokens, int Hq,
+    int Hkv, int G, int D, float scale_log2e, int B) {
   typedef Block<E, KS, AUX, FULL> Blk;
   constexpr int X = Elem<E>::X, NK = Blk::NK, NV = Blk::NV;
   constexpr int kTiles = NV < 8 ? NV : 8, kSlice = kTiles * 16;  // elements of a head vector combined at a time
@@ -773,7 +773,7 @@ void launch_decode_typed(const AttnArgs& a, const int32_t* ctx_len, int32_t spli
     hipLaunchKernelGGL(kernel, balanced ? dim3((unsigned)a.Hkv, (unsigned)n_split_max) : dim3((unsigned)n_split_max, (unsigned)a.Hkv, (unsigned)a.B), dim3(W * 64), 0, s,
                        (const E*)a.q, a.q_row_stride, (const E*)a.k_new, (const E*)a.v_new, a.new_row_stride,
                        (E*)const_cast<void*>(a.k_cache), (E*)const_cast<void*>(a.v_cache), a.block_table, a.bt_stride, ctx_len,
-                       (E*)a.out, a.lse, ws_acc, ws_ml, counters, split_tokens, a.B, a.Hq, a.Hkv, a.Hq / a.Hkv, a.D, a.scale_log2e);
+                       (E*)a.out, a.lse, ws_acc, ws_ml, counters, split_tokens, a.Hq, a.Hkv, a.Hq / a.Hkv, a.D, a.scale_log2e, a.B);
   };
   for_head_size(a.D, [&](auto ks) {
     // eight wavefronts per workgroup while two blocks of K and V fit beside the rest in 256 registers
