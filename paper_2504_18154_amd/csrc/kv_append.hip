@@ -10,10 +10,10 @@
 // Eq. 1); destination is the library's block layout
 //   K: [blk][Hkv][D/x][16 slots][x]   (x = elements per 16 bytes)
 //   V: [blk][Hkv][D][16 slots]
-// One workgroup fills one destination block for up to four adjacent K/V heads: up to 16 token
+// One workgroup fills one destination block for one, two or four adjacent K/V heads: up to 16 token
 // rows in, per head one contiguous K piece and one contiguous V piece out (4 KiB each for
 // bf16, D = 128).  Several heads per workgroup keep more loads in flight per thread and
-// spread the cost of finding the block over more bytes.
+// spread the cost of finding the block over more bytes; a small call ends sooner with one (launch_typed has the line).
 // K units keep their 16 bytes and only change place, so they are copied directly with the
 // writes running along the destination.  V needs a transposition (16 slots of one element
 // become contiguous): the token rows are staged in LDS with coalesced reads and written
@@ -29,13 +29,15 @@
 // 5.4 us; the tables of the whole batch also no longer take the LDS of a workgroup).
 // A call that brings at most one token per sequence (the decode step) takes a leaner kernel:
 // one wavefront per (sequence, K/V head), no numbering, no staging.
+#include <type_traits>
+
 #include "common.h"
 
 namespace eco {
 
 constexpr int kAppendThreads = 256;
 
-template <typename E, int HPW>
+template <typename E, int HPW, bool kAtOnce>
 __global__ __launch_bounds__(kAppendThreads) void kv_append_kernel(E* __restrict__ k_cache, E* __restrict__ v_cache,
                                                                     const E* __restrict__ k_new,
                                                                     const E* __restrict__ v_new, int new_row_stride,
@@ -62,10 +64,28 @@ __global__ __launch_bounds__(kAppendThreads) void kv_append_kernel(E* __restrict
   const int64_t blk = block_table[(size_t)b * bt_stride + j];
   const int upr = D / X;                              // 16-byte units per head row
 
+  E* kdst = k_cache + ((size_t)blk * Hkv + g0) * 16 * D;
+  if constexpr (kAtOnce) {
+    // one unit of K and one of V per thread and head (16 D / X <= threads), all asked for before the first use
+    const int kslot = tid & 15, kc = tid >> 4, vslot = tid / upr, vc = tid % upr;
+    const bool kin = tid < 16 * upr && kslot >= lo && kslot < hi, vin = tid < 16 * upr && vslot >= lo && vslot < hi;
+    u4 kval[HPW], vval[HPW];
+    const E* const ksrc = k_new + (size_t)(t_slot0 + kslot) * new_row_stride + g0 * D + kc * X;
+    const E* const vsrc = v_new + (size_t)(t_slot0 + vslot) * new_row_stride + g0 * D + vc * X;
+#pragma unroll
+    for (int h = 0; h < HPW; ++h) vval[h] = vin ? *reinterpret_cast<const u4*>(vsrc + (size_t)h * D) : u4{0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int h = 0; h < HPW; ++h) kval[h] = kin ? *reinterpret_cast<const u4*>(ksrc + (size_t)h * D) : u4{0u, 0u, 0u, 0u};
+    if (vin)
+#pragma unroll
+      for (int h = 0; h < HPW; ++h) *reinterpret_cast<u4*>(vt + ((size_t)h * 16 + vslot) * vrow + vc * X) = vval[h];
+    if (kin)
+#pragma unroll
+      for (int h = 0; h < HPW; ++h) *reinterpret_cast<u4*>(kdst + ((size_t)h * 16 * D) + (size_t)tid * X) = kval[h];
+  } else {
   // The HPW heads of one token are adjacent in the source, so each pass below issues HPW
   // independent 16-byte loads per thread before the first use.
   // K: unit (c, slot) -> destination [c][slot][X]; threads run along the destination
-  E* kdst = k_cache + ((size_t)blk * Hkv + g0) * 16 * D;
   for (int u = tid; u < 16 * upr; u += kAppendThreads) {
     const int slot = u & 15, c = u >> 4;
     if (slot >= lo && slot < hi) {
@@ -88,6 +108,7 @@ __global__ __launch_bounds__(kAppendThreads) void kv_append_kernel(E* __restrict
 #pragma unroll
       for (int h = 0; h < HPW; ++h) *reinterpret_cast<u4*>(vt + ((size_t)h * 16 + slot) * vrow + c * X) = val[h];
     }
+  }
   }
   __syncthreads();
   // ... and write [d][16 slots] in 16-byte units of X slots (threads run along the destination)
@@ -141,7 +162,7 @@ static size_t append_lds_bytes(int D, int hpw) {
   return (size_t)hpw * 16 * (D + Elem<E>::X) * sizeof(E);
 }
 
-template <typename E, int HPW>
+template <typename E, int HPW, bool kAtOnce>
 static void launch_tiled(const ecoserve_layout& L, void* k_cache, void* v_cache, const void* k_new, const void* v_new,
                          int32_t new_row_stride, const int32_t* cu_q, const int32_t* ctx_before, const int32_t* block_table,
                          int32_t bt_stride, int32_t B, int32_t T, hipStream_t s) {
@@ -149,7 +170,7 @@ static void launch_tiled(const ecoserve_layout& L, void* k_cache, void* v_cache,
   const dim3 grid((unsigned)max_units, (unsigned)(L.num_kv_heads / HPW));
   // (above 64 KiB - fp32 with large heads - the kernel's limit was raised when the context was created)
   const size_t lds = append_lds_bytes<E>(L.head_dim, HPW);
-  hipLaunchKernelGGL((kv_append_kernel<E, HPW>), grid, dim3(kAppendThreads), lds, s, (E*)k_cache, (E*)v_cache,
+  hipLaunchKernelGGL((kv_append_kernel<E, HPW, kAtOnce>), grid, dim3(kAppendThreads), lds, s, (E*)k_cache, (E*)v_cache,
                      (const E*)k_new, (const E*)v_new, new_row_stride, cu_q, ctx_before, block_table, bt_stride, B,
                      L.num_kv_heads, L.head_dim);
 }
@@ -157,7 +178,7 @@ static void launch_tiled(const ecoserve_layout& L, void* k_cache, void* v_cache,
 template <typename E>
 static void launch_typed(const ecoserve_layout& L, void* k_cache, void* v_cache, const void* k_new, const void* v_new,
                          int32_t new_row_stride, const int32_t* cu_q, const int32_t* ctx_before, const int32_t* block_table,
-                         int32_t bt_stride, int32_t B, int32_t T, int32_t max_new_len, int32_t pos_bias,
+                         int32_t bt_stride, int32_t B, int32_t T, int32_t max_new_len, int32_t pos_bias, int num_cu,
                          hipStream_t s) {
   if (max_new_len <= 1) {
     const int per_wg = kAppendThreads / 64;
@@ -165,12 +186,29 @@ static void launch_typed(const ecoserve_layout& L, void* k_cache, void* v_cache,
     hipLaunchKernelGGL((kv_append_one_kernel<E>), grid, dim3(kAppendThreads), 0, s, (E*)k_cache, (E*)v_cache,
                        (const E*)k_new, (const E*)v_new, new_row_stride, cu_q, ctx_before, block_table, bt_stride, B,
                        L.num_kv_heads, L.head_dim, pos_bias);
-  } else if (L.num_kv_heads % 4 == 0) {
-    launch_tiled<E, 4>(L, k_cache, v_cache, k_new, v_new, new_row_stride, cu_q, ctx_before, block_table, bt_stride, B, T, s);
-  } else if (L.num_kv_heads % 2 == 0) {
-    launch_tiled<E, 2>(L, k_cache, v_cache, k_new, v_new, new_row_stride, cu_q, ctx_before, block_table, bt_stride, B, T, s);
+    return;
+  }
+  // K/V heads per workgroup.  A small call is a chain of round trips, and the less each workgroup brings in the sooner it
+  // ends: one head, all loads asked for at once, while no more than eight workgroups per CU come of it.  Beyond that the cost
+  // of finding the block counts, and adjacent heads share it: two, and four from about forty heads' blocks per CU.
+  // (us, four heads / two / one / one at once, 8 K/V heads of bf16, 128, unless named: 93 tokens 4.95 / 3.66 / 3.10 / 2.92, 512
+  // 4.59 / 3.94 / 3.77 / 3.44, 2048 6.34 / 5.65 / 5.38 / 5.31, 64 x 20 6.15 / 5.35 / 5.17 / 4.93, 52 heads 5 x 51 6.53 / 5.63 / 5.18 / 5.12;
+  // 16 x 200 9.11 / 8.69 / 8.62 / 8.74, 4096 10.72 / 9.67 / 9.41 / 9.77, 8192 16.81 / 15.53 / 16.06 / 16.70, 15 x 1024 26.74 / 25.81 /
+  // 26.86 / 27.27, 256 x 20 19.26 / 17.42 / 18.87 / 18.35, 52 heads 4 x 500 25.99 / 25.10 / 25.90 / 26.28; 4 x 8192 52.79 / 53.65 / 54.10 /
+  // 56.08.)
+  const int64_t one_head_wgs = ((int64_t)T / 16 + 2 * (int64_t)B) * L.num_kv_heads;
+  auto launch = [&](auto hpw, auto at_once) {
+    launch_tiled<E, decltype(hpw)::value, decltype(at_once)::value>(L, k_cache, v_cache, k_new, v_new, new_row_stride, cu_q, ctx_before, block_table,
+                                                                    bt_stride, B, T, s);
+  };
+  typedef std::integral_constant<int, 1> One;
+  if (one_head_wgs <= 8 * num_cu || L.num_kv_heads % 2 != 0) {
+    if (one_head_wgs <= 8 * num_cu && 16 * L.head_dim / Elem<E>::X <= kAppendThreads) launch(One(), std::true_type());
+    else launch(One(), std::false_type());
+  } else if (one_head_wgs <= 40 * num_cu || L.num_kv_heads % 4 != 0) {
+    launch(std::integral_constant<int, 2>(), std::false_type());
   } else {
-    launch_tiled<E, 1>(L, k_cache, v_cache, k_new, v_new, new_row_stride, cu_q, ctx_before, block_table, bt_stride, B, T, s);
+    launch(std::integral_constant<int, 4>(), std::false_type());
   }
 }
 
@@ -178,7 +216,7 @@ template <typename E, int HPW>
 static hipError_t raise_lds_limit(const ecoserve_ctx* ctx) {
   const size_t lds = append_lds_bytes<E>(ctx->lay.head_dim, HPW);
   if (lds <= 60 * 1024) return hipSuccess;
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(&kv_append_kernel<E, HPW>),
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(&kv_append_kernel<E, HPW, false>),
                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
 }
 
@@ -198,10 +236,10 @@ hipError_t launch_kv_append(const ecoserve_ctx* ctx, void* k_cache, void* v_cach
   const ecoserve_layout& L = ctx->lay;
   if (L.dtype == ECOSERVE_BF16)
     launch_typed<uint16_t>(L, k_cache, v_cache, k_new, v_new, new_row_stride, cu_q, ctx_before, block_table, bt_stride, B, T,
-                           max_new_len, pos_bias, s);
+                           max_new_len, pos_bias, ctx->num_cu, s);
   else
     launch_typed<float>(L, k_cache, v_cache, k_new, v_new, new_row_stride, cu_q, ctx_before, block_table, bt_stride, B, T,
-                        max_new_len, pos_bias, s);
+                        max_new_len, pos_bias, ctx->num_cu, s);
   return hipGetLastError();
 }
 
