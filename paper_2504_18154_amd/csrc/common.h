@@ -261,21 +261,6 @@ __device__ __forceinline__ size_t v_index(int64_t blk, int g, int slot, int d, i
   return (((size_t)blk * Hkv + g) * D + d) * kBlockSize + slot;
 }
 
-// One wavefront stores one new token of one (sequence, K/V head) into its cache slot: the K row as
-// 16-byte units, the V row scattered into the slot's column.  `lane` 0..63.
-template <typename E>
-__device__ __forceinline__ void append_one_row(E* __restrict__ k_cache, E* __restrict__ v_cache,
-                                               const E* __restrict__ ksrc, const E* __restrict__ vsrc, int64_t blk,
-                                               int g, int slot, int Hkv, int D, int lane) {
-  constexpr int X = Elem<E>::X;
-  typedef uint32_t u4 __attribute__((ext_vector_type(4)));
-  E* kdst = k_cache + ((size_t)blk * Hkv + g) * 16 * D + (size_t)slot * X;
-  for (int c = lane; c < D / X; c += 64)
-    *reinterpret_cast<u4*>(kdst + (size_t)c * 16 * X) = *reinterpret_cast<const u4*>(ksrc + c * X);
-  E* vdst = v_cache + ((size_t)blk * Hkv + g) * D * 16 + slot;
-  for (int d = lane; d < D; d += 64) vdst[(size_t)d * 16] = vsrc[d];
-}
-
 // The sequence that work unit `unit` belongs to, for units numbered so that sequence b's begin at
 // first(cu_q[b], b), increasing in b, first(0, 0) = 0: a search with 64 candidates at a time, no prefix sum over the batch
 // and no barrier; what the caller needs of the batch description comes along with the last round.  Whole wavefronts.

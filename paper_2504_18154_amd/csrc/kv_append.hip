@@ -133,7 +133,9 @@ __global__ __launch_bounds__(kAppendThreads) void kv_append_kernel(E* __restrict
 }
 
 // At most one new token per sequence (the decode step): one wavefront per (sequence, K/V head)
-// copies the token's K row as 16-byte units and scatters its V row into the slot's column.
+// copies the token's K row as 16-byte units and scatters its V row into the slot's column.  Launch latency and two round
+// trips bound it (16 sequences, 8 K/V heads, bf16, 128: 2.94 us with the rows and stores of K and V one after the
+// other, 2.47 now), and from a thousand pairs on the V columns, 128 sectors that the memory reads and writes for two bytes.
 template <typename E>
 __global__ __launch_bounds__(kAppendThreads) void kv_append_one_kernel(E* __restrict__ k_cache, E* __restrict__ v_cache,
                                                                         const E* __restrict__ k_new,
@@ -143,17 +145,31 @@ __global__ __launch_bounds__(kAppendThreads) void kv_append_one_kernel(E* __rest
                                                                         const int32_t* __restrict__ block_table,
                                                                         int bt_stride, int B, int Hkv, int D,
                                                                         int pos_bias) {
-  const int pair = blockIdx.x * (kAppendThreads / 64) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  constexpr int X = Elem<E>::X, kPer = 256 / 64;  // V elements per lane of the largest head
+  typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+  const int pair = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (pair >= B * Hkv) return;
   const int b = pair / Hkv, g = pair % Hkv;
   // cu_q == NULL: exactly one token per sequence, token b belongs to sequence b
-  const int tok = cu_q ? cu_q[b] : b;
-  if (cu_q && cu_q[b + 1] - tok <= 0) return;
-  const int p = ctx_before[b] + pos_bias;
-  if (p < 0) return;  // (pos_bias -1 on an empty sequence: nothing to store)
+  const int p = ctx_before[b] + pos_bias, tok = cu_q ? cu_q[b] : b, end = cu_q ? cu_q[b + 1] : b + 1;
+  if (end - tok <= 0 || p < 0) return;  // (p: pos_bias -1 on an empty sequence: nothing to store)
+  // the token's rows are asked for before the block that they go to: neither waits for the other
+  const E* const ksrc = k_new + (size_t)tok * new_row_stride + g * D;
+  const E* const vsrc = v_new + (size_t)tok * new_row_stride + g * D;
+  u4 kval = {0u, 0u, 0u, 0u};
+  E vval[kPer];
+  if (lane < D / X) kval = *reinterpret_cast<const u4*>(ksrc + lane * X);
+#pragma unroll
+  for (int r = 0; r < kPer; ++r) vval[r] = lane + 64 * r < D ? vsrc[lane + 64 * r] : E(0);
   const int64_t blk = block_table[(size_t)b * bt_stride + (p >> 4)];
-  append_one_row<E>(k_cache, v_cache, k_new + (size_t)tok * new_row_stride + g * D,
-                    v_new + (size_t)tok * new_row_stride + g * D, blk, g, p & 15, Hkv, D, lane);
+  // K: unit c of the row to [c][slot][X elements], V: element d to [d][slot]
+  const int slot = p & 15;
+  E* const kdst = k_cache + ((size_t)blk * Hkv + g) * 16 * D + (size_t)slot * X;
+  E* const vdst = v_cache + ((size_t)blk * Hkv + g) * D * 16 + slot;
+  if (lane < D / X) *reinterpret_cast<u4*>(kdst + (size_t)lane * 16 * X) = kval;
+#pragma unroll
+  for (int r = 0; r < kPer; ++r)
+    if (lane + 64 * r < D) vdst[(size_t)(lane + 64 * r) * 16] = vval[r];
 }
 
 // Dynamic LDS of the tiled kernel: HPW staged V tiles.
@@ -181,9 +197,12 @@ static void launch_typed(const ecoserve_layout& L, void* k_cache, void* v_cache,
                          int32_t bt_stride, int32_t B, int32_t T, int32_t max_new_len, int32_t pos_bias, int num_cu,
                          hipStream_t s) {
   if (max_new_len <= 1) {
-    const int per_wg = kAppendThreads / 64;
-    const dim3 grid((unsigned)(((int64_t)B * L.num_kv_heads + per_wg - 1) / per_wg));
-    hipLaunchKernelGGL((kv_append_one_kernel<E>), grid, dim3(kAppendThreads), 0, s, (E*)k_cache, (E*)v_cache,
+    // (one wavefront per workgroup spreads a small batch over more CUs: 16 sequences, 8 K/V heads 2.47 us, 2.70 with four;
+    // from two per CU on four are as good or better: 256 sequences 5.83 and 5.64)
+    const int64_t pairs = (int64_t)B * L.num_kv_heads;
+    const int per_wg = pairs <= 2 * num_cu ? 1 : kAppendThreads / 64;
+    const dim3 grid((unsigned)((pairs + per_wg - 1) / per_wg));
+    hipLaunchKernelGGL((kv_append_one_kernel<E>), grid, dim3(per_wg * 64), 0, s, (E*)k_cache, (E*)v_cache,
                        (const E*)k_new, (const E*)v_new, new_row_stride, cu_q, ctx_before, block_table, bt_stride, B,
                        L.num_kv_heads, L.head_dim, pos_bias);
     return;
