@@ -490,7 +490,9 @@ static int decode_impl(ecoserve_ctx* c, const void* q, int64_t q_row_stride, con
     a.new_row_stride = (int32_t)new_row_stride;
   }
   const bool automatic = !c->opt_force_plain && c->opt_split_tokens == 0;
-  const SmallDecode small = use_mfma(c) && automatic ? small_decode(B, a.Hkv, max_ctx_len, c->num_cu) : SmallDecode{0, 0};
+  const SmallDecode small = !automatic   ? SmallDecode{0, 0}
+                          : use_mfma(c) ? small_decode(B, a.Hkv, max_ctx_len, c->num_cu)
+                                        : any_decode(B, a.Hkv, a.D, a.dtype == ECOSERVE_BF16 ? 2 : 4, max_ctx_len, c->num_cu);
   if (use_mfma(c) && small.n_split == 0) {
     const int n_wgs = c->num_cu * kDecodeWgsPerCu;
     const bool adaptive = c->opt_adaptive && c->opt_split_tokens == 0 && n_wgs % 8 == 0;
@@ -511,10 +513,8 @@ static int decode_impl(ecoserve_ctx* c, const void* q, int64_t q_row_stride, con
                                  n_wgs * 4, s);
     return e == hipSuccess ? ECOSERVE_OK : ECOSERVE_EHIP;
   }
-  const int32_t split_tokens = use_mfma(c) ? small.split_tokens
-                             : automatic ? decode_any_split_tokens(B, a.Hkv, max_ctx_len, c->num_cu)
-                                         : plan_split_tokens(c, B, max_ctx_len);
-  const int32_t n_split_max = use_mfma(c) ? small.n_split : ceil_div(max_ctx_len, split_tokens);
+  const int32_t split_tokens = automatic ? small.split_tokens : plan_split_tokens(c, B, max_ctx_len);
+  const int32_t n_split_max = automatic ? small.n_split : ceil_div(max_ctx_len, split_tokens);
   // cannot happen: split_tokens >= kMinSplitTokens, and (bf16, 128) comes here with one slice per workgroup that fits
   if (n_split_max > 1 && (use_mfma(c) ? (int64_t)(split_tokens ? B : 1) * a.Hq * n_split_max > c->ws_slots : n_split_max > c->ws_splits)) return ECOSERVE_EINVAL;
   {

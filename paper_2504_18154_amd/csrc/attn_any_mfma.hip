@@ -488,15 +488,16 @@ __global__ __launch_bounds__(W * 64) void decode_any_kernel(
   if (s_order != n_split - 1) return;
   for (int h = wave; h < G; h += W) {
     const size_t slot = slot0 - sp * next_slice + h * slot_step;
-    auto states = [&](int k, float (&ak)[8][(KS + 1) / 2]) {  // of slices k .. k + 7
+    constexpr int kAtOnce = KS <= 4 ? 8 : 4;  // (larger heads have no registers for eight)
+    auto states = [&](int k, float (&ak)[kAtOnce][(KS + 1) / 2]) {  // of slices k .. k + kAtOnce - 1
 #pragma unroll
-      for (int j = 0; j < 8; ++j)
+      for (int j = 0; j < kAtOnce; ++j)
 #pragma unroll
         for (int r = 0; r < (KS + 1) / 2; ++r)
           ak[j][r] = k + j < n_split && lane + 64 * r < D ? load_shared(ws_acc + (slot + (k + j) * next_slice) * D + lane + 64 * r) : 0.f;
     };
-    float ak[8][(KS + 1) / 2];
-    states(0, ak);  // (asked for together with the slices' maxima)
+    float ak[kAtOnce][(KS + 1) / 2];
+    if constexpr (KS <= 4) states(0, ak);  // (asked for together with the slices' maxima)
     float m2 = -INFINITY, l2 = 0.f, o2[4] = {0.f, 0.f, 0.f, 0.f};
     for (int base = 0; base < n_split; base += 64) {  // 64 slices at a time: lane k holds the (max, sum) of slice k
       const int nk = min(64, n_split - base);
@@ -510,10 +511,10 @@ __global__ __launch_bounds__(W * 64) void decode_any_kernel(
       l2 = l2 * old + wave_sum(lk * wk);
 #pragma unroll
       for (int r = 0; r < 4; ++r) o2[r] *= old;
-      for (int k = 0; k < nk; k += 8) {
-        if (base + k > 0) states(base + k, ak);
+      for (int k = 0; k < nk; k += kAtOnce) {
+        if (KS > 4 || base + k > 0) states(base + k, ak);
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
+        for (int j = 0; j < kAtOnce; ++j) {
           const float w = k + j < nk ? __shfl(wk, k + j) : 0.f;
 #pragma unroll
           for (int r = 0; r < (KS + 1) / 2; ++r) o2[r] += ak[j][r] * w;
@@ -765,6 +766,9 @@ void launch_prefill_typed(const AttnArgs& a, const int32_t* cu_q, const int32_t*
   });
 }
 
+// Wavefronts of a decode workgroup: eight while two blocks of K and V fit beside the rest in 256 registers.
+constexpr int decode_wavefronts(int D, int elem_bytes) { return D > (elem_bytes == 4 ? 128 : 192) ? 4 : 8; }
+
 template <typename E>
 void launch_decode_typed(const AttnArgs& a, const int32_t* ctx_len, int32_t split_tokens, int32_t n_split_max, float* ws_acc,
                          float* ws_ml, uint32_t* counters, bool many, hipStream_t s) {
@@ -776,8 +780,7 @@ void launch_decode_typed(const AttnArgs& a, const int32_t* ctx_len, int32_t spli
                        (E*)a.out, a.lse, ws_acc, ws_ml, counters, split_tokens, a.Hq, a.Hkv, a.Hq / a.Hkv, a.D, a.scale_log2e, a.B);
   };
   for_head_size(a.D, [&](auto ks) {
-    // eight wavefronts per workgroup while two blocks of K and V fit beside the rest in 256 registers
-    constexpr int KS = decltype(ks)::value, W = KS > (sizeof(E) == 4 ? 4 : 6) ? 4 : 8;
+    constexpr int KS = decltype(ks)::value, W = decode_wavefronts(32 * KS, sizeof(E));
     if constexpr (KS == 4 && sizeof(E) == 2) {
       if (a.D == 128 && balanced) return launch(decode_any_kernel<E, KS, W, 0, false, true>, W);
       if (a.D == 128) return many ? launch(decode_any_kernel<E, KS, 4, kNonTemporal, false>, 4) : launch(decode_any_kernel<E, KS, W, 0, false>, W);
@@ -792,10 +795,29 @@ void launch_decode_typed(const AttnArgs& a, const int32_t* ctx_len, int32_t spli
 // Contexts up to 1024 tokens stay whole (no merge); longer ones are cut into slices of 256 tokens, or of 512 or 1024
 // when that already makes enough workgroups.  (8 K/V heads, bf16, 128, us in slices of 256 / 512 / 1024: one sequence of 2000
 // tokens 9.6 / 10.3 / 12.7, of 8000 14.9 / 12.6 / 13.8; 4 x 2000 11.1 / 10.9 / 13.3.)
-int32_t decode_any_split_tokens(int32_t B, int32_t Hkv, int32_t max_ctx_len, int32_t num_cu) {
+static int32_t decode_any_split_tokens(int32_t B, int32_t Hkv, int32_t max_ctx_len, int32_t num_cu) {
   int32_t st = max_ctx_len > 1024 ? 256 : 1024;
   while (st < 1024 && (int64_t)B * Hkv * ((max_ctx_len + st - 1) / st) > num_cu / 2) st *= 2;
   return st;
+}
+
+// For every other layout: contexts are cut, into slices of whole rounds of the wavefronts, where that makes no more than one
+// workgroup per CU and the walk it saves is worth a merge.  A block's walk takes 0.012 us per KiB of it in bf16, 0.018 in fp32 (one of
+// 700 tokens against one of 50: 64 0.05 and 0.16, fp32 128 0.28, 192 0.13, 256 0.21 and 0.57 us a block); a merge 2.7
+// (1.8 in fp32), more for large heads, and 0.13 a slice.  Us per call whole / cut: fp32, 64, 2 K/V heads: 1 x 700 tokens 11.2 / 7.6, 16 x 700 11.5 / 9.0; fp32, 128, 3:
+// 1 x 400 14.2 / 9.5, 4 x 37..708 15.6 / 10.4, 8 x 3000 33.6 / 22.6; fp32, 256, 2: 16 x 700 41.4 / 21.2; bf16, 192, 2: 16 x 700 16.7 / 12.8; bf16, 256, 1:
+// 1 x 200 11.7 / 13.1, 1 x 400 14.3 / 13.6, 64 x 800 27.1 / 21.3; bf16, 96, 2: 16 x 700 8.4 / 9.0; 64, 8: 1 x 700 6.6 whole.
+SmallDecode any_decode(int32_t B, int32_t Hkv, int32_t D, int32_t elem_bytes, int32_t max_ctx_len, int32_t num_cu) {
+  const int32_t W = decode_wavefronts(D, elem_bytes), nb = (max_ctx_len + kBlockSize - 1) / kBlockSize;
+  const int64_t slots = num_cu / ((int64_t)B * Hkv);
+  const float large = std::max(1.f, (float)D / 192.f), walk = (elem_bytes == 2 ? 0.012f : 0.018f) * (float)(32 * D * elem_bytes) / 1024.f;
+  if (slots > 1 && walk * (float)(nb - W) > (elem_bytes == 2 ? 2.7f : 1.8f) * large) {
+    const int64_t least = std::max<int64_t>((int64_t)sqrtf(0.13f * large / walk * (float)nb), (nb + slots - 1) / slots);
+    const int32_t st = (int32_t)std::min<int64_t>((least + W - 1) / W * W, 64) * kBlockSize;
+    return {st, (max_ctx_len + st - 1) / st};
+  }
+  const int32_t st = decode_any_split_tokens(B, Hkv, max_ctx_len, num_cu);
+  return {st, (max_ctx_len + st - 1) / st};
 }
 
 // For (bf16, 128): how this kernel takes a small batch, n_split 0 if it does not.  It needs no numbering of the batch and no

@@ -165,10 +165,10 @@ hipError_t launch_decode_merge(const AttnArgs& a, const int32_t* ctx_len, int32_
 // (one launch; with a.k_new given it appends the step's tokens too; split_tokens: a multiple of 16 per slice of the
 // context, n_split_max slices, partial states [B][Hq][n_split_max]; or, (bf16, 128) and B <= 64 only, 0: balanced slices, n_split_max
 // per K/V head in all, at least B, partial states [n_split_max][Hq]; counters [B][Hkv] that are zero and stay so)
-int32_t decode_any_split_tokens(int32_t B, int32_t Hkv, int32_t max_ctx_len, int32_t num_cu);
 struct SmallDecode {
   int32_t split_tokens, n_split;  // as launch_decode_any takes them
 };
+SmallDecode any_decode(int32_t B, int32_t Hkv, int32_t D, int32_t elem_bytes, int32_t max_ctx_len, int32_t num_cu);
 SmallDecode small_decode(int32_t B, int32_t Hkv, int32_t max_ctx_len, int32_t num_cu);
 hipError_t launch_prefill_any(const AttnArgs& a, const int32_t* cu_q, const int32_t* ctx_before, int32_t T, hipStream_t s);
 hipError_t launch_decode_any(const AttnArgs& a, const int32_t* ctx_len, int32_t split_tokens, int32_t n_split_max,

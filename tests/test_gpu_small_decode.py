@@ -157,3 +157,31 @@ def test_balanced_slices(heads, lens, loose):
     assert torch.equal(no[idx], out[idx]), "the call without a context differs"
     layer.assert_cache_bit_exact()
     layer.close()
+
+
+@pytest.mark.parametrize("dtype,heads,D,lens", [("f32", (4, 2), 64, [700, 337, 128, 129, 1]), ("f32", (6, 3), 128, [400, 225, 16]), ("f32", (4, 2), 256, [200, 65, 64, 63]),
+                                                ("bf16", (16, 2), 192, [700, 512]), ("bf16", (8, 1), 256, [800, 400, 17]), ("bf16", (8, 2), 96, [1024, 1023])],
+                         ids=lambda x: str(x).replace(" ", ""))
+def test_short_slices_of_other_layouts(dtype, heads, D, lens):
+    """Contexts that other layouts cut below 1024 tokens: against the oracle, and with the append fused in, three times."""
+    model = wl.ModelShape("other", heads[0], heads[1], D, 1, dtype)
+    lens = np.asarray(lens, dtype=np.int32)
+    say(f"decode, {dtype}, head size {D}, heads {heads}, lengths {lens.tolist()}")
+    pb = wl.prefill_batch(model, lens, 60)
+    layer = Layer(model, pb.num_blocks, pb.B, pb.block_table.shape[1])
+    k, v = (wl.randn((pb.T, model.Hkv, D), dtype, s) for s in (1, 2))
+    layer.append(k, v, pb.cu_q, pb.ctx_before, pb.block_table)
+    q = wl.randn((pb.B, model.Hq, D), dtype, 3)
+    ref, ref_lse = layer.decode_oracle(q, pb.block_table, lens)
+    out, lse = layer.decode_gpu(q, pb.block_table, lens)
+    compare("decode", out, ref, dtype)
+    compare_lse("decode", lse, ref_lse, dtype)
+    last = torch.as_tensor(pb.cu_q[1:] - 1, dtype=torch.long)
+    layer.wipe_newest(pb.block_table, lens)
+    for call in range(3):
+        fused = torch.full_like(out, float("nan"))
+        layer.ctx.attn_decode_append(q.cuda(), k[last].cuda(), v[last].cuda(), layer.kc, layer.vc, dev_i32(pb.block_table), dev_i32(lens), fused, int(lens.max()))
+        torch.cuda.synchronize()
+        assert torch.equal(fused, out), f"call {call} with the append fused in differs"
+    layer.assert_cache_bit_exact()
+    layer.close()
