@@ -239,7 +239,7 @@ __device__ __forceinline__ int lanes_max(int x) {
 // (A trial is one scan; with all lanes as candidates and a loop over the sequences, 16 of them took 0.3 us longer.)
 __device__ __forceinline__ int balanced_slice_blocks(int nb, int Hkv, int slots, int W, int& n, int& end) {
   const int longest = lanes_max(nb), sum = __builtin_amdgcn_readlane(lanes_prefix_sum(nb), 63);
-  const bool whole = whole_context((float)longest, (float)sum * (float)Hkv);
+  const bool whole = W == 8 && whole_context((float)longest, (float)sum * (float)Hkv);  // (four: two workgroups per CU, see small_decode)
   const float shortest = fmaxf(least_slice((float)longest) - 0.5f * (float)W, (float)sum * __builtin_amdgcn_rcpf((float)slots));
   int st = whole ? max(longest, 1) : ((int)shortest / W + 1) * W;
   for (;;) {
@@ -782,7 +782,8 @@ void launch_decode_typed(const AttnArgs& a, const int32_t* ctx_len, int32_t spli
   for_head_size(a.D, [&](auto ks) {
     constexpr int KS = decltype(ks)::value, W = decode_wavefronts(32 * KS, sizeof(E));
     if constexpr (KS == 4 && sizeof(E) == 2) {
-      if (a.D == 128 && balanced) return launch(decode_any_kernel<E, KS, W, 0, false, true>, W);
+      if (a.D == 128 && balanced)
+        return many ? launch(decode_any_kernel<E, KS, 4, kNonTemporal, false, true>, 4) : launch(decode_any_kernel<E, KS, W, 0, false, true>, W);
       if (a.D == 128) return many ? launch(decode_any_kernel<E, KS, 4, kNonTemporal, false>, 4) : launch(decode_any_kernel<E, KS, W, 0, false>, W);
       if (many) return launch(decode_any_kernel<E, KS, 4, kNonTemporal>, 4);
     }
@@ -832,9 +833,13 @@ SmallDecode any_decode(int32_t B, int32_t Hkv, int32_t D, int32_t elem_bytes, in
 //   No balancing where every sequence may have as many slices as one of max_ctx_len tokens gets for itself: the slices of
 //   balanced_slice_blocks for that (1 x 777: 9.4 / 8.5, 1 x 1000: 10.7 / 8.9, 1 x 16000: 21.9 / 20.8).
 //   Else uniform slices if all workgroups run at once - one of eight wavefronts per CU, or (short contexts) two of four (us per call
-//   persistent / here: 16 x 1000 tokens 20.7 / 14.1; 32 x 200: 15.7 / 7.4; 64 x 500: 35.0 / 23.5), but nothing evens out the
-//   lengths of more workgroups than fit: 128 sequences around 500 tokens, lognormal, take 62 there and 74 here, 40 of them 25
+//   persistent / here: 16 x 1000 tokens 20.7 / 14.1; 32 x 200: 15.7 / 7.4; 64 x 500: 35.0 / 23.5); with uniform slices nothing evens out
+//   the lengths of more workgroups than fit: 128 sequences around 500 tokens, lognormal, take 62 there and 74 here, 40 of them 25
 //   and 28 (128 of 500 each: 54 and 50).
+//   Else balanced slices for two workgroups of four wavefronts per CU, all of which run at once too, with as many to spare, up
+//   to 300 MB (persistent / here: 40 x 100..1000 27.2 / 24.6, 40 x 600 29.8 / 24.4, 40 x 20..2000 25.1 / 21.2, 28 x 100..3000 37.5 /
+//   33.5, 24 x 100..3000 33.0 / 30.2, 16 query heads on 4, 64 x 100..2000 31.9 / 28.3; 36 x 1500 49.0 / 49.0, 40 x 2000 65.3 / 66.1, 24 x
+//   4000 74 / 80; with nothing to spare 64 x 20..2000 33.7 / 39.2; three workgroups and more per CU 40 x 100..1000 28.5).
 SmallDecode small_decode(int32_t B, int32_t Hkv, int32_t max_ctx_len, int32_t num_cu) {
   const int64_t pairs = (int64_t)B * Hkv;
   const int32_t nb = (max_ctx_len + kBlockSize - 1) / kBlockSize, slots = num_cu / Hkv;
@@ -846,7 +851,10 @@ SmallDecode small_decode(int32_t B, int32_t Hkv, int32_t max_ctx_len, int32_t nu
   }
   if (B > 1 && B <= 64 && nb > 48 && 8 * B <= 5 * slots && pairs * max_ctx_len <= 800000) return {0, slots};
   const int32_t st = decode_any_split_tokens(B, Hkv, max_ctx_len, num_cu), n = (max_ctx_len + st - 1) / st;
-  return pairs * n <= num_cu || (max_ctx_len <= 512 && pairs <= 2 * num_cu) ? SmallDecode{st, n} : SmallDecode{0, 0};
+  if (pairs * n <= num_cu || (max_ctx_len <= 512 && pairs <= 2 * num_cu)) return {st, n};
+  const int32_t slots2 = 2 * num_cu / Hkv;
+  if (B <= 64 && 8 * B <= 5 * slots2 && pairs * max_ctx_len <= 600000) return {0, slots2};
+  return {0, 0};
 }
 
 hipError_t launch_prefill_any(const AttnArgs& a, const int32_t* cu_q, const int32_t* ctx_before, int32_t T, hipStream_t s) {
@@ -857,7 +865,7 @@ hipError_t launch_prefill_any(const AttnArgs& a, const int32_t* cu_q, const int3
 
 hipError_t launch_decode_any(const AttnArgs& a, const int32_t* ctx_len, int32_t split_tokens, int32_t n_split_max, float* ws_acc,
                              float* ws_ml, uint32_t* counters, int32_t num_cu, hipStream_t s) {
-  const bool many = (int64_t)a.B * a.Hkv * n_split_max > num_cu;
+  const bool many = (int64_t)(split_tokens ? a.B : 1) * a.Hkv * n_split_max > num_cu;
   if (a.dtype == ECOSERVE_BF16) launch_decode_typed<uint16_t>(a, ctx_len, split_tokens, n_split_max, ws_acc, ws_ml, counters, many, s);
   else launch_decode_typed<float>(a, ctx_len, split_tokens, n_split_max, ws_acc, ws_ml, counters, many, s);
   return hipGetLastError();

@@ -122,7 +122,8 @@ def test_the_persistent_kernel_passes_over_sequences_without_tokens():
 # several sequences, cut into slices that fill the workgroups: lengths and slices at the edges of blocks, of the wavefronts' rounds
 # and of the rule that leaves contexts whole; empty sequences; as many sequences as a wavefront has lanes
 BALANCED = [((40, 8), [769, 1]), ((40, 8), [2000, 128, 129, 127, 16, 17, 0, 1024]), ((64, 8), [1025] * 20), ((5, 1), [0, 3000, 0, 0, 2999, 1, 0]),
-            ((16, 1), [4095, 4096, 4097] + [1] * 61), ((3, 3), [900, 700, 5000]), ((52, 52), [800, 1500]), ((8, 1), [30000, 20, 700])]
+            ((16, 1), [4095, 4096, 4097] + [1] * 61), ((3, 3), [900, 700, 5000]), ((52, 52), [800, 1500]), ((8, 1), [30000, 20, 700]),
+            ((40, 8), [600] * 36 + [0, 1, 128, 1000]), ((16, 4), [1 + 17 * i for i in range(64)])]  # two workgroups of four wavefronts per CU
 
 
 @pytest.mark.parametrize("heads,lens", BALANCED, ids=[f"{h[0]}x{h[1]}-B{len(n)}-L{max(n)}" for h, n in BALANCED])
