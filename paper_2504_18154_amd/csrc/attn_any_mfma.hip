@@ -783,7 +783,9 @@ void launch_decode_typed(const AttnArgs& a, const int32_t* ctx_len, int32_t spli
     constexpr int KS = decltype(ks)::value, W = decode_wavefronts(32 * KS, sizeof(E));
     if constexpr (KS == 4 && sizeof(E) == 2) {
       if (a.D == 128 && balanced)
-        return many ? launch(decode_any_kernel<E, KS, 4, kNonTemporal, false, true>, 4) : launch(decode_any_kernel<E, KS, W, 0, false, true>, W);
+        // (non-temporal: a batch of several long contexts comes from memory, layer after layer: 16 x 20..2000 tokens 15.7 us without the
+        // hint and 14.5 with it, 16 x 2000 30.5 and 27.8, 9 x 1196..9574 32.2 and 29.0; a single one may still be in the last-level cache)
+        return many ? launch(decode_any_kernel<E, KS, 4, kNonTemporal, false, true>, 4) : launch(decode_any_kernel<E, KS, W, kNonTemporal, false, true>, W);
       if (a.D == 128) return many ? launch(decode_any_kernel<E, KS, 4, kNonTemporal, false>, 4) : launch(decode_any_kernel<E, KS, W, 0, false>, W);
       if (many) return launch(decode_any_kernel<E, KS, 4, kNonTemporal>, 4);
     }
@@ -825,11 +827,11 @@ SmallDecode any_decode(int32_t B, int32_t Hkv, int32_t D, int32_t elem_bytes, in
 // second launch, which is what such a batch spends its time on in the persistent kernel.
 //   Several sequences, one of them of more than 768 tokens, and eight workgroups (one per CU) or more per five (sequence, K/V
 //   head)s: balanced slices.  Us per call before (uniform slices or the persistent kernel) / balanced: 64 query heads on 8, 16 x
-//   20..2000 tokens 18.4 / 15.9, 8 x 20..8000 19.2 / 15.3; 5 on 1, 13 x 745..5960 16.2 / 12.8; 8 on 1, 64 x 50..8000 37.0 / 16.2; 32 on 8,
-//   18 x 116..935 15.5 / 14.4, 9 x 1196..9574 35.6 / 31.5; 40 on 8, 20 x 2000 38.9 / 34.5, 20 x 100..3000 30.2 / 28.8.  Finding the slices
-//   takes half a microsecond, which equal lengths do not give back: 16 x 2000 29.1 / 29.7, 4 x 2000 13.9 / 14.9.  Fewer spare workgroups
-//   even out too little (24 x 100..3000 33 / 34, 24 x 1000..10000 84 / 98), and from 400 MB on the persistent kernel's
-//   stream is the faster one (16 x 8000 93 / 99).
+//   20..2000 tokens 18.4 / 14.5, 8 x 20..8000 19.2 / 14.6; 5 on 1, 13 x 745..5960 16.3 / 12.1; 8 on 1, 64 x 1000..8000 38.5 / 28.8; 32 on 8, 9 x
+//   1196..9574 35.8 / 29.0; 40 on 8, 18 x 116..935 15.6 / 14.3, 8 x 1000 16.0 / 13.9, 16 x 1000 18.9 / 18.4, 16 x 2000 29.2 / 27.8, 20 x 2000 38.9 / 32.8, 20 x
+//   100..3000 30.2 / 26.1, 15 x 1142..9140 51.8 / 51.7; 52 on 52, 2 x 1000..2000 20.7 / 21.0.  Finding the slices takes half a microsecond.  Fewer
+//   spare workgroups even out too little (24 x 1000..10000 84 / 98), and from 400 MB on the persistent kernel's stream is the
+//   faster one (16 x 8000 93 / 99; both without the non-temporal hint).
 //   No balancing where every sequence may have as many slices as one of max_ctx_len tokens gets for itself: the slices of
 //   balanced_slice_blocks for that (1 x 777: 9.4 / 8.5, 1 x 1000: 10.7 / 8.9, 1 x 16000: 21.9 / 20.8).
 //   Else uniform slices if all workgroups run at once - one of eight wavefronts per CU, or (short contexts) two of four (us per call
