@@ -295,7 +295,7 @@ __global__ __launch_bounds__(W * 64) void decode_any_kernel(
   // Asked for with the length, before anything that depends on it: the new rows, the query rows.  (The block ids have to
   // wait: entries behind the sequence's last block are not read.)
   const SliceOf at = slice_of_workgroup<BALANCED>(ctx_len, B, Hkv, split_tokens, W);
-  if (at.sp < 0) return;
+  if (BALANCED && at.sp < 0) return;
   const int b = at.b, sp = at.sp, L = at.L;
   const int32_t* const bt_row = block_table + (size_t)b * bt_stride;
   const bool fused = k_new != nullptr;
