@@ -18,12 +18,12 @@
 // (decode), or (position, query head of the group) pairs of a prompt (prefill), position-major.
 //
 // What bounds them: such batches are small (tens of MB of K/V at most), so a step is latency: launches, the chain
-// length -> block ids -> blocks, and the walk of the blocks.  Hence decode takes contexts up to 1024 tokens in one
-// launch, eight wavefronts per (sequence, K/V head) (four for large heads and for batches of more than one workgroup per
-// CU) and the step's append inside (one launch instead of three).
+// length -> block ids -> blocks, and the walk of the blocks.  Hence decode is one
+// launch (instead of three): eight wavefronts (four for large heads and for batches of more than one workgroup per CU) per
+// (sequence, K/V head) and slice of the context, slices as short as a merge allows, the step's append inside.
 // Measured beside the plain kernels (one wavefront per query row, a scalar product per lane): a prompt batch of 4 x
 // 50..600 tokens and 8 decode steps, bf16, head size 64, 32/8 heads: 398 -> 65 us (prefill kernel 243 -> 11 us, a
-// decode step's kernels 21.8 -> 6.1 us); 4 x 37..700 tokens in fp32, 4/2 heads: 195 -> 75 us (55 -> 8 us, 19.1 -> 7.8 us).
+// decode step's kernels 21.8 -> 6.1 us); 4 x 37..700 tokens in fp32, 4/2 heads: 195 -> 71 us (55 -> 8 us, 19.1 -> 7.3 us).
 // Not gained: a prompt of 8 tokens or fewer with nothing cached (a graph of such calls: 0.2 to 0.9 us more than the plain
 // kernel's 3 to 8); with 40 to 100 tokens cached, which the host cannot see, the plain kernel takes up to six times as long.
 #include <algorithm>
