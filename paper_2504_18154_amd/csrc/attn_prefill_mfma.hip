@@ -77,7 +77,6 @@ constexpr int kBalanceMinItems = 3072;          // batches with fewer items keep
 constexpr float kShareGain = 2.5f, kShareMin = 0.5f, kShareMax = 1.5f;  // control of the queues' shares
 constexpr int kQueues = 8;                     // work queues (a multiple of 8; more did not help)
 constexpr int kShareMaxTiles = kPlanBins - 1;   // shares: most query tiles of a batch (their step sums lie in LDS)
-constexpr int kShareMaxRounds = 4;              // shares: most items per workgroup of a batch (more even themselves out)
 constexpr int kPieceFloats = kTQ * 128;         // partial state of a piece: unnormalised outputs, then (max, sum) per row
 constexpr int kPieceStride = kPieceFloats + 2 * kTQ;
 constexpr int kAgentScope = 16;                 // cache policy sc1: past the caches that the XCDs do not share
@@ -350,10 +349,12 @@ __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(const int32_
   for (int i = tid; i < n_tiles_all; i += kPlanThreads) {
     int b, qt, steps;
     atomicAdd(&bins[locate(i, b, qt, steps)], 1);
-    if (may_share) units[i] = steps + kItemCost;
-    sum += steps + kItemCost;
-    heaviest = max(heaviest, steps);
-    lightest = min(lightest, steps);
+    if (may_share) {  // (the sums below fit 32 bits: may_share_steps)
+      units[i] = steps + kItemCost;
+      sum += steps + kItemCost;
+      heaviest = max(heaviest, steps);
+      lightest = min(lightest, steps);
+    }
   }
   if (may_share && __any(sum > 0)) {  // (a wavefront at a time: a thousand atomics on one address take 10 us)
 #pragma unroll
@@ -1138,9 +1139,9 @@ __global__ __launch_bounds__(256, 2) void prefill_mfma_kernel(
 // Key steps of a row of the block table: no item has more.
 static int64_t table_steps(const AttnArgs& a) { return ((int64_t)a.bt_stride * kBlockSize + kTK - 1) / kTK; }
 
-// Whether the plan may share out the batch's key steps: not for tables so short or batches of so many items that it never would.
+// Whether the plan may share out the batch's key steps.
 static bool may_share(const AttnArgs& a, int64_t n_items, int32_t n_persistent_wgs, const float* ws_pieces) {
-  return ws_pieces && n_persistent_wgs <= kPlanMaxWgs && table_steps(a) >= kShareMinUnits && n_items <= (int64_t)kShareMaxRounds * n_persistent_wgs;
+  return ws_pieces && n_persistent_wgs <= kPlanMaxWgs && may_share_steps(n_items, table_steps(a), n_persistent_wgs);
 }
 
 // Workgroups of the attention launch: the persistent grid, or fewer if the batch cannot hold that

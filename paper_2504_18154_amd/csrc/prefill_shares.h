@@ -13,7 +13,8 @@
 namespace eco {
 
 constexpr int kItemCost = 3;
-constexpr int kShareMinUnits = 8;  // fewest units of a share
+constexpr int kShareMinUnits = 8;   // fewest units of a share
+constexpr int kShareMaxRounds = 4;  // most items per workgroup of a batch
 
 // Workgroups that take shares, 0: the items go through the queues instead, whole.  `units` of all items together, `heaviest`
 // and `lightest` item in key steps, n_wgs workgroups, two per CU.
@@ -30,7 +31,7 @@ constexpr int kShareMinUnits = 8;  // fewest units of a share
 //   whole:   64/8 512+0: 15 / 18            64/8 512+2000: 53 / 53        32/8 4 x 749+89: 40 / 41      40/8 4 x 1024+0: 61 / 63
 //            64/8 4 x 256+2000: 79 / 84     64/8 8 x 256+8000: 513 / 525  8/1 16 x 500+500: 35 / 40     64/8 2048+0: 86 / 84
 ECO_HD int share_wgs(int n_items, long long units, int heaviest, int lightest, int n_wgs) {
-  if (heaviest < kShareMinUnits || n_items <= 0 || n_wgs <= 0 || units > 0x7fffffff) return 0;
+  if (heaviest < kShareMinUnits || n_items <= 0 || n_wgs <= 0) return 0;
   const float w = (float)n_wgs, u = (float)units;
   // a share is no shorter than what its merge takes: a tile of s steps then has about 0.7 sqrt(s) pieces at most
   int least = kShareMinUnits;
@@ -59,6 +60,13 @@ ECO_HD int share_wgs(int n_items, long long units, int heaviest, int lightest, i
     t_items = all + (last > 0 ? 0.6f * (1.f - (float)last / w) * (float)lightest : 0.f);
   }
   return t_share < 0.97f * t_items ? n : 0;
+}
+
+// Whether a batch's key steps may be shared out at all, as far as the host can see: at most n_items items of at most `steps` key
+// steps (the width of the block table).  Not for tables so short or batches of so many items that they never would be (more than
+// kShareMaxRounds items per workgroup even themselves out), nor for more units than the plan's 32-bit sums hold.
+ECO_HD bool may_share_steps(long long n_items, long long steps, int n_wgs) {
+  return steps >= kShareMinUnits && n_items <= (long long)kShareMaxRounds * n_wgs && n_items * (steps + kItemCost) <= 0x7fffffff;
 }
 
 // Where a share begins: key step `step` of item `item`.

@@ -80,6 +80,14 @@ int main() {
   // whole items: tiles too short to cut, full rounds of equal items, many light items; shares: one long item, a bad last round
   if (share_wgs(32, 32 * 5, 2, 2, 512) || share_wgs(512, 512 * 53, 50, 50, 512) || share_wgs(1280, 1280 * 20, 32, 1, 512)) return fail("shares");
   if (!share_wgs(8, 8 * 253, 250, 250, 512) || !share_wgs(584, 584LL * 171, 200, 103, 512)) return fail("no shares");
+  // every sum that the plan makes of a batch it may share fits 32 bits: at the line, and beyond it not (2047 tiles of one K/V head
+  // behind 68 million cached tokens: the sum of their units wraps around)
+  for (long long items : {1LL, 7LL, 512LL, 2047LL, 2048LL}) {
+    const long long most = 0x7fffffff / items - kItemCost;
+    if (!may_share_steps(items, most, 512) || may_share_steps(items, most + 1, 512)) return fail("units that 32 bits do not hold");
+  }
+  if (may_share_steps(2047, 68000000 / 64 + 1, 512)) return fail("a sum that wraps around");
+  if (may_share_steps(2049, 100, 512) || may_share_steps(8, kShareMinUnits - 1, 512) || !may_share_steps(2048, 100, 512)) return fail("may share");
   std::printf("ok\n");
 }
 """
