@@ -214,25 +214,6 @@ __device__ __forceinline__ void attend_row(const E* __restrict__ qrow, const E* 
 __device__ __forceinline__ void store_shared(float* p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ float load_shared(float* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
-// Inclusive prefix sums and the maximum over the lanes of a wavefront, for non-negative x, within the vector unit (a
-// shuffle takes a trip through LDS per step, six of them 0.2 us).
-template <typename F>
-__device__ __forceinline__ int lanes_scan(int x, F f) {
-  x = f(x, __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false));  // row_shr:1
-  x = f(x, __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false));  // row_shr:2
-  x = f(x, __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false));  // row_shr:4
-  x = f(x, __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false));  // row_shr:8
-  x = f(x, __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false));  // row_bcast:15
-  x = f(x, __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false));  // row_bcast:31
-  return x;
-}
-__device__ __forceinline__ int lanes_prefix_sum(int x) {
-  return lanes_scan(x, [](int a, int b) { return a + b; });
-}
-__device__ __forceinline__ int lanes_max(int x) {
-  return __builtin_amdgcn_readlane(lanes_scan(x, [](int a, int b) { return max(a, b); }), 63);
-}
-
 // Balanced slices: lane b holds the number of blocks of sequence b; every K/V head has `slots` workgroups.  Whole contexts,
 // or slices of whole rounds of the W wavefronts, as short as all sequences' slices fit the workgroups and a merge stays short
 // (least_slice).  Returns the slice in blocks; `end`: inclusive prefix sums of the sequences' numbers of slices, `n`.

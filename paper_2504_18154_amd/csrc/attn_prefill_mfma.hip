@@ -250,30 +250,22 @@ __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(const int32_
   __shared__ int pre[kMaxBatch + 1];
   __shared__ int bins[kPlanBins];   // weight classes
   __shared__ int units[kPlanBins];  // (shares) the tiles' units, one K/V head's
-  __shared__ int s_weight[3];       // their sum; the largest and the smallest number of key steps
+  __shared__ uint8_t s_rows[kPlanBins];  // (shares) key steps between the last keys of a tile's first and last row
+  __shared__ int s_weight[3];       // sum of the units; the largest number of key steps; 2^31 - 1 less the smallest
+  __shared__ int s_active;
   __shared__ Cut s_cut[kPlanMaxWgs + 1];
-  __shared__ int wsum[kPlanThreads / 64];
+  __shared__ int wsum[2][kPlanThreads / 64];
   __shared__ __attribute__((aligned(16))) int s_rec[kPlanThreads / 64][64][kRecInts];
   __shared__ int s_slot[kPlanThreads / 64][64];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  // exclusive prefix of one value per thread over the workgroup; `total` receives the sum
-  auto block_scan = [&](int local, int& total) -> int {
-    int x = local;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const int y = __shfl_up(x, o);
-      if (lane >= o) x += y;
-    }
-    if (lane == 63) wsum[wave] = x;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // exclusive prefix of one value per thread over the workgroup; `total` receives the sum (`sums`: used by this scan alone)
+  auto block_scan = [&](int local, int& total, int* sums) -> int {
+    const int x = lanes_prefix_sum(local);
+    if (lane == 63) sums[wave] = x;
     __syncthreads();
-    int run = x - local;
-    total = 0;
-    for (int w = 0; w < kPlanThreads / 64; ++w) {
-      if (w < wave) run += wsum[w];
-      total += wsum[w];
-    }
-    __syncthreads();
-    return run;
+    const int of_wave = lane < kPlanThreads / 64 ? sums[lane] : 0, before = lanes_prefix_sum(of_wave);
+    total = __builtin_amdgcn_readlane(before, 63);
+    return x - local + __builtin_amdgcn_readlane(before - of_wave, wave);
   };
   auto tiles_of = [&](int b) { return ((cu_q[b + 1] - cu_q[b]) * G + kTQ - 1) / kTQ; };
   // rows [first, last) of tile qt of a prompt of S new tokens
@@ -292,7 +284,7 @@ __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(const int32_
       if (i == 0) tiles0 = n;
     }
   int n_tiles_all;
-  int run = block_scan(local, n_tiles_all);
+  int run = block_scan(local, n_tiles_all, wsum[0]);
   // never more records than the host sized the launch (and the plan buffer) for, whatever cu_q says
   n_tiles_all = min(n_tiles_all, max_tiles);
   for (int i = 0; i < per; ++i)
@@ -303,7 +295,7 @@ __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(const int32_
   if (tid == 0) pre[B] = n_tiles_all;
   __syncthreads();
 
-  // tile i of the batch (sequence after sequence) -> sequence, tile, key steps, first row; its weight class
+  // tile i of the batch (sequence after sequence) -> sequence, tile, key steps; its weight class
   auto locate = [&](int i, int& b, int& qt, int& steps) -> int {
     int lo = 0, hi = B;
     while (hi - lo > 1) {
@@ -329,7 +321,7 @@ __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(const int32_
       sum += cnt[i];
     }
     int total;
-    int start = block_scan(sum, total);
+    int start = block_scan(sum, total, wsum[1]);
 #pragma unroll
     for (int i = 0; i < kPer; ++i) {
       v[tid * kPer + i] = start;
@@ -343,92 +335,97 @@ __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(const int32_
     bins[i] = 0;
     if (may_share && i >= n_tiles_all) units[i] = 0;
   }
-  if (tid < 3) s_weight[tid] = tid == 2 ? 0x7fffffff : 0;
+  if (tid < 3) s_weight[tid] = 0;
   __syncthreads();
-  int sum = 0, heaviest = 0, lightest = 0x7fffffff;
+  int sum = 0, heaviest = 0, lightness = 0;
   for (int i = tid; i < n_tiles_all; i += kPlanThreads) {
     int b, qt, steps;
     atomicAdd(&bins[locate(i, b, qt, steps)], 1);
     if (may_share) {  // (the sums below fit 32 bits: may_share_steps)
+      int first, last;
+      tile_rows(cu_q[b + 1] - cu_q[b], qt, first, last);
       units[i] = steps + kItemCost;
+      s_rows[i] = (uint8_t)(steps - 1 - (ctx_before[b] + fast_div(first, div_g)) / kTK);
       sum += steps + kItemCost;
       heaviest = max(heaviest, steps);
-      lightest = min(lightest, steps);
+      lightness = max(lightness, 0x7fffffff - steps);
     }
   }
   if (may_share && __any(sum > 0)) {  // (a wavefront at a time: a thousand atomics on one address take 10 us)
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      sum += __shfl_xor(sum, o);
-      heaviest = max(heaviest, __shfl_xor(heaviest, o));
-      lightest = min(lightest, __shfl_xor(lightest, o));
-    }
-    if (lane == 0) {
+    sum = lanes_prefix_sum(sum);
+    heaviest = lanes_max(heaviest);
+    lightness = lanes_max(lightness);
+    if (lane == 63) {
       atomicAdd(&s_weight[0], sum);
       atomicMax(&s_weight[1], heaviest);
-      atomicMin(&s_weight[2], lightest);
+      atomicMax(&s_weight[2], lightness);
     }
   }
   __syncthreads();
+  // The kernel is one workgroup on one CU, and an instruction of all its wavefronts takes that CU 16 cycles: the rule is left to
+  // one of them, and to none where no tile is long enough (a call that does not share: 4.06 us without the question, 5.02 and,
+  // of 512 tokens, 5.76 with every wavefront asking it).
+  int n_active = 0;
   const int n_items = n_tiles_all * Hkv, head_units = s_weight[0];  // units: key steps and kItemCost, of one K/V head's tiles
-  const int n_active = may_share ? share_wgs(n_items, (long long)head_units * Hkv, s_weight[1], s_weight[2], n_main_wgs) : 0;
+  if (may_share && s_weight[1] >= kShareMinUnits) {
+    if (wave == 0) {
+      const int n = share_wgs(n_items, head_units * Hkv, s_weight[1], 0x7fffffff - s_weight[2], n_main_wgs);
+      if (lane == 0) s_active = n;
+    }
+    __syncthreads();
+    n_active = __builtin_amdgcn_readfirstlane(s_active);
+  }
   if (n_active > 0) {
     scan_array(units);
     // boundary r of the shares: unit head_units * Hkv * r / n_active, as the item and the key step it falls on
     for (int r = tid; r <= n_active; r += kPlanThreads) {
-      const int u = share_begin(head_units * Hkv, n_active, r), g = u / head_units, v = u - g * head_units;
+      const uint32_t u = share_begin(head_units * Hkv, n_active, r), g = u / (uint32_t)head_units;
+      const int v = (int)(u - g * head_units);
       int lo = 0, hi = n_tiles_all;
       while (hi - lo > 1) {
         const int mid = (lo + hi) >> 1;
         if (units[mid] <= v) lo = mid; else hi = mid;
       }
-      int b, qt, steps, first, last;
-      locate(lo, b, qt, steps);
-      tile_rows(cu_q[b + 1] - cu_q[b], qt, first, last);
-      s_cut[r] = r == n_active ? Cut{n_items, 0} : share_cut(g * n_tiles_all + lo, v - units[lo], steps, (ctx_before[b] + fast_div(first, div_g)) / kTK);
+      const int steps = units[lo + 1] - units[lo] - kItemCost;  // (behind the last tile stands the sum: kShareMaxTiles)
+      s_cut[r] = r == n_active ? Cut{n_items, 0} : share_cut((int)g * n_tiles_all + lo, v - units[lo], steps, steps - 1 - s_rows[lo]);
     }
     __syncthreads();
-    // (records go through LDS and out in neighbouring words, as the tiles' do below)
-    int* const share_rec = &s_rec[0][0][0];
-    constexpr int kPad = kShareInts + 1;
-    static_assert(sizeof(s_rec) >= kPlanMaxWgs / 2 * kPad * sizeof(int), "half of the shares at a time");
-    for (int w0 = 0; w0 < n_main_wgs; w0 += kPlanMaxWgs / 2) {
-      const int w = w0 + tid;
-      if (tid < kPlanMaxWgs / 2 && w < n_active) {
-        int* const rec = share_rec + tid * kPad;
-        const int r = share_of_wg(w, n_active);
-        const int i0 = s_cut[r].item, j0 = s_cut[r].step, j_end = s_cut[r + 1].step, i_last = s_cut[r + 1].item - (j_end == 0 ? 1 : 0);
-        rec[kShareLeft] = i_last - i0;
-        if (i_last >= i0) {  // (else nothing lies between the two boundaries)
-          const int g = i0 / n_tiles_all, t = i0 - g * n_tiles_all;
-          int b, qt, steps;
-          locate(t, b, qt, steps);
-          const int cb = ctx_before[b], S = cu_q[b + 1] - cu_q[b];
-          const int nblk_total = (int)(((long long)cb + S + 15) >> 4);
+    // one record (one line of memory) per thread
+    for (int w = tid; w < n_main_wgs; w += kPlanThreads) {
+      plan[kPlanPieces0 + w] = 0;
+      if (w >= n_active) continue;
+      const int r = share_of_wg(w, n_active);
+      const int i0 = s_cut[r].item, j0 = s_cut[r].step, j_end = s_cut[r + 1].step, i_last = s_cut[r + 1].item - (j_end == 0 ? 1 : 0);
+      int rec[kShareInts] = {};
+      rec[kShareLeft] = i_last - i0;
+      if (i_last >= i0) {  // (else nothing lies between the two boundaries)
+        const int g = (int)((uint32_t)i0 / (uint32_t)n_tiles_all), t = i0 - g * n_tiles_all;
+        int b, qt, steps;
+        locate(t, b, qt, steps);
+        const int cb = ctx_before[b], S = cu_q[b + 1] - cu_q[b];
+        const int nblk_total = (int)(((long long)cb + S + 15) >> 4);
 #pragma unroll
-          for (int j = 0; j < 12; ++j) rec[8 + j] = block_table[(size_t)b * bt_stride + min(4 * j0 + j, nblk_total - 1)];
-          rec[0] = b;
-          rec[1] = r;
-          rec[2] = cu_q[b];
-          rec[3] = S;
-          rec[4] = cb;
-          rec[5] = i0 == i_last && j_end > 0 ? j_end : steps;
-          tile_rows(S, qt, rec[6], rec[7]);
-          const int begin0 = share_that_begins(s_cut, r);
-          rec[kShareStep0] = j0;
-          rec[kShareItem] = t * Hkv + g;
-          rec[kShareEnd] = j_end;
-          rec[kShareBegin0] = begin0;
-          rec[kSharePieces0] = share_that_ends(s_cut, n_active, r, i0) - begin0 + 1;
-          rec[kSharePieces1] = share_that_ends(s_cut, n_active, r, i_last) - (i_last == i0 ? begin0 : r) + 1;
-        }
+        for (int j = 0; j < 12; ++j) rec[8 + j] = block_table[(size_t)b * bt_stride + min(4 * j0 + j, nblk_total - 1)];
+        rec[0] = b;
+        rec[1] = r;
+        rec[2] = cu_q[b];
+        rec[3] = S;
+        rec[4] = cb;
+        rec[5] = i0 == i_last && j_end > 0 ? j_end : steps;
+        tile_rows(S, qt, rec[6], rec[7]);
+        const int begin0 = share_that_begins(s_cut, r);
+        rec[kShareStep0] = j0;
+        rec[kShareItem] = t * Hkv + g;
+        rec[kShareEnd] = j_end;
+        rec[kShareBegin0] = begin0;
+        rec[kSharePieces0] = share_that_ends(s_cut, n_active, r, i0) - begin0 + 1;
+        rec[kSharePieces1] = share_that_ends(s_cut, n_active, r, i_last) - (i_last == i0 ? begin0 : r) + 1;
       }
-      __syncthreads();
-      const int n = min(kPlanMaxWgs / 2, n_active - w0);
-      for (int i = tid; i < n * kShareInts; i += kPlanThreads)
-        plan[kPlanShareRec0 + (size_t)w0 * kShareInts + i] = share_rec[(i / kShareInts) * kPad + i % kShareInts];
-      if (tid < kPlanMaxWgs / 2 && w < n_main_wgs) plan[kPlanPieces0 + w] = 0;
-      __syncthreads();
+      static_assert(kShareInts % 4 == 0 && kPlanShareRec0 % 4 == 0, "records are written in 16-byte pieces");
+#pragma unroll
+      for (int p = 0; p < kShareInts; p += 4)
+        *reinterpret_cast<u32x4*>(plan + kPlanShareRec0 + (size_t)w * kShareInts + p) =
+            u32x4{(uint32_t)rec[p], (uint32_t)rec[p + 1], (uint32_t)rec[p + 2], (uint32_t)rec[p + 3]};
     }
   } else {
     scan_array(bins);
@@ -436,7 +433,8 @@ __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(const int32_
   // A wavefront's 64 records go through LDS and out in 16-byte pieces, neighbouring lanes writing neighbouring pieces: one
   // record per lane, 80 bytes apart, every store instruction touches 64 cache lines, and one workgroup writes them all
   // (4096 tiles: 20.5 -> 15.4 us; 600: 9.0 -> 7.7).
-  for (int base = wave * 64; base < n_tiles_all; base += kPlanThreads) {
+  // (With shares the last wavefronts take the first tiles: the first ones are at the shares.)
+  for (int base = (n_active > 0 ? kPlanThreads / 64 - 1 - wave : wave) * 64; base < n_tiles_all; base += kPlanThreads) {
     const int i = base + lane, n = min(64, n_tiles_all - base);
     if (lane < n) {
       int b, qt, steps;

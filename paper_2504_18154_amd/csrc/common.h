@@ -290,6 +290,25 @@ __device__ __forceinline__ SeqOf find_sequence(const int32_t* __restrict__ cu_q,
   return r;
 }
 
+// Inclusive prefix sums and the maximum over the lanes of a wavefront, for non-negative x, within the vector unit (a
+// shuffle takes a trip through LDS per step, six of them 0.2 us).
+template <typename F>
+__device__ __forceinline__ int lanes_scan(int x, F f) {
+  x = f(x, __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false));  // row_shr:1
+  x = f(x, __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false));  // row_shr:2
+  x = f(x, __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false));  // row_shr:4
+  x = f(x, __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false));  // row_shr:8
+  x = f(x, __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false));  // row_bcast:15
+  x = f(x, __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false));  // row_bcast:31
+  return x;
+}
+__device__ __forceinline__ int lanes_prefix_sum(int x) {
+  return lanes_scan(x, [](int a, int b) { return a + b; });
+}
+__device__ __forceinline__ int lanes_max(int x) {
+  return __builtin_amdgcn_readlane(lanes_scan(x, [](int a, int b) { return max(a, b); }), 63);
+}
+
 __device__ __forceinline__ float wave_max(float v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));

@@ -4,6 +4,8 @@
 // arithmetic, for the plan kernel and for a host program alike.
 #pragma once
 
+#include <math.h>
+
 #if defined(__HIPCC__)
 #define ECO_HD __host__ __device__ __forceinline__
 #else
@@ -15,6 +17,22 @@ namespace eco {
 constexpr int kItemCost = 3;
 constexpr int kShareMinUnits = 8;   // fewest units of a share
 constexpr int kShareMaxRounds = 4;  // most items per workgroup of a batch
+
+// Quotient and root as the rule below needs them: to a few units in the last place, with the bare instructions on the device.
+ECO_HD float over(float a, float b) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return a * __builtin_amdgcn_rcpf(b);
+#else
+  return a / b;
+#endif
+}
+ECO_HD float root(float a) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return __builtin_amdgcn_sqrtf(a);
+#else
+  return sqrtf(a);
+#endif
+}
 
 // Workgroups that take shares, 0: the items go through the queues instead, whole.  `units` of all items together, `heaviest`
 // and `lightest` item in key steps, n_wgs workgroups, two per CU.
@@ -30,25 +48,23 @@ constexpr int kShareMaxRounds = 4;  // most items per workgroup of a batch
 //            round: 427 / 370               64/8 8+30000: 445 / 48
 //   whole:   64/8 512+0: 15 / 18            64/8 512+2000: 53 / 53        32/8 4 x 749+89: 40 / 41      40/8 4 x 1024+0: 61 / 63
 //            64/8 4 x 256+2000: 79 / 84     64/8 8 x 256+8000: 513 / 525  8/1 16 x 500+500: 35 / 40     64/8 2048+0: 86 / 84
-ECO_HD int share_wgs(int n_items, long long units, int heaviest, int lightest, int n_wgs) {
+ECO_HD int share_wgs(int n_items, int units, int heaviest, int lightest, int n_wgs) {
   if (heaviest < kShareMinUnits || n_items <= 0 || n_wgs <= 0) return 0;
-  const float w = (float)n_wgs, u = (float)units;
+  const float w = (float)n_wgs, u = (float)units, all = 1.95f * over(u, w);
   // a share is no shorter than what its merge takes: a tile of s steps then has about 0.7 sqrt(s) pieces at most
-  int least = kShareMinUnits;
-  while (least * least < 2 * heaviest) ++least;
-  const long long most = units / least;
-  const int n = most < 1 ? 1 : most < n_wgs ? (int)most : n_wgs;
-  const float share = u / (float)n, all = 1.95f * u / w;
-  const float alone = 1.06f * share, t_share = (alone > all ? alone : all) + 8.f + 0.9f * (float)heaviest / share;
+  const int least = (int)ceilf(root((float)(2 * heaviest))), most = units / (least > kShareMinUnits ? least : kShareMinUnits);
+  const int n = most < 1 ? 1 : most < n_wgs ? most : n_wgs;
+  const float share = over(u, (float)n);
+  const float alone = 1.06f * share, t_share = (alone > all ? alone : all) + 8.f + 0.9f * over((float)heaviest, share);
   float t_items;
   if (n_items <= n_wgs) {
     // the heaviest item, beside the one of rank n_wgs / 2, which is the mean if all are alike, or about this much if not
-    const float mean = u / (float)n_items, h = (float)(heaviest + kItemCost), half = 0.5f * w;
-    const float rest = (float)n_items - half;
+    const float items = (float)n_items, h = (float)(heaviest + kItemCost), half = 0.5f * w;
+    const float rest = items - half;
     float second = 0.f;
     if (rest > 0.f) {
-      second = 2.f * mean * rest / (float)n_items;
-      const float low = (u - half * h) / rest;
+      second = 2.f * over(u, items) * over(rest, items);
+      const float low = over(u - half * h, rest);
       second = low > second ? low : second;
       second = second < h ? second : h;
     }
@@ -57,7 +73,7 @@ ECO_HD int share_wgs(int n_items, long long units, int heaviest, int lightest, i
   } else {
     // the last round is not full, and it is made of the lightest items
     const int last = n_items % n_wgs;
-    t_items = all + (last > 0 ? 0.6f * (1.f - (float)last / w) * (float)lightest : 0.f);
+    t_items = all + (last > 0 ? 0.6f * (1.f - over((float)last, w)) * (float)lightest : 0.f);
   }
   return t_share < 0.97f * t_items ? n : 0;
 }
