@@ -353,8 +353,14 @@ __global__ __launch_bounds__(W * 64) void decode_any_kernel(
     const int last = blocks.first + W * (n - 1);
     if (base + 64 >= n && last == (t1 - 1) >> 4) {  // f[0] is the slice's last block
       tail = t1 - (last << 4);
-      if (newest) f[0].put_token(s_new[0], s_new[1], tail - 1, D, col, quad);
-      if (tail < 16) f[0].clear_tail(tail, quad);
+      // (Where the lane stands is worked out here: kept from in front of the loop, with all that follows from it, it took the
+      // registers of the blocks.  fp32, 256, spilled them, and its first and last blocks went through scratch memory: 50
+      // tokens 12.2 us, 10.6 without; bf16, 128, kept 16 scalars in vector registers: 2000 tokens 10.8 and 10.7.  Heads of up to 96
+      // elements have registers enough, and lose 0.06.)
+      int at_lane = lane;
+      if constexpr (KS > 3) asm volatile("" : "+v"(at_lane));
+      if (newest) f[0].put_token(s_new[0], s_new[1], tail - 1, D, at_lane & 15, at_lane >> 4);
+      if (tail < 16) f[0].clear_tail(tail, at_lane >> 4);
     }
     // Only blocks that exist are asked for: a load of nothing still takes its turn in the address unit, and three such
     // blocks (36 loads) per wavefront were 1 us of a context of 100 tokens.  Inside the loop every path issues the same
