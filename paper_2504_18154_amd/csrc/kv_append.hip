@@ -13,7 +13,7 @@
 // One workgroup fills one destination block for one, two or four adjacent K/V heads: up to 16 token
 // rows in, per head one contiguous K piece and one contiguous V piece out (4 KiB each for
 // bf16, D = 128).  Several heads per workgroup keep more loads in flight per thread and
-// spread the cost of finding the block over more bytes; a small call ends sooner with one (launch_typed has the line).
+// spread the cost of finding the block over more bytes; a small call ends sooner with one (append_heads.h has the line).
 // K units keep their 16 bytes and only change place, so they are copied directly with the
 // writes running along the destination.  V needs a transposition (16 slots of one element
 // become contiguous): the token rows are staged in LDS with coalesced reads and written
@@ -31,11 +31,12 @@
 // one wavefront per (sequence, K/V head), no numbering, no staging.
 #include <type_traits>
 
+#include "append_heads.h"
 #include "common.h"
 
 namespace eco {
 
-constexpr int kAppendThreads = 256;
+static_assert(kAppendThreads == 16 * kAppendAtOnceBytes / 16, "one unit of K and one of V per thread");
 
 template <typename E, int HPW, bool kAtOnce>
 __global__ __launch_bounds__(kAppendThreads) void kv_append_kernel(E* __restrict__ k_cache, E* __restrict__ v_cache,
@@ -207,28 +208,16 @@ static void launch_typed(const ecoserve_layout& L, void* k_cache, void* v_cache,
                        L.num_kv_heads, L.head_dim, pos_bias);
     return;
   }
-  // K/V heads per workgroup.  A small call is a chain of round trips, and the less each workgroup brings in the sooner it
-  // ends: one head, all loads asked for at once, while no more than eight workgroups per CU come of it.  Beyond that the cost
-  // of finding the block counts, and adjacent heads share it: two, and four from about forty heads' blocks per CU.
-  // (us, four heads / two / one / one at once, 8 K/V heads of bf16, 128, unless named: 93 tokens 4.95 / 3.66 / 3.10 / 2.92, 512
-  // 4.59 / 3.94 / 3.77 / 3.44, 2048 6.34 / 5.65 / 5.38 / 5.31, 64 x 20 6.15 / 5.35 / 5.17 / 4.93, 52 heads 5 x 51 6.53 / 5.63 / 5.18 / 5.12;
-  // 16 x 200 9.11 / 8.69 / 8.62 / 8.74, 4096 10.72 / 9.67 / 9.41 / 9.77, 8192 16.81 / 15.53 / 16.06 / 16.70, 15 x 1024 26.74 / 25.81 /
-  // 26.86 / 27.27, 256 x 20 19.26 / 17.42 / 18.87 / 18.35, 52 heads 4 x 500 25.99 / 25.10 / 25.90 / 26.28; 4 x 8192 52.79 / 53.65 / 54.10 /
-  // 56.08.)
-  const int64_t one_head_wgs = ((int64_t)T / 16 + 2 * (int64_t)B) * L.num_kv_heads;
+  const AppendHeads by = append_heads(T, B, L.num_kv_heads, (int64_t)L.head_dim * sizeof(E), num_cu);
   auto launch = [&](auto hpw, auto at_once) {
     launch_tiled<E, decltype(hpw)::value, decltype(at_once)::value>(L, k_cache, v_cache, k_new, v_new, new_row_stride, cu_q, ctx_before, block_table,
                                                                     bt_stride, B, T, s);
   };
   typedef std::integral_constant<int, 1> One;
-  if (one_head_wgs <= 8 * num_cu || L.num_kv_heads % 2 != 0) {
-    if (one_head_wgs <= 8 * num_cu && 16 * L.head_dim / Elem<E>::X <= kAppendThreads) launch(One(), std::true_type());
-    else launch(One(), std::false_type());
-  } else if (one_head_wgs <= 40 * num_cu || L.num_kv_heads % 4 != 0) {
-    launch(std::integral_constant<int, 2>(), std::false_type());
-  } else {
-    launch(std::integral_constant<int, 4>(), std::false_type());
-  }
+  if (by.heads == 4) launch(std::integral_constant<int, 4>(), std::false_type());
+  else if (by.heads == 2) launch(std::integral_constant<int, 2>(), std::false_type());
+  else if (by.at_once) launch(One(), std::true_type());
+  else launch(One(), std::false_type());
 }
 
 template <typename E, int HPW>
