@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "common.h"
+#include "decode_slices.h"
 #include "prefill_shares.h"
 
 using namespace eco;

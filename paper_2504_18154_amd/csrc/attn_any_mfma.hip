@@ -220,15 +220,12 @@ __device__ __forceinline__ float load_shared(float* p) { return __hip_atomic_loa
 // (A trial is one scan; with all lanes as candidates and a loop over the sequences, 16 of them took 0.3 us longer.)
 __device__ __forceinline__ int balanced_slice_blocks(int nb, int Hkv, int slots, int W, int& n, int& end) {
   const int longest = lanes_max(nb), sum = __builtin_amdgcn_readlane(lanes_prefix_sum(nb), 63);
-  const bool whole = W == 8 && whole_context((float)longest, (float)sum * (float)Hkv);  // (four: two workgroups per CU, see small_decode)
-  const float shortest = fmaxf(least_slice((float)longest) - 0.5f * (float)W, (float)sum * __builtin_amdgcn_rcpf((float)slots));
-  int st = whole ? max(longest, 1) : ((int)shortest / W + 1) * W;
+  int st = first_balanced_slice(longest, sum, Hkv, slots, W);
   for (;;) {
-    // (exact up to 2^21 blocks; a slice too many would find nothing left to do, and the last of one too few takes the rest)
-    n = (int)(((float)nb + ((float)st - 0.5f)) * __builtin_amdgcn_rcpf((float)st));
+    n = balanced_slices_of(nb, st);
     end = lanes_prefix_sum(n);
     if (st >= longest || __builtin_amdgcn_readlane(end, 63) <= slots) return st;
-    st += max(st >> 2, W) / W * W;
+    st = next_balanced_slice(st, W);
   }
 }
 
@@ -755,9 +752,6 @@ void launch_prefill_typed(const AttnArgs& a, const int32_t* cu_q, const int32_t*
   });
 }
 
-// Wavefronts of a decode workgroup: eight while two blocks of K and V fit beside the rest in 256 registers.
-constexpr int decode_wavefronts(int D, int elem_bytes) { return D > (elem_bytes == 4 ? 128 : 192) ? 4 : 8; }
-
 template <typename E>
 void launch_decode_typed(const AttnArgs& a, const int32_t* ctx_len, int32_t split_tokens, int32_t n_split_max, float* ws_acc,
                          float* ws_ml, uint32_t* counters, bool many, hipStream_t s) {
@@ -783,70 +777,6 @@ void launch_decode_typed(const AttnArgs& a, const int32_t* ctx_len, int32_t spli
 }
 
 }  // namespace
-
-// Contexts up to 1024 tokens stay whole (no merge); longer ones are cut into slices of 256 tokens, or of 512 or 1024
-// when that already makes enough workgroups.  (8 K/V heads, bf16, 128, us in slices of 256 / 512 / 1024: one sequence of 2000
-// tokens 9.6 / 10.3 / 12.7, of 8000 14.9 / 12.6 / 13.8; 4 x 2000 11.1 / 10.9 / 13.3.)
-static int32_t decode_any_split_tokens(int32_t B, int32_t Hkv, int32_t max_ctx_len, int32_t num_cu) {
-  int32_t st = max_ctx_len > 1024 ? 256 : 1024;
-  while (st < 1024 && (int64_t)B * Hkv * ((max_ctx_len + st - 1) / st) > num_cu / 2) st *= 2;
-  return st;
-}
-
-// For every other layout: contexts are cut, into slices of whole rounds of the wavefronts, where that makes no more than one
-// workgroup per CU and the walk it saves is worth a merge.  A block's walk takes 0.012 us per KiB of it in bf16, 0.018 in fp32 (one of
-// 700 tokens against one of 50: 64 0.05 and 0.16, fp32 128 0.28, 192 0.13, 256 0.21 and 0.57 us a block); a merge 2.7
-// (1.8 in fp32), more for large heads, and 0.13 a slice.  Us per call whole / cut: fp32, 64, 2 K/V heads: 1 x 700 tokens 11.2 / 7.6, 16 x 700 11.5 / 9.0; fp32, 128, 3:
-// 1 x 400 14.2 / 9.5, 4 x 37..708 15.6 / 10.4, 8 x 3000 33.6 / 22.6; fp32, 256, 2: 16 x 700 41.4 / 21.2; bf16, 192, 2: 16 x 700 16.7 / 12.8; bf16, 256, 1:
-// 1 x 200 11.7 / 13.1, 1 x 400 14.3 / 13.6, 64 x 800 27.1 / 21.3; bf16, 96, 2: 16 x 700 8.4 / 9.0; 64, 8: 1 x 700 6.6 whole.
-SmallDecode any_decode(int32_t B, int32_t Hkv, int32_t D, int32_t elem_bytes, int32_t max_ctx_len, int32_t num_cu) {
-  const int32_t W = decode_wavefronts(D, elem_bytes), nb = (max_ctx_len + kBlockSize - 1) / kBlockSize;
-  const int64_t slots = num_cu / ((int64_t)B * Hkv);
-  const float large = std::max(1.f, (float)D / 192.f), walk = (elem_bytes == 2 ? 0.012f : 0.018f) * (float)(32 * D * elem_bytes) / 1024.f;
-  if (slots > 1 && walk * (float)(nb - W) > (elem_bytes == 2 ? 2.7f : 1.8f) * large) {
-    const int64_t least = std::max<int64_t>((int64_t)sqrtf(0.13f * large / walk * (float)nb), (nb + slots - 1) / slots);
-    const int32_t st = (int32_t)std::min<int64_t>((least + W - 1) / W * W, 64) * kBlockSize;
-    return {st, (max_ctx_len + st - 1) / st};
-  }
-  const int32_t st = decode_any_split_tokens(B, Hkv, max_ctx_len, num_cu);
-  return {st, (max_ctx_len + st - 1) / st};
-}
-
-// For (bf16, 128): how this kernel takes a small batch, n_split 0 if it does not.  It needs no numbering of the batch and no
-// second launch, which is what such a batch spends its time on in the persistent kernel.
-//   Several sequences, one of them of more than 768 tokens, and eight workgroups (one per CU) or more per five (sequence, K/V
-//   head)s: balanced slices.  Us per call before (uniform slices or the persistent kernel) / balanced: 64 query heads on 8, 16 x
-//   20..2000 tokens 18.4 / 14.5, 8 x 20..8000 19.2 / 14.6; 5 on 1, 13 x 745..5960 16.3 / 12.1; 8 on 1, 64 x 1000..8000 38.5 / 28.8; 32 on 8, 9 x
-//   1196..9574 35.8 / 29.0; 40 on 8, 18 x 116..935 15.6 / 14.3, 8 x 1000 16.0 / 13.9, 16 x 1000 18.9 / 18.4, 16 x 2000 29.2 / 27.8, 20 x 2000 38.9 / 32.8, 20 x
-//   100..3000 30.2 / 26.1, 15 x 1142..9140 51.8 / 51.7; 52 on 52, 2 x 1000..2000 20.7 / 21.0.  Finding the slices takes half a microsecond.  Fewer
-//   spare workgroups even out too little (24 x 1000..10000 84 / 98), and from 400 MB on the persistent kernel's stream is the
-//   faster one (16 x 8000 93 / 99; both without the non-temporal hint).
-//   No balancing where every sequence may have as many slices as one of max_ctx_len tokens gets for itself: the slices of
-//   balanced_slice_blocks for that (1 x 777: 9.4 / 8.5, 1 x 1000: 10.7 / 8.9, 1 x 16000: 21.9 / 20.8).
-//   Else uniform slices if all workgroups run at once - one of eight wavefronts per CU, or (short contexts) two of four (us per call
-//   persistent / here: 16 x 1000 tokens 20.7 / 14.1; 32 x 200: 15.7 / 7.4; 64 x 500: 35.0 / 23.5); with uniform slices nothing evens out
-//   the lengths of more workgroups than fit: 128 sequences around 500 tokens, lognormal, take 62 there and 74 here, 40 of them 25
-//   and 28 (128 of 500 each: 54 and 50).
-//   Else balanced slices for two workgroups of four wavefronts per CU, all of which run at once too, with as many to spare, up
-//   to 300 MB (persistent / here: 40 x 100..1000 27.2 / 24.6, 40 x 600 29.8 / 24.4, 40 x 20..2000 25.1 / 21.2, 28 x 100..3000 37.5 /
-//   33.5, 24 x 100..3000 33.0 / 30.2, 16 query heads on 4, 64 x 100..2000 31.9 / 28.3; 36 x 1500 49.0 / 49.0, 40 x 2000 65.3 / 66.1, 24 x
-//   4000 74 / 80; with nothing to spare 64 x 20..2000 33.7 / 39.2; three workgroups and more per CU 40 x 100..1000 28.5).
-SmallDecode small_decode(int32_t B, int32_t Hkv, int32_t max_ctx_len, int32_t num_cu) {
-  const int64_t pairs = (int64_t)B * Hkv;
-  const int32_t nb = (max_ctx_len + kBlockSize - 1) / kBlockSize, slots = num_cu / Hkv;
-  const bool whole = whole_context((float)nb, (float)nb * (float)Hkv);  // (also of more sequences, then)
-  if (!whole && slots > 0 && pairs * ((max_ctx_len + 1023) / 1024) <= num_cu) {
-    int32_t st = ((int32_t)least_slice((float)nb) + 4) / 8 * 8;  // whole rounds of eight wavefronts
-    if (B == 1) st = std::max(st, (nb + 8 * slots - 1) / (8 * slots) * 8);
-    if (B * ((nb + st - 1) / st) <= slots && (B == 1 || nb > 48)) return {st * kBlockSize, (nb + st - 1) / st};
-  }
-  if (B > 1 && B <= 64 && nb > 48 && 8 * B <= 5 * slots && pairs * max_ctx_len <= 800000) return {0, slots};
-  const int32_t st = decode_any_split_tokens(B, Hkv, max_ctx_len, num_cu), n = (max_ctx_len + st - 1) / st;
-  if (pairs * n <= num_cu || (max_ctx_len <= 512 && pairs <= 2 * num_cu)) return {st, n};
-  const int32_t slots2 = 2 * num_cu / Hkv;
-  if (B <= 64 && 8 * B <= 5 * slots2 && pairs * max_ctx_len <= 600000) return {0, slots2};
-  return {0, 0};
-}
 
 hipError_t launch_prefill_any(const AttnArgs& a, const int32_t* cu_q, const int32_t* ctx_before, int32_t T, hipStream_t s) {
   if (a.dtype == ECOSERVE_BF16) launch_prefill_typed<uint16_t>(a, cu_q, ctx_before, T, s);

@@ -164,12 +164,8 @@ hipError_t launch_decode_merge(const AttnArgs& a, const int32_t* ctx_len, int32_
 // attn_any_mfma.hip: every layout on matrix cores (bf16, D = 128: small decode batches only)
 // (one launch; with a.k_new given it appends the step's tokens too; split_tokens: a multiple of 16 per slice of the
 // context, n_split_max slices, partial states [B][Hq][n_split_max]; or, (bf16, 128) and B <= 64 only, 0: balanced slices, n_split_max
-// per K/V head in all, at least B, partial states [n_split_max][Hq]; counters [B][Hkv] that are zero and stay so)
-struct SmallDecode {
-  int32_t split_tokens, n_split;  // as launch_decode_any takes them
-};
-SmallDecode any_decode(int32_t B, int32_t Hkv, int32_t D, int32_t elem_bytes, int32_t max_ctx_len, int32_t num_cu);
-SmallDecode small_decode(int32_t B, int32_t Hkv, int32_t max_ctx_len, int32_t num_cu);
+// per K/V head in all, at least B, partial states [n_split_max][Hq]; counters [B][Hkv] that are zero and stay so:
+// any_decode and small_decode in decode_slices.h)
 hipError_t launch_prefill_any(const AttnArgs& a, const int32_t* cu_q, const int32_t* ctx_before, int32_t T, hipStream_t s);
 hipError_t launch_decode_any(const AttnArgs& a, const int32_t* ctx_len, int32_t split_tokens, int32_t n_split_max,
                              float* ws_acc, float* ws_ml, uint32_t* counters, int32_t num_cu, hipStream_t s);

@@ -16,6 +16,7 @@
 #include <mutex>
 
 #include "common.h"
+#include "decode_slices.h"
 
 namespace eco {
 namespace {

@@ -50,3 +50,93 @@ def test_slices_and_block_table_entries(tmp_path):
                    check=True)
     r = subprocess.run([str(exe)], capture_output=True, text=True)
     assert r.returncode == 0 and r.stdout == "ok\n", r.stdout
+
+
+RULE = r"""
+#include <cstdio>
+#include <cstdlib>
+#include "decode_slices.h"
+using namespace eco;
+// the balanced slices of the contexts `len`, as the kernel finds them; false: they do not cover every context once
+static bool covers(const int* len, int B, int Hkv, int slots, int W) {
+  int longest = 0, sum = 0, n[64];
+  for (int b = 0; b < B; ++b) {
+    const int nb = (len[b] + 15) >> 4;
+    longest = nb > longest ? nb : longest;
+    sum += nb;
+  }
+  int st = first_balanced_slice(longest, sum, Hkv, slots, W), all;
+  for (;; st = next_balanced_slice(st, W)) {
+    all = 0;
+    for (int b = 0; b < B; ++b) all += n[b] = balanced_slices_of((len[b] + 15) >> 4, st);
+    if (st >= longest || all <= slots) break;
+  }
+  if (all > slots || st <= 0) return false;
+  for (int b = 0; b < B; ++b) {
+    int next = 0;
+    for (int sp = 0; sp < n[b]; ++sp) {
+      const Slice s = decode_slice(len[b], st * 16, n[b], sp);
+      if (s.n != n[b] || s.t0 != next || s.t1 <= s.t0) return false;
+      next = s.t1;
+    }
+    if (next != len[b]) return false;
+  }
+  return true;
+}
+// for each "B Hkv longest bound len..." line: the rule's answer, and whether its balanced slices cover the contexts; then random ones
+int main() {
+  int B, Hkv, bound, len[64];
+  while (std::scanf("%d %d %d", &B, &Hkv, &bound) == 3) {
+    for (int b = 0; b < B; ++b) {
+      int x;
+      if (std::scanf("%d", &x) != 1) return 1;
+      if (b < 64) len[b] = x;
+    }
+    const SmallDecode d = small_decode(B, Hkv, bound, 256);
+    const int W = d.n_split == 256 / Hkv ? 8 : 4;
+    std::printf("%s\n", d.n_split == 0 ? "persistent" : d.split_tokens > 0 ? "uniform" : !covers(len, B, Hkv, d.n_split, W) ? "wrong" : W == 8 ? "8" : "4");
+  }
+  unsigned seed = 12345;
+  auto rnd = [&](unsigned n) { return (seed = seed * 1664525u + 1013904223u, (unsigned)((unsigned long long)(seed >> 8) * n >> 24)); };
+  int balanced = 0;
+  for (int i = 0; i < 200000; ++i) {
+    const int heads[] = {1, 2, 3, 4, 5, 8, 16, 52};
+    Hkv = heads[rnd(8)];
+    B = 2 + rnd(63);
+    const int most = 1 + rnd(rnd(3) ? 3000 : 600000 / (B * Hkv)), shape = rnd(4);
+    for (int b = 0; b < B; ++b) len[b] = shape == 0 ? rnd(most + 1) : shape == 1 ? (rnd(2) ? 0 : rnd(most + 1)) : shape == 2 ? (b ? rnd(40) : most) : most;
+    bound = most + (rnd(2) ? 0 : rnd(2000));
+    const SmallDecode d = small_decode(B, Hkv, bound, 256);
+    if (d.n_split == 0 || d.split_tokens > 0) continue;
+    ++balanced;
+    if (!covers(len, B, Hkv, d.n_split, d.n_split == 256 / Hkv ? 8 : 4)) return std::printf("B %d, %d heads, up to %d tokens: not covered\n", B, Hkv, most), 1;
+  }
+  std::printf("%s\n", balanced > 20000 ? "covered" : "too few");
+}
+"""
+
+# the paths that the batches of the GPU tests are there for: at the longest context's length, and with the looser bound
+PATHS = {"RAGGED": ["uniform uniform", "8 8", "8 8", "uniform uniform", "8 8", "uniform uniform", "8 8", "uniform uniform", "4 persistent", "4 persistent"]}
+
+
+def test_paths_of_the_batches_of_the_gpu_tests_and_their_balanced_slices(tmp_path):
+    from tests import test_gpu_small_decode as t
+    src, exe = tmp_path / "rule.cpp", tmp_path / "rule"
+    src.write_text(RULE)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-I", os.path.join(ROOT, "paper_2504_18154_amd", "csrc"), str(src), "-o", str(exe)], check=True)
+    calls, want = [], []
+    for (heads, lens), path in zip(t.RAGGED, PATHS["RAGGED"], strict=True):
+        for above, p in zip((0, 3000), path.split()):
+            calls.append((heads[1], lens, max(lens) + above))
+            want.append(p)
+    for heads, lens, above, waves in t.BALANCED:
+        calls += [(heads[1], lens, max(lens)), (heads[1], lens, max(lens) + above)]
+        want += [str(waves)] * 2
+    # batches with empty sequences, and those without a context
+    calls += [(8, [1500] + [0] * 39, 1500), (8, [1500] + [0] * 47, 1500), (8, [34000, 40], 34000), (8, [60000, 40], 60000), (8, [8000, 40], 8000)]
+    want += ["4", "persistent", "8", "persistent", "8"]
+    text = "\n".join(f"{len(n)} {h} {bound} " + " ".join(map(str, n)) for h, n, bound in calls) + "\n"
+    r = subprocess.run([str(exe)], input=text, capture_output=True, text=True)
+    got = r.stdout.split("\n")
+    assert got[len(want):] == ["covered", ""], r.stdout[-300:]
+    assert got[:len(want)] == want, [(c[0], len(c[1]), c[2], g, w) for c, g, w in zip(calls, got, want) if g != w]

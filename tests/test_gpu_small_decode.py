@@ -97,12 +97,14 @@ def test_infinite_values_reach_only_their_own_elements(lens):
     layer.close()
 
 
-def test_the_persistent_kernel_passes_over_sequences_without_tokens():
-    """A batch too large for the single launch (40 sequences of up to 1500 tokens: 640 slices for 256 workgroups), with lengths of zero first,
-    in the middle, several in a row, and last; with a context and without."""
+@pytest.mark.parametrize("each", [15, 19], ids=["B40", "B48"])
+def test_sequences_without_tokens_are_passed_over(each):
+    """Lengths of zero first, in the middle, several in a row, and last, among up to 1500 tokens; with a context and without.  48 sequences
+    (384 (sequence, K/V head)s for 256 workgroups) go to the persistent kernel, 40 take balanced slices, two workgroups per CU
+    (PATHS in test_decode_slices.py)."""
     model = wl.ModelShape("30B-heads", 40, 8, 128, 1, "bf16")
     rng = np.random.default_rng(58)
-    lens = np.r_[0, 0, 700, 0, rng.integers(1, 600, size=15), 0, 0, 1500, 0, rng.integers(1, 600, size=15), 16, 0].astype(np.int32)
+    lens = np.r_[0, 0, 700, 0, rng.integers(1, 600, size=each), 0, 0, 1500, 0, rng.integers(1, 600, size=each), 16, 0].astype(np.int32)
     pb = wl.prefill_batch(model, np.maximum(lens, 1), 59)
     layer = Layer(model, pb.num_blocks, len(lens), pb.block_table.shape[1])
     layer.append(*(wl.randn((int(lens.sum()), 8, 128), "bf16", s) for s in (1, 2)), wl.cu_from_lengths(lens), np.zeros_like(lens), pb.block_table)
@@ -119,21 +121,37 @@ def test_the_persistent_kernel_passes_over_sequences_without_tokens():
     layer.close()
 
 
-# several sequences, cut into slices that fill the workgroups: lengths and slices at the edges of blocks, of the wavefronts' rounds
-# and of the rule that leaves contexts whole; empty sequences; as many sequences as a wavefront has lanes
-BALANCED = [((40, 8), [769, 1]), ((40, 8), [2000, 128, 129, 127, 16, 17, 0, 1024]), ((64, 8), [1025] * 20), ((5, 1), [0, 3000, 0, 0, 2999, 1, 0]),
-            ((16, 1), [4095, 4096, 4097] + [1] * 61), ((3, 3), [900, 700, 5000]), ((52, 52), [800, 1500]), ((8, 1), [30000, 20, 700]),
-            ((40, 8), [600] * 36 + [0, 1, 128, 1000]), ((16, 4), [1 + 17 * i for i in range(64)])]  # two workgroups of four wavefronts per CU
+# Several sequences of very different lengths: at the edges of blocks, of the wavefronts' rounds and of the rule that leaves contexts
+# whole; empty sequences; as many sequences as a wavefront has lanes.  Which of them are cut into balanced slices with the caller's bound
+# at the longest and 3000 tokens above it: PATHS in test_decode_slices.py.
+RAGGED = [((40, 8), [769, 1]), ((40, 8), [2000, 128, 129, 127, 16, 17, 0, 1024]), ((64, 8), [1025] * 20), ((5, 1), [0, 3000, 0, 0, 2999, 1, 0]),
+          ((16, 1), [4095, 4096, 4097] + [1] * 61), ((3, 3), [900, 700, 5000]), ((52, 52), [800, 1500]), ((8, 1), [30000, 20, 700]),
+          ((40, 8), [600] * 36 + [0, 1, 128, 1000]), ((16, 4), [1 + 17 * i for i in range(64)])]
+# Balanced slices on one workgroup per CU (8 wavefronts) or two (4), with what the bound may lie above the longest context: empty
+# sequences first, last and in a row; one long context beside many tiny ones; several trials until the slices fit.
+BALANCED = [((40, 8), [0, 0, 3000, 0, 0, 0, 40, 0, 2999, 1, 0, 0], 3000, 8), ((8, 1), [12000] + [20] * 40, 3000, 8), ((40, 8), [2000] * 20, 3000, 8),
+            ((5, 1), [0] * 20 + [3000, 0, 0, 2999, 1, 0] + [5] * 30, 3000, 8), ((40, 8), [4000 - 7 * i for i in range(20)], 900, 8), ((16, 4), [0] * 39 + [2500], 2000, 8),
+            ((40, 8), [0, 0, 0, 1100, 0] + [300] * 18 + [0], 1500, 4), ((40, 8), [1100, 1099] + [1030] * 36 + [1, 0], 700, 4),
+            ((16, 4), [1200] + [20] * 62 + [0], 1100, 4), ((52, 52), [0, 2500, 20, 1025], 300, 4), ((8, 1), [290000], 300000, 4)]
 
 
-@pytest.mark.parametrize("heads,lens", BALANCED, ids=[f"{h[0]}x{h[1]}-B{len(n)}-L{max(n)}" for h, n in BALANCED])
+@pytest.mark.parametrize("heads,lens", RAGGED, ids=[f"{h[0]}x{h[1]}-B{len(n)}-L{max(n)}" for h, n in RAGGED])
 @pytest.mark.parametrize("loose", [False, True], ids=["tight", "loose"])
-def test_balanced_slices(heads, lens, loose):
+def test_ragged_lengths(heads, lens, loose):
+    _against_the_oracle(heads, lens, max(lens) + (3000 if loose else 0))
+
+
+@pytest.mark.parametrize("heads,lens,above,waves", BALANCED, ids=[f"{c[0][0]}x{c[0][1]}-B{len(c[1])}-L{max(c[1])}" for c in BALANCED])
+@pytest.mark.parametrize("loose", [False, True], ids=["tight", "loose"])
+def test_balanced_slices(heads, lens, above, waves, loose):
+    _against_the_oracle(heads, lens, max(lens) + (above if loose else 0))
+
+
+def _against_the_oracle(heads, lens, bound):
     model = wl.ModelShape("balanced", heads[0], heads[1], 128, 1, "bf16")
     lens = np.asarray(lens, dtype=np.int32)
-    say(f"decode, balanced slices, heads {heads}, lengths {lens.tolist()}")
+    say(f"decode, heads {heads}, lengths {lens.tolist()}, the caller's bound {bound}")
     pb = wl.prefill_batch(model, lens, 57)
-    bound = int(lens.max()) + (3000 if loose else 0)  # the caller's bound on the lengths
     table = np.pad(pb.block_table, ((0, 0), (0, (bound + 15) // 16 - pb.block_table.shape[1])), constant_values=2**30)  # never read there
     layer = Layer(model, pb.num_blocks, pb.B, table.shape[1])
     k, v = (wl.randn((pb.T, model.Hkv, 128), "bf16", s) for s in (1, 2))

@@ -51,10 +51,11 @@ def test_noalloc_decode_matches_the_context_call_twice_in_a_row():
     _decode_both_ways(model, np.array([700, 3, 64, 1, 129], dtype=np.int32), 902)
     say("noalloc decode: group size 8, one long sequence in slices, small enough for the single launch")
     _decode_both_ways(wl.ModelShape("70B-heads", 64, 8, 128, 1, "bf16"), np.array([8000, 40], dtype=np.int32), 903)
-    # (544 slices of 1024 tokens are more than run at once: the persistent kernel, about 125 states per (sequence, head), so the
-    # merge of the cut ones goes through its rounds of 64)
-    say("noalloc decode: group size 8, one long sequence cut into hundreds of pieces")
-    _decode_both_ways(wl.ModelShape("70B-heads", 64, 8, 128, 1, "bf16"), np.array([34000, 40], dtype=np.int32), 904)
+    # (34000 tokens: balanced slices; 60000: the persistent kernel, well over a hundred states per
+    # (sequence, head), so the merge of the cut ones goes through its rounds of 64; PATHS in test_decode_slices.py)
+    for n in (34000, 60000):
+        say(f"noalloc decode: group size 8, one long sequence of {n} tokens cut into many pieces")
+        _decode_both_ways(wl.ModelShape("70B-heads", 64, 8, 128, 1, "bf16"), np.array([n, 40], dtype=np.int32), 870 + n // 1000)
 
 
 def test_noalloc_decode_rejects_what_it_cannot_hold():
