@@ -102,17 +102,27 @@ inline int32_t decode_any_split_tokens(int32_t B, int32_t Hkv, int32_t max_ctx_l
 // (1.8 in fp32), more for large heads, and 0.13 a slice.  Us per call whole / cut: fp32, 64, 2 K/V heads: 1 x 700 tokens 11.2 / 7.6, 16 x 700 11.5 / 9.0; fp32, 128, 3:
 // 1 x 400 14.2 / 9.5, 4 x 37..708 15.6 / 10.4, 8 x 3000 33.6 / 22.6; fp32, 256, 2: 16 x 700 41.4 / 21.2; bf16, 192, 2: 16 x 700 16.7 / 12.8; bf16, 256, 1:
 // 1 x 200 11.7 / 13.1, 1 x 400 14.3 / 13.6, 64 x 800 27.1 / 21.3; bf16, 96, 2: 16 x 700 8.4 / 9.0; 64, 8: 1 x 700 6.6 whole.
+//   Slices beyond 1024 tokens are no longer than the uniform ones would be (bf16, 32, 1 x 2000: 256 tokens 7.1, 512 7.6; 96, 2 x 4000: 256
+//   10.3, 384 11.1), and a slice is as much shorter than the context as half a merge's walk (fp32, 128, 16 K/V heads, 8 x 300 tokens:
+//   whole 17.2, 256 and the rest 18.5; 96, 32 heads, 4 x 300 14.1 / 15.5).  bf16 heads above 192 merge four states at a time: no
+//   less than 256 tokens beyond 1024 (256, 1 x 1100: 256 tokens 15.1, 128 16.4; 1 x 4000 18.6, 192 21.3; but 1 x 700 15.2, 128 14.0).
+//   Against the best of nine forced lengths of slices, 1558 batches of 15 layouts: 2.3% longer on average in bf16, 4.1% in fp32 (8.4 and 32
+//   with the uniform slices alone, 2.6 and 4.2 without these three rules).
 inline SmallDecode any_decode(int32_t B, int32_t Hkv, int32_t D, int32_t elem_bytes, int32_t max_ctx_len, int32_t num_cu) {
   const int32_t W = decode_wavefronts(D, elem_bytes), nb = (max_ctx_len + 15) / 16;
   const int64_t slots = num_cu / ((int64_t)B * Hkv);
   const float large = std::max(1.f, (float)D / 192.f), walk = (elem_bytes == 2 ? 0.012f : 0.018f) * (float)(32 * D * elem_bytes) / 1024.f;
-  if (slots > 1 && walk * (float)(nb - W) > (elem_bytes == 2 ? 2.7f : 1.8f) * large) {
-    const int64_t least = std::max<int64_t>((int64_t)sqrtf(0.13f * large / walk * (float)nb), (nb + slots - 1) / slots);
-    const int32_t st = (int32_t)std::min<int64_t>((least + W - 1) / W * W, 64) * 16;
-    return {st, (max_ctx_len + st - 1) / st};
+  const float merge = (elem_bytes == 2 ? 2.7f : 1.8f) * large, state = 0.13f * large;
+  const int32_t uniform = decode_any_split_tokens(B, Hkv, max_ctx_len, num_cu), n_uniform = (max_ctx_len + uniform - 1) / uniform;
+  if (slots > 1 && walk * (float)(nb - W) > merge) {
+    const int64_t least = std::max<int64_t>((int64_t)sqrtf(state / walk * (float)nb), (nb + slots - 1) / slots);
+    int32_t st = (int32_t)std::min<int64_t>((least + W - 1) / W * W, 64) * 16;
+    if (max_ctx_len > 1024 && n_uniform <= slots) st = std::min(st, uniform);
+    if (max_ctx_len > 1024 && elem_bytes == 2 && D > 192 && (max_ctx_len + 255) / 256 <= slots) st = std::max(st, 256);
+    const int32_t n = (max_ctx_len + st - 1) / st;
+    if (max_ctx_len > 1024 || walk * (float)(nb - st / 16) > 0.5f * merge + state * (float)n) return {st, n};
   }
-  const int32_t st = decode_any_split_tokens(B, Hkv, max_ctx_len, num_cu);
-  return {st, (max_ctx_len + st - 1) / st};
+  return {uniform, n_uniform};
 }
 
 // For (bf16, 128): how this kernel takes a small batch, n_split 0 if it does not.  It needs no numbering of the batch and no

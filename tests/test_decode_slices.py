@@ -140,3 +140,38 @@ def test_paths_of_the_batches_of_the_gpu_tests_and_their_balanced_slices(tmp_pat
     got = r.stdout.split("\n")
     assert got[len(want):] == ["covered", ""], r.stdout[-300:]
     assert got[:len(want)] == want, [(c[0], len(c[1]), c[2], g, w) for c, g, w in zip(calls, got, want) if g != w]
+
+
+ANY = r"""
+#include <cstdio>
+#include "decode_slices.h"
+using namespace eco;
+int main() {
+  // head sizes, lengths and batches of every layout: slices of whole rounds, never longer than 1024 tokens (a wavefront's 64 block ids),
+  // as many as the context has, and no more than one workgroup per CU where the uniform ones would not be more either
+  for (int es : {2, 4})
+    for (int D = es == 2 ? 8 : 4; D <= 256; D += es == 2 ? 8 : 4)
+      for (int pairs : {1, 2, 3, 8, 40, 64, 128, 200, 256, 300, 5000})
+        for (int L = 1; L < 40000; L += L / 16 + 1) {
+          if (D == 128 && es == 2) continue;
+          const SmallDecode d = any_decode(pairs, 1, D, es, L, 256);
+          const int u = decode_any_split_tokens(pairs, 1, L, 256), n_u = (L + u - 1) / u;
+          if (d.split_tokens < 64 || d.split_tokens > 1024 || d.split_tokens % (16 * decode_wavefronts(D, es)) || d.n_split != (L + d.split_tokens - 1) / d.split_tokens ||
+              (pairs * d.n_split > 256 && d.n_split > n_u))
+            return std::printf("%d bytes, head size %d, %d pairs, %d tokens: %d of %d\n", es, D, pairs, L, d.n_split, d.split_tokens), 1;
+        }
+  // where cutting a context costs more than it saves
+  struct { int pairs, D, es, L, tokens; } at[] = {{2, 32, 2, 2000, 256}, {4, 96, 2, 4000, 256}, {128, 128, 4, 300, 1024}, {128, 96, 4, 300, 1024}, {1, 256, 2, 1100, 256}};
+  for (auto& c : at)
+    if (any_decode(c.pairs, 1, c.D, c.es, c.L, 256).split_tokens != c.tokens) return std::printf("head size %d, %d tokens\n", c.D, c.L), 1;
+  std::printf("ok\n");
+}
+"""
+
+
+def test_slices_of_other_layouts(tmp_path):
+    src, exe = tmp_path / "any.cpp", tmp_path / "any"
+    src.write_text(ANY)
+    subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", "-I", os.path.join(ROOT, "paper_2504_18154_amd", "csrc"), str(src), "-o", str(exe)], check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0 and r.stdout == "ok\n", r.stdout
