@@ -369,7 +369,7 @@ __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(const int32_
   const int n_items = n_tiles_all * Hkv, head_units = s_weight[0];  // units: key steps and kItemCost, of one K/V head's tiles
   if (may_share && s_weight[1] >= kShareMinUnits) {
     if (wave == 0) {
-      const int n = share_wgs(n_items, head_units * Hkv, s_weight[1], 0x7fffffff - s_weight[2], n_main_wgs);
+      const int n = share_wgs(n_items, head_units * Hkv, s_weight[1], 0x7fffffff - s_weight[2], n_main_wgs, B, n_tiles_all);
       if (lane == 0) s_active = n;
     }
     __syncthreads();

@@ -35,27 +35,32 @@ ECO_HD float root(float a) {
 }
 
 // Workgroups that take shares, 0: the items go through the queues instead, whole.  `units` of all items together, `heaviest`
-// and `lightest` item in key steps, n_wgs workgroups, two per CU.
+// and `lightest` item in key steps, n_wgs workgroups, two per CU; n_seqs sequences, of n_tiles query tiles (per K/V head) together.
 //
 // Shares cost a state of 64 KiB or two per cut, written, read and added up, and even out nothing while they run; items
-// cost what the last of them leave idle.  Both are estimated in microseconds (a step takes about 1.06 with a workgroup alone
-// on its CU, 1.95 with two; an item that shares its CU with another for s steps ends 0.65 s later; 8 are the start and a
-// first merge, 0.9 each further piece of the longest item).  Kernel us, items whole / shares (query / K/V heads, new +
-// cached tokens):
+// cost what the last of them leave idle.  Both are estimated in microseconds: a step takes about 1.06 with a workgroup alone
+// on its CU, 1.95 with two; an item that shares its CU with another for s steps ends 0.65 s later; 9 are the start, a first merge
+// and some of the 2 to 3 by which the plan takes longer, 0.9 each further piece of the longest item; and a step that no other
+// tile of its sequence reads too takes the memory 0.006, whoever computes it, beside what shares write and read in addition.
+// Of 222 random batches none takes longer by more than 3% than with whole items where the layers share a plan, 3 do (by 4%)
+// where each makes its own; without the last term 40/40 8 x 56+2506 took 99 instead of 87, and 52/52 4 x 100+3000 82 instead of 79.
+// Kernel us, items whole / shares (query / K/V heads, new + cached tokens):
 //   shares:  64/8 366+4351, 366+11326: 228 / 200    64/8 512+16000: 280 / 264     40/8 32+2000: 36 / 19    40/8 32+16000: 244 / 40
 //            40/8 3 x 300+5000: 137 / 111   8/1 5 x 293+8333: 134 / 69    8/1 8192+0: 170 / 148    8/1 2000+0: 36 / 27
 //            52/52 200+4000: 72 / 45        8/1 16 x 100+3000: 57 / 41    40/8 584 items of 170 steps, 72 of them in a second
 //            round: 427 / 370               64/8 8+30000: 445 / 48
 //   whole:   64/8 512+0: 15 / 18            64/8 512+2000: 53 / 53        32/8 4 x 749+89: 40 / 41      40/8 4 x 1024+0: 61 / 63
 //            64/8 4 x 256+2000: 79 / 84     64/8 8 x 256+8000: 513 / 525  8/1 16 x 500+500: 35 / 40     64/8 2048+0: 86 / 84
-ECO_HD int share_wgs(int n_items, int units, int heaviest, int lightest, int n_wgs) {
-  if (heaviest < kShareMinUnits || n_items <= 0 || n_wgs <= 0) return 0;
-  const float w = (float)n_wgs, u = (float)units, all = 1.95f * over(u, w);
+//            40/40 8 x 56+2506: 81 / 91
+ECO_HD int share_wgs(int n_items, int units, int heaviest, int lightest, int n_wgs, int n_seqs, int n_tiles) {
+  if (heaviest < kShareMinUnits || n_items <= 0 || n_wgs <= 0 || n_tiles <= 0) return 0;
+  const float w = (float)n_wgs, u = (float)units, read = 0.006f * u * (n_seqs < n_tiles ? over((float)n_seqs, (float)n_tiles) : 1.f);
+  const float work = 1.95f * over(u, w), all = work > read ? work : read;
   // a share is no shorter than what its merge takes: a tile of s steps then has about 0.7 sqrt(s) pieces at most
   const int least = (int)ceilf(root((float)(2 * heaviest))), most = units / (least > kShareMinUnits ? least : kShareMinUnits);
   const int n = most < 1 ? 1 : most < n_wgs ? most : n_wgs;
   const float share = over(u, (float)n);
-  const float alone = 1.06f * share, t_share = (alone > all ? alone : all) + 8.f + 0.9f * over((float)heaviest, share);
+  const float alone = 1.06f * share, t_share = (alone > all ? alone : all) + 9.f + 0.9f * over((float)heaviest, share);
   float t_items;
   if (n_items <= n_wgs) {
     // the heaviest item, beside the one of rank n_wgs / 2, which is the mean if all are alike, or about this much if not

@@ -78,8 +78,8 @@ int main() {
   }
   if (cut_items < 10000) return fail("too few cut items");
   // whole items: tiles too short to cut, full rounds of equal items, many light items; shares: one long item, a bad last round
-  if (share_wgs(32, 32 * 5, 2, 2, 512) || share_wgs(512, 512 * 53, 50, 50, 512) || share_wgs(1280, 1280 * 20, 32, 1, 512)) return fail("shares");
-  if (!share_wgs(8, 8 * 253, 250, 250, 512) || !share_wgs(584, 584LL * 171, 200, 103, 512)) return fail("no shares");
+  if (share_wgs(32, 32 * 5, 2, 2, 512, 1, 32) || share_wgs(512, 512 * 53, 50, 50, 512, 1, 512) || share_wgs(1280, 1280 * 20, 32, 1, 512, 16, 1280)) return fail("shares");
+  if (!share_wgs(8, 8 * 253, 250, 250, 512, 1, 1) || !share_wgs(584, 584 * 171, 200, 103, 512, 2, 73)) return fail("no shares");
   // every sum that the plan makes of a batch it may share fits 32 bits: at the line, and beyond it not (2047 tiles of one K/V head
   // behind 68 million cached tokens: the sum of their units wraps around)
   for (long long items : {1LL, 7LL, 512LL, 2047LL, 2048LL}) {
@@ -100,3 +100,55 @@ def test_every_key_step_is_computed_once(tmp_path):
                    check=True)
     r = subprocess.run([str(exe)], capture_output=True, text=True)
     assert r.returncode == 0 and r.stdout == "ok\n", r.stdout
+
+
+SHARED = r"""
+#include <algorithm>
+#include <cstdio>
+#include "prefill_shares.h"
+using namespace eco;
+// for each "Hq Hkv B new... cached..." line: the number of shares, from the tiles and key steps as the plan kernel finds them
+int main() {
+  int Hq, Hkv, B;
+  while (std::scanf("%d %d %d", &Hq, &Hkv, &B) == 3) {
+    int S[64], cb[64], tiles = 0, units = 0, heaviest = 0, lightest = 1 << 30, table = 0;
+    for (int b = 0; b < B; ++b)
+      if (std::scanf("%d", S + b) != 1) return 1;
+    for (int b = 0; b < B; ++b)
+      if (std::scanf("%d", cb + b) != 1) return 1;
+    const int G = Hq / Hkv;
+    for (int b = 0; b < B; ++b) {
+      const int rows = S[b] * G, r = rows % 128;
+      table = std::max(table, (S[b] + cb[b] + 63) / 64);
+      for (int last = r > 0 ? r : 128; last <= rows; last += 128, ++tiles) {
+        const int steps = (cb[b] + (last - 1) / G + 1 + 63) / 64;
+        units += steps + kItemCost;
+        heaviest = std::max(heaviest, steps);
+        lightest = std::min(lightest, steps);
+      }
+    }
+    std::printf("%d\n", may_share_steps((long long)tiles * Hkv, table, 512) ? share_wgs(tiles * Hkv, units * Hkv, heaviest, lightest, 512, B, tiles) : 0);
+  }
+}
+"""
+
+# the batches whose times stand at share_wgs, and some whose K and V no other tile reads
+FIGURES = [((64, 8), [(366, 4351), (366, 11326)], True), ((64, 8), [(512, 16000)], True), ((40, 8), [(32, 2000)], True), ((40, 8), [(32, 16000)], True),
+           ((40, 8), [(300, 5000)] * 3, True), ((8, 1), [(293, 8333)] * 5, True), ((8, 1), [(8192, 0)], True), ((8, 1), [(2000, 0)], True), ((52, 52), [(200, 4000)], True),
+           ((8, 1), [(100, 3000)] * 16, True), ((64, 8), [(8, 30000)], True), ((64, 8), [(512, 0)], False), ((64, 8), [(512, 2000)], False),
+           ((32, 8), [(749, 89)] * 4, False), ((40, 8), [(1024, 0)] * 4, False), ((64, 8), [(256, 2000)] * 4, False), ((64, 8), [(256, 8000)] * 8, False),
+           ((8, 1), [(500, 500)] * 16, False), ((64, 8), [(2048, 0)], False), ((40, 40), [(56, 2506)] * 8, False), ((52, 52), [(100, 3000)] * 4, False),
+           ((64, 8), [(1, 3000)] * 30, False), ((32, 32), [(100, 6000)] * 3, True), ((40, 8), [(20, 8000)] * 12, True)]
+
+
+def test_which_batches_are_shared_out(tmp_path):
+    """The batches of tests/test_gpu_prefill_shares.py are, or they would test nothing; those whose times stand beside the rule are where
+    it says so."""
+    from tests import test_gpu_prefill_shares as t
+    src, exe = tmp_path / "rule.cpp", tmp_path / "rule"
+    src.write_text(SHARED)
+    subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", "-I", os.path.join(ROOT, "paper_2504_18154_amd", "csrc"), str(src), "-o", str(exe)], check=True)
+    calls = [(h, s, True) for h, s in t.CASES] + [((40, 8), [(8, 4000)], True)] + FIGURES
+    text = "".join(f"{h[0]} {h[1]} {len(s)} " + " ".join(str(n) for n, _ in s) + " " + " ".join(str(c) for _, c in s) + "\n" for h, s, _ in calls)
+    out = subprocess.run([str(exe)], input=text, capture_output=True, text=True, check=True).stdout.split()
+    assert [(c, int(n) > 0) for c, n in zip(calls, out, strict=True) if (int(n) > 0) != c[2]] == []
