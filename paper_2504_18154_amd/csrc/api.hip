@@ -114,11 +114,19 @@ int alloc_fixed_workspace(ecoserve_ctx* c) {
   const size_t plan_records = listed ? (size_t)(c->plan_tiles + 1) * (c->lay.num_q_heads / c->lay.num_kv_heads) : 0;
   const size_t plan_bytes = (((size_t)kPlanHeaderInts + plan_records * kRecInts) * sizeof(int32_t) + 255) & ~(size_t)255;
   // (contexts whose sequences are too short for it never share out a batch's key steps)
-  const bool pieces = listed && (int64_t)c->max_blocks_per_seq * kBlockSize >= 64 * kShareMinUnits;
-  const size_t piece_bytes = pieces ? (size_t)prefill_piece_floats(c->num_cu * kPrefillWgsPerCu) * sizeof(float) : 0;
-  // (one allocation: plan, pieces, numbering)
-  if (hipMalloc(&c->ws_plan, plan_bytes + piece_bytes + meta_bytes) != hipSuccess) {
+  bool pieces = listed && (int64_t)c->max_blocks_per_seq * kBlockSize >= 64 * kShareMinUnits;
+  size_t piece_bytes = pieces ? (size_t)prefill_piece_floats(c->num_cu * kPrefillWgsPerCu) * sizeof(float) : 0;
+  // (one allocation: plan, pieces, numbering; without the pieces where the device has no room for them)
+  hipError_t e = hipMalloc(&c->ws_plan, plan_bytes + piece_bytes + meta_bytes);
+  if (e != hipSuccess && pieces) {
     (void)hipGetLastError();
+    pieces = false;
+    piece_bytes = 0;
+    e = hipMalloc(&c->ws_plan, plan_bytes + meta_bytes);
+  }
+  if (e != hipSuccess) {
+    (void)hipGetLastError();
+    c->ws_plan = nullptr;
     return ECOSERVE_ENOMEM;
   }
   char* const rest = reinterpret_cast<char*>(c->ws_plan) + plan_bytes;
