@@ -129,13 +129,14 @@ inline SmallDecode any_decode(int32_t B, int32_t Hkv, int32_t D, int32_t elem_by
 // second launch, which is what such a batch spends its time on in the persistent kernel.
 //   Several sequences, one of them of more than 768 tokens, and eight workgroups (one per CU) or more per five (sequence, K/V
 //   head)s: balanced slices.  Us per call before (uniform slices or the persistent kernel) / balanced: 64 query heads on 8, 16 x
-//   20..2000 tokens 18.4 / 14.5, 8 x 20..8000 19.2 / 14.6; 5 on 1, 13 x 745..5960 16.3 / 12.1; 8 on 1, 64 x 1000..8000 38.5 / 28.8; 32 on 8, 9 x
+//   20..2000 tokens 18.4 / 14.5, 8 x 20..8000 19.2 / 14.6; 8 on 1, 64 x 1000..8000 38.5 / 28.8; 32 on 8, 9 x
 //   1196..9574 35.8 / 29.0; 40 on 8, 18 x 116..935 15.6 / 14.3, 8 x 1000 16.0 / 13.9, 16 x 1000 18.9 / 18.4, 16 x 2000 29.2 / 27.8, 20 x 2000 38.9 / 32.8, 20 x
-//   100..3000 30.2 / 26.1, 15 x 1142..9140 51.8 / 51.7; 52 on 52, 2 x 1000..2000 20.7 / 21.0.  Finding the slices takes half a microsecond.  Fewer
-//   spare workgroups even out too little (24 x 1000..10000 84 / 98), and from 400 MB on the persistent kernel's stream is the
-//   faster one (16 x 8000 93 / 99; both without the non-temporal hint).
+//   100..3000 30.2 / 26.1.  Finding the slices takes half a microsecond, and just above 768 tokens a batch whose longest context
+//   is alone gains what an evenly ragged one loses (16 x 50..800 13.7 / 14.2, 15 x 50 and one of 800 12.4 / 10.0; 52 on 52, 1000 and 2000
+//   20.1 / 20.5).  Fewer spare workgroups even out too little (24 x 1000..10000 84 / 98), and from 400 MB on the persistent kernel's stream
+//   is the faster one (16 x 8000 93 / 99, both without the non-temporal hint; 15 x 1142..9140, forced, 51.8 / 51.7).
 //   No balancing where every sequence may have as many slices as one of max_ctx_len tokens gets for itself: the slices of
-//   balanced_slice_blocks for that (1 x 777: 9.4 / 8.5, 1 x 1000: 10.7 / 8.9, 1 x 16000: 21.9 / 20.8).
+//   balanced_slice_blocks for that (1 x 777: 9.4 / 8.3, 1 x 1000: 10.6 / 8.6, 1 x 16000: 21.3 / 20.9; 5 on 1, 13 x 745..5960 17.3 / 12.7).
 //   Else uniform slices if all workgroups run at once - one of eight wavefronts per CU, or (short contexts) two of four (us per call
 //   persistent / here: 16 x 1000 tokens 20.7 / 14.1; 32 x 200: 15.7 / 7.4; 64 x 500: 35.0 / 23.5); with uniform slices nothing evens out
 //   the lengths of more workgroups than fit: 128 sequences around 500 tokens, lognormal, take 62 there and 74 here, 40 of them 25
@@ -144,6 +145,8 @@ inline SmallDecode any_decode(int32_t B, int32_t Hkv, int32_t D, int32_t elem_by
 //   to 300 MB (persistent / here: 40 x 100..1000 27.2 / 24.6, 40 x 600 29.8 / 24.4, 40 x 20..2000 25.1 / 21.2, 28 x 100..3000 37.5 /
 //   33.5, 24 x 100..3000 33.0 / 30.2, 16 query heads on 4, 64 x 100..2000 31.9 / 28.3; 36 x 1500 49.0 / 49.0, 40 x 2000 65.3 / 66.1, 24 x
 //   4000 74 / 80; with nothing to spare 64 x 20..2000 33.7 / 39.2; three workgroups and more per CU 40 x 100..1000 28.5).
+//   One context too long for the first of these rules comes here too (1 x 40000 52.3 / 43.5, 1 x 75000 75.1 / 64.4; 8 on 1, 1 x 300000 226 / 60,
+//   1 x 600000, cut into 171 slices, 252 / 86; 20 on 4, 1 x 150000 91 / 77).
 inline SmallDecode small_decode(int32_t B, int32_t Hkv, int32_t max_ctx_len, int32_t num_cu) {
   const int64_t pairs = (int64_t)B * Hkv;
   const int32_t nb = (max_ctx_len + 15) / 16, slots = num_cu / Hkv;
