@@ -52,7 +52,7 @@ def test_noalloc_decode_matches_the_context_call_twice_in_a_row():
     say("noalloc decode: group size 8, one long sequence in slices, small enough for the single launch")
     _decode_both_ways(wl.ModelShape("70B-heads", 64, 8, 128, 1, "bf16"), np.array([8000, 40], dtype=np.int32), 903)
     # (34000 tokens: balanced slices; 60000: the persistent kernel, well over a hundred states per
-    # (sequence, head), so the merge of the cut ones goes through its rounds of 64; PATHS in test_decode_slices.py)
+    # (sequence, head), so the merge of the cut ones goes through its rounds of 64; test_decode_slices.py asserts both)
     for n in (34000, 60000):
         say(f"noalloc decode: group size 8, one long sequence of {n} tokens cut into many pieces")
         _decode_both_ways(wl.ModelShape("70B-heads", 64, 8, 128, 1, "bf16"), np.array([n, 40], dtype=np.int32), 870 + n // 1000)
