@@ -199,6 +199,8 @@ int ecoserve_kv_append(ecoserve_ctx* ctx, void* k_cache, void* v_cache, const vo
  *   Batches of few query tiles behind long contexts (bf16, head size 128) have the keys of a tile
  *   shared out among workgroups; partial states go through the workspace and are merged exactly,
  *   in an order that the lengths, B, T and bt_stride decide.
+ *   Batches behind short contexts (bf16, head size 128; by B, T and the tokens that bt_stride blocks
+ *   hold) need no list of query tiles and no workspace.
  *   The workspace also carries, from one launch to the next, how long each workgroup was busy and
  *   the work queues' shares (ecoserve_debug_prefill_queue_shares): they decide which workgroup
  *   computes which query tile, never a result; out and lse of a call are the same bits whatever
@@ -252,8 +254,8 @@ int ecoserve_debug_validate(ecoserve_ctx* ctx, const int32_t* cu_q, const int32_
  * Section 2.1: prefill attention is the compute-bound phase, a launch is
  * over when its slowest part is).  Which workgroup computes an item does not
  * change any result.  shares[q] == 1 for every queue while no measurement
- * applies: the first launch of a batch, batches below 3072 items, the plain
- * kernels.
+ * applies: the first launch of a batch, batches below 3072 items or behind short
+ * contexts (no queues), the plain kernels.
  *
  *   shares : host, float[8]; mean 1 over the queues
  */

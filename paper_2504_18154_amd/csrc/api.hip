@@ -11,6 +11,7 @@
 #include "common.h"
 #include "decode_slices.h"
 #include "prefill_shares.h"
+#include "prefill_short.h"
 
 using namespace eco;
 
@@ -229,6 +230,7 @@ int ecoserve_create(ecoserve_ctx** out, int device, const ecoserve_layout* layou
   c->opt_reuse_plan = 0;
   c->plan_parity = 0;
   c->plan_key.valid = false;
+  c->prefill_was_short = false;
   c->share_parity = 0;
   c->ws_share = nullptr;
   c->ws_acc = nullptr;
@@ -414,6 +416,12 @@ int ecoserve_attn_prefill_strided(ecoserve_ctx* c, const void* q, int64_t q_row_
       if (hipStreamIsCapturing(s, &cap) != hipSuccess) { (void)hipGetLastError(); return ECOSERVE_EHIP; }
       if (cap != hipStreamCaptureStatusNone) return ECOSERVE_EINVAL;
     }
+    const PrefillShort how = prefill_short(B, T, a.Hq, a.Hkv, (int64_t)bt_stride * kBlockSize, c->num_cu);
+    c->prefill_was_short = how != PrefillShort::kNo;
+    if (c->prefill_was_short) {
+      key.valid = false;  // (a list made for an earlier call is not taken up again behind one for another batch)
+      return launch_prefill_short(a, cu_q, ctx_before, T, how, s) == hipSuccess ? ECOSERVE_OK : ECOSERVE_EHIP;
+    }
     const bool same = c->opt_reuse_plan && key.valid && key.cu_q == cu_q && key.ctx_before == ctx_before &&
                       key.block_table == block_table && key.bt_stride == bt_stride && key.B == B && key.T == T &&
                       key.n_wg == grid;
@@ -548,7 +556,7 @@ int ecoserve_debug_prefill_queue_shares(ecoserve_ctx* c, float* shares) {
   const int32_t* src = c->ws_plan + kPlanShare0 + kPlanMaxQueues * (c->plan_parity ^ 1);
   if (hipMemcpy(shares, src, kPlanMaxQueues * sizeof(float), hipMemcpyDeviceToHost) != hipSuccess) return ECOSERVE_EHIP;
   for (int q = 0; q < kPlanMaxQueues; ++q)
-    if (!(shares[q] > 0.f)) shares[q] = 1.f;  // nothing launched yet
+    if (c->prefill_was_short || !(shares[q] > 0.f)) shares[q] = 1.f;  // no queues, or nothing launched yet
   return ECOSERVE_OK;
 }
 

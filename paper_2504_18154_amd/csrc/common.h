@@ -109,6 +109,7 @@ struct ecoserve_ctx {
     const int32_t *cu_q, *ctx_before, *block_table;
     int32_t bt_stride, B, T, n_wg;
   } plan_key;
+  bool prefill_was_short;      // the last prefill call took the kernel for short contexts, which has no list and no queues
   size_t ws_bytes;
   // profiling
   std::vector<eco::EventPair> ev[3];
@@ -187,6 +188,10 @@ hipError_t launch_decode_mfma(const AttnArgs& a, const int32_t* ctx_len, int32_t
 hipError_t launch_decode_mfma_merge(const AttnArgs& a, const int32_t* ctx_len, const float* ws_acc, const float* ws_ml,
                                     const int32_t* ws_meta, float* xcd_speed,
                                     const int32_t* ws_wave, const int32_t* ws_cut, int32_t n_waves, hipStream_t s);
+
+// attn_prefill_short.hip: bf16, D = 128 (prefill_short in prefill_short.h says which batches and how)
+enum class PrefillShort;
+hipError_t launch_prefill_short(const AttnArgs& a, const int32_t* cu_q, const int32_t* ctx_before, int32_t T, PrefillShort how, hipStream_t s);
 
 // attn_prefill_mfma.hip: bf16, D = 128
 // (ws_plan must hold kPlanHeaderInts + prefill_plan_tiles(B, T, G) * kRecInts int32; make_plan false: the tile list
