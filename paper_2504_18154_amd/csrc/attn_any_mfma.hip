@@ -515,6 +515,195 @@ __global__ __launch_bounds__(W * 64) void decode_any_kernel(
   }
 }
 
+// Decode of (bf16, 128) batches of short contexts (decode_short in decode_slices.h has the line, and the number of wavefronts): grid
+// (Hkv, B), the W wavefronts of a workgroup walk the blocks of one (sequence, K/V head) in turn; no numbering, no slices, nothing
+// shared between workgroups, whom the hardware hands out.  The wavefront that has the last block takes it last.  With k_new given it puts the
+// newest token into the block's registers and writes the whole V block back (see there).
+// Such a batch is the cost of a piece (the persistent kernel spends 1.2 us of a wavefront on each, and the device's start-up of 7 us once) and the
+// token's V column, which a launch of its own reads and writes sector by sector; a few sequences are round trips.  us per call with the append, the
+// kernels that had these batches / now: 40 query heads on 8, 1024 x ~103 tokens up to 800 130 / 123, 819 x 193 159 / 146, 139 x ~46 20.7 / 13.1, 112 x
+// 8 13.9 / 6.4; 32 on 8, 375 x ~18 28.6 / 15.3, 112 x 866 82.8 / 69.4; 52 on 52, 628 x 49..99 380 / 332, 23 x 63 21.3 / 13.1; 8 on 1, 1 x 180
+// 6.5 / 5.1, 1 x 14 5.6 / 3.6.  Of that, whole V blocks instead of columns: 375 x ~18 19.4 -> 15.3 (one wavefront, decode_any_kernel before).  Tried: V
+// written, or the last block read, with and without the non-temporal hint (52 on 52, 628 x 49..99 13% better with it written so, smaller ones 1 to
+// 2% worse), K written back whole as well (4% worse), eight and sixteen wavefronts (one CU takes in 24 bytes a clock, however many ask:
+// 1 x 777 tokens 10.2, 10.1, 10.9 with 4, 8, 16).
+template <int W>
+__global__ __launch_bounds__(W * 64, 3) void decode_short_kernel(
+    const uint16_t* __restrict__ q, int q_row_stride, const uint16_t* __restrict__ k_new, const uint16_t* __restrict__ v_new, int new_row_stride,
+    uint16_t* k_cache, uint16_t* v_cache, const int32_t* __restrict__ block_table, int bt_stride, const int32_t* __restrict__ ctx_len,
+    uint16_t* __restrict__ out, float* __restrict__ lse, int Hq, int Hkv, int G, float scale_log2e) {
+  typedef Block<uint16_t, 4, kNonTemporal, false> Blk;
+  constexpr int D = 128, kPiece = 16 * D * 2;
+  static_assert(W <= 8, "a wavefront adds up whole tiles");
+  __shared__ __attribute__((aligned(16))) uint16_t s_new[256];   // the newest token's K row, then its V row
+  __shared__ __attribute__((aligned(16))) char s_out[16 * 256];  // output rows: chunk c of row r at 256 r + 16 (c ^ r)
+  __shared__ __attribute__((aligned(16))) f32x4 s_acc[W > 1 ? W : 1][W > 1 ? 8 : 1][64];
+  __shared__ float s_m[W][16], s_l[W][16];
+  __shared__ int s_bad;
+  const int g = blockIdx.x, b = blockIdx.y;
+  const int tid = threadIdx.x, lane = tid & 63, wave = W > 1 ? __builtin_amdgcn_readfirstlane(tid >> 6) : 0;
+  const int col = lane & 15, quad = lane >> 4;
+  const int32_t* const bt_row = block_table + (size_t)b * bt_stride;
+  const bool fused = k_new != nullptr;
+  const int L = __builtin_amdgcn_readfirstlane(ctx_len[b]);
+  u32x2 row = {0u, 0u};  // 8 bytes per lane of (K row, V row)
+  if (fused) row = *reinterpret_cast<const u32x2*>((lane < 32 ? k_new : v_new) + (size_t)b * new_row_stride + (size_t)g * D + (lane & 31) * 4);
+  u32x4 qf[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const u32x4 z = {0u, 0u, 0u, 0u};
+    qf[j] = col < G ? *reinterpret_cast<const u32x4*>(q + (size_t)b * q_row_stride + (size_t)(g * G + col) * D + (4 * j + quad) * 8) : z;
+  }
+  if (L <= 0) return;  // (no output for an empty sequence)
+  const int nb = (L + 15) >> 4, n = (nb - wave + W - 1) / W;  // this wavefront's blocks: wave + W i, i < n
+  const bool has_last = wave + W * (n - 1) == nb - 1;
+  const char* const kc = reinterpret_cast<const char*>(k_cache) + (size_t)g * kPiece;
+  const char* const vc = reinterpret_cast<const char*>(v_cache) + (size_t)g * kPiece;
+  const size_t blk_stride = (size_t)Hkv * kPiece;
+  f32x4 acc[8];
+#pragma unroll
+  for (int dt = 0; dt < 8; ++dt) acc[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float m = -INFINITY, l = 0.f;
+  auto work = [&](const Blk& f, int tail) {
+    f32x4 s = f.scores(qf) * scale_log2e;
+    if (tail < 16) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (4 * quad + e >= tail) s[e] = -INFINITY;
+    }
+    const f32x4 p = softmax_step<false>(s, m, l, acc);
+    f.values(p, acc);
+  };
+  Blk f0;
+  for (int base = 0; base < n; base += 64) {  // (the 64 ids that a register holds: 1024 W tokens)
+    const int nw = min(64, n - base);
+    const int ids = lane < nw ? bt_row[wave + W * (base + lane)] : 0;
+    if (base == 0 && has_last && fused) {  // (kept in LDS: it was asked for before the ids, and registers are short)
+      *reinterpret_cast<u32x2*>(s_new + lane * 4) = row;
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    }
+    auto fetch = [&](Blk& f, int i) {
+      const size_t off = (size_t)__builtin_amdgcn_readlane(ids, i) * blk_stride;
+      f.load(kc + off, vc + off, kPiece, lane, col, quad);
+    };
+    // Two blocks in flight, and no branch around a load inside the loop: its waits are exact.  An even number of blocks begins with
+    // one of the other parity, so that the last block always lies in f0 and what it needs stands once.
+    Blk f1;
+    int i = 0;
+    if (nw & 1) {
+      fetch(f0, 0);
+      if (nw > 1) fetch(f1, 1);
+    } else {
+      fetch(f1, 0);
+      fetch(f0, 1);
+      work(f1, 16);
+      i = 1;
+      if (nw > 2) fetch(f1, 2);
+    }
+    for (; i + 4 < nw; i += 2) {
+      work(f0, 16);
+      fetch(f0, i + 2);
+      work(f1, 16);
+      fetch(f1, i + 3);
+    }
+    if (i + 2 < nw) {
+      work(f0, 16);
+      fetch(f0, i + 2);
+      work(f1, 16);
+    }
+    int tail = 16;
+    if (base + 64 >= n && has_last) {  // f0 is the sequence's last block
+      tail = L - 16 * (nb - 1);
+      if (fused) {
+        f0.put_token(s_new, s_new + D, tail - 1, D, col, quad);
+        // K: 16 bytes in each of 16 places.  V: a token is 128 places of two bytes, which the memory reads and writes 64 bytes at a
+        // time; the whole block, which is in the registers, goes back in whole lines instead, and nothing is read for it.  (Nobody else
+        // in the launch reads or writes this piece; slots behind the end keep what they hold.)
+        const size_t off = (size_t)__builtin_amdgcn_readlane(ids, nw - 1) * blk_stride;
+        char* const kd = const_cast<char*>(kc) + off;
+        char* const vd = const_cast<char*>(vc) + off;
+        int ln = lane;
+        asm volatile("" : "+v"(ln));  // (where the lane writes is worked out here, not kept through the walk)
+        if (ln < 16) *reinterpret_cast<u32x4*>(kd + ln * 256 + (tail - 1) * 16) = *reinterpret_cast<const u32x4*>(s_new + ln * 8);
+#pragma unroll
+        for (int dt = 0; dt < 8; ++dt) *reinterpret_cast<s16x4*>(vd + (ln & 15) * 32 + (ln >> 4) * 8 + dt * 512) = f0.v[dt];
+      }
+      if (tail < 16) f0.clear_tail(tail, quad);
+    }
+    work(f0, tail);
+  }
+  l += __shfl_xor(l, 16);
+  l += __shfl_xor(l, 32);
+  // Lanes (col = head, quad) hold o[16 dt + 4 quad ..].  Through LDS into whole rows; with several wavefronts each adds up the states of
+  // 8 / W tiles:   M = max_w m_w;  l = sum_w l_w 2^(m_w - M);  o = sum_w o_w 2^(m_w - M) / l.
+  float zero = 0.f;  // (not a number if an element is not finite)
+  auto to_rows = [&](const f32x4& v, int dt, float inv) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) zero = __builtin_fmaf(v[e], 0.f, zero);
+    const u32x2 w = {pack_bf16x2(v[0] * inv, v[1] * inv), pack_bf16x2(v[2] * inv, v[3] * inv)};
+    *reinterpret_cast<u32x2*>(s_out + col * 256 + ((2 * dt + (quad >> 1)) ^ col) * 16 + (quad & 1) * 8) = w;
+  };
+  bool bad;
+  if constexpr (W > 1) {
+    constexpr int kOwn = 8 / W;  // tiles of a wavefront
+    if (quad == 0) {
+      s_m[wave][col] = m;
+      s_l[wave][col] = l;
+    }
+#pragma unroll
+    for (int dt = 0; dt < 8; ++dt) s_acc[wave][dt][lane] = acc[dt];
+    if (tid == 0) s_bad = 0;
+    __syncthreads();
+    float M = s_m[0][col];
+#pragma unroll
+    for (int w = 1; w < W; ++w) M = fmaxf(M, s_m[w][col]);
+    float total = 0.f;
+    f32x4 sum[kOwn];
+#pragma unroll
+    for (int t = 0; t < kOwn; ++t) sum[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int dt0 = wave * kOwn;
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+      const float mw = s_m[w][col], wk = mw == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mw - M);
+      total += s_l[w][col] * (mw == -INFINITY ? 1.f : wk);
+#pragma unroll
+      for (int t = 0; t < kOwn; ++t) sum[t] += s_acc[w][dt0 + t][lane] * wk;
+    }
+    const float inv = 1.f / total;
+#pragma unroll
+    for (int t = 0; t < kOwn; ++t) to_rows(sum[t], dt0 + t, inv);
+    if (zero != zero && col < G && total == total) s_bad = 1;
+    m = M;
+    l = total;
+    __syncthreads();
+    bad = s_bad != 0;
+  } else {
+    const float inv = 1.f / l;
+#pragma unroll
+    for (int dt = 0; dt < 8; ++dt) to_rows(acc[dt], dt, inv);
+    bad = __any(zero != zero && col < G && l == l);
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  }
+  const size_t row0 = (size_t)b * Hq + (size_t)g * G;
+  for (int r = wave * 4 + quad; r < G; r += 4 * W)
+    *reinterpret_cast<u32x4*>(out + (row0 + r) * D + col * 8) = *reinterpret_cast<const u32x4*>(s_out + r * 256 + (col ^ r) * 16);
+  if (lse && wave == 0 && lane < G) lse[row0 + lane] = (m + log2f(l)) * kLn2;
+  if (bad) {  // (see attend_row)
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();  // (the newest token is in the cache)
+    for (int h = wave; h < G; h += W) {
+      float rm, rl, o[4];
+      attend_row<uint16_t>(q + (size_t)b * q_row_stride + (size_t)(g * G + h) * D, k_cache, v_cache, bt_row, g, Hkv, D, 0, L, scale_log2e, rm, rl, o);
+#pragma unroll
+      for (int r = 0; r < 2; ++r) Elem<uint16_t>::store(out + (row0 + h) * D + lane + 64 * r, o[r] / rl);
+    }
+  }
+}
+
 // Prefill.  The rows of one (sequence, K/V head) are (position, query head of the group) pairs, position-major:
 // row r = position r / G, head r % G, so the 16 columns of a product cover few positions and the causal bound cuts
 // close.  Two ways to share the work in a workgroup of four wavefronts:
@@ -769,7 +958,7 @@ void launch_decode_typed(const AttnArgs& a, const int32_t* ctx_len, int32_t spli
         // (non-temporal: a batch of several long contexts comes from memory, layer after layer: 16 x 20..2000 tokens 15.7 us without the
         // hint and 14.5 with it, 16 x 2000 30.5 and 27.8, 9 x 1196..9574 32.2 and 29.0; a single one may still be in the last-level cache)
         return many ? launch(decode_any_kernel<E, KS, 4, kNonTemporal, false, true>, 4) : launch(decode_any_kernel<E, KS, W, kNonTemporal, false, true>, W);
-      if (a.D == 128) return many ? launch(decode_any_kernel<E, KS, 4, kNonTemporal, false>, 4) : launch(decode_any_kernel<E, KS, W, 0, false>, W);
+      if (a.D == 128) return launch(decode_any_kernel<E, KS, W, 0, false>, W);
       if (many) return launch(decode_any_kernel<E, KS, 4, kNonTemporal>, 4);
     }
     launch(decode_any_kernel<E, KS, W>, W);
@@ -782,6 +971,16 @@ hipError_t launch_prefill_any(const AttnArgs& a, const int32_t* cu_q, const int3
   if (a.dtype == ECOSERVE_BF16) launch_prefill_typed<uint16_t>(a, cu_q, ctx_before, T, s);
   else launch_prefill_typed<float>(a, cu_q, ctx_before, T, s);
   return hipGetLastError();
+}
+
+hipError_t launch_decode_short(const AttnArgs& a, const int32_t* ctx_len, int32_t waves, hipStream_t s) {
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)a.Hkv, (unsigned)a.B), dim3(waves * 64), 0, s, (const uint16_t*)a.q, a.q_row_stride, (const uint16_t*)a.k_new,
+                       (const uint16_t*)a.v_new, a.new_row_stride, (uint16_t*)const_cast<void*>(a.k_cache), (uint16_t*)const_cast<void*>(a.v_cache),
+                       a.block_table, a.bt_stride, ctx_len, (uint16_t*)a.out, a.lse, a.Hq, a.Hkv, a.Hq / a.Hkv, a.scale_log2e);
+    return hipGetLastError();
+  };
+  return waves == 1 ? launch(decode_short_kernel<1>) : waves == 2 ? launch(decode_short_kernel<2>) : waves == 4 ? launch(decode_short_kernel<4>) : hipErrorInvalidValue;
 }
 
 hipError_t launch_decode_any(const AttnArgs& a, const int32_t* ctx_len, int32_t split_tokens, int32_t n_split_max, float* ws_acc,

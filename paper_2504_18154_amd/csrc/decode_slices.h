@@ -125,7 +125,24 @@ inline SmallDecode any_decode(int32_t B, int32_t Hkv, int32_t D, int32_t elem_by
   return {uniform, n_uniform};
 }
 
-// For (bf16, 128): how this kernel takes a small batch, n_split 0 if it does not.  It needs no numbering of the batch and no
+// For (bf16, 128): wavefronts per (sequence, K/V head) with which decode_short_kernel takes a batch whole, 0 if it does not.
+//   Few (sequence, K/V head)s: up to where contexts cut into slices, or eight wavefronts to a context, end sooner (us there / here: 1 x 496
+// tokens, 8 K/V heads, 8.0 / 6.9, 2 x 458 8.1 / 8.5; 7 x 204 7.5 / 6.4; 26 x 259, 8 heads, 7.7 / 7.2, 18 x 479 9.2 / 9.9).
+//   More than fit one workgroup of eight wavefronts per CU: up to 640 tokens (52 x 566, 8 heads, 33.0 / 24.1, 36 x 700 16.9 / 16.6, 33 x 1098
+// 16.7 / 17.7), and beyond one and a half per CU, where slices no longer help and the persistent kernel is no faster at any length, until the
+// longest context's walk, 0.07 us a block of four wavefronts, stands out (79 x 1106, 8 heads, 76 / 62, 137 x up to 2072 156 / 153, 517 x up to
+// 1421 311 / 317; 789 x 467 301 / 291).
+//   One wavefront is the cheapest for contexts of two blocks, two for those of six, and for longer ones while there are
+// workgroups enough (112 x 866 tokens 67.4, with four 69.4; 325 x 226 29.3 / 30.0).
+//   Of 700 random batches up to 3000 tokens 564 go here, 0.72 of the time on average, 0.97 at most.
+inline int32_t decode_short(int32_t B, int32_t Hkv, int32_t max_ctx_len, int32_t num_cu) {
+  const int64_t pairs = (int64_t)B * Hkv, cu = num_cu;
+  const int32_t most = 32 * pairs <= cu ? 512 : 4 * pairs <= cu ? 384 : pairs <= cu ? 320 : 2 * pairs <= 3 * cu ? 640 : pairs <= 4 * cu ? 1152 : 1024;
+  if (max_ctx_len > most) return 0;
+  return max_ctx_len <= 32 ? 1 : max_ctx_len <= (pairs > 2 * cu ? 384 : 96) ? 2 : 4;
+}
+
+// For (bf16, 128), batches that decode_short leaves: how decode_any_kernel takes a small one, n_split 0 if it does not.  It needs no numbering of the batch and no
 // second launch, which is what such a batch spends its time on in the persistent kernel.
 //   Several sequences, one of them of more than 768 tokens, and eight workgroups (one per CU) or more per five (sequence, K/V
 //   head)s: balanced slices.  Us per call before (uniform slices or the persistent kernel) / balanced: 64 query heads on 8, 16 x
@@ -137,10 +154,8 @@ inline SmallDecode any_decode(int32_t B, int32_t Hkv, int32_t D, int32_t elem_by
 //   is the faster one (16 x 8000 93 / 99, both without the non-temporal hint; 15 x 1142..9140, forced, 51.8 / 51.7).
 //   No balancing where every sequence may have as many slices as one of max_ctx_len tokens gets for itself: the slices of
 //   balanced_slice_blocks for that (1 x 777: 9.4 / 8.3, 1 x 1000: 10.6 / 8.6, 1 x 16000: 21.3 / 20.9; 5 on 1, 13 x 745..5960 17.3 / 12.7).
-//   Else uniform slices if all workgroups run at once - one of eight wavefronts per CU, or (short contexts) two of four (us per call
-//   persistent / here: 16 x 1000 tokens 20.7 / 14.1; 32 x 200: 15.7 / 7.4; 64 x 500: 35.0 / 23.5); with uniform slices nothing evens out
-//   the lengths of more workgroups than fit: 128 sequences around 500 tokens, lognormal, take 62 there and 74 here, 40 of them 25
-//   and 28 (128 of 500 each: 54 and 50).
+//   Else uniform slices if all workgroups run at once, one of eight wavefronts per CU (us per call persistent / here: 16 x 1000
+//   tokens 20.7 / 14.1).
 //   Else balanced slices for two workgroups of four wavefronts per CU, all of which run at once too, with as many to spare, up
 //   to 300 MB (persistent / here: 40 x 100..1000 27.2 / 24.6, 40 x 600 29.8 / 24.4, 40 x 20..2000 25.1 / 21.2, 28 x 100..3000 37.5 /
 //   33.5, 24 x 100..3000 33.0 / 30.2, 16 query heads on 4, 64 x 100..2000 31.9 / 28.3; 36 x 1500 49.0 / 49.0, 40 x 2000 65.3 / 66.1, 24 x
@@ -158,7 +173,7 @@ inline SmallDecode small_decode(int32_t B, int32_t Hkv, int32_t max_ctx_len, int
   }
   if (B > 1 && B <= 64 && nb > 48 && 8 * B <= 5 * slots && pairs * max_ctx_len <= 800000) return {0, slots};
   const int32_t st = decode_any_split_tokens(B, Hkv, max_ctx_len, num_cu), n = (max_ctx_len + st - 1) / st;
-  if (pairs * n <= num_cu || (max_ctx_len <= 512 && pairs <= 2 * num_cu)) return {st, n};
+  if (pairs * n <= num_cu) return {st, n};
   const int32_t slots2 = 2 * num_cu / Hkv;
   if (B <= 64 && 8 * B <= 5 * slots2 && pairs * max_ctx_len <= 600000) return {0, slots2};
   return {0, 0};
