@@ -1,7 +1,9 @@
-"""Thin ctypes binding of the C ABI in include/ecoserve.h.
+"""Thin binding of the C ABI in include/ecoserve.h.
 
 Argument marshalling only: every step of the hot path runs in the HIP kernels of
 libecoserve.so.  PyTorch tensors provide device memory and the current HIP stream.
+The hot calls' arguments are marshalled in C++ (csrc/bind.cpp) where they are what they
+usually are, tensors and small integers, and through ctypes where they are anything else.
 Importing this module without a built library raises: there is no fallback.
 """
 from __future__ import annotations
@@ -84,6 +86,14 @@ def _load(path: str = LIB_PATH) -> ctypes.CDLL:
 
 
 _lib = _load()
+try:
+    from . import _bind as _fast
+except ImportError as e:
+    raise ImportError(f"{os.path.join(_HERE, '_bind.so')} is missing or does not fit the installed torch: build it with "
+                      "`python -m paper_2504_18154_amd.build` (there is no fallback path)") from e
+_fast.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (_lib.ecoserve_kv_append_strided, _lib.ecoserve_attn_prefill_strided,
+                                                             _lib.ecoserve_attn_decode_strided, _lib.ecoserve_attn_decode_append,
+                                                             _lib.ecoserve_attn_decode_noalloc)))
 
 
 def strerror(status: int) -> str:
@@ -137,10 +147,9 @@ def probe_mfma_valu(with_mfma: bool, fma_per_slot: int, exp_per_slot: int, waves
     return clocks.value, ghz.value
 
 
-# A hot call on a small batch keeps the GPU busy for 6 to 10 us, less than the marshalling of its arguments used to take
-# (11 us for attn_decode_append: 7 of them four times _row_stride, a Python call into the tensor per dimension).  So:
-# addresses go to ctypes as plain integers, a tensor is asked once for all its strides, and the stream's handle comes
-# without a Stream object around it.
+# A hot call on a small batch keeps the GPU busy for 4 to 8 us, and its way through ctypes takes the host 6 to 7, launch included
+# (through _bind 3.5).  Each call below therefore asks _bind first, whose answer is the status, or -1 for arguments that it
+# leaves to the lines that follow.
 def _ptr(t):
     return t.data_ptr() if t is not None else None
 
@@ -148,6 +157,10 @@ def _ptr(t):
 def attn_decode_noalloc(layout: Layout, q, k_cache, v_cache, block_table, ctx_len, out, max_ctx_len, lse=None,
                         device: int = 0) -> int:
     """ecoserve_attn_decode without a context and without any allocation; returns the status code."""
+    if type(layout) is Layout:
+        status = _fast.attn_decode_noalloc(device, ctypes.addressof(layout), q, k_cache, v_cache, block_table, ctx_len, out, max_ctx_len, lse)
+        if status >= 0:
+            return status
     return int(_lib.ecoserve_attn_decode_noalloc(int(device), ctypes.byref(layout), _ptr(q), _ptr(k_cache),
                                                  _ptr(v_cache), _ptr(block_table), block_table.shape[1],
                                                  _ptr(ctx_len), _ptr(out), _ptr(lse), ctx_len.numel(),
@@ -185,11 +198,13 @@ class Context:
         self._h = ctypes.c_void_p()
         _check(_lib.ecoserve_create(ctypes.byref(self._h), int(device), ctypes.byref(self.layout), int(max_batch),
                                     int(max_blocks_per_seq)), "ecoserve_create")
+        self._address = self._h.value
+        self._q_row, self._kv_row = self.layout.num_q_heads * self.layout.head_dim, self.layout.num_kv_heads * self.layout.head_dim
 
     def close(self):
         if getattr(self, "_h", None):
             _lib.ecoserve_destroy(self._h)
-            self._h = None
+            self._h = self._address = None
 
     __del__ = close
 
@@ -229,6 +244,9 @@ class Context:
 
     # ---- the three hot calls -------------------------------------------------------------
     def kv_append(self, k_cache, v_cache, k_new, v_new, cu_q, ctx_before, block_table, max_new_len=None):
+        status = _fast.kv_append(self._address, k_cache, v_cache, k_new, v_new, cu_q, ctx_before, block_table, max_new_len, self._kv_row)
+        if status >= 0:
+            return _check(status, "ecoserve_kv_append")
         B = ctx_before.numel()
         T = k_new.shape[0]
         if max_new_len is None:
@@ -238,6 +256,9 @@ class Context:
                                        T, int(max_new_len), _stream()), "ecoserve_kv_append")
 
     def attn_prefill(self, q, k_cache, v_cache, cu_q, ctx_before, block_table, out, lse=None, max_q_len=None):
+        status = _fast.attn_prefill(self._address, q, k_cache, v_cache, cu_q, ctx_before, block_table, out, lse, max_q_len, self._q_row)
+        if status >= 0:
+            return _check(status, "ecoserve_attn_prefill")
         B = ctx_before.numel()
         T = q.shape[0]
         if max_q_len is None:
@@ -249,6 +270,9 @@ class Context:
 
     # the same on views into wider rows (e.g. slices of a fused projection output [T, Hq + 2 Hkv, D])
     def kv_append_strided(self, k_cache, v_cache, k_new, v_new, cu_q, ctx_before, block_table, max_new_len=None):
+        status = _fast.kv_append(self._address, k_cache, v_cache, k_new, v_new, cu_q, ctx_before, block_table, max_new_len, 0)
+        if status >= 0:
+            return _check(status, "ecoserve_kv_append_strided")
         B = ctx_before.numel()
         T = k_new.shape[0]
         if max_new_len is None:
@@ -263,6 +287,9 @@ class Context:
 
     def attn_prefill_strided(self, q, k_cache, v_cache, cu_q, ctx_before, block_table, out, lse=None,
                              max_q_len=None):
+        status = _fast.attn_prefill(self._address, q, k_cache, v_cache, cu_q, ctx_before, block_table, out, lse, max_q_len, 0)
+        if status >= 0:
+            return _check(status, "ecoserve_attn_prefill_strided")
         B = ctx_before.numel()
         T = q.shape[0]
         if max_q_len is None:
@@ -273,6 +300,9 @@ class Context:
                                                   int(max_q_len), _stream()), "ecoserve_attn_prefill_strided")
 
     def attn_decode_strided(self, q, k_cache, v_cache, block_table, ctx_len, out, max_ctx_len, lse=None):
+        status = _fast.attn_decode(self._address, q, k_cache, v_cache, block_table, ctx_len, out, max_ctx_len, lse, 0)
+        if status >= 0:
+            return _check(status, "ecoserve_attn_decode_strided")
         B = ctx_len.numel()
         _check(_lib.ecoserve_attn_decode_strided(self._h, _ptr(q), _row_stride(q), _ptr(k_cache), _ptr(v_cache),
                                                  _ptr(block_table), block_table.shape[1], _ptr(ctx_len),
@@ -281,6 +311,9 @@ class Context:
 
     def attn_decode_append(self, q, k_new, v_new, k_cache, v_cache, block_table, ctx_len, out, max_ctx_len, lse=None):
         """Decode with the append of the step's one new token per sequence fused in (ctx_len counts it)."""
+        status = _fast.attn_decode_append(self._address, q, k_new, v_new, k_cache, v_cache, block_table, ctx_len, out, max_ctx_len, lse)
+        if status >= 0:
+            return _check(status, "ecoserve_attn_decode_append")
         B = ctx_len.numel()
         new_stride = _row_stride(k_new)
         if new_stride != _row_stride(v_new):
@@ -291,6 +324,9 @@ class Context:
                                                 int(max_ctx_len), _stream()), "ecoserve_attn_decode_append")
 
     def attn_decode(self, q, k_cache, v_cache, block_table, ctx_len, out, max_ctx_len, lse=None):
+        status = _fast.attn_decode(self._address, q, k_cache, v_cache, block_table, ctx_len, out, max_ctx_len, lse, self._q_row)
+        if status >= 0:
+            return _check(status, "ecoserve_attn_decode")
         B = ctx_len.numel()
         _check(_lib.ecoserve_attn_decode(self._h, _ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(block_table),
                                          block_table.shape[1], _ptr(ctx_len), _ptr(out), _ptr(lse), B,

@@ -1,4 +1,5 @@
-"""Compile csrc/*.hip for gfx950 into paper_2504_18154_amd/libecoserve.so (in-tree).
+"""Compile csrc/*.hip for gfx950 into paper_2504_18154_amd/libecoserve.so, and csrc/bind.cpp (the binding's marshalling, against the
+installed torch) into paper_2504_18154_amd/_bind.so (in-tree).
 
     python -m paper_2504_18154_amd.build [--force]
 
@@ -9,12 +10,14 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libecoserve.so")
+BIND = os.path.join(HERE, "_bind.so")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 
 SOURCES = ["api.hip", "kv_append.hip", "attn_plain.hip", "attn_any_mfma.hip", "attn_decode_mfma.hip", "decode_noalloc.hip", "attn_prefill_mfma.hip", "attn_prefill_short.hip", "probes.hip", "padg.hip"]
@@ -36,7 +39,23 @@ def _deps_mtime() -> float:
 
 
 def is_current() -> bool:
-    return os.path.exists(LIB) and os.path.getmtime(LIB) >= _deps_mtime()
+    return all(os.path.exists(p) and os.path.getmtime(p) >= _deps_mtime() for p in (LIB, BIND))
+
+
+def _build_bind() -> None:
+    import torch
+    root = os.path.dirname(torch.__file__)
+    rocm = os.path.dirname(os.path.dirname(os.path.realpath(_hipcc()))) if os.path.isabs(_hipcc()) else "/opt/rocm"
+    includes = [os.path.join(root, "include"), os.path.join(root, "include", "torch", "csrc", "api", "include"), os.path.join(rocm, "include"),
+                sysconfig.get_paths()["include"]]
+    abi = f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"
+    libs = os.path.join(root, "lib")
+    cmd = [os.environ.get("CXX") or "g++", "-std=c++17", "-O2", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", abi,
+           *(a for i in includes for a in ("-isystem", i)), os.path.join(CSRC, "bind.cpp"), "-o", BIND, "-L", libs, "-ltorch_python", "-ltorch_cpu", "-lc10",
+           "-lc10_hip", f"-Wl,-rpath,{libs}"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"{cmd[0]} failed on bind.cpp:\n{r.stderr}")
 
 
 def build(force: bool = False, verbose: bool = True) -> str:
@@ -57,8 +76,10 @@ def build(force: bool = False, verbose: bool = True) -> str:
             print(err, file=sys.stderr)
         return obj
 
-    with ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
+    with ThreadPoolExecutor(max_workers=min(8, len(SOURCES) + 1)) as ex:
+        bind = ex.submit(_build_bind)
         objs = list(ex.map(compile_one, SOURCES))
+        bind.result()
     cmd = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
