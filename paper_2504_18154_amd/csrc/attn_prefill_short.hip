@@ -59,9 +59,14 @@ __global__ __launch_bounds__(kWaves * 64, kWaves > 1 || NC > 1 ? 2 : 3) void pre
   const int col = lane & 31, half = lane >> 5;
   const float c = scale_log2e;
 
-  // Workgroup w is K/V head w % Hkv of tile n_tiles - 1 - w / Hkv: later tiles of a sequence are longer and go first, and with eight
-  // K/V heads a head stays with one XCD, whose cache then holds what its tiles share.
-  const int unit = fast_div((int)blockIdx.x, div_hkv), tile_no = n_tiles - 1 - unit, g = (int)blockIdx.x - unit * Hkv;
+  // Unit w is K/V head w % Hkv of tile n_tiles - 1 - w / Hkv: later tiles of a sequence are longer and go first.  Workgroups go to the
+  // XCDs in turn.  With eight K/V heads, unit for workgroup, a head stays with one XCD, whose cache then holds what its tiles share; with fewer
+  // than eight an XCD takes eight units in a row out of 64, the tiles of a sequence or two (us in turn / in a row: 8 on 1, 250 x 25 tokens behind
+  // 43..86 19.5 / 15.2, 366 x 15 behind up to 113 14.9 / 11.8, 5 on 1, 414 x 26 13.0 / 10.4, 76 x 24 behind ~260, keys shared, 12.0 / 9.6; 223 batches
+  // of 8 on 1 and 5 on 1: 32 rows 0.94 of the time, 64 rows and keys shared 0.965, the worst 1.08 of 4 us).
+  int w = blockIdx.x;
+  if (Hkv < 8 && w < (int)(gridDim.x & ~63u)) w = (w & ~63) | (w & 7) << 3 | (w >> 3 & 7);
+  const int unit = fast_div(w, div_hkv), tile_no = n_tiles - 1 - unit, g = w - unit * Hkv;
   auto first_tile = [&](int cu, int b) { return (long long)cu * G / kRows + b; };
   const SeqOf seq = find_sequence(cu_q, ctx_before, B, tile_no, first_tile);
   const int tok0 = seq.tok0, cb = seq.cb, L = cb + seq.S, n_rows = seq.S * G;

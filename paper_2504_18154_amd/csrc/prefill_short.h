@@ -21,7 +21,7 @@ constexpr int64_t kShortMostKeys = 1024;  // a wavefront's walk: the 64 block id
 // Keys are shared while all workgroups run at once, two per CU (to 1.25 times that many: 1 x 381 tokens, 52 heads, 13.6 there, 11.9
 // here; 1 x 569, 64 on 8, 18.1 / 18.6), and while a walk of a quarter of the keys is no longer than what the persistent kernel takes with
 // its key steps shared out (40 on 8, us there / here: 32 + 500 tokens 15.4 / 7.8, 67 + 960 23.8 / 12.3, 32 + 2000 19.2 / 14.4, but 32 + 5300
-// 27.6 / 39.8; 8 on 1, 17 x 20 + 2800 22.5 / 24.7).  Contexts of one group of 32 keys have none to share (16 tokens 4.4 against 4.2).
+// 27.6 / 39.8; 8 on 1, 17 x 20 + 2800 22.5 / 24.7; half that where the tiles of a head do not stay with one XCD: 52 on 52, 3 x 66 + 1350 32.3 / 42.2).  Contexts of one group of 32 keys have none to share (16 tokens 4.4 against 4.2).
 //   Rows: no list and no change of tiles, but K and V come once per 32 or 64 rows through the first-level cache, where the
 // persistent kernel reads them once per 128 through LDS: the longer the contexts and the fewer the wavefronts, the sooner it wins.
 // The line, a context against the cube root of the number of tiles, from 320 random batches (there / here): 52 heads, 128 x 22 tokens 114 / 55,
@@ -34,7 +34,7 @@ inline PrefillShort prefill_short(int64_t B, int64_t T, int64_t Hq, int64_t Hkv,
   const int64_t tiles = (T * (Hq / Hkv) / 32 + B) * Hkv, wgs = 2 * num_cu;  // tiles of 32 rows, upper bound
   if (tiles >= (int64_t)1 << 30) return PrefillShort::kNo;
   if (max_ctx <= 32) return PrefillShort::kRows32;
-  if (tiles <= wgs && max_ctx <= 2 * kShortMostKeys) return PrefillShort::kSplitKeys;
+  if (tiles <= wgs && max_ctx <= (Hkv < 8 || Hkv % 8 == 0 ? 2 : 1) * kShortMostKeys) return PrefillShort::kSplitKeys;
   if (max_ctx <= kShortMostKeys && max_ctx * max_ctx * max_ctx <= 6750 * 256 / num_cu * tiles)
     return tiles >= 12 * num_cu && max_ctx > 96 ? PrefillShort::kRows64 : PrefillShort::kRows32;
   if (max_ctx <= kShortMostKeys && 4 * tiles <= 5 * wgs) return PrefillShort::kSplitKeys;
