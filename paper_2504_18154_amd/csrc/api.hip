@@ -509,7 +509,7 @@ static int decode_impl(ecoserve_ctx* c, const void* q, int64_t q_row_stride, con
   const bool automatic = !c->opt_force_plain && c->opt_split_tokens == 0;
   if (const int32_t waves = automatic && use_mfma(c) ? decode_short(B, a.Hkv, max_ctx_len, c->num_cu) : 0) {
     ProfileScope prof(c, ECOSERVE_KERNEL_DECODE, s);
-    e = launch_decode_short(a, ctx_len, waves, s);
+    e = launch_decode_short(a, ctx_len, waves, max_ctx_len, c->num_cu, s);
     return e == hipSuccess ? ECOSERVE_OK : ECOSERVE_EHIP;
   }
   const SmallDecode small = !automatic   ? SmallDecode{0, 0}

@@ -515,23 +515,30 @@ __global__ __launch_bounds__(W * 64) void decode_any_kernel(
   }
 }
 
-// Decode of (bf16, 128) batches of short contexts (decode_short in decode_slices.h has the line, and the number of wavefronts): grid
-// (Hkv, B), the W wavefronts of a workgroup walk the blocks of one (sequence, K/V head) in turn; no numbering, no slices, nothing
+// Decode of (bf16, 128), whole contexts (decode_short in decode_slices.h has the line, and the number of wavefronts): the W wavefronts of a
+// workgroup walk the blocks of one (sequence, K/V head) in turn; no numbering, no slices, nothing
 // shared between workgroups, whom the hardware hands out.  The wavefront that has the last block takes it last.  With k_new given it puts the
-// newest token into the block's registers and writes the whole V block back (see there).
-// Such a batch is the cost of a piece (the persistent kernel spends 1.2 us of a wavefront on each, and the device's start-up of 7 us once) and the
-// token's V column, which a launch of its own reads and writes sector by sector; a few sequences are round trips.  us per call with the append, the
-// kernels that had these batches / now: 40 query heads on 8, 1024 x ~103 tokens up to 800 130 / 123, 819 x 193 159 / 146, 139 x ~46 20.7 / 13.1, 112 x
+// newest token into the block's registers and writes the block's V whole, and of its K whole lines, back (see there).
+// Small batches are round trips; large ones are bound by memory and by what still runs when the rest is done.  Hence ORDERED, for batches of more
+// workgroups than run at once: grid (K/V heads, groups of up to 64 sequences, rank), and the workgroup takes the sequence of its rank in its group, by
+// length (in 16 classes of 2^shift tokens), longest first.  A wavefront finds it among its lanes' 64 lengths with four ballots (0.2 to 1 us
+// of a launch, which is why a batch that starts all at once, or has little to gain, does without: the grid is (K/V heads, B) then).
+// us per call with the append, in the order of the batch / longest first: 40 query heads on 8, 1024 x ~103 tokens up to 800, one
+// wavefront 124 / 100, 2 wavefronts 116 / 102, 4 117 / 110; 512 x 20..600 133 / 121; 128 x 512..4096 (4 wavefronts) 217 / 194, where the persistent kernel and
+// its merge take 203; 8 on 1, 1024 x 8..600 39 / 34; 32 on 8, 152 x ~412 up to 1391 62 / 51 (persistent 65).
+// What the persistent kernel spends on such batches: 1.2 us of a wavefront on a piece, a start-up of 7 us, and a second launch for the V columns.
+// us per call, the kernels that had these batches / without order: 40 on 8, 819 x 193 159 / 146, 139 x ~46 20.7 / 13.1, 112 x
 // 8 13.9 / 6.4; 32 on 8, 375 x ~18 28.6 / 15.3, 112 x 866 82.8 / 69.4; 52 on 52, 628 x 49..99 380 / 332, 23 x 63 21.3 / 13.1; 8 on 1, 1 x 180
-// 6.5 / 5.1, 1 x 14 5.6 / 3.6.  Of that, whole V blocks instead of columns: 375 x ~18 19.4 -> 15.3 (one wavefront, decode_any_kernel before).  Tried: V
-// written, or the last block read, with and without the non-temporal hint (52 on 52, 628 x 49..99 13% better with it written so, smaller ones 1 to
-// 2% worse), K written back whole as well (4% worse), eight and sixteen wavefronts (one CU takes in 24 bytes a clock, however many ask:
-// 1 x 777 tokens 10.2, 10.1, 10.9 with 4, 8, 16).
-template <int W>
+// 6.5 / 5.1, 1 x 14 5.6 / 3.6.  Of that, whole V blocks instead of columns: 375 x ~18 19.4 -> 15.3 (one wavefront, decode_any_kernel before).  Tried:
+// the last block read with the non-temporal hint or without, all of the block's K written back (4% worse than 16 bytes a unit), eight and
+// sixteen wavefronts (one CU takes in 24 bytes a clock, however many ask: 1 x 777 tokens 10.2, 10.1, 10.9 with 4, 8, 16), fewer workgroups
+// on a CU at a time (1024 x ~103: 118 with six, 124 with four, 160 with two).
+template <int W, bool ORDERED>
 __global__ __launch_bounds__(W * 64, 3) void decode_short_kernel(
     const uint16_t* __restrict__ q, int q_row_stride, const uint16_t* __restrict__ k_new, const uint16_t* __restrict__ v_new, int new_row_stride,
     uint16_t* k_cache, uint16_t* v_cache, const int32_t* __restrict__ block_table, int bt_stride, const int32_t* __restrict__ ctx_len,
-    uint16_t* __restrict__ out, float* __restrict__ lse, int Hq, int Hkv, int G, float scale_log2e) {
+    uint16_t* __restrict__ out, float* __restrict__ lse, int Hq, int Hkv, int G, float scale_log2e, int B,
+    int per_group, int shift, int stream) {
   typedef Block<uint16_t, 4, kNonTemporal, false> Blk;
   constexpr int D = 128, kPiece = 16 * D * 2;
   static_assert(W <= 8, "a wavefront adds up whole tiles");
@@ -540,12 +547,33 @@ __global__ __launch_bounds__(W * 64, 3) void decode_short_kernel(
   __shared__ __attribute__((aligned(16))) f32x4 s_acc[W > 1 ? W : 1][W > 1 ? 8 : 1][64];
   __shared__ float s_m[W][16], s_l[W][16];
   __shared__ int s_bad;
-  const int g = blockIdx.x, b = blockIdx.y;
+  const int g = blockIdx.x;
   const int tid = threadIdx.x, lane = tid & 63, wave = W > 1 ? __builtin_amdgcn_readfirstlane(tid >> 6) : 0;
   const int col = lane & 15, quad = lane >> 4;
+  int b = blockIdx.y, L;
+  if constexpr (ORDERED) {
+    const int first = b * per_group, have = min(per_group, B - first);
+    int r = blockIdx.z;
+    if (r >= have) return;
+    const int len = lane < have ? ctx_len[first + lane] : 0, key = min(len >> shift, 15);
+    // `left`: the lanes among which the one of rank r still is; a bit of the key at a time, those that have it come first
+    unsigned long long left = ~0ull >> (64 - have);
+#pragma unroll
+    for (int bit = 8; bit > 0; bit >>= 1) {
+      const unsigned long long ones = __ballot((key & bit) != 0) & left;
+      const int n_ones = __popcll(ones);
+      left = r < n_ones ? ones : left & ~ones;
+      r = r < n_ones ? r : r - n_ones;
+    }
+    const int before = __builtin_amdgcn_mbcnt_hi((unsigned)(left >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)left, 0u));
+    const int at = __builtin_ctzll(__ballot((left >> lane & 1) != 0 && before == r));
+    b = first + at;
+    L = __builtin_amdgcn_readlane(len, at);
+  } else {
+    L = __builtin_amdgcn_readfirstlane(ctx_len[b]);
+  }
   const int32_t* const bt_row = block_table + (size_t)b * bt_stride;
   const bool fused = k_new != nullptr;
-  const int L = __builtin_amdgcn_readfirstlane(ctx_len[b]);
   u32x2 row = {0u, 0u};  // 8 bytes per lane of (K row, V row)
   if (fused) row = *reinterpret_cast<const u32x2*>((lane < 32 ? k_new : v_new) + (size_t)b * new_row_stride + (size_t)g * D + (lane & 31) * 4);
   u32x4 qf[4];
@@ -618,17 +646,30 @@ __global__ __launch_bounds__(W * 64, 3) void decode_short_kernel(
       tail = L - 16 * (nb - 1);
       if (fused) {
         f0.put_token(s_new, s_new + D, tail - 1, D, col, quad);
-        // K: 16 bytes in each of 16 places.  V: a token is 128 places of two bytes, which the memory reads and writes 64 bytes at a
-        // time; the whole block, which is in the registers, goes back in whole lines instead, and nothing is read for it.  (Nobody else
-        // in the launch reads or writes this piece; slots behind the end keep what they hold.)
+        // A token is 16 places of 16 bytes of K and 128 places of two bytes of V, and the memory reads and writes 64 bytes at a time.  The
+        // block is in the registers: the V block, and the four tokens of K that share the newest one's 64 bytes, go back whole, and nothing is read
+        // for it (52 on 52, 320 x 49..99: 151 us with K's 16 bytes alone, 146).  Nobody else in the launch reads or writes this
+        // piece; slots behind the end keep what they hold.
         const size_t off = (size_t)__builtin_amdgcn_readlane(ids, nw - 1) * blk_stride;
         char* const kd = const_cast<char*>(kc) + off;
         char* const vd = const_cast<char*>(vc) + off;
         int ln = lane;
         asm volatile("" : "+v"(ln));  // (where the lane writes is worked out here, not kept through the walk)
-        if (ln < 16) *reinterpret_cast<u32x4*>(kd + ln * 256 + (tail - 1) * 16) = *reinterpret_cast<const u32x4*>(s_new + ln * 8);
+        const bool of_k = ((ln & 15) >> 2) == (tail - 1) >> 2;
+        // (nothing follows in this wavefront that waits for the stores)
+        if (stream) {
 #pragma unroll
-        for (int dt = 0; dt < 8; ++dt) *reinterpret_cast<s16x4*>(vd + (ln & 15) * 32 + (ln >> 4) * 8 + dt * 512) = f0.v[dt];
+          for (int j = 0; j < 4; ++j)
+            if (of_k) __builtin_nontemporal_store(f0.k[j], reinterpret_cast<u32x4*>(kd + ln * 16 + j * 1024));
+#pragma unroll
+          for (int dt = 0; dt < 8; ++dt) __builtin_nontemporal_store(f0.v[dt], reinterpret_cast<s16x4*>(vd + (ln & 15) * 32 + (ln >> 4) * 8 + dt * 512));
+        } else {
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            if (of_k) *reinterpret_cast<u32x4*>(kd + ln * 16 + j * 1024) = f0.k[j];
+#pragma unroll
+          for (int dt = 0; dt < 8; ++dt) *reinterpret_cast<s16x4*>(vd + (ln & 15) * 32 + (ln >> 4) * 8 + dt * 512) = f0.v[dt];
+        }
       }
       if (tail < 16) f0.clear_tail(tail, quad);
     }
@@ -973,14 +1014,26 @@ hipError_t launch_prefill_any(const AttnArgs& a, const int32_t* cu_q, const int3
   return hipGetLastError();
 }
 
-hipError_t launch_decode_short(const AttnArgs& a, const int32_t* ctx_len, int32_t waves, hipStream_t s) {
+hipError_t launch_decode_short(const AttnArgs& a, const int32_t* ctx_len, int32_t waves, int32_t max_ctx_len, int32_t num_cu, hipStream_t s) {
+  const int64_t pairs = (int64_t)a.B * a.Hkv;
+  const bool ordered = decode_short_ordered(pairs, max_ctx_len, num_cu);
+  // groups of equal size, at most one sequence per lane; length classes: the largest holds max_ctx_len and what lies above it
+  const int groups = (a.B + 63) / 64, per_group = (a.B + groups - 1) / groups;
+  int shift = 4;
+  while (max_ctx_len >> shift > 15) ++shift;
   auto launch = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, dim3((unsigned)a.Hkv, (unsigned)a.B), dim3(waves * 64), 0, s, (const uint16_t*)a.q, a.q_row_stride, (const uint16_t*)a.k_new,
-                       (const uint16_t*)a.v_new, a.new_row_stride, (uint16_t*)const_cast<void*>(a.k_cache), (uint16_t*)const_cast<void*>(a.v_cache),
-                       a.block_table, a.bt_stride, ctx_len, (uint16_t*)a.out, a.lse, a.Hq, a.Hkv, a.Hq / a.Hkv, a.scale_log2e);
+    hipLaunchKernelGGL(kernel, ordered ? dim3((unsigned)a.Hkv, (unsigned)groups, (unsigned)per_group) : dim3((unsigned)a.Hkv, (unsigned)a.B), dim3(waves * 64), 0, s,
+                       (const uint16_t*)a.q, a.q_row_stride, (const uint16_t*)a.k_new, (const uint16_t*)a.v_new, a.new_row_stride,
+                       (uint16_t*)const_cast<void*>(a.k_cache), (uint16_t*)const_cast<void*>(a.v_cache), a.block_table, a.bt_stride, ctx_len,
+                       (uint16_t*)a.out, a.lse, a.Hq, a.Hkv, a.Hq / a.Hkv, a.scale_log2e, a.B, per_group, shift, decode_short_stream(pairs, max_ctx_len) ? 1 : 0);
     return hipGetLastError();
   };
-  return waves == 1 ? launch(decode_short_kernel<1>) : waves == 2 ? launch(decode_short_kernel<2>) : waves == 4 ? launch(decode_short_kernel<4>) : hipErrorInvalidValue;
+  auto of = [&](auto w) {
+    constexpr int W = decltype(w)::value;
+    return ordered ? launch(decode_short_kernel<W, true>) : launch(decode_short_kernel<W, false>);
+  };
+  return waves == 1 ? of(std::integral_constant<int, 1>()) : waves == 2 ? of(std::integral_constant<int, 2>()) : waves == 4 ? of(std::integral_constant<int, 4>())
+                                                                                                                  : hipErrorInvalidValue;
 }
 
 hipError_t launch_decode_any(const AttnArgs& a, const int32_t* ctx_len, int32_t split_tokens, int32_t n_split_max, float* ws_acc,

@@ -172,7 +172,7 @@ hipError_t launch_decode_any(const AttnArgs& a, const int32_t* ctx_len, int32_t 
                              float* ws_acc, float* ws_ml, uint32_t* counters, int32_t num_cu, hipStream_t s);
 // (bf16, 128), whole contexts: `waves` (1, 2 or 4) wavefronts per (sequence, K/V head), see decode_short in decode_slices.h; no workspace; with
 // a.k_new given it appends the step's tokens too
-hipError_t launch_decode_short(const AttnArgs& a, const int32_t* ctx_len, int32_t waves, hipStream_t s);
+hipError_t launch_decode_short(const AttnArgs& a, const int32_t* ctx_len, int32_t waves, int32_t max_ctx_len, int32_t num_cu, hipStream_t s);
 
 // attn_decode_mfma.hip: bf16, D = 128
 // (split_tokens 0 = equal share per wavefront of the persistent grid; > 0 forces the chunk size)

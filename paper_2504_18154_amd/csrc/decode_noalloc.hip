@@ -124,7 +124,7 @@ extern "C" int ecoserve_attn_decode_noalloc(int device, const ecoserve_layout* l
   const int n_wgs = dev.num_cu * kDecodeWgsPerCu < kNoallocMaxWgs ? dev.num_cu * kDecodeWgsPerCu : kNoallocMaxWgs;
   hipStream_t s = (hipStream_t)stream;
   if (const int32_t waves = decode_short(B, a.Hkv, max_ctx_len, n_wgs))
-    return launch_decode_short(a, ctx_len, waves, s) == hipSuccess ? ECOSERVE_OK : ECOSERVE_EHIP;
+    return launch_decode_short(a, ctx_len, waves, max_ctx_len, n_wgs, s) == hipSuccess ? ECOSERVE_OK : ECOSERVE_EHIP;
   const SmallDecode small = small_decode(B, a.Hkv, max_ctx_len, n_wgs);
   if (small.n_split > 0) {
     // (at most n_wgs slices in all, or one per (sequence, K/V head) of up to twice as many: their states of Hq / Hkv <= kMaxGroup

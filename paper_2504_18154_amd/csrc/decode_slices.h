@@ -125,22 +125,38 @@ inline SmallDecode any_decode(int32_t B, int32_t Hkv, int32_t D, int32_t elem_by
   return {uniform, n_uniform};
 }
 
-// For (bf16, 128): wavefronts per (sequence, K/V head) with which decode_short_kernel takes a batch whole, 0 if it does not.
+// For (bf16, 128): wavefronts per (sequence, K/V head) with which decode_short_kernel takes a batch whole, 0 if it does not.  From 2700 random
+// batches of the six head shapes of perf/cases.py, up to 8192 tokens, each with 1, 2 and 4 wavefronts, in order of length and not, and by the other kernels.
 //   Few (sequence, K/V head)s: up to where contexts cut into slices, or eight wavefronts to a context, end sooner (us there / here: 1 x 496
-// tokens, 8 K/V heads, 8.0 / 6.9, 2 x 458 8.1 / 8.5; 7 x 204 7.5 / 6.4; 26 x 259, 8 heads, 7.7 / 7.2, 18 x 479 9.2 / 9.9).
-//   More than fit one workgroup of eight wavefronts per CU: up to 640 tokens (52 x 566, 8 heads, 33.0 / 24.1, 36 x 700 16.9 / 16.6, 33 x 1098
-// 16.7 / 17.7), and beyond one and a half per CU, where slices no longer help and the persistent kernel is no faster at any length, until the
-// longest context's walk, 0.07 us a block of four wavefronts, stands out (79 x 1106, 8 heads, 76 / 62, 137 x up to 2072 156 / 153, 517 x up to
-// 1421 311 / 317; 789 x 467 301 / 291).
-//   One wavefront is the cheapest for contexts of two blocks, two for those of six, and for longer ones while there are
-// workgroups enough (112 x 866 tokens 67.4, with four 69.4; 325 x 226 29.3 / 30.0).
-//   Of 700 random batches up to 3000 tokens 564 go here, 0.72 of the time on average, 0.97 at most.
+// tokens, 8 K/V heads, 8.0 / 6.9, 2 x 458 8.1 / 8.5; 7 x 204 7.5 / 6.4; 26 x 259, 8 heads, 7.7 / 7.2).  From half a workgroup per CU on slices have
+// little to even out (others / here: 129 to 192 (sequence, head)s of 1025..1536 tokens 1.20 / 1.04 of the best, 1537..2048 1.08 / 1.06, 2049..3072 1.05 / 1.10; 193 to
+// 256: 3073..4096 1.12 / 1.00, 4097..6144 1.05 / 1.13), just above one per CU some CUs have two (257 to 384: 1025..1536 1.14 / 1.02, 1537..2048
+// 1.08 / 1.06, 3073..4096 1.01 / 1.07).
+//   Many: as long as the longest is walked before the rest is done (385 to 768, 3073..4096 tokens: 1.06 / 1.02), and while the batch is not so
+// large that the persistent kernel's start and end no longer count (8192 x 513..768 1.09 / 1.00, x 769..1024 1.07 / 1.01; 4096 x 1537..2048 1.05 / 1.02;
+// 2048 x 2049..3072 1.05 / 1.01, 2048 x 1024..4096 469 / 473 and 449 / 447 us; 1024 x 4097..6144 1.05 / 1.01; 1024 x 512..4096 203 / 194 us).
+//   One wavefront is the cheapest for contexts of two blocks, and for longer ones while enough others run (768 to 1024: 97..128 tokens 1.00, two
+// 1.02, 193..256 1.08 / 1.00; 6144 to 8192: x 257..512 1.00 / 1.02); two likewise (385 to 512: 97..192 1.02, four 1.00; 769 to 1024: 385..512 1.00 / 1.14; 2048 to
+// 3072: 513..768 1.01 / 1.01).
 inline int32_t decode_short(int32_t B, int32_t Hkv, int32_t max_ctx_len, int32_t num_cu) {
-  const int64_t pairs = (int64_t)B * Hkv, cu = num_cu;
-  const int32_t most = 32 * pairs <= cu ? 512 : 4 * pairs <= cu ? 384 : pairs <= cu ? 320 : 2 * pairs <= 3 * cu ? 640 : pairs <= 4 * cu ? 1152 : 1024;
-  if (max_ctx_len > most) return 0;
-  return max_ctx_len <= 32 ? 1 : max_ctx_len <= (pairs > 2 * cu ? 384 : 96) ? 2 : 4;
+  const int64_t pairs = (int64_t)B * Hkv, cu = num_cu, tokens = max_ctx_len;
+  const int64_t most = 32 * pairs <= cu ? 512 : 4 * pairs <= cu ? 384 : 2 * pairs <= cu ? 320 : 4 * pairs <= 3 * cu ? 2048 : pairs <= cu ? 4096
+                     : 2 * pairs <= 3 * cu ? 2048 : pairs <= 3 * cu ? 4096 : 32000 * cu / pairs;
+  if (tokens > most) return 0;
+  return tokens <= 32 || tokens * cu <= 32 * pairs ? 1 : tokens <= 96 || tokens * cu <= 96 * pairs ? 2 : 4;
 }
+// Whether its workgroups are handed out by length, longest first: more of them than CUs, and contexts long enough for the end of the launch to
+// show it (in order of the batch / of length, of the best: 385 to 512 (sequence, head)s, up to 192 tokens 1.00 / 1.07, 193..256 1.08 / 1.00; 1024 x 65..128 1.00 / 1.02;
+// 4096 x 33..64 1.00 / 1.01, 65..128 1.10 / 1.00).
+inline bool decode_short_ordered(int64_t pairs, int32_t max_ctx_len, int32_t num_cu) {
+  return pairs > num_cu && max_ctx_len > (pairs > (int64_t)4 * num_cu ? 96 : 192);
+}
+// Whether what it writes back goes past the caches: 5 KiB per (sequence, head), which the last-level cache (256 MB) holds until the next step for a few layers,
+// not for those of a model, and written back from there it costs more.  1024 x ~103 tokens on 8 K/V heads, 2, 4 and 8 layers, kept / past the caches: 99.9 /
+// 104.5, 103.3 / 104.7, 115.7 / 104.9 us a layer; 512 x ~103 60.7 / 61.8, 60.8 / 62.3, 62.8 / 62.4.  With three sets of 2 to 8 layers in turn (1387 batches; of the
+// best): 2049 to 4096 (sequence, head)s, up to 96 tokens 1.09 / 1.00, 97..192 1.02 / 1.01, 193..384 1.01 / 1.02; 4097 to 8192, 97..192 1.06 / 1.01, 385..768 1.01 /
+// 1.01; 16385 to 32768, 97..192 1.19 / 1.01.
+constexpr bool decode_short_stream(int64_t pairs, int32_t max_ctx_len) { return pairs > (max_ctx_len <= 192 ? 2048 : 4096); }
 
 // For (bf16, 128), batches that decode_short leaves: how decode_any_kernel takes a small one, n_split 0 if it does not.  It needs no numbering of the batch and no
 // second launch, which is what such a batch spends its time on in the persistent kernel.

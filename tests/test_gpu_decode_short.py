@@ -24,7 +24,12 @@ CASES = [("one-block", (40, 8), [1, 15, 16, 2], 1), ("two-blocks", (8, 1), [17, 
          ("two", (5, 1), [33, 48, 64, 65, 96, 1, 80, 95], 2), ("two-many", (40, 8), _ragged(130, 384), 2), ("two-G16", (16, 1), _ragged(600, 200), 2),
          ("four", (64, 8), [384, 97, 383, 1, 17, 130], 4), ("four-one-sequence", (3, 3), [512], 4), ("four-most", (40, 8), _ragged(36, 640), 4),
          ("four-many", (32, 8), _ragged(90, 1152), 4), ("four-very-many", (8, 8), _ragged(200, 1024), 4),
-         ("slices", (40, 8), [513], 0), ("persistent", (32, 8), [1025] * 129, 0)]
+         # more workgroups than CUs, handed out by length: groups of 33 and 32 sequences, more ids than a register holds, and with more than 4096
+         # (sequence, K/V head)s, whose blocks are written past the caches
+         ("four-two-groups", (16, 4), _ragged(65, 400), 4), ("four-windows", (8, 8), [60, 4300, 4096, 4097, 2049] + _ragged(96, 60), 4),
+         ("one-stream", (8, 8), _ragged(520, 128), 1), ("two-stream", (16, 8), [17, 530, 600] + _ragged(517, 40), 2),
+         ("four-stream", (8, 8), _ragged(510, 30) + [33, 1545, 1550], 4),
+         ("slices", (40, 8), [513], 0), ("persistent", (52, 52), [1025] * 128, 0)]
 
 
 def test_each_case_gets_the_wavefronts_it_is_listed_for(tmp_path):
