@@ -29,7 +29,7 @@ CASES = [("one-block", (40, 8), [1, 15, 16, 2], 1), ("two-blocks", (8, 1), [17, 
          ("four-two-groups", (16, 4), _ragged(65, 400), 4), ("four-windows", (8, 8), [60, 4300, 4096, 4097, 2049] + _ragged(96, 60), 4),
          ("one-stream", (8, 8), _ragged(520, 128), 1), ("two-stream", (16, 8), [17, 530, 600] + _ragged(517, 40), 2),
          ("four-stream", (8, 8), _ragged(510, 30) + [33, 1545, 1550], 4),
-         ("slices", (40, 8), [513], 0), ("persistent", (52, 52), [1025] * 128, 0)]
+         ("slices", (40, 8), [513], 0), ("persistent", (52, 52), [1300] * 128, 0)]
 
 
 def test_each_case_gets_the_wavefronts_it_is_listed_for(tmp_path):
