@@ -1,6 +1,6 @@
 // Paged attention on gfx950 matrix cores for every layout except bf16 with head size 128: bf16 of any head size
 // that is a multiple of 8 and fp32 of any that is a multiple of 4, up to 256.  The decode kernel here also serves
-// small batches of that layout (small_decode).
+// small batches of that layout (small_decode), and decode_short_kernel those whose contexts it takes whole (decode_short).
 //
 // Eq. 2 of Section 2.1 over the paged cache, as the kernels for (bf16, 128) evaluate it, with the arithmetic of
 // the plain kernels: scores, weights and sums are fp32.
