@@ -26,6 +26,7 @@ CASES = [
     ("split-long", (3, 3), [(31, 2017), (65, 1)], SPLIT),
     ("split-G16", (16, 1), [(2, 30), (4, 127), (6, 128)], SPLIT),
     ("split-more-than-a-round", (52, 52), [(300, 0)], SPLIT),
+    ("split-one-and-a-half-rounds", (40, 8), [(507, 0), (63, 449), (46, 0)], SPLIT), ("split-to-1536", (8, 1), [(280, 1250), (1, 1535)] + [(200, 0)] * 10, SPLIT),
     ("rows32-many-sequences", (8, 1), _ragged(300, 40, 50), ROWS32),
     ("rows32-mha", (52, 52), _ragged(70, 20, 40), ROWS32),
     ("rows64", (40, 8), _ragged(90, 100, 60), ROWS64),
