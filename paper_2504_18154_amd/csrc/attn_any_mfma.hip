@@ -524,8 +524,7 @@ __global__ __launch_bounds__(W * 64) void decode_any_kernel(
 // length (in 16 classes of 2^shift tokens), longest first.  A wavefront finds it among its lanes' 64 lengths with four ballots (0.2 to 1 us
 // of a launch, which is why a batch that starts all at once, or has little to gain, does without: the grid is (K/V heads, B) then).
 // us per call with the append, in the order of the batch / longest first: 40 query heads on 8, 1024 x ~103 tokens up to 800, one
-// wavefront 124 / 100, 2 wavefronts 116 / 102, 4 117 / 110; 512 x 20..600 133 / 121; 128 x 512..4096 (4 wavefronts) 217 / 194, where the persistent kernel and
-// its merge take 203; 8 on 1, 1024 x 8..600 39 / 34; 32 on 8, 152 x ~412 up to 1391 62 / 51 (persistent 65).
+// wavefront 124 / 100, 2 wavefronts 116 / 102, 4 117 / 110; 512 x 20..600 133 / 121; 8 on 1, 1024 x 8..600 39 / 34; 32 on 8, 152 x ~412 up to 1391 62 / 51 (persistent 65).
 // What the persistent kernel spends on such batches: 1.2 us of a wavefront on a piece, a start-up of 7 us, and a second launch for the V columns.
 // us per call, the kernels that had these batches / without order: 40 on 8, 819 x 193 159 / 146, 139 x ~46 20.7 / 13.1, 112 x
 // 8 13.9 / 6.4; 32 on 8, 375 x ~18 28.6 / 15.3, 112 x 866 82.8 / 69.4; 52 on 52, 628 x 49..99 380 / 332, 23 x 63 21.3 / 13.1; 8 on 1, 1 x 180

@@ -125,23 +125,26 @@ inline SmallDecode any_decode(int32_t B, int32_t Hkv, int32_t D, int32_t elem_by
   return {uniform, n_uniform};
 }
 
-// For (bf16, 128): wavefronts per (sequence, K/V head) with which decode_short_kernel takes a batch whole, 0 if it does not.  From 2700 random
-// batches of the six head shapes of perf/cases.py, up to 8192 tokens, each with 1, 2 and 4 wavefronts, in order of length and not, and by the other kernels.
-//   Few (sequence, K/V head)s: up to where contexts cut into slices, or eight wavefronts to a context, end sooner (us there / here: 1 x 496
-// tokens, 8 K/V heads, 8.0 / 6.9, 2 x 458 8.1 / 8.5; 7 x 204 7.5 / 6.4; 26 x 259, 8 heads, 7.7 / 7.2).  From half a workgroup per CU on slices have
-// little to even out (others / here: 129 to 192 (sequence, head)s of 1025..1536 tokens 1.20 / 1.04 of the best, 1537..2048 1.08 / 1.06, 2049..3072 1.05 / 1.10; 193 to
-// 256: 3073..4096 1.12 / 1.00, 4097..6144 1.05 / 1.13), just above one per CU some CUs have two (257 to 384: 1025..1536 1.14 / 1.02, 1537..2048
-// 1.08 / 1.06, 3073..4096 1.01 / 1.07).
-//   Many: as long as the longest is walked before the rest is done (385 to 768, 3073..4096 tokens: 1.06 / 1.02), and while the batch is not so
-// large that the persistent kernel's start and end no longer count (8192 x 513..768 1.09 / 1.00, x 769..1024 1.07 / 1.01; 4096 x 1537..2048 1.05 / 1.02;
-// 2048 x 2049..3072 1.05 / 1.01, 2048 x 1024..4096 469 / 473 and 449 / 447 us; 1024 x 4097..6144 1.05 / 1.01; 1024 x 512..4096 203 / 194 us).
+// For (bf16, 128): wavefronts per (sequence, K/V head) with which decode_short_kernel takes a batch whole, 0 if it does not.  The host knows the longest
+// context, not the others, and walking it is the launch's time at least (20 us for 1700 tokens by four wavefronts) however short those are: the line lies
+// where no lengths make it cost more than a few percent.  From 18800 random batches of seven head shapes, up to 9000 tokens: lengths equal, uniform from 1/2, 1/8 and 1/64 of the
+// longest on, lognormal around 1/3, 1/6 and 1/10 of it, and one sequence in 16 ten times as long as the others.  Of the time of the other kernels (their
+// mean, the worst):
+//   Few (sequence, K/V head)s, up to where contexts cut into slices, or eight wavefronts to a context, end sooner: 0.80, 0.97.
+//   129 to 256, up to 384 tokens: 0.89, 1.00.  Beyond, slices even out ragged lengths: 385 to 512 0.99, 1.11; 513 to 1024 1.02, 1.33; 1025 to 4096 1.02, 2.15
+// (0.87 where all are as long, 1.22 where most are a sixth and less of it).
+//   257 to 320, up to 640: 0.85, 1.07; 641 to 1024 0.85, 1.14; 1025 to 2048 1.01, 1.58.
+//   More: against the persistent kernel, whose launch is even whatever the lengths.  321 to 768, up to 1280: 0.75, 1.03; 1281 to 2048 0.92, 1.20; 2049 to
+// 4096 1.04, 1.63.  769 to 2048, up to 1664: 0.70, 1.06; 1665 to 2048 0.92, 1.11; 2049 to 4096 0.98, 1.32.  In the largest batches its start and end no
+// longer count.  2049 to 3072, up to 1280: 0.71, 1.04; 1281 to 2048 0.91, 1.07, lengths all equal 1.03.  From 3073 on, up to 832: 0.72, 1.05; 833 to 1280 0.89, 1.07,
+// equal 1.03.
 //   One wavefront is the cheapest for contexts of two blocks, and for longer ones while enough others run (768 to 1024: 97..128 tokens 1.00, two
 // 1.02, 193..256 1.08 / 1.00; 6144 to 8192: x 257..512 1.00 / 1.02); two likewise (385 to 512: 97..192 1.02, four 1.00; 769 to 1024: 385..512 1.00 / 1.14; 2048 to
 // 3072: 513..768 1.01 / 1.01).
 inline int32_t decode_short(int32_t B, int32_t Hkv, int32_t max_ctx_len, int32_t num_cu) {
   const int64_t pairs = (int64_t)B * Hkv, cu = num_cu, tokens = max_ctx_len;
-  const int64_t most = 32 * pairs <= cu ? 512 : 4 * pairs <= cu ? 384 : 2 * pairs <= cu ? 320 : 4 * pairs <= 3 * cu ? 2048 : pairs <= cu ? 4096
-                     : 2 * pairs <= 3 * cu ? 2048 : pairs <= 3 * cu ? 4096 : 32000 * cu / pairs;
+  const int64_t most = 32 * pairs <= cu ? 512 : 4 * pairs <= cu ? 384 : 2 * pairs <= cu ? 320 : pairs <= cu ? 384 : 4 * pairs <= 5 * cu ? 640
+                     : pairs <= 3 * cu ? 1280 : pairs <= 8 * cu ? 1664 : pairs <= 12 * cu ? 1280 : std::min<int64_t>(832, 32000 * cu / pairs);
   if (tokens > most) return 0;
   return tokens <= 32 || tokens * cu <= 32 * pairs ? 1 : tokens <= 96 || tokens * cu <= 96 * pairs ? 2 : 4;
 }
