@@ -22,10 +22,11 @@ constexpr int64_t kShortMostKeys = 1024;  // a wavefront's walk: the 64 block id
 // its key steps shared out (40 on 8, us there / here: 32 + 500 tokens 15.4 / 7.8, 67 + 960 23.8 / 12.3, 32 + 2000 19.2 / 14.4, but 32 + 5300
 // 27.6 / 39.8; 8 on 1, 17 x 20 + 2800 22.5 / 24.7; half that where the tiles of a head do not stay with one XCD: 52 on 52, 3 x 66 + 1350 32.3 / 42.2).  Contexts
 // of one group of 32 keys have none to share (16 tokens 4.4 against 4.2).  To 1.25 times that many workgroups up to 1536 tokens, and to 1.56 times
-// between 256 and 1024 (of the time of the better of the others: 513 to 640 tiles, 513..1024 tokens 0.74 to 0.78, 1025..1536 0.71 to 0.88; 641 to 800, 257..512 0.79 to
-// 1.01, 513..1024 0.63 to 0.97; 801 to 960, 257..768 0.85 to 1.19; us there / here: 40 on 8, 616 tokens of 63..507 14.7 / 11.7, 64 on 8, 19 x 11 behind
-// 672..1345 28.5 / 20.2, 5 on 1, 9 x 528 behind ~80 21.0 / 16.7; not for more than 16 sequences, whose tiles end at many lengths: 64 on 8, 18 of up to 448 tokens 21.9 / 24.8, 8 on
-// 1, 81 of up to 672 26.7 / 29.0).
+// between 256 and 1024 where the tiles of a head stay with one XCD.  Not in the longest contexts, and not beyond 1.25 times, for more than 16 sequences,
+// whose K and V come from memory and whose tiles end at many lengths (64 on 8, 17 sequences of 56 to 1652 tokens, eight layers in turn 21.9 / 32.8, one again and again 26.6 /
+// 21.2; 16 on 4, 21 up to 1152 26.8 / 29.0; 8 on 1, 81 of up to 672, 1.5 rounds, 26.7 / 29.0).  Of 8755 random batches of seven head shapes (lengths equal, uniform, lognormal, one in 16 ten times the others), of
+// the persistent kernel's time on average, the worst: one round 0.64, 1.22; to 1.25 0.74, 1.22; to 1.56 0.77, 1.10; 20 of 8506 more than 4% slower.  What is left to that
+// kernel: 17 sequences and more beyond 1536 tokens (in 1.25 rounds 1024) 0.86, 1.50; the last, 52 on 52, 0.87, 1.18.
 //   Rows: no list and no change of tiles, but K and V come once per 32 or 64 rows through the first-level cache, where the
 // persistent kernel reads them once per 128 through LDS: the longer the contexts and the fewer the wavefronts, the sooner it wins.
 // The line, a context against the cube root of the number of tiles, from 320 random batches (there / here): 52 heads, 128 x 22 tokens 114 / 55,
@@ -39,10 +40,11 @@ inline PrefillShort prefill_short(int64_t B, int64_t T, int64_t Hq, int64_t Hkv,
   if (tiles >= (int64_t)1 << 30) return PrefillShort::kNo;
   if (max_ctx <= 32) return PrefillShort::kRows32;
   const bool local = Hkv < 8 || Hkv % 8 == 0;  // the tiles of a head stay with one XCD
-  if (tiles <= wgs && max_ctx <= (local ? 2 : 1) * kShortMostKeys) return PrefillShort::kSplitKeys;
+  const bool few = B <= 16;
+  if (tiles <= wgs && 2 * max_ctx <= (!local ? 2 : few ? 4 : 3) * kShortMostKeys) return PrefillShort::kSplitKeys;
   if (max_ctx <= kShortMostKeys && max_ctx * max_ctx * max_ctx <= 6750 * 256 / num_cu * tiles)
     return tiles >= 12 * num_cu && max_ctx > 96 ? PrefillShort::kRows64 : PrefillShort::kRows32;
-  if (4 * tiles <= 5 * wgs ? 2 * max_ctx <= (local ? 3 : 2) * kShortMostKeys : 16 * tiles <= 25 * wgs && B <= 16 && max_ctx > 256 && max_ctx <= kShortMostKeys)
+  if (4 * tiles <= 5 * wgs ? 2 * max_ctx <= (local && few ? 3 : 2) * kShortMostKeys : 16 * tiles <= 25 * wgs && few && local && max_ctx > 256 && max_ctx <= kShortMostKeys)
     return PrefillShort::kSplitKeys;
   return PrefillShort::kNo;
 }

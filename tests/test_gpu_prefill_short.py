@@ -33,6 +33,10 @@ CASES = [
     ("rows64-mha", (52, 52), [(64, 0), (63, 1), (65, 63), (128, 2), (1, 0), (150, 31), (0, 33), (33, 96), (127, 64)] * 3, ROWS64),
     ("rows64-G8", (64, 8), [(300, 100), (399, 1), (1, 399), (257, 130)] * 6, ROWS64),
     ("too-long", (40, 8), [(20, 3000)], NO),
+    # more than 16 sequences, some of them long (us by the persistent kernel / keys shared: 21.9 / 32.8, 26.8 / 29.0), and heads whose tiles do not stay
+    # with one XCD, beyond 1.25 rounds of workgroups (19.4 / 22.9)
+    ("17-up-to-1652", (64, 8), [(2, 200)] * 13 + [(1, 1651)] * 3 + [(51, 384)], NO), ("21-up-to-1152", (16, 4), [(53, 400)] * 20 + [(33, 1119)], NO),
+    ("far-tiles-in-1.4-rounds", (52, 52), [(86, 354)] * 3 + [(87, 393)], NO),
 ]
 
 
