@@ -38,8 +38,18 @@ def _deps_mtime() -> float:
     return max(os.path.getmtime(p) for p in deps)
 
 
+def _bind_fits() -> str:
+    """What csrc/bind.cpp is compiled against, as it stands in _bind.so (its module's documentation)."""
+    import torch
+    return f"for {sys.implementation.cache_tag}, torch {torch.__version__}, C++11 ABI {int(torch._C._GLIBCXX_USE_CXX11_ABI)}."
+
+
 def is_current() -> bool:
-    return all(os.path.exists(p) and os.path.getmtime(p) >= _deps_mtime() for p in (LIB, BIND))
+    """Both libraries are newer than their sources, and _bind.so is for the installed torch and this interpreter."""
+    if not all(os.path.exists(p) and os.path.getmtime(p) >= _deps_mtime() for p in (LIB, BIND)):
+        return False
+    with open(BIND, "rb") as f:
+        return _bind_fits().encode() in f.read()
 
 
 def _build_bind() -> None:
@@ -51,6 +61,7 @@ def _build_bind() -> None:
     abi = f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"
     libs = os.path.join(root, "lib")
     cmd = [os.environ.get("CXX") or "g++", "-std=c++17", "-O2", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", abi,
+           f'-DECO_BIND_FITS="{_bind_fits()}"',
            *(a for i in includes for a in ("-isystem", i)), os.path.join(CSRC, "bind.cpp"), "-o", BIND, "-L", libs, "-ltorch_python", "-ltorch_cpu", "-lc10",
            "-lc10_hip", f"-Wl,-rpath,{libs}"]
     r = subprocess.run(cmd, capture_output=True, text=True)

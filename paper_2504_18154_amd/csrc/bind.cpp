@@ -185,7 +185,8 @@ PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n) {
 #define ECO_FAST(f) {#f, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(f)), METH_FASTCALL, nullptr}
 PyMethodDef methods[] = {ECO_FAST(bind), ECO_FAST(kv_append), ECO_FAST(attn_prefill), ECO_FAST(attn_decode), ECO_FAST(attn_decode_append),
                          ECO_FAST(attn_decode_noalloc), {nullptr, nullptr, 0, nullptr}};
-PyModuleDef module = {PyModuleDef_HEAD_INIT, "_bind", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
+// (ECO_BIND_FITS: the interpreter and the torch that this is compiled for; build.py looks for it in the built file)
+PyModuleDef module = {PyModuleDef_HEAD_INIT, "_bind", "Marshalling of the hot calls' arguments, " ECO_BIND_FITS, -1, methods, nullptr, nullptr, nullptr, nullptr};
 
 }  // namespace
 

@@ -98,3 +98,12 @@ def test_what_reaches_the_c_abi():
         lib = binding._lib
         fast.bind(*(ctypes.cast(f, vp).value for f in (lib.ecoserve_kv_append_strided, lib.ecoserve_attn_prefill_strided, lib.ecoserve_attn_decode_strided,
                                                        lib.ecoserve_attn_decode_append, lib.ecoserve_attn_decode_noalloc)))
+
+
+def test_a_library_for_another_torch_is_not_current(monkeypatch):
+    """Built for another torch _bind.so does not load, and what the error says to run must then build it."""
+    from paper_2504_18154_amd import build
+    monkeypatch.setattr(build, "_deps_mtime", lambda: 0.0)
+    assert build.is_current() and build._bind_fits() in fast.__doc__
+    monkeypatch.setattr(torch, "__version__", "0.0.0")
+    assert not build.is_current()
