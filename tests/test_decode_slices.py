@@ -94,7 +94,7 @@ int main() {
     }
     const SmallDecode d = small_decode(B, Hkv, bound, 256);
     const int W = d.n_split == 256 / Hkv ? 8 : 4;
-    std::printf("%s\n", d.n_split == 0 ? "persistent" : d.split_tokens > 0 ? "uniform" : !covers(len, B, Hkv, d.n_split, W) ? "wrong" : W == 8 ? "8" : "4");
+    std::printf("%s\n", decode_short(B, Hkv, bound, 256) ? "whole" : d.n_split == 0 ? "persistent" : d.split_tokens > 0 ? "uniform" : !covers(len, B, Hkv, d.n_split, W) ? "wrong" : W == 8 ? "8" : "4");
   }
   unsigned seed = 12345;
   auto rnd = [&](unsigned n) { return (seed = seed * 1664525u + 1013904223u, (unsigned)((unsigned long long)(seed >> 8) * n >> 24)); };
@@ -107,7 +107,7 @@ int main() {
     for (int b = 0; b < B; ++b) len[b] = shape == 0 ? rnd(most + 1) : shape == 1 ? (rnd(2) ? 0 : rnd(most + 1)) : shape == 2 ? (b ? rnd(40) : most) : most;
     bound = most + (rnd(2) ? 0 : rnd(2000));
     const SmallDecode d = small_decode(B, Hkv, bound, 256);
-    if (d.n_split == 0 || d.split_tokens > 0) continue;
+    if (decode_short(B, Hkv, bound, 256) || d.n_split == 0 || d.split_tokens > 0) continue;
     ++balanced;
     if (!covers(len, B, Hkv, d.n_split, d.n_split == 256 / Hkv ? 8 : 4)) return std::printf("B %d, %d heads, up to %d tokens: not covered\n", B, Hkv, most), 1;
   }
@@ -132,6 +132,13 @@ def test_paths_of_the_batches_of_the_gpu_tests_and_their_balanced_slices(tmp_pat
     for heads, lens, above, waves in t.BALANCED:
         calls += [(heads[1], lens, max(lens)), (heads[1], lens, max(lens) + above)]
         want += [str(waves)] * 2
+    # the short ones in slices, with the bounds that the tests hand over
+    calls += [(heads[1], lens, max(lens)) for heads, lens in t.CASES + t.WHOLE] + [(8, [9000, 20], 600), (8, [700, 40], 700), (2, [320], 1000), (2, [320] * 90, 1000)]
+    want += ["uniform"] * len(t.CASES) + ["whole"] * len(t.WHOLE) + ["uniform"] * 4
+    # many short ones that the persistent kernel has with a loose bound (test_gpu_parity.py), and its batches in test_gpu_full_configs.py, test_zz_no_alloc.py and bench.py
+    calls += [(8, [300] * 800, 300), (8, [300] * 800, 1000), (8, [100] * 800, 1000), (8, [3000] * 96, 3000), (8, [4096] * 128, 4096), (8, [4096] * 256, 4096), (52, [700] * 7, 700),
+              (8, [9000] * 200, 9000)]
+    want += ["whole", "persistent", "persistent", "persistent", "persistent", "persistent", "whole", "persistent"]
     # batches with empty sequences, and those without a context
     calls += [(8, [1500] + [0] * 39, 1500), (8, [1500] + [0] * 47, 1500), (8, [34000, 40], 34000), (8, [60000, 40], 60000), (8, [8000, 40], 8000)]
     want += ["4", "persistent", "8", "persistent", "8"]

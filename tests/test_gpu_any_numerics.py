@@ -13,7 +13,7 @@ from tests.parity_util import dev_i32, say
 pytestmark = pytest.mark.gpu
 
 # (type, head size, K/V heads): fp32, bf16, and the layout whose small decode batches take the same kernel (with weights of
-# 16 bits and none below 2^-126, where its other kernels have 8 bits)
+# 16 bits and none below 2^-126, where its other kernels have 8 bits) or the one for whole contexts beside it
 LAYOUTS = [("f32", 64, 2), ("bf16", 64, 2), ("bf16", 128, 2)]
 IDS = ["f32-d64", "bf16-d64", "bf16-d128"]
 
@@ -26,6 +26,7 @@ class Scored:
         n = len(log2_w)
         self.B, self.n, self.D, self.Hq, self.Hkv, self.dtype = B, n, D, 2 * Hkv, Hkv, dtype
         table, num_blocks = wl.make_block_table(wl.rng_for(5), np.full(B, n))
+        table = np.pad(table, ((0, 0), (0, max(0, 64 - table.shape[1]))), constant_values=-1)   # (room for a bound above the lengths)
         self.ctx = binding.Context(self.Hq, Hkv, D, num_blocks, dtype, B, table.shape[1], softmax_scale=math.log(2.0))
         self.kc, self.vc = self.ctx.new_cache()
         dt = self.ctx.torch_dtype
@@ -44,10 +45,14 @@ class Scored:
         q[:, :, 0] = 1.0
         return q
 
-    def decode(self):
+    def decode(self, bound=0):
         out = torch.full((self.B, self.Hq, self.D), float("nan"), dtype=self.ctx.torch_dtype, device="cuda")
-        self.ctx.attn_decode(self.query(self.B), self.kc, self.vc, self.table, self.lens, out, self.n)
+        self.ctx.attn_decode(self.query(self.B), self.kc, self.vc, self.table, self.lens, out, bound or self.n)
         return out.double().cpu()
+
+    def decode_by_slices(self):
+        """With a bound of 1000 tokens, beyond what is decoded whole."""
+        return self.decode(1000)
 
     def prefill(self):
         """The last position of every sequence (which sees all its keys), as decode returns it."""
@@ -60,7 +65,7 @@ class Scored:
     def ways(self):
         """(name, result) of every kernel that serves this layout."""
         # (bf16, 128) prefill is another kernel, with another way of holding its weights
-        names = ["decode"] if (self.dtype, self.D) == ("bf16", 128) else ["decode", "prefill"]
+        names = ["decode", "decode_by_slices"] if (self.dtype, self.D) == ("bf16", 128) else ["decode", "prefill"]
         for plain in (0, 1):
             self.ctx.set_option(binding.OPT_FORCE_PLAIN, plain)
             for name in names:

@@ -155,9 +155,9 @@ def test_config3_prefill_queue_shares_follow_the_xcds_and_change_no_result():
 @pytest.mark.parametrize("dataset, seed, n_prefill, n_decode, decode_seed", [("alpaca", 32, 512, 1024, 22), ("sharegpt", 31, 64, 512, 21)])
 def test_chat_shaped_prefill_and_decode_batches_in_full(dataset, seed, n_prefill, n_decode, decode_seed):
     """The batches `bench.py --sweep` times for the paper's chat workloads (Table 4; Alpaca: some twenty input
-    tokens, some sixty output tokens): the prompts prefilled in one batch - of the Alpaca-shaped ones most in
-    packed tiles, the tail of the length distribution in ordinary ones - and the decode step of twice as many
-    such sequences, many (sequence, head) pieces per wavefront.  Every output row against the oracle."""
+    tokens, some sixty output tokens): the prompts prefilled in one batch - the Alpaca-shaped ones by the kernel for short
+    contexts, and once more with a block table so wide that another has them, most in packed tiles, the tail of the length
+    distribution in ordinary ones - and the decode step of twice as many such sequences.  Every output row against the oracle."""
     model = wl.M30B
     q_len = wl.table4_lengths(dataset, wl.rng_for(seed), n_prefill)[0]
     pb = wl.prefill_batch(model, q_len, 3)
@@ -171,6 +171,11 @@ def test_chat_shaped_prefill_and_decode_batches_in_full(dataset, seed, n_prefill
     ref, ref_lse = layer.prefill_oracle(q, pb.cu_q, pb.ctx_before, pb.block_table)
     compare(f"{dataset}-shaped prefill", out, ref, "bf16")
     compare_lse(f"{dataset}-shaped prefill", lse, ref_lse, "bf16", bf16_row_sum=True)
+    if dataset == "alpaca":
+        wide = np.pad(pb.block_table, ((0, 0), (0, 129 - pb.block_table.shape[1])), constant_values=2**30)   # never read there
+        out, lse = layer.prefill_gpu(q, pb.cu_q, pb.ctx_before, wide, max_q_len=pb.max_q_len)
+        compare(f"{dataset}-shaped prefill, wide block table", out, ref, "bf16")
+        compare_lse(f"{dataset}-shaped prefill, wide block table", lse, ref_lse, "bf16", bf16_row_sum=True)
     layer.close()
     _decode_full(wl.table4_decode_batch(model, dataset, n_decode, decode_seed), f"{dataset}-shaped decode batch")
 

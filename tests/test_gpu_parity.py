@@ -15,8 +15,11 @@ M30 = wl.ModelShape("30B-heads", 40, 8, 128, 1, "bf16")
 M70 = wl.ModelShape("70B-heads", 64, 8, 128, 1, "bf16")
 
 
-def _mk(model, q_len, ctx_before=None, seed=1, grow=0):
+def _mk(model, q_len, ctx_before=None, seed=1, grow=0, blocks=0):
+    """blocks: least width of the block table (what lies behind a sequence's own entries is never read)."""
     pb = wl.prefill_batch(model, q_len, seed, ctx_before=ctx_before, grow=grow)
+    if blocks > pb.block_table.shape[1]:
+        pb.block_table = np.pad(pb.block_table, ((0, 0), (0, blocks - pb.block_table.shape[1])), constant_values=2**30)
     layer = Layer(model, pb.num_blocks, max_batch=max(pb.B, 1), max_blocks_per_seq=pb.block_table.shape[1])
     return pb, layer
 
@@ -77,7 +80,9 @@ def test_bf16_prefill_of_short_prompts_in_packed_tiles(heads):
     heads of a K/V head into one tile.  Lengths 0 .. P including both ends, with and without a cached prefix
     (then the packed rows sit behind hundreds of cached keys); a prompt that breaks the rule by one token and
     takes ordinary tiles beside packed ones; and sixty-three prompts of mixed lengths, one of them two tiles
-    long.  The caller's bound on the lengths is exact, too small and generous in turn: it decides nothing."""
+    long.  The caller's bound on the lengths is exact, too small and generous in turn: it decides nothing.  Each batch
+    with a block table of more than 2048 tokens, behind which the kernel with packed tiles has it (test_gpu_prefill_short.py
+    asserts it), and with one as wide as its longest sequence, where most go to the kernel for short contexts."""
     model = wl.ModelShape("short", heads[0], heads[1], 128, 1, "bf16")
     G = heads[0] // heads[1]
     P = 128 // G
@@ -99,10 +104,12 @@ def test_bf16_prefill_of_short_prompts_in_packed_tiles(heads):
         layer.append(k2, v2, cu, prefix, pb.block_table)
         layer.assert_cache_bit_exact()
         ref, ref_lse = layer.prefill_oracle(q, cu, prefix, pb.block_table)
+        wide = np.pad(pb.block_table, ((0, 0), (0, 129 - pb.block_table.shape[1])), constant_values=2**30)   # never read there
         for bound in (int(new.max()), min(P, int(new.max())), min(128, int(new.sum()))):   # exact, as small as packing needs, generous
-            out, lse = layer.prefill_gpu(q, cu, prefix, pb.block_table, max_q_len=bound)
-            compare(f"prefill, max_q_len = {bound}", out, ref, "bf16")
-            compare_lse(f"prefill, max_q_len = {bound}", lse, ref_lse, "bf16", bf16_row_sum=True)
+            for table in (wide, pb.block_table):
+                out, lse = layer.prefill_gpu(q, cu, prefix, table, max_q_len=bound)
+                compare(f"prefill, max_q_len = {bound}, {table.shape[1]} blocks", out, ref, "bf16")
+                compare_lse(f"prefill, max_q_len = {bound}, {table.shape[1]} blocks", lse, ref_lse, "bf16", bf16_row_sum=True)
         layer.close()
 
 
@@ -297,25 +304,26 @@ def test_bf16_decode_of_hundreds_of_short_sequences():
     wavefront, so the block pipeline crosses piece boundaries all the time, the results leave through the
     LDS buffer in several batches, and nearly every (sequence, head) is written in final form by the
     decode kernel while the merge handles the few that a chunk boundary cuts.  Equal and measured per-XCD
-    shares."""
+    shares.  (The caller's bound is 1000 tokens: with the longest context's the batch is decoded whole,
+    test_decode_slices.py.)"""
     from paper_2504_18154_amd import binding
     model = M30
     rng = np.random.default_rng(47)
     lens = rng.integers(1, 151, size=800)
     lens[[0, 1, 799]] = [1, 300, 16]
     say(f"bf16 decode of {len(lens)} short sequences, {int(lens.sum())} tokens")
-    pb, layer = _mk(model, lens, seed=48)
+    pb, layer = _mk(model, lens, seed=48, blocks=63)
     _, k, v = _qkv(model, pb.T, 470)
     layer.append(k, v, pb.cu_q, pb.ctx_before, pb.block_table)
     layer.assert_cache_bit_exact()
     q = wl.randn((pb.B, model.Hq, model.D), "bf16", 471)
     ref, ref_lse = layer.decode_oracle(q, pb.block_table, pb.q_len)
-    out, lse = layer.decode_gpu(q, pb.block_table, pb.q_len)
+    out, lse = layer.decode_gpu(q, pb.block_table, pb.q_len, 1000)
     compare("decode, equal shares", out, ref, "bf16")
     compare_lse("decode, equal shares", lse, ref_lse, "bf16")
     layer.ctx.set_option(binding.OPT_DECODE_ADAPTIVE, 1)
     for call in range(4):
-        out, lse = layer.decode_gpu(q, pb.block_table, pb.q_len)
+        out, lse = layer.decode_gpu(q, pb.block_table, pb.q_len, 1000)
         compare(f"decode, measured shares, call {call}", out, ref, "bf16")
         compare_lse(f"decode, measured shares, call {call}", lse, ref_lse, "bf16")
     layer.close()
@@ -393,7 +401,7 @@ def test_bf16_decode_passes_over_sequences_without_tokens():
     layer.close()
 
 
-@pytest.mark.parametrize("shape", ["bf16-G5", "bf16-mha", "bf16-many-short", "bf16-forced-split", "f32-plain"])
+@pytest.mark.parametrize("shape", ["bf16-G5", "bf16-mha", "bf16-many-short", "bf16-many-whole", "bf16-forced-split", "f32-plain"])
 def test_decode_with_the_append_fused_in(shape):
     """ecoserve_attn_decode_append against the two separate calls on a copy of the same cache: cache and
     output must agree bit for bit, step after step (positions crossing block boundaries, contexts that end
@@ -403,8 +411,8 @@ def test_decode_with_the_append_fused_in(shape):
         model, lens = wl.ModelShape("small-f32", 4, 2, 64, 1, "f32"), [0, 15, 16, 17, 100]
     elif shape == "bf16-mha":
         model, lens = wl.ModelShape("mha", 6, 6, 128, 1, "bf16"), [0, 15, 16, 31, 32, 700]
-    elif shape == "bf16-many-short":
-        model, lens = M30, list(np.random.default_rng(49).integers(0, 100, size=800))   # many pieces per wavefront
+    elif shape in ("bf16-many-short", "bf16-many-whole"):   # many pieces per wavefront with a bound of 1000 tokens, else decoded whole
+        model, lens = M30, list(np.random.default_rng(49).integers(0, 100, size=800))
     elif shape == "bf16-forced-split":      # fixed chunks of 256 tokens: the other merge kernel carries the stores
         model, lens = M30, [0, 1, 15, 16, 255, 256, 600, 2047]
     else:
@@ -412,7 +420,8 @@ def test_decode_with_the_append_fused_in(shape):
     steps = 3
     say(f"fused append + decode, {shape}: {len(lens)} sequences, {steps} steps")
     lens = np.asarray(lens, dtype=np.int32)
-    pb, layer = _mk(model, lens + steps, seed=62)
+    bound = 1000 if shape == "bf16-many-short" else 0
+    pb, layer = _mk(model, lens + steps, seed=62, blocks=(bound + 15) // 16)
     if shape == "bf16-forced-split":
         layer.ctx.set_option(binding.OPT_DECODE_SPLIT_TOKENS, 256)
     table = dev_i32(pb.block_table)
@@ -434,10 +443,10 @@ def test_decode_with_the_append_fused_in(shape):
         ctx = ctx + 1
         want = torch.full((B, model.Hq, model.D), float("nan"), dtype=q.dtype, device="cuda")
         want_lse = torch.full((B, model.Hq), float("nan"), dtype=torch.float32, device="cuda")
-        layer.ctx.attn_decode_strided(q, layer.kc, layer.vc, table, dev_i32(ctx), want, int(ctx.max()), want_lse)
+        layer.ctx.attn_decode_strided(q, layer.kc, layer.vc, table, dev_i32(ctx), want, bound or int(ctx.max()), want_lse)
         # ... against the fused call
         out, lse = torch.full_like(want, float("nan")), torch.full_like(want_lse, float("nan"))
-        layer.ctx.attn_decode_append(q, kn, vn, kc2, vc2, table, dev_i32(ctx), out, int(ctx.max()), lse)
+        layer.ctx.attn_decode_append(q, kn, vn, kc2, vc2, table, dev_i32(ctx), out, bound or int(ctx.max()), lse)
         torch.cuda.synchronize()
         assert torch.equal(out.view(torch.uint8), want.view(torch.uint8)), f"step {step}: outputs differ"
         assert torch.equal(lse, want_lse), f"step {step}: log-sum-exp differs"

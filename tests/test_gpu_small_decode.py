@@ -11,13 +11,15 @@ from tests.parity_util import Layer, compare, compare_lse, dev_i32, say
 
 pytestmark = pytest.mark.gpu
 
-CASES = [((40, 8), [1]), ((40, 8), [16, 17, 127, 128, 129]), ((40, 8), [1024]), ((64, 8), [1025]), ((5, 1), [4097, 255, 257, 1, 513]),
+# In slices of the small-batch kernel, most of them one each (test_decode_slices.py asserts it):
+CASES = [((40, 8), [1, 513]), ((40, 8), [16, 17, 127, 128, 129, 385]), ((40, 8), [1024]), ((64, 8), [1025]), ((5, 1), [4097, 255, 257, 1, 513]),
          ((8, 1), [9000]), ((16, 1), [1023] * 3 + [2048] * 20), ((40, 8), [30] * 31 + [1024]),          # 256 (sequence, K/V head)s
-         ((40, 8), [30] * 32 + [512]),                                                                  # 264: four wavefronts each
-         ((64, 8), [17] * 60 + [1, 496, 511, 512]), ((52, 52), [100] * 9), ((3, 3), [700, 2000, 40])]
+         ((64, 8), [17] * 28 + [1, 496, 511, 512]), ((52, 52), [100, 100, 100, 400]), ((3, 3), [700, 2000, 40])]
+# decoded whole:
+WHOLE = [((40, 8), [1]), ((40, 8), [16, 17, 127, 128, 129]), ((40, 8), [30] * 32 + [512]), ((64, 8), [17] * 60 + [1, 496, 511, 512]), ((52, 52), [100] * 9)]
 
 
-@pytest.mark.parametrize("heads,lens", CASES, ids=[f"{h[0]}x{h[1]}-B{len(n)}-L{max(n)}" for h, n in CASES])
+@pytest.mark.parametrize("heads,lens", CASES + WHOLE, ids=[f"{h[0]}x{h[1]}-B{len(n)}-L{max(n)}" for h, n in CASES + WHOLE])
 def test_small_decode_batches(heads, lens):
     model = wl.ModelShape("small", heads[0], heads[1], 128, 1, "bf16")
     lens = np.asarray(lens, dtype=np.int32)
@@ -48,10 +50,11 @@ def test_small_decode_batches(heads, lens):
     layer.close()
 
 
-@pytest.mark.parametrize("lens,bound", [([9000, 20], 16), ([30] * 32 + [4200], 512)], ids=["eight-wavefronts", "four-wavefronts"])
+@pytest.mark.parametrize("lens,bound", [([9000, 20], 600), ([9000, 20], 16), ([30] * 32 + [4200], 512)], ids=["eight-wavefronts", "whole-by-one", "four-wavefronts"])
 def test_a_bound_on_the_lengths_that_is_too_low_costs_time_only(lens, bound):
     """max_ctx_len is to be an upper bound; the persistent kernel never used it, and where this kernel's grid ends short of a
-    context its last slice takes the rest: more blocks than the 64 ids a wavefront holds, so it walks them in windows."""
+    context its last slice takes the rest: more blocks than the 64 ids a wavefront holds, so it walks them in windows, as does the
+    kernel for whole contexts."""
     model = wl.ModelShape("small", 40, 8, 128, 1, "bf16")
     lens = np.asarray(lens, dtype=np.int32)
     pb = wl.prefill_batch(model, lens, 56)
@@ -65,7 +68,7 @@ def test_a_bound_on_the_lengths_that_is_too_low_costs_time_only(lens, bound):
     layer.close()
 
 
-@pytest.mark.parametrize("lens", [[300, 40], [3000, 40]], ids=["one-slice", "slices"])
+@pytest.mark.parametrize("lens", [[300, 40], [700, 40], [3000, 40]], ids=["whole", "one-slice", "slices"])
 def test_infinite_values_reach_only_their_own_elements(lens):
     """Infinite V elements (the weights' remainders are zero for some keys, and must not make them NaN), one of them in the token
     that the fused append brings: infinite there, elsewhere as the plain kernels have it."""
