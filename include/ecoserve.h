@@ -114,8 +114,9 @@ enum {
    * differ by several percent and finish together only with unequal shares).  Results stay
    * within the tolerance of the split-context merge but are no longer bit-identical from call
    * to call, because the cut points move with the measurements.  Batches that a single launch takes
-   * (small ones, and those whose contexts are not cut: up to 32000 tokens per compute unit, counted as
-   * B * Hkv * max_ctx_len) have no shares, and their results are bit-identical from call to call either way.
+   * (small ones, and those of contexts too short to be cut) have no shares; which these are follows from B,
+   * num_kv_heads, max_ctx_len and the device's size, and is no promise: identical bits from call to call are
+   * promised with the option off.
    * 0 (default): equal shares, bit-reproducible. */
   ECOSERVE_OPT_DECODE_ADAPTIVE = 4,
   /* 1: consecutive ecoserve_attn_prefill calls (bf16, head size 128) that pass the same cu_q,
