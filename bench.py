@@ -742,7 +742,7 @@ def time_decode_batch(E: Env, name, db, layers=4, warm_ms=60.0, timed_ms=60.0):
     by = acc.decode_bytes(db.ctx_len, m.Hq, m.Hkv, m.D, m.bs)
     rate = by / (ms / n * 1e-3) / 1e9
     ctx.close()
-    return {"workload": name, "kernel": "decode_mfma_kernel", "avg_launch_us": ms / n * 1e3, "launches": n,
+    return {"workload": name, "kernel": "the decode call's attention launch (csrc/decode_slices.h says which kernel has the batch)", "avg_launch_us": ms / n * 1e3, "launches": n,
             "algorithmic_bytes_per_launch": by, "GBps": rate, "frac_of_hbm_peak": rate / acc.PEAK_HBM_GBPS}
 
 
@@ -847,7 +847,7 @@ def sweep() -> int:
         fl = acc.prefill_flops_causal(pb.q_len, m.Hq, m.D)
         tf = fl / (ms / n * 1e-3) / 1e12
         ab = acc.append_bytes(pb.T, m.Hkv, m.D)
-        rows.append({"workload": name, "kernel": "prefill_mfma_kernel", "avg_launch_us": ms / n * 1e3, "launches": n,
+        rows.append({"workload": name, "kernel": "the prefill call's attention launch (csrc/prefill_short.h says which kernel has the batch)", "avg_launch_us": ms / n * 1e3, "launches": n,
                      "algorithmic_flops_per_launch": fl, "TFLOPs": tf, "frac_of_bf16_peak": tf / acc.PEAK_BF16_TFLOPS,
                      "append_us": ams / an * 1e3, "append_GBps": ab / (ams / an * 1e-3) / 1e9})
         ctx.close()

@@ -5,8 +5,8 @@
 //
 // Why: a call on a small batch keeps the GPU busy for 4 to 8 us, and the way through ctypes took the host 5.3 to 5.9 before the
 // launch, of which 2 to 3 were a method call into the tensor per address and dimension; here it is 0.8 to 1.  Launches included, the
-// host takes 56 us for 16 decode calls on one sequence (111 before), 107 us for 16 times append and prefill of one short prompt (185
-// before; these passes are bound by the host no more: 188.7 -> 127.2 us back to back, 126.2 replayed from a graph).
+// host takes 64 us for 16 decode calls on one sequence (111 before; the device 131), 134 us for 16 times append and prefill of one short
+// prompt (185 before), about as long as the device (132 replayed from a graph): 188 -> 132 to 147 us back to back.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 

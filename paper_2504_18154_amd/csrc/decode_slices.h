@@ -176,7 +176,7 @@ constexpr bool decode_short_stream(int64_t pairs, int32_t max_ctx_len) { return 
 //   Else uniform slices if all workgroups run at once, one of eight wavefronts per CU (us per call persistent / here: 16 x 1000
 //   tokens 20.7 / 14.1).
 //   Else balanced slices for two workgroups of four wavefronts per CU, all of which run at once too, with as many to spare, up
-//   to 300 MB (persistent / here: 40 x 100..1000 27.2 / 24.6, 40 x 600 29.8 / 24.4, 40 x 20..2000 25.1 / 21.2, 28 x 100..3000 37.5 /
+//   to 300 MB (persistent / here: 40 x 100..1000 27.2 / 24.6, 40 x 20..2000 25.1 / 21.2, 28 x 100..3000 37.5 /
 //   33.5, 24 x 100..3000 33.0 / 30.2, 16 query heads on 4, 64 x 100..2000 31.9 / 28.3; 36 x 1500 49.0 / 49.0, 40 x 2000 65.3 / 66.1, 24 x
 //   4000 74 / 80; with nothing to spare 64 x 20..2000 33.7 / 39.2; three workgroups and more per CU 40 x 100..1000 28.5).
 //   One context too long for the first of these rules comes here too (1 x 40000 52.3 / 43.5, 1 x 75000 75.1 / 64.4; 8 on 1, 1 x 300000 226 / 60,

@@ -34,7 +34,8 @@ constexpr int64_t kShortMostKeys = 1024;  // a wavefront's walk: the 64 block id
 // x 180 15.0 / 16.5; 16 on 4, 19 x 375 35.9 / 44.0; 40 on 8, 15 385 tokens of 128..4096 504 / 551.  64 rows halve that
 // traffic, 32 fill the chip with half the rows (40 on 8, 226 x 12: 20.7 with 32, 22.6 with 64; 446 x 80 308 / 251).
 //   Of those 320 batches 228 take the new way: 0.71 of the time on average where the list is made, one 7% slower (8 on 1, 84 x 16 behind up
-// to 170: 9.4 / 10.1), the rest no more than 1%; 0.52 where each call makes its own.
+// to 170: 9.4 / 10.1), the rest no more than 1%; 0.52 where each call makes its own.  Of 4529 of the random ones, 0.62 with 32 rows and 0.73 with 64; of the latter
+// 723 eleven are 4 to 21% slower (lengths all equal and a few rows above a multiple of 64: 52 on 52, 39 x 66 behind ~88 53.9 / 65.2).
 inline PrefillShort prefill_short(int64_t B, int64_t T, int64_t Hq, int64_t Hkv, int64_t max_ctx, int64_t num_cu) {
   const int64_t tiles = (T * (Hq / Hkv) / 32 + B) * Hkv, wgs = 2 * num_cu;  // tiles of 32 rows, upper bound
   if (tiles >= (int64_t)1 << 30) return PrefillShort::kNo;
