@@ -190,8 +190,8 @@ __global__ __launch_bounds__(kWaves * 64, kWaves > 1 || NC > 1 ? 2 : 3) void pre
 #pragma unroll
       for (int dt = 0; dt < 4; ++dt) {
         vf[u][dt] = __builtin_bit_cast(bf16x8, __builtin_bit_cast(u32x4, vf[u][dt]) & keep);
-        // (whole from here on: joined with the other path element by element, the compiler lost track of some, and gave their registers
-        // to other values while the products still read them)
+        // (whole from here on, and not joined with the other path element by element.  In all three instances the registers that are cleared are
+        // those that the products read, and nothing writes to them between)
         asm volatile("" : "+v"(vf[u][dt]));
       }
     }
