@@ -157,6 +157,7 @@ def _ptr(t):
 def attn_decode_noalloc(layout: Layout, q, k_cache, v_cache, block_table, ctx_len, out, max_ctx_len, lse=None,
                         device: int = 0) -> int:
     """ecoserve_attn_decode without a context and without any allocation; returns the status code."""
+    max_ctx_len = int(max_ctx_len)
     if type(layout) is Layout:
         status = _fast.attn_decode_noalloc(device, ctypes.addressof(layout), q, k_cache, v_cache, block_table, ctx_len, out, max_ctx_len, lse)
         if status >= 0:
@@ -164,7 +165,7 @@ def attn_decode_noalloc(layout: Layout, q, k_cache, v_cache, block_table, ctx_le
     return int(_lib.ecoserve_attn_decode_noalloc(int(device), ctypes.byref(layout), _ptr(q), _ptr(k_cache),
                                                  _ptr(v_cache), _ptr(block_table), block_table.shape[1],
                                                  _ptr(ctx_len), _ptr(out), _ptr(lse), ctx_len.numel(),
-                                                 int(max_ctx_len), _stream()))
+                                                 max_ctx_len, _stream()))
 
 
 def _row_stride(t) -> int:
@@ -244,6 +245,7 @@ class Context:
 
     # ---- the three hot calls -------------------------------------------------------------
     def kv_append(self, k_cache, v_cache, k_new, v_new, cu_q, ctx_before, block_table, max_new_len=None):
+        max_new_len = None if max_new_len is None else int(max_new_len)
         status = _fast.kv_append(self._address, k_cache, v_cache, k_new, v_new, cu_q, ctx_before, block_table, max_new_len, self._kv_row)
         if status >= 0:
             return _check(status, "ecoserve_kv_append")
@@ -253,9 +255,10 @@ class Context:
             max_new_len = T
         _check(_lib.ecoserve_kv_append(self._h, _ptr(k_cache), _ptr(v_cache), _ptr(k_new), _ptr(v_new), _ptr(cu_q),
                                        _ptr(ctx_before), _ptr(block_table), block_table.shape[1], B,
-                                       T, int(max_new_len), _stream()), "ecoserve_kv_append")
+                                       T, max_new_len, _stream()), "ecoserve_kv_append")
 
     def attn_prefill(self, q, k_cache, v_cache, cu_q, ctx_before, block_table, out, lse=None, max_q_len=None):
+        max_q_len = None if max_q_len is None else int(max_q_len)
         status = _fast.attn_prefill(self._address, q, k_cache, v_cache, cu_q, ctx_before, block_table, out, lse, max_q_len, self._q_row)
         if status >= 0:
             return _check(status, "ecoserve_attn_prefill")
@@ -265,11 +268,12 @@ class Context:
             max_q_len = T
         _check(_lib.ecoserve_attn_prefill(self._h, _ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(cu_q),
                                           _ptr(ctx_before), _ptr(block_table), block_table.shape[1], _ptr(out),
-                                          _ptr(lse), B, T, int(max_q_len), _stream()),
+                                          _ptr(lse), B, T, max_q_len, _stream()),
                "ecoserve_attn_prefill")
 
     # the same on views into wider rows (e.g. slices of a fused projection output [T, Hq + 2 Hkv, D])
     def kv_append_strided(self, k_cache, v_cache, k_new, v_new, cu_q, ctx_before, block_table, max_new_len=None):
+        max_new_len = None if max_new_len is None else int(max_new_len)
         status = _fast.kv_append(self._address, k_cache, v_cache, k_new, v_new, cu_q, ctx_before, block_table, max_new_len, 0)
         if status >= 0:
             return _check(status, "ecoserve_kv_append_strided")
@@ -282,11 +286,12 @@ class Context:
             raise ValueError("k_new and v_new must have the same row stride")
         _check(_lib.ecoserve_kv_append_strided(self._h, _ptr(k_cache), _ptr(v_cache), _ptr(k_new), _ptr(v_new),
                                                new_stride, _ptr(cu_q), _ptr(ctx_before), _ptr(block_table),
-                                               block_table.shape[1], B, T, int(max_new_len),
+                                               block_table.shape[1], B, T, max_new_len,
                                                _stream()), "ecoserve_kv_append_strided")
 
     def attn_prefill_strided(self, q, k_cache, v_cache, cu_q, ctx_before, block_table, out, lse=None,
                              max_q_len=None):
+        max_q_len = None if max_q_len is None else int(max_q_len)
         status = _fast.attn_prefill(self._address, q, k_cache, v_cache, cu_q, ctx_before, block_table, out, lse, max_q_len, 0)
         if status >= 0:
             return _check(status, "ecoserve_attn_prefill_strided")
@@ -297,20 +302,22 @@ class Context:
         _check(_lib.ecoserve_attn_prefill_strided(self._h, _ptr(q), _row_stride(q), _ptr(k_cache), _ptr(v_cache),
                                                   _ptr(cu_q), _ptr(ctx_before), _ptr(block_table),
                                                   block_table.shape[1], _ptr(out), _ptr(lse), B, T,
-                                                  int(max_q_len), _stream()), "ecoserve_attn_prefill_strided")
+                                                  max_q_len, _stream()), "ecoserve_attn_prefill_strided")
 
     def attn_decode_strided(self, q, k_cache, v_cache, block_table, ctx_len, out, max_ctx_len, lse=None):
+        max_ctx_len = int(max_ctx_len)
         status = _fast.attn_decode(self._address, q, k_cache, v_cache, block_table, ctx_len, out, max_ctx_len, lse, 0)
         if status >= 0:
             return _check(status, "ecoserve_attn_decode_strided")
         B = ctx_len.numel()
         _check(_lib.ecoserve_attn_decode_strided(self._h, _ptr(q), _row_stride(q), _ptr(k_cache), _ptr(v_cache),
                                                  _ptr(block_table), block_table.shape[1], _ptr(ctx_len),
-                                                 _ptr(out), _ptr(lse), B, int(max_ctx_len), _stream()),
+                                                 _ptr(out), _ptr(lse), B, max_ctx_len, _stream()),
                "ecoserve_attn_decode_strided")
 
     def attn_decode_append(self, q, k_new, v_new, k_cache, v_cache, block_table, ctx_len, out, max_ctx_len, lse=None):
         """Decode with the append of the step's one new token per sequence fused in (ctx_len counts it)."""
+        max_ctx_len = int(max_ctx_len)
         status = _fast.attn_decode_append(self._address, q, k_new, v_new, k_cache, v_cache, block_table, ctx_len, out, max_ctx_len, lse)
         if status >= 0:
             return _check(status, "ecoserve_attn_decode_append")
@@ -321,16 +328,17 @@ class Context:
         _check(_lib.ecoserve_attn_decode_append(self._h, _ptr(q), _row_stride(q), _ptr(k_new), _ptr(v_new),
                                                 new_stride, _ptr(k_cache), _ptr(v_cache), _ptr(block_table),
                                                 block_table.shape[1], _ptr(ctx_len), _ptr(out), _ptr(lse), B,
-                                                int(max_ctx_len), _stream()), "ecoserve_attn_decode_append")
+                                                max_ctx_len, _stream()), "ecoserve_attn_decode_append")
 
     def attn_decode(self, q, k_cache, v_cache, block_table, ctx_len, out, max_ctx_len, lse=None):
+        max_ctx_len = int(max_ctx_len)
         status = _fast.attn_decode(self._address, q, k_cache, v_cache, block_table, ctx_len, out, max_ctx_len, lse, self._q_row)
         if status >= 0:
             return _check(status, "ecoserve_attn_decode")
         B = ctx_len.numel()
         _check(_lib.ecoserve_attn_decode(self._h, _ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(block_table),
                                          block_table.shape[1], _ptr(ctx_len), _ptr(out), _ptr(lse), B,
-                                         int(max_ctx_len), _stream()), "ecoserve_attn_decode")
+                                         max_ctx_len, _stream()), "ecoserve_attn_decode")
 
     # ---- debugging / profiling -----------------------------------------------------------
     def debug_validate(self, cu_q, ctx_total, block_table):

@@ -29,137 +29,147 @@ struct Entries {
   decltype(&ecoserve_attn_decode_noalloc) noalloc;
 } entry;
 
-struct NotTaken {};  // thrown for arguments that are binding.py's business
+// Reads the arguments of a call.  What is binding.py's business is noted, and not thrown: an exception takes 2.5 us, half of what the
+// other way takes for such a call.
+struct Arguments {
+  PyObject* const* a;
+  bool taken = true;
 
-const at::Tensor& tensor(PyObject* o) {
-  if (!THPVariable_CheckExact(o)) throw NotTaken();
-  return THPVariable_Unpack(o);
-}
-void* address(PyObject* o) { return o == Py_None ? nullptr : tensor(o).data_ptr(); }
-template <typename T>
-T* as(PyObject* o) {
-  return static_cast<T*>(address(o));
-}
+  const at::Tensor* tensor(int i) {
+    if (THPVariable_CheckExact(a[i])) return &THPVariable_Unpack(a[i]);
+    taken = false;
+    return nullptr;
+  }
+  void* address(int i) {
+    if (a[i] == Py_None) return nullptr;
+    const at::Tensor* const t = tensor(i);
+    return t ? t->data_ptr() : nullptr;
+  }
+  template <typename T>
+  T* as(int i) {
+    return static_cast<T*>(address(i));
+  }
+  int32_t narrow(int64_t n) {
+    if (n < std::numeric_limits<int32_t>::min() || n > std::numeric_limits<int32_t>::max()) taken = false;
+    return (int32_t)n;
+  }
+  int64_t integer(int i) {
+    if (!PyLong_CheckExact(a[i])) return taken = false;
+    int overflow = 0;
+    const long long n = PyLong_AsLongLongAndOverflow(a[i], &overflow);
+    if (overflow) taken = false;
+    return n;
+  }
+  int32_t narrow_integer(int i) { return narrow(integer(i)); }
+  void* handle(int i) { return reinterpret_cast<void*>((uintptr_t)integer(i)); }
+  int32_t size(int i, int64_t d) {
+    const at::Tensor* const t = tensor(i);
+    if (t && t->dim() > d) return narrow(t->size(d));
+    return taken = false;
+  }
+  int32_t numel(int i) {
+    const at::Tensor* const t = tensor(i);
+    return t ? narrow(t->numel()) : 0;
+  }
+  // Elements between consecutive tokens of a [tokens, heads, D] tensor or view whose heads are contiguous.
+  int64_t row_stride(int i) {
+    const at::Tensor* const t = tensor(i);
+    if (!t || t->dim() != 3 || t->stride(2) != 1 || t->stride(1) != t->size(2)) return taken = false;
+    return t->size(0) > 1 ? t->stride(0) : t->size(1) * t->size(2);
+  }
+  int32_t or_all(int i, int32_t all) { return a[i] == Py_None ? all : narrow_integer(i); }
+};
 
-int32_t narrow(int64_t n) {
-  if (n < std::numeric_limits<int32_t>::min() || n > std::numeric_limits<int32_t>::max()) throw NotTaken();
-  return (int32_t)n;
-}
-int64_t integer(PyObject* o) {
-  int overflow = 0;
-  if (!PyLong_CheckExact(o)) throw NotTaken();
-  const long long n = PyLong_AsLongLongAndOverflow(o, &overflow);
-  if (overflow) throw NotTaken();
-  return n;
-}
-void* handle(PyObject* o) { return reinterpret_cast<void*>((uintptr_t)integer(o)); }
-
-int32_t size(PyObject* o, int64_t d) {
-  const at::Tensor& t = tensor(o);
-  if (t.dim() <= d) throw NotTaken();
-  return narrow(t.size(d));
-}
-int32_t numel(PyObject* o) { return narrow(tensor(o).numel()); }
-// Elements between consecutive tokens of a [tokens, heads, D] tensor or view whose heads are contiguous.
-int64_t row_stride(PyObject* o) {
-  const at::Tensor& t = tensor(o);
-  if (t.dim() != 3 || t.stride(2) != 1 || t.stride(1) != t.size(2)) throw NotTaken();
-  return t.size(0) > 1 ? t.stride(0) : t.size(1) * t.size(2);
-}
-int32_t or_all(PyObject* most, int32_t all) { return most == Py_None ? all : narrow(integer(most)); }
-void* stream() { return c10::hip::getCurrentHIPStream().stream(); }
-
-// Runs f with `want` arguments at hand; -1: not taken.
+// Runs f on `want` arguments; -1: not taken.
 template <typename F>
-PyObject* guarded(Py_ssize_t n, Py_ssize_t want, F f) {
+PyObject* guarded(PyObject* const* a, Py_ssize_t n, Py_ssize_t want, F f) {
   int status = -1;
   try {
-    if (n == want) status = f();
-  } catch (...) {  // (NotTaken, and what torch throws for a tensor without storage: the other way raises it again, for the caller)
+    Arguments in{a};
+    if (n == want) status = f(in);
+  } catch (...) {  // (what torch throws for a tensor without storage: the other way raises it again, for the caller)
     status = -1;
   }
   return PyLong_FromLong(status);
 }
+// The call itself on the current stream, without the interpreter's lock, if all its arguments are taken.
 template <typename F>
-int unlocked(F f) {
+int unlocked(const Arguments& in, F f) {
+  if (!in.taken) return -1;
+  void* const s = c10::hip::getCurrentHIPStream().stream();
   struct Unlocked {
     PyThreadState* const state = PyEval_SaveThread();
     ~Unlocked() { PyEval_RestoreThread(state); }
   } scope;
-  return f();
+  return f(s);
 }
 
 // (handle, k_cache, v_cache, k_new, v_new, cu_q, ctx_before, block_table, max_new_len, row stride of a packed array or 0: the tensors')
 PyObject* kv_append(PyObject*, PyObject* const* a, Py_ssize_t n) {
-  return guarded(n, 10, [&] {
-    auto* const c = static_cast<ecoserve_ctx*>(handle(a[0]));
-    void *const kc = address(a[1]), *const vc = address(a[2]), *const kn = address(a[3]), *const vn = address(a[4]);
-    const auto *cu = as<const int32_t>(a[5]), *before = as<const int32_t>(a[6]), *table = as<const int32_t>(a[7]);
-    const int32_t B = numel(a[6]), T = size(a[3], 0), width = size(a[7], 1), most = or_all(a[8], T);
-    int64_t stride = integer(a[9]);
+  return guarded(a, n, 10, [](Arguments& in) {
+    auto* const c = static_cast<ecoserve_ctx*>(in.handle(0));
+    void *const kc = in.address(1), *const vc = in.address(2), *const kn = in.address(3), *const vn = in.address(4);
+    const auto *cu = in.as<const int32_t>(5), *before = in.as<const int32_t>(6), *table = in.as<const int32_t>(7);
+    const int32_t B = in.numel(6), T = in.size(3, 0), width = in.size(7, 1), most = in.or_all(8, T);
+    int64_t stride = in.integer(9);
     if (stride == 0) {
-      stride = row_stride(a[3]);
-      if (stride != row_stride(a[4])) throw NotTaken();
+      stride = in.row_stride(3);
+      if (stride != in.row_stride(4)) in.taken = false;
     }
-    void* const s = stream();
-    return unlocked([&] { return entry.append(c, kc, vc, kn, vn, stride, cu, before, table, width, B, T, most, s); });
+    return unlocked(in, [&](void* s) { return entry.append(c, kc, vc, kn, vn, stride, cu, before, table, width, B, T, most, s); });
   });
 }
 
 // (handle, q, k_cache, v_cache, cu_q, ctx_before, block_table, out, lse, max_q_len, row stride of a packed array or 0: the tensor's)
 PyObject* attn_prefill(PyObject*, PyObject* const* a, Py_ssize_t n) {
-  return guarded(n, 11, [&] {
-    auto* const c = static_cast<ecoserve_ctx*>(handle(a[0]));
-    void *const q = address(a[1]), *const kc = address(a[2]), *const vc = address(a[3]), *const out = address(a[7]);
-    const auto *cu = as<const int32_t>(a[4]), *before = as<const int32_t>(a[5]), *table = as<const int32_t>(a[6]);
-    auto* const lse = as<float>(a[8]);
-    const int32_t B = numel(a[5]), T = size(a[1], 0), width = size(a[6], 1), most = or_all(a[9], T);
-    const int64_t packed = integer(a[10]), stride = packed ? packed : row_stride(a[1]);
-    void* const s = stream();
-    return unlocked([&] { return entry.prefill(c, q, stride, kc, vc, cu, before, table, width, out, lse, B, T, most, s); });
+  return guarded(a, n, 11, [](Arguments& in) {
+    auto* const c = static_cast<ecoserve_ctx*>(in.handle(0));
+    void *const q = in.address(1), *const kc = in.address(2), *const vc = in.address(3), *const out = in.address(7);
+    const auto *cu = in.as<const int32_t>(4), *before = in.as<const int32_t>(5), *table = in.as<const int32_t>(6);
+    auto* const lse = in.as<float>(8);
+    const int32_t B = in.numel(5), T = in.size(1, 0), width = in.size(6, 1), most = in.or_all(9, T);
+    const int64_t packed = in.integer(10), stride = packed ? packed : in.row_stride(1);
+    return unlocked(in, [&](void* s) { return entry.prefill(c, q, stride, kc, vc, cu, before, table, width, out, lse, B, T, most, s); });
   });
 }
 
 // (handle, q, k_cache, v_cache, block_table, ctx_len, out, max_ctx_len, lse, row stride of a packed array or 0: the tensor's)
 PyObject* attn_decode(PyObject*, PyObject* const* a, Py_ssize_t n) {
-  return guarded(n, 10, [&] {
-    auto* const c = static_cast<ecoserve_ctx*>(handle(a[0]));
-    void *const q = address(a[1]), *const kc = address(a[2]), *const vc = address(a[3]), *const out = address(a[6]);
-    const auto *table = as<const int32_t>(a[4]), *len = as<const int32_t>(a[5]);
-    auto* const lse = as<float>(a[8]);
-    const int32_t B = numel(a[5]), width = size(a[4], 1), most = narrow(integer(a[7]));
-    const int64_t packed = integer(a[9]), stride = packed ? packed : row_stride(a[1]);
-    void* const s = stream();
-    return unlocked([&] { return entry.decode(c, q, stride, kc, vc, table, width, len, out, lse, B, most, s); });
+  return guarded(a, n, 10, [](Arguments& in) {
+    auto* const c = static_cast<ecoserve_ctx*>(in.handle(0));
+    void *const q = in.address(1), *const kc = in.address(2), *const vc = in.address(3), *const out = in.address(6);
+    const auto *table = in.as<const int32_t>(4), *len = in.as<const int32_t>(5);
+    auto* const lse = in.as<float>(8);
+    const int32_t B = in.numel(5), width = in.size(4, 1), most = in.narrow_integer(7);
+    const int64_t packed = in.integer(9), stride = packed ? packed : in.row_stride(1);
+    return unlocked(in, [&](void* s) { return entry.decode(c, q, stride, kc, vc, table, width, len, out, lse, B, most, s); });
   });
 }
 
 // (handle, q, k_new, v_new, k_cache, v_cache, block_table, ctx_len, out, max_ctx_len, lse)
 PyObject* attn_decode_append(PyObject*, PyObject* const* a, Py_ssize_t n) {
-  return guarded(n, 11, [&] {
-    auto* const c = static_cast<ecoserve_ctx*>(handle(a[0]));
-    const int64_t stride = row_stride(a[1]), fresh = row_stride(a[2]);
-    if (fresh != row_stride(a[3])) throw NotTaken();
-    void *const q = address(a[1]), *const kn = address(a[2]), *const vn = address(a[3]), *const kc = address(a[4]), *const vc = address(a[5]), *const out = address(a[8]);
-    const auto *table = as<const int32_t>(a[6]), *len = as<const int32_t>(a[7]);
-    auto* const lse = as<float>(a[10]);
-    const int32_t B = numel(a[7]), width = size(a[6], 1), most = narrow(integer(a[9]));
-    void* const s = stream();
-    return unlocked([&] { return entry.decode_append(c, q, stride, kn, vn, fresh, kc, vc, table, width, len, out, lse, B, most, s); });
+  return guarded(a, n, 11, [](Arguments& in) {
+    auto* const c = static_cast<ecoserve_ctx*>(in.handle(0));
+    const int64_t stride = in.row_stride(1), fresh = in.row_stride(2);
+    if (fresh != in.row_stride(3)) in.taken = false;
+    void *const q = in.address(1), *const kn = in.address(2), *const vn = in.address(3), *const kc = in.address(4), *const vc = in.address(5), *const out = in.address(8);
+    const auto *table = in.as<const int32_t>(6), *len = in.as<const int32_t>(7);
+    auto* const lse = in.as<float>(10);
+    const int32_t B = in.numel(7), width = in.size(6, 1), most = in.narrow_integer(9);
+    return unlocked(in, [&](void* s) { return entry.decode_append(c, q, stride, kn, vn, fresh, kc, vc, table, width, len, out, lse, B, most, s); });
   });
 }
 
 // (device, address of the layout, q, k_cache, v_cache, block_table, ctx_len, out, max_ctx_len, lse)
 PyObject* attn_decode_noalloc(PyObject*, PyObject* const* a, Py_ssize_t n) {
-  return guarded(n, 10, [&] {
-    const int32_t device = narrow(integer(a[0]));
-    const auto* const layout = static_cast<const ecoserve_layout*>(handle(a[1]));
-    void *const q = address(a[2]), *const kc = address(a[3]), *const vc = address(a[4]), *const out = address(a[7]);
-    const auto *table = as<const int32_t>(a[5]), *len = as<const int32_t>(a[6]);
-    auto* const lse = as<float>(a[9]);
-    const int32_t B = numel(a[6]), width = size(a[5], 1), most = narrow(integer(a[8]));
-    void* const s = stream();
-    return unlocked([&] { return entry.noalloc(device, layout, q, kc, vc, table, width, len, out, lse, B, most, s); });
+  return guarded(a, n, 10, [](Arguments& in) {
+    const int32_t device = in.narrow_integer(0);
+    const auto* const layout = static_cast<const ecoserve_layout*>(in.handle(1));
+    void *const q = in.address(2), *const kc = in.address(3), *const vc = in.address(4), *const out = in.address(7);
+    const auto *table = in.as<const int32_t>(5), *len = in.as<const int32_t>(6);
+    auto* const lse = in.as<float>(9);
+    const int32_t B = in.numel(6), width = in.size(5, 1), most = in.narrow_integer(8);
+    return unlocked(in, [&](void* s) { return entry.noalloc(device, layout, q, kc, vc, table, width, len, out, lse, B, most, s); });
   });
 }
 

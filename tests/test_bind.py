@@ -107,3 +107,29 @@ def test_a_library_for_another_torch_is_not_current(monkeypatch):
     assert build.is_current() and build._bind_fits() in fast.__doc__
     monkeypatch.setattr(torch, "__version__", "0.0.0")
     assert not build.is_current()
+
+
+@pytest.mark.parametrize("bound", [np.int32(40), np.int64(40), torch.tensor(40), 40.0, 40], ids=["int32", "int64", "tensor", "float", "int"])
+def test_bounds_that_are_no_plain_integers_take_the_usual_way(bound, monkeypatch):
+    """lens.max() of an array is a bound like any other: the hot calls hand it over as an integer."""
+    class Noted:
+        def __getattr__(self, name):
+            return lambda *args: seen.update({name: args}) or 0
+
+    monkeypatch.setattr(binding, "_fast", Noted())
+    c = object.__new__(binding.Context)
+    c._address, c._h, c._q_row, c._kv_row = 77, None, 128, 32
+    at = {"kv_append": 8, "attn_prefill": 9, "attn_decode": 7, "attn_decode_append": 9, "attn_decode_noalloc": 8}
+    t = [None] * 7
+    for call, name in ((lambda: c.kv_append(*t, bound), "kv_append"), (lambda: c.kv_append_strided(*t, bound), "kv_append"),
+                       (lambda: c.attn_prefill(*t, None, bound), "attn_prefill"), (lambda: c.attn_prefill_strided(*t, None, bound), "attn_prefill"),
+                       (lambda: c.attn_decode(*t[:6], bound), "attn_decode"), (lambda: c.attn_decode_strided(*t[:6], bound), "attn_decode"),
+                       (lambda: c.attn_decode_append(*t, None, bound), "attn_decode_append"),
+                       (lambda: binding.attn_decode_noalloc(binding.Layout(), *t[:6], bound), "attn_decode_noalloc")):
+        seen = {}
+        call()
+        assert type(seen[name][at[name]]) is int and seen[name][at[name]] == 40, name
+    seen = {}
+    c.kv_append(*t)
+    c.attn_prefill(*t)
+    assert seen["kv_append"][8] is None and seen["attn_prefill"][9] is None   # (all the tokens)
