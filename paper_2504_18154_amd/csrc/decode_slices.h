@@ -128,8 +128,8 @@ inline SmallDecode any_decode(int32_t B, int32_t Hkv, int32_t D, int32_t elem_by
 // For (bf16, 128): wavefronts per (sequence, K/V head) with which decode_short_kernel takes a batch whole, 0 if it does not.  The host knows the longest
 // context, not the others, and walking it is the launch's time at least (20 us for 1700 tokens by four wavefronts) however short those are: the line lies
 // where no lengths make it cost more than a few percent.  From 18800 random batches of seven head shapes, up to 9000 tokens: lengths equal, uniform from 1/2, 1/8 and 1/64 of the
-// longest on, lognormal around 1/3, 1/6 and 1/10 of it, and one sequence in 16 ten times as long as the others.  Of the time of the other kernels (their
-// mean, the worst):
+// longest on, lognormal around 1/3, 1/6 and 1/10 of it, and one sequence in 16 ten times as long as the others.  Of the time of the other kernels, with
+// the append fused in (mean, the worst; of 7700 without the append 0.79, 1.11, of 3600 against the persistent kernel's measured shares 0.70, 1.05):
 //   Few (sequence, K/V head)s, up to where contexts cut into slices, or eight wavefronts to a context, end sooner: 0.80, 0.97.
 //   129 to 256, up to 384 tokens: 0.89, 1.00.  Beyond, slices even out ragged lengths: 385 to 512 0.99, 1.11; 513 to 1024 1.02, 1.33; 1025 to 4096 1.02, 2.15
 // (0.87 where all are as long, 1.22 where most are a sixth and less of it).

@@ -23,8 +23,8 @@ constexpr int64_t kShortMostKeys = 1024;  // a wavefront's walk: the 64 block id
 // 27.6 / 39.8; 8 on 1, 17 x 20 + 2800 22.5 / 24.7; half that where the tiles of a head do not stay with one XCD: 52 on 52, 3 x 66 + 1350 32.3 / 42.2).  Contexts
 // of one group of 32 keys have none to share (16 tokens 4.4 against 4.2).  To 1.25 times that many workgroups up to 1536 tokens, and to 1.56 times
 // between 256 and 1024 where the tiles of a head stay with one XCD.  Not in the longest contexts, and not beyond 1.25 times, for more than 16 sequences,
-// whose K and V come from memory and whose tiles end at many lengths (64 on 8, 17 sequences of 56 to 1652 tokens, eight layers in turn 21.9 / 32.8, one again and again 26.6 /
-// 21.2; 16 on 4, 21 up to 1152 26.8 / 29.0; 8 on 1, 81 of up to 672, 1.5 rounds, 26.7 / 29.0).  Of 8755 random batches of seven head shapes (lengths equal, uniform, lognormal, one in 16 ten times the others), of
+// whose K and V come from memory and whose tiles end at many lengths (64 on 8, 17 sequences of 56 to 1652 tokens, eight layers in turn 21.9 / 32.8, one again and again 21.2
+// here; 16 on 4, 21 up to 1152 26.8 / 29.0; 8 on 1, 81 of up to 672, 1.5 rounds, 26.7 / 29.0).  Of 8755 random batches of seven head shapes (lengths equal, uniform, lognormal, one in 16 ten times the others), of
 // the persistent kernel's time on average, the worst: one round 0.64, 1.22; to 1.25 0.74, 1.22; to 1.56 0.77, 1.10; 20 of 8506 more than 4% slower.  What is left to that
 // kernel: 17 sequences and more beyond 1536 tokens (in 1.25 rounds 1024) 0.86, 1.50; the last, 52 on 52, 0.87, 1.18.
 //   Rows: no list and no change of tiles, but K and V come once per 32 or 64 rows through the first-level cache, where the
