@@ -149,7 +149,7 @@ def probe_mfma_valu(with_mfma: bool, fma_per_slot: int, exp_per_slot: int, waves
 
 # A hot call on a small batch keeps the GPU busy for 4 to 8 us, and its way through ctypes takes the host 6 to 7, launch included
 # (through _bind 3.5).  Each call below therefore asks _bind first, whose answer is the status, or -1 for arguments that it
-# leaves to the lines that follow.
+# leaves to the lines that follow; with a bound that is an integer of another type (lens.max()) it is asked again.
 def _ptr(t):
     return t.data_ptr() if t is not None else None
 
@@ -157,15 +157,16 @@ def _ptr(t):
 def attn_decode_noalloc(layout: Layout, q, k_cache, v_cache, block_table, ctx_len, out, max_ctx_len, lse=None,
                         device: int = 0) -> int:
     """ecoserve_attn_decode without a context and without any allocation; returns the status code."""
-    max_ctx_len = int(max_ctx_len)
     if type(layout) is Layout:
         status = _fast.attn_decode_noalloc(device, ctypes.addressof(layout), q, k_cache, v_cache, block_table, ctx_len, out, max_ctx_len, lse)
         if status >= 0:
             return status
+        if type(max_ctx_len) is not int:
+            return attn_decode_noalloc(layout, q, k_cache, v_cache, block_table, ctx_len, out, int(max_ctx_len), lse, device)
     return int(_lib.ecoserve_attn_decode_noalloc(int(device), ctypes.byref(layout), _ptr(q), _ptr(k_cache),
                                                  _ptr(v_cache), _ptr(block_table), block_table.shape[1],
                                                  _ptr(ctx_len), _ptr(out), _ptr(lse), ctx_len.numel(),
-                                                 max_ctx_len, _stream()))
+                                                 int(max_ctx_len), _stream()))
 
 
 def _row_stride(t) -> int:
@@ -245,10 +246,11 @@ class Context:
 
     # ---- the three hot calls -------------------------------------------------------------
     def kv_append(self, k_cache, v_cache, k_new, v_new, cu_q, ctx_before, block_table, max_new_len=None):
-        max_new_len = None if max_new_len is None else int(max_new_len)
         status = _fast.kv_append(self._address, k_cache, v_cache, k_new, v_new, cu_q, ctx_before, block_table, max_new_len, self._kv_row)
         if status >= 0:
             return _check(status, "ecoserve_kv_append")
+        if max_new_len is not None and type(max_new_len) is not int:
+            return self.kv_append(k_cache, v_cache, k_new, v_new, cu_q, ctx_before, block_table, int(max_new_len))
         B = ctx_before.numel()
         T = k_new.shape[0]
         if max_new_len is None:
@@ -258,10 +260,11 @@ class Context:
                                        T, max_new_len, _stream()), "ecoserve_kv_append")
 
     def attn_prefill(self, q, k_cache, v_cache, cu_q, ctx_before, block_table, out, lse=None, max_q_len=None):
-        max_q_len = None if max_q_len is None else int(max_q_len)
         status = _fast.attn_prefill(self._address, q, k_cache, v_cache, cu_q, ctx_before, block_table, out, lse, max_q_len, self._q_row)
         if status >= 0:
             return _check(status, "ecoserve_attn_prefill")
+        if max_q_len is not None and type(max_q_len) is not int:
+            return self.attn_prefill(q, k_cache, v_cache, cu_q, ctx_before, block_table, out, lse, int(max_q_len))
         B = ctx_before.numel()
         T = q.shape[0]
         if max_q_len is None:
@@ -273,10 +276,11 @@ class Context:
 
     # the same on views into wider rows (e.g. slices of a fused projection output [T, Hq + 2 Hkv, D])
     def kv_append_strided(self, k_cache, v_cache, k_new, v_new, cu_q, ctx_before, block_table, max_new_len=None):
-        max_new_len = None if max_new_len is None else int(max_new_len)
         status = _fast.kv_append(self._address, k_cache, v_cache, k_new, v_new, cu_q, ctx_before, block_table, max_new_len, 0)
         if status >= 0:
             return _check(status, "ecoserve_kv_append_strided")
+        if max_new_len is not None and type(max_new_len) is not int:
+            return self.kv_append_strided(k_cache, v_cache, k_new, v_new, cu_q, ctx_before, block_table, int(max_new_len))
         B = ctx_before.numel()
         T = k_new.shape[0]
         if max_new_len is None:
@@ -291,10 +295,11 @@ class Context:
 
     def attn_prefill_strided(self, q, k_cache, v_cache, cu_q, ctx_before, block_table, out, lse=None,
                              max_q_len=None):
-        max_q_len = None if max_q_len is None else int(max_q_len)
         status = _fast.attn_prefill(self._address, q, k_cache, v_cache, cu_q, ctx_before, block_table, out, lse, max_q_len, 0)
         if status >= 0:
             return _check(status, "ecoserve_attn_prefill_strided")
+        if max_q_len is not None and type(max_q_len) is not int:
+            return self.attn_prefill_strided(q, k_cache, v_cache, cu_q, ctx_before, block_table, out, lse, int(max_q_len))
         B = ctx_before.numel()
         T = q.shape[0]
         if max_q_len is None:
@@ -305,10 +310,11 @@ class Context:
                                                   max_q_len, _stream()), "ecoserve_attn_prefill_strided")
 
     def attn_decode_strided(self, q, k_cache, v_cache, block_table, ctx_len, out, max_ctx_len, lse=None):
-        max_ctx_len = int(max_ctx_len)
         status = _fast.attn_decode(self._address, q, k_cache, v_cache, block_table, ctx_len, out, max_ctx_len, lse, 0)
         if status >= 0:
             return _check(status, "ecoserve_attn_decode_strided")
+        if type(max_ctx_len) is not int:
+            return self.attn_decode_strided(q, k_cache, v_cache, block_table, ctx_len, out, int(max_ctx_len), lse)
         B = ctx_len.numel()
         _check(_lib.ecoserve_attn_decode_strided(self._h, _ptr(q), _row_stride(q), _ptr(k_cache), _ptr(v_cache),
                                                  _ptr(block_table), block_table.shape[1], _ptr(ctx_len),
@@ -317,10 +323,11 @@ class Context:
 
     def attn_decode_append(self, q, k_new, v_new, k_cache, v_cache, block_table, ctx_len, out, max_ctx_len, lse=None):
         """Decode with the append of the step's one new token per sequence fused in (ctx_len counts it)."""
-        max_ctx_len = int(max_ctx_len)
         status = _fast.attn_decode_append(self._address, q, k_new, v_new, k_cache, v_cache, block_table, ctx_len, out, max_ctx_len, lse)
         if status >= 0:
             return _check(status, "ecoserve_attn_decode_append")
+        if type(max_ctx_len) is not int:
+            return self.attn_decode_append(q, k_new, v_new, k_cache, v_cache, block_table, ctx_len, out, int(max_ctx_len), lse)
         B = ctx_len.numel()
         new_stride = _row_stride(k_new)
         if new_stride != _row_stride(v_new):
@@ -331,10 +338,11 @@ class Context:
                                                 max_ctx_len, _stream()), "ecoserve_attn_decode_append")
 
     def attn_decode(self, q, k_cache, v_cache, block_table, ctx_len, out, max_ctx_len, lse=None):
-        max_ctx_len = int(max_ctx_len)
         status = _fast.attn_decode(self._address, q, k_cache, v_cache, block_table, ctx_len, out, max_ctx_len, lse, self._q_row)
         if status >= 0:
             return _check(status, "ecoserve_attn_decode")
+        if type(max_ctx_len) is not int:
+            return self.attn_decode(q, k_cache, v_cache, block_table, ctx_len, out, int(max_ctx_len), lse)
         B = ctx_len.numel()
         _check(_lib.ecoserve_attn_decode(self._h, _ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(block_table),
                                          block_table.shape[1], _ptr(ctx_len), _ptr(out), _ptr(lse), B,
