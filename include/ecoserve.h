@@ -328,7 +328,7 @@ int ecoserve_attn_decode_append(ecoserve_ctx* ctx, const void* q, int64_t q_row_
  * hipMalloc.  No context: the layout is passed directly, and the scratch
  * memory of the launches (partial softmax states of the split contexts, the
  * launch's numbering, the list of cut sequences, merge counters) is a fixed array of
- * 16.3 MiB inside the library's device code, one copy per GPU, held until the
+ * 20.4 MiB inside the library's device code, one copy per GPU, held until the
  * process ends.  The call allocates nothing (no hipMalloc / hipFree, no
  * events), does not synchronise, and launches the same kernels as
  * ecoserve_attn_decode with its default options (persistent grid, equal
@@ -346,9 +346,9 @@ int ecoserve_attn_decode_append(ecoserve_ctx* ctx, const void* q, int64_t q_row_
  *
  * All calls on one GPU share that GPU's array: calls that overlap there (two
  * streams, two threads) race, and a race may spoil later calls too (it can
- * leave a merge counter away from zero); order them.  The array needs no
+ * leave a merge counter or a partial state away from zero); order them.  The array needs no
  * clearing between calls (a launch writes every word it later reads, and
- * leaves the counters at zero), and a call may follow a larger one.
+ * leaves the counters and states at zero), and a call may follow a larger one.
  */
 int ecoserve_attn_decode_noalloc(int device, const ecoserve_layout* layout, const void* q, const void* k_cache,
                                  const void* v_cache, const int32_t* block_table, int32_t bt_stride,

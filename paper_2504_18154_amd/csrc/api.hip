@@ -72,12 +72,49 @@ int64_t slots_needed(const ecoserve_ctx* c, int32_t* plain_splits) {
   return (int64_t)c->max_batch * c->lay.num_q_heads * *plain_splits;
 }
 
+// States that the slices of the kernels of attn_any_mfma.hip leave, as the rules in decode_slices.h cut: at most two workgroups per CU, or slices
+// of 1024 tokens, or as long as the option says.
+int64_t part_slots_needed(const ecoserve_ctx* c) {
+  const int64_t G = c->lay.num_q_heads / c->lay.num_kv_heads, few = 2 * (int64_t)c->num_cu * G;
+  if (c->opt_force_plain || use_mfma(c)) return few;
+  const int32_t st = c->opt_split_tokens > 0 ? c->opt_split_tokens : 1024;
+  return std::max(few, (int64_t)c->max_batch * c->lay.num_q_heads * ceil_div(c->max_blocks_per_seq * kBlockSize, st));
+}
+
+// More of the slices' states than the context was made with (see ensure_partial_states), zeroed.
+int ensure_parts(ecoserve_ctx* c) {
+  const int64_t need = part_slots_needed(c);
+  if (need <= c->part_slots) return ECOSERVE_OK;
+  const size_t slot = (size_t)(c->lay.head_dim + 4) * sizeof(uint32_t);
+  uint32_t* parts = nullptr;
+  if (hipMalloc(&parts, (size_t)need * slot) != hipSuccess) {
+    (void)hipGetLastError();
+    return ECOSERVE_ENOMEM;
+  }
+  // (launches in flight may still use those it had)
+  if (hipMemset(parts, 0, (size_t)need * slot) != hipSuccess || hipDeviceSynchronize() != hipSuccess) {
+    (void)hipGetLastError();
+    (void)hipFree(parts);
+    return ECOSERVE_EHIP;
+  }
+  if (c->ws_more_parts) {
+    (void)hipFree(c->ws_more_parts);
+    c->ws_bytes -= (size_t)c->part_slots * slot;
+  }
+  c->ws_parts = c->ws_more_parts = parts;
+  c->part_slots = need;
+  c->ws_bytes += (size_t)need * slot;
+  return ECOSERVE_OK;
+}
+
 // Makes the partial-state arrays large enough for the current options (they only ever grow).  Called where
 // allocation is allowed: ecoserve_create and ecoserve_set_option.
 int ensure_partial_states(ecoserve_ctx* c) {
   int32_t plain_splits;
   const int64_t need = slots_needed(c, &plain_splits);
   if (plain_splits) c->ws_splits = plain_splits;
+  if (c->ws_share)  // (not while the context is made)
+    if (const int st = ensure_parts(c); st != ECOSERVE_OK) return st;
   if (need <= c->ws_slots) return ECOSERVE_OK;
   if (c->ws_acc || c->ws_ml) {
     if (hipDeviceSynchronize() != hipSuccess) return ECOSERVE_EHIP;  // launches in flight may still use them
@@ -239,6 +276,9 @@ int ecoserve_create(ecoserve_ctx** out, int device, const ecoserve_layout* layou
   c->ws_plan = nullptr;
   c->ws_pieces = nullptr;
   c->ws_count = nullptr;
+  c->ws_parts = nullptr;
+  c->ws_more_parts = nullptr;
+  c->part_slots = 0;
   c->plan_tiles = 0;
   c->ws_splits = 0;
   c->ws_slots = 0;
@@ -250,9 +290,11 @@ int ecoserve_create(ecoserve_ctx** out, int device, const ecoserve_layout* layou
   if (st != ECOSERVE_OK) { (void)ecoserve_destroy(c); return st; }
   {
     // per-XCD shares start equal; samples of 4 wavefronts per CU follow, then each chunk's report to the merge, then
-    // the small-batch kernel's counters (one allocation: creating a context is a few of them and their clearing)
+    // the small-batch kernel's counters and, on a boundary of 256 bytes, its slices' states (one allocation: creating a context is a few of them and their clearing)
     const size_t share_words = 24 + 6 * (size_t)c->num_cu * kDecodeWgsPerCu * 4;
-    const size_t share_bytes = (share_words + (size_t)c->max_batch * c->lay.num_kv_heads) * sizeof(int32_t);
+    const size_t parts_at = (share_words + (size_t)c->max_batch * c->lay.num_kv_heads + 63) / 64 * 64;
+    const int64_t part_slots = part_slots_needed(c);
+    const size_t share_bytes = (parts_at + (size_t)part_slots * (c->lay.head_dim + 4)) * sizeof(int32_t);
     const float ones[16] = {1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f};
     if (hipMalloc(&c->ws_share, share_bytes) != hipSuccess || hipMemset(c->ws_share, 0, share_bytes) != hipSuccess ||
         hipMemcpy(c->ws_share, ones, sizeof(ones), hipMemcpyHostToDevice) != hipSuccess) {
@@ -261,6 +303,8 @@ int ecoserve_create(ecoserve_ctx** out, int device, const ecoserve_layout* layou
       return ECOSERVE_ENOMEM;
     }
     c->ws_count = reinterpret_cast<uint32_t*>(c->ws_share + share_words);
+    c->ws_parts = c->ws_count + (parts_at - share_words);
+    c->part_slots = part_slots;
     c->ws_bytes += share_bytes;
   }
   *out = c;
@@ -274,6 +318,7 @@ int ecoserve_destroy(ecoserve_ctx* c) {
   if (!guard.ok || hipDeviceSynchronize() != hipSuccess) rc = ECOSERVE_EHIP;
   if (c->ws_acc) (void)hipFree(c->ws_acc);
   if (c->ws_ml) (void)hipFree(c->ws_ml);
+  if (c->ws_more_parts) (void)hipFree(c->ws_more_parts);
   if (c->ws_plan) (void)hipFree(c->ws_plan);
   if (c->ws_share) (void)hipFree(c->ws_share);
   for (int i = 0; i < 3; ++i)
@@ -538,11 +583,11 @@ static int decode_impl(ecoserve_ctx* c, const void* q, int64_t q_row_stride, con
   const int32_t split_tokens = automatic ? small.split_tokens : plan_split_tokens(c, B, max_ctx_len);
   const int32_t n_split_max = automatic ? small.n_split : ceil_div(max_ctx_len, split_tokens);
   // cannot happen: split_tokens >= kMinSplitTokens, and (bf16, 128) comes here with one slice per workgroup that fits
-  if (n_split_max > 1 && (use_mfma(c) ? (int64_t)(split_tokens ? B : 1) * a.Hq * n_split_max > c->ws_slots : n_split_max > c->ws_splits)) return ECOSERVE_EINVAL;
+  if (n_split_max > 1 && (c->opt_force_plain ? n_split_max > c->ws_splits : (int64_t)(split_tokens ? B : 1) * a.Hq * n_split_max > c->part_slots)) return ECOSERVE_EINVAL;
   {
     ProfileScope prof(c, ECOSERVE_KERNEL_DECODE, s);
     e = c->opt_force_plain ? launch_decode_plain(a, ctx_len, split_tokens, n_split_max, c->ws_acc, c->ws_ml, c->ws_splits, s)
-                           : launch_decode_any(a, ctx_len, split_tokens, n_split_max, c->ws_acc, c->ws_ml, c->ws_count, c->num_cu, s);
+                           : launch_decode_any(a, ctx_len, split_tokens, n_split_max, c->ws_parts, c->ws_count, c->num_cu, s);
   }
   if (e != hipSuccess) return ECOSERVE_EHIP;
   if (c->opt_force_plain && n_split_max > 1) {

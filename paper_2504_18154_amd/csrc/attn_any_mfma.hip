@@ -173,6 +173,25 @@ __device__ __forceinline__ f32x4 softmax_step(const f32x4& s, float& m, float& l
   return p;
 }
 
+// Values all lanes have, as scalars, and a lane's own, that are known from here on only: what follows from them is worked out behind this
+// point.  Otherwise it may stand in front of the branch that leads here, or (a scalar base and the lanes' offsets) be added up per lane and access.
+template <typename T>
+__device__ __forceinline__ T* scalar_here(T* p) {
+  const uint64_t u = (uint64_t)p;
+  uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)u), hi = __builtin_amdgcn_readfirstlane((uint32_t)(u >> 32));
+  asm volatile("" : "+s"(lo), "+s"(hi));
+  return (T*)((uint64_t)hi << 32 | lo);
+}
+__device__ __forceinline__ int scalar_here(int x) {
+  int y = __builtin_amdgcn_readfirstlane(x);
+  asm volatile("" : "+s"(y));
+  return y;
+}
+__device__ __forceinline__ int here(int x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
+
 // One row over keys [t0, t1), one wavefront, key after key: what a row falls back to when its sums are not finite
 // although its weights are.  Either a V element that is infinite or not a number met the zero weight of a
 // masked key, or the zero remainder of a bf16 weight, in the products above; here it meets only the rows that see
@@ -184,7 +203,7 @@ __device__ __forceinline__ void attend_row(const E* __restrict__ qrow, const E* 
                                         const int32_t* __restrict__ bt_row, int g, int Hkv, int D, int t0, int t1, float scale_log2e,
                                         float& m, float& l, float (&o)[4]) {
   constexpr int X = Elem<E>::X;
-  const int lane = threadIdx.x & 63;
+  const int lane = here((int)threadIdx.x & 63);
   m = -INFINITY;
   l = 0.f;
 #pragma unroll
@@ -210,9 +229,41 @@ __device__ __forceinline__ void attend_row(const E* __restrict__ qrow, const E* 
   }
 }
 
-// Values that another workgroup of the same launch reads, possibly on another XCD: past the caches that XCDs do not share.
-__device__ __forceinline__ void store_shared(float* p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-__device__ __forceinline__ float load_shared(float* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+// Partial states, from the workgroup of one slice to the one that merges them, within a launch and possibly between XCDs: past the
+// caches that XCDs do not share, and word by word.  A word holds the complement of the value's bits and is zero while it holds none, so a reader
+// sees by itself whether what it asked for has arrived, and nobody waits for a store to be acknowledged before it is announced.  (The one value
+// whose complement is zero, a NaN, is stored as its neighbour.)  Who reads a state clears it: the words are zero between launches.
+__device__ __forceinline__ uint32_t part_bits(float v) { return max(~__float_as_uint(v), 1u); }
+__device__ __forceinline__ float part_value(uint32_t bits) { return __uint_as_float(~bits); }
+// (The instructions of relaxed atomics of agent scope, as buffer accesses: a scalar base and 32 bits of offset per lane, and nothing is read behind
+// the range.)
+constexpr int kAuxAgent = 16;  // sc1
+__device__ __forceinline__ u32x4 part_bits(const f32x4& v) { return u32x4{part_bits(v[0]), part_bits(v[1]), part_bits(v[2]), part_bits(v[3])}; }
+__device__ __forceinline__ void store_part(__amdgpu_buffer_rsrc_t r, int byte, const u32x2& w) { __builtin_amdgcn_raw_buffer_store_b64(w, r, byte, 0, kAuxAgent); }
+__device__ __forceinline__ void store_part(__amdgpu_buffer_rsrc_t r, int byte, const u32x4& w) { __builtin_amdgcn_raw_buffer_store_b128(w, r, byte, 0, kAuxAgent); }
+constexpr int part_words(int D) { return D + 4; }  // of a state: the unnormalised head vector, its maximum, its sum, and two that keep 16 bytes aligned
+// A merging wavefront asks again at most so often (half a second).  The slices it waits for run already and wait for nothing themselves, microseconds from their end,
+// so it never does, but for calls that overlap on one workspace, which they may not: they end with NaN then.
+constexpr int kMostPolls = 1 << 19;
+
+// Over the two halves, or (N 4) the four 16-lane groups, of a wavefront, lane by lane.
+template <int N, typename F>
+__device__ __forceinline__ float of_groups(float v, F f) {
+  if constexpr (N == 4) {
+    const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = f(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  }
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return f(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+template <int N>
+__device__ __forceinline__ float max_of_groups(float v) {
+  return of_groups<N>(v, [](float a, float b) { return fmaxf(a, b); });
+}
+template <int N>
+__device__ __forceinline__ float sum_of_groups(float v) {
+  return of_groups<N>(v, [](float a, float b) { return a + b; });
+}
 
 // Balanced slices: lane b holds the number of blocks of sequence b; every K/V head has `slots` workgroups.  Whole contexts,
 // or slices of whole rounds of the W wavefronts, as short as all sequences' slices fit the workgroups and a merge stays short
@@ -245,66 +296,79 @@ __device__ __forceinline__ SliceOf slice_of_workgroup(const int32_t* __restrict_
     const int b = __popcll(__ballot(end - n <= x)) - 1;  // (lanes behind B have no slices: their first is behind the last)
     return {b, x - __builtin_amdgcn_readlane(end - n, b), __builtin_amdgcn_readlane(len, b), st * 16, __builtin_amdgcn_readlane(n, b)};
   } else {
-    return {(int)blockIdx.z, (int)blockIdx.x, ctx_len[blockIdx.z], split_tokens, (int)gridDim.x};
+    // (the constant address space: a scalar load)
+    return {(int)blockIdx.z, (int)blockIdx.x, ((const __attribute__((address_space(4))) int32_t*)(uintptr_t)ctx_len)[blockIdx.z], split_tokens, (int)gridDim.x};
   }
 }
 
 // Decode: grid (splits, Hkv, B), or (Hkv, slices of all sequences) with balanced slices, W wavefronts; the blocks of a slice of `split_tokens` tokens of one (sequence, K/V
 // head) go to the wavefronts in turn, whose states are combined through LDS.  With one slice the result is final,
-// otherwise it is a partial state, and the last workgroup of the (sequence, K/V head) to be done merges them
-// (`counters`, one per (sequence, K/V head): zero before and after).  With k_new given the workgroup of the last slice takes
-// the newest token (position ctx_len - 1) from the new rows and stores it into the cache.
+// otherwise it is a partial state, and one workgroup of the (sequence, K/V head) merges them (`counters`, one per (sequence, K/V head), and `parts`: zero before
+// and after).  With k_new given the wavefront that has the last block takes the newest token (position ctx_len - 1) from the new rows and stores it into the cache.
+// What such a launch is made of (1 x 777 tokens, 40 query heads on 8, 8.4 us a call, time stamps): 0.4 us to the length, 0.5 to the block ids, 1.4 to the blocks,
+// 1.6 for the states through LDS (three barriers, divisions, the code of a row taken again in front of them), 0.2 and 0.35 for stores acknowledged and the count,
+// 1.2 for the maxima, 1.4 for the states and the result.  Now 6.8 us: one barrier, whole rows per wavefront, 16 bytes per lane; the count asked for behind the
+// first blocks; states that say by themselves when they have arrived; arguments fetched at once, query rows while the ids are on their way.  The same steps elsewhere, us:
+// 64 on 8, 16 x 20..2000 19.6 / 17.8, 40 on 8, 1 x 2000 9.8 / 8.5, 8 x 1000 14.0 / 12.4, 52 on 52, 1 x 700 10.2 / 8.5, 32 on 8, 1 x 16000 20.7 / 18.9, fp32, 64, 2 K/V heads, 1 x 700
+// 7.9 / 6.4, fp32, 128, 3, 4 x 400 9.9 / 8.6, bf16, 256, 1, 1 x 800 14.2 / 10.8, bf16, 64, 8, 4 x 600 7.9 / 7.8; 8 on 1, 1 x 60000 (52 slices) 19.4 / 20.3.
 template <typename E, int KS, int W, int AUX = 0, bool FULL = true, bool BALANCED = false>
 __global__ __launch_bounds__(W * 64) void decode_any_kernel(
     const E* __restrict__ q, int q_row_stride, const E* __restrict__ k_new, const E* __restrict__ v_new, int new_row_stride,
     E* k_cache, E* v_cache, const int32_t* __restrict__ block_table, int bt_stride, const int32_t* __restrict__ ctx_len,
-    E* __restrict__ out, float* __restrict__ lse, float* ws_acc, float* ws_ml, uint32_t* counters, int split_tokens, int Hq,
-    int Hkv, int G, int D, float scale_log2e, int B) {
+    E* __restrict__ out, float* __restrict__ lse, uint32_t* parts, uint32_t* counters, int split_tokens, int Hq,
+    int Hkv, int G, int head_size, float scale_log2e, int B) {
   typedef Block<E, KS, AUX, FULL> Blk;
   constexpr int X = Elem<E>::X, NK = Blk::NK, NV = Blk::NV;
-  constexpr int kTiles = NV < 8 ? NV : 8, kSlice = kTiles * 16;  // elements of a head vector combined at a time
+  // Where a wavefront has a row: NG groups of lanes share the states, and a lane has four elements of every 128 (or of 64).
+  constexpr int NC = (KS + 3) / 4, NG = KS <= 2 ? 4 : 2, LG = 64 / NG;
   __shared__ __attribute__((aligned(16))) E s_new[2][256];
-  __shared__ float s_m[W][16], s_l[W][16], s_tot[2][16];
-  __shared__ __attribute__((aligned(16))) float s_acc[W][16][kSlice + 4];
-  __shared__ int s_bad, s_order;
+  __shared__ __attribute__((aligned(16))) float2 s_ml[16][W];
+  __shared__ __attribute__((aligned(16))) float s_acc[W][16][32 * KS + 4];
+  __shared__ int s_order;
   const int g = BALANCED ? blockIdx.x : blockIdx.y;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int col = lane & 15, quad = lane >> 4;
-  // Asked for with the length, before anything that depends on it: the new rows, the query rows.  (The block ids have to
-  // wait: entries behind the sequence's last block are not read.)
+  const int D = FULL ? head_size : 128;
+  // All arguments at once: fetched where they are wanted, they came in six round trips one behind the other.
+  asm volatile("" ::"s"(q), "s"(q_row_stride), "s"(k_new), "s"(v_new), "s"(new_row_stride), "s"(k_cache), "s"(v_cache), "s"(block_table), "s"(bt_stride),
+               "s"(ctx_len), "s"(split_tokens), "s"(Hkv), "s"(G), "s"(head_size));
   const SliceOf at = slice_of_workgroup<BALANCED>(ctx_len, B, Hkv, split_tokens, W);
   if (BALANCED && at.sp < 0) return;
   const int b = at.b, sp = at.sp, L = at.L;
   const int32_t* const bt_row = block_table + (size_t)b * bt_stride;
-  const bool fused = k_new != nullptr;
-  constexpr int NN = (32 * KS + W * 64 - 1) / (W * 64);  // elements of the new rows per thread
-  E kn[NN], vn[NN];
-#pragma unroll
-  for (int i = 0; i < NN; ++i) {
-    const int d = tid + i * W * 64;
-    const bool in = (BALANCED ? at.sp == at.most - 1 && fused : fused) && d < D;
-    kn[i] = in ? k_new[(size_t)b * new_row_stride + (size_t)g * D + d] : E(0);
-    vn[i] = in ? v_new[(size_t)b * new_row_stride + (size_t)g * D + d] : E(0);
-  }
+  const Slice slice = decode_slice(L, at.tokens, at.most, sp);
+  const int t0 = slice.t0, t1 = slice.t1;
+  if (t1 <= t0) return;
+  const WaveBlocks blocks = wave_blocks(t0, t1, wave, W);  // this wavefront's
+  const int n = blocks.n;
+  // (the block ids wait for the length: entries behind the sequence's last block are not read)
+  int ids = lane < n ? bt_row[blocks.first + W * lane] : 0;
+  // While the ids are on their way: the query rows (columns behind the group's heads have the last one's and are not used) and, for the wavefront
+  // that has the block of the newest token, the new rows, element lane + 64 i.
   u32x4 qf[NK];
 #pragma unroll
   for (int j = 0; j < NK; ++j) {
     const int d = (4 * j + quad) * X;
-    const u32x4 z = {0u, 0u, 0u, 0u};
-    qf[j] = col < G && d < D ? *reinterpret_cast<const u32x4*>(q + (size_t)b * q_row_stride + (size_t)(g * G + col) * D + d) : z;
+    qf[j] = *reinterpret_cast<const u32x4*>(q + (size_t)b * q_row_stride + (size_t)(g * G + min(col, G - 1)) * D + (FULL ? min(d, D - X) : d));
+    if (FULL && d >= D) qf[j] = u32x4{0u, 0u, 0u, 0u};
   }
-  const Slice slice = decode_slice(L, at.tokens, at.most, sp);
-  const int n_split = slice.n, t0 = slice.t0, t1 = slice.t1;
-  if (sp >= n_split) return;
-  const WaveBlocks blocks = wave_blocks(t0, t1, wave, W);  // this wavefront's
-  const int n = blocks.n;
-  int ids = lane < n ? bt_row[blocks.first + W * lane] : 0;
+  const bool newest = k_new != nullptr && t1 == L && n > 0 && blocks.first + W * (n - 1) == (L - 1) >> 4;
+  constexpr int NN = (KS + 1) / 2;
+  typedef typename std::conditional<Blk::kF32, float, uint32_t>::type Word;  // (two elements of 16 bits to a register would be put together here, and waited for)
+  Word kn[NN], vn[NN];
+  if (newest) {
+#pragma unroll
+    for (int i = 0; i < NN; ++i) {
+      const int d = FULL ? min(lane + 64 * i, D - 1) : lane + 64 * i;
+      kn[i] = k_new[(size_t)b * new_row_stride + (size_t)g * D + d];
+      vn[i] = v_new[(size_t)b * new_row_stride + (size_t)g * D + d];
+    }
+  }
   // (a scalar copy of its own: the merge below takes D into vector registers, and the blocks' addresses with it, were it the
   // same value - every load then goes through a loop over its descriptors, 1 us per call)
   int d_scalar = D;
-  asm("" : "+s"(d_scalar));
+  if constexpr (FULL) asm("" : "+s"(d_scalar));
   const size_t piece = (size_t)16 * d_scalar * sizeof(E);
-  const bool newest = fused && sp == n_split - 1;
   const char* const kc = reinterpret_cast<const char*>(k_cache);
   const char* const vc = reinterpret_cast<const char*>(v_cache);
 
@@ -324,6 +388,7 @@ __global__ __launch_bounds__(W * 64) void decode_any_kernel(
 #pragma unroll
   for (int dt = 0; dt < NV; ++dt) acc[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
   float m = -INFINITY, l = 0.f;
+  auto weight = [](float x) { return FULL ? exp2f(x) : __builtin_amdgcn_exp2f(x); };  // (see softmax_step)
   auto work = [&](const Blk& fr, int tail) {
     f32x4 s = fr.scores(qf) * scale_log2e;
     if (tail < 16) {
@@ -336,15 +401,24 @@ __global__ __launch_bounds__(W * 64) void decode_any_kernel(
   };
   if (n > 0) fetch(f[0], 0);
   if (n > 1) fetch(f[1], 1);
-  if (newest)
+  // Which of the slices starts last merges them all (see the end).  Asked here, behind the first blocks, the answer is there before it is wanted.  Slices of
+  // more than four rounds end at so many times that who waits for them is in their way: there it is the one that is done last (1 x 75000 tokens, 62.3 us; waiting 65.2).
+  const int n_split = slice.n;
+  const bool early = t1 - t0 <= 4 * 16 * W;
+  auto arrive = [&]() { return (int)atomicInc(counters + (size_t)b * Hkv + g, (unsigned)n_split - 1); };  // (the last one wraps it to zero)
+  int order = 0, newest_blk = 0;
+  if (n_split > 1 && early && tid == 0) order = arrive();
+  if (newest) {
 #pragma unroll
     for (int i = 0; i < NN; ++i)
-      if (tid + i * W * 64 < D) {
-        s_new[0][tid + i * W * 64] = kn[i];
-        s_new[1][tid + i * W * 64] = vn[i];
+      if (lane + 64 * i < 32 * KS) {
+        s_new[0][lane + 64 * i] = (E)kn[i];
+        s_new[1][lane + 64 * i] = (E)vn[i];
       }
-  if (tid == 0) s_bad = 0;
-  __syncthreads();
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  }
   while (base < n) {
     int tail = 16;
     const int last = blocks.first + W * (n - 1);
@@ -356,7 +430,10 @@ __global__ __launch_bounds__(W * 64) void decode_any_kernel(
       // elements have registers enough, and lose 0.06.)
       int at_lane = lane;
       if constexpr (KS > 3) asm volatile("" : "+v"(at_lane));
-      if (newest) f[0].put_token(s_new[0], s_new[1], tail - 1, D, at_lane & 15, at_lane >> 4);
+      if (newest) {
+        f[0].put_token(s_new[0], s_new[1], tail - 1, D, at_lane & 15, at_lane >> 4);
+        newest_blk = __builtin_amdgcn_readlane(ids, nw - 1);
+      }
       if (tail < 16) f[0].clear_tail(tail, at_lane >> 4);
     }
     // Only blocks that exist are asked for: a load of nothing still takes its turn in the address unit, and three such
@@ -383,135 +460,210 @@ __global__ __launch_bounds__(W * 64) void decode_any_kernel(
       if (nw > 1) fetch(f[1], 1);
     }
   }
-  l += __shfl_xor(l, 16);
-  l += __shfl_xor(l, 32);
-  if (quad == 0) {
-    s_m[wave][col] = m;
-    s_l[wave][col] = l;
-  }
-  __syncthreads();
-  if (newest) {  // (every wavefront's loads have been consumed: nothing in this launch reads the slot any more)
-    const int64_t blk = bt_row[(L - 1) >> 4];
+  // The wavefronts' states through LDS, one barrier; then a wavefront has whole rows (heads h = wave + W k of the group), each group of lanes
+  // the states of its share of the wavefronts:   M = max_w m_w;  total = sum_w l_w 2^(m_w - M);  o = sum_w acc_w 2^(m_w - M).
+  l = sum_of_groups<4>(l);
+  if (quad == 0) s_ml[col][wave] = float2{m, l};
+#pragma unroll
+  for (int dt = 0; dt < NV; ++dt)
+    if (col < G) *reinterpret_cast<f32x4*>(&s_acc[wave][col][dt * 16 + 4 * quad]) = acc[dt];
+  if (newest) {  // (nobody else in this launch needs the slot)
+    const size_t off = ((size_t)newest_blk * Hkv + g) * piece;
+    const int slot = (L - 1) & 15, units = D / X;
+    const __amdgpu_buffer_rsrc_t rk = __builtin_amdgcn_make_buffer_rsrc(scalar_here(const_cast<char*>(kc) + off), 0, (int)piece, kRsrc32);
+    const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc(scalar_here(const_cast<char*>(vc) + off), 0, (int)piece, kRsrc32);
+    if (lane < units) __builtin_amdgcn_raw_buffer_store_b128(*reinterpret_cast<const u32x4*>(&s_new[0][lane * X]), rk, (lane * 16 + slot) * 16, 0, 0);
 #pragma unroll
     for (int i = 0; i < NN; ++i) {
-      const int d = tid + i * W * 64;
+      const int d = lane + 64 * i, at_d = (d * 16 + slot) * (int)sizeof(E);
       if (d >= D) continue;
-      k_cache[k_index<X>(blk, g, (L - 1) & 15, d, Hkv, D)] = kn[i];
-      v_cache[v_index(blk, g, (L - 1) & 15, d, Hkv, D)] = vn[i];
+      if constexpr (Blk::kF32) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(s_new[1][d]), rv, at_d, 0, 0);
+      else __builtin_amdgcn_raw_buffer_store_b16(s_new[1][d], rv, at_d, 0, 0);
     }
   }
-  float M = -INFINITY, total = 0.f;
-#pragma unroll
-  for (int w = 0; w < W; ++w) M = fmaxf(M, s_m[w][col]);
-#pragma unroll
-  for (int w = 0; w < W; ++w) total += s_m[w][col] == -INFINITY ? s_l[w][col] : s_l[w][col] * __builtin_amdgcn_exp2f(s_m[w][col] - M);
-  const float mine = m == -INFINITY ? 0.f : exp2f(m - M);
-  if (tid < 16) {
-    s_tot[0][col] = M;
-    s_tot[1][col] = total;
+  if (tid == 0) {
+    if (n_split > 1 && !early) order = arrive();
+    s_order = order;
   }
-  const bool final_result = n_split == 1;
+  __syncthreads();
+  const bool merges = __builtin_amdgcn_readfirstlane(s_order) == n_split - 1;  // (one slice: it is the last one, and there is nothing to merge)
   // Partial states: [B][Hq][slices], or (balanced) [slices of all sequences][Hq].  slot0: of this slice and the group's first head.
+  const int row_words = part_words(d_scalar), grp = lane / LG, el = (lane % LG) * 4;
   const size_t slot0 = BALANCED ? (size_t)blockIdx.y * Hq + (size_t)g * G : ((size_t)b * Hq + (size_t)g * G) * gridDim.x + sp;
-  const size_t slot_step = BALANCED ? 1 : gridDim.x, next_slice = BALANCED ? Hq : 1;
-#pragma unroll
-  for (int t = 0; t < NV; t += kTiles) {
-#pragma unroll
-    for (int i = 0; i < kTiles; ++i)
-      if (t + i < NV && col < G) *reinterpret_cast<f32x4*>(&s_acc[wave][col][i * 16 + 4 * quad]) = acc[t + i] * mine;
-    __syncthreads();
-    for (int idx = tid; idx < G * kSlice; idx += W * 64) {
-      const int h = idx / kSlice, dl = idx % kSlice, d = t * 16 + dl;
-      if (d >= D) continue;
-      float o = 0.f;
-#pragma unroll
-      for (int w = 0; w < W; ++w) o += s_acc[w][h][dl];
-      const float sum = s_tot[1][h];
-      if (not_finite(o) && sum == sum) s_bad = 1;  // (see attend_row)
-      if (final_result) Elem<E>::store(out + ((size_t)b * Hq + g * G + h) * D + d, o / sum);
-      else store_shared(ws_acc + (slot0 + h * slot_step) * D + d, o);
-    }
-    __syncthreads();
-  }
-  if (tid < G) {
-    if (final_result) {
-      if (lse) lse[(size_t)b * Hq + g * G + tid] = (s_tot[0][tid] + log2f(s_tot[1][tid])) * kLn2;
-    } else {
-      store_shared(ws_ml + (slot0 + tid * slot_step) * 2 + 0, s_tot[0][tid]);
-      store_shared(ws_ml + (slot0 + tid * slot_step) * 2 + 1, s_tot[1][tid]);
-    }
-  }
-  if (s_bad) {
-    __syncthreads();
-    for (int h = wave; h < G; h += W) {
-      float rm, rl, o[4];
-      attend_row<E>(q + (size_t)b * q_row_stride + (size_t)(g * G + h) * D, k_cache, v_cache, bt_row, g, Hkv, D, t0, t1, scale_log2e, rm, rl, o);
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int d = lane + 64 * r;
-        if (d >= D) continue;
-        if (final_result) Elem<E>::store(out + ((size_t)b * Hq + g * G + h) * D + d, o[r] / rl);
-        else store_shared(ws_acc + (slot0 + h * slot_step) * D + d, o[r]);
-      }
-      if (!final_result && lane == 0) {
-        store_shared(ws_ml + (slot0 + h * slot_step) * 2 + 0, rm);
-        store_shared(ws_ml + (slot0 + h * slot_step) * 2 + 1, rl);
-      }
-    }
-  }
-  if (final_result) return;
-
-  // The slice that is done last merges them all:
-  //   M = max_k m_k;  l = sum_k l_k 2^(m_k - M);  o = sum_k acc_k 2^(m_k - M) / l.
-  // Every thread's stores have reached the level the XCDs share before its workgroup is counted (store_shared, and the
-  // wait below), and what is read back is read from there, so no cache has to be written back or dropped.
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  __syncthreads();
-  if (tid == 0) s_order = (int)atomicInc(counters + (size_t)b * Hkv + g, (unsigned)n_split - 1);  // (the last one wraps it to zero)
-  __syncthreads();
-  if (s_order != n_split - 1) return;
+  const size_t slot_step = BALANCED ? 1 : gridDim.x, slice_words = (size_t)(BALANCED ? Hq : 1) * row_words;
+#pragma unroll 1
   for (int h = wave; h < G; h += W) {
-    const size_t slot = slot0 - sp * next_slice + h * slot_step;
-    // Eight states are asked for at once (larger heads have no registers for them), and behind the maxima: those answer first
-    // then, and the weights are ready when the states arrive.  Together with the maxima they took 0.35 us more (40 query heads
-    // on 8, one context of 2000 tokens 10.7 / 10.3; four at once, one after the other, 10.7; sixteen 10.5).
-    constexpr int kAtOnce = KS <= 4 ? 8 : 4;
-    auto states = [&](int k, float (&ak)[kAtOnce][(KS + 1) / 2]) {  // of slices k .. k + kAtOnce - 1
+    float2 ml[W / NG];
 #pragma unroll
-      for (int j = 0; j < kAtOnce; ++j)
+    for (int w = 0; w < W / NG; ++w) ml[w] = s_ml[h][grp * (W / NG) + w];
+    float M = ml[0].x, total = 0.f;
 #pragma unroll
-        for (int r = 0; r < (KS + 1) / 2; ++r)
-          ak[j][r] = k + j < n_split && lane + 64 * r < D ? load_shared(ws_acc + (slot + (k + j) * next_slice) * D + lane + 64 * r) : 0.f;
-    };
-    float ak[kAtOnce][(KS + 1) / 2];
-    float m2 = -INFINITY, l2 = 0.f, o2[4] = {0.f, 0.f, 0.f, 0.f};
-    for (int base = 0; base < n_split; base += 64) {  // 64 slices at a time: lane k holds the (max, sum) of slice k
-      const int nk = min(64, n_split - base);
-      const float mk = lane < nk ? load_shared(ws_ml + (slot + (base + lane) * next_slice) * 2) : -INFINITY;
-      const float lk = lane < nk ? load_shared(ws_ml + (slot + (base + lane) * next_slice) * 2 + 1) : 0.f;
-      const float m_new = fmaxf(m2, wave_max(mk));
-      // (slices whose scores are all -inf so far weigh nothing: their m is -inf, their sums are zero)
-      const float mu = m_new == -INFINITY ? 0.f : m_new;
-      const float old = m2 == -INFINITY ? 0.f : exp2f(m2 - mu), wk = lane < nk ? exp2f(mk - mu) : 0.f;
-      m2 = m_new;
-      l2 = l2 * old + wave_sum(lk * wk);
+    for (int w = 1; w < W / NG; ++w) M = fmaxf(M, ml[w].x);
+    M = max_of_groups<NG>(M);
+    f32x4 o[NC];
 #pragma unroll
-      for (int r = 0; r < 4; ++r) o2[r] *= old;
-      for (int k = 0; k < nk; k += kAtOnce) {
-        states(base + k, ak);
+    for (int c = 0; c < NC; ++c) o[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < W / NG; ++w) {
+      const float wk = ml[w].x == -INFINITY ? 0.f : weight(ml[w].x - M);
+      total += ml[w].y * (ml[w].x == -INFINITY ? 1.f : wk);
+#pragma unroll
+      for (int c = 0; c < NC; ++c)  // (lanes behind the last element have that one's four)
+        o[c] += *reinterpret_cast<const f32x4*>(&s_acc[grp * (W / NG) + w][h][KS == 2 || KS % 4 == 0 ? el + 128 * c : min(el + 128 * c, 32 * KS - 4)]) * wk;
+    }
+    total = sum_of_groups<NG>(total);
+    float zero = 0.f;  // (not a number if an element is not finite)
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        o[c][e] = sum_of_groups<NG>(o[c][e]);
+        zero = __builtin_fmaf(o[c][e], 0.f, zero);
+      }
+    if (__any(zero != zero && total == total)) {  // (see attend_row)
+      float r[4];
+      attend_row<E>(scalar_here(q + (size_t)b * q_row_stride) + (size_t)(scalar_here(g) * G + h) * D, scalar_here(k_cache), scalar_here(v_cache), scalar_here(bt_row),
+                    scalar_here(g), scalar_here(Hkv), scalar_here(D), scalar_here(t0), scalar_here(t1), scale_log2e, M, total, r);
+      const int ln = here(lane);
+#pragma unroll
+      for (int k = 0; k < (KS + 1) / 2; ++k)
+        if (ln + 64 * k < 32 * KS) s_acc[0][h][ln + 64 * k] = r[k];  // (nobody else reads this row)
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+        o[c] = *reinterpret_cast<const f32x4*>(&s_acc[0][h][min((ln % LG) * 4 + 128 * c, 32 * KS - 4)]);
+    }
+    uint32_t* const mine = parts + (slot0 + h * slot_step) * row_words;
+    if (!merges) {
+      const __amdgpu_buffer_rsrc_t to = __builtin_amdgcn_make_buffer_rsrc(scalar_here(mine), 0, row_words * 4, kRsrc32);
+      if (grp == 0) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+          if (!FULL || el + 128 * c < D) store_part(to, (el + 128 * c) * 4, part_bits(o[c]));
+      } else {
+        store_part(to, D * 4, u32x2{part_bits(M), part_bits(total)});
+      }
+      continue;
+    }
+    if (n_split > 1) {
+      //   M = max_k m_k;  l = sum_k l_k 2^(m_k - M);  o = sum_k acc_k 2^(m_k - M) / l,  in the order of the slices, whichever merges.
+      // The states of eight slices are asked for at once, those of the next eight while they are added up, and all again until they have
+      // arrived: every slice has started, and none waits for another.  Each group of lanes takes every NG-th slice.  (Slices whose scores are all
+      // -inf weigh nothing: their m is -inf, their sums are zero.)
+      constexpr int kAtOnce = 8 / NG;  // per group
+      const int slice_bytes = scalar_here((int)slice_words * 4);
+      float m2 = -INFINITY, l2 = 0.f;
+      f32x4 o2[NC];
+      int at_o[NC];
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        o2[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+        at_o[c] = (FULL ? min(el + 128 * c, D - 4) : el + 128 * c) * 4 + grp * slice_bytes;
+      }
+      const int at_ml = D * 4 + grp * slice_bytes;
+      struct Group {
+        u32x2 ml[kAtOnce];
+        u32x4 o[kAtOnce][NC];
+      };
+      auto range = [&](int base) {  // of the slices from `base` on, up to eight
+        const int more = min(n_split - base, NG * kAtOnce);
+        return __builtin_amdgcn_make_buffer_rsrc(scalar_here(mine + (int64_t)(base - sp) * (int64_t)slice_words), 0,
+                                                 more > 0 ? (more - 1) * slice_bytes + row_words * 4 : 0, kRsrc32);
+      };
+      auto ask = [&](__amdgpu_buffer_rsrc_t from, Group& x) {  // (behind the last slice: out of range, zeros)
+        asm volatile("" ::: "memory");  // (memory has changed: without this the loads of a poll are taken for the same as before, and its loop for none)
 #pragma unroll
         for (int j = 0; j < kAtOnce; ++j) {
-          const float w = k + j < nk ? __shfl(wk, k + j) : 0.f;
+          x.ml[j] = __builtin_amdgcn_raw_buffer_load_b64(from, at_ml + NG * j * slice_bytes, 0, kAuxAgent);
 #pragma unroll
-          for (int r = 0; r < (KS + 1) / 2; ++r) o2[r] += ak[j][r] * w;
+          for (int c = 0; c < NC; ++c) x.o[j][c] = __builtin_amdgcn_raw_buffer_load_b128(from, at_o[c] + NG * j * slice_bytes, 0, kAuxAgent);
         }
-      }
-    }
-    E* const orow = out + ((size_t)b * Hq + g * G + h) * D;
+      };
+      Group now, then;
+      int polls = 0;
+      __amdgpu_buffer_rsrc_t from = range(0);
+      ask(from, now);
+      for (int base = 0; base < n_split; base += NG * kAtOnce) {
+        const int more = n_split - base - grp, own = sp - base - grp;  // (slice NG j of this group of lanes: there, if NG j < more, this workgroup's, if NG j = own)
+        const __amdgpu_buffer_rsrc_t next = range(base + NG * kAtOnce);
+        ask(next, then);
+        auto missing = [&]() {
+          bool any = false;
 #pragma unroll
-    for (int r = 0; r < (KS + 1) / 2; ++r)
-      if (lane + 64 * r < D) Elem<E>::store(orow + lane + 64 * r, o2[r] / l2);
-    if (lse && lane == 0) lse[(size_t)b * Hq + g * G + h] = (m2 + log2f(l2)) * kLn2;
+          for (int j = 0; j < kAtOnce; ++j) {
+            uint32_t least = min(now.ml[j][0], now.ml[j][1]);
+#pragma unroll
+            for (int c = 0; c < NC; ++c)
+#pragma unroll
+              for (int e = 0; e < 4; ++e) least = min(least, now.o[j][c][e]);
+            any |= (least == 0) & (NG * j < more) & (NG * j != own);
+          }
+          return __any(any);
+        };
+        if (missing()) {  // (apart from the first look, which then waits for these slices alone)
+          asm volatile("" ::: "memory");
+          do {
+            // who waits for long keeps out of the others' way: 0.4 us between looks, at the sums alone
+            for (bool wait = polls > 1; wait && polls < kMostPolls; ++polls) {
+              __builtin_amdgcn_s_sleep(16);
+              asm volatile("" ::: "memory");
+              bool any = false;
+#pragma unroll
+              for (int j = 0; j < kAtOnce; ++j)
+                any |= (__builtin_amdgcn_raw_buffer_load_b32(from, at_ml + 4 + NG * j * slice_bytes, 0, kAuxAgent) == 0) & (NG * j < more) & (NG * j != own);
+              wait = __any(any);
+            }
+            ask(from, now);
+          } while (missing() && ++polls < kMostPolls);
+        }
+        float m_new = m2, x[kAtOnce];
+#pragma unroll
+        for (int j = 0; j < kAtOnce; ++j) {  // (behind the last slice: nothing, of no weight)
+          x[j] = NG * j == own ? M : NG * j < more ? part_value(now.ml[j][0]) : -INFINITY;
+          m_new = fmaxf(m_new, x[j]);
+        }
+#pragma unroll
+        for (int j = 0; j < kAtOnce; ++j) {  // (this workgroup's own words are zero already)
+#pragma unroll
+          for (int c = 0; c < NC; ++c) store_part(from, at_o[c] + NG * j * slice_bytes, u32x4{0u, 0u, 0u, 0u});
+          store_part(from, at_ml + NG * j * slice_bytes, u32x2{0u, 0u});
+        }
+        const float mu = m_new == -INFINITY ? 0.f : m_new, old = m2 == -INFINITY ? 0.f : weight(m2 - mu);
+        m2 = m_new;
+        l2 *= old;
+#pragma unroll
+        for (int c = 0; c < NC; ++c) o2[c] *= old;
+#pragma unroll
+        for (int j = 0; j < kAtOnce; ++j) {
+          const float wk = weight(x[j] - mu);
+          l2 += (NG * j == own ? total : NG * j < more ? part_value(now.ml[j][1]) : 0.f) * wk;
+#pragma unroll
+          for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o2[c][e] += (NG * j == own ? o[c][e] : NG * j < more ? part_value(now.o[j][c][e]) : 0.f) * wk;
+        }
+        from = next;
+        now = then;
+      }
+      M = max_of_groups<NG>(m2);
+      const float mine_weighs = m2 == -INFINITY ? 0.f : weight(m2 - M);
+      total = sum_of_groups<NG>(l2 * (m2 == -INFINITY ? 1.f : mine_weighs));
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[c][e] = sum_of_groups<NG>(o2[c][e] * mine_weighs);
+    }
+    const float inv = 1.f / total;
+    const size_t row = (size_t)b * Hq + g * G + h;
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+      if (grp == 0 && (!FULL || el + 128 * c < D)) {
+        if constexpr (Blk::kF32) store4(out + row * D + el + 128 * c, f32x4{o[c][0] / total, o[c][1] / total, o[c][2] / total, o[c][3] / total});
+        else store4(out + row * D + el + 128 * c, o[c] * inv);
+      }
+    if (lse && lane == 0) lse[row] = (M + log2f(total)) * kLn2;
   }
 }
 
@@ -982,14 +1134,14 @@ void launch_prefill_typed(const AttnArgs& a, const int32_t* cu_q, const int32_t*
 }
 
 template <typename E>
-void launch_decode_typed(const AttnArgs& a, const int32_t* ctx_len, int32_t split_tokens, int32_t n_split_max, float* ws_acc,
-                         float* ws_ml, uint32_t* counters, bool many, hipStream_t s) {
+void launch_decode_typed(const AttnArgs& a, const int32_t* ctx_len, int32_t split_tokens, int32_t n_split_max, uint32_t* parts,
+                         uint32_t* counters, bool many, hipStream_t s) {
   const bool balanced = split_tokens == 0;
   auto launch = [&](auto kernel, int W) {
     hipLaunchKernelGGL(kernel, balanced ? dim3((unsigned)a.Hkv, (unsigned)n_split_max) : dim3((unsigned)n_split_max, (unsigned)a.Hkv, (unsigned)a.B), dim3(W * 64), 0, s,
                        (const E*)a.q, a.q_row_stride, (const E*)a.k_new, (const E*)a.v_new, a.new_row_stride,
                        (E*)const_cast<void*>(a.k_cache), (E*)const_cast<void*>(a.v_cache), a.block_table, a.bt_stride, ctx_len,
-                       (E*)a.out, a.lse, ws_acc, ws_ml, counters, split_tokens, a.Hq, a.Hkv, a.Hq / a.Hkv, a.D, a.scale_log2e, a.B);
+                       (E*)a.out, a.lse, parts, counters, split_tokens, a.Hq, a.Hkv, a.Hq / a.Hkv, a.D, a.scale_log2e, a.B);
   };
   for_head_size(a.D, [&](auto ks) {
     constexpr int KS = decltype(ks)::value, W = decode_wavefronts(32 * KS, sizeof(E));
@@ -1035,11 +1187,11 @@ hipError_t launch_decode_short(const AttnArgs& a, const int32_t* ctx_len, int32_
                                                                                                                   : hipErrorInvalidValue;
 }
 
-hipError_t launch_decode_any(const AttnArgs& a, const int32_t* ctx_len, int32_t split_tokens, int32_t n_split_max, float* ws_acc,
-                             float* ws_ml, uint32_t* counters, int32_t num_cu, hipStream_t s) {
+hipError_t launch_decode_any(const AttnArgs& a, const int32_t* ctx_len, int32_t split_tokens, int32_t n_split_max, uint32_t* parts,
+                             uint32_t* counters, int32_t num_cu, hipStream_t s) {
   const bool many = (int64_t)(split_tokens ? a.B : 1) * a.Hkv * n_split_max > num_cu;
-  if (a.dtype == ECOSERVE_BF16) launch_decode_typed<uint16_t>(a, ctx_len, split_tokens, n_split_max, ws_acc, ws_ml, counters, many, s);
-  else launch_decode_typed<float>(a, ctx_len, split_tokens, n_split_max, ws_acc, ws_ml, counters, many, s);
+  if (a.dtype == ECOSERVE_BF16) launch_decode_typed<uint16_t>(a, ctx_len, split_tokens, n_split_max, parts, counters, many, s);
+  else launch_decode_typed<float>(a, ctx_len, split_tokens, n_split_max, parts, counters, many, s);
   return hipGetLastError();
 }
 

@@ -98,7 +98,10 @@ struct ecoserve_ctx {
   float* ws_share;             // per-XCD shares (mean 1) [2][8], speeds [8], then as int32 [2 * wavefronts]: units, ticks,
                                // then [4 * wavefronts]: the cut (sequence, K/V head) each chunk reports to the merge
   int share_parity;            // which of the two share vectors the next adaptive decode launch reads
-  uint32_t* ws_count;          // [max_batch][Hkv], zero between launches: slices of a (sequence, K/V head) that are done
+  uint32_t* ws_count;          // [max_batch][Hkv], zero between launches: slices of a (sequence, K/V head) that have started
+  uint32_t* ws_parts;          // part_slots partial states of D + 4 words, zero between launches: slices of the kernels of attn_any_mfma.hip
+  uint32_t* ws_more_parts;     // where ws_parts points once an option has asked for more of them than the context was made with, else NULL
+  int64_t part_slots;
   int32_t ws_splits;
   int32_t* ws_plan;            // prefill plan: header and one record per query tile of the last prefill launch
   float* ws_pieces;            // prefill: states of the pieces of tiles whose key steps are shared out (bf16, D = 128)
@@ -165,11 +168,11 @@ hipError_t launch_decode_merge(const AttnArgs& a, const int32_t* ctx_len, int32_
 // attn_any_mfma.hip: every layout on matrix cores (bf16, D = 128: small decode batches only)
 // (one launch; with a.k_new given it appends the step's tokens too; split_tokens: a multiple of 16 per slice of the
 // context, n_split_max slices, partial states [B][Hq][n_split_max]; or, (bf16, 128) and B <= 64 only, 0: balanced slices, n_split_max
-// per K/V head in all, at least B, partial states [n_split_max][Hq]; counters [B][Hkv] that are zero and stay so:
+// per K/V head in all, at least B, partial states [n_split_max][Hq], D + 4 words each; words and counters [B][Hkv] are zero and stay so:
 // any_decode and small_decode in decode_slices.h)
 hipError_t launch_prefill_any(const AttnArgs& a, const int32_t* cu_q, const int32_t* ctx_before, int32_t T, hipStream_t s);
 hipError_t launch_decode_any(const AttnArgs& a, const int32_t* ctx_len, int32_t split_tokens, int32_t n_split_max,
-                             float* ws_acc, float* ws_ml, uint32_t* counters, int32_t num_cu, hipStream_t s);
+                             uint32_t* parts, uint32_t* counters, int32_t num_cu, hipStream_t s);
 // (bf16, 128), whole contexts: `waves` (1, 2 or 4) wavefronts per (sequence, K/V head), see decode_short in decode_slices.h; no workspace; with
 // a.k_new given it appends the step's tokens too
 hipError_t launch_decode_short(const AttnArgs& a, const int32_t* ctx_len, int32_t waves, int32_t max_ctx_len, int32_t num_cu, hipStream_t s);

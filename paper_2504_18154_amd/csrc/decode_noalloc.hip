@@ -10,7 +10,7 @@
 //
 // Every GPU holds its own copy of the array at its own address; the address is looked up once per device
 // (hipGetSymbolAddress with that device current) and kept.  All calls on one GPU share that GPU's array:
-// calls that overlap on one GPU (two streams, two threads) race on it.  The counters start at zero, as the array does,
+// calls that overlap on one GPU (two streams, two threads) race on it.  The counters and the slices' states start at zero, as the array does,
 // and every launch leaves them there; nothing else has to: a launch writes every word it later reads (each wavefront
 // writes its report, the merge reads only the states a report names).
 #include <mutex>
@@ -28,7 +28,8 @@ constexpr size_t kMlFloats = (size_t)2 * kNoallocMaxWaves * kMaxGroup * 2;
 constexpr size_t kMetaInts = (kMaxBatch + 19 + 63) / 64 * 64;
 constexpr size_t kCutInts = (size_t)4 * kNoallocMaxWaves;
 constexpr size_t kCountInts = (size_t)2 * kNoallocMaxWgs;  // small_decode: at most this many (sequence, K/V head)s
-constexpr size_t kScratchBytes = (kAccFloats + kMlFloats + kMetaInts + kCutInts + kCountInts) * 4;  // 16.3 MiB
+constexpr size_t kPartWords = (size_t)2 * kNoallocMaxWgs * kMaxGroup * (128 + 4);  // small_decode: slices' states, two workgroups per CU
+constexpr size_t kScratchBytes = (kAccFloats + kMlFloats + kMetaInts + kCutInts + kCountInts + kPartWords) * 4;  // 20.4 MiB
 
 // On the host this name is only a handle for hipGetSymbolAddress; device code and kernel arguments use the
 // address looked up below.
@@ -127,10 +128,9 @@ extern "C" int ecoserve_attn_decode_noalloc(int device, const ecoserve_layout* l
     return launch_decode_short(a, ctx_len, waves, max_ctx_len, n_wgs, s) == hipSuccess ? ECOSERVE_OK : ECOSERVE_EHIP;
   const SmallDecode small = small_decode(B, a.Hkv, max_ctx_len, n_wgs);
   if (small.n_split > 0) {
-    // (at most n_wgs slices in all, or one per (sequence, K/V head) of up to twice as many: their states of Hq / Hkv <= kMaxGroup
-    // heads fit the two groups of kMaxGroup slots per wavefront)
-    return launch_decode_any(a, ctx_len, small.split_tokens, small.n_split, ws_acc, ws_ml, reinterpret_cast<uint32_t*>(ws_cut + kCutInts),
-                             n_wgs, s) == hipSuccess ? ECOSERVE_OK : ECOSERVE_EHIP;
+    // (at most two slices per CU in all, of Hq / Hkv <= kMaxGroup heads)
+    uint32_t* const counts = reinterpret_cast<uint32_t*>(ws_cut + kCutInts);
+    return launch_decode_any(a, ctx_len, small.split_tokens, small.n_split, counts + kCountInts, counts, n_wgs, s) == hipSuccess ? ECOSERVE_OK : ECOSERVE_EHIP;
   }
   // (a slot group holds G <= kMaxGroup states, so the array covers kNoallocMaxWaves wavefronts whatever G is)
   hipError_t e = launch_decode_mfma(a, ctx_len, 0, max_ctx_len, n_wgs, ws_acc, ws_ml, ws_meta, kNoallocMaxWaves,

@@ -65,8 +65,10 @@ struct Slice {
 };
 constexpr Slice decode_slice(int ctx_len, int split_tokens, int max_slices, int sp) {
   const int want = (ctx_len + split_tokens - 1) / split_tokens, n = want < max_slices ? want : max_slices;
-  if (sp >= n) return {n, 0, 0};
-  return {n, sp * split_tokens, sp == n - 1 ? ctx_len : (sp + 1) * split_tokens};
+  // (without the number of slices, whose division a kernel need not wait for)
+  if (sp >= max_slices || (int64_t)sp * split_tokens >= ctx_len) return {n, 0, 0};
+  const int t0 = sp * split_tokens;
+  return {n, t0, sp == max_slices - 1 || ctx_len - t0 <= split_tokens ? ctx_len : t0 + split_tokens};
 }
 
 // The blocks of tokens [t0, t1) (t0 a multiple of 16) go to the wavefronts in turn: entries first + step i, i < n.

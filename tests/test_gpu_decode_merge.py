@@ -1,0 +1,75 @@
+"""Decode in slices: the merge of their partial states, which is done by the slice that starts last (short slices) or is done last (long ones), eight
+states at a time, and clears what it has read: every call finds the words as the first one did, whichever slices it has."""
+import os
+import subprocess
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2504_18154_amd import binding
+from paper_2504_18154_amd import workloads as wl
+from tests.parity_util import Layer, compare, compare_lse, say
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+# (type, head size, heads, lengths, forced slices or 0): 2, 8, 9 and some 60 slices; heads whose rows a group of 16 lanes, of 32, or
+# two rounds of 32 hold, whole and ragged; slices of more than four rounds; more workgroups than run at once
+CASES = [("bf16", 128, (40, 8), [700, 1100, 40], 0), ("bf16", 128, (8, 1), [60000], 0), ("bf16", 128, (16, 1), [9000, 129, 3000], 0),
+         ("f32", 64, (4, 2), [513, 64, 577], 64), ("f32", 32, (4, 2), [1025, 130], 128), ("bf16", 24, (6, 3), [700, 65], 64), ("bf16", 80, (8, 8), [600, 64, 1], 64),
+         ("f32", 100, (6, 3), [577, 512], 64), ("bf16", 200, (8, 2), [640, 70], 64), ("f32", 256, (4, 2), [577, 128], 64), ("bf16", 64, (32, 8), [1300] * 40, 64)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,D,heads,lens,split", CASES, ids=[f"{c[0]}-D{c[1]}-{c[2][0]}x{c[2][1]}-B{len(c[3])}-L{max(c[3])}-{c[4]}" for c in CASES])
+def test_merged_slices_call_after_call(dtype, D, heads, lens, split):
+    model = wl.ModelShape("merge", heads[0], heads[1], D, 1, dtype)
+    lens = np.asarray(lens, dtype=np.int32)
+    say(f"decode in slices, {dtype}, head size {D}, {len(lens)} sequences up to {lens.max()} tokens, slices of {split or 'its own choice'}")
+    pb = wl.prefill_batch(model, lens, 71)
+    layer = Layer(model, pb.num_blocks, pb.B, pb.block_table.shape[1])
+    if split:
+        layer.ctx.set_option(binding.OPT_DECODE_SPLIT_TOKENS, split)
+    layer.append(*(wl.randn((pb.T, model.Hkv, D), dtype, s) for s in (1, 2)), pb.cu_q, pb.ctx_before, pb.block_table)
+    q = wl.randn((pb.B, model.Hq, D), dtype, 3)
+    ref, ref_lse = layer.decode_oracle(q, pb.block_table, lens)
+    out, lse = layer.decode_gpu(q, pb.block_table, lens)
+    compare("decode", out, ref, dtype)
+    compare_lse("decode", lse, ref_lse, dtype)
+    fewer = np.maximum(1, lens // 3).astype(np.int32)
+    ref2, _ = layer.decode_oracle(q, pb.block_table, fewer)
+    for call in range(3):   # other slices, and the same again
+        out2, _ = layer.decode_gpu(q, pb.block_table, fewer)
+        compare("decode, shorter contexts", out2, ref2, dtype)
+        again, lse2 = layer.decode_gpu(q, pb.block_table, lens)
+        assert torch.equal(again, out) and torch.equal(lse2, lse), f"call {call} differs"
+    layer.close()
+
+
+BOUND = r"""
+#include <cstdio>
+#include "decode_slices.h"
+using namespace eco;
+// what a context holds (part_slots_needed in api.hip), in states per query head of a group: two workgroups per CU, or slices of 1024 tokens
+int main() {
+  unsigned seed = 7;
+  auto rnd = [&](unsigned n) { return (seed = seed * 1664525u + 1013904223u, (unsigned)((unsigned long long)(seed >> 8) * n >> 24)); };
+  for (int i = 0; i < 400000; ++i) {
+    const int cu = rnd(4) ? 256 : 8 + 8 * rnd(38), Hkv = 1 + rnd(rnd(2) ? 8 : 64), B = 1 + rnd(rnd(2) ? 64 : 4096), L = 1 + rnd(1 + rnd(rnd(2) ? 4096 : 400000)), D = 8 * (1 + rnd(32)), es = rnd(2) ? 2 : 4;
+    const SmallDecode s = small_decode(B, Hkv, L, cu), a = any_decode(B, Hkv, D, es, L, cu);
+    const long long of_s = (long long)(s.split_tokens ? B : 1) * Hkv * s.n_split, of_a = (long long)B * Hkv * a.n_split, few = 2LL * cu;
+    const long long uniform = (long long)B * Hkv * ((L + 1023) / 1024);
+    if (of_s > few) return std::printf("bf16, 128: B %d, %d heads, %d tokens, %d CUs: %lld states\n", B, Hkv, L, cu, of_s), 1;
+    if (of_a > (few > uniform ? few : uniform)) return std::printf("%d bytes, %d: B %d, %d heads, %d tokens, %d CUs: %lld states\n", es, D, B, Hkv, L, cu, of_a), 1;
+  }
+  std::printf("ok\n");
+}
+"""
+
+
+def test_slices_states_fit_what_a_context_holds(tmp_path):
+    src, exe = tmp_path / "bound.cpp", tmp_path / "bound"
+    src.write_text(BOUND)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-I", os.path.join(ROOT, "paper_2504_18154_amd", "csrc"), str(src), "-o", str(exe)], check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0 and r.stdout == "ok\n", r.stdout
