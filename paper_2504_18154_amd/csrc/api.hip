@@ -72,10 +72,10 @@ int64_t slots_needed(const ecoserve_ctx* c, int32_t* plain_splits) {
   return (int64_t)c->max_batch * c->lay.num_q_heads * *plain_splits;
 }
 
-// States that the slices of the kernels of attn_any_mfma.hip leave, as the rules in decode_slices.h cut: at most two workgroups per CU, or slices
+// States that the slices of the kernels of attn_any_mfma.hip leave, as the rules in decode_slices.h cut: at most eight per CU, or slices
 // of 1024 tokens, or as long as the option says.
 int64_t part_slots_needed(const ecoserve_ctx* c) {
-  const int64_t G = c->lay.num_q_heads / c->lay.num_kv_heads, few = 2 * (int64_t)c->num_cu * G;
+  const int64_t G = c->lay.num_q_heads / c->lay.num_kv_heads, few = 8 * (int64_t)c->num_cu * G;
   if (c->opt_force_plain || use_mfma(c)) return few;
   const int32_t st = c->opt_split_tokens > 0 ? c->opt_split_tokens : 1024;
   return std::max(few, (int64_t)c->max_batch * c->lay.num_q_heads * ceil_div(c->max_blocks_per_seq * kBlockSize, st));
@@ -116,10 +116,9 @@ int ensure_partial_states(ecoserve_ctx* c) {
   if (c->ws_share)  // (not while the context is made)
     if (const int st = ensure_parts(c); st != ECOSERVE_OK) return st;
   if (need <= c->ws_slots) return ECOSERVE_OK;
-  if (c->ws_acc || c->ws_ml) {
+  if (c->ws_acc) {
     if (hipDeviceSynchronize() != hipSuccess) return ECOSERVE_EHIP;  // launches in flight may still use them
-    if (c->ws_acc) (void)hipFree(c->ws_acc);
-    if (c->ws_ml) (void)hipFree(c->ws_ml);
+    (void)hipFree(c->ws_acc);
     c->ws_bytes -= (size_t)c->ws_slots * (c->lay.head_dim + 2) * sizeof(float);
   }
   c->ws_acc = nullptr;
@@ -127,13 +126,12 @@ int ensure_partial_states(ecoserve_ctx* c) {
   c->ws_slots = 0;
   const size_t acc_bytes = (size_t)need * c->lay.head_dim * sizeof(float);
   const size_t ml_bytes = (size_t)need * 2 * sizeof(float);
-  if (hipMalloc(&c->ws_acc, acc_bytes) != hipSuccess || hipMalloc(&c->ws_ml, ml_bytes) != hipSuccess) {
+  if (hipMalloc(&c->ws_acc, acc_bytes + ml_bytes) != hipSuccess) {  // (one allocation: each is tens of microseconds of creating a context)
     (void)hipGetLastError();
-    if (c->ws_acc) (void)hipFree(c->ws_acc);
     c->ws_acc = nullptr;
-    c->ws_ml = nullptr;
     return ECOSERVE_ENOMEM;
   }
+  c->ws_ml = c->ws_acc + (size_t)need * c->lay.head_dim;
   c->ws_slots = need;
   c->ws_bytes += acc_bytes + ml_bytes;
   return ECOSERVE_OK;
@@ -292,7 +290,7 @@ int ecoserve_create(ecoserve_ctx** out, int device, const ecoserve_layout* layou
     // per-XCD shares start equal; samples of 4 wavefronts per CU follow, then each chunk's report to the merge, then
     // the small-batch kernel's counters and, on a boundary of 256 bytes, its slices' states (one allocation: creating a context is a few of them and their clearing)
     const size_t share_words = 24 + 6 * (size_t)c->num_cu * kDecodeWgsPerCu * 4;
-    const size_t parts_at = (share_words + (size_t)c->max_batch * c->lay.num_kv_heads + 63) / 64 * 64;
+    const size_t counts = std::max((size_t)c->max_batch * c->lay.num_kv_heads, (size_t)8 * c->num_cu), parts_at = (share_words + counts + 63) / 64 * 64;
     const int64_t part_slots = part_slots_needed(c);
     const size_t share_bytes = (parts_at + (size_t)part_slots * (c->lay.head_dim + 4)) * sizeof(int32_t);
     const float ones[16] = {1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f};
@@ -317,7 +315,6 @@ int ecoserve_destroy(ecoserve_ctx* c) {
   int rc = ECOSERVE_OK;
   if (!guard.ok || hipDeviceSynchronize() != hipSuccess) rc = ECOSERVE_EHIP;
   if (c->ws_acc) (void)hipFree(c->ws_acc);
-  if (c->ws_ml) (void)hipFree(c->ws_ml);
   if (c->ws_more_parts) (void)hipFree(c->ws_more_parts);
   if (c->ws_plan) (void)hipFree(c->ws_plan);
   if (c->ws_share) (void)hipFree(c->ws_share);
@@ -560,6 +557,11 @@ static int decode_impl(ecoserve_ctx* c, const void* q, int64_t q_row_stride, con
   const SmallDecode small = !automatic   ? SmallDecode{0, 0}
                           : use_mfma(c) ? small_decode(B, a.Hkv, max_ctx_len, c->num_cu)
                                         : any_decode(B, a.Hkv, a.D, a.dtype == ECOSERVE_BF16 ? 2 : 4, max_ctx_len, c->num_cu);
+  if (use_mfma(c) && automatic && small.n_split == 0 && decode_sliced(B, a.Hkv, c->num_cu)) {
+    ProfileScope prof(c, ECOSERVE_KERNEL_DECODE, s);
+    e = launch_decode_sliced(a, ctx_len, max_ctx_len, c->ws_parts, c->ws_count, c->num_cu, s);
+    return e == hipSuccess ? ECOSERVE_OK : ECOSERVE_EHIP;
+  }
   if (use_mfma(c) && small.n_split == 0) {
     const int n_wgs = c->num_cu * kDecodeWgsPerCu;
     const bool adaptive = c->opt_adaptive && c->opt_split_tokens == 0 && n_wgs % 8 == 0;

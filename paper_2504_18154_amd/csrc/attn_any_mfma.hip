@@ -301,6 +301,122 @@ __device__ __forceinline__ SliceOf slice_of_workgroup(const int32_t* __restrict_
   }
 }
 
+// A row's partial states, one wavefront:
+//   M = max_k m_k;  l = sum_k l_k 2^(m_k - M);  o = sum_k acc_k 2^(m_k - M) / l,  in the order of the slices, whichever merges
+// (the division is the caller's).  `first`: the state of slice 0, the next ones slice_bytes further on each; slice `own` (-1: none) is in M, total and o.
+// The states of eight slices are asked for at once, those of the next eight while they are added up, and all again until they have
+// arrived: every slice has started, and none waits for another.  Each group of lanes takes every NG-th slice.  (Slices whose scores are all
+// -inf weigh nothing: their m is -inf, their sums are zero.)  Lane l has elements 4 (l % LG) of every 128.
+constexpr int lane_groups(int KS) { return KS <= 2 ? 4 : 2; }
+template <int KS, bool FULL>
+__device__ __forceinline__ void merge_slices(uint32_t* first, int slice_bytes, int row_bytes, int D, int n_split, int own_slice, float& M, float& total,
+                                             f32x4 (&o)[(KS + 3) / 4]) {
+  constexpr int NC = (KS + 3) / 4, NG = lane_groups(KS), LG = 64 / NG, kAtOnce = 8 / NG;  // (per group of lanes)
+  const int lane = threadIdx.x & 63, grp = lane / LG, el = (lane % LG) * 4;
+  auto weight = [](float x) { return FULL ? exp2f(x) : __builtin_amdgcn_exp2f(x); };  // (see softmax_step)
+  slice_bytes = scalar_here(slice_bytes);
+  float m2 = -INFINITY, l2 = 0.f;
+  f32x4 o2[NC];
+  int at_o[NC];
+#pragma unroll
+  for (int c = 0; c < NC; ++c) {
+    o2[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+    at_o[c] = (FULL ? min(el + 128 * c, D - 4) : el + 128 * c) * 4 + grp * slice_bytes;
+  }
+  const int at_ml = D * 4 + grp * slice_bytes;
+  struct Group {
+    u32x2 ml[kAtOnce];
+    u32x4 o[kAtOnce][NC];
+  };
+  auto range = [&](int base) {  // of the slices from `base` on, up to eight
+    const int more = min(n_split - base, NG * kAtOnce);
+    return __builtin_amdgcn_make_buffer_rsrc(scalar_here(reinterpret_cast<char*>(first) + (int64_t)base * slice_bytes), 0,
+                                             more > 0 ? (more - 1) * slice_bytes + row_bytes : 0, kRsrc32);
+  };
+  auto ask = [&](__amdgpu_buffer_rsrc_t from, Group& x) {  // (behind the last slice: out of range, zeros)
+    asm volatile("" ::: "memory");  // (memory has changed: without this the loads of a poll are taken for the same as before, and its loop for none)
+#pragma unroll
+    for (int j = 0; j < kAtOnce; ++j) {
+      x.ml[j] = __builtin_amdgcn_raw_buffer_load_b64(from, at_ml + NG * j * slice_bytes, 0, kAuxAgent);
+#pragma unroll
+      for (int c = 0; c < NC; ++c) x.o[j][c] = __builtin_amdgcn_raw_buffer_load_b128(from, at_o[c] + NG * j * slice_bytes, 0, kAuxAgent);
+    }
+  };
+  Group now, then;
+  int polls = 0;
+  __amdgpu_buffer_rsrc_t from = range(0);
+  ask(from, now);
+  for (int base = 0; base < n_split; base += NG * kAtOnce) {
+    const int more = n_split - base - grp, own = own_slice - base - grp;  // (slice NG j of this group of lanes: there, if NG j < more, this workgroup's, if NG j = own)
+    const __amdgpu_buffer_rsrc_t next = range(base + NG * kAtOnce);
+    ask(next, then);
+    auto missing = [&]() {
+      bool any = false;
+#pragma unroll
+      for (int j = 0; j < kAtOnce; ++j) {
+        uint32_t least = min(now.ml[j][0], now.ml[j][1]);
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) least = min(least, now.o[j][c][e]);
+        any |= (least == 0) & (NG * j < more) & (NG * j != own);
+      }
+      return __any(any);
+    };
+    if (missing()) {  // (apart from the first look, which then waits for these slices alone)
+      asm volatile("" ::: "memory");
+      do {
+        // who waits for long keeps out of the others' way: 0.4 us between looks, at the sums alone
+        for (bool wait = polls > 1; wait && polls < kMostPolls; ++polls) {
+          __builtin_amdgcn_s_sleep(16);
+          asm volatile("" ::: "memory");
+          bool any = false;
+#pragma unroll
+          for (int j = 0; j < kAtOnce; ++j)
+            any |= (__builtin_amdgcn_raw_buffer_load_b32(from, at_ml + 4 + NG * j * slice_bytes, 0, kAuxAgent) == 0) & (NG * j < more) & (NG * j != own);
+          wait = __any(any);
+        }
+        ask(from, now);
+      } while (missing() && ++polls < kMostPolls);
+    }
+    float m_new = m2, x[kAtOnce];
+#pragma unroll
+    for (int j = 0; j < kAtOnce; ++j) {  // (behind the last slice: nothing, of no weight)
+      x[j] = NG * j == own ? M : NG * j < more ? part_value(now.ml[j][0]) : -INFINITY;
+      m_new = fmaxf(m_new, x[j]);
+    }
+#pragma unroll
+    for (int j = 0; j < kAtOnce; ++j) {  // (this workgroup's own words are zero already)
+#pragma unroll
+      for (int c = 0; c < NC; ++c) store_part(from, at_o[c] + NG * j * slice_bytes, u32x4{0u, 0u, 0u, 0u});
+      store_part(from, at_ml + NG * j * slice_bytes, u32x2{0u, 0u});
+    }
+    const float mu = m_new == -INFINITY ? 0.f : m_new, old = m2 == -INFINITY ? 0.f : weight(m2 - mu);
+    m2 = m_new;
+    l2 *= old;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) o2[c] *= old;
+#pragma unroll
+    for (int j = 0; j < kAtOnce; ++j) {
+      const float wk = weight(x[j] - mu);
+      l2 += (NG * j == own ? total : NG * j < more ? part_value(now.ml[j][1]) : 0.f) * wk;
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o2[c][e] += (NG * j == own ? o[c][e] : NG * j < more ? part_value(now.o[j][c][e]) : 0.f) * wk;
+    }
+    from = next;
+    now = then;
+  }
+  M = max_of_groups<NG>(m2);
+  const float mine_weighs = m2 == -INFINITY ? 0.f : weight(m2 - M);
+  total = sum_of_groups<NG>(l2 * (m2 == -INFINITY ? 1.f : mine_weighs));
+#pragma unroll
+  for (int c = 0; c < NC; ++c)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) o[c][e] = sum_of_groups<NG>(o2[c][e] * mine_weighs);
+}
+
 // Decode: grid (splits, Hkv, B), or (Hkv, slices of all sequences) with balanced slices, W wavefronts; the blocks of a slice of `split_tokens` tokens of one (sequence, K/V
 // head) go to the wavefronts in turn, whose states are combined through LDS.  With one slice the result is final,
 // otherwise it is a partial state, and one workgroup of the (sequence, K/V head) merges them (`counters`, one per (sequence, K/V head), and `parts`: zero before
@@ -320,7 +436,7 @@ __global__ __launch_bounds__(W * 64) void decode_any_kernel(
   typedef Block<E, KS, AUX, FULL> Blk;
   constexpr int X = Elem<E>::X, NK = Blk::NK, NV = Blk::NV;
   // Where a wavefront has a row: NG groups of lanes share the states, and a lane has four elements of every 128 (or of 64).
-  constexpr int NC = (KS + 3) / 4, NG = KS <= 2 ? 4 : 2, LG = 64 / NG;
+  constexpr int NC = (KS + 3) / 4, NG = lane_groups(KS), LG = 64 / NG;
   __shared__ __attribute__((aligned(16))) E s_new[2][256];
   __shared__ __attribute__((aligned(16))) float2 s_ml[16][W];
   __shared__ __attribute__((aligned(16))) float s_acc[W][16][32 * KS + 4];
@@ -547,114 +663,7 @@ __global__ __launch_bounds__(W * 64) void decode_any_kernel(
       }
       continue;
     }
-    if (n_split > 1) {
-      //   M = max_k m_k;  l = sum_k l_k 2^(m_k - M);  o = sum_k acc_k 2^(m_k - M) / l,  in the order of the slices, whichever merges.
-      // The states of eight slices are asked for at once, those of the next eight while they are added up, and all again until they have
-      // arrived: every slice has started, and none waits for another.  Each group of lanes takes every NG-th slice.  (Slices whose scores are all
-      // -inf weigh nothing: their m is -inf, their sums are zero.)
-      constexpr int kAtOnce = 8 / NG;  // per group
-      const int slice_bytes = scalar_here((int)slice_words * 4);
-      float m2 = -INFINITY, l2 = 0.f;
-      f32x4 o2[NC];
-      int at_o[NC];
-#pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        o2[c] = f32x4{0.f, 0.f, 0.f, 0.f};
-        at_o[c] = (FULL ? min(el + 128 * c, D - 4) : el + 128 * c) * 4 + grp * slice_bytes;
-      }
-      const int at_ml = D * 4 + grp * slice_bytes;
-      struct Group {
-        u32x2 ml[kAtOnce];
-        u32x4 o[kAtOnce][NC];
-      };
-      auto range = [&](int base) {  // of the slices from `base` on, up to eight
-        const int more = min(n_split - base, NG * kAtOnce);
-        return __builtin_amdgcn_make_buffer_rsrc(scalar_here(mine + (int64_t)(base - sp) * (int64_t)slice_words), 0,
-                                                 more > 0 ? (more - 1) * slice_bytes + row_words * 4 : 0, kRsrc32);
-      };
-      auto ask = [&](__amdgpu_buffer_rsrc_t from, Group& x) {  // (behind the last slice: out of range, zeros)
-        asm volatile("" ::: "memory");  // (memory has changed: without this the loads of a poll are taken for the same as before, and its loop for none)
-#pragma unroll
-        for (int j = 0; j < kAtOnce; ++j) {
-          x.ml[j] = __builtin_amdgcn_raw_buffer_load_b64(from, at_ml + NG * j * slice_bytes, 0, kAuxAgent);
-#pragma unroll
-          for (int c = 0; c < NC; ++c) x.o[j][c] = __builtin_amdgcn_raw_buffer_load_b128(from, at_o[c] + NG * j * slice_bytes, 0, kAuxAgent);
-        }
-      };
-      Group now, then;
-      int polls = 0;
-      __amdgpu_buffer_rsrc_t from = range(0);
-      ask(from, now);
-      for (int base = 0; base < n_split; base += NG * kAtOnce) {
-        const int more = n_split - base - grp, own = sp - base - grp;  // (slice NG j of this group of lanes: there, if NG j < more, this workgroup's, if NG j = own)
-        const __amdgpu_buffer_rsrc_t next = range(base + NG * kAtOnce);
-        ask(next, then);
-        auto missing = [&]() {
-          bool any = false;
-#pragma unroll
-          for (int j = 0; j < kAtOnce; ++j) {
-            uint32_t least = min(now.ml[j][0], now.ml[j][1]);
-#pragma unroll
-            for (int c = 0; c < NC; ++c)
-#pragma unroll
-              for (int e = 0; e < 4; ++e) least = min(least, now.o[j][c][e]);
-            any |= (least == 0) & (NG * j < more) & (NG * j != own);
-          }
-          return __any(any);
-        };
-        if (missing()) {  // (apart from the first look, which then waits for these slices alone)
-          asm volatile("" ::: "memory");
-          do {
-            // who waits for long keeps out of the others' way: 0.4 us between looks, at the sums alone
-            for (bool wait = polls > 1; wait && polls < kMostPolls; ++polls) {
-              __builtin_amdgcn_s_sleep(16);
-              asm volatile("" ::: "memory");
-              bool any = false;
-#pragma unroll
-              for (int j = 0; j < kAtOnce; ++j)
-                any |= (__builtin_amdgcn_raw_buffer_load_b32(from, at_ml + 4 + NG * j * slice_bytes, 0, kAuxAgent) == 0) & (NG * j < more) & (NG * j != own);
-              wait = __any(any);
-            }
-            ask(from, now);
-          } while (missing() && ++polls < kMostPolls);
-        }
-        float m_new = m2, x[kAtOnce];
-#pragma unroll
-        for (int j = 0; j < kAtOnce; ++j) {  // (behind the last slice: nothing, of no weight)
-          x[j] = NG * j == own ? M : NG * j < more ? part_value(now.ml[j][0]) : -INFINITY;
-          m_new = fmaxf(m_new, x[j]);
-        }
-#pragma unroll
-        for (int j = 0; j < kAtOnce; ++j) {  // (this workgroup's own words are zero already)
-#pragma unroll
-          for (int c = 0; c < NC; ++c) store_part(from, at_o[c] + NG * j * slice_bytes, u32x4{0u, 0u, 0u, 0u});
-          store_part(from, at_ml + NG * j * slice_bytes, u32x2{0u, 0u});
-        }
-        const float mu = m_new == -INFINITY ? 0.f : m_new, old = m2 == -INFINITY ? 0.f : weight(m2 - mu);
-        m2 = m_new;
-        l2 *= old;
-#pragma unroll
-        for (int c = 0; c < NC; ++c) o2[c] *= old;
-#pragma unroll
-        for (int j = 0; j < kAtOnce; ++j) {
-          const float wk = weight(x[j] - mu);
-          l2 += (NG * j == own ? total : NG * j < more ? part_value(now.ml[j][1]) : 0.f) * wk;
-#pragma unroll
-          for (int c = 0; c < NC; ++c)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) o2[c][e] += (NG * j == own ? o[c][e] : NG * j < more ? part_value(now.o[j][c][e]) : 0.f) * wk;
-        }
-        from = next;
-        now = then;
-      }
-      M = max_of_groups<NG>(m2);
-      const float mine_weighs = m2 == -INFINITY ? 0.f : weight(m2 - M);
-      total = sum_of_groups<NG>(l2 * (m2 == -INFINITY ? 1.f : mine_weighs));
-#pragma unroll
-      for (int c = 0; c < NC; ++c)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) o[c][e] = sum_of_groups<NG>(o2[c][e] * mine_weighs);
-    }
+    if (n_split > 1) merge_slices<KS, FULL>(mine - (int64_t)sp * (int64_t)slice_words, (int)slice_words * 4, row_words * 4, D, n_split, sp, M, total, o);
     const float inv = 1.f / total;
     const size_t row = (size_t)b * Hq + g * G + h;
 #pragma unroll
@@ -684,12 +693,13 @@ __global__ __launch_bounds__(W * 64) void decode_any_kernel(
 // the last block read with the non-temporal hint or without, all of the block's K written back (4% worse than 16 bytes a unit), eight and
 // sixteen wavefronts (one CU takes in 24 bytes a clock, however many ask: 1 x 777 tokens 10.2, 10.1, 10.9 with 4, 8, 16), fewer workgroups
 // on a CU at a time (1024 x ~103: 118 with six, 124 with four, 160 with two).
-template <int W, bool ORDERED>
+enum class Order { kBatch, kLongest, kSliced };
+template <int W, Order ORDER>
 __global__ __launch_bounds__(W * 64, 3) void decode_short_kernel(
     const uint16_t* __restrict__ q, int q_row_stride, const uint16_t* __restrict__ k_new, const uint16_t* __restrict__ v_new, int new_row_stride,
     uint16_t* k_cache, uint16_t* v_cache, const int32_t* __restrict__ block_table, int bt_stride, const int32_t* __restrict__ ctx_len,
     uint16_t* __restrict__ out, float* __restrict__ lse, int Hq, int Hkv, int G, float scale_log2e, int B,
-    int per_group, int shift, int stream) {
+    int per_group, int shift, int stream, uint32_t* parts, uint32_t* counters, int max_full) {
   typedef Block<uint16_t, 4, kNonTemporal, false> Blk;
   constexpr int D = 128, kPiece = 16 * D * 2;
   static_assert(W <= 8, "a wavefront adds up whole tiles");
@@ -697,16 +707,13 @@ __global__ __launch_bounds__(W * 64, 3) void decode_short_kernel(
   __shared__ __attribute__((aligned(16))) char s_out[16 * 256];  // output rows: chunk c of row r at 256 r + 16 (c ^ r)
   __shared__ __attribute__((aligned(16))) f32x4 s_acc[W > 1 ? W : 1][W > 1 ? 8 : 1][64];
   __shared__ float s_m[W][16], s_l[W][16];
-  __shared__ int s_bad;
+  __shared__ int s_bad, s_order;
   const int g = blockIdx.x;
   const int tid = threadIdx.x, lane = tid & 63, wave = W > 1 ? __builtin_amdgcn_readfirstlane(tid >> 6) : 0;
   const int col = lane & 15, quad = lane >> 4;
-  int b = blockIdx.y, L;
-  if constexpr (ORDERED) {
-    const int first = b * per_group, have = min(per_group, B - first);
-    int r = blockIdx.z;
-    if (r >= have) return;
-    const int len = lane < have ? ctx_len[first + lane] : 0, key = min(len >> shift, 15);
+  int b = blockIdx.y, L, n_split = 1, slice_no = 0, slot = 0, blk0 = 0, blk1 = 0;  // (sliced: the slices of the context, this one, its slot and its blocks)
+  // the lane of rank r, by a class of 0 to 15, largest first, among lanes 0 .. have - 1
+  auto select = [&](int key, int have, int r) {
     // `left`: the lanes among which the one of rank r still is; a bit of the key at a time, those that have it come first
     unsigned long long left = ~0ull >> (64 - have);
 #pragma unroll
@@ -717,9 +724,57 @@ __global__ __launch_bounds__(W * 64, 3) void decode_short_kernel(
       r = r < n_ones ? r : r - n_ones;
     }
     const int before = __builtin_amdgcn_mbcnt_hi((unsigned)(left >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)left, 0u));
-    const int at = __builtin_ctzll(__ballot((left >> lane & 1) != 0 && before == r));
+    return (int)__builtin_ctzll(__ballot((left >> lane & 1) != 0 && before == r));
+  };
+  if constexpr (ORDER == Order::kLongest) {
+    const int first = b * per_group, have = min(per_group, B - first), r = blockIdx.z;
+    if (r >= have) return;
+    const int len = lane < have ? ctx_len[first + lane] : 0, at = select(min(len >> shift, 15), have, r);
     b = first + at;
     L = __builtin_amdgcn_readlane(len, at);
+  } else if constexpr (ORDER == Order::kSliced) {
+    // Group j has the sequences j, j + groups, ..: much the same lengths where a batch is sorted.  The groups take turns with the XCDs.
+    const int groups = gridDim.y, group = (int)(b + (blockIdx.z >> 1) + (blockIdx.z >> 3)) % groups, have = (B - group + groups - 1) / groups;
+    int len[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int s = lane * groups + j;
+      len[j] = j < groups && s < B ? ctx_len[s] : 0;
+    }
+    int sum = 0, mine = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      sum += (len[j] + 15) >> 4;
+      mine = j == group ? len[j] : mine;
+    }
+    const SlicedContexts cut = sliced_contexts(__builtin_amdgcn_readlane(lanes_prefix_sum(sum), 63), max_full, W);
+    const int nb = (mine + 15) >> 4, full = cut.full(nb);
+    const int upto = lanes_prefix_sum(full), n_full = __builtin_amdgcn_readlane(upto, 63);
+    // slots of the groups before this one: their whole slices, and one more for each context that is cut
+    int earlier = 0;
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+      const int f = j < group ? cut.full((len[j] + 15) >> 4) : 0;
+      earlier += f + (f > 0 ? 1 : 0);
+    }
+    earlier = __builtin_amdgcn_readlane(lanes_prefix_sum(earlier), 63);
+    int r = blockIdx.z, at, k;
+    if (r < n_full) {
+      at = __builtin_ctzll(__ballot(upto > r));
+      k = r - __builtin_amdgcn_readlane(upto - full, at);
+    } else {
+      r -= n_full;
+      if (r >= have) return;
+      at = select(cut.size_class(nb - full * cut.blocks), have, r);
+      k = __builtin_amdgcn_readlane(full, at);
+    }
+    b = at * groups + group;
+    L = __builtin_amdgcn_readlane(mine, at);
+    n_split = __builtin_amdgcn_readlane(full, at) + 1;
+    slice_no = k;
+    blk0 = k * cut.blocks;
+    blk1 = k < n_split - 1 ? blk0 + cut.blocks : (L + 15) >> 4;
+    slot = earlier + __builtin_amdgcn_readlane(upto - full, at) + (int)__popcll(__ballot(full > 0) & ((1ull << at) - 1)) + k;
   } else {
     L = __builtin_amdgcn_readfirstlane(ctx_len[b]);
   }
@@ -734,8 +789,9 @@ __global__ __launch_bounds__(W * 64, 3) void decode_short_kernel(
     qf[j] = col < G ? *reinterpret_cast<const u32x4*>(q + (size_t)b * q_row_stride + (size_t)(g * G + col) * D + (4 * j + quad) * 8) : z;
   }
   if (L <= 0) return;  // (no output for an empty sequence)
-  const int nb = (L + 15) >> 4, n = (nb - wave + W - 1) / W;  // this wavefront's blocks: wave + W i, i < n
-  const bool has_last = wave + W * (n - 1) == nb - 1;
+  if (ORDER != Order::kSliced) blk1 = (L + 15) >> 4;
+  const int nb = blk1 - blk0, n = (nb - wave + W - 1) / W;  // this wavefront's blocks: blk0 + wave + W i, i < n
+  const bool ends = ORDER != Order::kSliced || blk1 == (L + 15) >> 4, has_last = ends && wave + W * (n - 1) == nb - 1;
   const char* const kc = reinterpret_cast<const char*>(k_cache) + (size_t)g * kPiece;
   const char* const vc = reinterpret_cast<const char*>(v_cache) + (size_t)g * kPiece;
   const size_t blk_stride = (size_t)Hkv * kPiece;
@@ -756,7 +812,7 @@ __global__ __launch_bounds__(W * 64, 3) void decode_short_kernel(
   Blk f0;
   for (int base = 0; base < n; base += 64) {  // (the 64 ids that a register holds: 1024 W tokens)
     const int nw = min(64, n - base);
-    const int ids = lane < nw ? bt_row[wave + W * (base + lane)] : 0;
+    const int ids = lane < nw ? bt_row[blk0 + wave + W * (base + lane)] : 0;
     if (base == 0 && has_last && fused) {  // (kept in LDS: it was asked for before the ids, and registers are short)
       *reinterpret_cast<u32x2*>(s_new + lane * 4) = row;
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -794,7 +850,7 @@ __global__ __launch_bounds__(W * 64, 3) void decode_short_kernel(
     }
     int tail = 16;
     if (base + 64 >= n && has_last) {  // f0 is the sequence's last block
-      tail = L - 16 * (nb - 1);
+      tail = L - 16 * (blk1 - 1);
       if (fused) {
         f0.put_token(s_new, s_new + D, tail - 1, D, col, quad);
         // A token is 16 places of 16 bytes of K and 128 places of two bytes of V, and the memory reads and writes 64 bytes at a time.  The
@@ -846,7 +902,11 @@ __global__ __launch_bounds__(W * 64, 3) void decode_short_kernel(
     }
 #pragma unroll
     for (int dt = 0; dt < 8; ++dt) s_acc[wave][dt][lane] = acc[dt];
-    if (tid == 0) s_bad = 0;
+    if (tid == 0) {
+      s_bad = 0;
+      if (ORDER == Order::kSliced && n_split > 1)  // (the slice that is done last merges them all, as in decode_any_kernel; the last one wraps the count to zero)
+        s_order = (int)atomicInc(counters + (size_t)(slot - slice_no) * Hkv + g, (unsigned)n_split - 1);
+    }
     __syncthreads();
     float M = s_m[0][col];
 #pragma unroll
@@ -862,6 +922,45 @@ __global__ __launch_bounds__(W * 64, 3) void decode_short_kernel(
       total += s_l[w][col] * (mw == -INFINITY ? 1.f : wk);
 #pragma unroll
       for (int t = 0; t < kOwn; ++t) sum[t] += s_acc[w][dt0 + t][lane] * wk;
+    }
+    if (ORDER == Order::kSliced && n_split > 1) {
+#pragma unroll
+      for (int t = 0; t < kOwn; ++t)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) zero = __builtin_fmaf(sum[t][e], 0.f, zero);
+      if (zero != zero && col < G && total == total) s_bad = 1;
+      __syncthreads();
+      const int row_words = part_words(D);
+      uint32_t* const first = parts + ((size_t)(slot - slice_no) * Hq + (size_t)g * G) * row_words;  // (slice 0, the group's first head)
+      const int slice_bytes = Hq * row_words * 4;
+      const __amdgpu_buffer_rsrc_t to = __builtin_amdgcn_make_buffer_rsrc(scalar_here(reinterpret_cast<char*>(first) + (size_t)slice_no * slice_bytes), 0, G * row_words * 4, kRsrc32);
+      if (!s_bad) {
+        if (col < G) {
+#pragma unroll
+          for (int t = 0; t < kOwn; ++t) store_part(to, (col * row_words + (dt0 + t) * 16 + 4 * quad) * 4, part_bits(sum[t]));
+          if (wave == 0 && quad == 0) store_part(to, (col * row_words + D) * 4, u32x2{part_bits(M), part_bits(total)});
+        }
+      } else {  // (see attend_row)
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();  // (the newest token is in the cache)
+        for (int h = wave; h < G; h += W) {
+          float rm, rl, o[4];
+          attend_row<uint16_t>(q + (size_t)b * q_row_stride + (size_t)(g * G + h) * D, k_cache, v_cache, bt_row, g, Hkv, D, 16 * blk0, min(L, 16 * blk1), scale_log2e, rm, rl, o);
+#pragma unroll
+          for (int r = 0; r < 2; ++r) __builtin_amdgcn_raw_buffer_store_b32(part_bits(o[r]), to, (h * row_words + lane + 64 * r) * 4, 0, kAuxAgent);
+          if (lane == 0) store_part(to, (h * row_words + D) * 4, u32x2{part_bits(rm), part_bits(rl)});
+        }
+      }
+      if (s_order != n_split - 1) return;
+      for (int h = wave; h < G; h += W) {
+        float rm = 0.f, rl = 0.f;
+        f32x4 o[1] = {f32x4{0.f, 0.f, 0.f, 0.f}};
+        merge_slices<4, false>(first + h * row_words, slice_bytes, row_words * 4, D, n_split, -1, rm, rl, o);
+        const size_t row = (size_t)b * Hq + (size_t)g * G + h;
+        if (lane < 32) store4(out + row * D + lane * 4, o[0] * (1.f / rl));
+        if (lse && lane == 0) lse[row] = (rm + log2f(rl)) * kLn2;
+      }
+      return;
     }
     const float inv = 1.f / total;
 #pragma unroll
@@ -1165,26 +1264,38 @@ hipError_t launch_prefill_any(const AttnArgs& a, const int32_t* cu_q, const int3
   return hipGetLastError();
 }
 
-hipError_t launch_decode_short(const AttnArgs& a, const int32_t* ctx_len, int32_t waves, int32_t max_ctx_len, int32_t num_cu, hipStream_t s) {
-  const int64_t pairs = (int64_t)a.B * a.Hkv;
-  const bool ordered = decode_short_ordered(pairs, max_ctx_len, num_cu);
+namespace {
+
+template <int W, Order ORDER>
+hipError_t launch_whole(const AttnArgs& a, const int32_t* ctx_len, int32_t max_ctx_len, bool stream, uint32_t* parts, uint32_t* counters, int32_t max_full, hipStream_t s) {
   // groups of equal size, at most one sequence per lane; length classes: the largest holds max_ctx_len and what lies above it
   const int groups = (a.B + 63) / 64, per_group = (a.B + groups - 1) / groups;
   int shift = 4;
   while (max_ctx_len >> shift > 15) ++shift;
-  auto launch = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, ordered ? dim3((unsigned)a.Hkv, (unsigned)groups, (unsigned)per_group) : dim3((unsigned)a.Hkv, (unsigned)a.B), dim3(waves * 64), 0, s,
-                       (const uint16_t*)a.q, a.q_row_stride, (const uint16_t*)a.k_new, (const uint16_t*)a.v_new, a.new_row_stride,
-                       (uint16_t*)const_cast<void*>(a.k_cache), (uint16_t*)const_cast<void*>(a.v_cache), a.block_table, a.bt_stride, ctx_len,
-                       (uint16_t*)a.out, a.lse, a.Hq, a.Hkv, a.Hq / a.Hkv, a.scale_log2e, a.B, per_group, shift, decode_short_stream(pairs, max_ctx_len) ? 1 : 0);
-    return hipGetLastError();
-  };
+  const dim3 grid = ORDER == Order::kBatch ? dim3((unsigned)a.Hkv, (unsigned)a.B) : dim3((unsigned)a.Hkv, (unsigned)groups, (unsigned)(per_group + max_full));
+  hipLaunchKernelGGL((decode_short_kernel<W, ORDER>), grid, dim3(W * 64), 0, s, (const uint16_t*)a.q, a.q_row_stride, (const uint16_t*)a.k_new, (const uint16_t*)a.v_new,
+                     a.new_row_stride, (uint16_t*)const_cast<void*>(a.k_cache), (uint16_t*)const_cast<void*>(a.v_cache), a.block_table, a.bt_stride, ctx_len,
+                     (uint16_t*)a.out, a.lse, a.Hq, a.Hkv, a.Hq / a.Hkv, a.scale_log2e, a.B, per_group, shift, stream ? 1 : 0, parts, counters, max_full);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_decode_short(const AttnArgs& a, const int32_t* ctx_len, int32_t waves, int32_t max_ctx_len, int32_t num_cu, hipStream_t s) {
+  const int64_t pairs = (int64_t)a.B * a.Hkv;
+  const bool stream = decode_short_stream(pairs, max_ctx_len);
   auto of = [&](auto w) {
     constexpr int W = decltype(w)::value;
-    return ordered ? launch(decode_short_kernel<W, true>) : launch(decode_short_kernel<W, false>);
+    return decode_short_ordered(pairs, max_ctx_len, num_cu) ? launch_whole<W, Order::kLongest>(a, ctx_len, max_ctx_len, stream, nullptr, nullptr, 0, s)
+                                                            : launch_whole<W, Order::kBatch>(a, ctx_len, max_ctx_len, stream, nullptr, nullptr, 0, s);
   };
   return waves == 1 ? of(std::integral_constant<int, 1>()) : waves == 2 ? of(std::integral_constant<int, 2>()) : waves == 4 ? of(std::integral_constant<int, 4>())
                                                                                                                   : hipErrorInvalidValue;
+}
+
+hipError_t launch_decode_sliced(const AttnArgs& a, const int32_t* ctx_len, int32_t max_ctx_len, uint32_t* parts, uint32_t* counters, int32_t num_cu, hipStream_t s) {
+  if (a.B > kSlicedMostSequences) return hipErrorInvalidValue;
+  return launch_whole<4, Order::kSliced>(a, ctx_len, max_ctx_len, decode_short_stream((int64_t)a.B * a.Hkv, max_ctx_len), parts, counters, sliced_most_full(a.B, a.Hkv, num_cu), s);
 }
 
 hipError_t launch_decode_any(const AttnArgs& a, const int32_t* ctx_len, int32_t split_tokens, int32_t n_split_max, uint32_t* parts,

@@ -98,7 +98,7 @@ struct ecoserve_ctx {
   float* ws_share;             // per-XCD shares (mean 1) [2][8], speeds [8], then as int32 [2 * wavefronts]: units, ticks,
                                // then [4 * wavefronts]: the cut (sequence, K/V head) each chunk reports to the merge
   int share_parity;            // which of the two share vectors the next adaptive decode launch reads
-  uint32_t* ws_count;          // [max_batch][Hkv], zero between launches: slices of a (sequence, K/V head) that have started
+  uint32_t* ws_count;          // [max_batch][Hkv] and at least eight per CU, zero between launches: slices of a (sequence, K/V head) that have started
   uint32_t* ws_parts;          // part_slots partial states of D + 4 words, zero between launches: slices of the kernels of attn_any_mfma.hip
   uint32_t* ws_more_parts;     // where ws_parts points once an option has asked for more of them than the context was made with, else NULL
   int64_t part_slots;
@@ -176,6 +176,10 @@ hipError_t launch_decode_any(const AttnArgs& a, const int32_t* ctx_len, int32_t 
 // (bf16, 128), whole contexts: `waves` (1, 2 or 4) wavefronts per (sequence, K/V head), see decode_short in decode_slices.h; no workspace; with
 // a.k_new given it appends the step's tokens too
 hipError_t launch_decode_short(const AttnArgs& a, const int32_t* ctx_len, int32_t waves, int32_t max_ctx_len, int32_t num_cu, hipStream_t s);
+
+// The same, longest first, long contexts cut (at most kSlicedMostSequences sequences, see decode_slices.h): parts and counters as launch_decode_any's, 2 sliced_most_full(B,
+// Hkv, num_cu) of each per K/V head
+hipError_t launch_decode_sliced(const AttnArgs& a, const int32_t* ctx_len, int32_t max_ctx_len, uint32_t* parts, uint32_t* counters, int32_t num_cu, hipStream_t s);
 
 // attn_decode_mfma.hip: bf16, D = 128
 // (split_tokens 0 = equal share per wavefront of the persistent grid; > 0 forces the chunk size)

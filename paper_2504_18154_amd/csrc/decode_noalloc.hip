@@ -27,9 +27,9 @@ constexpr size_t kAccFloats = (size_t)2 * kNoallocMaxWaves * kMaxGroup * 128;  /
 constexpr size_t kMlFloats = (size_t)2 * kNoallocMaxWaves * kMaxGroup * 2;
 constexpr size_t kMetaInts = (kMaxBatch + 19 + 63) / 64 * 64;
 constexpr size_t kCutInts = (size_t)4 * kNoallocMaxWaves;
-constexpr size_t kCountInts = (size_t)2 * kNoallocMaxWgs;  // small_decode: at most this many (sequence, K/V head)s
-constexpr size_t kPartWords = (size_t)2 * kNoallocMaxWgs * kMaxGroup * (128 + 4);  // small_decode: slices' states, two workgroups per CU
-constexpr size_t kScratchBytes = (kAccFloats + kMlFloats + kMetaInts + kCutInts + kCountInts + kPartWords) * 4;  // 20.4 MiB
+constexpr size_t kCountInts = (size_t)8 * kNoallocMaxWgs;  // small_decode, decode_sliced: at most this many contexts that are cut
+constexpr size_t kPartWords = (size_t)8 * kNoallocMaxWgs * kMaxGroup * (128 + 4);  // their slices' states, eight per CU
+constexpr size_t kScratchBytes = (kAccFloats + kMlFloats + kMetaInts + kCutInts + kCountInts + kPartWords) * 4;  // 32.8 MiB
 
 // On the host this name is only a handle for hipGetSymbolAddress; device code and kernel arguments use the
 // address looked up below.
@@ -131,6 +131,10 @@ extern "C" int ecoserve_attn_decode_noalloc(int device, const ecoserve_layout* l
     // (at most two slices per CU in all, of Hq / Hkv <= kMaxGroup heads)
     uint32_t* const counts = reinterpret_cast<uint32_t*>(ws_cut + kCutInts);
     return launch_decode_any(a, ctx_len, small.split_tokens, small.n_split, counts + kCountInts, counts, n_wgs, s) == hipSuccess ? ECOSERVE_OK : ECOSERVE_EHIP;
+  }
+  if (decode_sliced(B, a.Hkv, n_wgs)) {
+    uint32_t* const counts = reinterpret_cast<uint32_t*>(ws_cut + kCutInts);
+    return launch_decode_sliced(a, ctx_len, max_ctx_len, counts + kCountInts, counts, n_wgs, s) == hipSuccess ? ECOSERVE_OK : ECOSERVE_EHIP;
   }
   // (a slot group holds G <= kMaxGroup states, so the array covers kNoallocMaxWaves wavefronts whatever G is)
   hipError_t e = launch_decode_mfma(a, ctx_len, 0, max_ctx_len, n_wgs, ws_acc, ws_ml, ws_meta, kNoallocMaxWaves,

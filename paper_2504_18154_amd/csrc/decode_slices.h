@@ -163,6 +163,30 @@ inline bool decode_short_ordered(int64_t pairs, int32_t max_ctx_len, int32_t num
 // 1.01; 16385 to 32768, 97..192 1.19 / 1.01.
 constexpr bool decode_short_stream(int64_t pairs, int32_t max_ctx_len) { return pairs > (max_ctx_len <= 192 ? 2048 : 4096); }
 
+// Whole contexts, longest first, the longer ones cut (decode_short_kernel, kSliced): slices of `blocks` blocks, whole ones first, then what is left of each context.  No
+// more than `max_full` whole slices per K/V head come of it, whatever the lengths, and twice as many slots for partial states.
+constexpr int32_t kSlicedMostSequences = 256;  // four lengths per lane
+inline int32_t sliced_most_full(int32_t B, int32_t Hkv, int32_t num_cu) { return ((int64_t)B * Hkv * 4 <= 7 * (int64_t)num_cu ? 4 : 2) * num_cu / Hkv; }
+struct SlicedContexts {
+  int blocks;
+  float per_block;
+  ECO_SLICES_HD int full(int nb) const {  // whole slices of a context of nb blocks, at least one block being left over
+    if (nb <= blocks) return 0;
+    const int f = (int)(((float)nb - 0.5f) * per_block);
+    return (int64_t)f * blocks >= nb ? f - 1 : f;
+  }
+  ECO_SLICES_HD int size_class(int left) const {  // 0 to 15
+    const int c = (int)((float)left * per_block * 15.f);
+    return c < 15 ? c : 15;
+  }
+};
+ECO_SLICES_HD SlicedContexts sliced_contexts(int sum, int max_full, int W) {
+  constexpr int kLeast = 24;
+  const int even = max_full > 0 ? (sum + max_full - 1) / max_full : sum, least = even > kLeast ? even : kLeast;
+  const int blocks = (least + W - 1) / W * W;
+  return {blocks, quotient(1.f, (float)blocks)};
+}
+
 // For (bf16, 128), batches that decode_short leaves: how decode_any_kernel takes a small one, n_split 0 if it does not.  It needs no numbering of the batch and no
 // second launch, which is what such a batch spends its time on in the persistent kernel.
 //   Several sequences, one of them of more than 768 tokens, and eight workgroups (one per CU) or more per five (sequence, K/V
@@ -199,5 +223,15 @@ inline SmallDecode small_decode(int32_t B, int32_t Hkv, int32_t max_ctx_len, int
   if (B <= 64 && 8 * B <= 5 * slots2 && pairs * max_ctx_len <= 600000) return {0, slots2};
   return {0, 0};
 }
+
+// For (bf16, 128), batches that neither of these takes: whether whole contexts with the longer ones cut have them (else the persistent kernel).  Up to where the
+// launch's start and end no longer count beside its stream: at 3120 (sequence, K/V head)s, 52 on 52, 60 x 1500..2000 tokens, the persistent kernel takes 461 us, this one 482.
+//   Us per call, fused append, the persistent kernel / here: 40 on 8, 128 x 512..4096 208 / 196, 64 x 20..2000 57.6 / 52.8, 100 x 50..3000 118.8 / 109.3, 256 x 100..1800 190 / 176,
+// 127 x 20 and one of 4000 24.0 / 16.2; 64 on 8, 256 x 1024..4096 459.5 / 451.3, 128 x 8192 671 / 672, 8 x 60000 323 / 313; 52 on 52, 24 x 300..3000 185 / 177; 32 on 8, 64 x 4096 183 / 170,
+// 84 x 300 and six of 6000 57.9 / 49.7; 8 on 1, 256 x 100..6000 78.7 / 78.0; 5 on 1, 150 x 300..16000 110 / 117.  Of 43 random batches of eight head shapes (lengths equal, from 1/2, 1/8, 1/64
+// of the longest, lognormal, one in 16 ten times the others) 0.93 of the time on average, the worst 1.03.
+//   Four whole slices per CU at most for up to 1.75 (sequence, head)s per CU, where one workgroup more or less on a CU shows, two above (two / four: 52 on 52, 5 x 200..6000
+// 76.0 / 71.5, 8 on 1, 200 x 8000 149.9 / 139.3, 32 on 8, 31 x 1000..9000 113 / 110, 64 x 4096 170 / 178, 40 on 8, 16 x 16000 169 / 173).
+inline bool decode_sliced(int32_t B, int32_t Hkv, int32_t num_cu) { return B <= kSlicedMostSequences && (int64_t)B * Hkv <= (int64_t)8 * num_cu; }
 
 }  // namespace eco
