@@ -166,9 +166,17 @@ __device__ __forceinline__ f32x4 softmax_step(const f32x4& s, float& m, float& l
     m = m_new;
   }
   const float mu = m == -INFINITY ? 0.f : m;  // (a row all of whose keys so far are masked)
-  f32x4 p;  // exp2f: the bare instruction flushes weights below 2^-126, which large values can still make count
+  f32x4 p;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) p[i] = FULL ? exp2f(s[i] - mu) : __builtin_amdgcn_exp2f(s[i] - mu);
+  for (int i = 0; i < 4; ++i) p[i] = s[i] - mu;
+  // The bare instruction flushes weights below 2^-126, which large values can still make count: where there are any (or masked keys), exp2f.
+  if (FULL && __any(fminf(fminf(p[0], p[1]), fminf(p[2], p[3])) < -126.f)) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) p[i] = exp2f(p[i]);
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) p[i] = __builtin_amdgcn_exp2f(p[i]);
+  }
   l += (p[0] + p[1]) + (p[2] + p[3]);
   return p;
 }
