@@ -213,7 +213,11 @@ inline SmallDecode small_decode(int32_t B, int32_t Hkv, int32_t max_ctx_len, int
   const bool whole = whole_context((float)nb, (float)nb * (float)Hkv);  // (also of more sequences, then)
   if (!whole && slots > 0 && pairs * ((max_ctx_len + 1023) / 1024) <= num_cu) {
     int32_t st = ((int32_t)least_slice((float)nb) + 4) / 8 * 8;  // whole rounds of eight wavefronts
+    // no more than 16 slices up to 40 blocks each (the merge adds up eight at a time; 1 x 8000, 64 heads on 8: 21 slices 14.2, 13 12.4, 8 on 1 11.0 / 9.9)
+    if (B == 1 && nb <= 16 * 40) st = std::max(st, (nb + 16 * 8 - 1) / (16 * 8) * 8);
     if (B == 1) st = std::max(st, (nb + 8 * slots - 1) / (8 * slots) * 8);
+    // slices of 256 tokens for all sooner than balanced ones: no search, and plain loads (40 on 8, 8 x 1000 12.4 balanced, 11.3 so)
+    if (B > 1 && st == 8 && B * ((nb + 7) / 8) > slots && B * ((nb + 15) / 16) <= slots) st = 16;
     if (B * ((nb + st - 1) / st) <= slots && (B == 1 || nb > 48)) return {st * 16, (nb + st - 1) / st};
   }
   if (B > 1 && B <= 64 && nb > 48 && 8 * B <= 5 * slots && pairs * max_ctx_len <= 800000) return {0, slots};
