@@ -557,7 +557,8 @@ static int decode_impl(ecoserve_ctx* c, const void* q, int64_t q_row_stride, con
   const SmallDecode small = !automatic   ? SmallDecode{0, 0}
                           : use_mfma(c) ? small_decode(B, a.Hkv, max_ctx_len, c->num_cu)
                                         : any_decode(B, a.Hkv, a.D, a.dtype == ECOSERVE_BF16 ? 2 : 4, max_ctx_len, c->num_cu);
-  if (use_mfma(c) && automatic && small.n_split == 0 && decode_sliced(B, a.Hkv, c->num_cu)) {
+  if (use_mfma(c) && automatic && small.n_split == 0 && decode_sliced(B, a.Hkv, c->num_cu) &&
+      !(c->opt_adaptive && adaptive_stream(B, a.Hkv, max_ctx_len, c->num_cu))) {
     ProfileScope prof(c, ECOSERVE_KERNEL_DECODE, s);
     e = launch_decode_sliced(a, ctx_len, max_ctx_len, c->ws_parts, c->ws_count, c->num_cu, s);
     return e == hipSuccess ? ECOSERVE_OK : ECOSERVE_EHIP;

@@ -237,5 +237,10 @@ inline SmallDecode small_decode(int32_t B, int32_t Hkv, int32_t max_ctx_len, int
 //   Four whole slices per CU at most for up to 1.75 (sequence, head)s per CU, where one workgroup more or less on a CU shows, two above (two / four: 52 on 52, 5 x 200..6000
 // 76.0 / 71.5, 8 on 1, 200 x 8000 149.9 / 139.3, 32 on 8, 31 x 1000..9000 113 / 110, 64 x 4096 170 / 178, 40 on 8, 16 x 16000 169 / 173).
 inline bool decode_sliced(int32_t B, int32_t Hkv, int32_t num_cu) { return B <= kSlicedMostSequences && (int64_t)B * Hkv <= (int64_t)8 * num_cu; }
+// A context that asks for shares by each XCD's measured speed keeps the persistent kernel for its longest launches: the shares take 1 to 3% off a stream, which is more
+// than the launch of the merge and the uneven end cost once the stream is long.  Us per call with such shares, the persistent kernel / here: 64 on 8, 256 x 1024..4096
+// 447 / 449, 200 x 1024..8300 624 / 636, 16 x 30000..60000 482 / 493; 32 on 32, 64 x 500..4096 392 / 398; 40 on 8, 160 x 512..4096 252 / 251, 128 x 512..4096 206 / 199.  (With
+// equal shares the first of these take 456, 631, 484, 397, 257: all but the third longer than here.)
+inline bool adaptive_stream(int32_t B, int32_t Hkv, int32_t max_ctx_len, int32_t num_cu) { return (int64_t)B * Hkv * max_ctx_len > (int64_t)20000 * num_cu; }
 
 }  // namespace eco

@@ -97,11 +97,12 @@ RULE = r"""
 #include <vector>
 #include "decode_slices.h"
 using namespace eco;
-// one line per batch: "B Hkv bound", answered by the kernel that takes it; then, over random batches, what the kernel makes of the lengths
+// one line per batch: "B Hkv bound adaptive", answered by the kernel that takes it; then, over random batches, what the kernel makes of the lengths
 int main() {
-  int B, Hkv, bound;
-  while (std::scanf("%d %d %d", &B, &Hkv, &bound) == 3)
-    std::printf("%s\n", decode_short(B, Hkv, bound, 256) ? "whole" : small_decode(B, Hkv, bound, 256).n_split ? "small" : decode_sliced(B, Hkv, 256) ? "sliced" : "persistent");
+  int B, Hkv, bound, adaptive;
+  while (std::scanf("%d %d %d %d", &B, &Hkv, &bound, &adaptive) == 4)
+    std::printf("%s\n", decode_short(B, Hkv, bound, 256) ? "whole" : small_decode(B, Hkv, bound, 256).n_split ? "small"
+                         : decode_sliced(B, Hkv, 256) && !(adaptive && adaptive_stream(B, Hkv, bound, 256)) ? "sliced" : "persistent");
   unsigned seed = 99;
   auto rnd = [&](unsigned n) { return (seed = seed * 1664525u + 1013904223u, (unsigned)((unsigned long long)(seed >> 8) * n >> 24)); };
   for (int i = 0; i < 30000; ++i) {
@@ -144,9 +145,11 @@ def test_slices_slots_and_the_kernels_of_the_batches(tmp_path):
     src, exe = tmp_path / "rule.cpp", tmp_path / "rule"
     src.write_text(RULE)
     subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-I", os.path.join(ROOT, "paper_2504_18154_amd", "csrc"), str(src), "-o", str(exe)], check=True)
-    calls = [(len(n), h[1], int(max(n))) for h, n in SLICED + PERSISTENT] + [(62, 8, 3000), (128, 8, 4096), (256, 8, 4096), (200, 8, 9000), (257, 8, 4096), (1024, 8, 1700)]
-    want = ["sliced"] * len(SLICED) + ["persistent"] * len(PERSISTENT) + ["sliced"] * 4 + ["persistent"] * 2
-    r = subprocess.run([str(exe)], input="".join(f"{b} {h} {n}\n" for b, h, n in calls), capture_output=True, text=True)
+    calls = [(len(n), h[1], int(max(n)), 0) for h, n in SLICED + PERSISTENT]
+    calls += [(62, 8, 3000, 0), (128, 8, 4096, 1), (256, 8, 4096, 0), (200, 8, 9000, 0), (160, 8, 4000, 1)]
+    calls += [(257, 8, 4096, 0), (1024, 8, 1700, 0), (256, 8, 4096, 1), (200, 8, 9000, 1), (160, 8, 4001, 1)]
+    want = ["sliced"] * len(SLICED) + ["persistent"] * len(PERSISTENT) + ["sliced"] * 5 + ["persistent"] * 5
+    r = subprocess.run([str(exe)], input="".join(f"{b} {h} {n} {a}\n" for b, h, n, a in calls), capture_output=True, text=True)
     got = r.stdout.split()
     assert got[len(want):] == ["ok"], r.stdout[-300:]
     assert got[:len(want)] == want, [(c, g, w) for c, g, w in zip(calls, got, want) if g != w]
