@@ -320,7 +320,7 @@ def run_30b(E: Env, args, res: dict):
             "frac_of_hbm_peak": res["value"] / acc.PEAK_HBM_GBPS,
             "append_us_per_layer": 1e3 * k_dapp_ms / k_dapp_n if k_dapp_n else None,
         }
-        roofs["decode"] = E.roofline("decode_mfma_kernel", "hbm", dec_bytes_layer, k_dec_ms, k_dec_n,
+        roofs["decode"] = E.roofline("decode_short_kernel", "hbm", dec_bytes_layer, k_dec_ms, k_dec_n,
                                      "30b_step" if layers == model.layers else None)
         roofs["decode"]["kernel_ms_per_step"] = k_dec_ms / max(k_dec_n, 1) * layers
     if do_pre:
@@ -473,7 +473,7 @@ def run_70b_decode(E: Env, args):
         "kv_cache_GB": need / 1e9, "decode_ctx_tokens": T0,
         "ms_per_step": phase_ms, "ms_per_layer": phase_ms / layers, "GBps": gbps, "frac_of_hbm_peak": gbps / acc.PEAK_HBM_GBPS,
         "passes_timed": passes,
-        "roofline": E.roofline("decode_mfma_kernel", "hbm", by, k_ms, k_n, "70b_decode" if layers == m.layers else None),
+        "roofline": E.roofline("decode_short_kernel" if args.equal_shares else "decode_mfma_kernel", "hbm", by, k_ms, k_n, "70b_decode" if layers == m.layers else None),
     }
     if not args.no_cpu_baseline:
         from oracle import oracle as orc
@@ -602,7 +602,7 @@ def run_70b_switch(E: Env, args):
                                   "frac_of_hbm_peak": dec_bytes_mean * layers * n_steps / (dec_ms * 1e-3) / 1e9 / acc.PEAK_HBM_GBPS},
         },
         "roofline": E.roofline("prefill_mfma_kernel", "mfma", flops, k_pre_ms, k_pre_n, "70b_switch" if layers == m.layers else None),
-        "roofline_decode": E.roofline("decode_mfma_kernel", "hbm", dec_bytes_mean, k_dec_ms, k_dec_n,
+        "roofline_decode": E.roofline("decode_short_kernel" if args.equal_shares else "decode_mfma_kernel", "hbm", dec_bytes_mean, k_dec_ms, k_dec_n,
                                       "70b_switch" if layers == m.layers else None),
         "roofline_append": E.roofline("kv_append_kernel", "hbm", app_bytes, k_app_ms, k_app_n,
                                       "70b_switch" if layers == m.layers else None),
