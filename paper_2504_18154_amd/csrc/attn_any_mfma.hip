@@ -1,6 +1,6 @@
 // Paged attention on gfx950 matrix cores for every layout except bf16 with head size 128: bf16 of any head size
 // that is a multiple of 8 and fp32 of any that is a multiple of 4, up to 256.  The decode kernel here also serves
-// small batches of that layout (small_decode), and decode_short_kernel those whose contexts it takes whole (decode_short).
+// small batches of that layout (small_decode), and decode_short_kernel those whose contexts it takes whole (decode_short) or cuts itself (decode_sliced).
 //
 // Eq. 2 of Section 2.1 over the paged cache, as the kernels for (bf16, 128) evaluate it, with the arithmetic of
 // the plain kernels: scores, weights and sums are fp32.
@@ -23,7 +23,7 @@
 // (sequence, K/V head) and slice of the context, slices as short as a merge allows, the step's append inside.
 // Measured beside the plain kernels (one wavefront per query row, a scalar product per lane): a prompt batch of 4 x
 // 50..600 tokens and 8 decode steps, bf16, head size 64, 32/8 heads: 398 -> 65 us (prefill kernel 243 -> 11 us, a
-// decode step's kernels 21.8 -> 6.1 us); 4 x 37..700 tokens in fp32, 4/2 heads: 195 -> 71 us (55 -> 8 us, 19.1 -> 7.3 us).
+// decode step's kernels 21.8 -> 5.6 us); 4 x 37..700 tokens in fp32, 4/2 heads: 195 -> 68 us (55 -> 8 us, 19.1 -> 7.1 us).
 // Not gained: a prompt of 8 tokens or fewer with nothing cached (a graph of such calls: 0.2 to 0.9 us more than the plain
 // kernel's 3 to 8); with 40 to 100 tokens cached, which the host cannot see, the plain kernel takes up to six times as long.
 #include <algorithm>
@@ -41,7 +41,7 @@ constexpr float kRaise = 8.f;        // the exponent offset is raised when a sco
 // Operands of one cache block for head sizes up to 32 KS, and the two products.  AUX: cache policy of the loads.  FULL:
 // weights have all bits of fp32; false is for (bf16, 128) alone, whose other kernels hold weights in 8 bits and flush those
 // below 2^-126: two parts (16 bits) and the bare exponent instruction there (one sequence of 777 tokens, 16 layers: 148 us,
-// with three parts and exp2f 157).
+// with three parts and exp2f 157, when the launch took 8 us).
 template <typename E, int KS, int AUX = 0, bool FULL = true>
 struct Block {
   static constexpr bool kF32 = std::is_same<E, float>::value;
@@ -453,7 +453,8 @@ __global__ __launch_bounds__(W * 64) void decode_any_kernel(
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int col = lane & 15, quad = lane >> 4;
   const int D = FULL ? head_size : 128;
-  // All arguments at once: fetched where they are wanted, they came in six round trips one behind the other.
+  // All arguments at once; fetched where they are wanted, they come in several round trips (us a call: 40 on 8, 1 x 2000 tokens 8.33 / 8.17, 52 on 52, 1 x 700
+  // 8.82 / 8.51, fp32, 128, 4 x 400 8.81 / 8.56, bf16, 64, 4 x 600 7.80 / 7.58; balanced 17.33 / 17.45).
   asm volatile("" ::"s"(q), "s"(q_row_stride), "s"(k_new), "s"(v_new), "s"(new_row_stride), "s"(k_cache), "s"(v_cache), "s"(block_table), "s"(bt_stride),
                "s"(ctx_len), "s"(split_tokens), "s"(Hkv), "s"(G), "s"(head_size));
   const SliceOf at = slice_of_workgroup<BALANCED>(ctx_len, B, Hkv, split_tokens, W);
@@ -684,11 +685,11 @@ __global__ __launch_bounds__(W * 64) void decode_any_kernel(
   }
 }
 
-// Decode of (bf16, 128), whole contexts (decode_short in decode_slices.h has the line, and the number of wavefronts): the W wavefronts of a
-// workgroup walk the blocks of one (sequence, K/V head) in turn; no numbering, no slices, nothing
-// shared between workgroups, whom the hardware hands out.  The wavefront that has the last block takes it last.  With k_new given it puts the
+// Decode of (bf16, 128), whole contexts (decode_short in decode_slices.h has the line, and the number of wavefronts) or, kSliced, the longer ones
+// cut (decode_sliced): the W wavefronts of a workgroup walk the blocks of one (sequence, K/V head) in turn; no numbering, and but for what is
+// cut nothing shared between workgroups, whom the hardware hands out.  The wavefront that has the last block takes it last.  With k_new given it puts the
 // newest token into the block's registers and writes the block's V whole, and of its K whole lines, back (see there).
-// Small batches are round trips; large ones are bound by memory and by what still runs when the rest is done.  Hence ORDERED, for batches of more
+// Small batches are round trips; large ones are bound by memory and by what still runs when the rest is done.  Hence kLongest, for batches of more
 // workgroups than run at once: grid (K/V heads, groups of up to 64 sequences, rank), and the workgroup takes the sequence of its rank in its group, by
 // length (in 16 classes of 2^shift tokens), longest first.  A wavefront finds it among its lanes' 64 lengths with four ballots (0.2 to 1 us
 // of a launch, which is why a batch that starts all at once, or has little to gain, does without: the grid is (K/V heads, B) then).
@@ -701,6 +702,13 @@ __global__ __launch_bounds__(W * 64) void decode_any_kernel(
 // the last block read with the non-temporal hint or without, all of the block's K written back (4% worse than 16 bytes a unit), eight and
 // sixteen wavefronts (one CU takes in 24 bytes a clock, however many ask: 1 x 777 tokens 10.2, 10.1, 10.9 with 4, 8, 16), fewer workgroups
 // on a CU at a time (1024 x ~103: 118 with six, 124 with four, 160 with two).
+// kSliced: bound by memory (reads at 6.0 to 6.4 TB/s, of the 7.0 that plain reads reach), and the order sees to it that the end is even whatever the
+// lengths, which the host does not know: grid (K/V heads, groups, rank).  Every wavefront reads all lengths (at most 256, four per lane), and their sum
+// gives the slice with which no more than `max_full` whole ones come of a K/V head.  Those are handed out first, then what is left of the contexts, longest first; a
+// workgroup without a rank ends.  Of a context that is cut, the workgroup that is done last adds the states up (merge_slices): one that waited for
+// the others while they walk slows them (long slices). `parts` has max_full slots of whole slices and as many of the rest per K/V head.  A slice below 24 blocks
+// costs more in states than it evens out.  us per layer, persistent kernel and its merge / here: 40 on 8, 128 x 512..4096 203 / 193, 52 on 52, 24 x 300..3000 (the append a
+// launch before it) 203 / 199, 64 on 8, 256 x 1024..4096 468 / 464; other batches at decode_sliced.
 enum class Order { kBatch, kLongest, kSliced };
 template <int W, Order ORDER>
 __global__ __launch_bounds__(W * 64, 3) void decode_short_kernel(

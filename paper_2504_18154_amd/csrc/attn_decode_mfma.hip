@@ -1,5 +1,8 @@
 // Split-context paged decode attention, bf16, head size 128, on gfx950 matrix cores.
 //
+// For the batches that the kernels of attn_any_mfma.hip leave: more than 256 sequences or eight (sequence, K/V head)s
+// per CU, unless their contexts are short; long launches with measured shares; forced splits.
+//
 // Eq. 2 of Section 2.1 for one new token per sequence against the whole cached context:
 // the memory-bound phase of Table 2 (every cached K and V byte is read once per step,
 // arithmetic intensity = the GQA group size).  The kernel is organised around the HBM
