@@ -205,8 +205,11 @@ ECO_SLICES_HD SlicedContexts sliced_contexts(int sum, int max_full, int W) {
 //   to 300 MB (persistent / here: 40 x 100..1000 27.2 / 24.6, 40 x 20..2000 25.1 / 21.2, 28 x 100..3000 37.5 /
 //   33.5, 24 x 100..3000 33.0 / 30.2, 16 query heads on 4, 64 x 100..2000 31.9 / 28.3; 36 x 1500 49.0 / 49.0, 40 x 2000 65.3 / 66.1, 24 x
 //   4000 74 / 80; with nothing to spare 64 x 20..2000 33.7 / 39.2; three workgroups and more per CU 40 x 100..1000 28.5).
-//   One context too long for the first of these rules comes here too (1 x 40000 52.3 / 43.5, 1 x 75000 75.1 / 64.4; 8 on 1, 1 x 300000 226 / 60,
-//   1 x 600000, cut into 171 slices, 252 / 86; 20 on 4, 1 x 150000 91 / 77).
+//   One context too long for the first of these rules comes here too, however long (1 x 40000 52.3 / 43.5, 1 x 75000 75.1 / 64.4; 8 on 1, 1 x 300000 226 / 60,
+//   1 x 600000, cut into 171 slices, 252 / 86; 20 on 4, 1 x 150000 91 / 77).  Beyond 600000 tokens of all K/V heads it was the persistent kernel's, then slices of whole blocks
+//   handed out by rank (decode_sliced); us persistent / by rank / here: 40 on 8, 1 x 80000 78.6 / 78.5 / 67.2, 1 x 400000 284 / 280 / 269; 64 on 8, 1 x 120000 113 / 104 / 92; 8 on 1, 1 x
+//   800000 267 / 219 / 101, 1 x 1500000 320 / 284 / 208; 32 on 32, 1 x 19000 60.0 / 57.1 / 53.4; 52 on 52, 1 x 60000 258 / 253 / 250.  (The non-temporal hint for
+//   contexts beyond the last-level cache changed nothing where the slices are uniform.)
 inline SmallDecode small_decode(int32_t B, int32_t Hkv, int32_t max_ctx_len, int32_t num_cu) {
   const int64_t pairs = (int64_t)B * Hkv;
   const int32_t nb = (max_ctx_len + 15) / 16, slots = num_cu / Hkv;
@@ -224,7 +227,7 @@ inline SmallDecode small_decode(int32_t B, int32_t Hkv, int32_t max_ctx_len, int
   const int32_t st = decode_any_split_tokens(B, Hkv, max_ctx_len, num_cu), n = (max_ctx_len + st - 1) / st;
   if (pairs * n <= num_cu) return {st, n};
   const int32_t slots2 = 2 * num_cu / Hkv;
-  if (B <= 64 && 8 * B <= 5 * slots2 && pairs * max_ctx_len <= 600000) return {0, slots2};
+  if (B <= 64 && 8 * B <= 5 * slots2 && (B == 1 || pairs * max_ctx_len <= 600000)) return {0, slots2};
   return {0, 0};
 }
 

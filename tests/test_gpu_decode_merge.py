@@ -15,7 +15,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 # (type, head size, heads, lengths, forced slices or 0): 2, 8, 9 and some 60 slices; heads whose rows a group of 16 lanes, of 32, or
 # two rounds of 32 hold, whole and ragged; slices of more than four rounds; more workgroups than run at once
-CASES = [("bf16", 128, (40, 8), [700, 1100, 40], 0), ("bf16", 128, (8, 1), [60000], 0), ("bf16", 128, (16, 1), [9000, 129, 3000], 0),
+CASES = [("bf16", 128, (40, 8), [700, 1100, 40], 0), ("bf16", 128, (8, 1), [60000], 0), ("bf16", 128, (16, 1), [9000, 129, 3000], 0), ("bf16", 128, (8, 2), [300100], 0),
          ("f32", 64, (4, 2), [513, 64, 577], 64), ("f32", 32, (4, 2), [1025, 130], 128), ("bf16", 24, (6, 3), [700, 65], 64), ("bf16", 80, (8, 8), [600, 64, 1], 64),
          ("f32", 100, (6, 3), [577, 512], 64), ("bf16", 200, (8, 2), [640, 70], 64), ("f32", 256, (4, 2), [577, 128], 64), ("bf16", 64, (32, 8), [1300] * 40, 64)]
 

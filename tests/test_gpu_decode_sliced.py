@@ -147,8 +147,8 @@ def test_slices_slots_and_the_kernels_of_the_batches(tmp_path):
     subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-I", os.path.join(ROOT, "paper_2504_18154_amd", "csrc"), str(src), "-o", str(exe)], check=True)
     calls = [(len(n), h[1], int(max(n)), 0) for h, n in SLICED + PERSISTENT]
     calls += [(62, 8, 3000, 0), (128, 8, 4096, 1), (256, 8, 4096, 0), (200, 8, 9000, 0), (160, 8, 4000, 1)]
-    calls += [(257, 8, 4096, 0), (1024, 8, 1700, 0), (256, 8, 4096, 1), (200, 8, 9000, 1), (160, 8, 4001, 1)]
-    want = ["sliced"] * len(SLICED) + ["persistent"] * len(PERSISTENT) + ["sliced"] * 5 + ["persistent"] * 5
+    calls += [(257, 8, 4096, 0), (1024, 8, 1700, 0), (256, 8, 4096, 1), (200, 8, 9000, 1), (160, 8, 4001, 1), (1, 8, 80000, 0), (1, 1, 4000000, 1)]
+    want = ["sliced"] * len(SLICED) + ["persistent"] * len(PERSISTENT) + ["sliced"] * 5 + ["persistent"] * 5 + ["small"] * 2
     r = subprocess.run([str(exe)], input="".join(f"{b} {h} {n} {a}\n" for b, h, n, a in calls), capture_output=True, text=True)
     got = r.stdout.split()
     assert got[len(want):] == ["ok"], r.stdout[-300:]
