@@ -239,9 +239,11 @@ __device__ __forceinline__ void attend_row(const E* __restrict__ qrow, const E* 
 
 // Partial states, from the workgroup of one slice to the one that merges them, within a launch and possibly between XCDs: past the
 // caches that XCDs do not share, and word by word.  A word holds the complement of the value's bits and is zero while it holds none, so a reader
-// sees by itself whether what it asked for has arrived, and nobody waits for a store to be acknowledged before it is announced.  (The one value
-// whose complement is zero, a NaN, is stored as its neighbour.)  Who reads a state clears it: the words are zero between launches.
-__device__ __forceinline__ uint32_t part_bits(float v) { return max(~__float_as_uint(v), 1u); }
+// sees by itself whether what it asked for has arrived, and nobody waits for a store to be acknowledged before it is announced.  Who reads a state clears it: the words
+// are zero between launches.  A slice that takes rows again (see attend_row) has been counted already: it says so in the rows' maximum and sum, and nobody gives up on it.
+// (The values whose complements are zero or kPartAgain, NaNs, are stored as their neighbour.)
+constexpr uint32_t kPartAgain = 1;
+__device__ __forceinline__ uint32_t part_bits(float v) { return max(~__float_as_uint(v), kPartAgain + 1); }
 __device__ __forceinline__ float part_value(uint32_t bits) { return __uint_as_float(~bits); }
 // (The instructions of relaxed atomics of agent scope, as buffer accesses: a scalar base and 32 bits of offset per lane, and nothing is read behind
 // the range.)
@@ -250,10 +252,6 @@ __device__ __forceinline__ u32x4 part_bits(const f32x4& v) { return u32x4{part_b
 __device__ __forceinline__ void store_part(__amdgpu_buffer_rsrc_t r, int byte, const u32x2& w) { __builtin_amdgcn_raw_buffer_store_b64(w, r, byte, 0, kAuxAgent); }
 __device__ __forceinline__ void store_part(__amdgpu_buffer_rsrc_t r, int byte, const u32x4& w) { __builtin_amdgcn_raw_buffer_store_b128(w, r, byte, 0, kAuxAgent); }
 constexpr int part_words(int D) { return D + 4; }  // of a state: the unnormalised head vector, its maximum, its sum, and two that keep 16 bytes aligned
-// A merging wavefront asks again at most so often (half a second).  The slices it waits for run already and wait for nothing themselves, microseconds from their end,
-// so it never does, but for calls that overlap on one workspace, which they may not: they end with NaN then.
-constexpr int kMostPolls = 1 << 19;
-
 // Over the two halves, or (N 4) the four 16-lane groups, of a wavefront, lane by lane.
 template <int N, typename F>
 __device__ __forceinline__ float of_groups(float v, F f) {
@@ -351,7 +349,7 @@ __device__ __forceinline__ void merge_slices(uint32_t* first, int slice_bytes, i
     }
   };
   Group now, then;
-  int polls = 0;
+  MergeLooks looks;
   __amdgpu_buffer_rsrc_t from = range(0);
   ask(from, now);
   for (int base = 0; base < n_split; base += NG * kAtOnce) {
@@ -367,7 +365,7 @@ __device__ __forceinline__ void merge_slices(uint32_t* first, int slice_bytes, i
         for (int c = 0; c < NC; ++c)
 #pragma unroll
           for (int e = 0; e < 4; ++e) least = min(least, now.o[j][c][e]);
-        any |= (least == 0) & (NG * j < more) & (NG * j != own);
+        any |= (least <= kPartAgain) & (NG * j < more) & (NG * j != own);
       }
       return __any(any);
     };
@@ -375,17 +373,20 @@ __device__ __forceinline__ void merge_slices(uint32_t* first, int slice_bytes, i
       asm volatile("" ::: "memory");
       do {
         // who waits for long keeps out of the others' way: 0.4 us between looks, at the sums alone
-        for (bool wait = polls > 1; wait && polls < kMostPolls; ++polls) {
+        for (bool look = looks.many(); look;) {
           __builtin_amdgcn_s_sleep(16);
           asm volatile("" ::: "memory");
-          bool any = false;
+          bool any = false, again = false;
 #pragma unroll
-          for (int j = 0; j < kAtOnce; ++j)
-            any |= (__builtin_amdgcn_raw_buffer_load_b32(from, at_ml + 4 + NG * j * slice_bytes, 0, kAuxAgent) == 0) & (NG * j < more) & (NG * j != own);
-          wait = __any(any);
+          for (int j = 0; j < kAtOnce; ++j) {
+            const uint32_t sum = __builtin_amdgcn_raw_buffer_load_b32(from, at_ml + 4 + NG * j * slice_bytes, 0, kAuxAgent);
+            any |= (sum <= kPartAgain) & (NG * j < more) & (NG * j != own);
+            again |= (sum == kPartAgain) & (NG * j < more) & (NG * j != own);
+          }
+          look = looks.once_more(__any(again)) && __any(any);
         }
         ask(from, now);
-      } while (missing() && ++polls < kMostPolls);
+      } while (missing() && looks.once_more(false));
     }
     float m_new = m2, x[kAtOnce];
 #pragma unroll
@@ -646,6 +647,9 @@ __global__ __launch_bounds__(W * 64) void decode_any_kernel(
         zero = __builtin_fmaf(o[c][e], 0.f, zero);
       }
     if (__any(zero != zero && total == total)) {  // (see attend_row)
+      if (!merges && h + W * lane < G)  // (counted already: whoever merges this row, or the wavefront's next ones, is to wait)
+        __hip_atomic_store(reinterpret_cast<uint64_t*>(parts + (slot0 + (h + W * lane) * slot_step) * row_words + D), (uint64_t)kPartAgain << 32 | kPartAgain, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
       float r[4];
       attend_row<E>(scalar_here(q + (size_t)b * q_row_stride) + (size_t)(scalar_here(g) * G + h) * D, scalar_here(k_cache), scalar_here(v_cache), scalar_here(bt_row),
                     scalar_here(g), scalar_here(Hkv), scalar_here(D), scalar_here(t0), scalar_here(t1), scale_log2e, M, total, r);
@@ -918,11 +922,7 @@ __global__ __launch_bounds__(W * 64, 3) void decode_short_kernel(
     }
 #pragma unroll
     for (int dt = 0; dt < 8; ++dt) s_acc[wave][dt][lane] = acc[dt];
-    if (tid == 0) {
-      s_bad = 0;
-      if (ORDER == Order::kSliced && n_split > 1)  // (the slice that is done last merges them all, as in decode_any_kernel; the last one wraps the count to zero)
-        s_order = (int)atomicInc(counters + (size_t)(slot - slice_no) * Hkv + g, (unsigned)n_split - 1);
-    }
+    if (tid == 0) s_bad = 0;
     __syncthreads();
     float M = s_m[0][col];
 #pragma unroll
@@ -966,7 +966,11 @@ __global__ __launch_bounds__(W * 64, 3) void decode_short_kernel(
           for (int r = 0; r < 2; ++r) __builtin_amdgcn_raw_buffer_store_b32(part_bits(o[r]), to, (h * row_words + lane + 64 * r) * 4, 0, kAuxAgent);
           if (lane == 0) store_part(to, (h * row_words + D) * 4, u32x2{part_bits(rm), part_bits(rl)});
         }
+        __syncthreads();
       }
+      // The slice that is done last merges them all (the last one wraps the count to zero).  Counted here, its states are on their way, rows taken again and all.
+      if (tid == 0) s_order = (int)atomicInc(counters + (size_t)(slot - slice_no) * Hkv + g, (unsigned)n_split - 1);
+      __syncthreads();
       if (s_order != n_split - 1) return;
       for (int h = wave; h < G; h += W) {
         float rm = 0.f, rl = 0.f;

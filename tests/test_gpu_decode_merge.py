@@ -9,7 +9,7 @@ import torch
 
 from paper_2504_18154_amd import binding
 from paper_2504_18154_amd import workloads as wl
-from tests.parity_util import Layer, compare, compare_lse, say
+from tests.parity_util import Layer, compare, compare_lse, dev_i32, say
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -44,6 +44,75 @@ def test_merged_slices_call_after_call(dtype, D, heads, lens, split):
         again, lse2 = layer.decode_gpu(q, pb.block_table, lens)
         assert torch.equal(again, out) and torch.equal(lse2, lse), f"call {call} differs"
     layer.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("heads,n", [((16, 1), 60000), ((16, 1), 270000)], ids=["eight-wavefronts", "four-wavefronts"])
+def test_rows_of_long_slices_that_are_taken_again(heads, n):
+    """Long slices, two and four rows to a wavefront, and infinite V elements in two of them, one of them the newest token's: their rows are taken again key by key
+    while another slice, long done, waits to merge them."""
+    model = wl.ModelShape("merge", heads[0], heads[1], 128, 1, "bf16")
+    lens = np.array([n], dtype=np.int32)
+    say(f"decode in slices, heads {heads}, {n} tokens, infinite values")
+    pb = wl.prefill_batch(model, lens, 72)
+    layer = Layer(model, pb.num_blocks, 1, pb.block_table.shape[1])
+    k, v = (wl.randn((n, heads[1], 128), "bf16", s) for s in (1, 2))
+    for t, d in ((n // 2, 6), (n - 1, 7)):
+        v[t, 0, d] = float("inf")
+    layer.append(k, v, pb.cu_q, pb.ctx_before, pb.block_table)
+    q, bt, tot = wl.randn((1, heads[0], 128), "bf16", 3).cuda(), dev_i32(pb.block_table), dev_i32(lens)
+    want = torch.full_like(q, float("nan"))
+    layer.ctx.set_option(binding.OPT_FORCE_PLAIN, 1)
+    layer.ctx.attn_decode(q, layer.kc, layer.vc, bt, tot, want, n)
+    layer.ctx.set_option(binding.OPT_FORCE_PLAIN, 0)
+    layer.wipe_newest(pb.block_table, lens)
+    want = want.float()
+    fin = torch.isfinite(want)
+    assert torch.isinf(want[0, :, 6:8]).all() and int((~fin).sum()) == 2 * heads[0]
+    for call in range(2):   # (the second one finds the words and counts as the first one left them)
+        got = torch.full_like(q, float("nan"))
+        layer.ctx.attn_decode_append(q, k[-1:].cuda(), v[-1:].cuda(), layer.kc, layer.vc, bt, tot, got, n)
+        got = got.float()
+        assert torch.equal(torch.isfinite(got), fin) and torch.equal(torch.isinf(got), torch.isinf(want)), f"call {call}"
+        assert (got[fin] - want[fin]).abs().max() <= 2.0 ** -6   # (half a spacing of bf16, 2^-7 of |o| < 4, each, and the weights' 2^-17)
+    layer.assert_cache_bit_exact()
+    layer.close()
+
+
+LOOKS = r"""
+#include <cstdio>
+#include "decode_slices.h"
+using namespace eco;
+// a merging wavefront and the slice it waits for, look by look: nothing, `from` looks later word that rows are taken again, `there` looks later the state
+int main() {
+  auto waits = [](long long from, long long there) {  // the looks until it goes on, or gives up
+    MergeLooks w;
+    long long i = 0;
+    while (i < there && w.once_more(i >= from)) ++i;
+    return i;
+  };
+  const long long most = MergeLooks::kMost, never = 1LL << 40;
+  if (waits(never, never) >= most) return std::printf("no end\n"), 1;
+  if (waits(never, most / 2) != most / 2) return std::printf("gives up on a state\n"), 1;
+  for (long long from : {0LL, 1LL, 50LL, most / 2})
+    for (long long there : {from + 1, from + most, from + 20 * most})
+      if (waits(from, there) != there) return std::printf("gives up on rows that are taken again: %lld, %lld\n", from, there), 1;
+  MergeLooks w;
+  for (long long i = 0; i < 3 * most; ++i) w.once_more(true);
+  long long i = 0;
+  while (w.once_more(false)) ++i;
+  if (i >= most || !w.many()) return std::printf("no end behind it\n"), 1;
+  std::printf("ok\n");
+}
+"""
+
+
+def test_nobody_gives_up_on_rows_that_are_taken_again(tmp_path):
+    src, exe = tmp_path / "looks.cpp", tmp_path / "looks"
+    src.write_text(LOOKS)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-I", os.path.join(ROOT, "paper_2504_18154_amd", "csrc"), str(src), "-o", str(exe)], check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0 and r.stdout == "ok\n", r.stdout
 
 
 BOUND = r"""
