@@ -79,6 +79,36 @@ def test_rows_of_long_slices_that_are_taken_again(heads, n):
     layer.close()
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("heads,lens", [((40, 8), [2000]), ((40, 8), [700, 1100, 40]), ((8, 1), [60000]), ((40, 8), [4000] + [20] * 63)],
+                         ids=["uniform", "balanced", "four-wavefronts", "cut-on-the-device"])
+def test_states_that_weigh_less_than_the_smallest_normal_number(heads, lens):
+    """One key of a context has all the weight, and values elsewhere, in other wavefronts' blocks (the second block) and in other slices (the last 200 tokens), are so
+    large that their weight of 2^-128 counts."""
+    model = wl.ModelShape("merge", heads[0], heads[1], 128, 1, "bf16")
+    lens = np.asarray(lens, dtype=np.int32)
+    say(f"decode in slices, heads {heads}, {len(lens)} sequences up to {lens.max()} tokens, states of weight 2^-128")
+    pb = wl.prefill_batch(model, lens, 73)
+    layer = Layer(model, pb.num_blocks, pb.B, pb.block_table.shape[1])
+    k, v = (torch.zeros((pb.T, heads[1], 128), dtype=torch.bfloat16) for _ in range(2))
+    q = torch.zeros((pb.B, heads[0], 128), dtype=torch.bfloat16)
+    q[:, :, 0] = 32.0
+    for first, n in zip(pb.cu_q, lens):
+        if n >= 700:
+            k[first, :, 0] = 31.375   # 32 x 31.375 / sqrt(128) = 88.74 = 128.03 ln 2 above the others
+            v[first + 16:first + 32] = 2.0 ** 122
+            v[first + n - 200:first + n] = 2.0 ** 118
+    layer.append(k, v, pb.cu_q, pb.ctx_before, pb.block_table)
+    ref, ref_lse = layer.decode_oracle(q, pb.block_table, lens)
+    assert (ref[lens >= 700] > 0.4).all()
+    out, lse = layer.decode_gpu(q, pb.block_table, lens)
+    # half a spacing of bf16, and the weights' error: scores of 128 to 2^-17, times ln 2, and 22 bits of a number of 2^-128
+    err, bound = float(np.abs(out.double().cpu().numpy() - ref).max()), float((2.0 ** -8 + 2.0 ** -16) * ref.max())
+    assert err <= bound
+    compare_lse("decode", lse, ref_lse, "bf16")
+    layer.close()
+
+
 LOOKS = r"""
 #include <cstdio>
 #include "decode_slices.h"
