@@ -713,9 +713,9 @@ __global__ __launch_bounds__(W * 64) void decode_any_kernel(
 // sixteen wavefronts (one CU takes in 24 bytes a clock, however many ask: 1 x 777 tokens 10.2, 10.1, 10.9 with 4, 8, 16), fewer workgroups
 // on a CU at a time (1024 x ~103: 118 with six, 124 with four, 160 with two).
 // kSliced: bound by memory (reads at 6.0 to 6.4 TB/s, of the 7.0 that plain reads reach), and the order sees to it that the end is even whatever the
-// lengths, which the host does not know: grid (K/V heads, groups, rank).  Every wavefront reads all lengths (at most 256, four per lane), and their sum
+// lengths, which the host does not know: grid (K/V heads, rank).  Every wavefront reads all lengths (at most 256, four per lane), and their sum
 // gives the slice with which no more than `max_full` whole ones come of a K/V head.  Those are handed out first, then what is left of the contexts, longest first; a
-// workgroup without a rank ends.  Of a context that is cut, the workgroup that is done last adds the states up (merge_slices): one that waited for
+// workgroup without a rank ends (ranked in each group of 64 sequences, up to 3000 of them stood at the end of a launch: 16 on 1, 238 x 1140..11406 tokens 63.8 us, 56.3 so).  Of a context that is cut, the workgroup that is done last adds the states up (merge_slices): one that waited for
 // the others while they walk slows them (long slices). `parts` has max_full slots of whole slices and as many of the rest per K/V head.  A slice below 24 blocks
 // costs more in states than it evens out.  us per layer, persistent kernel and its merge / here: 40 on 8, 128 x 512..4096 203 / 193, 52 on 52, 24 x 300..3000 (the append a
 // launch before it) 203 / 199, 64 on 8, 256 x 1024..4096 468 / 464; other batches at decode_sliced.
@@ -759,48 +759,62 @@ __global__ __launch_bounds__(W * 64, 3) void decode_short_kernel(
     b = first + at;
     L = __builtin_amdgcn_readlane(len, at);
   } else if constexpr (ORDER == Order::kSliced) {
-    // Group j has the sequences j, j + groups, ..: much the same lengths where a batch is sorted.  The groups take turns with the XCDs.
-    const int groups = gridDim.y, group = (int)(b + (blockIdx.z >> 1) + (blockIdx.z >> 3)) % groups, have = (B - group + groups - 1) / groups;
-    int len[4];
+    // Lane l has the sequences l groups + j, j < groups; group j, whose rests are ranked among themselves, the j-th of all lanes: much the same lengths where a
+    // batch is sorted.
+    const int groups = (B + 63) >> 6;
+    int len[4], sum = 0;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const int s = lane * groups + j;
       len[j] = j < groups && s < B ? ctx_len[s] : 0;
     }
-    int sum = 0, mine = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) sum += (len[j] + 15) >> 4;
+    const SlicedContexts cut = sliced_contexts(__builtin_amdgcn_readlane(lanes_prefix_sum(sum), 63), max_full, W);
+    // whole slices, and (from bit 16 on) the contexts that are cut, of this lane's sequences and of those before them
+    int full[4], own = 0;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      sum += (len[j] + 15) >> 4;
-      mine = j == group ? len[j] : mine;
+      full[j] = cut.full((len[j] + 15) >> 4);
+      own += full[j] + (full[j] > 0 ? 1 << 16 : 0);
     }
-    const SlicedContexts cut = sliced_contexts(__builtin_amdgcn_readlane(lanes_prefix_sum(sum), 63), max_full, W);
-    const int nb = (mine + 15) >> 4, full = cut.full(nb);
-    const int upto = lanes_prefix_sum(full), n_full = __builtin_amdgcn_readlane(upto, 63);
-    // slots of the groups before this one: their whole slices, and one more for each context that is cut
-    int earlier = 0;
+    const int upto = lanes_prefix_sum(own), n_full = __builtin_amdgcn_readlane(upto, 63) & 0xffff;
+    int r = blockIdx.y, at, group = 0;
+    const bool whole = r < n_full;
+    if (whole) {
+      at = __builtin_ctzll(__ballot((upto & 0xffff) > r));
+      slice_no = r - (__builtin_amdgcn_readlane(upto - own, at) & 0xffff);
 #pragma unroll
-    for (int j = 0; j < 3; ++j) {
-      const int f = j < group ? cut.full((len[j] + 15) >> 4) : 0;
-      earlier += f + (f > 0 ? 1 : 0);
-    }
-    earlier = __builtin_amdgcn_readlane(lanes_prefix_sum(earlier), 63);
-    int r = blockIdx.z, at, k;
-    if (r < n_full) {
-      at = __builtin_ctzll(__ballot(upto > r));
-      k = r - __builtin_amdgcn_readlane(upto - full, at);
+      for (int j = 0; j < 3; ++j) {
+        const int f = __builtin_amdgcn_readlane(full[j], at);
+        if (group == j && slice_no >= f) {
+          slice_no -= f;
+          group = j + 1;
+        }
+      }
     } else {
       r -= n_full;
-      if (r >= have) return;
-      at = select(cut.size_class(nb - full * cut.blocks), have, r);
-      k = __builtin_amdgcn_readlane(full, at);
+      if (r >= B) return;
+      group = r % groups;
+    }
+    int mine = len[0], mine_full = full[0], before = 0;  // (of this group's sequence; whole slices and cuts in the lane's earlier groups)
+#pragma unroll
+    for (int j = 1; j < 4; ++j) {
+      before += j <= group ? full[j - 1] + (full[j - 1] > 0 ? 1 << 16 : 0) : 0;
+      mine = j == group ? len[j] : mine;
+      mine_full = j == group ? full[j] : mine_full;
+    }
+    if (!whole) {
+      at = select(cut.size_class(((mine + 15) >> 4) - mine_full * cut.blocks), (B - group + groups - 1) / groups, r / groups);
+      slice_no = __builtin_amdgcn_readlane(mine_full, at);
     }
     b = at * groups + group;
     L = __builtin_amdgcn_readlane(mine, at);
-    n_split = __builtin_amdgcn_readlane(full, at) + 1;
-    slice_no = k;
-    blk0 = k * cut.blocks;
-    blk1 = k < n_split - 1 ? blk0 + cut.blocks : (L + 15) >> 4;
-    slot = earlier + __builtin_amdgcn_readlane(upto - full, at) + (int)__popcll(__ballot(full > 0) & ((1ull << at) - 1)) + k;
+    n_split = __builtin_amdgcn_readlane(mine_full, at) + 1;
+    blk0 = slice_no * cut.blocks;
+    blk1 = slice_no < n_split - 1 ? blk0 + cut.blocks : (L + 15) >> 4;
+    const int first = __builtin_amdgcn_readlane(upto - own + before, at);  // (a slot for each whole slice, and one for the rest of each context that is cut)
+    slot = (first & 0xffff) + (first >> 16) + slice_no;
   } else {
     L = __builtin_amdgcn_readfirstlane(ctx_len[b]);
   }
@@ -1298,7 +1312,7 @@ hipError_t launch_whole(const AttnArgs& a, const int32_t* ctx_len, int32_t max_c
   const int groups = (a.B + 63) / 64, per_group = (a.B + groups - 1) / groups;
   int shift = 4;
   while (max_ctx_len >> shift > 15) ++shift;
-  const dim3 grid = ORDER == Order::kBatch ? dim3((unsigned)a.Hkv, (unsigned)a.B) : dim3((unsigned)a.Hkv, (unsigned)groups, (unsigned)(per_group + max_full));
+  const dim3 grid = ORDER == Order::kLongest ? dim3((unsigned)a.Hkv, (unsigned)groups, (unsigned)per_group) : dim3((unsigned)a.Hkv, (unsigned)(a.B + max_full));
   hipLaunchKernelGGL((decode_short_kernel<W, ORDER>), grid, dim3(W * 64), 0, s, (const uint16_t*)a.q, a.q_row_stride, (const uint16_t*)a.k_new, (const uint16_t*)a.v_new,
                      a.new_row_stride, (uint16_t*)const_cast<void*>(a.k_cache), (uint16_t*)const_cast<void*>(a.v_cache), a.block_table, a.bt_stride, ctx_len,
                      (uint16_t*)a.out, a.lse, a.Hq, a.Hkv, a.Hq / a.Hkv, a.scale_log2e, a.B, per_group, shift, stream ? 1 : 0, parts, counters, max_full);

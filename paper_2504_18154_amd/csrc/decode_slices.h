@@ -179,7 +179,8 @@ constexpr bool decode_short_stream(int64_t pairs, int32_t max_ctx_len) { return 
 // Whole contexts, longest first, the longer ones cut (decode_short_kernel, kSliced): slices of `blocks` blocks, whole ones first, then what is left of each context.  No
 // more than `max_full` whole slices per K/V head come of it, whatever the lengths, and twice as many slots for partial states.
 constexpr int32_t kSlicedMostSequences = 256;  // four lengths per lane
-inline int32_t sliced_most_full(int32_t B, int32_t Hkv, int32_t num_cu) { return ((int64_t)B * Hkv * 4 <= 7 * (int64_t)num_cu ? 4 : 2) * num_cu / Hkv; }
+// (three per CU: as many workgroups as run there at a time, and the rests follow them)
+inline int32_t sliced_most_full(int32_t, int32_t Hkv, int32_t num_cu) { return 3 * num_cu / Hkv; }
 struct SlicedContexts {
   int blocks;
   float per_block;
@@ -250,8 +251,10 @@ inline SmallDecode small_decode(int32_t B, int32_t Hkv, int32_t max_ctx_len, int
 // 127 x 20 and one of 4000 24.0 / 16.2; 64 on 8, 256 x 1024..4096 459.5 / 451.3, 128 x 8192 671 / 672, 8 x 60000 323 / 313; 52 on 52, 24 x 300..3000 185 / 177; 32 on 8, 64 x 4096 183 / 170,
 // 84 x 300 and six of 6000 57.9 / 49.7; 8 on 1, 256 x 100..6000 78.7 / 78.0; 5 on 1, 150 x 300..16000 110 / 117.  Of 43 random batches of eight head shapes (lengths equal, from 1/2, 1/8, 1/64
 // of the longest, lognormal, one in 16 ten times the others) 0.93 of the time on average, the worst 1.03.
-//   Four whole slices per CU at most for up to 1.75 (sequence, head)s per CU, where one workgroup more or less on a CU shows, two above (two / four: 52 on 52, 5 x 200..6000
-// 76.0 / 71.5, 8 on 1, 200 x 8000 149.9 / 139.3, 32 on 8, 31 x 1000..9000 113 / 110, 64 x 4096 170 / 178, 40 on 8, 16 x 16000 169 / 173).
+//   Whole slices per CU, at most: three, as many workgroups as run there at a time.  Of 60 random batches that come here, of the persistent kernel's time, (two, three, four): up to 1.75
+// (sequence, head)s per CU 0.936, 0.934, 0.943 on average, the worst 1.14, 1.05, 1.07; above 0.932, 0.929, 0.936.  (52 on 52, 5 x 5594 143, 131, 130 us, 8 on 1, 256 x 100..6000
+// 80.6, 78.0, 80.4, 5 on 1, 150 x 300..16000 118, 115, 116.)  What stays slower than the persistent kernel, by up to 5%, are few long contexts of much the same length, whose rests run at a
+// third of the CUs' workgroups; where one in 16 is long, as the host cannot see, these batches take 10 to 35% less than there.
 inline bool decode_sliced(int32_t B, int32_t Hkv, int32_t num_cu) { return B <= kSlicedMostSequences && (int64_t)B * Hkv <= (int64_t)8 * num_cu; }
 // A context that asks for shares by each XCD's measured speed keeps the persistent kernel for its longest launches: the shares take 1 to 3% off a stream, which is more
 // than the launch of the merge and the uneven end cost once the stream is long.  Us per call with such shares, the persistent kernel / here: 64 on 8, 256 x 1024..4096
