@@ -328,7 +328,7 @@ int ecoserve_attn_decode_append(ecoserve_ctx* ctx, const void* q, int64_t q_row_
  * hipMalloc.  No context: the layout is passed directly, and the scratch
  * memory of the launches (partial softmax states of the split contexts, the
  * launch's numbering, the list of cut sequences, merge counters) is a fixed array of
- * 32.8 MiB inside the library's device code, one copy per GPU, held until the
+ * 20.4 MiB inside the library's device code, one copy per GPU, held until the
  * process ends.  The call allocates nothing (no hipMalloc / hipFree, no
  * events), does not synchronise, and launches the same kernels as
  * ecoserve_attn_decode with its default options (no measured

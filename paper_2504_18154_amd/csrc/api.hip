@@ -72,38 +72,37 @@ int64_t slots_needed(const ecoserve_ctx* c, int32_t* plain_splits) {
   return (int64_t)c->max_batch * c->lay.num_q_heads * *plain_splits;
 }
 
-// States that the slices of the kernels of attn_any_mfma.hip leave, as the rules in decode_slices.h cut: at most eight per CU, or slices
-// of 1024 tokens, or as long as the option says.
-int64_t part_slots_needed(const ecoserve_ctx* c) {
-  const int64_t G = c->lay.num_q_heads / c->lay.num_kv_heads, few = 8 * (int64_t)c->num_cu * G;
-  if (c->opt_force_plain || use_mfma(c)) return few;
-  const int32_t st = c->opt_split_tokens > 0 ? c->opt_split_tokens : 1024;
-  return std::max(few, (int64_t)c->max_batch * c->lay.num_q_heads * ceil_div(c->max_blocks_per_seq * kBlockSize, st));
+// Partial states of the slices of the kernels of attn_any_mfma.hip, as the rules in decode_slices.h cut.  Zeroed ones, of short slices: at most two per CU.  The others: six
+// per CU for (bf16, 128), where the persistent kernel's lie (eight per CU and group head, of 130 words), else one per CU or slices of 1024 tokens.
+int64_t group_of(const ecoserve_ctx* c) { return c->lay.num_q_heads / c->lay.num_kv_heads; }
+bool has_mfma(const ecoserve_ctx* c) { return c->lay.dtype == ECOSERVE_BF16 && c->lay.head_dim == 128; }
+size_t state_bytes(const ecoserve_ctx* c) { return (size_t)(c->lay.head_dim + 4) * sizeof(uint32_t); }
+int64_t slices_at_most(const ecoserve_ctx* c, int32_t tokens) {
+  return (int64_t)c->max_batch * c->lay.num_q_heads * ceil_div(c->max_blocks_per_seq * kBlockSize, tokens);
+}
+SliceStates slice_states(const ecoserve_ctx* c) {
+  if (!has_mfma(c)) return c->opt_split_tokens > 0 ? c->forced : c->parts;
+  return {c->parts.parts, reinterpret_cast<uint32_t*>(c->ws_acc), c->parts.part_slots, 6 * c->num_cu * group_of(c)};
 }
 
-// More of the slices' states than the context was made with (see ensure_partial_states), zeroed.
-int ensure_parts(ecoserve_ctx* c) {
-  const int64_t need = part_slots_needed(c);
-  if (need <= c->part_slots) return ECOSERVE_OK;
-  const size_t slot = (size_t)(c->lay.head_dim + 4) * sizeof(uint32_t);
-  uint32_t* parts = nullptr;
-  if (hipMalloc(&parts, (size_t)need * slot) != hipSuccess) {
+// For layouts other than (bf16, 128), once an option forces a length of slices: states for any length of them.
+int ensure_forced_states(ecoserve_ctx* c) {
+  if (has_mfma(c) || c->opt_split_tokens <= 0 || c->forced.parts) return ECOSERVE_OK;
+  SliceStates f;
+  f.part_slots = f.state_slots = slices_at_most(c, kMinSplitTokens);
+  const size_t zeroed = (size_t)f.part_slots * state_bytes(c), bytes = zeroed + (size_t)f.state_slots * state_bytes(c);
+  if (hipMalloc(&f.parts, bytes) != hipSuccess) {
     (void)hipGetLastError();
     return ECOSERVE_ENOMEM;
   }
-  // (launches in flight may still use those it had)
-  if (hipMemset(parts, 0, (size_t)need * slot) != hipSuccess || hipDeviceSynchronize() != hipSuccess) {
+  if (hipMemset(f.parts, 0, zeroed) != hipSuccess || hipDeviceSynchronize() != hipSuccess) {
     (void)hipGetLastError();
-    (void)hipFree(parts);
+    (void)hipFree(f.parts);
     return ECOSERVE_EHIP;
   }
-  if (c->ws_more_parts) {
-    (void)hipFree(c->ws_more_parts);
-    c->ws_bytes -= (size_t)c->part_slots * slot;
-  }
-  c->ws_parts = c->ws_more_parts = parts;
-  c->part_slots = need;
-  c->ws_bytes += (size_t)need * slot;
+  f.states = f.parts + zeroed / sizeof(uint32_t);
+  c->forced = f;
+  c->ws_bytes += bytes;
   return ECOSERVE_OK;
 }
 
@@ -113,8 +112,7 @@ int ensure_partial_states(ecoserve_ctx* c) {
   int32_t plain_splits;
   const int64_t need = slots_needed(c, &plain_splits);
   if (plain_splits) c->ws_splits = plain_splits;
-  if (c->ws_share)  // (not while the context is made)
-    if (const int st = ensure_parts(c); st != ECOSERVE_OK) return st;
+  if (const int st = ensure_forced_states(c); st != ECOSERVE_OK) return st;
   if (need <= c->ws_slots) return ECOSERVE_OK;
   if (c->ws_acc) {
     if (hipDeviceSynchronize() != hipSuccess) return ECOSERVE_EHIP;  // launches in flight may still use them
@@ -124,16 +122,15 @@ int ensure_partial_states(ecoserve_ctx* c) {
   c->ws_acc = nullptr;
   c->ws_ml = nullptr;
   c->ws_slots = 0;
-  const size_t acc_bytes = (size_t)need * c->lay.head_dim * sizeof(float);
-  const size_t ml_bytes = (size_t)need * 2 * sizeof(float);
-  if (hipMalloc(&c->ws_acc, acc_bytes + ml_bytes) != hipSuccess) {  // (one allocation: each is tens of microseconds of creating a context)
+  const size_t bytes = (size_t)need * (c->lay.head_dim + 2) * sizeof(float);
+  if (hipMalloc(&c->ws_acc, bytes) != hipSuccess) {  // (one allocation: each is tens of microseconds of creating a context)
     (void)hipGetLastError();
     c->ws_acc = nullptr;
     return ECOSERVE_ENOMEM;
   }
   c->ws_ml = c->ws_acc + (size_t)need * c->lay.head_dim;
   c->ws_slots = need;
-  c->ws_bytes += acc_bytes + ml_bytes;
+  c->ws_bytes += bytes;
   return ECOSERVE_OK;
 }
 
@@ -274,9 +271,6 @@ int ecoserve_create(ecoserve_ctx** out, int device, const ecoserve_layout* layou
   c->ws_plan = nullptr;
   c->ws_pieces = nullptr;
   c->ws_count = nullptr;
-  c->ws_parts = nullptr;
-  c->ws_more_parts = nullptr;
-  c->part_slots = 0;
   c->plan_tiles = 0;
   c->ws_splits = 0;
   c->ws_slots = 0;
@@ -288,21 +282,23 @@ int ecoserve_create(ecoserve_ctx** out, int device, const ecoserve_layout* layou
   if (st != ECOSERVE_OK) { (void)ecoserve_destroy(c); return st; }
   {
     // per-XCD shares start equal; samples of 4 wavefronts per CU follow, then each chunk's report to the merge, then
-    // the small-batch kernel's counters and, on a boundary of 256 bytes, its slices' states (one allocation: creating a context is a few of them and their clearing)
+    // the small-batch kernel's counters and, on a boundary of 256 bytes, its slices' states, the zeroed ones first (one allocation: creating a context is a few of them and their clearing)
     const size_t share_words = 24 + 6 * (size_t)c->num_cu * kDecodeWgsPerCu * 4;
-    const size_t counts = std::max((size_t)c->max_batch * c->lay.num_kv_heads, (size_t)8 * c->num_cu), parts_at = (share_words + counts + 63) / 64 * 64;
-    const int64_t part_slots = part_slots_needed(c);
-    const size_t share_bytes = (parts_at + (size_t)part_slots * (c->lay.head_dim + 4)) * sizeof(int32_t);
+    const size_t counts = std::max((size_t)c->max_batch * c->lay.num_kv_heads, (size_t)6 * c->num_cu), parts_at = (share_words + counts + 63) / 64 * 64;
+    SliceStates& p = c->parts;
+    p.part_slots = 2 * (int64_t)c->num_cu * group_of(c);
+    p.state_slots = has_mfma(c) ? 0 : std::max(c->num_cu * group_of(c), slices_at_most(c, 1024));
+    const size_t zeroed = parts_at * sizeof(int32_t) + (size_t)p.part_slots * state_bytes(c), share_bytes = zeroed + (size_t)p.state_slots * state_bytes(c);
     const float ones[16] = {1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f};
-    if (hipMalloc(&c->ws_share, share_bytes) != hipSuccess || hipMemset(c->ws_share, 0, share_bytes) != hipSuccess ||
+    if (hipMalloc(&c->ws_share, share_bytes) != hipSuccess || hipMemset(c->ws_share, 0, zeroed) != hipSuccess ||
         hipMemcpy(c->ws_share, ones, sizeof(ones), hipMemcpyHostToDevice) != hipSuccess) {
       (void)hipGetLastError();
       (void)ecoserve_destroy(c);
       return ECOSERVE_ENOMEM;
     }
     c->ws_count = reinterpret_cast<uint32_t*>(c->ws_share + share_words);
-    c->ws_parts = c->ws_count + (parts_at - share_words);
-    c->part_slots = part_slots;
+    p.parts = c->ws_count + (parts_at - share_words);
+    p.states = reinterpret_cast<uint32_t*>(c->ws_share) + zeroed / sizeof(uint32_t);
     c->ws_bytes += share_bytes;
   }
   *out = c;
@@ -315,7 +311,7 @@ int ecoserve_destroy(ecoserve_ctx* c) {
   int rc = ECOSERVE_OK;
   if (!guard.ok || hipDeviceSynchronize() != hipSuccess) rc = ECOSERVE_EHIP;
   if (c->ws_acc) (void)hipFree(c->ws_acc);
-  if (c->ws_more_parts) (void)hipFree(c->ws_more_parts);
+  if (c->forced.parts) (void)hipFree(c->forced.parts);
   if (c->ws_plan) (void)hipFree(c->ws_plan);
   if (c->ws_share) (void)hipFree(c->ws_share);
   for (int i = 0; i < 3; ++i)
@@ -560,7 +556,7 @@ static int decode_impl(ecoserve_ctx* c, const void* q, int64_t q_row_stride, con
   if (use_mfma(c) && automatic && small.n_split == 0 && decode_sliced(B, a.Hkv, c->num_cu) &&
       !(c->opt_adaptive && adaptive_stream(B, a.Hkv, max_ctx_len, c->num_cu))) {
     ProfileScope prof(c, ECOSERVE_KERNEL_DECODE, s);
-    e = launch_decode_sliced(a, ctx_len, max_ctx_len, c->ws_parts, c->ws_count, c->num_cu, s);
+    e = launch_decode_sliced(a, ctx_len, max_ctx_len, slice_states(c).states, c->ws_count, c->num_cu, s);
     return e == hipSuccess ? ECOSERVE_OK : ECOSERVE_EHIP;
   }
   if (use_mfma(c) && small.n_split == 0) {
@@ -585,12 +581,16 @@ static int decode_impl(ecoserve_ctx* c, const void* q, int64_t q_row_stride, con
   }
   const int32_t split_tokens = automatic ? small.split_tokens : plan_split_tokens(c, B, max_ctx_len);
   const int32_t n_split_max = automatic ? small.n_split : ceil_div(max_ctx_len, split_tokens);
-  // cannot happen: split_tokens >= kMinSplitTokens, and (bf16, 128) comes here with one slice per workgroup that fits
-  if (n_split_max > 1 && (c->opt_force_plain ? n_split_max > c->ws_splits : (int64_t)(split_tokens ? B : 1) * a.Hq * n_split_max > c->part_slots)) return ECOSERVE_EINVAL;
+  // cannot happen: split_tokens >= kMinSplitTokens, and the states are there for what the rules cut
+  const SliceStates to = slice_states(c);
+  const int64_t slots = (int64_t)(split_tokens ? B : 1) * a.Hq * n_split_max;
+  if (n_split_max > 1 && (c->opt_force_plain ? n_split_max > c->ws_splits
+                                             : slots > to.state_slots || (split_tokens <= kShortSlice && slots > to.part_slots)))
+    return ECOSERVE_EINVAL;
   {
     ProfileScope prof(c, ECOSERVE_KERNEL_DECODE, s);
     e = c->opt_force_plain ? launch_decode_plain(a, ctx_len, split_tokens, n_split_max, c->ws_acc, c->ws_ml, c->ws_splits, s)
-                           : launch_decode_any(a, ctx_len, split_tokens, n_split_max, c->ws_parts, c->ws_count, c->num_cu, s);
+                           : launch_decode_any(a, ctx_len, split_tokens, n_split_max, to.parts, to.states, c->ws_count, c->num_cu, s);
   }
   if (e != hipSuccess) return ECOSERVE_EHIP;
   if (c->opt_force_plain && n_split_max > 1) {

@@ -250,11 +250,12 @@ __device__ __forceinline__ void attend_row(const E* __restrict__ qrow, const E* 
 
 // Partial states, from the workgroup of one slice to the one that merges them, within a launch and possibly between XCDs: past the
 // caches that XCDs do not share, and word by word.  A word holds the complement of the value's bits and is zero while it holds none, so a reader
-// sees by itself whether what it asked for has arrived, and nobody waits for a store to be acknowledged before it is announced.  Who reads a state clears it: the words
-// are zero between launches.  A slice that takes rows again (see attend_row) has been counted already: it says so in the rows' maximum and sum, and nobody gives up on it.
-// (The values whose complements are zero or kPartAgain, NaNs, are stored as their neighbour.)
-constexpr uint32_t kPartAgain = 1;
-__device__ __forceinline__ uint32_t part_bits(float v) { return max(~__float_as_uint(v), kPartAgain + 1); }
+// sees by itself whether what it asked for has arrived, and nobody waits for a store to be acknowledged before it is announced.  (The one value
+// whose complement is zero, a NaN, is stored as its neighbour.)  Who reads a state clears it: the words are zero between launches.
+// That is for a few states of short slices.  Long ones end at very different times, and many take long to clear: those lie elsewhere, and who has stored his, and has had the
+// stores acknowledged, is counted; the last one finds all of them and leaves the words as they are.  (Clearing is a store of one CU's for each state it reads: us per
+// call with it, 8 on 1, 1 x 150000 tokens 36.5, 30.9 so; 16 on 1, 1 x 60000 32.7, 25.8.)  Nobody waits for such a slice, however long it takes rows again (see attend_row).
+__device__ __forceinline__ uint32_t part_bits(float v) { return max(~__float_as_uint(v), 1u); }
 __device__ __forceinline__ float part_value(uint32_t bits) { return __uint_as_float(~bits); }
 // (The instructions of relaxed atomics of agent scope, as buffer accesses: a scalar base and 32 bits of offset per lane, and nothing is read behind
 // the range.)
@@ -263,6 +264,10 @@ __device__ __forceinline__ u32x4 part_bits(const f32x4& v) { return u32x4{part_b
 __device__ __forceinline__ void store_part(__amdgpu_buffer_rsrc_t r, int byte, const u32x2& w) { __builtin_amdgcn_raw_buffer_store_b64(w, r, byte, 0, kAuxAgent); }
 __device__ __forceinline__ void store_part(__amdgpu_buffer_rsrc_t r, int byte, const u32x4& w) { __builtin_amdgcn_raw_buffer_store_b128(w, r, byte, 0, kAuxAgent); }
 constexpr int part_words(int D) { return D + 4; }  // of a state: the unnormalised head vector, its maximum, its sum, and two that keep 16 bytes aligned
+// A merging wavefront asks again at most so often (half a second).  The slices it waits for run already, wait for nothing themselves and are short: microseconds from their
+// end, milliseconds where rows are taken again.  So it never gives up, but for calls that overlap on one workspace, which they may not: they end with NaN then.
+constexpr int kMostPolls = 1 << 19;
+
 // Over the two halves, or (N 4) the four 16-lane groups, of a wavefront, lane by lane.
 template <int N, typename F>
 __device__ __forceinline__ float of_groups(float v, F f) {
@@ -322,11 +327,11 @@ __device__ __forceinline__ SliceOf slice_of_workgroup(const int32_t* __restrict_
 //   M = max_k m_k;  l = sum_k l_k 2^(m_k - M);  o = sum_k acc_k 2^(m_k - M) / l,  in the order of the slices, whichever merges
 // (the division is the caller's), with weights below the smallest normal number, which the bare exponent flushes: whole states weigh that little beside
 // another one, and large values make them count (the bare instruction: 1 x 777 tokens, 40 on 8, 6.81 us a call, 6.89 so).  `first`: the state of slice 0, the next ones slice_bytes further on each; slice `own` (-1: none) is in M, total and o.
-// The states of eight slices are asked for at once, those of the next eight while they are added up, and all again until they have
+// The states of eight slices are asked for at once, those of the next eight while they are added up, and, unless they are COUNTED and there, all again until they have
 // arrived: every slice has started, and none waits for another.  Each group of lanes takes every NG-th slice.  (Slices whose scores are all
 // -inf weigh nothing: their m is -inf, their sums are zero.)  Lane l has elements 4 (l % LG) of every 128.
 constexpr int lane_groups(int KS) { return KS <= 2 ? 4 : 2; }
-template <int KS, bool FULL>
+template <int KS, bool FULL, bool COUNTED>
 __device__ __forceinline__ void merge_slices(uint32_t* first, int slice_bytes, int row_bytes, int D, int n_split, int own_slice, float& M, float& total,
                                              f32x4 (&o)[(KS + 3) / 4]) {
   constexpr int NC = (KS + 3) / 4, NG = lane_groups(KS), LG = 64 / NG, kAtOnce = 8 / NG;  // (per group of lanes)
@@ -360,7 +365,7 @@ __device__ __forceinline__ void merge_slices(uint32_t* first, int slice_bytes, i
     }
   };
   Group now, then;
-  MergeLooks looks;
+  int polls = 0;
   __amdgpu_buffer_rsrc_t from = range(0);
   ask(from, now);
   for (int base = 0; base < n_split; base += NG * kAtOnce) {
@@ -376,28 +381,25 @@ __device__ __forceinline__ void merge_slices(uint32_t* first, int slice_bytes, i
         for (int c = 0; c < NC; ++c)
 #pragma unroll
           for (int e = 0; e < 4; ++e) least = min(least, now.o[j][c][e]);
-        any |= (least <= kPartAgain) & (NG * j < more) & (NG * j != own);
+        any |= (least == 0) & (NG * j < more) & (NG * j != own);
       }
       return __any(any);
     };
-    if (missing()) {  // (apart from the first look, which then waits for these slices alone)
+    if (!COUNTED && missing()) {  // (apart from the first look, which then waits for these slices alone)
       asm volatile("" ::: "memory");
       do {
         // who waits for long keeps out of the others' way: 0.4 us between looks, at the sums alone
-        for (bool look = looks.many(); look;) {
+        for (bool wait = polls > 1; wait && polls < kMostPolls; ++polls) {
           __builtin_amdgcn_s_sleep(16);
           asm volatile("" ::: "memory");
-          bool any = false, again = false;
+          bool any = false;
 #pragma unroll
-          for (int j = 0; j < kAtOnce; ++j) {
-            const uint32_t sum = __builtin_amdgcn_raw_buffer_load_b32(from, at_ml + 4 + NG * j * slice_bytes, 0, kAuxAgent);
-            any |= (sum <= kPartAgain) & (NG * j < more) & (NG * j != own);
-            again |= (sum == kPartAgain) & (NG * j < more) & (NG * j != own);
-          }
-          look = looks.once_more(__any(again)) && __any(any);
+          for (int j = 0; j < kAtOnce; ++j)
+            any |= (__builtin_amdgcn_raw_buffer_load_b32(from, at_ml + 4 + NG * j * slice_bytes, 0, kAuxAgent) == 0) & (NG * j < more) & (NG * j != own);
+          wait = __any(any);
         }
         ask(from, now);
-      } while (missing() && looks.once_more(false));
+      } while (missing() && ++polls < kMostPolls);
     }
     float m_new = m2, x[kAtOnce];
 #pragma unroll
@@ -406,16 +408,19 @@ __device__ __forceinline__ void merge_slices(uint32_t* first, int slice_bytes, i
       m_new = fmaxf(m_new, x[j]);
     }
 #pragma unroll
-    for (int j = 0; j < kAtOnce; ++j) {  // (this workgroup's own words are zero already)
+    for (int j = 0; j < kAtOnce && !COUNTED; ++j) {  // (this workgroup's own words are zero already)
 #pragma unroll
       for (int c = 0; c < NC; ++c) store_part(from, at_o[c] + NG * j * slice_bytes, u32x4{0u, 0u, 0u, 0u});
       store_part(from, at_ml + NG * j * slice_bytes, u32x2{0u, 0u});
     }
-    const float mu = m_new == -INFINITY ? 0.f : m_new, old = m2 == -INFINITY ? 0.f : exp2f(m2 - mu);
-    m2 = m_new;
-    l2 *= old;
+    const float mu = m_new == -INFINITY ? 0.f : m_new;
+    if (base > 0) {
+      const float old = m2 == -INFINITY ? 0.f : exp2f(m2 - mu);
+      l2 *= old;
 #pragma unroll
-    for (int c = 0; c < NC; ++c) o2[c] *= old;
+      for (int c = 0; c < NC; ++c) o2[c] *= old;
+    }
+    m2 = m_new;
 #pragma unroll
     for (int j = 0; j < kAtOnce; ++j) {
       const float wk = exp2f(x[j] - mu);
@@ -439,8 +444,8 @@ __device__ __forceinline__ void merge_slices(uint32_t* first, int slice_bytes, i
 
 // Decode: grid (splits, Hkv, B), or (Hkv, slices of all sequences) with balanced slices, W wavefronts; the blocks of a slice of `split_tokens` tokens of one (sequence, K/V
 // head) go to the wavefronts in turn, whose states are combined through LDS.  With one slice the result is final,
-// otherwise it is a partial state, and one workgroup of the (sequence, K/V head) merges them (`counters`, one per (sequence, K/V head), and `parts`: zero before
-// and after).  With k_new given the wavefront that has the last block takes the newest token (position ctx_len - 1) from the new rows and stores it into the cache.
+// otherwise it is a partial state, and one workgroup of the (sequence, K/V head) merges them (`counters`, one per (sequence, K/V head), and `parts`, a few short slices'
+// states: zero before and after; `states`: the others').  With k_new given the wavefront that has the last block takes the newest token (position ctx_len - 1) from the new rows and stores it into the cache.
 // What such a launch is made of (1 x 777 tokens, 40 query heads on 8, 8.4 us a call, time stamps): 0.4 us to the length, 0.5 to the block ids, 1.4 to the blocks,
 // 1.6 for the states through LDS (three barriers, divisions, the code of a row taken again in front of them), 0.2 and 0.35 for stores acknowledged and the count,
 // 1.2 for the maxima, 1.4 for the states and the result.  Now 6.8 us: one barrier, whole rows per wavefront, 16 bytes per lane; the count asked for behind the
@@ -451,7 +456,7 @@ template <typename E, int KS, int W, int AUX = 0, bool FULL = true, bool BALANCE
 __global__ __launch_bounds__(W * 64) void decode_any_kernel(
     const E* __restrict__ q, int q_row_stride, const E* __restrict__ k_new, const E* __restrict__ v_new, int new_row_stride,
     E* k_cache, E* v_cache, const int32_t* __restrict__ block_table, int bt_stride, const int32_t* __restrict__ ctx_len,
-    E* __restrict__ out, float* __restrict__ lse, uint32_t* parts, uint32_t* counters, int split_tokens, int Hq,
+    E* __restrict__ out, float* __restrict__ lse, uint32_t* parts, uint32_t* states, uint32_t* counters, int split_tokens, int Hq,
     int Hkv, int G, int head_size, float scale_log2e, int B) {
   typedef Block<E, KS, AUX, FULL> Blk;
   constexpr int X = Elem<E>::X, NK = Blk::NK, NV = Blk::NV;
@@ -540,7 +545,9 @@ __global__ __launch_bounds__(W * 64) void decode_any_kernel(
   // Which of the slices starts last merges them all (see the end).  Asked here, behind the first blocks, the answer is there before it is wanted.  Slices of
   // more than four rounds end at so many times that who waits for them is in their way: there it is the one that is done last (1 x 75000 tokens, 62.3 us; waiting 65.2).
   const int n_split = slice.n;
-  const bool early = t1 - t0 <= 4 * 16 * W;
+  // So it is where there are many states: those of the others are cleared by one CU (16 on 1, 17 x 100..6425 tokens 18.2 us, 15.6 so, 1 x 3000 11.8, 11.3; at 96 and 128 states, 8 on 1,
+  // 2 x 3878, 1 x 8000, no difference).
+  const bool early = at.tokens <= kShortRounds * 16 * W && n_split * G <= 128;  // (the same for all slices of a context)
   auto arrive = [&]() { return (int)atomicInc(counters + (size_t)b * Hkv + g, (unsigned)n_split - 1); };  // (the last one wraps it to zero)
   int order = 0, newest_blk = 0;
   if (n_split > 1 && early && tid == 0) order = arrive();
@@ -617,16 +624,20 @@ __global__ __launch_bounds__(W * 64) void decode_any_kernel(
       else __builtin_amdgcn_raw_buffer_store_b16(s_new[1][d], rv, at_d, 0, 0);
     }
   }
-  if (tid == 0) {
-    if (n_split > 1 && !early) order = arrive();
-    s_order = order;
-  }
+  if (tid == 0) s_order = order;
   __syncthreads();
-  const bool merges = __builtin_amdgcn_readfirstlane(s_order) == n_split - 1;  // (one slice: it is the last one, and there is nothing to merge)
+  const bool merges = (early || n_split == 1) && __builtin_amdgcn_readfirstlane(s_order) == n_split - 1;  // (one slice: it is the last one, and there is nothing to merge)
   // Partial states: [B][Hq][slices], or (balanced) [slices of all sequences][Hq].  slot0: of this slice and the group's first head.
   const int row_words = part_words(d_scalar), grp = lane / LG, el = (lane % LG) * 4;
   const size_t slot0 = BALANCED ? (size_t)blockIdx.y * Hq + (size_t)g * G : ((size_t)b * Hq + (size_t)g * G) * gridDim.x + sp;
   const size_t slot_step = BALANCED ? 1 : gridDim.x, slice_words = (size_t)(BALANCED ? Hq : 1) * row_words;
+  auto to_out = [&](int h, float M, float total, const f32x4 (&o)[NC]) {
+    const size_t row = (size_t)b * Hq + g * G + h;
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+      if (grp == 0 && (!FULL || el + 128 * c < D)) store4(out + row * D + el + 128 * c, divided(o[c], total));
+    if (lse && lane == 0) lse[row] = (M + log2f(total)) * kLn2;
+  };
 #pragma unroll 1
   for (int h = wave; h < G; h += W) {
     float2 ml[W / NG];
@@ -657,9 +668,6 @@ __global__ __launch_bounds__(W * 64) void decode_any_kernel(
         zero = __builtin_fmaf(o[c][e], 0.f, zero);
       }
     if (__any(zero != zero && total == total)) {  // (see attend_row)
-      if (!merges && h + W * lane < G)  // (counted already: whoever merges this row, or the wavefront's next ones, is to wait)
-        __hip_atomic_store(reinterpret_cast<uint64_t*>(parts + (slot0 + (h + W * lane) * slot_step) * row_words + D), (uint64_t)kPartAgain << 32 | kPartAgain, __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_AGENT);
       float r[4];
       attend_row<E>(scalar_here(q + (size_t)b * q_row_stride) + (size_t)(scalar_here(g) * G + h) * D, scalar_here(k_cache), scalar_here(v_cache), scalar_here(bt_row),
                     scalar_here(g), scalar_here(Hkv), scalar_here(D), scalar_here(t0), scalar_here(t1), scale_log2e, M, total, r);
@@ -674,7 +682,7 @@ __global__ __launch_bounds__(W * 64) void decode_any_kernel(
       for (int c = 0; c < NC; ++c)
         o[c] = *reinterpret_cast<const f32x4*>(&s_acc[0][h][min((ln % LG) * 4 + 128 * c, 32 * KS - 4)]);
     }
-    uint32_t* const mine = parts + (slot0 + h * slot_step) * row_words;
+    uint32_t* const mine = (early ? parts : states) + (slot0 + h * slot_step) * row_words;
     if (!merges) {
       const __amdgpu_buffer_rsrc_t to = __builtin_amdgcn_make_buffer_rsrc(scalar_here(mine), 0, row_words * 4, kRsrc32);
       if (grp == 0) {
@@ -686,12 +694,23 @@ __global__ __launch_bounds__(W * 64) void decode_any_kernel(
       }
       continue;
     }
-    if (n_split > 1) merge_slices<KS, FULL>(mine - (int64_t)sp * (int64_t)slice_words, (int)slice_words * 4, row_words * 4, D, n_split, sp, M, total, o);
-    const size_t row = (size_t)b * Hq + g * G + h;
+    if (n_split > 1) merge_slices<KS, FULL, false>(mine - (int64_t)sp * (int64_t)slice_words, (int)slice_words * 4, row_words * 4, D, n_split, sp, M, total, o);
+    to_out(h, M, total, o);
+  }
+  if (early || n_split == 1) return;
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (this wavefront's states are where every XCD finds them)
+  __syncthreads();
+  if (tid == 0) s_order = arrive();
+  __syncthreads();
+  if (__builtin_amdgcn_readfirstlane(s_order) != n_split - 1) return;
+#pragma unroll 1
+  for (int h = wave; h < G; h += W) {
+    float M = 0.f, total = 0.f;
+    f32x4 o[NC];
 #pragma unroll
-    for (int c = 0; c < NC; ++c)
-      if (grp == 0 && (!FULL || el + 128 * c < D)) store4(out + row * D + el + 128 * c, divided(o[c], total));
-    if (lse && lane == 0) lse[row] = (M + log2f(total)) * kLn2;
+    for (int c = 0; c < NC; ++c) o[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+    merge_slices<KS, FULL, true>(states + (slot0 + h * slot_step) * row_words - (int64_t)sp * (int64_t)slice_words, (int)slice_words * 4, row_words * 4, D, n_split, -1, M, total, o);
+    to_out(h, M, total, o);
   }
 }
 
@@ -716,7 +735,7 @@ __global__ __launch_bounds__(W * 64) void decode_any_kernel(
 // lengths, which the host does not know: grid (K/V heads, rank).  Every wavefront reads all lengths (at most 256, four per lane), and their sum
 // gives the slice with which no more than `max_full` whole ones come of a K/V head.  Those are handed out first, then what is left of the contexts, longest first; a
 // workgroup without a rank ends (ranked in each group of 64 sequences, up to 3000 of them stood at the end of a launch: 16 on 1, 238 x 1140..11406 tokens 63.8 us, 56.3 so).  Of a context that is cut, the workgroup that is done last adds the states up (merge_slices): one that waited for
-// the others while they walk slows them (long slices). `parts` has max_full slots of whole slices and as many of the rest per K/V head.  A slice below 24 blocks
+// the others while they walk slows them (long slices). `states` has max_full slots of whole slices and as many of the rest per K/V head.  A slice below 24 blocks
 // costs more in states than it evens out.  us per layer, persistent kernel and its merge / here: 40 on 8, 128 x 512..4096 203 / 193, 52 on 52, 24 x 300..3000 (the append a
 // launch before it) 203 / 199, 64 on 8, 256 x 1024..4096 468 / 464; other batches at decode_sliced.
 enum class Order { kBatch, kLongest, kSliced };
@@ -725,7 +744,7 @@ __global__ __launch_bounds__(W * 64, 3) void decode_short_kernel(
     const uint16_t* __restrict__ q, int q_row_stride, const uint16_t* __restrict__ k_new, const uint16_t* __restrict__ v_new, int new_row_stride,
     uint16_t* k_cache, uint16_t* v_cache, const int32_t* __restrict__ block_table, int bt_stride, const int32_t* __restrict__ ctx_len,
     uint16_t* __restrict__ out, float* __restrict__ lse, int Hq, int Hkv, int G, float scale_log2e, int B,
-    int per_group, int shift, int stream, uint32_t* parts, uint32_t* counters, int max_full) {
+    int per_group, int shift, int stream, uint32_t* states, uint32_t* counters, int max_full) {
   typedef Block<uint16_t, 4, kNonTemporal, false> Blk;
   constexpr int D = 128, kPiece = 16 * D * 2;
   static_assert(W <= 8, "a wavefront adds up whole tiles");
@@ -967,7 +986,7 @@ __global__ __launch_bounds__(W * 64, 3) void decode_short_kernel(
       if (zero != zero && col < G && total == total) s_bad = 1;
       __syncthreads();
       const int row_words = part_words(D);
-      uint32_t* const first = parts + ((size_t)(slot - slice_no) * Hq + (size_t)g * G) * row_words;  // (slice 0, the group's first head)
+      uint32_t* const first = states + ((size_t)(slot - slice_no) * Hq + (size_t)g * G) * row_words;  // (slice 0, the group's first head)
       const int slice_bytes = Hq * row_words * 4;
       const __amdgpu_buffer_rsrc_t to = __builtin_amdgcn_make_buffer_rsrc(scalar_here(reinterpret_cast<char*>(first) + (size_t)slice_no * slice_bytes), 0, G * row_words * 4, kRsrc32);
       if (!s_bad) {
@@ -986,16 +1005,17 @@ __global__ __launch_bounds__(W * 64, 3) void decode_short_kernel(
           for (int r = 0; r < 2; ++r) __builtin_amdgcn_raw_buffer_store_b32(part_bits(o[r]), to, (h * row_words + lane + 64 * r) * 4, 0, kAuxAgent);
           if (lane == 0) store_part(to, (h * row_words + D) * 4, u32x2{part_bits(rm), part_bits(rl)});
         }
-        __syncthreads();
       }
-      // The slice that is done last merges them all (the last one wraps the count to zero).  Counted here, its states are on their way, rows taken again and all.
+      // The slice that is done last merges them all (the last one wraps the count to zero).
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (this wavefront's states are where every XCD finds them)
+      __syncthreads();
       if (tid == 0) s_order = (int)atomicInc(counters + (size_t)(slot - slice_no) * Hkv + g, (unsigned)n_split - 1);
       __syncthreads();
       if (s_order != n_split - 1) return;
       for (int h = wave; h < G; h += W) {
         float rm = 0.f, rl = 0.f;
         f32x4 o[1] = {f32x4{0.f, 0.f, 0.f, 0.f}};
-        merge_slices<4, false>(first + h * row_words, slice_bytes, row_words * 4, D, n_split, -1, rm, rl, o);
+        merge_slices<4, false, true>(first + h * row_words, slice_bytes, row_words * 4, D, n_split, -1, rm, rl, o);
         const size_t row = (size_t)b * Hq + (size_t)g * G + h;
         if (lane < 32) store4(out + row * D + lane * 4, o[0] * (1.f / rl));
         if (lse && lane == 0) lse[row] = (rm + log2f(rl)) * kLn2;
@@ -1274,13 +1294,13 @@ void launch_prefill_typed(const AttnArgs& a, const int32_t* cu_q, const int32_t*
 
 template <typename E>
 void launch_decode_typed(const AttnArgs& a, const int32_t* ctx_len, int32_t split_tokens, int32_t n_split_max, uint32_t* parts,
-                         uint32_t* counters, bool many, hipStream_t s) {
+                         uint32_t* states, uint32_t* counters, bool many, hipStream_t s) {
   const bool balanced = split_tokens == 0;
   auto launch = [&](auto kernel, int W) {
     hipLaunchKernelGGL(kernel, balanced ? dim3((unsigned)a.Hkv, (unsigned)n_split_max) : dim3((unsigned)n_split_max, (unsigned)a.Hkv, (unsigned)a.B), dim3(W * 64), 0, s,
                        (const E*)a.q, a.q_row_stride, (const E*)a.k_new, (const E*)a.v_new, a.new_row_stride,
                        (E*)const_cast<void*>(a.k_cache), (E*)const_cast<void*>(a.v_cache), a.block_table, a.bt_stride, ctx_len,
-                       (E*)a.out, a.lse, parts, counters, split_tokens, a.Hq, a.Hkv, a.Hq / a.Hkv, a.D, a.scale_log2e, a.B);
+                       (E*)a.out, a.lse, parts, states, counters, split_tokens, a.Hq, a.Hkv, a.Hq / a.Hkv, a.D, a.scale_log2e, a.B);
   };
   for_head_size(a.D, [&](auto ks) {
     constexpr int KS = decltype(ks)::value, W = decode_wavefronts(32 * KS, sizeof(E));
@@ -1307,7 +1327,7 @@ hipError_t launch_prefill_any(const AttnArgs& a, const int32_t* cu_q, const int3
 namespace {
 
 template <int W, Order ORDER>
-hipError_t launch_whole(const AttnArgs& a, const int32_t* ctx_len, int32_t max_ctx_len, bool stream, uint32_t* parts, uint32_t* counters, int32_t max_full, hipStream_t s) {
+hipError_t launch_whole(const AttnArgs& a, const int32_t* ctx_len, int32_t max_ctx_len, bool stream, uint32_t* states, uint32_t* counters, int32_t max_full, hipStream_t s) {
   // groups of equal size, at most one sequence per lane; length classes: the largest holds max_ctx_len and what lies above it
   const int groups = (a.B + 63) / 64, per_group = (a.B + groups - 1) / groups;
   int shift = 4;
@@ -1315,7 +1335,7 @@ hipError_t launch_whole(const AttnArgs& a, const int32_t* ctx_len, int32_t max_c
   const dim3 grid = ORDER == Order::kLongest ? dim3((unsigned)a.Hkv, (unsigned)groups, (unsigned)per_group) : dim3((unsigned)a.Hkv, (unsigned)(a.B + max_full));
   hipLaunchKernelGGL((decode_short_kernel<W, ORDER>), grid, dim3(W * 64), 0, s, (const uint16_t*)a.q, a.q_row_stride, (const uint16_t*)a.k_new, (const uint16_t*)a.v_new,
                      a.new_row_stride, (uint16_t*)const_cast<void*>(a.k_cache), (uint16_t*)const_cast<void*>(a.v_cache), a.block_table, a.bt_stride, ctx_len,
-                     (uint16_t*)a.out, a.lse, a.Hq, a.Hkv, a.Hq / a.Hkv, a.scale_log2e, a.B, per_group, shift, stream ? 1 : 0, parts, counters, max_full);
+                     (uint16_t*)a.out, a.lse, a.Hq, a.Hkv, a.Hq / a.Hkv, a.scale_log2e, a.B, per_group, shift, stream ? 1 : 0, states, counters, max_full);
   return hipGetLastError();
 }
 
@@ -1333,16 +1353,16 @@ hipError_t launch_decode_short(const AttnArgs& a, const int32_t* ctx_len, int32_
                                                                                                                   : hipErrorInvalidValue;
 }
 
-hipError_t launch_decode_sliced(const AttnArgs& a, const int32_t* ctx_len, int32_t max_ctx_len, uint32_t* parts, uint32_t* counters, int32_t num_cu, hipStream_t s) {
+hipError_t launch_decode_sliced(const AttnArgs& a, const int32_t* ctx_len, int32_t max_ctx_len, uint32_t* states, uint32_t* counters, int32_t num_cu, hipStream_t s) {
   if (a.B > kSlicedMostSequences) return hipErrorInvalidValue;
-  return launch_whole<4, Order::kSliced>(a, ctx_len, max_ctx_len, decode_short_stream((int64_t)a.B * a.Hkv, max_ctx_len), parts, counters, sliced_most_full(a.B, a.Hkv, num_cu), s);
+  return launch_whole<4, Order::kSliced>(a, ctx_len, max_ctx_len, decode_short_stream((int64_t)a.B * a.Hkv, max_ctx_len), states, counters, sliced_most_full(a.B, a.Hkv, num_cu), s);
 }
 
 hipError_t launch_decode_any(const AttnArgs& a, const int32_t* ctx_len, int32_t split_tokens, int32_t n_split_max, uint32_t* parts,
-                             uint32_t* counters, int32_t num_cu, hipStream_t s) {
+                             uint32_t* states, uint32_t* counters, int32_t num_cu, hipStream_t s) {
   const bool many = (int64_t)(split_tokens ? a.B : 1) * a.Hkv * n_split_max > num_cu;
-  if (a.dtype == ECOSERVE_BF16) launch_decode_typed<uint16_t>(a, ctx_len, split_tokens, n_split_max, parts, counters, many, s);
-  else launch_decode_typed<float>(a, ctx_len, split_tokens, n_split_max, parts, counters, many, s);
+  if (a.dtype == ECOSERVE_BF16) launch_decode_typed<uint16_t>(a, ctx_len, split_tokens, n_split_max, parts, states, counters, many, s);
+  else launch_decode_typed<float>(a, ctx_len, split_tokens, n_split_max, parts, states, counters, many, s);
   return hipGetLastError();
 }
 

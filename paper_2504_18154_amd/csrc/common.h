@@ -75,6 +75,12 @@ struct DeviceGuard {
 
 }  // namespace eco
 
+// Partial states of slices that a kernel of attn_any_mfma.hip merges itself.
+struct SliceStates {
+  uint32_t *parts = nullptr, *states = nullptr;
+  int64_t part_slots = 0, state_slots = 0;
+};
+
 struct ecoserve_ctx {
   int device;
   ecoserve_layout lay;
@@ -98,10 +104,10 @@ struct ecoserve_ctx {
   float* ws_share;             // per-XCD shares (mean 1) [2][8], speeds [8], then as int32 [2 * wavefronts]: units, ticks,
                                // then [4 * wavefronts]: the cut (sequence, K/V head) each chunk reports to the merge
   int share_parity;            // which of the two share vectors the next adaptive decode launch reads
-  uint32_t* ws_count;          // [max_batch][Hkv] and at least eight per CU, zero between launches: slices of a (sequence, K/V head) that have started
-  uint32_t* ws_parts;          // part_slots partial states of D + 4 words, zero between launches: slices of the kernels of attn_any_mfma.hip
-  uint32_t* ws_more_parts;     // where ws_parts points once an option has asked for more of them than the context was made with, else NULL
-  int64_t part_slots;
+  uint32_t* ws_count;          // [max_batch][Hkv] and at least six per CU, zero between launches: slices of a (sequence, K/V head) that have started
+  // Partial states of D + 4 words, of the slices of the kernels of attn_any_mfma.hip: those of a few short slices, zero between launches, and all others.  The second set,
+  // for layouts other than (bf16, 128), is there once ECOSERVE_OPT_DECODE_SPLIT_TOKENS has been set, and for calls with that option alone.
+  SliceStates parts, forced;
   int32_t ws_splits;
   int32_t* ws_plan;            // prefill plan: header and one record per query tile of the last prefill launch
   float* ws_pieces;            // prefill: states of the pieces of tiles whose key steps are shared out (bf16, D = 128)
@@ -168,18 +174,18 @@ hipError_t launch_decode_merge(const AttnArgs& a, const int32_t* ctx_len, int32_
 // attn_any_mfma.hip: every layout on matrix cores (bf16, D = 128: small decode batches only)
 // (one launch; with a.k_new given it appends the step's tokens too; split_tokens: a multiple of 16 per slice of the
 // context, n_split_max slices, partial states [B][Hq][n_split_max]; or, (bf16, 128) and B <= 64 only, 0: balanced slices, n_split_max
-// per K/V head in all, at least B, partial states [n_split_max][Hq], D + 4 words each; words and counters [B][Hkv] are zero and stay so:
-// any_decode and small_decode in decode_slices.h)
+// per K/V head in all, at least B, partial states [n_split_max][Hq], D + 4 words each, in `parts`, whose words are zero and stay so, or, slices of more
+// than four rounds of the wavefronts and many states, in `states`; counters [B][Hkv] that are zero and stay so: any_decode and small_decode in decode_slices.h)
 hipError_t launch_prefill_any(const AttnArgs& a, const int32_t* cu_q, const int32_t* ctx_before, int32_t T, hipStream_t s);
 hipError_t launch_decode_any(const AttnArgs& a, const int32_t* ctx_len, int32_t split_tokens, int32_t n_split_max,
-                             uint32_t* parts, uint32_t* counters, int32_t num_cu, hipStream_t s);
+                             uint32_t* parts, uint32_t* states, uint32_t* counters, int32_t num_cu, hipStream_t s);
 // (bf16, 128), whole contexts: `waves` (1, 2 or 4) wavefronts per (sequence, K/V head), see decode_short in decode_slices.h; no workspace; with
 // a.k_new given it appends the step's tokens too
 hipError_t launch_decode_short(const AttnArgs& a, const int32_t* ctx_len, int32_t waves, int32_t max_ctx_len, int32_t num_cu, hipStream_t s);
 
-// The same, longest first, long contexts cut (at most kSlicedMostSequences sequences, see decode_slices.h): parts and counters as launch_decode_any's, 2 sliced_most_full(B,
+// The same, longest first, long contexts cut (at most kSlicedMostSequences sequences, see decode_slices.h): states and counters as launch_decode_any's, 2 sliced_most_full(B,
 // Hkv, num_cu) of each per K/V head
-hipError_t launch_decode_sliced(const AttnArgs& a, const int32_t* ctx_len, int32_t max_ctx_len, uint32_t* parts, uint32_t* counters, int32_t num_cu, hipStream_t s);
+hipError_t launch_decode_sliced(const AttnArgs& a, const int32_t* ctx_len, int32_t max_ctx_len, uint32_t* states, uint32_t* counters, int32_t num_cu, hipStream_t s);
 
 // attn_decode_mfma.hip: bf16, D = 128
 // (split_tokens 0 = equal share per wavefront of the persistent grid; > 0 forces the chunk size)

@@ -27,9 +27,11 @@ constexpr size_t kAccFloats = (size_t)2 * kNoallocMaxWaves * kMaxGroup * 128;  /
 constexpr size_t kMlFloats = (size_t)2 * kNoallocMaxWaves * kMaxGroup * 2;
 constexpr size_t kMetaInts = (kMaxBatch + 19 + 63) / 64 * 64;
 constexpr size_t kCutInts = (size_t)4 * kNoallocMaxWaves;
-constexpr size_t kCountInts = (size_t)8 * kNoallocMaxWgs;  // small_decode, decode_sliced: at most this many contexts that are cut
-constexpr size_t kPartWords = (size_t)8 * kNoallocMaxWgs * kMaxGroup * (128 + 4);  // their slices' states, eight per CU
-constexpr size_t kScratchBytes = (kAccFloats + kMlFloats + kMetaInts + kCutInts + kCountInts + kPartWords) * 4;  // 32.8 MiB
+constexpr size_t kCountInts = (size_t)6 * kNoallocMaxWgs;  // small_decode, decode_sliced: at most this many contexts that are cut
+constexpr size_t kPartWords = (size_t)2 * kNoallocMaxWgs * kMaxGroup * (128 + 4);   // short slices' states, two per CU
+constexpr size_t kScratchBytes = (kAccFloats + kMlFloats + kMetaInts + kCutInts + kCountInts + kPartWords) * 4;  // 20.4 MiB
+// (long slices' states, six per CU, lie where the persistent kernel's do)
+static_assert((size_t)6 * kNoallocMaxWgs * kMaxGroup * (128 + 4) <= kAccFloats + kMlFloats);
 
 // On the host this name is only a handle for hipGetSymbolAddress; device code and kernel arguments use the
 // address looked up below.
@@ -101,6 +103,9 @@ extern "C" int ecoserve_attn_decode_noalloc(int device, const ecoserve_layout* l
   float* const ws_ml = ws_acc + kAccFloats;
   int32_t* const ws_meta = reinterpret_cast<int32_t*>(ws_ml + kMlFloats);
   int32_t* const ws_cut = ws_meta + kMetaInts;
+  uint32_t* const counts = reinterpret_cast<uint32_t*>(ws_cut + kCutInts);
+  uint32_t* const parts = counts + kCountInts;
+  uint32_t* const states = reinterpret_cast<uint32_t*>(ws_acc);
 
   AttnArgs a;
   a.q = q;
@@ -129,13 +134,10 @@ extern "C" int ecoserve_attn_decode_noalloc(int device, const ecoserve_layout* l
   const SmallDecode small = small_decode(B, a.Hkv, max_ctx_len, n_wgs);
   if (small.n_split > 0) {
     // (at most two slices per CU in all, of Hq / Hkv <= kMaxGroup heads)
-    uint32_t* const counts = reinterpret_cast<uint32_t*>(ws_cut + kCutInts);
-    return launch_decode_any(a, ctx_len, small.split_tokens, small.n_split, counts + kCountInts, counts, n_wgs, s) == hipSuccess ? ECOSERVE_OK : ECOSERVE_EHIP;
+    return launch_decode_any(a, ctx_len, small.split_tokens, small.n_split, parts, states, counts, n_wgs, s) == hipSuccess ? ECOSERVE_OK : ECOSERVE_EHIP;
   }
-  if (decode_sliced(B, a.Hkv, n_wgs)) {
-    uint32_t* const counts = reinterpret_cast<uint32_t*>(ws_cut + kCutInts);
-    return launch_decode_sliced(a, ctx_len, max_ctx_len, counts + kCountInts, counts, n_wgs, s) == hipSuccess ? ECOSERVE_OK : ECOSERVE_EHIP;
-  }
+  if (decode_sliced(B, a.Hkv, n_wgs))
+    return launch_decode_sliced(a, ctx_len, max_ctx_len, states, counts, n_wgs, s) == hipSuccess ? ECOSERVE_OK : ECOSERVE_EHIP;
   // (a slot group holds G <= kMaxGroup states, so the array covers kNoallocMaxWaves wavefronts whatever G is)
   hipError_t e = launch_decode_mfma(a, ctx_len, 0, max_ctx_len, n_wgs, ws_acc, ws_ml, ws_meta, kNoallocMaxWaves,
                                     nullptr, nullptr, nullptr, nullptr, ws_cut, s);

@@ -80,23 +80,13 @@ constexpr WaveBlocks wave_blocks(int t0, int t1, int wave, int n_waves) {
   return {blk0 + wave, n_waves, wave < count ? (count - wave + n_waves - 1) / n_waves : 0};
 }
 
-// How often a merging wavefront looks for the states it waits for.  Slices are counted when they begin and have four rounds of blocks at most, or when a wavefront is through
-// with its blocks: their states, or word that rows are taken again, are microseconds away.  Half a second of looks without either, and it gives up: calls overlap on one
-// workspace, which they may not, and end with NaN.  A slice that takes rows again key by key may take long (a slice may have any length), but it ends.
-struct MergeLooks {
-  static constexpr int kMost = 1 << 19;  // half a second
-  int looks = 0;
-  ECO_SLICES_HD bool many() const { return looks > 1; }
-  ECO_SLICES_HD bool once_more(bool rows_are_taken_again) {
-    looks = rows_are_taken_again ? 2 : looks + 1;
-    return looks < kMost;
-  }
-};
-
 // ---- how the host has the decode kernel of attn_any_mfma.hip launched ---------------------------
 
 // Wavefronts of a decode workgroup: eight while two blocks of K and V fit beside the rest in 256 registers.
 constexpr int decode_wavefronts(int D, int elem_bytes) { return D > (elem_bytes == 4 ? 128 : 192) ? 4 : 8; }
+
+// A slice of up to so many rounds of the wavefronts is a short one; so many tokens are it at most, in eight wavefronts.
+constexpr int kShortRounds = 4, kShortSlice = kShortRounds * 8 * 16;
 
 struct SmallDecode {
   int32_t split_tokens, n_split;  // as launch_decode_any takes them
