@@ -135,7 +135,8 @@ enum { ECOSERVE_KERNEL_APPEND = 0, ECOSERVE_KERNEL_PREFILL = 1, ECOSERVE_KERNEL_
 
 /* Create a context on `device` for batches of at most max_batch sequences whose
  * block tables have at most max_blocks_per_seq entries per sequence.
- * Allocates the workspace (partial results of split contexts: a few MB for decode, and 65 MiB for
+ * Allocates the workspace (partial results of split contexts: a few MB for decode, in layouts other than bf16 of head size 128 a state
+ * per 1024 tokens of the limits and query head if that is more, and 65 MiB for
  * prefill in bf16 layouts of head size 128 whose sequences may exceed 512 tokens; a device without
  * room for these 65 MiB does not share out key steps, see ecoserve_attn_prefill).  On failure
  * *out is NULL. */

@@ -67,6 +67,7 @@ int64_t slots_needed(const ecoserve_ctx* c, int32_t* plain_splits) {
                                             c->opt_split_tokens, c->num_cu * kDecodeWgsPerCu);
     return 2 * waves * (c->lay.num_q_heads / c->lay.num_kv_heads);
   }
+  if (!c->opt_force_plain) return 0;  // (the other layouts' kernels have states of their own, see slice_states)
   // a sequence of n blocks cut into chunks of >= c blocks at arbitrary offsets has at most n/c + 2 pieces
   *plain_splits = ceil_div(c->max_blocks_per_seq * kBlockSize, kMinSplitTokens) + 2;
   return (int64_t)c->max_batch * c->lay.num_q_heads * *plain_splits;
@@ -82,7 +83,7 @@ int64_t slices_at_most(const ecoserve_ctx* c, int32_t tokens) {
 }
 SliceStates slice_states(const ecoserve_ctx* c) {
   if (!has_mfma(c)) return c->opt_split_tokens > 0 ? c->forced : c->parts;
-  return {c->parts.parts, reinterpret_cast<uint32_t*>(c->ws_acc), c->parts.part_slots, 6 * c->num_cu * group_of(c)};
+  return {c->parts.parts, reinterpret_cast<uint32_t*>(c->ws_acc), c->parts.part_slots, c->ws_acc ? 6 * c->num_cu * group_of(c) : 0};
 }
 
 // For layouts other than (bf16, 128), once an option forces a length of slices: states for any length of them.
@@ -114,24 +115,31 @@ int ensure_partial_states(ecoserve_ctx* c) {
   if (plain_splits) c->ws_splits = plain_splits;
   if (const int st = ensure_forced_states(c); st != ECOSERVE_OK) return st;
   if (need <= c->ws_slots) return ECOSERVE_OK;
+  auto give = [&](int64_t slots) {  // (one allocation: each is tens of microseconds of creating a context)
+    const size_t bytes = (size_t)slots * (c->lay.head_dim + 2) * sizeof(float);
+    float* p = nullptr;
+    if (slots <= 0 || hipMalloc(&p, bytes) != hipSuccess) {
+      (void)hipGetLastError();
+      return false;
+    }
+    c->ws_acc = p;
+    c->ws_ml = p + (size_t)slots * c->lay.head_dim;
+    c->ws_slots = slots;
+    c->ws_bytes += bytes;
+    return true;
+  };
+  const int64_t had = c->ws_slots;
   if (c->ws_acc) {
     if (hipDeviceSynchronize() != hipSuccess) return ECOSERVE_EHIP;  // launches in flight may still use them
     (void)hipFree(c->ws_acc);
-    c->ws_bytes -= (size_t)c->ws_slots * (c->lay.head_dim + 2) * sizeof(float);
+    c->ws_bytes -= (size_t)had * (c->lay.head_dim + 2) * sizeof(float);
   }
   c->ws_acc = nullptr;
   c->ws_ml = nullptr;
   c->ws_slots = 0;
-  const size_t bytes = (size_t)need * (c->lay.head_dim + 2) * sizeof(float);
-  if (hipMalloc(&c->ws_acc, bytes) != hipSuccess) {  // (one allocation: each is tens of microseconds of creating a context)
-    (void)hipGetLastError();
-    c->ws_acc = nullptr;
-    return ECOSERVE_ENOMEM;
-  }
-  c->ws_ml = c->ws_acc + (size_t)need * c->lay.head_dim;
-  c->ws_slots = need;
-  c->ws_bytes += bytes;
-  return ECOSERVE_OK;
+  if (give(need)) return ECOSERVE_OK;
+  (void)give(had);  // (the option is refused: what it had, again)
+  return ECOSERVE_ENOMEM;
 }
 
 // The parts of the workspace whose size the options do not change: the decode launch's numbering and the
@@ -555,8 +563,10 @@ static int decode_impl(ecoserve_ctx* c, const void* q, int64_t q_row_stride, con
                                         : any_decode(B, a.Hkv, a.D, a.dtype == ECOSERVE_BF16 ? 2 : 4, max_ctx_len, c->num_cu);
   if (use_mfma(c) && automatic && small.n_split == 0 && decode_sliced(B, a.Hkv, c->num_cu) &&
       !(c->opt_adaptive && adaptive_stream(B, a.Hkv, max_ctx_len, c->num_cu))) {
+    const SliceStates to = slice_states(c);
+    if (!to.state_slots) return ECOSERVE_EHIP;  // (lost when an option asked for more than the device had)
     ProfileScope prof(c, ECOSERVE_KERNEL_DECODE, s);
-    e = launch_decode_sliced(a, ctx_len, max_ctx_len, slice_states(c).states, c->ws_count, c->num_cu, s);
+    e = launch_decode_sliced(a, ctx_len, max_ctx_len, to.states, c->ws_count, c->num_cu, s);
     return e == hipSuccess ? ECOSERVE_OK : ECOSERVE_EHIP;
   }
   if (use_mfma(c) && small.n_split == 0) {
