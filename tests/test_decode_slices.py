@@ -94,7 +94,7 @@ int main() {
     }
     const SmallDecode d = small_decode(B, Hkv, bound, 256);
     const int W = d.n_split == 256 / Hkv ? 8 : 4;
-    std::printf("%s\n", decode_short(B, Hkv, bound, 256) ? "whole" : d.n_split == 0 ? "persistent" : d.split_tokens > 0 ? "uniform" : !covers(len, B, Hkv, d.n_split, W) ? "wrong" : W == 8 ? "8" : "4");
+    std::printf("%s\n", decode_short(B, Hkv, bound, 256) ? "whole" : d.n_split == 0 ? (decode_sliced(B, Hkv, 256) ? "sliced" : "persistent") : d.split_tokens > 0 ? "uniform" : !covers(len, B, Hkv, d.n_split, W) ? "wrong" : W == 8 ? "8" : "4");
   }
   unsigned seed = 12345;
   auto rnd = [&](unsigned n) { return (seed = seed * 1664525u + 1013904223u, (unsigned)((unsigned long long)(seed >> 8) * n >> 24)); };
@@ -116,7 +116,7 @@ int main() {
 """
 
 # the paths that the batches of the GPU tests are there for: at the longest context's length, and with the looser bound
-PATHS = {"RAGGED": ["uniform uniform", "8 8", "8 8", "uniform uniform", "8 8", "uniform uniform", "8 8", "uniform uniform", "4 persistent", "4 persistent"]}
+PATHS = {"RAGGED": ["uniform uniform", "8 8", "8 8", "uniform uniform", "8 8", "uniform uniform", "8 8", "uniform uniform", "4 sliced", "4 sliced"]}
 
 
 def test_paths_of_the_batches_of_the_gpu_tests_and_their_balanced_slices(tmp_path):
@@ -135,18 +135,51 @@ def test_paths_of_the_batches_of_the_gpu_tests_and_their_balanced_slices(tmp_pat
     # the short ones in slices, with the bounds that the tests hand over
     calls += [(heads[1], lens, max(lens)) for heads, lens in t.CASES + t.WHOLE] + [(8, [9000, 20], 600), (8, [700, 40], 700), (2, [320], 1000), (2, [320] * 90, 1000)]
     want += ["uniform"] * len(t.CASES) + ["whole"] * len(t.WHOLE) + ["uniform"] * 4
-    # many short ones that the persistent kernel has with a loose bound (test_gpu_parity.py), and its batches in test_gpu_full_configs.py, test_zz_no_alloc.py and bench.py
+    # many short ones that the persistent kernel has with a loose bound (test_gpu_parity.py), and the batches of test_gpu_full_configs.py, test_zz_no_alloc.py and bench.py
     calls += [(8, [300] * 800, 300), (8, [300] * 800, 1000), (8, [100] * 800, 1000), (8, [3000] * 96, 3000), (8, [4096] * 128, 4096), (8, [4096] * 256, 4096), (52, [700] * 7, 700),
               (8, [9000] * 200, 9000)]
-    want += ["whole", "persistent", "persistent", "persistent", "persistent", "persistent", "whole", "persistent"]
+    want += ["whole", "persistent", "persistent", "sliced", "sliced", "sliced", "whole", "sliced"]
     # batches with empty sequences, and those without a context
     calls += [(8, [1500] + [0] * 39, 1500), (8, [1500] + [0] * 47, 1500), (8, [34000, 40], 34000), (8, [60000, 40], 60000), (8, [8000, 40], 8000)]
-    want += ["4", "persistent", "8", "persistent", "8"]
+    want += ["4", "sliced", "8", "sliced", "8"]
     text = "\n".join(f"{len(n)} {h} {bound} " + " ".join(map(str, n)) for h, n, bound in calls) + "\n"
     r = subprocess.run([str(exe)], input=text, capture_output=True, text=True)
     got = r.stdout.split("\n")
     assert got[len(want):] == ["covered", ""], r.stdout[-300:]
     assert got[:len(want)] == want, [(c[0], len(c[1]), c[2], g, w) for c, g, w in zip(calls, got, want) if g != w]
+
+
+SLOTS = r"""
+#include <cstdio>
+#include "decode_slices.h"
+using namespace eco;
+// partial states per CU and query head of a group, of a device of `cu`: two for what (bf16, 128) cuts and one for what other layouts do, unless in slices of 1024 tokens; six for
+// what is cut on the device
+int main() {
+  for (int cu : {256, 304, 64, 7})
+    for (int Hkv : {1, 2, 3, 4, 5, 8, 16, 52, 256, 300})
+      for (int B = 1; B <= 600; B += B / 8 + 1)
+        for (int L = 1; L < 2000000; L += L / 12 + 1) {
+          const long long pairs = (long long)B * Hkv;
+          const SmallDecode d = small_decode(B, Hkv, L, cu);
+          if (d.n_split > 1 && (d.split_tokens ? pairs : Hkv) * d.n_split > 2 * cu) return std::printf("%d x %d on %d heads: %d slices of %d\n", B, L, Hkv, d.n_split, d.split_tokens), 1;
+          if (2LL * sliced_most_full(B, Hkv, cu) * Hkv > 6 * cu) return std::printf("%d on %d heads: %d whole slices\n", B, Hkv, sliced_most_full(B, Hkv, cu)), 1;
+          for (int D : {24, 64, 200, 256}) {
+            const SmallDecode a = any_decode(B, Hkv, D, D == 64 ? 4 : 2, L, cu);
+            if (a.n_split > 1 && pairs * a.n_split > cu && a.split_tokens != 1024) return std::printf("head size %d, %d x %d on %d heads: %d slices of %d\n", D, B, L, Hkv, a.n_split, a.split_tokens), 1;
+          }
+        }
+  std::printf("ok\n");
+}
+"""
+
+
+def test_the_states_of_what_is_cut_fit_what_a_context_holds(tmp_path):
+    src, exe = tmp_path / "slots.cpp", tmp_path / "slots"
+    src.write_text(SLOTS)
+    subprocess.run(["g++", "-std=c++17", "-O2", "-Wall", "-Werror", "-I", os.path.join(ROOT, "paper_2504_18154_amd", "csrc"), str(src), "-o", str(exe)], check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0 and r.stdout == "ok\n", r.stdout
 
 
 ANY = r"""

@@ -1,5 +1,5 @@
-"""Decode in slices: the merge of their partial states, which is done by the slice that starts last (short slices) or is done last (long ones), eight
-states at a time, and clears what it has read: every call finds the words as the first one did, whichever slices it has."""
+"""Decode in slices: the merge of their partial states, which is done by the slice that starts last (a few short slices: it waits for the others' states, and clears
+what it has read) or is done last (long slices, or many states), eight at a time: every call finds words and counts as the first one did, whichever slices it has."""
 import os
 import subprocess
 
@@ -109,6 +109,29 @@ def test_states_that_weigh_less_than_the_smallest_normal_number(heads, lens):
     err, bound = float(np.abs(out.double().cpu().numpy() - ref).max()), float((2.0 ** -8 + 2.0 ** -16) * ref.max())
     assert err <= bound
     compare_lse("decode", lse, ref_lse, "bf16")
+    layer.close()
+
+
+@pytest.mark.gpu
+def test_one_context_in_slices_of_several_windows():
+    """52 K/V heads, one context: nine slices of some 4450 tokens in four wavefronts, whose block ids take two registers' worth one after the other."""
+    model = wl.ModelShape("merge", 52, 52, 128, 1, "bf16")
+    lens = np.array([40011], dtype=np.int32)
+    say("decode in slices of more than 4096 tokens")
+    pb = wl.prefill_batch(model, lens, 74)
+    layer = Layer(model, pb.num_blocks, 1, pb.block_table.shape[1])
+    k, v = (wl.randn((pb.T, 52, 128), "bf16", s, device="cuda") for s in (1, 2))
+    layer.append(k, v, pb.cu_q, pb.ctx_before, pb.block_table)
+    q = wl.randn((1, 52, 128), "bf16", 3)
+    ref, ref_lse = layer.decode_oracle(q, pb.block_table, lens)
+    out, lse = layer.decode_gpu(q, pb.block_table, lens)
+    compare("decode", out, ref, "bf16")
+    compare_lse("decode", lse, ref_lse, "bf16")
+    layer.wipe_newest(pb.block_table, lens)
+    fused = torch.full_like(out, float("nan"))
+    layer.ctx.attn_decode_append(q.cuda(), k[-1:].contiguous(), v[-1:].contiguous(), layer.kc, layer.vc, dev_i32(pb.block_table), dev_i32(lens), fused, int(lens[0]))
+    assert torch.equal(fused, out), "the fused append changes the result"
+    layer.assert_cache_bit_exact()
     layer.close()
 
 

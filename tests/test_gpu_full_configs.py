@@ -58,7 +58,8 @@ def _decode_full_layer(db: wl.DecodeBatch, name, seed_offset):
     compare_lse(f"{name} decode", lse, ref_lse, "bf16")
     out2, _ = layer.decode_gpu(q, db.block_table, db.ctx_len)
     assert torch.equal(out.view(torch.int16), out2.view(torch.int16)), "not run-to-run deterministic"
-    # the configuration bench.py times: per-XCD shares that follow the measured speeds.  The cut
+    # the configuration bench.py times: with the option for per-XCD shares that follow the measured speeds, which the
+    # launch of the larger batch has (the other one is cut on the device, without shares).  The cut
     # points move from call to call, so every call is held to the oracle, not to the one before.
     layer.ctx.set_option(binding.OPT_DECODE_ADAPTIVE, 1)
     for call in range(6):

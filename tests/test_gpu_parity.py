@@ -195,8 +195,7 @@ def test_bf16_multi_head_attention_no_kv_sharing():
 
 
 def test_bf16_decode_adaptive_shares_small_and_ragged():
-    """Per-XCD shares on launches that are too small to measure (shares must stay equal and
-    results identical to the equal-share mode) and on ragged contexts over many calls."""
+    """The option for per-XCD shares on a batch whose launch has none (it is cut on the device), over many calls; the launches that have them: below."""
     from paper_2504_18154_amd import binding
     model = M30
     say("bf16 decode with per-XCD shares, ragged contexts")
@@ -214,6 +213,42 @@ def test_bf16_decode_adaptive_shares_small_and_ragged():
     layer.ctx.set_option(binding.OPT_DECODE_ADAPTIVE, 0)
     again, _ = layer.decode_gpu(q, pb.block_table, pb.q_len)
     assert torch.equal(base.view(torch.int16), again.view(torch.int16)), "equal-share mode is not reproducible"
+    layer.close()
+
+
+@pytest.mark.parametrize("heads,lens,bound", [((40, 8), DECODE_LENS + [4000, 3500, 2222, 1234] * 6, 17000), ((40, 8), [4000, 3500, 1, 2222, 1234] * 12 + [37, 300, 5, 90] * 51, 4000),
+                                              ((8, 1), [5, 1, 16] * 87, 700)], ids=["loose-bound", "many-and-ragged", "too-small-to-measure"])
+def test_bf16_decode_adaptive_shares_of_the_persistent_kernel(heads, lens, bound):
+    """Per-XCD shares that follow the measured speeds, where a launch has them: longer than 20000 tokens of a K/V head per CU by the caller's bound, or of more
+    than 256 sequences.  Ragged contexts, the append fused in and not, over many calls; a launch too small to measure, whose shares stay equal."""
+    from paper_2504_18154_amd import binding
+    model = wl.ModelShape("shares", heads[0], heads[1], 128, 1, "bf16")
+    say(f"bf16 decode with per-XCD shares by the persistent kernel, {len(lens)} sequences, bound {bound}")
+    assert len(lens) > 256 or len(lens) * model.Hkv * bound > 20000 * 256
+    pb = wl.prefill_batch(model, lens, 24)
+    table = np.pad(pb.block_table, ((0, 0), (0, max(0, -(-bound // 16) - pb.block_table.shape[1]))))
+    layer = Layer(model, pb.num_blocks, pb.B, table.shape[1])
+    _, k, v = _qkv(model, pb.T, 240)
+    layer.append(k, v, pb.cu_q, pb.ctx_before, table)
+    q = wl.randn((pb.B, model.Hq, model.D), "bf16", 241)
+    ref, ref_lse = layer.decode_oracle(q, table, pb.q_len)
+    layer.ctx.set_option(binding.OPT_DECODE_ADAPTIVE, 1)
+    last = torch.as_tensor(np.asarray(pb.cu_q[1:]) - 1, dtype=torch.long)
+    kn, vn, tot, bt = k[last].cuda(), v[last].cuda(), dev_i32(pb.q_len), dev_i32(table)
+    for call in range(12):
+        if call % 3 == 2:
+            layer.wipe_newest(table, pb.q_len)
+            out, lse = torch.full_like(q, float("nan"), device="cuda"), torch.full((pb.B, model.Hq), float("nan"), device="cuda")
+            layer.ctx.attn_decode_append(q.cuda(), kn, vn, layer.kc, layer.vc, bt, tot, out, bound, lse)
+        else:
+            out, lse = layer.decode_gpu(q, table, pb.q_len, max_ctx_len=bound)
+        compare(f"adaptive call {call}", out, ref, "bf16")
+        compare_lse(f"adaptive call {call}", lse, ref_lse, "bf16")
+        if call == 0:
+            first = out
+        if max(lens) < 100:
+            assert torch.equal(out.view(torch.int16), first.view(torch.int16)), "shares moved without a measurement"
+    layer.assert_cache_bit_exact()
     layer.close()
 
 

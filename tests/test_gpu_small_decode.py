@@ -103,8 +103,8 @@ def test_infinite_values_reach_only_their_own_elements(lens):
 @pytest.mark.parametrize("each", [15, 19], ids=["B40", "B48"])
 def test_sequences_without_tokens_are_passed_over(each):
     """Lengths of zero first, in the middle, several in a row, and last, among up to 1500 tokens; with a context and without.  48 sequences
-    (384 (sequence, K/V head)s for 256 workgroups) go to the persistent kernel, 40 take balanced slices, two workgroups per CU
-    (test_decode_slices.py asserts it)."""
+    (384 (sequence, K/V head)s for 256 workgroups) are cut on the device, 40 take balanced slices, two workgroups per CU
+    (test_decode_slices.py asserts it; the persistent kernel's empty sequences are in test_gpu_decode_sliced.py)."""
     model = wl.ModelShape("30B-heads", 40, 8, 128, 1, "bf16")
     rng = np.random.default_rng(58)
     lens = np.r_[0, 0, 700, 0, rng.integers(1, 600, size=each), 0, 0, 1500, 0, rng.integers(1, 600, size=each), 16, 0].astype(np.int32)

@@ -45,14 +45,13 @@ def _decode_both_ways(model, ctx_len, seed):
 def test_noalloc_decode_matches_the_context_call_twice_in_a_row():
     model = wl.ModelShape("30B-heads", 40, 8, 128, 1, "bf16")
     rng = np.random.default_rng(2024)
-    say("noalloc decode: 96 sequences, contexts 1..3000 (most (sequence, head)s cut between wavefronts)")
+    say("noalloc decode: 96 sequences, contexts 1..3000 (most of them cut, on the device)")
     _decode_both_ways(model, np.r_[1, 15, 16, 17, 2049, rng.integers(1, 3000, size=91)].astype(np.int32), 901)
     say("noalloc decode: 5 sequences right after it (the scratch array still holds the larger call's states)")
     _decode_both_ways(model, np.array([700, 3, 64, 1, 129], dtype=np.int32), 902)
     say("noalloc decode: group size 8, one long sequence in slices, small enough for the single launch")
     _decode_both_ways(wl.ModelShape("70B-heads", 64, 8, 128, 1, "bf16"), np.array([8000, 40], dtype=np.int32), 903)
-    # (34000 tokens: balanced slices; 60000: the persistent kernel, well over a hundred states per
-    # (sequence, head), so the merge of the cut ones goes through its rounds of 64; test_decode_slices.py asserts both)
+    # (34000 tokens: balanced slices; 60000: cut on the device; test_decode_slices.py asserts both)
     for n in (34000, 60000):
         say(f"noalloc decode: group size 8, one long sequence of {n} tokens cut into many pieces")
         _decode_both_ways(wl.ModelShape("70B-heads", 64, 8, 128, 1, "bf16"), np.array([n, 40], dtype=np.int32), 870 + n // 1000)
