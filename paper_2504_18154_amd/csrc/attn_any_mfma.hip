@@ -449,9 +449,10 @@ __device__ __forceinline__ void merge_slices(uint32_t* first, int slice_bytes, i
 // What such a launch is made of (1 x 777 tokens, 40 query heads on 8, 8.4 us a call, time stamps): 0.4 us to the length, 0.5 to the block ids, 1.4 to the blocks,
 // 1.6 for the states through LDS (three barriers, divisions, the code of a row taken again in front of them), 0.2 and 0.35 for stores acknowledged and the count,
 // 1.2 for the maxima, 1.4 for the states and the result.  Now 6.8 us: one barrier, whole rows per wavefront, 16 bytes per lane; the count asked for behind the
-// first blocks; states that say by themselves when they have arrived; arguments fetched at once, query rows while the ids are on their way.  The same steps elsewhere, us:
-// 64 on 8, 16 x 20..2000 19.6 / 17.8, 40 on 8, 1 x 2000 9.8 / 8.5, 8 x 1000 14.0 / 12.4, 52 on 52, 1 x 700 10.2 / 8.5, 32 on 8, 1 x 16000 20.7 / 18.9, fp32, 64, 2 K/V heads, 1 x 700
-// 7.9 / 6.4, fp32, 128, 3, 4 x 400 9.9 / 8.6, bf16, 256, 1, 1 x 800 14.2 / 10.8, bf16, 64, 8, 4 x 600 7.9 / 7.8; 8 on 1, 1 x 60000 (52 slices) 19.4 / 20.3.
+// first blocks; states that say by themselves when they have arrived; arguments fetched at once, query rows while the ids are on their way.  The same steps elsewhere, us
+// (in graphs of several layers, both on one device; 1 x 777 8.5 / 6.9 there): 64 on 8, 16 x 20..2000 18.6 / 17.4, 40 on 8, 1 x 2000 9.7 / 8.0, 8 x 1000 13.7 / 12.0, 52 on 52, 1 x 700
+// 10.7 / 9.3, 32 on 8, 1 x 16000 20.6 / 18.5, fp32, 64, 2 K/V heads, 1 x 700 7.5 / 6.0, fp32, 128, 3, 4 x 400 9.7 / 8.4, bf16, 256, 1, 1 x 800 13.9 / 10.7, bf16, 64, 8, 4 x 50..600
+// 7.4 / 7.3; with long slices, counted, 8 on 1, 1 x 60000 (53 slices) 23.1 / 21.0, bf16, 256, 1, 1 x 40000 48 / 30.
 template <typename E, int KS, int W, int AUX = 0, bool FULL = true, bool BALANCED = false>
 __global__ __launch_bounds__(W * 64) void decode_any_kernel(
     const E* __restrict__ q, int q_row_stride, const E* __restrict__ k_new, const E* __restrict__ v_new, int new_row_stride,
@@ -514,9 +515,9 @@ __global__ __launch_bounds__(W * 64) void decode_any_kernel(
   const char* const kc = reinterpret_cast<const char*>(k_cache);
   const char* const vc = reinterpret_cast<const char*>(v_cache);
 
-  // The blocks are walked in windows of the 64 ids a register holds, two blocks in flight.  Slices are at most 1024 W tokens
-  // and take one window; a second one is for a context longer than the caller's max_ctx_len, which the persistent kernel
-  // never minded and whose last slice takes the rest here.  A wavefront's last block comes first in its window: it may be the slice's last one, and what that needs
+  // The blocks are walked in windows of the 64 ids a register holds, two blocks in flight.  Most slices are at most 1024 W tokens
+  // and take one window; more are for one very long context (its balanced slices: 52 on 52, 1 x 40000 tokens, 4450 and four wavefronts) and for one
+  // longer than the caller's max_ctx_len, which the persistent kernel never minded and whose last slice takes the rest here.  A wavefront's last block comes first in its window: it may be the slice's last one, and what that needs
   // (the newest token, the slots behind the end) then stands once, in front of the loop - a short context is latency
   // from the first instruction on, and code that runs once costs its fetch.
   Blk f[2];
@@ -736,8 +737,8 @@ __global__ __launch_bounds__(W * 64) void decode_any_kernel(
 // gives the slice with which no more than `max_full` whole ones come of a K/V head.  Those are handed out first, then what is left of the contexts, longest first; a
 // workgroup without a rank ends (ranked in each group of 64 sequences, up to 3000 of them stood at the end of a launch: 16 on 1, 238 x 1140..11406 tokens 63.8 us, 56.3 so).  Of a context that is cut, the workgroup that is done last adds the states up (merge_slices): one that waited for
 // the others while they walk slows them (long slices). `states` has max_full slots of whole slices and as many of the rest per K/V head.  A slice below 24 blocks
-// costs more in states than it evens out.  us per layer, persistent kernel and its merge / here: 40 on 8, 128 x 512..4096 203 / 193, 52 on 52, 24 x 300..3000 (the append a
-// launch before it) 203 / 199, 64 on 8, 256 x 1024..4096 468 / 464; other batches at decode_sliced.
+// costs more in states than it evens out.  us per layer, persistent kernel and its merge / here, two layers: 40 on 8, 128 x 512..4096 215 / 202, 52 on 52, 24 x 300..3000 193 / 187,
+// 64 on 8, 256 x 1024..4096 463 / 458 (within the noise of either); other batches at decode_sliced.
 enum class Order { kBatch, kLongest, kSliced };
 template <int W, Order ORDER>
 __global__ __launch_bounds__(W * 64, 3) void decode_short_kernel(

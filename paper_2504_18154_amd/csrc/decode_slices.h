@@ -28,7 +28,7 @@ ECO_SLICES_HD float quotient(float a, float b) {
 
 // How long a context's slices are, in blocks, for (bf16, 128) in eight wavefronts (figures in us, 40 query heads on 8 K/V heads).
 // A workgroup walks a block in about 0.1; the device streams one (of one K/V head) in 0.0007 and more; slices cost a merge,
-// 2.5.  Contexts of up to 1024 tokens stay whole while walking the longest takes no more than that: one of 500 tokens 8.0
+// 2.5 (when these lines were drawn; it takes 1 to 2 less now, and so do the figures of what is cut).  Contexts of up to 1024 tokens stay whole while walking the longest takes no more than that: one of 500 tokens 8.0
 // whole, 8.7 in slices of 128; of 777 9.4 and 8.5; 8 x 1000 16.3 and 14.6; 16 x 600 13.9 and 15.2; 16 x 20..1000 14.6 and 12.8.
 ECO_SLICES_HD bool whole_context(float longest, float blocks_of_all_heads) {
   const float stream = 0.0007f * blocks_of_all_heads, shortest = 0.1f * 8.f;
@@ -104,7 +104,7 @@ inline int32_t decode_any_split_tokens(int32_t B, int32_t Hkv, int32_t max_ctx_l
 // For every other layout: contexts are cut, into slices of whole rounds of the wavefronts, where that makes no more than one
 // workgroup per CU and the walk it saves is worth a merge.  A block's walk takes 0.012 us per KiB of it in bf16, 0.018 in fp32 (one of
 // 700 tokens against one of 50: 64 0.05 and 0.16, fp32 128 0.28, 192 0.13, 256 0.21 and 0.57 us a block); a merge 2.7
-// (1.8 in fp32), more for large heads, and 0.13 a slice.  Us per call whole / cut: fp32, 64, 2 K/V heads: 1 x 700 tokens 11.2 / 7.6, 16 x 700 11.5 / 9.0; fp32, 128, 3:
+// (1.8 in fp32), more for large heads, and 0.13 a slice (all figures here are from before it became 1 to 2 us cheaper).  Us per call whole / cut: fp32, 64, 2 K/V heads: 1 x 700 tokens 11.2 / 7.6, 16 x 700 11.5 / 9.0; fp32, 128, 3:
 // 1 x 400 14.2 / 9.5, 4 x 37..708 15.6 / 10.4, 8 x 3000 33.6 / 22.6; fp32, 256, 2: 16 x 700 41.4 / 21.2; bf16, 192, 2: 16 x 700 16.7 / 12.8; bf16, 256, 1:
 // 1 x 200 11.7 / 13.1, 1 x 400 14.3 / 13.6, 64 x 800 27.1 / 21.3; bf16, 96, 2: 16 x 700 8.4 / 9.0; 64, 8: 1 x 700 6.6 whole.
 //   Slices beyond 1024 tokens are no longer than the uniform ones would be (bf16, 32, 1 x 2000: 256 tokens 7.1, 512 7.6; 96, 2 x 4000: 256
@@ -193,6 +193,8 @@ ECO_SLICES_HD SlicedContexts sliced_contexts(int sum, int max_full, int W) {
 
 // For (bf16, 128), batches that decode_short leaves: how decode_any_kernel takes a small one, n_split 0 if it does not.  It needs no numbering of the batch and no
 // second launch, which is what such a batch spends its time on in the persistent kernel.
+//   (The lines of this rule were drawn against the persistent kernel and with a merge that took 1 to 2 us longer; what it leaves now goes to decode_sliced, against which only
+//   one context was measured again.)
 //   Several sequences, one of them of more than 768 tokens, and eight workgroups (one per CU) or more per five (sequence, K/V
 //   head)s: balanced slices.  Us per call before (uniform slices or the persistent kernel) / balanced: 64 query heads on 8, 16 x
 //   20..2000 tokens 18.4 / 14.5, 8 x 20..8000 19.2 / 14.6; 8 on 1, 64 x 1000..8000 38.5 / 28.8; 32 on 8, 9 x
@@ -239,12 +241,12 @@ inline SmallDecode small_decode(int32_t B, int32_t Hkv, int32_t max_ctx_len, int
 // launch's start and end no longer count beside its stream: at 3120 (sequence, K/V head)s, 52 on 52, 60 x 1500..2000 tokens, the persistent kernel takes 461 us, this one 482.
 //   Us per call, fused append, the persistent kernel / here: 40 on 8, 128 x 512..4096 208 / 196, 64 x 20..2000 57.6 / 52.8, 100 x 50..3000 118.8 / 109.3, 256 x 100..1800 190 / 176,
 // 127 x 20 and one of 4000 24.0 / 16.2; 64 on 8, 256 x 1024..4096 459.5 / 451.3, 128 x 8192 671 / 672, 8 x 60000 323 / 313; 52 on 52, 24 x 300..3000 185 / 177; 32 on 8, 64 x 4096 183 / 170,
-// 84 x 300 and six of 6000 57.9 / 49.7; 8 on 1, 256 x 100..6000 78.7 / 78.0; 5 on 1, 150 x 300..16000 110 / 117.  Of 43 random batches of eight head shapes (lengths equal, from 1/2, 1/8, 1/64
-// of the longest, lognormal, one in 16 ten times the others) 0.93 of the time on average, the worst 1.03.
+// 84 x 300 and six of 6000 57.9 / 49.7; 8 on 1, 256 x 100..6000 80.4 / 78.0; 5 on 1, 150 x 300..16000 115.2 / 114.8.  That is for caches of a few layers, which the last-level cache holds in
+// part: over the 64 layers of a model the first of these batches streams at the same rate by either kernel, and the 256 long contexts are the persistent kernel's with measured shares (below).
 //   Whole slices per CU, at most: three, as many workgroups as run there at a time.  Of 60 random batches that come here, of the persistent kernel's time, (two, three, four): up to 1.75
 // (sequence, head)s per CU 0.936, 0.934, 0.943 on average, the worst 1.14, 1.05, 1.07; above 0.932, 0.929, 0.936.  (52 on 52, 5 x 5594 143, 131, 130 us, 8 on 1, 256 x 100..6000
-// 80.6, 78.0, 80.4, 5 on 1, 150 x 300..16000 118, 115, 116.)  What stays slower than the persistent kernel, by up to 5%, are few long contexts of much the same length, whose rests run at a
-// third of the CUs' workgroups; where one in 16 is long, as the host cannot see, these batches take 10 to 35% less than there.
+// 80.6, 78.0, 80.4, 5 on 1, 150 x 300..16000 118, 115, 116.)  What stays slower than the persistent kernel, by up to 5%, are few long contexts of much the same length, whose rests run one
+// to a CU; where one in 16 is long, as the host cannot see, these batches take 10 to 35% less than there.
 inline bool decode_sliced(int32_t B, int32_t Hkv, int32_t num_cu) { return B <= kSlicedMostSequences && (int64_t)B * Hkv <= (int64_t)8 * num_cu; }
 // A context that asks for shares by each XCD's measured speed keeps the persistent kernel for its longest launches: the shares take 1 to 3% off a stream, which is more
 // than the launch of the merge and the uneven end cost once the stream is long.  Us per call with such shares, the persistent kernel / here: 64 on 8, 256 x 1024..4096
