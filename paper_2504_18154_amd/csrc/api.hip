@@ -74,7 +74,7 @@ int64_t slots_needed(const ecoserve_ctx* c, int32_t* plain_splits) {
 }
 
 // Partial states of the slices of the kernels of attn_any_mfma.hip, as the rules in decode_slices.h cut.  Zeroed ones, of short slices: at most two per CU.  The others: six
-// per CU for (bf16, 128), where the persistent kernel's lie (eight per CU and group head, of 130 words), else one per CU or slices of 1024 tokens.
+// per CU for (bf16, 128), where the persistent kernel's lie (eight per CU and group head, of 130 words), else two per CU or slices of 1024 tokens.
 int64_t group_of(const ecoserve_ctx* c) { return c->lay.num_q_heads / c->lay.num_kv_heads; }
 bool has_mfma(const ecoserve_ctx* c) { return c->lay.dtype == ECOSERVE_BF16 && c->lay.head_dim == 128; }
 size_t state_bytes(const ecoserve_ctx* c) { return (size_t)(c->lay.head_dim + 4) * sizeof(uint32_t); }
@@ -295,7 +295,7 @@ int ecoserve_create(ecoserve_ctx** out, int device, const ecoserve_layout* layou
     const size_t counts = std::max((size_t)c->max_batch * c->lay.num_kv_heads, (size_t)6 * c->num_cu), parts_at = (share_words + counts + 63) / 64 * 64;
     SliceStates& p = c->parts;
     p.part_slots = 2 * (int64_t)c->num_cu * group_of(c);
-    p.state_slots = has_mfma(c) ? 0 : std::max(c->num_cu * group_of(c), slices_at_most(c, 1024));
+    p.state_slots = has_mfma(c) ? 0 : std::max(p.part_slots, slices_at_most(c, 1024));
     const size_t zeroed = parts_at * sizeof(int32_t) + (size_t)p.part_slots * state_bytes(c), share_bytes = zeroed + (size_t)p.state_slots * state_bytes(c);
     const float ones[16] = {1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f};
     if (hipMalloc(&c->ws_share, share_bytes) != hipSuccess || hipMemset(c->ws_share, 0, zeroed) != hipSuccess ||

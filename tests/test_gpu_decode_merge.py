@@ -139,7 +139,7 @@ BOUND = r"""
 #include <cstdio>
 #include "decode_slices.h"
 using namespace eco;
-// what a context holds (part_slots_needed in api.hip), in states per query head of a group: two workgroups per CU, or slices of 1024 tokens
+// what a context holds (slice_states in api.hip), in states per query head of a group: two workgroups per CU, or slices of 1024 tokens
 int main() {
   unsigned seed = 7;
   auto rnd = [&](unsigned n) { return (seed = seed * 1664525u + 1013904223u, (unsigned)((unsigned long long)(seed >> 8) * n >> 24)); };

@@ -225,9 +225,8 @@ def test_bf16_decode_adaptive_shares_of_the_persistent_kernel(heads, lens, bound
     model = wl.ModelShape("shares", heads[0], heads[1], 128, 1, "bf16")
     say(f"bf16 decode with per-XCD shares by the persistent kernel, {len(lens)} sequences, bound {bound}")
     assert len(lens) > 256 or len(lens) * model.Hkv * bound > 20000 * 256
-    pb = wl.prefill_batch(model, lens, 24)
-    table = np.pad(pb.block_table, ((0, 0), (0, max(0, -(-bound // 16) - pb.block_table.shape[1]))))
-    layer = Layer(model, pb.num_blocks, pb.B, table.shape[1])
+    pb, layer = _mk(model, lens, seed=24, blocks=-(-bound // 16))
+    table = pb.block_table
     _, k, v = _qkv(model, pb.T, 240)
     layer.append(k, v, pb.cu_q, pb.ctx_before, table)
     q = wl.randn((pb.B, model.Hq, model.D), "bf16", 241)
@@ -367,8 +366,8 @@ def test_bf16_decode_of_hundreds_of_short_sequences():
 def test_bf16_decode_random_batches():
     """Sixteen seeded random decode batches: group sizes 1..16, 1..8 K/V heads, 1..47 sequences whose lengths
     mix a few tokens, a few hundred, about a thousand and up to five thousand, automatic and forced splits,
-    equal and measured shares, the plain call and the fused append + decode call (the last token of every
-    sequence wiped from the cache and handed in as the new one)."""
+    measured shares (with the split automatic and a caller's bound that makes a launch long enough for them), the plain call and the fused
+    append + decode call (the last token of every sequence wiped from the cache and handed in as the new one)."""
     from paper_2504_18154_amd import binding
     rng = np.random.default_rng(2025)
     for case in range(16):
@@ -385,7 +384,8 @@ def test_bf16_decode_random_batches():
         split, adaptive, fused = int(rng.choice([0, 0, 64, 256, 1024])), int(rng.integers(0, 2)), int(rng.integers(0, 2))
         say(f"random decode batch {case}: Hq {model.Hq} Hkv {Hkv} B {B} tokens {int(lens.sum())} max {int(lens.max())} "
             f"split {split} measured shares {adaptive} fused {fused}")
-        pb, layer = _mk(model, lens, seed=900 + case)
+        bound = max(int(lens.max()), 20000 * 256 // (B * Hkv) + 16 if adaptive and not split else 0)
+        pb, layer = _mk(model, lens, seed=900 + case, blocks=-(-bound // 16))
         _, k, v = _qkv(model, pb.T, 910 + 3 * case)
         layer.append(k, v, pb.cu_q, pb.ctx_before, pb.block_table)
         layer.ctx.set_option(binding.OPT_DECODE_SPLIT_TOKENS, split)
@@ -402,12 +402,11 @@ def test_bf16_decode_random_batches():
                                     dev_i32(lens - 1), table, max_new_len=1)
                 out = torch.full((B, model.Hq, model.D), float("nan"), dtype=torch.bfloat16, device="cuda")
                 lse = torch.full((B, model.Hq), float("nan"), dtype=torch.float32, device="cuda")
-                layer.ctx.attn_decode_append(q.cuda(), kn, vn, layer.kc, layer.vc, table, ctx_dev, out,
-                                             int(lens.max()), lse)
+                layer.ctx.attn_decode_append(q.cuda(), kn, vn, layer.kc, layer.vc, table, ctx_dev, out, bound, lse)
                 torch.cuda.synchronize()
                 layer.assert_cache_bit_exact()
             else:
-                out, lse = layer.decode_gpu(q, pb.block_table, lens)
+                out, lse = layer.decode_gpu(q, pb.block_table, lens, max_ctx_len=bound)
             compare(f"batch {case} call {rep}", out, ref, "bf16")
             compare_lse(f"batch {case} call {rep}", lse, ref_lse, "bf16")
         layer.close()
@@ -618,8 +617,8 @@ def test_bf16_prefill_reuses_the_tile_list_across_layers():
 @pytest.mark.parametrize("seed", [101, 102, 103, 104, 105, 106])
 def test_bf16_seeded_random_batches(seed):
     """Seeded random shapes: head counts, batch size, prefixes, prompt lengths (zeros, one token,
-    around the 16/64/128 boundaries, a few long ones), then two decode steps with per-XCD shares
-    on and off.  Everything against the oracle."""
+    around the 16/64/128 boundaries, a few long ones), then two decode steps, the option for per-XCD shares
+    off and on (batches this small have none of them).  Everything against the oracle."""
     from paper_2504_18154_amd import binding
     rng = np.random.default_rng(seed)
     hkv = int(rng.choice([1, 2, 4, 8]))
