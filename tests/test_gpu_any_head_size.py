@@ -67,6 +67,37 @@ def test_prefill_and_decode_against_the_oracle(dtype, D, Hq, Hkv):
     layer.close()
 
 
+@pytest.mark.parametrize("dtype,D,heads", [("bf16", 24, (9, 1)), ("bf16", 32, (32, 2)), ("bf16", 64, (8, 1)), ("f32", 36, (15, 1)), ("bf16", 88, (32, 2)), ("f32", 128, (16, 1)), ("bf16", 104, (4, 4)),
+                                           ("bf16", 128, (16, 1))], ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
+def test_decode_of_whole_contexts_with_one_row_to_a_wavefront_or_two(dtype, D, heads):
+    """Groups of up to 16 rows over eight wavefronts, contexts that end in the first block, in some of the wavefronts' and in all; then an infinite V element, which takes the rows of its
+    sequence and K/V head to the other way through the kernel's end."""
+    from paper_2504_18154_amd import binding
+    model = wl.ModelShape(f"{dtype}-d{D}", *heads, D, 1, dtype)
+    lens = np.asarray([1, 16, 17, 70, 128, 129, 9, 400, 33], dtype=np.int32)
+    say(f"{dtype}, head size {D}, heads {heads}: decode of whole contexts")
+    pb = wl.prefill_batch(model, lens, 83)
+    layer = Layer(model, pb.num_blocks, pb.B, pb.block_table.shape[1])
+    k, v, q = (wl.randn((n, h, D), dtype, s) for s, n, h in ((1, pb.T, heads[1]), (2, pb.T, heads[1]), (3, pb.B, heads[0])))
+    layer.append(k, v, pb.cu_q, pb.ctx_before, pb.block_table)
+    ref, ref_lse = layer.decode_oracle(q, pb.block_table, lens)
+    out, lse = layer.decode_gpu(q, pb.block_table, lens)
+    compare("decode", out, ref, dtype)
+    compare_lse("decode", lse, ref_lse, dtype)
+    v[int(pb.cu_q[3]) + 40, 0, 5] = float("inf")   # of the fourth sequence
+    layer.append(k, v, pb.cu_q, pb.ctx_before, pb.block_table)
+    got, glse = layer.decode_gpu(q, pb.block_table, lens)
+    layer.ctx.set_option(binding.OPT_FORCE_PLAIN, 1)
+    want, _ = layer.decode_gpu(q, pb.block_table, lens)
+    G, fin = heads[0] // heads[1], torch.isfinite(want)
+    assert torch.isinf(want[3, :G, 5].float()).all() and int((~fin).sum()) == G
+    assert torch.equal(torch.isfinite(got), fin) and torch.equal(torch.isinf(got), torch.isinf(want))
+    compare_lse("decode, an infinite value", glse, ref_lse, dtype)
+    others = [b for b in range(pb.B) if b != 3]
+    assert torch.equal(got[others], out[others]) and torch.equal(glse[others], lse[others])
+    layer.close()
+
+
 @pytest.mark.parametrize("dtype,D", [("f32", 64), ("bf16", 64)])
 def test_decode_over_contexts_of_several_slices(dtype, D):
     """Contexts above 1024 tokens are cut into slices whose states are merged, the newest token in the last one:
