@@ -546,9 +546,9 @@ __global__ __launch_bounds__(W * 64) void decode_any_kernel(
   // Which of the slices starts last merges them all (see the end).  Asked here, behind the first blocks, the answer is there before it is wanted.  Slices of
   // more than four rounds end at so many times that who waits for them is in their way: there it is the one that is done last (1 x 75000 tokens, 62.3 us; waiting 65.2).
   const int n_split = slice.n;
-  // So it is where there are many states: those of the others are cleared by one CU (16 on 1, 17 x 100..6425 tokens 18.2 us, 15.6 so, 1 x 3000 11.8, 11.3; at 96 and 128 states, 8 on 1,
-  // 2 x 3878, 1 x 8000, no difference).
-  const bool early = at.tokens <= kShortRounds * 16 * W && n_split * G <= 128;  // (the same for all slices of a context)
+  // So it is where there are many states: those of the others are cleared by one CU (16 on 1, 17 x 100..6425 tokens 18.2 us, 15.6 so, 1 x 3000 11.8, 11.3; 8 on 1, 1 x 8000, 128 states,
+  // 10.0, 9.9; fewer lose: 5 on 1, 4 x 130..1300, 55 states, 6.9, 7.2).
+  const bool early = at.tokens <= kShortRounds * 16 * W && n_split * G <= 96;  // (the same for all slices of a context)
   auto arrive = [&]() { return (int)atomicInc(counters + (size_t)b * Hkv + g, (unsigned)n_split - 1); };  // (the last one wraps it to zero)
   int order = 0, newest_blk = 0;
   if (n_split > 1 && early && tid == 0) order = arrive();
@@ -710,7 +710,7 @@ __global__ __launch_bounds__(W * 64) void decode_any_kernel(
         o[c][e] = sum_of_groups<NG>(o[c][e]);
         zero = __builtin_fmaf(o[c][e], 0.f, zero);
       }
-    if (__any(zero != zero && total == total)) {  // (see attend_row)
+    if (__builtin_expect(__any(zero != zero && total == total), 0)) {  // (see attend_row)
       float r[4];
       attend_row<E>(scalar_here(q + (size_t)b * q_row_stride) + (size_t)(scalar_here(g) * G + h) * D, scalar_here(k_cache), scalar_here(v_cache), scalar_here(bt_row),
                     scalar_here(g), scalar_here(Hkv), scalar_here(D), scalar_here(t0), scalar_here(t1), scale_log2e, M, total, r);

@@ -18,7 +18,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CASES = [("bf16", 128, (40, 8), [700, 1100, 40], 0), ("bf16", 128, (8, 1), [60000], 0), ("bf16", 128, (16, 1), [9000, 129, 3000], 0), ("bf16", 128, (8, 2), [300100], 0),
          ("f32", 64, (4, 2), [513, 64, 577], 64), ("f32", 32, (4, 2), [1025, 130], 128), ("bf16", 24, (6, 3), [700, 65], 64), ("bf16", 80, (8, 8), [600, 64, 1], 64),
          ("f32", 100, (6, 3), [577, 512], 64), ("bf16", 200, (8, 2), [640, 70], 64), ("f32", 256, (4, 2), [577, 128], 64), ("bf16", 64, (32, 8), [1300] * 40, 64),
-         # counted states (long slices, or more than 128 states of short ones): all at once, and behind calls that clear theirs
+         # counted states (long slices, or more than 96 states of short ones): all at once, and behind calls that clear theirs
          ("bf16", 128, (16, 1), [1500], 0), ("bf16", 64, (16, 1), [900, 130, 520], 64), ("f32", 64, (4, 2), [5000, 1300], 1024), ("f32", 256, (4, 2), [3000, 500], 320),
          ("bf16", 104, (24, 2), [3100, 700, 2000], 0)]
 
